@@ -830,9 +830,12 @@ zgr_status zgr_cloud_basis(const float* const* snapshots, int32_t n_snap, int64_
   float* T = reinterpret_cast<float*>(ws + 2 * yb);      // G_t^T Q of one snapshot
   int* dep = reinterpret_cast<int*>(ws + 2 * yb + align_up((size_t)cols * k * 4));
   float* part = reinterpret_cast<float*>(ws + 2 * yb + align_up((size_t)cols * k * 4) + 256);   // partial sums of the split products
+  // the orthonormalisation's partial sums live there too, between the products: (ceil(rows / 64) + 1) k^2 doubles are at most
+  // 8 rows k + 16 k^2 <= 24 rows k bytes (k <= rows, k <= 64) of the region's 64 rows k
+  double* orth = reinterpret_cast<double*>(part);
   // Q = orth(sum_t G_t Omega)
   for (int t = 0; t < n_snap; ++t) HIP_TRY(nullptr, launch_cloud_g_t(snapshots[t], rows, cols, omega, k, Q, t > 0, s, part));
-  HIP_TRY(nullptr, launch_cloud_orth(Q, rows, k, dep, s));
+  HIP_TRY(nullptr, launch_cloud_orth(Q, rows, k, dep, orth, s));
   // sweeps Q <- orth(sum_t G_t (G_t^T Q))
   for (int it = 0; it < n_iter; ++it) {
     for (int t = 0; t < n_snap; ++t) {
@@ -840,7 +843,7 @@ zgr_status zgr_cloud_basis(const float* const* snapshots, int32_t n_snap, int64_
       HIP_TRY(nullptr, launch_cloud_g_t(snapshots[t], rows, cols, T, k, Y, t > 0, s, part));
     }
     float* tmp = Q; Q = Y; Y = tmp;
-    HIP_TRY(nullptr, launch_cloud_orth(Q, rows, k, dep, s));
+    HIP_TRY(nullptr, launch_cloud_orth(Q, rows, k, dep, orth, s));
   }
   HIP_TRY(nullptr, launch_cloud_copy_basis(Q, rows, k, U, ldu, s));
   if (dependent_out) {

@@ -9,12 +9,10 @@
 //     Q = orth(Y)
 //     n_iter times:  T_t = G_t^T Q,  Y = sum_t G_t T_t,  Q = orth(Y)
 // Each sweep reads every snapshot twice and is a pair of tall-skinny products (HBM-bound: 2 rows cols 4 bytes per
-// snapshot and sweep); orth is classical Gram-Schmidt with one re-orthogonalisation per column, in one workgroup
-// (rows x k with k <= 64 is at most a few MB: it lives in L2).  The subspace converges like (sigma_{k+1} / sigma_k)^(2 n):
+// snapshot and sweep); orth is Gram-Schmidt in matrix form (Cholesky-QR) in fp64, taken twice.  The subspace converges like (sigma_{k+1} / sigma_k)^(2 n):
 // the caller picks n_iter for the gap it expects.  This runs every gamma rounds on the cloud, not on the client's
 // step: it is written to be correct and bandwidth-shaped, not tuned.
 #include "internal.h"
-#include <atomic>
 
 namespace zgr {
 
@@ -99,89 +97,125 @@ __global__ void __launch_bounds__(256) g_t_kernel(const float* __restrict__ G, i
     }
 }
 
-// In-place orthonormalisation of the k columns of Y [rows, k] (row stride k), one workgroup of 1024 threads.
-// Column j: r = Q_{<j}^T y_j, y_j -= Q_{<j} r, once more (which makes classical Gram-Schmidt as orthogonal as
-// Householder for any column that is not dependent to working precision), then y_j /= ||y_j||.  Dot products are
-// accumulated in fp64.  A column that the earlier ones already span (norm below 1e-6 of what it started with)
-// is stored as zeros and counted in *dependent.
-// IN_LDS: the block is copied into LDS first (row stride k + 1, so that threads on consecutive rows hit different banks) and
-// written back at the end: the 3 k sweeps over the rows then cost LDS latency instead of L2 latency.  Same arithmetic, same order.
-template <bool IN_LDS>
-__global__ void __launch_bounds__(1024) orth_kernel(float* __restrict__ Yg, int64_t rows, int k, int* __restrict__ dependent) {
-  __shared__ double red[16][kMaxK];
-  __shared__ double coef[kMaxK];
-  __shared__ int n_dep;
-  extern __shared__ float orth_lds[];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int ld = IN_LDS ? k + 1 : k;
-  float* Y = IN_LDS ? orth_lds : Yg;
-  if (IN_LDS) {
-    for (int64_t i = tid; i < rows * k; i += 1024) Y[(i / k) * ld + (i % k)] = Yg[i];
+// In-place orthonormalisation of the k columns of Y [rows, k] (row stride k), in the order of the columns: Gram-Schmidt in its
+// matrix form, Cholesky-QR, taken twice.  One round is
+//     W = Y^T Y        (fp64 sums, one partial W per block of rows: gram_kernel)
+//     W = L L^T        (fp64, one workgroup, which first adds the partial W in their order: cholesky_kernel)
+//     Y <- Y L^-T      (fp64 forward substitution, one row per thread: substitute_kernel)
+// Column j becomes y_j minus its projection on the earlier columns, divided by the norm that is left.  The second round takes
+// out what the first left of the earlier columns (at most cond(Y)^2 2^-53, 1e-4 at the dependence threshold), so the result is
+// orthonormal to the rounding of its fp32 entries.  A column that the earlier ones already span (norm below 1e-6 of what it
+// started with) is stored as zeros and counted in *dependent.
+// The column-by-column form needs 3 k dependent sweeps over the rows, which one workgroup has to make: 33 ms for
+// 8192 x 64, waiting for the L2 in every sweep.  This form reads the block three times per round, spread over all the rows'
+// blocks, and what is serial (k pivots) stays inside one workgroup's LDS.
+constexpr int kGramRows = 64;        // rows staged at a time
+constexpr int kGramMaxParts = 64;    // partial W at most: the workgroup that factorises adds them all
+constexpr int kGramLd = kMaxK + 1;
+
+// part[p][i k + j] = sum over the rows of part p of Y[r][i] Y[r][j], for every i >= j (16 x 16 tiles on and below the diagonal).
+// Thread (tx, ty) holds element (16 a + ty, 16 b + tx) of each tile (a, b).  NT = ceil(k / 16) tiles.
+template <int NT>
+__global__ void __launch_bounds__(256) gram_kernel(const float* __restrict__ Y, int64_t rows, int k, int64_t rows_per_part, double* __restrict__ part) {
+  __shared__ float Ys[kGramRows][NT * 16 + 1];
+  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
+  const int64_t r_begin = (int64_t)blockIdx.x * rows_per_part;
+  const int64_t r_end = rows < r_begin + rows_per_part ? rows : r_begin + rows_per_part;
+  double acc[NT][NT];
+#pragma unroll
+  for (int a = 0; a < NT; ++a)
+#pragma unroll
+    for (int b = 0; b <= a; ++b) acc[a][b] = 0.0;
+  for (int64_t r0 = r_begin; r0 < r_end; r0 += kGramRows) {
     __syncthreads();
-  }
-  if (tid == 0) n_dep = 0;
-  for (int j = 0; j < k; ++j) {
-    double norm0 = 0.0;
-    for (int pass = 0; pass < 3; ++pass) {
-      // pass 0, 1: coefficients against the earlier columns; pass 2: the norm of what is left (slot j)
-      const int n_dot = pass < 2 ? j : 1;
-      for (int i0 = 0; i0 < n_dot; i0 += 8) {                      // eight dot products per sweep over the rows
-        double part[8];
+    for (int i = tid; i < kGramRows * NT * 16; i += 256) {
+      const int rr = i / (NT * 16), c = i % (NT * 16);
+      Ys[rr][c] = (r0 + rr < r_end && c < k) ? Y[(r0 + rr) * k + c] : 0.f;
+    }
+    __syncthreads();
+#pragma unroll 2
+    for (int rr = 0; rr < kGramRows; ++rr) {
+      double yi[NT], yj[NT];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) part[i] = 0.0;
-        for (int64_t r = tid; r < rows; r += 1024) {
-          const float* row = Y + r * ld;
-          const double yj = (double)row[j];
+      for (int a = 0; a < NT; ++a) { yi[a] = (double)Ys[rr][16 * a + ty]; yj[a] = (double)Ys[rr][16 * a + tx]; }
 #pragma unroll
-          for (int i = 0; i < 8; ++i)
-            if (i0 + i < n_dot) part[i] += yj * (pass < 2 ? (double)row[i0 + i] : yj);
-        }
+      for (int a = 0; a < NT; ++a)
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          double v = part[i];
-          for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-          if (lane == 0 && i0 + i < n_dot) red[wave][i0 + i] = v;
-        }
-      }
-      __syncthreads();
-      if (tid < n_dot) {
-        double v = 0.0;
-        for (int w = 0; w < 16; ++w) v += red[w][tid];
-        coef[tid] = v;
-      }
-      __syncthreads();
-      if (pass < 2) {
-        if (pass == 0) {                                           // remember the column's size before anything is taken out
-          double n0 = 0.0;
-          for (int64_t r = tid; r < rows; r += 1024) { const double y = (double)Y[r * ld + j]; n0 += y * y; }
-          for (int o = 32; o > 0; o >>= 1) n0 += __shfl_xor(n0, o, 64);
-          __syncthreads();
-          if (lane == 0) red[wave][kMaxK - 1] = n0;
-          __syncthreads();
-          for (int w = 0; w < 16; ++w) norm0 += red[w][kMaxK - 1];
-        }
-        for (int64_t r = tid; r < rows; r += 1024) {
-          float* row = Y + r * ld;
-          double y = (double)row[j];
-          for (int i = 0; i < j; ++i) y -= coef[i] * (double)row[i];
-          row[j] = (float)y;
-        }
-        __syncthreads();
-      } else {
-        const double nrm2 = coef[0];
-        const bool dep = !(nrm2 > 1e-12 * norm0) || !(nrm2 > 0.0);
-        const double inv = dep ? 0.0 : 1.0 / sqrt(nrm2);
-        for (int64_t r = tid; r < rows; r += 1024) Y[r * ld + j] = (float)((double)Y[r * ld + j] * inv);
-        if (tid == 0 && dep) n_dep += 1;
-        __syncthreads();
-      }
+        for (int b = 0; b <= a; ++b) acc[a][b] = __builtin_fma(yi[a], yj[b], acc[a][b]);
     }
   }
-  if (IN_LDS) {
-    __syncthreads();
-    for (int64_t i = tid; i < rows * k; i += 1024) Yg[i] = Y[(i / k) * ld + (i % k)];
+  double* out = part + (int64_t)blockIdx.x * k * k;
+#pragma unroll
+  for (int a = 0; a < NT; ++a)
+#pragma unroll
+    for (int b = 0; b <= a; ++b) {
+      const int i = 16 * a + ty, j = 16 * b + tx;
+      if (i < k && j <= i) out[i * k + j] = acc[a][b];
+    }
+}
+
+// Adds the partial W and factorises it in LDS, one pivot per barrier.  fac [k][k]: below the diagonal L, on it 1 / L_jj
+// (0 for a dependent column, whose row and column of L are zero as well).
+__global__ void __launch_bounds__(256) cholesky_kernel(const double* __restrict__ part, int n_parts, int k, double* __restrict__ fac, int* __restrict__ dependent) {
+  __shared__ double W[kMaxK][kGramLd];
+  __shared__ double inv[kMaxK], norm0[kMaxK];
+  const int tid = threadIdx.x;
+  const int n = k * k;
+  for (int e = tid; e < n; e += 256) {
+    const int i = e / k, j = e % k;
+    if (j > i) continue;
+    double v = 0.0;
+#pragma unroll 8
+    for (int p = 0; p < n_parts; ++p) v += part[(int64_t)p * n + e];
+    W[i][j] = v;
+    if (i == j) norm0[j] = v;                      // the column's size before anything is taken out
+  }
+  int n_dep = 0;
+  const int tx = tid & 15, ty = tid >> 4;
+  for (int j = 0; j < k; ++j) {
+    __syncthreads();                               // W is final up to column j
+    const double pivot = W[j][j];
+    const bool dep = !(pivot > 1e-12 * norm0[j]) || !(pivot > 0.0);
+    n_dep += dep;
+    const double ip = dep ? 0.0 : 1.0 / pivot;
+    if (tid == 0) inv[j] = dep ? 0.0 : 1.0 / sqrt(pivot);
+    for (int i = j + 1 + ty; i < k; i += 16) {
+      const double f = W[i][j] * ip;
+      for (int c = j + 1 + tx; c <= i; c += 16) W[i][c] -= f * W[c][j];
+    }
+  }
+  __syncthreads();
+  for (int e = tid; e < n; e += 256) {
+    const int i = e / k, j = e % k;
+    fac[e] = j < i ? W[i][j] * inv[j] : (j == i ? inv[i] : 0.0);
   }
   if (tid == 0) *dependent = n_dep;
+}
+
+// Row y of Y becomes q with q_j = (y_j - sum_{i<j} L_ji q_i) / L_jj.  One wave per block, 64 rows, one row per lane in registers;
+// rows come and go through LDS so that global accesses are contiguous.
+template <int NT>
+__global__ void __launch_bounds__(64) substitute_kernel(float* __restrict__ Y, int64_t rows, int k, const double* __restrict__ fac) {
+  constexpr int KP = NT * 16;
+  __shared__ double F[KP][KP];
+  __shared__ float Ys[64][KP + 1];
+  const int lane = threadIdx.x;
+  const int64_t r0 = (int64_t)blockIdx.x * 64;
+  const int n_rows = (int)(rows - r0 < 64 ? rows - r0 : 64);
+  for (int i = lane; i < KP * KP; i += 64) { const int a = i / KP, b = i % KP; F[a][b] = (a < k && b < k) ? fac[a * k + b] : 0.0; }
+  for (int i = lane; i < n_rows * k; i += 64) Ys[i / k][i % k] = Y[r0 * k + i];
+  __syncthreads();
+  double q[KP];
+#pragma unroll
+  for (int j = 0; j < KP; ++j) {
+    double v = j < k ? (double)Ys[lane][j] : 0.0;
+#pragma unroll
+    for (int i = 0; i < j; ++i) v = __builtin_fma(-F[j][i], q[i], v);
+    q[j] = v * F[j][j];
+    if (j < k) Ys[lane][j] = (float)q[j];
+  }
+  __syncthreads();
+  for (int i = lane; i < n_rows * k; i += 64) Y[r0 * k + i] = Ys[i / k][i % k];
 }
 
 // out[i] = (accumulate ? out[i] : 0) + scale (part[0][i] + part[1][i] + ...): the parts of a split sum, added in their order
@@ -251,21 +285,34 @@ hipError_t launch_cloud_g_t(const float* G, int64_t rows, int64_t cols, const fl
   return launch_sum_parts(part, z, stride, stride, Y, 1.0f, accumulate, s);
 }
 
-hipError_t launch_cloud_orth(float* Y, int64_t rows, int k, int* dependent, hipStream_t s) {
-  // the block in LDS when it fits beside the kernel's own 9 KB (rows (k + 1) floats: 2048 x 16 does, 8192 x 16 does not)
-  const size_t lds = (size_t)rows * (size_t)(k + 1) * sizeof(float);
-  if (lds <= 144 * 1024) {
-    static std::atomic<bool> attr_set{false};              // set twice by racing threads at worst: the call is idempotent
-    if (!attr_set) {
-      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(orth_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize, 144 * 1024);
-      if (e != hipSuccess) return e;
-      attr_set = true;
-    }
-    hipLaunchKernelGGL(orth_kernel<true>, dim3(1), dim3(1024), lds, s, Y, rows, k, dependent);
-  } else {
-    hipLaunchKernelGGL(orth_kernel<false>, dim3(1), dim3(1024), 0, s, Y, rows, k, dependent);
-  }
+size_t cloud_orth_scratch_doubles(int64_t rows, int k) {
+  const int64_t parts = (rows + kGramRows - 1) / kGramRows;
+  return (size_t)((parts < kGramMaxParts ? parts : kGramMaxParts) + 1) * (size_t)k * (size_t)k;
+}
+
+template <int NT>
+static hipError_t orth_round(float* Y, int64_t rows, int k, int* dependent, double* scratch, hipStream_t s) {
+  const int64_t chunks = (rows + kGramRows - 1) / kGramRows;
+  const int64_t per = (chunks + kGramMaxParts - 1) / kGramMaxParts, parts = (chunks + per - 1) / per;
+  double* fac = scratch + parts * k * k;
+  hipLaunchKernelGGL(gram_kernel<NT>, dim3((unsigned)parts), dim3(256), 0, s, Y, rows, k, per * kGramRows, scratch);
+  hipLaunchKernelGGL(cholesky_kernel, dim3(1), dim3(256), 0, s, scratch, (int)parts, k, fac, dependent);
+  hipLaunchKernelGGL(substitute_kernel<NT>, dim3((unsigned)((rows + 63) / 64)), dim3(64), 0, s, Y, rows, k, fac);
   return hipGetLastError();
+}
+
+hipError_t launch_cloud_orth(float* Y, int64_t rows, int k, int* dependent, double* scratch, hipStream_t s) {
+  for (int round = 0; round < 2; ++round) {                 // the count of the second round includes the first one's zero columns
+    hipError_t e;
+    switch ((k + 15) / 16) {
+      case 1:  e = orth_round<1>(Y, rows, k, dependent, scratch, s); break;
+      case 2:  e = orth_round<2>(Y, rows, k, dependent, scratch, s); break;
+      case 3:  e = orth_round<3>(Y, rows, k, dependent, scratch, s); break;
+      default: e = orth_round<4>(Y, rows, k, dependent, scratch, s); break;
+    }
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_cloud_copy_basis(const float* Q, int64_t rows, int k, float* U, int ldu, hipStream_t s) {

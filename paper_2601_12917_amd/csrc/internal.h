@@ -101,7 +101,9 @@ constexpr int kCloudMaxParts = 16;
 hipError_t launch_cloud_gt_q(const float* G, int64_t rows, int64_t cols, int64_t ldg, const float* Q, int n, int64_t ldq, float* T, int64_t ldt, float scale,
                              int accumulate, hipStream_t s, float* part = nullptr);
 hipError_t launch_cloud_g_t(const float* G, int64_t rows, int64_t cols, const float* T, int k, float* Y, int accumulate, hipStream_t s, float* part = nullptr);
-hipError_t launch_cloud_orth(float* Y, int64_t rows, int k, int* dependent, hipStream_t s);
+// scratch: cloud_orth_scratch_doubles(rows, k) doubles
+size_t     cloud_orth_scratch_doubles(int64_t rows, int k);
+hipError_t launch_cloud_orth(float* Y, int64_t rows, int k, int* dependent, double* scratch, hipStream_t s);
 hipError_t launch_cloud_copy_basis(const float* Q, int64_t rows, int k, float* U, int ldu, hipStream_t s);
 hipError_t launch_cloud_residual(float* R, const float* Y, int64_t n, hipStream_t s);
 
