@@ -32,6 +32,7 @@ std::string g_init_error;   // message of the last failed zgr_init / context-fre
 size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 
 constexpr size_t kMinStageTiles = 8192;   // tiles that make a tile launch long enough to amortise its start-up and tail
+constexpr int kCloudUnits = 16;           // scratch of zgr_cloud_basis, in blocks of max(rows, cols) x k floats
 constexpr int kSpcSlots = 2;   // layers' worth of streamed bases resident at once: the one in use and the one arriving
 
 struct Layer {
@@ -813,7 +814,7 @@ zgr_status zgr_quantize_basis(const float* U, int64_t rows, int32_t k, int32_t l
 size_t zgr_cloud_basis_workspace(int64_t rows, int64_t cols, int32_t k) {
   if (rows < 1 || cols < 1 || k < 1 || k > kMaxK) return 0;
   const size_t longer = (size_t)(rows > cols ? rows : cols);
-  return 2 * align_up((size_t)rows * k * 4) + align_up((size_t)cols * k * 4) + 256 + align_up((size_t)kCloudMaxParts * longer * k * 4);
+  return 2 * align_up((size_t)rows * k * 4) + align_up((size_t)cols * k * 4) + 256 + align_up((size_t)kCloudUnits * longer * k * 4);
 }
 
 zgr_status zgr_cloud_basis(const float* const* snapshots, int32_t n_snap, int64_t rows, int64_t cols, int32_t k, const float* omega, int32_t n_iter,
@@ -827,20 +828,30 @@ zgr_status zgr_cloud_basis(const float* const* snapshots, int32_t n_snap, int64_
   const size_t yb = align_up((size_t)rows * k * 4);
   float* Q = reinterpret_cast<float*>(ws);               // the current orthonormal block
   float* Y = reinterpret_cast<float*>(ws + yb);          // the block being built by a sweep
-  float* T = reinterpret_cast<float*>(ws + 2 * yb);      // G_t^T Q of one snapshot
+  const size_t longer = (size_t)(rows > cols ? rows : cols) * (size_t)k;
   int* dep = reinterpret_cast<int*>(ws + 2 * yb + align_up((size_t)cols * k * 4));
-  float* part = reinterpret_cast<float*>(ws + 2 * yb + align_up((size_t)cols * k * 4) + 256);   // partial sums of the split products
-  // the orthonormalisation's partial sums live there too, between the products: (ceil(rows / 64) + 1) k^2 doubles are at most
-  // 8 rows k + 16 k^2 <= 24 rows k bytes (k <= rows, k <= 64) of the region's 64 rows k
-  double* orth = reinterpret_cast<double*>(part);
+  // kCloudUnits times `longer` floats: the products G_t^T Q of up to kCloudSnaps snapshots, then the parts of split sums
+  float* T = reinterpret_cast<float*>(ws + 2 * yb + align_up((size_t)cols * k * 4) + 256);
+  float* part = T + kCloudSnaps * longer;
+  const int64_t part_floats = (int64_t)((kCloudUnits - kCloudSnaps) * longer);
+  // the orthonormalisation's partial sums live there too, between the products: (ceil(rows / 64) + 2) k^2 doubles are at most
+  // 8 rows k + 24 k^2 <= 32 rows k bytes (k <= rows, k <= 64) of the region's 64 rows k
+  double* orth = reinterpret_cast<double*>(T);
+  auto batch_of = [&](int t0) {
+    CloudSnaps g{};
+    for (int i = 0; i < kCloudSnaps && t0 + i < n_snap; ++i) g.G[i] = snapshots[t0 + i];
+    return g;
+  };
+  auto in_batch = [&](int t0) { return n_snap - t0 < kCloudSnaps ? n_snap - t0 : kCloudSnaps; };
   // Q = orth(sum_t G_t Omega)
-  for (int t = 0; t < n_snap; ++t) HIP_TRY(nullptr, launch_cloud_g_t(snapshots[t], rows, cols, omega, k, Q, t > 0, s, part));
+  for (int t = 0; t < n_snap; t += kCloudSnaps)
+    HIP_TRY(nullptr, launch_cloud_g_t_all(batch_of(t), in_batch(t), rows, cols, omega, 0, k, Q, t > 0, part, part_floats, s));
   HIP_TRY(nullptr, launch_cloud_orth(Q, rows, k, dep, orth, s));
   // sweeps Q <- orth(sum_t G_t (G_t^T Q))
   for (int it = 0; it < n_iter; ++it) {
-    for (int t = 0; t < n_snap; ++t) {
-      HIP_TRY(nullptr, launch_cloud_gt_q(snapshots[t], rows, cols, cols, Q, k, k, T, k, 1.0f, 0, s, part));
-      HIP_TRY(nullptr, launch_cloud_g_t(snapshots[t], rows, cols, T, k, Y, t > 0, s, part));
+    for (int t = 0; t < n_snap; t += kCloudSnaps) {
+      HIP_TRY(nullptr, launch_cloud_gt_q_all(batch_of(t), in_batch(t), rows, cols, Q, k, T, part, part_floats, s));
+      HIP_TRY(nullptr, launch_cloud_g_t_all(batch_of(t), in_batch(t), rows, cols, T, cols * k, k, Y, t > 0, part, part_floats, s));
     }
     float* tmp = Q; Q = Y; Y = tmp;
     HIP_TRY(nullptr, launch_cloud_orth(Q, rows, k, dep, orth, s));

@@ -8,110 +8,310 @@
 //     Y = sum_t G_t Omega              (Omega [cols, k]: the caller's seeded Gaussian start)
 //     Q = orth(Y)
 //     n_iter times:  T_t = G_t^T Q,  Y = sum_t G_t T_t,  Q = orth(Y)
-// Each sweep reads every snapshot twice and is a pair of tall-skinny products (HBM-bound: 2 rows cols 4 bytes per
-// snapshot and sweep); orth is Gram-Schmidt in matrix form (Cholesky-QR) in fp64, taken twice.  The subspace converges like (sigma_{k+1} / sigma_k)^(2 n):
-// the caller picks n_iter for the gap it expects.  This runs every gamma rounds on the cloud, not on the client's
-// step: it is written to be correct and bandwidth-shaped, not tuned.
+// Each sweep reads every snapshot twice and is a pair of tall-skinny products (2 rows cols 4 bytes per
+// snapshot and sweep); orth is Gram-Schmidt in matrix form (Cholesky-QR) in fp64, taken twice.  The subspace converges like
+// (sigma_{k+1} / sigma_k)^(2 n): the caller picks n_iter for the gap it expects.
 #include "internal.h"
 
 namespace zgr {
 
 namespace {
 
-constexpr int kTile = 64;      // columns (or rows) of G a block owns
-constexpr int kChunk = 32;     // the other dimension, staged per step
+// Both products run on the fp32 matrix instruction (16x16x4), a wave owning a 64 x 64 piece of the result and a share of the
+// sum, with the operands loaded from global memory straight into the layout the instruction takes: lane (i = lane % 16,
+// kg = lane / 16) supplies element i of the free index and element kg of the summed one.  Nothing passes through LDS but the
+// waves' partial results at the end.  At 8192 x 2048 and rank 64 a product reads 64 MB (13 us at the rate of a large copy) and
+// multiplies 2.1 GFLOP (14 us on these matrix cores); on the vector unit, with both operands
+// staged in LDS, it took 180 us; three snapshots together now take 63-66 us, 0.65 of the matrix cores' rate.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+constexpr int kTile = 64;      // rows (or columns) of G and columns of the block a wave's result covers
+constexpr int kStep = 16;      // terms of the sum a wave takes per step
+constexpr int kWaves = 4;      // waves of a block: they take turns over the steps of the block's part of the sum
 
-// T[c][j] (+)= sum_r G[r][c] Q[r][j],  c < cols, j < n: G [rows, cols] (row stride ldg), Q [rows, n] (row stride ldq).
-// Block = 64 columns c x 64 columns j (blockIdx.y tiles j); thread (c = tid % 64, jg = tid / 64) holds 16 values of j.
-// blockIdx.z = part of the sum: rows [z row_part, (z + 1) row_part) go to T + z t_part (partial sums that sum_parts_kernel adds in order).
-__global__ void __launch_bounds__(256) gt_q_kernel(const float* __restrict__ G, int64_t rows, int64_t cols, int64_t ldg, const float* __restrict__ Q, int n, int64_t ldq,
-                                                   float* __restrict__ T, int64_t ldt, float scale, int accumulate, int64_t row_part, int64_t t_part) {
-  __shared__ float Gs[kChunk][kTile + 1], Qs[kChunk][kTile + 1];
-  const int tid = threadIdx.x, cl = tid & 63, jg = tid >> 6;
-  const int64_t c0 = (int64_t)blockIdx.x * kTile;
-  const int j0 = blockIdx.y * kTile;
-  const int64_t r_begin = (int64_t)blockIdx.z * row_part;
-  rows = rows < r_begin + row_part ? rows : r_begin + row_part;
-  T += (int64_t)blockIdx.z * t_part;
-  float acc[16];
-#pragma unroll
-  for (int i = 0; i < 16; ++i) acc[i] = 0.f;
-  for (int64_t r0 = r_begin; r0 < rows; r0 += kChunk) {
-    __syncthreads();
-    for (int i = tid; i < kChunk * kTile; i += 256) {
-      const int rr = i >> 6, cc = i & 63;
-      const int64_t r = r0 + rr;
-      Gs[rr][cc] = (r < rows && c0 + cc < cols) ? G[r * ldg + c0 + cc] : 0.f;
-      Qs[rr][cc] = (r < rows && j0 + cc < n) ? Q[r * ldq + j0 + cc] : 0.f;
-    }
-    __syncthreads();
-#pragma unroll 4
-    for (int rr = 0; rr < kChunk; ++rr) {
-      const float g = Gs[rr][cl];
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[i] = __builtin_fmaf(g, Qs[rr][jg * 16 + i], acc[i]);
-    }
-  }
-  if (c0 + cl < cols)
-    for (int i = 0; i < 16; ++i) {
-      const int j = j0 + jg * 16 + i;
-      if (j < n) { float* t = T + (c0 + cl) * ldt + j; *t = (accumulate ? *t : 0.f) + scale * acc[i]; }
-    }
+// Nothing is scheduled across this point: left to itself the compiler moves a step's loads down to where they are used.
+__device__ __forceinline__ void in_this_order() {
+#if defined(__HIP_DEVICE_COMPILE__)
+  __builtin_amdgcn_sched_barrier(0);
+#endif
 }
 
-// Y[r][j] (+)= sum_c G[r][c] T[c][j],  r < rows, j < k <= 64.  Block = 64 rows; thread (r = tid % 64, jg = tid / 64).
-// blockIdx.y = part of the sum: columns [y col_part, (y + 1) col_part) go to Y + y y_part.
-__global__ void __launch_bounds__(256) g_t_kernel(const float* __restrict__ G, int64_t rows, int64_t cols, const float* __restrict__ T, int k,
-                                                  float* __restrict__ Y, int accumulate, int64_t col_part, int64_t y_part) {
-  __shared__ float Gs[kTile][kChunk + 1], Ts[kChunk][kTile + 1];
-  const int tid = threadIdx.x, rl = tid & 63, jg = tid >> 6;
-  const int64_t r0 = (int64_t)blockIdx.x * kTile;
+// A value all lanes agree on as a scalar (a wave's index, its number of steps): every address of its main loop is then a scalar base
+// and a lane offset that stays the same (buffer addressing), and the loop holds loads, matrix instructions and scalar arithmetic
+// only.  With vector instructions for the addresses each of them queued behind the matrix instructions of the SIMD's other waves:
+// 111 us for 48 us of matrix instructions and 23 us of loads.
+__device__ __forceinline__ int uniform(int v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_readfirstlane(v);
+#else
+  return v;
+#endif
+}
+// The float(s) `byte` bytes (< 2^32, a multiple of 4) past a scalar base.
+__device__ __forceinline__ float load1_at(const float* base, uint32_t byte) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, 0xFFFFFFFFu, 0x00020000);
+  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, byte, 0, 0));
+#else
+  return base[byte / 4];
+#endif
+}
+__device__ __forceinline__ f32x4 load4_at(const float* base, uint32_t byte) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, 0xFFFFFFFFu, 0x00020000);
+  return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, byte, 0, 0));
+#else
+  return f32x4{base[byte / 4], base[byte / 4 + 1], base[byte / 4 + 2], base[byte / 4 + 3]};
+#endif
+}
+
+// Adds the four waves' accumulators in a fixed order: ((0 + 2) + (1 + 3)), left in wave 0.
+template <int NT> __device__ __forceinline__ void add_waves(f32x4 (&acc)[4][NT], float* lds, int wave, int lane) {
+#pragma unroll
+  for (int half = 2; half >= 1; half >>= 1) {
+    __syncthreads();
+    if (wave >= half && wave < 2 * half)
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int n = 0; n < NT; ++n) *reinterpret_cast<f32x4*>(lds + (((wave - half) * 4 * NT + t * NT + n) * 64 + lane) * 4) = acc[t][n];
+    __syncthreads();
+    if (wave < half)
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int n = 0; n < NT; ++n) acc[t][n] += *reinterpret_cast<const f32x4*>(lds + ((wave * 4 * NT + t * NT + n) * 64 + lane) * 4);
+  }
+}
+
+// T[c][j] (+)= scale sum_r G[r][c] Q[r][j]: G [rows, cols] (row stride ldg), Q [rows, n] (row stride ldq), T row stride ldt.
+// blockIdx.x: 64 columns c; blockIdx.y: NT 16 columns j, or, where one such tile is all (one_tile), the snapshot; blockIdx.z = part of the sum:
+// rows [part row_part, (part + 1) row_part), result at T + (snapshot gridDim.z + part) t_part.  A lane's four consecutive columns of G feed four tiles: tile m holds the
+// columns c0 + 4 i + m (a lane that would reach past the last column takes the last four instead).  NEAR: the lane offsets of a step fit
+// 32 bits and there are four columns; the general form is for what is left.
+template <int NT, bool NEAR>
+__global__ void __launch_bounds__(64 * kWaves, 2) gt_q_kernel(CloudSnaps g, int one_tile, int64_t rows, int64_t cols, int64_t ldg, const float* __restrict__ Q, int n, int64_t ldq,
+                                                           float* __restrict__ T, int64_t ldt, float scale, int accumulate, int64_t row_part, int64_t t_part) {
+  __shared__ __attribute__((aligned(16))) float lds[2 * 4 * NT * 256];
+  const int lane = threadIdx.x & 63, wave = uniform((int)threadIdx.x >> 6), i16 = lane & 15, kg = lane >> 4;
+  const int snap = one_tile ? blockIdx.y : 0;
+  const float* G = g.G[snap];
+  const int64_t r_begin = (int64_t)blockIdx.z * row_part;
+  const int64_t r_end = rows < r_begin + row_part ? rows : r_begin + row_part;
+  const int64_t c0 = (int64_t)blockIdx.x * kTile;
+  const int j0 = one_tile ? 0 : blockIdx.y * NT * 16;
+  T += (int64_t)(snap * gridDim.z + blockIdx.z) * t_part;
+  // a lane past the last column (of G or of Q) repeats columns that exist: its results are not stored
+  auto first_col = [&](int i) { const int64_t c = c0 + 4 * i; return NEAR && c > cols - 4 ? cols - 4 : c; };
+  const int64_t cl = first_col(i16);
+  int64_t cm[4];
+#pragma unroll
+  for (int m = 0; m < 4; ++m) cm[m] = cl + m < cols ? cl + m : cols - 1;
+  int jq[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) jq[t] = j0 + 16 * t + i16 < n ? j0 + 16 * t + i16 : n - 1;
+  f32x4 acc[4][NT];
+#pragma unroll
+  for (int m = 0; m < 4; ++m)
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[m][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  struct Operands { f32x4 a[kStep / 4]; float b[kStep / 4][NT]; };
+  uint32_t go[kStep / 4], qo[kStep / 4][NT];            // byte offsets from the step's first row of G and of Q
+#pragma unroll
+  for (int s = 0; s < kStep / 4; ++s) {
+    go[s] = (uint32_t)(4 * s + kg) * (uint32_t)ldg * 4u + (uint32_t)(cl - c0) * 4u;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) qo[s][t] = ((uint32_t)(4 * s + kg) * (uint32_t)ldq + (uint32_t)jq[t]) * 4u;
+  }
+  auto fetch = [&](int64_t r0, Operands& o) {
+    const float* gr = G + r0 * ldg + c0;
+    const float* qr = Q + r0 * ldq;
+#pragma unroll
+    for (int s = 0; s < kStep / 4; ++s) {
+      if (NEAR) o.a[s] = load4_at(gr, go[s]);
+      else
+#pragma unroll
+        for (int m = 0; m < 4; ++m) o.a[s][m] = G[(r0 + 4 * s + kg) * ldg + cm[m]];
+#pragma unroll
+      for (int t = 0; t < NT; ++t) o.b[s][t] = NEAR ? load1_at(qr, qo[s][t]) : Q[(r0 + 4 * s + kg) * ldq + jq[t]];
+    }
+  };
+  auto multiply = [&](const Operands& o) {
+#pragma unroll
+    for (int s = 0; s < kStep / 4; ++s)
+#pragma unroll
+      for (int m = 0; m < 4; ++m)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[m][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(o.a[s][m], o.b[s][t], acc[m][t], 0, 0, 0);
+  };
+  // Whole steps: the operands of the wave's next one travel while this one is multiplied (behind the last, it is read again).
+  const int64_t r_full = r_begin + (r_end - r_begin) / kStep * kStep;
+  int64_t r0 = r_begin + wave * kStep;
+  const int steps = uniform(r0 < r_full ? (int)((r_full - r0 + kWaves * kStep - 1) / (kWaves * kStep)) : 0);
+  if (steps > 0) {
+    Operands o0, o1;
+    auto step = [&](int i) { return r0 + (int64_t)(i < steps ? i : steps - 1) * (kWaves * kStep); };
+    int i = 0;
+    if (steps & 1) { fetch(r0, o0); multiply(o0); i = 1; }
+    fetch(step(i), o0);
+    for (; i < steps; i += 2) {
+      fetch(step(i + 1), o1);
+      in_this_order();
+      multiply(o0);
+      in_this_order();
+      fetch(step(i + 2), o0);
+      in_this_order();
+      multiply(o1);
+      in_this_order();
+    }
+    r0 += (int64_t)steps * (kWaves * kStep);
+  }
+  if (r0 == r_full && r_full < r_end) {                 // the rows left over: zeros past the end
+    Operands o;
+#pragma unroll
+    for (int s = 0; s < kStep / 4; ++s) {
+      const int64_t r = r0 + 4 * s + kg;
+      const bool ok = r < r_end;
+#pragma unroll
+      for (int m = 0; m < 4; ++m) o.a[s][m] = ok ? G[r * ldg + cm[m]] : 0.f;
+#pragma unroll
+      for (int t = 0; t < NT; ++t) o.b[s][t] = ok ? Q[r * ldq + jq[t]] : 0.f;
+    }
+    multiply(o);
+  }
+  add_waves<NT>(acc, lds, wave, lane);
+  if (wave != 0) return;
+#pragma unroll
+  for (int m = 0; m < 4; ++m)
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int64_t c = first_col(4 * kg + v) + m;
+        const int j = j0 + 16 * t + i16;
+        if (c >= c0 + 4 * (4 * kg + v) && c < cols && j < n) { float* o = T + c * ldt + j; *o = (accumulate ? *o : 0.f) + scale * acc[m][t][v]; }
+      }
+}
+
+// Y[r][j] (+)= sum_c G[r][c] T[c][j], j < k <= 64: G [rows, cols], T [cols, k] (that of snapshot z at T + z t_snap), Y [rows, k].
+// blockIdx.x: 64 rows, blockIdx.y = part of the sum: columns [part col_part, (part + 1) col_part), blockIdx.z = snapshot,
+// result at Y + (snapshot gridDim.y + part) y_part.
+// A lane's four consecutive columns of G are its terms of four matrix instructions: the step's terms are taken in the order
+// c = 4 kg + s, which the rows of T are read in as well.
+template <int NT, bool NEAR>
+__global__ void __launch_bounds__(64 * kWaves, 2) g_t_kernel(CloudSnaps g, int64_t rows, int64_t cols, const float* __restrict__ T, int64_t t_snap, int k,
+                                                          float* __restrict__ Y, int accumulate, int64_t col_part, int64_t y_part) {
+  __shared__ __attribute__((aligned(16))) float lds[2 * 4 * NT * 256];
+  const int lane = threadIdx.x & 63, wave = uniform((int)threadIdx.x >> 6), i16 = lane & 15, kg = lane >> 4;
+  const float* G = g.G[blockIdx.z];
+  T += blockIdx.z * t_snap;
   const int64_t c_begin = (int64_t)blockIdx.y * col_part;
   const int64_t c_end = cols < c_begin + col_part ? cols : c_begin + col_part;
-  Y += (int64_t)blockIdx.y * y_part;
-  float acc[16];
+  const int64_t r0 = (int64_t)blockIdx.x * kTile;
+  Y += (int64_t)(blockIdx.z * gridDim.y + blockIdx.y) * y_part;
+  int64_t rt[4];                                        // a row past the last repeats it: not stored
 #pragma unroll
-  for (int i = 0; i < 16; ++i) acc[i] = 0.f;
-  for (int64_t c0 = c_begin; c0 < c_end; c0 += kChunk) {
-    __syncthreads();
-    for (int i = tid; i < kTile * kChunk; i += 256) {
-      const int rr = i >> 5, cc = i & 31;                 // consecutive threads read consecutive columns of G
-      Gs[rr][cc] = (r0 + rr < rows && c0 + cc < c_end) ? G[(r0 + rr) * cols + c0 + cc] : 0.f;
-    }
-    for (int i = tid; i < kChunk * kTile; i += 256) {
-      const int cc = i >> 6, jj = i & 63;
-      Ts[cc][jj] = (c0 + cc < c_end && jj < k) ? T[(c0 + cc) * k + jj] : 0.f;
-    }
-    __syncthreads();
-#pragma unroll 4
-    for (int cc = 0; cc < kChunk; ++cc) {
-      const float g = Gs[rl][cc];
+  for (int t = 0; t < 4; ++t) rt[t] = r0 + 16 * t + i16 < rows ? r0 + 16 * t + i16 : rows - 1;
+  int jt[NT];
 #pragma unroll
-      for (int i = 0; i < 16; ++i) acc[i] = __builtin_fmaf(g, Ts[cc][jg * 16 + i], acc[i]);
-    }
+  for (int n = 0; n < NT; ++n) jt[n] = 16 * n + i16 < k ? 16 * n + i16 : k - 1;
+  f32x4 acc[4][NT];
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int n = 0; n < NT; ++n) acc[t][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+  struct Operands { f32x4 a[4]; float b[4][NT]; };
+  uint32_t go[4], to[4][NT];                            // byte offsets from the step's first column of G and row of T
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    go[t] = ((uint32_t)(rt[t] - r0) * (uint32_t)cols + 4u * kg) * 4u;
+#pragma unroll
+    for (int n = 0; n < NT; ++n) to[t][n] = (uint32_t)((4 * kg + t) * k + jt[n]) * 4u;
   }
-  if (r0 + rl < rows)
-    for (int i = 0; i < 16; ++i) {
-      const int j = jg * 16 + i;
-      if (j < k) { float* y = Y + (r0 + rl) * k + j; *y = (accumulate ? *y : 0.f) + acc[i]; }
+  auto fetch = [&](int64_t c0, Operands& o) {
+    const float* gr = G + r0 * cols + c0;
+    const float* tr = T + c0 * k;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      if (NEAR) o.a[t] = load4_at(gr, go[t]);
+      else
+#pragma unroll
+        for (int s = 0; s < 4; ++s) o.a[t][s] = G[rt[t] * cols + c0 + 4 * kg + s];
     }
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int n = 0; n < NT; ++n) o.b[s][n] = load1_at(tr, to[s][n]);
+  };
+  auto multiply = [&](const Operands& o) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int n = 0; n < NT; ++n) acc[t][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(o.a[t][s], o.b[s][n], acc[t][n], 0, 0, 0);
+  };
+  const int64_t c_full = c_begin + (c_end - c_begin) / kStep * kStep;
+  int64_t c0 = c_begin + wave * kStep;
+  const int steps = uniform(c0 < c_full ? (int)((c_full - c0 + kWaves * kStep - 1) / (kWaves * kStep)) : 0);
+  if (steps > 0) {
+    Operands o0, o1;
+    auto step = [&](int i) { return c0 + (int64_t)(i < steps ? i : steps - 1) * (kWaves * kStep); };
+    int i = 0;
+    if (steps & 1) { fetch(c0, o0); multiply(o0); i = 1; }
+    fetch(step(i), o0);
+    for (; i < steps; i += 2) {
+      fetch(step(i + 1), o1);
+      in_this_order();
+      multiply(o0);
+      in_this_order();
+      fetch(step(i + 2), o0);
+      in_this_order();
+      multiply(o1);
+      in_this_order();
+    }
+    c0 += (int64_t)steps * (kWaves * kStep);
+  }
+  if (c0 == c_full && c_full < c_end) {
+    Operands o;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int64_t c = c0 + 4 * kg + s;
+      const bool ok = c < c_end;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) o.a[t][s] = ok ? G[rt[t] * cols + c] : 0.f;
+#pragma unroll
+      for (int n = 0; n < NT; ++n) o.b[s][n] = ok ? T[c * k + jt[n]] : 0.f;
+    }
+    multiply(o);
+  }
+  add_waves<NT>(acc, lds, wave, lane);
+  if (wave != 0) return;
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int n = 0; n < NT; ++n)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int64_t r = r0 + 16 * t + 4 * kg + v;
+        const int j = 16 * n + i16;
+        if (r < rows && j < k) { float* y = Y + r * k + j; *y = (accumulate ? *y : 0.f) + acc[t][n][v]; }
+      }
 }
 
 // In-place orthonormalisation of the k columns of Y [rows, k] (row stride k), in the order of the columns: Gram-Schmidt in its
 // matrix form, Cholesky-QR, taken twice.  One round is
 //     W = Y^T Y        (fp64 sums, one partial W per block of rows: gram_kernel)
-//     W = L L^T        (fp64, one workgroup, which first adds the partial W in their order: cholesky_kernel)
-//     Y <- Y L^-T      (fp64 forward substitution, one row per thread: substitute_kernel)
+//     W = L L^T        (sum_gram_kernel adds the partial W in their order, cholesky_kernel factorises: fp64, one workgroup)
+//     Y <- Y L^-T      (fp64: apply_factor_kernel)
 // Column j becomes y_j minus its projection on the earlier columns, divided by the norm that is left.  The second round takes
 // out what the first left of the earlier columns (at most cond(Y)^2 2^-53, 1e-4 at the dependence threshold), so the result is
 // orthonormal to the rounding of its fp32 entries.  A column that the earlier ones already span (norm below 1e-6 of what it
 // started with) is stored as zeros and counted in *dependent.
 // The column-by-column form needs 3 k dependent sweeps over the rows, which one workgroup has to make: 33 ms for
-// 8192 x 64, waiting for the L2 in every sweep.  This form reads the block three times per round, spread over all the rows'
-// blocks, and what is serial (k pivots) stays inside one workgroup's LDS.
+// 8192 x 64, waiting for the L2 in every sweep.  This form reads the block twice per round, spread over all the rows'
+// blocks, and what is serial (k pivots, one barrier each) stays inside one workgroup.
 constexpr int kGramRows = 64;        // rows staged at a time
-constexpr int kGramMaxParts = 64;    // partial W at most: the workgroup that factorises adds them all
-constexpr int kGramLd = kMaxK + 1;
+constexpr int kGramMaxParts = 128;   // partial W at most
 
 // part[p][i k + j] = sum over the rows of part p of Y[r][i] Y[r][j], for every i >= j (16 x 16 tiles on and below the diagonal).
 // Thread (tx, ty) holds element (16 a + ty, 16 b + tx) of each tile (a, b).  NT = ceil(k / 16) tiles.
@@ -154,76 +354,139 @@ __global__ void __launch_bounds__(256) gram_kernel(const float* __restrict__ Y, 
     }
 }
 
-// Adds the partial W and factorises it in LDS, one pivot per barrier.  fac [k][k]: below the diagonal L, on it 1 / L_jj
-// (0 for a dependent column, whose row and column of L are zero as well).
-__global__ void __launch_bounds__(256) cholesky_kernel(const double* __restrict__ part, int n_parts, int k, double* __restrict__ fac, int* __restrict__ dependent) {
-  __shared__ double W[kMaxK][kGramLd];
-  __shared__ double inv[kMaxK], norm0[kMaxK];
-  const int tid = threadIdx.x;
-  const int n = k * k;
-  for (int e = tid; e < n; e += 256) {
-    const int i = e / k, j = e % k;
-    if (j > i) continue;
-    double v = 0.0;
+// W[e] = sum over p of part[p][e]: 64 entries per block, four threads per entry, each adding a quarter of the parts in order.
+__global__ void __launch_bounds__(256) sum_gram_kernel(const double* __restrict__ part, int n_parts, int n, double* __restrict__ W) {
+  __shared__ double sums[4][64];
+  const int e = blockIdx.x * 64 + (threadIdx.x & 63), q = threadIdx.x >> 6, per = (n_parts + 3) / 4;
+  double v = 0.0;
+  if (e < n) {
+    const int end = n_parts < (q + 1) * per ? n_parts : (q + 1) * per;
 #pragma unroll 8
-    for (int p = 0; p < n_parts; ++p) v += part[(int64_t)p * n + e];
-    W[i][j] = v;
-    if (i == j) norm0[j] = v;                      // the column's size before anything is taken out
+    for (int p = q * per; p < end; ++p) v += part[(int64_t)p * n + e];
   }
-  int n_dep = 0;
-  const int tx = tid & 15, ty = tid >> 4;
-  for (int j = 0; j < k; ++j) {
-    __syncthreads();                               // W is final up to column j
-    const double pivot = W[j][j];
-    const bool dep = !(pivot > 1e-12 * norm0[j]) || !(pivot > 0.0);
-    n_dep += dep;
-    const double ip = dep ? 0.0 : 1.0 / pivot;
-    if (tid == 0) inv[j] = dep ? 0.0 : 1.0 / sqrt(pivot);
-    for (int i = j + 1 + ty; i < k; i += 16) {
-      const double f = W[i][j] * ip;
-      for (int c = j + 1 + tx; c <= i; c += 16) W[i][c] -= f * W[c][j];
+  sums[q][threadIdx.x & 63] = v;
+  __syncthreads();
+  if (q == 0 && e < n) W[e] = (sums[0][threadIdx.x] + sums[1][threadIdx.x]) + (sums[2][threadIdx.x] + sums[3][threadIdx.x]);
+}
+
+// Factorises W [k][k] (its lower triangle is read) and inverts the factor: fac[i k + j] = (L^-1)_ji for i <= j, 0 otherwise and for
+// a dependent column j.  W = U D U^T with U unit lower triangular; X = U^-1 grows row by row under the same eliminations.
+// Thread (tx, ty) keeps the entries (16 a + ty, 16 b + tx) of what is left of W in registers, all of them updated at every pivot
+// (those of finished rows and columns are never read again), and those of X; the pivot's column and X's row go round through LDS, one barrier per pivot.
+// What bounds it is that chain of k barriers, LDS reads and reciprocals (about 0.35 us each).
+template <int NT>
+__global__ void __launch_bounds__(256) cholesky_kernel(const double* __restrict__ W, int k, double* __restrict__ fac, int* __restrict__ dependent) {
+  __shared__ double col[2][NT * 16], row[2][NT * 16], pivots[NT * 16], norm0[NT * 16], inv[NT * 16];
+  __shared__ int n_dep;
+  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
+  double w[NT][NT], x[NT][NT];
+#pragma unroll
+  for (int a = 0; a < NT; ++a)
+#pragma unroll
+    for (int b = 0; b < NT; ++b) {
+      const int i = 16 * a + ty, j = 16 * b + tx;
+      x[a][b] = i == j ? 1.0 : 0.0;
+      w[a][b] = (i < k && j < k) ? W[i >= j ? i * k + j : j * k + i] : 0.0;
+      if (i == j) norm0[j] = w[a][b];                 // the column's size before anything is taken out
     }
+  if (tid == 0) n_dep = 0;
+#pragma unroll
+  for (int b = 0; b < NT; ++b)
+    for (int jj = 0; jj < 16; ++jj) {
+      const int j = 16 * b + jj;
+      if (j >= k) break;                              // uniform
+      if (tx == jj)
+#pragma unroll
+        for (int a = 0; a < NT; ++a) col[j & 1][16 * a + ty] = w[a][b];
+      if (ty == jj)
+#pragma unroll
+        for (int c = 0; c < NT; ++c) row[j & 1][16 * c + tx] = x[b][c];
+      __syncthreads();
+      const double pivot = col[j & 1][j];
+      const bool dep = !(pivot > 1e-12 * norm0[j]) || !(pivot > 0.0);
+      if (tid == 0) pivots[j] = dep ? 0.0 : pivot;
+      double ip = __builtin_amdgcn_rcp(pivot);        // two Newton steps take the estimate to fp64 rounding
+      ip = __builtin_fma(__builtin_fma(-pivot, ip, 1.0), ip, ip);
+      ip = __builtin_fma(__builtin_fma(-pivot, ip, 1.0), ip, ip);
+      if (dep) ip = 0.0;
+      double g[NT], h[NT];
+#pragma unroll
+      for (int c = 0; c < NT; ++c) { g[c] = col[j & 1][16 * c + tx]; h[c] = row[j & 1][16 * c + tx]; }
+#pragma unroll
+      for (int a = 0; a < NT; ++a) {
+        const double f = 16 * a + ty > j ? -col[j & 1][16 * a + ty] * ip : 0.0;
+#pragma unroll
+        for (int c = 0; c < NT; ++c) { w[a][c] = __builtin_fma(f, g[c], w[a][c]); x[a][c] = __builtin_fma(f, h[c], x[a][c]); }
+      }
+    }
+  __syncthreads();
+  if (tid < k) {
+    inv[tid] = pivots[tid] > 0.0 ? 1.0 / sqrt(pivots[tid]) : 0.0;
+    if (!(pivots[tid] > 0.0)) atomicAdd(&n_dep, 1);
   }
   __syncthreads();
-  for (int e = tid; e < n; e += 256) {
-    const int i = e / k, j = e % k;
-    fac[e] = j < i ? W[i][j] * inv[j] : (j == i ? inv[i] : 0.0);
-  }
+#pragma unroll
+  for (int a = 0; a < NT; ++a)
+#pragma unroll
+    for (int b = 0; b < NT; ++b) {
+      const int j = 16 * a + ty, i = 16 * b + tx;
+      if (i < k && j < k) fac[i * k + j] = i <= j ? x[a][b] * inv[j] : 0.0;
+    }
   if (tid == 0) *dependent = n_dep;
 }
 
-// Row y of Y becomes q with q_j = (y_j - sum_{i<j} L_ji q_i) / L_jj.  One wave per block, 64 rows, one row per lane in registers;
-// rows come and go through LDS so that global accesses are contiguous.
+// Y <- Y fac: row q_j = sum_{i<=j} y_i fac[i][j] in fp64, 32 rows per block; thread (tx, ty) holds rows ty, 16 + ty and columns 16 b + tx.
+// (Forward substitution with a row per lane, everything unrolled, took 45 us at 8192 x 64: 30 KB of code fetched once.)
+constexpr int kApplyRows = 32;
 template <int NT>
-__global__ void __launch_bounds__(64) substitute_kernel(float* __restrict__ Y, int64_t rows, int k, const double* __restrict__ fac) {
+__global__ void __launch_bounds__(256) apply_factor_kernel(float* __restrict__ Y, int64_t rows, int k, const double* __restrict__ fac) {
   constexpr int KP = NT * 16;
   __shared__ double F[KP][KP];
-  __shared__ float Ys[64][KP + 1];
-  const int lane = threadIdx.x;
-  const int64_t r0 = (int64_t)blockIdx.x * 64;
-  const int n_rows = (int)(rows - r0 < 64 ? rows - r0 : 64);
-  for (int i = lane; i < KP * KP; i += 64) { const int a = i / KP, b = i % KP; F[a][b] = (a < k && b < k) ? fac[a * k + b] : 0.0; }
-  for (int i = lane; i < n_rows * k; i += 64) Ys[i / k][i % k] = Y[r0 * k + i];
-  __syncthreads();
-  double q[KP];
+  __shared__ float Ys[kApplyRows][KP + 1];
+  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
+  const int64_t r0 = (int64_t)blockIdx.x * kApplyRows;
 #pragma unroll
-  for (int j = 0; j < KP; ++j) {
-    double v = j < k ? (double)Ys[lane][j] : 0.0;
+  for (int e = tid; e < KP * KP; e += 256) { const int i = e / KP, j = e % KP; F[i][j] = (i < k && j < k) ? fac[i * k + j] : 0.0; }
 #pragma unroll
-    for (int i = 0; i < j; ++i) v = __builtin_fma(-F[j][i], q[i], v);
-    q[j] = v * F[j][j];
-    if (j < k) Ys[lane][j] = (float)q[j];
-  }
+  for (int e = tid; e < kApplyRows * KP; e += 256) { const int r = e / KP, c = e % KP; Ys[r][c] = (r0 + r < rows && c < k) ? Y[(r0 + r) * k + c] : 0.f; }
   __syncthreads();
-  for (int i = lane; i < n_rows * k; i += 64) Y[r0 * k + i] = Ys[i / k][i % k];
+  double acc[2][NT];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < NT; ++b) acc[a][b] = 0.0;
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll 4
+    for (int i = 16 * t; i < 16 * t + 16; ++i) {
+      const double y0 = (double)Ys[ty][i], y1 = (double)Ys[16 + ty][i];
+#pragma unroll
+      for (int b = t; b < NT; ++b) {
+        const double f = F[i][16 * b + tx];
+        acc[0][b] = __builtin_fma(y0, f, acc[0][b]);
+        acc[1][b] = __builtin_fma(y1, f, acc[1][b]);
+      }
+    }
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < NT; ++b) {
+      const int64_t r = r0 + 16 * a + ty;
+      const int j = 16 * b + tx;
+      if (r < rows && j < k) Y[r * k + j] = (float)acc[a][b];
+    }
 }
 
-// out[i] = (accumulate ? out[i] : 0) + scale (part[0][i] + part[1][i] + ...): the parts of a split sum, added in their order
-__global__ void __launch_bounds__(256) sum_parts_kernel(const float* __restrict__ part, int n_parts, int64_t stride, int64_t n, float* __restrict__ out, float scale, int accumulate) {
+// out[i] = (accumulate ? out[i] : 0) + part[0][i] + part[1][i] + ...: the parts of a split sum, added in their order.
+// blockIdx.y = y: parts y n_parts ... of the buffer into out + y n.
+__global__ void __launch_bounds__(256) sum_parts_kernel(const float* __restrict__ part, int n_parts, int64_t n, float* __restrict__ out, int accumulate) {
+  part += (int64_t)blockIdx.y * n_parts * n;
+  out += (int64_t)blockIdx.y * n;
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
     float v = 0.f;
-    for (int z = 0; z < n_parts; ++z) v += part[(int64_t)z * stride + i];
-    out[i] = (accumulate ? out[i] : 0.f) + scale * v;
+#pragma unroll 4
+    for (int z = 0; z < n_parts; ++z) v += part[(int64_t)z * n + i];
+    out[i] = (accumulate ? out[i] : 0.f) + v;
   }
 }
 
@@ -239,65 +502,87 @@ __global__ void __launch_bounds__(256) residual_kernel(float* __restrict__ R, co
 
 }  // namespace
 
-// How many parts to split a sum over `span` terms into, so that `blocks` blocks become about one per CU-slot: at most kCloudMaxParts,
-// each part a whole number of staged chunks.
-static int cloud_sum_parts(int64_t blocks, int64_t span) {
-  int64_t z = blocks > 0 ? 512 / blocks : 1;
-  const int64_t chunks = (span + kChunk - 1) / kChunk;
-  if (z > chunks) z = chunks;
-  if (z > kCloudMaxParts) z = kCloudMaxParts;
+// How many parts to split a sum over `span` terms into when `blocks` blocks take it undivided: three blocks per CU, which is
+// what the kernels' registers admit (G^T Q of three 8192 x 2048 snapshots at rank 64: 63 us with 768 blocks, 88 with 384), each part
+// at least two steps per wave, at most max_parts.
+static int cloud_sum_parts(int64_t blocks, int64_t span, int64_t max_parts) {
+  int64_t z = blocks > 0 ? 768 / blocks : 1;
+  const int64_t longest = span / (2 * kWaves * kStep);
+  if (z > longest) z = longest;
+  if (z > max_parts) z = max_parts;
   return z < 1 ? 1 : (int)z;
 }
 
-static hipError_t launch_sum_parts(const float* part, int n_parts, int64_t stride, int64_t n, float* out, float scale, int accumulate, hipStream_t s) {
-  hipLaunchKernelGGL(sum_parts_kernel, dim3((unsigned)(n / 256 + 1 < 1024 ? n / 256 + 1 : 1024)), dim3(256), 0, s, part, n_parts, stride, n, out, scale, accumulate);
+static hipError_t launch_sum_parts(const float* part, int n_parts, int64_t n, int n_out, float* out, int accumulate, hipStream_t s) {
+  hipLaunchKernelGGL(sum_parts_kernel, dim3((unsigned)(n / 256 + 1 < 1024 ? n / 256 + 1 : 1024), (unsigned)n_out), dim3(256), 0, s, part, n_parts, n, out, accumulate);
   return hipGetLastError();
 }
 
-// part: scratch of kCloudMaxParts * cols * n floats (ldt == n), or NULL for a single pass over all the rows
+// Whether the byte offsets within a step fit 32 bits (64 rows or 16, of at most `ld` floats) and a row holds the four columns a lane loads.
+static bool near_rows(int64_t cols, int64_t ld) { return cols >= 4 && ld < ((int64_t)1 << 24); }
+
+static int column_tiles(int n) { return n >= kTile ? 4 : (n + 15) / 16; }
+
+// The variant of a product kernel for NT = nt column tiles.
+#define ZGR_CLOUD_LAUNCH(KERNEL, nt, near, grid, ...)                                                                                                \
+  switch ((nt) * 2 + ((near) ? 1 : 0)) {                                                                                                             \
+    case 2: hipLaunchKernelGGL((KERNEL<1, false>), grid, dim3(64 * kWaves), 0, __VA_ARGS__); break;                                                  \
+    case 3: hipLaunchKernelGGL((KERNEL<1, true>), grid, dim3(64 * kWaves), 0, __VA_ARGS__); break;                                                   \
+    case 4: hipLaunchKernelGGL((KERNEL<2, false>), grid, dim3(64 * kWaves), 0, __VA_ARGS__); break;                                                  \
+    case 5: hipLaunchKernelGGL((KERNEL<2, true>), grid, dim3(64 * kWaves), 0, __VA_ARGS__); break;                                                   \
+    case 6: hipLaunchKernelGGL((KERNEL<3, false>), grid, dim3(64 * kWaves), 0, __VA_ARGS__); break;                                                  \
+    case 7: hipLaunchKernelGGL((KERNEL<3, true>), grid, dim3(64 * kWaves), 0, __VA_ARGS__); break;                                                   \
+    case 8: hipLaunchKernelGGL((KERNEL<4, false>), grid, dim3(64 * kWaves), 0, __VA_ARGS__); break;                                                  \
+    default: hipLaunchKernelGGL((KERNEL<4, true>), grid, dim3(64 * kWaves), 0, __VA_ARGS__); break;                                                  \
+  }
+
 hipError_t launch_cloud_gt_q(const float* G, int64_t rows, int64_t cols, int64_t ldg, const float* Q, int n, int64_t ldq, float* T, int64_t ldt, float scale,
-                             int accumulate, hipStream_t s, float* part) {
-  const unsigned gx = (unsigned)((cols + kTile - 1) / kTile), gy = (unsigned)((n + kTile - 1) / kTile);
-  const int z = (part && ldt == n) ? cloud_sum_parts((int64_t)gx * gy, rows) : 1;
-  if (z <= 1) {
-    hipLaunchKernelGGL(gt_q_kernel, dim3(gx, gy), dim3(256), 0, s, G, rows, cols, ldg, Q, n, ldq, T, ldt, scale, accumulate, rows, (int64_t)0);
-    return hipGetLastError();
-  }
-  const int64_t chunks = (rows + kChunk - 1) / kChunk, row_part = (chunks + z - 1) / z * kChunk, stride = cols * (int64_t)n;
-  hipLaunchKernelGGL(gt_q_kernel, dim3(gx, gy, (unsigned)z), dim3(256), 0, s, G, rows, cols, ldg, Q, n, ldq, part, (int64_t)n, 1.0f, 0, row_part, stride);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return launch_sum_parts(part, z, stride, stride, T, scale, accumulate, s);
+                             int accumulate, hipStream_t s) {
+  const CloudSnaps g{{G}};
+  const int nt = column_tiles(n);
+  const dim3 grid((unsigned)((cols + kTile - 1) / kTile), (unsigned)((n + 16 * nt - 1) / (16 * nt)), 1);
+  ZGR_CLOUD_LAUNCH(gt_q_kernel, nt, near_rows(cols, ldg > ldq ? ldg : ldq), grid, s, g, 0, rows, cols, ldg, Q, n, ldq, T, ldt, scale, accumulate, rows, (int64_t)0)
+  return hipGetLastError();
 }
 
-// part: scratch of kCloudMaxParts * rows * k floats, or NULL for a single pass over all the columns
-hipError_t launch_cloud_g_t(const float* G, int64_t rows, int64_t cols, const float* T, int k, float* Y, int accumulate, hipStream_t s, float* part) {
-  const unsigned gx = (unsigned)((rows + kTile - 1) / kTile);
-  const int z = part ? cloud_sum_parts(gx, cols) : 1;
-  if (z <= 1) {
-    hipLaunchKernelGGL(g_t_kernel, dim3(gx), dim3(256), 0, s, G, rows, cols, T, k, Y, accumulate, cols, (int64_t)0);
-    return hipGetLastError();
-  }
-  const int64_t chunks = (cols + kChunk - 1) / kChunk, col_part = (chunks + z - 1) / z * kChunk, stride = rows * (int64_t)k;
-  hipLaunchKernelGGL(g_t_kernel, dim3(gx, (unsigned)z), dim3(256), 0, s, G, rows, cols, T, k, part, 0, col_part, stride);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return launch_sum_parts(part, z, stride, stride, Y, 1.0f, accumulate, s);
+hipError_t launch_cloud_gt_q_all(const CloudSnaps& g, int n_snap, int64_t rows, int64_t cols, const float* Q, int k, float* T, float* part, int64_t part_floats, hipStream_t s) {
+  const int nt = column_tiles(k);
+  const int64_t strips = (cols + kTile - 1) / kTile, n = cols * k;
+  const int z = cloud_sum_parts(strips * n_snap, rows, part_floats / n / n_snap);
+  const int64_t steps = (rows + kStep - 1) / kStep, row_part = (steps + z - 1) / z * kStep;
+  const dim3 grid((unsigned)strips, (unsigned)n_snap, (unsigned)z);
+  ZGR_CLOUD_LAUNCH(gt_q_kernel, nt, near_rows(cols, cols), grid, s, g, 1, rows, cols, cols, Q, k, (int64_t)k, z > 1 ? part : T, (int64_t)k, 1.0f, 0, row_part, n)
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || z == 1) return e;
+  return launch_sum_parts(part, z, n, n_snap, T, 0, s);
 }
 
-size_t cloud_orth_scratch_doubles(int64_t rows, int k) {
-  const int64_t parts = (rows + kGramRows - 1) / kGramRows;
-  return (size_t)((parts < kGramMaxParts ? parts : kGramMaxParts) + 1) * (size_t)k * (size_t)k;
+hipError_t launch_cloud_g_t_all(const CloudSnaps& g, int n_snap, int64_t rows, int64_t cols, const float* T, int64_t t_snap, int k, float* Y, int accumulate, float* part, int64_t part_floats,
+                                hipStream_t s) {
+  const int nt = column_tiles(k);
+  const int64_t strips = (rows + kTile - 1) / kTile, n = rows * k;
+  const int z = cloud_sum_parts(strips * n_snap, cols, part_floats / n / n_snap);
+  const int64_t steps = (cols + kStep - 1) / kStep, col_part = (steps + z - 1) / z * kStep;
+  const bool whole = n_snap * z == 1;
+  const dim3 grid((unsigned)strips, (unsigned)z, (unsigned)n_snap);
+  ZGR_CLOUD_LAUNCH(g_t_kernel, nt, near_rows(cols, cols), grid, s, g, rows, cols, T, t_snap, k, whole ? Y : part, whole ? accumulate : 0, col_part, n)
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || whole) return e;
+  return launch_sum_parts(part, n_snap * z, n, 1, Y, accumulate, s);
 }
+#undef ZGR_CLOUD_LAUNCH
 
 template <int NT>
 static hipError_t orth_round(float* Y, int64_t rows, int k, int* dependent, double* scratch, hipStream_t s) {
   const int64_t chunks = (rows + kGramRows - 1) / kGramRows;
   const int64_t per = (chunks + kGramMaxParts - 1) / kGramMaxParts, parts = (chunks + per - 1) / per;
-  double* fac = scratch + parts * k * k;
+  const int n = k * k;
+  double* W = scratch + parts * n;
+  double* fac = W + n;
   hipLaunchKernelGGL(gram_kernel<NT>, dim3((unsigned)parts), dim3(256), 0, s, Y, rows, k, per * kGramRows, scratch);
-  hipLaunchKernelGGL(cholesky_kernel, dim3(1), dim3(256), 0, s, scratch, (int)parts, k, fac, dependent);
-  hipLaunchKernelGGL(substitute_kernel<NT>, dim3((unsigned)((rows + 63) / 64)), dim3(64), 0, s, Y, rows, k, fac);
+  hipLaunchKernelGGL(sum_gram_kernel, dim3((unsigned)((n + 63) / 64)), dim3(256), 0, s, scratch, (int)parts, n, W);
+  hipLaunchKernelGGL(cholesky_kernel<NT>, dim3(1), dim3(256), 0, s, W, k, fac, dependent);
+  hipLaunchKernelGGL(apply_factor_kernel<NT>, dim3((unsigned)((rows + kApplyRows - 1) / kApplyRows)), dim3(256), 0, s, Y, rows, k, fac);
   return hipGetLastError();
 }
 

@@ -95,14 +95,18 @@ hipError_t launch_debug_issue(int op, int ilp, int blocks, int iters, unsigned l
 hipError_t launch_debug_generator(int part, int blocks, int iters, unsigned long long* out, hipStream_t s);
 
 // cloud side (cloud.hip): tall-skinny products with the gradient snapshots, orthonormalisation, least-squares residual.
-// part (optional scratch): the sum over the long dimension is split into up to kCloudMaxParts parts over more blocks and the
-// parts are added in their order; kCloudMaxParts * cols * n floats for gt_q (needs ldt == n), kCloudMaxParts * rows * k for g_t.
-constexpr int kCloudMaxParts = 16;
+constexpr int kCloudSnaps = 4;       // snapshots one launch takes
+struct CloudSnaps { const float* G[kCloudSnaps]; };
+// T[c][j] (+)= scale sum_r G[r][c] Q[r][j]
 hipError_t launch_cloud_gt_q(const float* G, int64_t rows, int64_t cols, int64_t ldg, const float* Q, int n, int64_t ldq, float* T, int64_t ldt, float scale,
-                             int accumulate, hipStream_t s, float* part = nullptr);
-hipError_t launch_cloud_g_t(const float* G, int64_t rows, int64_t cols, const float* T, int k, float* Y, int accumulate, hipStream_t s, float* part = nullptr);
-// scratch: cloud_orth_scratch_doubles(rows, k) doubles
-size_t     cloud_orth_scratch_doubles(int64_t rows, int k);
+                             int accumulate, hipStream_t s);
+// T_i = G_i^T Q into T + i cols k, and Y (+)= sum_i G_i T_i with T_i at T + i t_snap, for n_snap <= kCloudSnaps snapshots at once.  The sums over
+// the long dimension are split over more blocks into parts that are added in their order; part: scratch of part_floats floats, which holds
+// n_snap results at least (n_snap cols k, n_snap rows k).
+hipError_t launch_cloud_gt_q_all(const CloudSnaps& g, int n_snap, int64_t rows, int64_t cols, const float* Q, int k, float* T, float* part, int64_t part_floats, hipStream_t s);
+hipError_t launch_cloud_g_t_all(const CloudSnaps& g, int n_snap, int64_t rows, int64_t cols, const float* T, int64_t t_snap, int k, float* Y, int accumulate, float* part, int64_t part_floats,
+                                hipStream_t s);
+// scratch: (min(ceil(rows / 64), 128) + 2) k^2 doubles
 hipError_t launch_cloud_orth(float* Y, int64_t rows, int k, int* dependent, double* scratch, hipStream_t s);
 hipError_t launch_cloud_copy_basis(const float* Q, int64_t rows, int k, float* U, int ldu, hipStream_t s);
 hipError_t launch_cloud_residual(float* R, const float* Y, int64_t n, hipStream_t s);

@@ -55,6 +55,40 @@ def test_basis_of_snapshots_with_a_spectral_gap(rows, cols, s, k, ldu):
     _check_basis(snaps, k, n_iter=3, ldu=ldu)
 
 
+@pytest.mark.parametrize("rows,cols,s,k", [
+    (1, 1, 1, 1),                # a single entry
+    (5, 3, 2, 3),                # fewer than four columns: the general form of the products
+    (64, 18, 13, 16),            # columns no multiple of four, several launches of four snapshots, one whole column tile
+    (65, 63, 5, 17),             # one row past a tile, one column past a tile of the block
+    (127, 66, 1, 33),
+    (192, 130, 2, 63),
+    (200, 4, 16, 4),             # exactly four columns
+    (8193, 257, 1, 48),          # the Gram matrix in its most parts, the last with one row
+])
+def test_basis_without_sweeps_is_the_orthonormalised_product(rows, cols, s, k):
+    """n_iter = 0: U is Gram-Schmidt of Y = sum_t G_t Omega, column by column, which fp64 QR with a positive diagonal gives.
+    An entry of Y carries at most about sqrt(s cols) fp32 roundings of its column's size, and a perturbation E of Y moves
+    the orthonormal factor by at most about cond(Y) |E| / |Y| times the width (columns scaled to unit norm).  k <= cols: columns
+    past the snapshots' width hold rounding noise only, up to sqrt(s cols) cond 2^-24 of their size, which may lie on either side
+    of the 1e-6 at which a column counts as dependent."""
+    from paper_2601_12917_amd.session import cloud_basis
+    rng = np.random.default_rng(rows * 7 + cols)
+    snaps = [rng.standard_normal((rows, cols)).astype(np.float32) for _ in range(s)]
+    omega = rng.standard_normal((cols, k)).astype(np.float32)
+    U, dep = cloud_basis(snaps, k, omega, 0)
+    Y = sum(g.astype(np.float64) @ omega.astype(np.float64) for g in snaps)
+    size = np.sqrt(sum((np.abs(g).astype(np.float64) ** 2).sum() for g in snaps) / rows * (omega.astype(np.float64) ** 2).sum(0) / cols)
+    assert dep == 0
+    Q, R = np.linalg.qr(Y)
+    Q = Q * np.sign(np.diag(R))
+    Yn = Y / np.linalg.norm(Y, axis=0)
+    grow = (size * np.sqrt(rows) / np.linalg.norm(Y, axis=0)).max()
+    tol = np.sqrt(s * cols) * k * np.linalg.cond(Yn) * grow * 2.0 ** -24 + 2.0 ** -22
+    assert np.abs(U - Q).max() <= tol, (np.abs(U - Q).max(), tol)
+    Uk = U.astype(np.float64)
+    assert np.abs(Uk.T @ Uk - np.eye(k)).max() <= 2e-6
+
+
 def test_lsq_gradient_and_basis_of_the_gradients_along_a_descent():
     """The cloud trains the least-squares model by gradient descent and keeps its last four gradients."""
     from paper_2601_12917_amd.session import cloud_lsq_gradient
