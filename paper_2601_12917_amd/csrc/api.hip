@@ -6,6 +6,7 @@
 #include "backward.h"
 #include "forward.h"
 #include "internal.h"
+#include "product.h"
 
 #include <cmath>
 #include <cstdarg>
@@ -893,8 +894,10 @@ struct BwCarve {
   size_t part = 0;                   // chunk sums of the column reductions
   size_t tA = 0, tB = 0, tW = 0;     // bf16 operands of the matrix-core products (bf16 models with a token count that is a multiple of 64)
   bool mfma = false;
+  size_t split = 0;                  // parts of split sums
   size_t total = 0;
 };
+constexpr size_t kProductScratch = ((size_t)1 << 21) + ((size_t)1 << 17);      // floats: 2048 waves, four to a 64 x 64 result, and row sums
 
 BwCarve bw_carve(const zgr_ctx* c, int batch, int seq) {
   BwCarve v;
@@ -930,6 +933,7 @@ BwCarve bw_carve(const zgr_ctx* c, int batch, int seq) {
   v.dS = take((size_t)batch * m.n_head * seq * seq * 4);
   v.stats = take(M * 2 * 4);
   v.part = take(4 * bw_colsum_scratch_floats((int)std::max(std::max(ff, 3 * d), (size_t)m.n_class)));
+  v.split = take(kProductScratch * 4);
   v.mfma = c->dtype == ZGR_BF16 && M % 64 == 0;
   if (v.mfma) {
     // widest contraction of a product: the feed-forward width, the three projections side by side, or (decoder) the
@@ -988,12 +992,18 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
   const int32_t* tok = reinterpret_cast<const int32_t*>(b->x);
   const int32_t* lengths = lm ? nullptr : b->lengths;
   const size_t xbytes = (size_t)M * d * 4;
-  // The products of the backward half.  fp32 models: the strided fp32 kernel on the operands as they lie.  bf16 models
+  // The products of the backward half.  fp32 models and ragged token counts: fp32 products on the operands as they lie.  bf16 models
   // (token count a multiple of 64): the forward pass's matrix-core GEMM, which contracts along the rows of both
   // operands, on bf16 copies written out with the contraction index innermost.
   unsigned char* tA = ws + v.tA; unsigned char* tB = ws + v.tB; unsigned char* tW = ws + v.tW;
   const void* tB_holds = nullptr;                       // the kept activation whose transpose tB holds
   // dA [M, Kp] = dY [M, Np] W [Np, Kp]
+  auto product = [&](const void* A, bool a_k, int64_t lda, const void* B, int64_t ldb, float* C, int64_t ldc, int Mp, int Np, int Kp, float* a_sums) {
+    ProductArgs p;
+    p.A = A; p.a_k = a_k; p.lda = lda; p.B = B; p.b_dtype = dt == ZGR_BF16 ? 1 : 0; p.b_k = false; p.ldb = ldb; p.C = C; p.ldc = ldc;
+    p.M = Mp; p.N = Np; p.K = Kp; p.a_sums = a_sums; p.scratch = F(v.split); p.scratch_floats = kProductScratch;
+    return launch_product(p, s);
+  };
   auto input_grad = [&](const float* dy, int Np, const void* W, int Kp, float* out) -> zgr_status {
     const size_t lim = (size_t)1 << 31;                          // the GEMM addresses its operands with 32-bit offsets
     const int Npad = (Np + 63) & ~63;                            // zeros in both operands past Np
@@ -1002,7 +1012,7 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
       HIP_TRY(c, launch_bw_transpose_bf16(1, W, Np, Kp, Kp, tW, Npad, s));
       HIP_TRY(c, launch_gemm(ZGR_BF16, tA, tW, nullptr, out, EPI_F32, M, Kp, Npad, s));
     } else {
-      HIP_TRY(c, launch_bw_gemm(dt, dy, Np, 1, W, Kp, 1, out, Kp, M, Kp, Np, 1.0f, 0, s));
+      HIP_TRY(c, product(dy, true, Np, W, Kp, out, Kp, M, Kp, Np, nullptr));
     }
     return ZGR_OK;
   };
@@ -1015,7 +1025,8 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
       if (tB_holds != a) { HIP_TRY(c, launch_bw_transpose_bf16(1, a, M, Kp, Kp, tB, M, s)); tB_holds = a; }
       HIP_TRY(c, launch_gemm(ZGR_BF16, tA, tB, nullptr, dW, EPI_F32, Np, Kp, M, s));
     } else {
-      HIP_TRY(c, launch_bw_gemm(dt, dy, 1, ldy, a, Kp, 1, dW, Kp, Np, Kp, M, 1.0f, 0, s));
+      HIP_TRY(c, product(dy, false, ldy, a, Kp, dW, Kp, Np, Kp, M, dbias));
+      return ZGR_OK;
     }
     if (dbias) HIP_TRY(c, launch_bw_colsum(dy, M, Np, ldy, dbias, F(v.part), s));
     return ZGR_OK;
@@ -1086,10 +1097,9 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
     HIP_TRY(c, launch_mean_f64(F(v.row_loss), B, 1.0 / B, loss_dev, s));
     HIP_TRY(c, launch_bw_cross_entropy(logits, labels, B, C, 1.0f / (float)B, s));
     // the head reads the first token of each sequence: rows b T of hf
-    HIP_TRY(c, launch_bw_gemm(dt, logits, 1, C, ws + v.hf, (int64_t)Tn * d, 1, grads[c->cls_w], d, C, d, B, 1.0f, 0, s));
-    HIP_TRY(c, launch_bw_colsum(logits, B, C, C, grads[c->cls_b], F(v.part), s));
+    HIP_TRY(c, product(logits, false, C, ws + v.hf, (int64_t)Tn * d, grads[c->cls_w], d, C, d, B, grads[c->cls_b]));
     HIP_TRY(c, launch_bw_fill(dtb, (int64_t)M * d, 0.f, s));
-    HIP_TRY(c, launch_bw_gemm(dt, logits, C, 1, T(c, c->cls_w), d, 1, dtb, (int64_t)Tn * d, B, d, C, 1.0f, 0, s));
+    HIP_TRY(c, product(logits, true, C, T(c, c->cls_w), d, dtb, (int64_t)Tn * d, B, d, C, nullptr));
     HIP_TRY(c, launch_bw_fill(grads[c->tok_emb], (int64_t)m.vocab * d, 0.f, s));
   }
   // ---- the blocks in reverse; dx holds dL/d(residual stream) at the block's output
@@ -1392,6 +1402,20 @@ zgr_status zgr_debug_gemm(int32_t dtype, const void* A, const void* W, const voi
   if ((dtype != ZGR_F32 && dtype != ZGR_BF16) || epilogue < 0 || epilogue > 3) return fail(nullptr, ZGR_ERR_CONFIG, "bad dtype or epilogue");
   if (M < 1 || N < 1 || K < 1 || (dtype == ZGR_BF16 && K % 64)) return fail(nullptr, ZGR_ERR_SHAPE, "bad GEMM shape");
   HIP_TRY(nullptr, launch_gemm(dtype, A, W, bias, out, epilogue, M, N, K, reinterpret_cast<hipStream_t>(hip_stream)));
+  return ZGR_OK;
+}
+
+zgr_status zgr_debug_product(const void* A, int32_t a_dtype, int32_t a_k, int64_t lda, int64_t a_batch, const void* B, int32_t b_dtype, int32_t b_k, int64_t ldb, int64_t b_batch,
+                             float* C, int64_t ldc, int64_t c_batch, int32_t M, int32_t N, int32_t K, float alpha, int32_t batches, float* a_sums, float* scratch, size_t scratch_floats,
+                             void* hip_stream) {
+  if (!A || !B || !C) return fail(nullptr, ZGR_ERR_NULL, "a pointer is NULL");
+  if (M < 1 || N < 1 || K < 1 || batches < 1 || batches > 65535) return fail(nullptr, ZGR_ERR_SHAPE, "bad shape");
+  ProductArgs p;
+  p.A = A; p.a_dtype = a_dtype; p.a_k = a_k != 0; p.lda = lda; p.a_outer = a_batch;
+  p.B = B; p.b_dtype = b_dtype; p.b_k = b_k != 0; p.ldb = ldb; p.b_outer = b_batch;
+  p.C = C; p.ldc = ldc; p.c_outer = c_batch; p.M = M; p.N = N; p.K = K; p.alpha = alpha; p.batches = batches;
+  p.a_sums = a_sums; p.scratch = scratch; p.scratch_floats = scratch_floats;
+  HIP_TRY(nullptr, launch_product(p, reinterpret_cast<hipStream_t>(hip_stream)));
   return ZGR_OK;
 }
 

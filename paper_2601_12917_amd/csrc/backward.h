@@ -8,9 +8,6 @@ namespace zgr {
 
 constexpr int kBackwardMaxSeq = 2048;      // keys one workgroup of the attention rule holds
 
-// C[i][j] (+)= alpha sum_k A[i ars + k acs] B[k brs + j bcs]; A fp32, B of b_dtype
-hipError_t launch_bw_gemm(int b_dtype, const float* A, int64_t ars, int64_t acs, const void* B, int64_t brs, int64_t bcs, float* C, int64_t ldc,
-                          int M, int N, int K, float alpha, int accumulate, hipStream_t s);
 // bf16 operands for the matrix-core products: out [cols, rows] (row stride ld_out) = in [rows, cols]^T, in fp32 or bf16
 // (row stride ld_in); out [rows, cols] (row stride ld_out) = in rounded.  What lies between the data and ld_out is written as zeros.
 hipError_t launch_bw_transpose_bf16(int in_dtype, const void* in, int rows, int cols, int64_t ld_in, void* out, int64_t ld_out, hipStream_t s);

@@ -3,10 +3,11 @@
 // layer by layer, in fp32.  The forward pass that precedes it runs the client's own kernels and keeps every layer's
 // intermediate results; these kernels take them back in reverse order.
 //
-// This runs on the cloud once per stored gradient snapshot, not on the client's step: the kernels are plain
-// (LDS-tiled fp32 products with general strides, one workgroup per row for the row-wise rules), deterministic (no
-// atomics: every sum has a fixed order) and not tuned.
+// This runs on the cloud once per stored gradient snapshot, not on the client's step.  The products run on the matrix cores (forward.hip
+// for bf16 operands, product.hip for the others); the row-wise rules take one workgroup per row.  Deterministic: no atomics, every
+// sum has a fixed order.
 #include "backward.h"
+#include "product.h"
 
 namespace zgr {
 
@@ -45,56 +46,6 @@ __device__ __forceinline__ float block_max(float v, float* red) {
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
   return fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-}
-
-// ------------------------------------------------------------------ C (+)= alpha A B with general strides
-// C[i][j] = sum_k A[i ars + k acs] B[k brs + j bcs], i < M, j < N, k < K; A and B fp32 (a gradient) or the storage
-// type (a weight or a kept activation).  64 x 64 tile, 16 deep, 4 x 4 outputs per thread; every output adds its K terms
-// in the order of k.  The two uses on weights:
-//   input gradient   dA [M, K'] = dY [M, N'] W [N', K']      : A = dY (ars = N', acs = 1), B = W  (brs = K', bcs = 1)
-//   weight gradient  dW [N', K'] = dY^T [N', M] A_in [M, K'] : A = dY (ars = 1, acs = N'), B = A_in (brs = K', bcs = 1)
-// Batched over blockIdx.z = z: operand X of batch z starts at X + (z / zdiv) * x_outer + (z % zdiv) * x_inner (elements).
-struct BatchOffsets { int zdiv; int64_t a_outer, a_inner, b_outer, b_inner, c_outer, c_inner; };
-
-template <typename TA, typename TB>
-__global__ void __launch_bounds__(256) gemm_strided_kernel(const TA* __restrict__ A, int64_t ars, int64_t acs, const TB* __restrict__ B, int64_t brs, int64_t bcs,
-                                                           float* __restrict__ C, int64_t ldc, int M, int N, int K, float alpha, int accumulate, BatchOffsets bo) {
-  __shared__ float As[16][64 + 4], Bs[16][64 + 4];
-  {
-    const int zo = (int)blockIdx.z / bo.zdiv, zi = (int)blockIdx.z % bo.zdiv;
-    A += zo * bo.a_outer + zi * bo.a_inner;
-    B += zo * bo.b_outer + zi * bo.b_inner;
-    C += zo * bo.c_outer + zi * bo.c_inner;
-  }
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  const bool a_rows_contig = ars == 1, b_k_contig = brs == 1;       // which index consecutive threads should walk
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    for (int i = threadIdx.x; i < 64 * 16; i += 256) {
-      const int ra = a_rows_contig ? (i & 63) : (i >> 4), ka = a_rows_contig ? (i >> 6) : (i & 15);
-      As[ka][ra] = (m0 + ra < M && k0 + ka < K) ? to_f32(A[(int64_t)(m0 + ra) * ars + (int64_t)(k0 + ka) * acs]) : 0.f;
-      const int cb = b_k_contig ? (i >> 4) : (i & 63), kb = b_k_contig ? (i & 15) : (i >> 6);
-      Bs[kb][cb] = (n0 + cb < N && k0 + kb < K) ? to_f32(B[(int64_t)(k0 + kb) * brs + (int64_t)(n0 + cb) * bcs]) : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      float a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) { a[i] = As[kk][ty * 4 + i]; b[i] = Bs[kk][tx * 4 + i]; }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-  for (int i = 0; i < 4; ++i)
-    for (int j = 0; j < 4; ++j) {
-      const int m = m0 + ty * 4 + i, n = n0 + tx * 4 + j;
-      if (m < M && n < N) { float* c = C + (int64_t)m * ldc + n; *c = (accumulate ? *c : 0.f) + alpha * acc[i][j]; }
-    }
 }
 
 // ------------------------------------------------------------------ operands for the matrix-core products (bf16 models)
@@ -329,22 +280,6 @@ __global__ void __launch_bounds__(256) embed_backward_kernel(const int32_t* __re
 
 static unsigned grid_1d(int64_t n) { const int64_t b = (n + 255) / 256; return (unsigned)(b < 1 ? 1 : (b > 4096 ? 4096 : b)); }
 
-template <typename TA>
-static hipError_t launch_bw_gemm_batched(const TA* A, int64_t ars, int64_t acs, int b_dtype, const void* B, int64_t brs, int64_t bcs, float* C, int64_t ldc,
-                                         int M, int N, int K, float alpha, int accumulate, int batches, const BatchOffsets& bo, hipStream_t s) {
-  if (M < 1 || N < 1 || batches < 1) return hipSuccess;
-  if (batches > 65535 || (M + 63) / 64 > 65535) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)((N + 63) / 64), (unsigned)((M + 63) / 64), (unsigned)batches);
-  if (b_dtype == 1) hipLaunchKernelGGL((gemm_strided_kernel<TA, bf16_t>), grid, dim3(256), 0, s, A, ars, acs, reinterpret_cast<const bf16_t*>(B), brs, bcs, C, ldc, M, N, K, alpha, accumulate, bo);
-  else              hipLaunchKernelGGL((gemm_strided_kernel<TA, float>), grid, dim3(256), 0, s, A, ars, acs, reinterpret_cast<const float*>(B), brs, bcs, C, ldc, M, N, K, alpha, accumulate, bo);
-  return hipGetLastError();
-}
-
-hipError_t launch_bw_gemm(int b_dtype, const float* A, int64_t ars, int64_t acs, const void* B, int64_t brs, int64_t bcs, float* C, int64_t ldc,
-                          int M, int N, int K, float alpha, int accumulate, hipStream_t s) {
-  return launch_bw_gemm_batched(A, ars, acs, b_dtype, B, brs, bcs, C, ldc, M, N, K, alpha, accumulate, 1, BatchOffsets{1, 0, 0, 0, 0, 0, 0}, s);
-}
-
 hipError_t launch_bw_transpose_bf16(int in_dtype, const void* in, int rows, int cols, int64_t ld_in, void* out, int64_t ld_out, hipStream_t s) {
   if (rows < 1 || cols < 1) return hipSuccess;
   const dim3 grid((unsigned)((cols + 63) / 64), (unsigned)((ld_out + 63) / 64));
@@ -425,27 +360,30 @@ hipError_t launch_bw_attention(int dtype, const void* qkv, const float* dctx, co
   const int64_t tt = (int64_t)seq * seq, ld = (int64_t)3 * d;
   const float scale = 1.0f / sqrtf((float)dh);
   const int64_t sq_outer = (int64_t)seq * ld, dc_outer = (int64_t)seq * d, p_outer = n_head * tt;
+  const size_t es = dtype == 1 ? 2 : 4;
+  const char* q0 = reinterpret_cast<const char*>(qkv);
+  const char* k0 = q0 + es * d;
+  const char* v0 = k0 + es * d;
+  ProductArgs p;
+  p.batches = heads; p.zdiv = n_head;
+  auto product = [&](const void* A, int a_dtype, bool a_k, int64_t lda, int64_t a_outer, int64_t a_inner, const void* B, int b_dtype, bool b_k, int64_t ldb, int64_t b_outer, int64_t b_inner,
+                     float* C, int64_t ldc, int64_t c_outer, int64_t c_inner, int N, int K, float alpha) {
+    p.A = A; p.a_dtype = a_dtype; p.a_k = a_k; p.lda = lda; p.a_outer = a_outer; p.a_inner = a_inner;
+    p.B = B; p.b_dtype = b_dtype; p.b_k = b_k; p.ldb = ldb; p.b_outer = b_outer; p.b_inner = b_inner;
+    p.C = C; p.ldc = ldc; p.c_outer = c_outer; p.c_inner = c_inner;
+    p.M = seq; p.N = N; p.K = K; p.alpha = alpha;
+    return launch_product(p, s);
+  };
   hipError_t e;
-  // S [i][j] = sum_t q[i][t] k[j][t] / sqrt dh
-  const BatchOffsets bs{n_head, sq_outer, dh, sq_outer, dh, p_outer, tt};
-  if (dtype == 1) e = launch_bw_gemm_batched(reinterpret_cast<const bf16_t*>(qkv), ld, 1, dtype, reinterpret_cast<const bf16_t*>(qkv) + d, 1, ld, P, seq, seq, seq, dh, scale, 0, heads, bs, s);
-  else            e = launch_bw_gemm_batched(reinterpret_cast<const float*>(qkv), ld, 1, dtype, reinterpret_cast<const float*>(qkv) + d, 1, ld, P, seq, seq, seq, dh, scale, 0, heads, bs, s);
-  if (e != hipSuccess) return e;
-  // dP [i][j] = sum_t dctx[i][t] v[j][t]
-  const void* v0 = dtype == 1 ? (const void*)(reinterpret_cast<const bf16_t*>(qkv) + 2 * d) : (const void*)(reinterpret_cast<const float*>(qkv) + 2 * d);
-  e = launch_bw_gemm_batched(dctx, (int64_t)d, 1, dtype, v0, 1, ld, dS, seq, seq, seq, dh, 1.0f, 0, heads, BatchOffsets{n_head, dc_outer, dh, sq_outer, dh, p_outer, tt}, s);
-  if (e != hipSuccess) return e;
+  // S [i][j] = sum_t q[i][t] k[j][t] / sqrt dh,  dP [i][j] = sum_t dctx[i][t] v[j][t]
+  if ((e = product(q0, dtype, true, ld, sq_outer, dh, k0, dtype, true, ld, sq_outer, dh, P, seq, p_outer, tt, seq, dh, scale)) != hipSuccess) return e;
+  if ((e = product(dctx, 0, true, d, dc_outer, dh, v0, dtype, true, ld, sq_outer, dh, dS, seq, p_outer, tt, seq, dh, 1.0f)) != hipSuccess) return e;
   hipLaunchKernelGGL(attn_backward_rows_kernel, dim3((unsigned)heads * seq), dim3(256), 0, s, lengths, seq, n_head, causal, P, dS);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  // dQ [i][t] = sum_j dS[i][j] k[j][t] / sqrt dh
-  const void* k0 = dtype == 1 ? (const void*)(reinterpret_cast<const bf16_t*>(qkv) + d) : (const void*)(reinterpret_cast<const float*>(qkv) + d);
-  e = launch_bw_gemm_batched(dS, (int64_t)seq, 1, dtype, k0, ld, 1, dqkv, ld, seq, dh, seq, scale, 0, heads, BatchOffsets{n_head, p_outer, tt, sq_outer, dh, sq_outer, dh}, s);
-  if (e != hipSuccess) return e;
-  // dK [j][t] = sum_i dS[i][j] q[i][t] / sqrt dh,  dV [j][t] = sum_i P[i][j] dctx[i][t]
-  e = launch_bw_gemm_batched(dS, 1, (int64_t)seq, dtype, qkv, ld, 1, dqkv + d, ld, seq, dh, seq, scale, 0, heads, BatchOffsets{n_head, p_outer, tt, sq_outer, dh, sq_outer, dh}, s);
-  if (e != hipSuccess) return e;
-  return launch_bw_gemm_batched(P, 1, (int64_t)seq, 0, dctx, (int64_t)d, 1, dqkv + 2 * d, ld, seq, dh, seq, 1.0f, 0, heads, BatchOffsets{n_head, p_outer, tt, dc_outer, dh, sq_outer, dh}, s);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  // dQ [i][t] = sum_j dS[i][j] k[j][t] / sqrt dh,  dK [j][t] = sum_i dS[i][j] q[i][t] / sqrt dh,  dV [j][t] = sum_i P[i][j] dctx[i][t]
+  if ((e = product(dS, 0, true, seq, p_outer, tt, k0, dtype, false, ld, sq_outer, dh, dqkv, ld, sq_outer, dh, dh, seq, scale)) != hipSuccess) return e;
+  if ((e = product(dS, 0, false, seq, p_outer, tt, q0, dtype, false, ld, sq_outer, dh, dqkv + d, ld, sq_outer, dh, dh, seq, scale)) != hipSuccess) return e;
+  return product(P, 0, false, seq, p_outer, tt, dctx, 0, false, d, dc_outer, dh, dqkv + 2 * d, ld, sq_outer, dh, dh, seq, 1.0f);
 }
 
 hipError_t launch_bw_embedding(const int32_t* tok, const float* dx, int M, int seq, int d, int vocab, float* dE, float* dPe, int max_pos, hipStream_t s) {

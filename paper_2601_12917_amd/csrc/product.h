@@ -1,0 +1,24 @@
+// Matrix products with fp32 accumulation on operands as they lie in memory (product.hip): the fp32 and the
+// odd-sized products of the cloud's backward pass.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+namespace zgr {
+
+// C[i][j] = alpha sum_k A[i][k] B[k][j] for every batch z: operand X of batch z starts at X + (z / zdiv) x_outer + (z % zdiv) x_inner elements.
+// An operand is fp32 or bf16 (dtype 0 / 1) and contiguous along k or along its other index; ld is the stride of the one that is not.
+struct ProductArgs {
+  const void* A = nullptr; int a_dtype = 0; bool a_k = true; int64_t lda = 0;       // a_k: A[i][k] at A + i lda + k, else A + k lda + i
+  const void* B = nullptr; int b_dtype = 0; bool b_k = true; int64_t ldb = 0;       // b_k: B[k][j] at B + j ldb + k, else B + k ldb + j
+  float* C = nullptr; int64_t ldc = 0;
+  int M = 0, N = 0, K = 0;
+  float alpha = 1.0f;
+  float* a_sums = nullptr;          // when not NULL: a_sums[i] = sum_k A[i][k] (fp32 A contiguous along i, one batch)
+  int batches = 1, zdiv = 1;
+  int64_t a_outer = 0, a_inner = 0, b_outer = 0, b_inner = 0, c_outer = 0, c_inner = 0;
+  float* scratch = nullptr; size_t scratch_floats = 0;    // for the parts of a split sum; without it sums are split inside workgroups only
+};
+hipError_t launch_product(const ProductArgs& p, hipStream_t s);
+
+}  // namespace zgr

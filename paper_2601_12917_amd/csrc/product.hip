@@ -1,0 +1,330 @@
+// C = alpha A B with fp32 products and sums on the matrix cores (v_mfma_f32_16x16x4_f32), for operands as they lie: fp32 or bf16,
+// contiguous along the summed index or along the other one, any sizes.  These are the backward products of fp32 models and of
+// bf16 models whose token count is no multiple of 64, and the five products per head of the attention rule.
+//
+// A wave owns a 64 x 64 piece of C and loads its operands from global memory straight into the instruction's layout: lane
+// (i = lane % 16, kg = lane / 16) supplies element i of the free index and kg of the summed one.  A step takes 16 terms,
+// k = k0 + 4 kg + s in instruction s.  An operand that is contiguous along k gives a lane four terms of one row per load (tile t: rows
+// 16 t + i); one that is contiguous along its other index gives it four rows of one term (tile t: rows 4 i + t).  So every load
+// is four elements wide whichever way the operand lies, and nothing passes through LDS but the partial sums of waves that
+// share a piece.
+// What bounds it is the fp32 matrix rate (157 TFLOP/s): 64 instructions of 32 cycles per step against 8 loads.  The loop holds nothing
+// else: addresses are a scalar base plus a lane offset that stays the same (a vector instruction would queue behind the matrix
+// instructions of the SIMD's other waves).  The LDS-tiled vector kernel this replaces reached 5 TFLOP/s on 231 tokens of a
+// 1024-wide model, where its grid left most of the chip idle (54 of the pass's 60 ms; the whole pass now takes 10).
+#include "product.h"
+
+namespace zgr {
+
+namespace {
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+struct bf16_t { uint16_t bits; };
+
+__device__ __forceinline__ float to_f32(float x) { return x; }
+__device__ __forceinline__ float to_f32(bf16_t x) { return __uint_as_float((uint32_t)x.bits << 16); }
+
+__device__ __forceinline__ int uniform(int v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_readfirstlane(v);
+#else
+  return v;
+#endif
+}
+// nothing is scheduled across this point
+__device__ __forceinline__ void in_this_order() {
+#if defined(__HIP_DEVICE_COMPILE__)
+  __builtin_amdgcn_sched_barrier(0);
+#endif
+}
+
+// Four consecutive elements `byte` bytes (< 2^32) past a scalar base, as loaded; widened when they are used.
+template <typename T> struct Raw4;
+template <> struct Raw4<float> {
+  f32x4 v;
+  __device__ __forceinline__ void load(const float* base, uint32_t byte) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, 0xFFFFFFFFu, 0x00020000);
+    v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, byte, 0, 0));
+#endif
+  }
+  __device__ __forceinline__ f32x4 widen() const { return v; }
+};
+template <> struct Raw4<bf16_t> {
+  u32x2 v;
+  __device__ __forceinline__ void load(const bf16_t* base, uint32_t byte) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(base), 0, 0xFFFFFFFFu, 0x00020000);
+    v = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(rs, byte, 0, 0));
+#endif
+  }
+  __device__ __forceinline__ f32x4 widen() const {
+    return f32x4{__uint_as_float(v[0] << 16), __uint_as_float(v[0] & 0xFFFF0000u), __uint_as_float(v[1] << 16), __uint_as_float(v[1] & 0xFFFF0000u)};
+  }
+};
+
+constexpr int kTile = 64, kStep = 16, kWaves = 2048;
+struct Yes { static constexpr bool value = true; };
+struct No { static constexpr bool value = false; };
+
+struct KernelArgs {
+  const void* A; const void* B; float* C; float* a_sums;
+  int64_t lda, ldb, ldc;
+  int M, N, K;
+  float alpha;
+  int split;                 // waves that share a piece of C, each taking every split-th step: 1 (a block is 2 x 2 pieces), 4 or 8 (one piece)
+  int k_part;                // terms of one part of the sum: part z writes its result at C + z c_part (a_sums + z M), batches = 1
+  int64_t c_part;
+  int batched, zdiv;
+  int64_t a_outer, a_inner, b_outer, b_inner, c_outer, c_inner;
+};
+
+// NEAR: the byte offsets of a step fit 32 bits, an operand contiguous along its free index has at least four entries of it, and bf16
+// operands lie on 4 bytes; the other form loads element by element.
+template <typename TA, typename TB, bool AK, bool BK, bool NEAR>
+__global__ void __launch_bounds__(512, 2) product_kernel(KernelArgs p) {
+  extern __shared__ __attribute__((aligned(16))) float lds[];
+  const int lane = threadIdx.x & 63, wave = uniform((int)threadIdx.x >> 6), il = lane & 15, kg = lane >> 4;
+  const TA* A = reinterpret_cast<const TA*>(p.A);
+  const TB* B = reinterpret_cast<const TB*>(p.B);
+  float* C = p.C;
+  int k_begin = 0, k_end = p.K;
+  if (p.batched) {
+    const int zo = uniform((int)blockIdx.z / p.zdiv), zi = (int)blockIdx.z - zo * p.zdiv;
+    A += zo * p.a_outer + zi * p.a_inner;
+    B += zo * p.b_outer + zi * p.b_inner;
+    C += zo * p.c_outer + zi * p.c_inner;
+  } else {
+    k_begin = (int)blockIdx.z * p.k_part;
+    k_end = p.K < k_begin + p.k_part ? p.K : k_begin + p.k_part;
+    C += blockIdx.z * p.c_part;
+  }
+  const bool alone = p.split == 1;
+  const int tm = alone ? (int)blockIdx.y * 2 + (wave >> 1) : (int)blockIdx.y, tn = alone ? (int)blockIdx.x * 2 + (wave & 1) : (int)blockIdx.x;
+  const int i0 = tm * kTile, j0 = tn * kTile;
+  if (alone && (i0 >= p.M || j0 >= p.N)) return;                 // no barrier follows for such a block
+  const int share = alone ? 0 : wave;
+  // Rows past the end: an operand contiguous along k repeats its last row, the other kind takes its last four entries instead;
+  // what comes of them is not stored.
+  auto first_i = [&](int q) { const int i = i0 + 4 * q; return NEAR && i > p.M - 4 ? p.M - 4 : i; };
+  auto first_j = [&](int q) { const int j = j0 + 4 * q; return NEAR && j > p.N - 4 ? p.N - 4 : j; };
+  auto row_i = [&](int t, int q) { const int i = AK ? i0 + 16 * t + q : first_i(q) + t; return i < p.M ? i : p.M - 1; };
+  auto row_j = [&](int t, int q) { const int j = BK ? j0 + 16 * t + q : first_j(q) + t; return j < p.N ? j : p.N - 1; };
+  uint32_t ao[4], bo[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    ao[t] = (uint32_t)sizeof(TA) * (AK ? (uint32_t)(row_i(t, il) - i0) * (uint32_t)p.lda + 4u * kg : (uint32_t)(4 * kg + t) * (uint32_t)p.lda + (uint32_t)first_i(il));
+    bo[t] = (uint32_t)sizeof(TB) * (BK ? (uint32_t)(row_j(t, il) - j0) * (uint32_t)p.ldb + 4u * kg : (uint32_t)(4 * kg + t) * (uint32_t)p.ldb + (uint32_t)first_j(il));
+  }
+  const TA* a_base = AK ? A + (int64_t)i0 * p.lda : A;
+  const TB* b_base = BK ? B + (int64_t)j0 * p.ldb : B;
+  auto a_at = [&](int i, int k) { return to_f32(AK ? A[(int64_t)i * p.lda + k] : A[(int64_t)k * p.lda + i]); };
+  auto b_at = [&](int j, int k) { return to_f32(BK ? B[(int64_t)j * p.ldb + k] : B[(int64_t)k * p.ldb + j]); };
+  f32x4 acc[4][4], sums[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    sums[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int n = 0; n < 4; ++n) acc[t][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  struct Operands { Raw4<TA> a[4]; Raw4<TB> b[4]; };
+  auto fetch = [&](int k0, Operands& o) {
+    if constexpr (NEAR) {
+      const TA* ak = a_base + (AK ? (int64_t)k0 : k0 * p.lda);
+      const TB* bk = b_base + (BK ? (int64_t)k0 : k0 * p.ldb);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) { o.a[t].load(ak, ao[t]); o.b[t].load(bk, bo[t]); }
+    }
+  };
+  // x[t] holds what load t brought: tile t, terms s (contiguous along k) or term t, tiles s
+  auto multiply4 = [&](const f32x4 (&a)[4], const f32x4 (&b)[4], auto with_sums) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const float av = AK ? a[t][s] : a[s][t];
+#pragma unroll
+        for (int n = 0; n < 4; ++n) acc[t][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, BK ? b[n][s] : b[s][n], acc[t][n], 0, 0, 0);
+        if (decltype(with_sums)::value) sums[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, 1.0f, sums[t], 0, 0, 0);
+      }
+  };
+  auto loop = [&](auto with_sums) {
+    auto multiply = [&](const Operands& o) {
+      const f32x4 a[4] = {o.a[0].widen(), o.a[1].widen(), o.a[2].widen(), o.a[3].widen()};
+      const f32x4 b[4] = {o.b[0].widen(), o.b[1].widen(), o.b[2].widen(), o.b[3].widen()};
+      multiply4(a, b, with_sums);
+    };
+    const int stride = p.split * kStep, full = k_begin + (k_end - k_begin) / kStep * kStep;
+    int k0 = k_begin + share * kStep;
+    const int steps = NEAR ? uniform(k0 < full ? (full - k0 + stride - 1) / stride : 0) : 0;
+    if (steps > 0) {
+      Operands o0, o1;
+      auto step = [&](int i) { return k0 + (i < steps ? i : steps - 1) * stride; };      // behind the last step it is read again
+      int i = 0;
+      if (steps & 1) { fetch(k0, o0); multiply(o0); i = 1; }
+      fetch(step(i), o0);
+      for (; i < steps; i += 2) {
+        fetch(step(i + 1), o1);
+        in_this_order();
+        multiply(o0);
+        in_this_order();
+        fetch(step(i + 2), o0);
+        in_this_order();
+        multiply(o1);
+        in_this_order();
+      }
+      k0 += steps * stride;
+    }
+    // the terms left over (the wave whose turn it is; every step in the element-by-element form): zeros past the end
+    for (; k0 < k_end; k0 += stride) {
+      f32x4 a[4], b[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const int ka = k0 + 4 * kg + (AK ? s : t), kb = k0 + 4 * kg + (BK ? s : t);
+          a[t][s] = ka < k_end ? a_at(row_i(AK ? t : s, il), ka) : 0.f;
+          b[t][s] = kb < k_end ? b_at(row_j(BK ? t : s, il), kb) : 0.f;
+        }
+      multiply4(a, b, with_sums);
+    }
+  };
+  const bool want_sums = !AK && p.a_sums && tn == 0;
+  if constexpr (!AK) { if (want_sums) loop(Yes{}); else loop(No{}); }
+  else loop(No{});
+  // waves that share the piece add up in a fixed order (8: 0+4, 1+5, 2+6, 3+7; then 0+2, 1+3; then 0+1)
+  if (!alone) {
+    for (int half = p.split >> 1; half >= 1; half >>= 1) {
+      __syncthreads();
+      if (wave >= half && wave < 2 * half)
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+          for (int n = 0; n < 4; ++n) *reinterpret_cast<f32x4*>(lds + (((wave - half) * 16 + t * 4 + n) * 64 + lane) * 4) = acc[t][n];
+      __syncthreads();
+      if (wave < half)
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+          for (int n = 0; n < 4; ++n) acc[t][n] += *reinterpret_cast<const f32x4*>(lds + ((wave * 16 + t * 4 + n) * 64 + lane) * 4);
+      if (want_sums) {                                           // uniform over the block
+        __syncthreads();
+        if (wave >= half && wave < 2 * half)
+#pragma unroll
+          for (int t = 0; t < 4; ++t) *reinterpret_cast<f32x4*>(lds + (((wave - half) * 4 + t) * 64 + lane) * 4) = sums[t];
+        __syncthreads();
+        if (wave < half)
+#pragma unroll
+          for (int t = 0; t < 4; ++t) sums[t] += *reinterpret_cast<const f32x4*>(lds + ((wave * 4 + t) * 64 + lane) * 4);
+      }
+    }
+    if (wave != 0) return;
+  }
+  // lane (il, kg) holds column il of a tile and its rows 4 kg + v.  A lane that took entries before its own stores its own only.
+  const float alpha = p.alpha;
+  if (want_sums && il == 0)
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int i = first_i(4 * kg + v) + t;
+        if (i >= i0 + 4 * (4 * kg + v) && i < p.M) p.a_sums[(int64_t)blockIdx.z * p.M + i] = sums[t][v];
+      }
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int i = AK ? i0 + 16 * t + 4 * kg + v : first_i(4 * kg + v) + t;
+      if (i >= p.M || (!AK && i < i0 + 4 * (4 * kg + v))) continue;
+      float* row = C + (int64_t)i * p.ldc;
+#pragma unroll
+      for (int n = 0; n < 4; ++n) {
+        const int j = BK ? j0 + 16 * n + il : first_j(il) + n;
+        if (j < p.N && (BK || j >= j0 + 4 * il)) row[j] = alpha * acc[t][n][v];
+      }
+    }
+}
+
+// C[i][j] = alpha (part 0 + part 1 + ...)[i][j], a_sums likewise without alpha: the parts in their order
+__global__ void __launch_bounds__(256) product_sum_kernel(const float* __restrict__ part, int parts, int64_t n, int N, float* __restrict__ C, int64_t ldc, float alpha,
+                                                          const float* __restrict__ sum_part, int M, float* __restrict__ a_sums) {
+  for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < n + (a_sums ? M : 0); e += (int64_t)gridDim.x * 256) {
+    const float* src = e < n ? part + e : sum_part + (e - n);
+    const int64_t stride = e < n ? n : M;
+    float v = 0.f;
+#pragma unroll 4
+    for (int z = 0; z < parts; ++z) v += src[(int64_t)z * stride];
+    if (e < n) C[e / N * ldc + e % N] = alpha * v; else a_sums[e - n] = v;
+  }
+}
+
+template <typename TA, typename TB, bool AK, bool BK>
+hipError_t launch_t(const KernelArgs& k, bool near, dim3 grid, hipStream_t s) {
+  const unsigned threads = k.split == 8 ? 512 : 256;
+  const size_t lds = k.split == 1 ? 0 : (size_t)(k.split / 2) * 16 * 64 * 16;       // 64 KB at most
+  if (near) hipLaunchKernelGGL((product_kernel<TA, TB, AK, BK, true>), grid, dim3(threads), lds, s, k);
+  else      hipLaunchKernelGGL((product_kernel<TA, TB, AK, BK, false>), grid, dim3(threads), lds, s, k);
+  return hipGetLastError();
+}
+
+// Whether an operand's step can be loaded four elements wide with 32-bit offsets (see product_kernel).
+bool near_operand(const void* p, int dtype, bool along_k, int64_t ld, int n, int64_t outer, int64_t inner) {
+  const int64_t es = dtype == 1 ? 2 : 4;
+  if ((along_k ? 64 : 16) * ld * es + (along_k ? 64 : (int64_t)n * es) >= ((int64_t)1 << 32)) return false;
+  if (!along_k && n < 4) return false;
+  if (dtype == 1 && (((uintptr_t)p & 3) || (ld & 1) || (outer & 1) || (inner & 1) || (!along_k && (n & 1)))) return false;
+  return true;
+}
+
+}  // namespace
+
+hipError_t launch_product(const ProductArgs& p, hipStream_t s) {
+  if (p.M < 1 || p.N < 1 || p.batches < 1) return hipSuccess;
+  if (p.K < 0 || p.batches > 65535 || p.zdiv < 1 || (p.a_sums && (p.a_k || p.a_dtype != 0 || p.batches != 1))) return hipErrorInvalidValue;
+  const int64_t tm = ((int64_t)p.M + kTile - 1) / kTile, tn = ((int64_t)p.N + kTile - 1) / kTile, pieces = tm * tn * p.batches;
+  if (tm > 65535) return hipErrorInvalidValue;
+  const int steps = (p.K + kStep - 1) / kStep;
+  // Two waves per SIMD hide each other's loads (one: 10.35 ms for the backward pass of a 24-block, 1024-wide encoder on 231 tokens, two:
+  // 10.06).  Fewer pieces than that: four or eight waves share each, and
+  // where that still leaves SIMDs empty the sum is also split over blocks, each share at least eight steps.
+  const int split = pieces >= kWaves || steps < 4 ? 1 : (pieces * 4 >= kWaves || steps < 32 ? 4 : 8);
+  int parts = 1;
+  if (p.batches == 1 && p.scratch) {
+    int64_t z = kWaves / (pieces * split);
+    const int64_t room = (int64_t)(p.scratch_floats / ((size_t)p.M * ((size_t)p.N + 1)));
+    if (z > steps / (8 * split)) z = steps / (8 * split);
+    if (z > room) z = room;
+    if (z > 1) parts = (int)z;
+  }
+  KernelArgs k{};
+  k.A = p.A; k.B = p.B; k.lda = p.lda; k.ldb = p.ldb; k.M = p.M; k.N = p.N; k.K = p.K; k.split = split;
+  k.batched = p.batches > 1; k.zdiv = p.zdiv;
+  k.a_outer = p.a_outer; k.a_inner = p.a_inner; k.b_outer = p.b_outer; k.b_inner = p.b_inner; k.c_outer = p.c_outer; k.c_inner = p.c_inner;
+  k.k_part = (steps + parts - 1) / parts * kStep;
+  if (k.k_part < 1) k.k_part = 1;
+  const int64_t n = (int64_t)p.M * p.N;
+  float* sum_part = p.scratch + (int64_t)parts * n;
+  if (parts > 1) { k.C = p.scratch; k.ldc = p.N; k.alpha = 1.0f; k.c_part = n; k.a_sums = p.a_sums ? sum_part : nullptr; }
+  else           { k.C = p.C; k.ldc = p.ldc; k.alpha = p.alpha; k.a_sums = p.a_sums; }
+  const bool near = near_operand(p.A, p.a_dtype, p.a_k, p.lda, p.M, p.a_outer, p.a_inner) && near_operand(p.B, p.b_dtype, p.b_k, p.ldb, p.N, p.b_outer, p.b_inner);
+  const dim3 grid((unsigned)(split == 1 ? (tn + 1) / 2 : tn), (unsigned)(split == 1 ? (tm + 1) / 2 : tm), (unsigned)(p.batches > 1 ? p.batches : parts));
+  hipError_t e = hipErrorInvalidValue;
+  const int form = (p.a_dtype << 3) | (p.b_dtype << 2) | ((p.a_k ? 1 : 0) << 1) | (p.b_k ? 1 : 0);
+  switch (form) {
+    case 0b0010: e = launch_t<float, float, true, false>(k, near, grid, s); break;
+    case 0b0110: e = launch_t<float, bf16_t, true, false>(k, near, grid, s); break;
+    case 0b0000: e = launch_t<float, float, false, false>(k, near, grid, s); break;
+    case 0b0100: e = launch_t<float, bf16_t, false, false>(k, near, grid, s); break;
+    case 0b0011: e = launch_t<float, float, true, true>(k, near, grid, s); break;
+    case 0b0111: e = launch_t<float, bf16_t, true, true>(k, near, grid, s); break;
+    case 0b1111: e = launch_t<bf16_t, bf16_t, true, true>(k, near, grid, s); break;
+    default: break;
+  }
+  if (e != hipSuccess || parts == 1) return e;
+  const int64_t total = n + (p.a_sums ? p.M : 0);
+  hipLaunchKernelGGL(product_sum_kernel, dim3((unsigned)(total / 256 + 1 < 2048 ? total / 256 + 1 : 2048)), dim3(256), 0, s, p.scratch, parts, n, p.N, p.C, p.ldc, p.alpha, sum_part, p.M, p.a_sums);
+  return hipGetLastError();
+}
+
+}  // namespace zgr

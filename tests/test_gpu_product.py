@@ -1,0 +1,51 @@
+"""The fp32 products of the cloud's backward pass (zgr_debug_product) against fp64 on the same values: every layout and storage
+type the pass uses, sizes at the edges of the 64 x 64 pieces and the 16-term steps, sums shared by one, four and eight waves and split
+over blocks, and the element-by-element form (fewer than four columns, odd bf16 row strides).
+
+A result is a sum of K products rounded to fp32 as it grows: |error| <= (K + parts) 2^-24 sum_k |a||b|, and in practice a
+random walk, so the bound asked for is 4 sqrt(K + 16) 2^-24 of that sum of magnitudes."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+# (a dtype, a along k, b dtype, b along k)
+FORMS = [("f32", 1, "f32", 0), ("f32", 1, "bf16", 0), ("f32", 0, "f32", 0), ("f32", 0, "bf16", 0), ("f32", 1, "f32", 1), ("f32", 1, "bf16", 1), ("bf16", 1, "bf16", 1)]
+#        M     N    K  batches pad
+SIZES = [(1, 1, 1, 1, 0), (3, 2, 5, 3, 0), (4, 4, 16, 2, 4), (63, 65, 17, 1, 1), (64, 64, 64, 5, 0), (65, 130, 15, 2, 2), (130, 66, 1040, 1, 0), (77, 100, 4100, 1, 4), (2100, 2050, 40, 1, 6)]
+
+
+@pytest.mark.parametrize("form", FORMS, ids=lambda f: f"{f[0]}{'k' if f[1] else 'i'}-{f[2]}{'k' if f[3] else 'j'}")
+@pytest.mark.parametrize("M,N,K,batches,pad", SIZES)
+def test_product_matches_fp64(form, M, N, K, batches, pad):
+    import torch
+    from paper_2601_12917_amd import binding as B
+    a_t, a_k, b_t, b_k = form
+    dev = "cuda:0"
+    gen = torch.Generator().manual_seed(M * 131 + N * 17 + K + 7 * a_k + b_k)
+
+    def operand(rows, cols, t):                            # [batches, rows, cols + pad], the padding set to what must not be used
+        x = torch.randn(batches, rows, cols + pad, generator=gen).to(torch.bfloat16 if t == "bf16" else torch.float32)
+        x[:, :, cols:] = float("nan")
+        return x.to(dev)
+    A = operand(*((M, K) if a_k else (K, M)), a_t)
+    Bm = operand(*((N, K) if b_k else (K, N)), b_t)
+    ldc = N + pad
+    out = torch.full((batches, M, ldc), 7.0, device=dev)
+    sums = torch.full((M,), 7.0, device=dev) if not a_k and batches == 1 else None
+    scratch = torch.full((1 << 20,), float("nan"), device=dev)
+    ad = A[:, :, :K if a_k else M].double()
+    bd = Bm[:, :, :K if b_k else N].double()
+    ad, bd = (ad if a_k else ad.transpose(1, 2)).cpu(), (bd.transpose(1, 2) if b_k else bd).cpu()
+    want, mag = -0.5 * torch.stack([x @ y for x, y in zip(ad, bd)]), 0.5 * torch.stack([x.abs() @ y.abs() for x, y in zip(ad, bd)])
+    for use_scratch in (True, False):
+        B.check(B.lib().zgr_debug_product(A.data_ptr(), int(a_t == "bf16"), a_k, A.shape[2], A[0].numel(), Bm.data_ptr(), int(b_t == "bf16"), b_k, Bm.shape[2], Bm[0].numel(),
+                                          out.data_ptr(), ldc, M * ldc, M, N, K, -0.5, batches, sums.data_ptr() if sums is not None else None,
+                                          scratch.data_ptr() if use_scratch else None, scratch.numel() if use_scratch else 0, torch.cuda.current_stream().cuda_stream))
+        torch.cuda.synchronize()
+        got = out.double().cpu()
+        assert torch.all(got[:, :, N:] == 7.0)             # nothing written past a row
+        bound = 4 * np.sqrt(K + 16) * 2.0 ** -24
+        assert torch.all((got[:, :, :N] - want).abs() <= bound * mag), float(((got[:, :, :N] - want).abs() / mag).max() / bound)
+        if sums is not None:
+            assert torch.all((sums.double().cpu() - ad[0].sum(1)).abs() <= bound * ad[0].abs().sum(1))
