@@ -932,7 +932,7 @@ BwCarve bw_carve(const zgr_ctx* c, int batch, int seq) {
   v.P = take((size_t)batch * m.n_head * seq * seq * 4);
   v.dS = take((size_t)batch * m.n_head * seq * seq * 4);
   v.stats = take(M * 2 * 4);
-  v.part = take(4 * bw_colsum_scratch_floats((int)std::max(std::max(ff, 3 * d), (size_t)m.n_class)));
+  v.part = take(4 * bw_scratch_floats((int)d, (int)std::max(std::max(ff, 3 * d), (size_t)m.n_class)));
   v.split = take(kProductScratch * 4);
   v.mfma = c->dtype == ZGR_BF16 && M % 64 == 0;
   if (v.mfma) {

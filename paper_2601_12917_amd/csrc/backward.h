@@ -6,19 +6,20 @@
 
 namespace zgr {
 
-constexpr int kBackwardMaxSeq = 2048;      // keys one workgroup of the attention rule holds
+constexpr int kBackwardMaxSeq = 2048;      // keys one wave of the attention rule holds
 
 // bf16 operands for the matrix-core products: out [cols, rows] (row stride ld_out) = in [rows, cols]^T, in fp32 or bf16
 // (row stride ld_in); out [rows, cols] (row stride ld_out) = in rounded.  What lies between the data and ld_out is written as zeros.
 hipError_t launch_bw_transpose_bf16(int in_dtype, const void* in, int rows, int cols, int64_t ld_in, void* out, int64_t ld_out, hipStream_t s);
 hipError_t launch_bw_round_bf16(const float* in, int rows, int cols, int64_t ld_in, void* out, int64_t ld_out, hipStream_t s);
-// out[n] = sum_m Y[m ld + n]; part: scratch of bw_colsum_scratch_floats(N) floats
-size_t     bw_colsum_scratch_floats(int n_max);
+// `part` of the column sums and of the LayerNorm rule: scratch of bw_scratch_floats(d, widest N) floats
+size_t     bw_scratch_floats(int d, int n_widest);
+// out[n] = sum_m Y[m ld + n]
 hipError_t launch_bw_colsum(const float* Y, int M, int N, int64_t ld, float* out, float* part, hipStream_t s);
 hipError_t launch_bw_fill(float* p, int64_t n, float v, hipStream_t s);
 // logits [rows, n] -> (softmax - onehot(target)) inv_count in place; rows with a target outside [0, n) become zeros
 hipError_t launch_bw_cross_entropy(float* logits, const int32_t* targets, int rows, int n, float inv_count, hipStream_t s);
-// y = LayerNorm(x) g + b: dx_out = (add ? add : 0) + dL/dx (dx_out may be add or dy), dg, db from dy; stats: 2 M floats of scratch, part: bw_colsum_scratch_floats(d)
+// y = LayerNorm(x) g + b: dx_out = (add ? add : 0) + dL/dx (dx_out may be add or dy), dg, db from dy; stats: 2 M floats of scratch
 hipError_t launch_bw_layernorm(int dtype, const float* x, const void* g, const float* dy, const float* add, float* dx_out, float* stats, float* dg, float* db,
                                float* part, int M, int d, float eps, hipStream_t s);
 // f = act(u) in the storage type (erf-GELU, or ReLU when relu != 0); df <- df act'(u); dst += src

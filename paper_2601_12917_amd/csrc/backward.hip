@@ -92,12 +92,26 @@ __global__ void __launch_bounds__(256) colsum_partial_kernel(const float* __rest
   __syncthreads();
   if (g == 0 && c < N) part[(size_t)blockIdx.y * N + c] = (acc[0][threadIdx.x] + acc[1][threadIdx.x]) + (acc[2][threadIdx.x] + acc[3][threadIdx.x]);
 }
-__global__ void __launch_bounds__(256) colsum_final_kernel(const float* __restrict__ part, int N, float* __restrict__ out) {
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  if (c >= N) return;
+// The second stage for up to two sums of n columns: out[c] = part[0][c] + part[1][c] + ..., blockIdx.y choosing (part, out).  32 columns per
+// block, eight threads to a column: each adds an eighth of the parts in order, then the eighths are added in order.
+__global__ void __launch_bounds__(256) colsum_final_kernel(const float* __restrict__ part0, float* __restrict__ out0, const float* __restrict__ part1, float* __restrict__ out1,
+                                                           int parts, int64_t stride, int n) {
+  __shared__ float sums[8][32];
+  const float* part = blockIdx.y ? part1 : part0;
+  float* out = blockIdx.y ? out1 : out0;
+  const int c = blockIdx.x * 32 + (threadIdx.x & 31), q = threadIdx.x >> 5, per = (parts + 7) / 8;
   float s = 0.f;
-  for (int p = 0; p < kColParts; ++p) s += part[(size_t)p * N + c];
-  out[c] = s;
+  if (c < n) {
+    const int end = parts < (q + 1) * per ? parts : (q + 1) * per;
+#pragma unroll 8
+    for (int p = q * per; p < end; ++p) s += part[p * stride + c];
+  }
+  sums[q][threadIdx.x & 31] = s;
+  __syncthreads();
+  if (q == 0 && c < n) {
+    for (int i = 1; i < 8; ++i) s += sums[i][threadIdx.x];
+    out[c] = s;
+  }
 }
 
 __global__ void __launch_bounds__(256) fill_kernel(float* __restrict__ p, int64_t n, float v) {
@@ -156,6 +170,79 @@ __global__ void __launch_bounds__(256) ln_backward_kernel(const float* __restric
   }
 }
 
+// The same rule and the parameter gradients in one pass over x and dy, for d % 4 == 0 and d <= 256 MAXV: a wave takes rows in turn, the
+// row in registers (one read of x and dy, no barrier), and keeps its rows' share of dg[c] = sum_m dy[m][c] xhat[m][c] and
+// db[c] = sum_m dy[m][c] in registers too.  part[b][0 | 1][c]: the block's sums, its four waves added in order.  Bound by launch and
+// load latency at a few thousand rows: with a kernel each for the row statistics, the partial sums and the two final sums the rule
+// took five launches and three reads (27 us per LayerNorm of 2048 x 768, now 13).
+template <typename T, int MAXV>
+__global__ void __launch_bounds__(256) ln_backward_wave_kernel(const float* __restrict__ x, const T* __restrict__ g, const float* dy, const float* add, float* dx_out,
+                                                               float* __restrict__ part, int M, int d, float eps) {            // add or dy may be dx_out
+  __shared__ __attribute__((aligned(16))) float red[4][256 * MAXV];
+  struct alignas(sizeof(T) * 4) V4 { T e[4]; };
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nv = d >> 2;
+  float4 gain[MAXV], sg[MAXV], sb[MAXV];
+#pragma unroll
+  for (int j = 0; j < MAXV; ++j) {
+    const int i = lane + 64 * j;
+    sg[j] = sb[j] = gain[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (i < nv) { const V4 t = *reinterpret_cast<const V4*>(g + 4 * i); gain[j] = make_float4(to_f32(t.e[0]), to_f32(t.e[1]), to_f32(t.e[2]), to_f32(t.e[3])); }
+  }
+  for (int row = blockIdx.x * 4 + wave; row < M; row += gridDim.x * 4) {
+    const float4* xr = reinterpret_cast<const float4*>(x + (size_t)row * d);
+    const float4* dr = reinterpret_cast<const float4*>(dy + (size_t)row * d);
+    float4 v[MAXV], w[MAXV];
+    float s = 0.f;
+#pragma unroll
+    for (int j = 0; j < MAXV; ++j) {
+      const int i = lane + 64 * j;
+      v[j] = w[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (i < nv) { v[j] = xr[i]; w[j] = dr[i]; }
+      s += (v[j].x + v[j].y) + (v[j].z + v[j].w);
+    }
+    const float mu = wave_sum(s) / d;
+    float q = 0.f;
+#pragma unroll
+    for (int j = 0; j < MAXV; ++j)
+      if (lane + 64 * j < nv) {
+        v[j].x -= mu; v[j].y -= mu; v[j].z -= mu; v[j].w -= mu;
+        q += (v[j].x * v[j].x + v[j].y * v[j].y) + (v[j].z * v[j].z + v[j].w * v[j].w);
+      }
+    const float rstd = 1.0f / sqrtf(wave_sum(q) / d + eps);
+    float s1 = 0.f, s2 = 0.f;
+#pragma unroll
+    for (int j = 0; j < MAXV; ++j) {
+      v[j].x *= rstd; v[j].y *= rstd; v[j].z *= rstd; v[j].w *= rstd;                  // xhat; zeros past the row's end
+      sg[j].x += w[j].x * v[j].x; sg[j].y += w[j].y * v[j].y; sg[j].z += w[j].z * v[j].z; sg[j].w += w[j].w * v[j].w;
+      sb[j].x += w[j].x; sb[j].y += w[j].y; sb[j].z += w[j].z; sb[j].w += w[j].w;
+      w[j].x *= gain[j].x; w[j].y *= gain[j].y; w[j].z *= gain[j].z; w[j].w *= gain[j].w;
+      s1 += (w[j].x + w[j].y) + (w[j].z + w[j].w);
+      s2 += (w[j].x * v[j].x + w[j].y * v[j].y) + (w[j].z * v[j].z + w[j].w * v[j].w);
+    }
+    s1 = wave_sum(s1) / d;
+    s2 = wave_sum(s2) / d;
+    const float4* ar = add ? reinterpret_cast<const float4*>(add + (size_t)row * d) : nullptr;
+    float4* out = reinterpret_cast<float4*>(dx_out + (size_t)row * d);
+#pragma unroll
+    for (int j = 0; j < MAXV; ++j) {
+      const int i = lane + 64 * j;
+      if (i < nv) {
+        float4 r = make_float4(rstd * (w[j].x - s1 - v[j].x * s2), rstd * (w[j].y - s1 - v[j].y * s2), rstd * (w[j].z - s1 - v[j].z * s2), rstd * (w[j].w - s1 - v[j].w * s2));
+        if (ar) { const float4 t = ar[i]; r.x += t.x; r.y += t.y; r.z += t.z; r.w += t.w; }
+        out[i] = r;
+      }
+    }
+  }
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < MAXV; ++j) *reinterpret_cast<float4*>(&red[wave][4 * (lane + 64 * j)]) = h ? sb[j] : sg[j];
+    __syncthreads();
+    for (int c = threadIdx.x; c < d; c += 256) part[((size_t)blockIdx.x * 2 + h) * d + c] = (red[0][c] + red[1][c]) + (red[2][c] + red[3][c]);
+  }
+}
+
 // (mu, rstd) of every row, for the parameter gradients
 __global__ void __launch_bounds__(256) ln_stats_kernel(const float* __restrict__ x, float* __restrict__ stats, int d, float eps) {
   __shared__ float red[4];
@@ -193,23 +280,40 @@ __global__ void __launch_bounds__(256) ln_param_grad_partial_kernel(const float*
 }
 
 // ------------------------------------------------------------------ feed-forward activation: erf-GELU or ReLU
+// Four entries per thread (n4 of them), the last n % 4 by the first threads of the grid.
+template <bool RELU> __device__ __forceinline__ float act_of(float x) { return RELU ? fmaxf(x, 0.f) : 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)); }
+__device__ __forceinline__ float gelu_slope(float x) {
+  const float cdf = 0.5f * (1.0f + erff(x * 0.70710678118654752f));
+  const float pdf = 0.3989422804014327f * expf(-0.5f * x * x);
+  return cdf + x * pdf;
+}
 template <typename T, bool RELU>
 __global__ void __launch_bounds__(256) act_forward_kernel(const float* __restrict__ u, T* __restrict__ f, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-    const float x = u[i];
-    from_f32(RELU ? fmaxf(x, 0.f) : 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)), f[i]);
+  struct alignas(sizeof(T) * 4) V4 { T e[4]; };
+  const int64_t first = (int64_t)blockIdx.x * 256 + threadIdx.x, n4 = n >> 2;
+  for (int64_t i = first; i < n4; i += (int64_t)gridDim.x * 256) {
+    const float4 x = reinterpret_cast<const float4*>(u)[i];
+    V4 r;
+    from_f32(act_of<RELU>(x.x), r.e[0]); from_f32(act_of<RELU>(x.y), r.e[1]); from_f32(act_of<RELU>(x.z), r.e[2]); from_f32(act_of<RELU>(x.w), r.e[3]);
+    reinterpret_cast<V4*>(f)[i] = r;
   }
+  if (first < (n & 3)) from_f32(act_of<RELU>(u[4 * n4 + first]), f[4 * n4 + first]);
 }
-// du = df * act'(u), in place on df: GELU' = Phi(u) + u phi(u), ReLU' = [u > 0]
+// du = df * act'(u), in place on df: GELU' = Phi(u) + u phi(u), ReLU' = [u > 0] (a zero slope gives zero whatever df holds)
+template <bool RELU> __device__ __forceinline__ float act_rule(float x, float df) {
+  if (RELU) return x > 0.f ? df : 0.f;
+  return df * gelu_slope(x);
+}
 template <bool RELU>
 __global__ void __launch_bounds__(256) act_backward_kernel(const float* __restrict__ u, float* __restrict__ df, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-    const float x = u[i];
-    if (RELU) { if (!(x > 0.f)) df[i] = 0.f; continue; }
-    const float cdf = 0.5f * (1.0f + erff(x * 0.70710678118654752f));
-    const float pdf = 0.3989422804014327f * expf(-0.5f * x * x);
-    df[i] *= cdf + x * pdf;
+  const int64_t first = (int64_t)blockIdx.x * 256 + threadIdx.x, n4 = n >> 2;
+  for (int64_t i = first; i < n4; i += (int64_t)gridDim.x * 256) {
+    const float4 x = reinterpret_cast<const float4*>(u)[i];
+    float4 r = reinterpret_cast<float4*>(df)[i];
+    r = make_float4(act_rule<RELU>(x.x, r.x), act_rule<RELU>(x.y, r.y), act_rule<RELU>(x.z, r.z), act_rule<RELU>(x.w, r.w));
+    reinterpret_cast<float4*>(df)[i] = r;
   }
+  if (first < (n & 3)) df[4 * n4 + first] = act_rule<RELU>(u[4 * n4 + first], df[4 * n4 + first]);
 }
 
 __global__ void __launch_bounds__(256) add_kernel(float* __restrict__ dst, const float* __restrict__ src, int64_t n) {
@@ -223,57 +327,107 @@ __global__ void __launch_bounds__(256) add_kernel(float* __restrict__ dst, const
 //   S = Q K^T / sqrt dh and dP = dctx V^T             (into the P and dS buffers)
 //   p = softmax(S) over the visible keys, ds = p (dP - p . dP), zeros at masked keys        (attn_backward_rows_kernel, in place)
 //   dQ = dS K / sqrt dh,   dK = dS^T Q / sqrt dh,   dV = P^T dctx
-// One block per row (b, h, i) of the two [T, T] buffers; a thread holds up to MAXJ of the row's entries (T <= 256 MAXJ).
-__global__ void __launch_bounds__(256) attn_backward_rows_kernel(const int32_t* __restrict__ lengths, int seq, int n_head, int causal,
+// One wave per row (b, h, i) of the two [T, T] buffers, four rows per block; a lane holds up to MAXJ of the row's entries (T <= 64 MAXJ),
+// so the three reductions stay inside the wave.  (One block of 256 threads per row: 40 us for 24576 rows of 128, most of the
+// threads without an entry and six barriers per row.)
+template <int MAXJ>
+__global__ void __launch_bounds__(256) attn_backward_rows_kernel(const int32_t* __restrict__ lengths, int64_t rows, int seq, int n_head, int causal,
                                                                  float* __restrict__ P, float* __restrict__ dS) {
-  __shared__ float red[4];
-  const int i = blockIdx.x % seq, b = blockIdx.x / (seq * n_head);
+  const int lane = threadIdx.x & 63;
+  const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (r >= rows) return;                                             // whole waves leave: no barrier below
+  const int i = (int)(r % seq), b = (int)(r / ((int64_t)seq * n_head));
   int kend = lengths ? lengths[b] : seq;
   kend = kend < seq ? kend : seq;
   if (causal) kend = kend < i + 1 ? kend : i + 1;
-  float* prow = P + (size_t)blockIdx.x * seq;
-  float* srow = dS + (size_t)blockIdx.x * seq;
-  constexpr int MAXJ = kBackwardMaxSeq / 256;
+  float* prow = P + (size_t)r * seq;
+  float* srow = dS + (size_t)r * seq;
   float sc[MAXJ], dp[MAXJ];
   float mx = -INFINITY;
 #pragma unroll
   for (int u = 0; u < MAXJ; ++u) {
-    const int j = threadIdx.x + 256 * u;
+    const int j = lane + 64 * u;
     sc[u] = -INFINITY; dp[u] = 0.f;
     if (j < kend) { sc[u] = prow[j]; dp[u] = srow[j]; mx = fmaxf(mx, sc[u]); }
   }
-  mx = block_max(mx, red);
+  mx = wave_max(mx);
   float den = 0.f;
 #pragma unroll
-  for (int u = 0; u < MAXJ; ++u) { sc[u] = (threadIdx.x + 256 * u < kend) ? expf(sc[u] - mx) : 0.f; den += sc[u]; }
-  den = block_sum(den, red);
+  for (int u = 0; u < MAXJ; ++u) { sc[u] = (lane + 64 * u < kend) ? expf(sc[u] - mx) : 0.f; den += sc[u]; }
+  den = wave_sum(den);
   const float inv = den > 0.f ? 1.0f / den : 0.f;
   float dot = 0.f;
 #pragma unroll
   for (int u = 0; u < MAXJ; ++u) { sc[u] *= inv; dot += sc[u] * dp[u]; }
-  dot = block_sum(dot, red);
+  dot = wave_sum(dot);
 #pragma unroll
   for (int u = 0; u < MAXJ; ++u) {
-    const int j = threadIdx.x + 256 * u;
+    const int j = lane + 64 * u;
     if (j < seq) { prow[j] = sc[u]; srow[j] = sc[u] * (dp[u] - dot); }
   }
 }
 
 // ------------------------------------------------------------------ embeddings
-// x0[m] = E[tok[m]] + Pe[m mod seq]: one thread per column walks the rows in order (tokens repeat, so the adds into
-// one row of dE must be ordered to be reproducible); dE accumulates (the tied head has written it), dPe is overwritten.
+// x0[m] = E[tok[m]] + Pe[m mod seq].  dE accumulates (the tied head has written it), dPe is overwritten; the rows that share a token or a
+// position are added in the order of the rows, so the result is reproducible.
+// Block m < M: if m is the first row with its token, adds every row with that token to the token's row of dE, in order (the tokens are
+// compared 256 at a time; a thread holds up to eight columns).  Block M + p: row p of dPe.
+// (One thread per column walking all the rows took 0.8 ms for 2048 rows of 768: three workgroups and a chain of 2048 additions to memory.)
+constexpr int kEmbedCols = 8;
 __global__ void __launch_bounds__(256) embed_backward_kernel(const int32_t* __restrict__ tok, const float* __restrict__ dx, int M, int seq, int d, int vocab,
-                                                             float* __restrict__ dE, float* __restrict__ dPe, int max_pos) {
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  if (c >= d) return;
-  for (int p = 0; p < max_pos; ++p) dPe[(size_t)p * d + c] = 0.f;
-  for (int m = 0; m < M; ++m) {
-    int t = tok[m];
-    t = t < 0 ? 0 : (t >= vocab ? vocab - 1 : t);
-    const float g = dx[(size_t)m * d + c];
-    dE[(size_t)t * d + c] += g;
-    dPe[(size_t)(m % seq) * d + c] += g;
+                                                             float* __restrict__ dE, float* __restrict__ dPe) {
+  __shared__ unsigned long long match[4];
+  const int tid = threadIdx.x, c0 = blockIdx.y * 256 * kEmbedCols + tid;
+  auto token = [&](int m) { const int t = tok[m]; return t < 0 ? 0 : (t >= vocab ? vocab - 1 : t); };
+  float acc[kEmbedCols];
+  float* row;
+  if ((int)blockIdx.x >= M) {
+    const int p = (int)blockIdx.x - M;
+    row = dPe + (size_t)p * d;
+#pragma unroll
+    for (int u = 0; u < kEmbedCols; ++u) acc[u] = 0.f;
+    if (p < seq)
+      for (int m = p; m < M; m += seq)
+#pragma unroll
+        for (int u = 0; u < kEmbedCols; ++u) if (c0 + 256 * u < d) acc[u] += dx[(size_t)m * d + c0 + 256 * u];
+  } else {
+    const int m = blockIdx.x, t = token(m);
+    for (int b = 0; b < m; b += 1024) {
+      bool seen = false;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) { const int q = b + 256 * u + tid; seen |= q < m && token(q) == t; }
+      if (__syncthreads_or(seen)) return;                            // the whole block leaves
+    }
+    row = dE + (size_t)t * d;
+#pragma unroll
+    for (int u = 0; u < kEmbedCols; ++u) acc[u] = c0 + 256 * u < d ? row[c0 + 256 * u] : 0.f;
+    for (int b = m; b < M; b += 256) {
+      const unsigned long long mine = __ballot(b + tid < M && token(b + tid) == t);
+      __syncthreads();                                               // the previous 256 rows' masks have been read
+      if ((tid & 63) == 0) match[tid >> 6] = mine;
+      __syncthreads();
+      for (int w = 0; w < 4; ++w)
+        for (unsigned long long left = match[w]; left;) {
+          // eight rows are requested before the first is added: a frequent token's rows would otherwise cost a memory latency each
+          float v[8][kEmbedCols];
+          bool have[8];
+#pragma unroll
+          for (int q = 0; q < 8; ++q) {
+            have[q] = left != 0;
+            const float* src = dx + (size_t)(b + 64 * w + (have[q] ? __builtin_ctzll(left) : 0)) * d;
+            left &= left - 1;
+#pragma unroll
+            for (int u = 0; u < kEmbedCols; ++u) v[q][u] = have[q] && c0 + 256 * u < d ? src[c0 + 256 * u] : 0.f;
+          }
+#pragma unroll
+          for (int q = 0; q < 8; ++q)
+#pragma unroll
+            for (int u = 0; u < kEmbedCols; ++u) acc[u] = have[q] ? acc[u] + v[q][u] : acc[u];
+        }
+    }
   }
+#pragma unroll
+  for (int u = 0; u < kEmbedCols; ++u) if (c0 + 256 * u < d) row[c0 + 256 * u] = acc[u];
 }
 
 }  // namespace
@@ -294,11 +448,15 @@ hipError_t launch_bw_round_bf16(const float* in, int rows, int cols, int64_t ld_
   return hipGetLastError();
 }
 
-size_t bw_colsum_scratch_floats(int n_max) { return (size_t)2 * kColParts * (size_t)n_max; }
+constexpr int kLnBlocks = 256;       // blocks of the LayerNorm rule, each with a partial sum of both parameter gradients
+size_t bw_scratch_floats(int d, int n_widest) {
+  const size_t ln = (size_t)2 * kLnBlocks * (size_t)d, sums = (size_t)2 * kColParts * (size_t)n_widest;
+  return ln > sums ? ln : sums;
+}
 
 hipError_t launch_bw_colsum(const float* Y, int M, int N, int64_t ld, float* out, float* part, hipStream_t s) {
   hipLaunchKernelGGL(colsum_partial_kernel, dim3((unsigned)((N + 63) / 64), kColParts), dim3(256), 0, s, Y, M, N, ld, part);
-  hipLaunchKernelGGL(colsum_final_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, s, part, N, out);
+  hipLaunchKernelGGL(colsum_final_kernel, dim3((unsigned)((N + 31) / 32), 1), dim3(256), 0, s, part, out, nullptr, nullptr, kColParts, (int64_t)N, N);
   return hipGetLastError();
 }
 
@@ -315,11 +473,20 @@ hipError_t launch_bw_cross_entropy(float* logits, const int32_t* targets, int ro
 
 hipError_t launch_bw_layernorm(int dtype, const float* x, const void* g, const float* dy, const float* add, float* dx_out, float* stats, float* dg, float* db,
                                float* part, int M, int d, float eps, hipStream_t s) {
+  if (d % 4 == 0 && d <= 2048) {
+    const int blocks = M < 4 * kLnBlocks ? (M + 3) / 4 : kLnBlocks;
+    const dim3 grid((unsigned)blocks);
+#define ZGR_LN_BACKWARD(T, MAXV) hipLaunchKernelGGL((ln_backward_wave_kernel<T, MAXV>), grid, dim3(256), 0, s, x, reinterpret_cast<const T*>(g), dy, add, dx_out, part, M, d, eps)
+    if (dtype == 1) { if (d <= 512) ZGR_LN_BACKWARD(bf16_t, 2); else if (d <= 1024) ZGR_LN_BACKWARD(bf16_t, 4); else ZGR_LN_BACKWARD(bf16_t, 8); }
+    else            { if (d <= 512) ZGR_LN_BACKWARD(float, 2); else if (d <= 1024) ZGR_LN_BACKWARD(float, 4); else ZGR_LN_BACKWARD(float, 8); }
+#undef ZGR_LN_BACKWARD
+    hipLaunchKernelGGL(colsum_final_kernel, dim3((unsigned)((d + 31) / 32), 2), dim3(256), 0, s, part, dg, part + d, db, blocks, (int64_t)2 * d, d);
+    return hipGetLastError();
+  }
   // the parameter gradients read dy: they go first, so that dx_out may overwrite it
   hipLaunchKernelGGL(ln_stats_kernel, dim3((unsigned)M), dim3(256), 0, s, x, stats, d, eps);
   hipLaunchKernelGGL(ln_param_grad_partial_kernel, dim3((unsigned)((d + 63) / 64), kColParts), dim3(256), 0, s, x, dy, stats, M, d, part);
-  hipLaunchKernelGGL(colsum_final_kernel, dim3((unsigned)((d + 255) / 256)), dim3(256), 0, s, part, d, dg);
-  hipLaunchKernelGGL(colsum_final_kernel, dim3((unsigned)((d + 255) / 256)), dim3(256), 0, s, part + (size_t)kColParts * d, d, db);
+  hipLaunchKernelGGL(colsum_final_kernel, dim3((unsigned)((d + 31) / 32), 2), dim3(256), 0, s, part, dg, part + (size_t)kColParts * d, db, kColParts, (int64_t)d, d);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (dtype == 1) hipLaunchKernelGGL(ln_backward_kernel<bf16_t>, dim3((unsigned)M), dim3(256), 0, s, x, reinterpret_cast<const bf16_t*>(g), dy, add, dx_out, d, eps);
@@ -378,7 +545,11 @@ hipError_t launch_bw_attention(int dtype, const void* qkv, const float* dctx, co
   // S [i][j] = sum_t q[i][t] k[j][t] / sqrt dh,  dP [i][j] = sum_t dctx[i][t] v[j][t]
   if ((e = product(q0, dtype, true, ld, sq_outer, dh, k0, dtype, true, ld, sq_outer, dh, P, seq, p_outer, tt, seq, dh, scale)) != hipSuccess) return e;
   if ((e = product(dctx, 0, true, d, dc_outer, dh, v0, dtype, true, ld, sq_outer, dh, dS, seq, p_outer, tt, seq, dh, 1.0f)) != hipSuccess) return e;
-  hipLaunchKernelGGL(attn_backward_rows_kernel, dim3((unsigned)heads * seq), dim3(256), 0, s, lengths, seq, n_head, causal, P, dS);
+  const int64_t rows = (int64_t)heads * seq;
+  const dim3 row_grid((unsigned)((rows + 3) / 4));
+  if (seq <= 128)      hipLaunchKernelGGL(attn_backward_rows_kernel<2>, row_grid, dim3(256), 0, s, lengths, rows, seq, n_head, causal, P, dS);
+  else if (seq <= 512) hipLaunchKernelGGL(attn_backward_rows_kernel<8>, row_grid, dim3(256), 0, s, lengths, rows, seq, n_head, causal, P, dS);
+  else                 hipLaunchKernelGGL(attn_backward_rows_kernel<kBackwardMaxSeq / 64>, row_grid, dim3(256), 0, s, lengths, rows, seq, n_head, causal, P, dS);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   // dQ [i][t] = sum_j dS[i][j] k[j][t] / sqrt dh,  dK [j][t] = sum_i dS[i][j] q[i][t] / sqrt dh,  dV [j][t] = sum_i P[i][j] dctx[i][t]
   if ((e = product(dS, 0, true, seq, p_outer, tt, k0, dtype, false, ld, sq_outer, dh, dqkv, ld, sq_outer, dh, dh, seq, scale)) != hipSuccess) return e;
@@ -387,7 +558,7 @@ hipError_t launch_bw_attention(int dtype, const void* qkv, const float* dctx, co
 }
 
 hipError_t launch_bw_embedding(const int32_t* tok, const float* dx, int M, int seq, int d, int vocab, float* dE, float* dPe, int max_pos, hipStream_t s) {
-  hipLaunchKernelGGL(embed_backward_kernel, dim3((unsigned)((d + 255) / 256)), dim3(256), 0, s, tok, dx, M, seq, d, vocab, dE, dPe, max_pos);
+  hipLaunchKernelGGL(embed_backward_kernel, dim3((unsigned)(M + max_pos), (unsigned)((d + 256 * kEmbedCols - 1) / (256 * kEmbedCols))), dim3(256), 0, s, tok, dx, M, seq, d, vocab, dE, dPe);
   return hipGetLastError();
 }
 

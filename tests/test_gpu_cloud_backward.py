@@ -88,6 +88,26 @@ def test_fp32_gradients_match_the_oracle_entry_by_entry(which, say):
     assert all(np.abs(grads[i]).max() > 0 for i, s in enumerate(specs) if s.role != I.ROLE_BK)
 
 
+@pytest.mark.parametrize("kw", [
+    dict(d_model=32, n_head=2, d_ff=64, vocab=5, max_pos=540, batch=2, seq=530),       # a lane of the softmax rule holds nine entries of a row; each token some 200 times
+    dict(d_model=1032, n_head=129, d_ff=40, vocab=67, max_pos=9, batch=1, seq=2),      # LayerNorm rows of 258 four-wide pieces, fewer rows than a block's waves
+    dict(d_model=2056, n_head=257, d_ff=36, vocab=70, max_pos=7, batch=3, seq=5),      # rows past what a wave holds
+    dict(d_model=24, n_head=3, d_ff=35, vocab=33, max_pos=33, batch=7, seq=33),        # odd feed-forward width: entries left over by the four-wide activation
+], ids=lambda k: f"d{k['d_model']}t{k['seq']}")
+def test_fp32_gradients_at_the_edges_of_the_row_rules(kw):
+    """Same comparison and bound as above, one block, at the sizes where the row-wise rules change form."""
+    cfg = I.shrink(I.CONFIGS["cfg2"], **dict(TINY_LM, name="bw_rows", n_layer=1, **kw))
+    sess, specs, P = _setup(cfg)
+    arrays = _batch(cfg, 3)
+    loss, grads = _device(sess, cfg, arrays)
+    loss_or, grads_or = _oracle(cfg, P, arrays)
+    assert abs(loss - loss_or) <= 2e-5 * max(1.0, abs(loss_or))
+    floor = 1e-6 * max(np.abs(g).max() for g in grads_or.values())
+    for i, s in enumerate(specs):
+        want = grads_or[s.name]
+        assert np.abs(grads[i] - want).max() <= 2e-4 * np.abs(want).max() + floor, s.name
+
+
 @pytest.mark.parametrize("batch,seq,act,post_ln", [(4, 48, "gelu", False), (3, 37, "gelu", False), (4, 48, "relu", True)])
 def test_bf16_gradients_point_where_the_oracle_gradients_point(batch, seq, act, post_ln, say):
     """192 tokens: the backward products run on the matrix cores; 111 tokens (not a multiple of 64): on the fp32 kernel."""
