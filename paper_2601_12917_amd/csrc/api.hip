@@ -892,7 +892,7 @@ struct BwCarve {
   size_t xfin = 0, hf = 0, logits = 0, targets = 0, row_loss = 0, loss = 0;
   size_t dx = 0, dt = 0, dff = 0, dqkv = 0, P = 0, dS = 0, stats = 0;
   size_t part = 0;                   // chunk sums of the column reductions
-  size_t tA = 0, tB = 0, tW = 0;     // bf16 operands of the matrix-core products (bf16 models with a token count that is a multiple of 64)
+  size_t tA = 0, tB = 0, tC = 0, tW = 0;     // bf16 operands of the matrix-core products (bf16 models with a token count that is a multiple of 64)
   bool mfma = false;
   size_t split = 0;                  // parts of split sums
   size_t total = 0;
@@ -941,6 +941,7 @@ BwCarve bw_carve(const zgr_ctx* c, int batch, int seq) {
     const size_t widest = std::max(std::max(ff, 3 * d), m.arch == ZGR_ARCH_DECODER_LM ? align_up((size_t)m.vocab, 64) : (size_t)0);
     v.tA = take(2 * M * widest);
     v.tB = take(2 * M * std::max(ff, d));
+    v.tC = take(2 * M * std::max(ff, 3 * d));
     v.tW = take(2 * d * widest);
   }
   v.total = off;
@@ -995,44 +996,42 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
   // The products of the backward half.  fp32 models and ragged token counts: fp32 products on the operands as they lie.  bf16 models
   // (token count a multiple of 64): the forward pass's matrix-core GEMM, which contracts along the rows of both
   // operands, on bf16 copies written out with the contraction index innermost.
-  unsigned char* tA = ws + v.tA; unsigned char* tB = ws + v.tB; unsigned char* tW = ws + v.tW;
-  const void* tB_holds = nullptr;                       // the kept activation whose transpose tB holds
-  // dA [M, Kp] = dY [M, Np] W [Np, Kp]
   auto product = [&](const void* A, bool a_k, int64_t lda, const void* B, int64_t ldb, float* C, int64_t ldc, int Mp, int Np, int Kp, float* a_sums) {
     ProductArgs p;
     p.A = A; p.a_k = a_k; p.lda = lda; p.B = B; p.b_dtype = dt == ZGR_BF16 ? 1 : 0; p.b_k = false; p.ldb = ldb; p.C = C; p.ldc = ldc;
     p.M = Mp; p.N = Np; p.K = Kp; p.a_sums = a_sums; p.scratch = F(v.split); p.scratch_floats = kProductScratch;
     return launch_product(p, s);
   };
-  auto input_grad = [&](const float* dy, int Np, const void* W, int Kp, float* out) -> zgr_status {
-    const size_t lim = (size_t)1 << 31;                          // the GEMM addresses its operands with 32-bit offsets
-    const int Npad = (Np + 63) & ~63;                            // zeros in both operands past Np
-    if (v.mfma && (size_t)M * Npad < lim && (size_t)Kp * Npad < lim) {
-      HIP_TRY(c, launch_bw_round_bf16(dy, M, Np, Np, tA, Npad, s));
-      HIP_TRY(c, launch_bw_transpose_bf16(1, W, Np, Kp, Kp, tW, Npad, s));
-      HIP_TRY(c, launch_gemm(ZGR_BF16, tA, tW, nullptr, out, EPI_F32, M, Kp, Npad, s));
-    } else {
-      HIP_TRY(c, product(dy, true, Np, W, Kp, out, Kp, M, Kp, Np, nullptr));
-    }
-    return ZGR_OK;
+  const int relu = m.act == ZGR_ACT_RELU ? 1 : 0;
+  // whether the GEMM's 32-bit offsets reach the operands of the products with dy [M, Np] and W [Np, Kp]
+  auto on_bf16 = [&](int Np, int Kp) {
+    const size_t lim = (size_t)1 << 31, Npad = ((size_t)Np + 63) / 64 * 64;
+    return v.mfma && (size_t)M * Npad < lim && (size_t)Kp * Npad < lim && (size_t)M * Kp < lim;
   };
-  // y = a W^T + bias with a [M, Kp] kept in the storage type and dy = columns of a row-major array with row stride ldy:
-  // dW [Np, Kp] = dy^T a, dbias = column sums of dy
-  auto param_grads = [&](const float* dy, int64_t ldy, const void* a, int Np, int Kp, float* dW, float* dbias) -> zgr_status {
-    const size_t lim = (size_t)1 << 31;
-    if (v.mfma && (size_t)Np * M < lim && (size_t)Kp * M < lim) {
-      HIP_TRY(c, launch_bw_transpose_bf16(0, dy, M, Np, ldy, tA, M, s));
-      if (tB_holds != a) { HIP_TRY(c, launch_bw_transpose_bf16(1, a, M, Kp, Kp, tB, M, s)); tB_holds = a; }
-      HIP_TRY(c, launch_gemm(ZGR_BF16, tA, tB, nullptr, dW, EPI_F32, Np, Kp, M, s));
+  // One linear layer y = a W^T + b, a [M, Kp] kept in the storage type, W [Np, Kp], with dL/dy = dy (act'(u) dy when u is given): dW = dy^T a, db = column
+  // sums, da = dy W.  The layer's outputs may be up to three equal blocks with weights and biases of their own (W's rows in one piece).
+  auto linear_backward = [&](float* dy, const float* u, int Np, const void* W, int Kp, const void* a, int blocks, const int* wi, const int* bi, float* da) -> zgr_status {
+    float* db[3] = {};
+    for (int p = 0; p < blocks; ++p) db[p] = grads[bi[p]];
+    const int n = Np / blocks;
+    if (on_bf16(Np, Kp)) {
+      unsigned char* tC = ws + v.tC;
+      HIP_TRY(c, launch_bw_gradient_operands(dy, u, relu, M, Np, tC, ws + v.tA, db, blocks, F(v.part), s));
+      HIP_TRY(c, launch_bw_transpose_bf16(a, M, Kp, Kp, ws + v.tB, M, s));
+      bool whole = true;                                 // the blocks' weight gradients in one piece: one product
+      for (int p = 1; p < blocks; ++p) whole = whole && grads[wi[p]] == grads[wi[0]] + (size_t)p * n * Kp;
+      for (int p = 0; p < (whole ? 1 : blocks); ++p)
+        HIP_TRY(c, launch_gemm(ZGR_BF16, tC + (size_t)p * n * M * 2, ws + v.tB, nullptr, grads[wi[p]], EPI_F32, whole ? Np : n, Kp, M, s));
+      HIP_TRY(c, launch_bw_transpose_bf16(W, Np, Kp, Kp, ws + v.tW, Np, s));
+      HIP_TRY(c, launch_gemm(ZGR_BF16, ws + v.tA, ws + v.tW, nullptr, da, EPI_F32, M, Kp, Np, s));
     } else {
-      HIP_TRY(c, product(dy, false, ldy, a, Kp, dW, Kp, Np, Kp, M, dbias));
-      return ZGR_OK;
+      if (u) HIP_TRY(c, launch_bw_act(relu, u, dy, (int64_t)M * Np, s));
+      for (int p = 0; p < blocks; ++p) HIP_TRY(c, product(dy + (size_t)p * n, false, Np, a, Kp, grads[wi[p]], Kp, n, Kp, M, db[p]));
+      HIP_TRY(c, product(dy, true, Np, W, Kp, da, Kp, M, Kp, Np, nullptr));
     }
-    if (dbias) HIP_TRY(c, launch_bw_colsum(dy, M, Np, ldy, dbias, F(v.part), s));
     return ZGR_OK;
   };
   // ---- forward, every layer's intermediate results kept
-  const int relu = m.act == ZGR_ACT_RELU ? 1 : 0;
   if (!m.post_ln) {
     HIP_TRY(c, launch_embed(dt, tok, T(c, c->tok_emb), T(c, c->pos_emb), F(v.layer[0].xin), M, Tn, d, m.vocab, s));
     for (int l = 0; l < m.n_layer; ++l) {
@@ -1083,19 +1082,30 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
     const double inv_n = 1.0 / ((double)B * (Tn - 1));
     HIP_TRY(c, launch_lm_targets(tok, tgt, M, Tn, m.vocab, s));
     HIP_TRY(c, launch_gemm(dt, ws + v.hf, T(c, c->tok_emb), nullptr, logits, EPI_F32, M, m.vocab, d, s));
-    HIP_TRY(c, launch_ce_rows(logits, tgt, F(v.row_loss), M, m.vocab, s));
-    HIP_TRY(c, launch_mean_f64(F(v.row_loss), M, inv_n, loss_dev, s));
-    HIP_TRY(c, launch_bw_cross_entropy(logits, tgt, M, m.vocab, (float)inv_n, s));
     // tied head: logits = hf E^T, so dE = dlogits^T hf (the embedding rule adds its share below), dhf = dlogits E
-    if ((st = param_grads(logits, m.vocab, ws + v.hf, m.vocab, d, grads[c->tok_emb], nullptr)) != ZGR_OK) return st;
-    if ((st = input_grad(logits, m.vocab, T(c, c->tok_emb), d, dtb)) != ZGR_OK) return st;
+    const void* E = T(c, c->tok_emb);
+    float* dE = grads[c->tok_emb];
+    if (on_bf16(m.vocab, d)) {
+      // dlogits in bf16 as rows for dhf; their transpose for dE takes the place of the logits
+      const int Vpad = (m.vocab + 63) & ~63;
+      HIP_TRY(c, launch_bw_cross_entropy(logits, tgt, M, m.vocab, (float)inv_n, F(v.row_loss), ws + v.tA, Vpad, s));
+      HIP_TRY(c, launch_bw_transpose_bf16(ws + v.tA, M, m.vocab, Vpad, logits, M, s));
+      HIP_TRY(c, launch_bw_transpose_bf16(ws + v.hf, M, d, d, ws + v.tB, M, s));
+      HIP_TRY(c, launch_gemm(ZGR_BF16, logits, ws + v.tB, nullptr, dE, EPI_F32, m.vocab, d, M, s));
+      HIP_TRY(c, launch_bw_transpose_bf16(E, m.vocab, d, d, ws + v.tW, Vpad, s));
+      HIP_TRY(c, launch_gemm(ZGR_BF16, ws + v.tA, ws + v.tW, nullptr, dtb, EPI_F32, M, d, Vpad, s));
+    } else {
+      HIP_TRY(c, launch_bw_cross_entropy(logits, tgt, M, m.vocab, (float)inv_n, F(v.row_loss), nullptr, 0, s));
+      HIP_TRY(c, product(logits, false, m.vocab, ws + v.hf, d, dE, d, m.vocab, d, M, nullptr));
+      HIP_TRY(c, product(logits, true, m.vocab, E, d, dtb, d, M, d, m.vocab, nullptr));
+    }
+    HIP_TRY(c, launch_mean_f64(F(v.row_loss), M, inv_n, loss_dev, s));
   } else {
     const int32_t* labels = reinterpret_cast<const int32_t*>(b->y);
     const int C = m.n_class;
     HIP_TRY(c, launch_cls_head(dt, ws + v.hf, T(c, c->cls_w), T(c, c->cls_b), logits, B, Tn, d, C, s));
-    HIP_TRY(c, launch_ce_rows(logits, labels, F(v.row_loss), B, C, s));
+    HIP_TRY(c, launch_bw_cross_entropy(logits, labels, B, C, 1.0f / (float)B, F(v.row_loss), nullptr, 0, s));
     HIP_TRY(c, launch_mean_f64(F(v.row_loss), B, 1.0 / B, loss_dev, s));
-    HIP_TRY(c, launch_bw_cross_entropy(logits, labels, B, C, 1.0f / (float)B, s));
     // the head reads the first token of each sequence: rows b T of hf
     HIP_TRY(c, product(logits, false, C, ws + v.hf, (int64_t)Tn * d, grads[c->cls_w], d, C, d, B, grads[c->cls_b]));
     HIP_TRY(c, launch_bw_fill(dtb, (int64_t)M * d, 0.f, s));
@@ -1114,12 +1124,9 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
     // post-LN: x_out = LN2(y2), dx <- dL/dy2
     if (m.post_ln) HIP_TRY(c, launch_bw_layernorm(dt, F(W.y2), T(c, L.ln2_g), dx, nullptr, dx, F(v.stats), grads[L.ln2_g], grads[L.ln2_b], F(v.part), M, d, m.ln_eps, s));
     // x_out (or y2) = x_mid (or x1n) + f W2^T + b2
-    if ((st = param_grads(dx, d, ws + W.f, d, ff, grads[L.w2], grads[L.b2])) != ZGR_OK) return st;
-    if ((st = input_grad(dx, d, T(c, L.w2), ff, dff)) != ZGR_OK) return st;
-    HIP_TRY(c, launch_bw_act(relu, F(W.u), dff, (int64_t)M * ff, s));
-    // u = h2 W1^T + b1
-    if ((st = param_grads(dff, ff, ws + W.h2, ff, d, grads[L.w1], grads[L.b1])) != ZGR_OK) return st;
-    if ((st = input_grad(dff, ff, T(c, L.w1), d, dtb)) != ZGR_OK) return st;
+    if ((st = linear_backward(dx, nullptr, d, T(c, L.w2), ff, ws + W.f, 1, &L.w2, &L.b2, dff)) != ZGR_OK) return st;
+    // f = act(u), u = h2 W1^T + b1
+    if ((st = linear_backward(dff, F(W.u), ff, T(c, L.w1), d, ws + W.h2, 1, &L.w1, &L.b1, dtb)) != ZGR_OK) return st;
     if (m.post_ln) {
       // h2 = x1n = LN1(y1): dL/dx1n = dx + dh2, then dx <- dL/dy1
       HIP_TRY(c, launch_bw_add(dtb, dx, nx, s));
@@ -1129,14 +1136,11 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
       HIP_TRY(c, launch_bw_layernorm(dt, F(W.xmid), T(c, L.ln2_g), dtb, dx, dx, F(v.stats), grads[L.ln2_g], grads[L.ln2_b], F(v.part), M, d, m.ln_eps, s));
     }
     // x_mid (or y1) = x_in + ctx Wo^T + bo
-    if ((st = param_grads(dx, d, ws + W.ctx, d, d, grads[L.wo], grads[L.bo])) != ZGR_OK) return st;
-    if ((st = input_grad(dx, d, T(c, L.wo), d, dtb)) != ZGR_OK) return st;
+    if ((st = linear_backward(dx, nullptr, d, T(c, L.wo), d, ws + W.ctx, 1, &L.wo, &L.bo, dtb)) != ZGR_OK) return st;
     HIP_TRY(c, launch_bw_attention(dt, ws + W.qkv, dtb, lengths, B, Tn, d, H, lm ? 1 : 0, F(v.P), F(v.dS), dqkv, s));
     // q, k, v = h1 W{q,k,v}^T + b{q,k,v}: three column blocks of dqkv; Wq, Wk, Wv are adjacent, one [3 d, d] matrix
     const int wi[3] = {L.wq, L.wk, L.wv}, bi[3] = {L.bq, L.bk, L.bv};
-    for (int p = 0; p < 3; ++p)
-      if ((st = param_grads(dqkv + (size_t)p * d, 3 * d, ws + W.h1, d, d, grads[wi[p]], grads[bi[p]])) != ZGR_OK) return st;
-    if ((st = input_grad(dqkv, 3 * d, T(c, L.wq), d, dtb)) != ZGR_OK) return st;
+    if ((st = linear_backward(dqkv, nullptr, 3 * d, T(c, L.wq), d, ws + W.h1, 3, wi, bi, dtb)) != ZGR_OK) return st;
     if (m.post_ln) HIP_TRY(c, launch_bw_add(dx, dtb, nx, s));                                    // h1 = x_in
     else HIP_TRY(c, launch_bw_layernorm(dt, F(W.xin), T(c, L.ln1_g), dtb, dx, dx, F(v.stats), grads[L.ln1_g], grads[L.ln1_b], F(v.part), M, d, m.ln_eps, s));
   }

@@ -40,65 +40,101 @@ __device__ __forceinline__ float block_sum(float v, float* red) {
   __syncthreads();
   return red[0] + red[1] + red[2] + red[3];
 }
-__device__ __forceinline__ float block_max(float v, float* red) {
-  v = wave_max(v);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  return fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+
+// ------------------------------------------------------------------ feed-forward activation: erf-GELU or ReLU
+template <bool RELU> __device__ __forceinline__ float act_of(float x) { return RELU ? fmaxf(x, 0.f) : 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)); }
+// du = df act'(u): GELU' = Phi(u) + u phi(u), ReLU' = [u > 0] (a zero slope gives zero whatever df holds)
+template <bool RELU> __device__ __forceinline__ float act_rule(float x, float df) {
+  if (RELU) return x > 0.f ? df : 0.f;
+  const float cdf = 0.5f * (1.0f + erff(x * 0.70710678118654752f));
+  const float pdf = 0.3989422804014327f * expf(-0.5f * x * x);
+  return df * (cdf + x * pdf);
 }
 
 // ------------------------------------------------------------------ operands for the matrix-core products (bf16 models)
 // The bf16 GEMM of the forward pass computes A W^T with both operands contiguous along the contraction.  A backward
-// product contracts over another index, so its operands are first written out in bf16 with that index innermost:
-//   out[c][r] = in[r][c]   (transpose, 64 x 64 tiles through LDS)      or      out[r][c] = in[r][c]   (rounding only)
-// Elements [rows, ld_out) of every output row (transpose) and [cols, ld_out) (rounding) are written as zeros: padding of the
-// contraction up to the multiple of 64 the GEMM asks for.
-template <typename TIN>
-__global__ void __launch_bounds__(256) transpose_bf16_kernel(const TIN* __restrict__ in, int rows, int cols, int64_t ld_in, bf16_t* __restrict__ out, int64_t ld_out) {
+// product contracts over another index, so its operands are first written out in bf16 with that index innermost.  One pass over
+// in [rows, cols] (row stride ld_in) writes what is asked for:
+//   cols_out[c][r] = in[r][c]  (row stride ld_cols, always),  rows_out[r][c] = in[r][c]  (ROWS, row stride ld_rows),
+//   part[blockIdx.y][c] = the sum of the block's rows of column c in fp32  (SUMS, the bias gradient's first stage),
+// with in = act'(u) in where ACT says so (1 GELU, 2 ReLU; u laid out as in).  What lies between the data and ld_cols or ld_rows (multiples of 64)
+// is written as zeros: padding of the contraction.  64 x 64 tiles through LDS, tiles_per_block of them one below the other per
+// block; loads and stores of 8 and 16 bytes.  Bound by memory: a gradient of 2048 x 3072 is read once and written twice in bf16,
+// 50 MB in 14 us with the activation's slope, 6 us at 2048 x 768.  (A rounding pass, a transposing pass with 2-byte stores, an activation pass and a column sum took 50 us at 2048 x 3072.)
+template <typename T> struct alignas(sizeof(T) * 4) Four { T e[4]; };
+template <typename TIN, int ACT, bool ROWS, bool SUMS>
+__global__ void __launch_bounds__(256) operand_kernel(const TIN* __restrict__ in, const float* __restrict__ u, int rows, int cols, int64_t ld_in, bf16_t* __restrict__ cols_out,
+                                                      int64_t ld_cols, bf16_t* __restrict__ rows_out, int64_t ld_rows, float* __restrict__ part, int tiles_per_block) {
   __shared__ float tile[64][65];
-  const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
-  for (int i = threadIdx.x; i < 64 * 64; i += 256) {
-    const int r = i >> 6, c = i & 63;
-    tile[r][c] = (r0 + r < rows && c0 + c < cols) ? to_f32(in[(int64_t)(r0 + r) * ld_in + c0 + c]) : 0.f;
+  const int tid = threadIdx.x, c4 = (tid & 15) * 4, rq = tid >> 4, c0 = blockIdx.x * 64;
+  float sum[4] = {0.f, 0.f, 0.f, 0.f};
+  for (int t = 0; t < tiles_per_block; ++t) {
+    const int r0 = ((int)blockIdx.y * tiles_per_block + t) * 64;
+    if (r0 >= rows && r0 >= ld_cols) break;
+    __syncthreads();                                       // the previous tile has been read
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = r0 + rq + 16 * i, c = c0 + c4;
+      float f[4] = {0.f, 0.f, 0.f, 0.f};
+      if (r < rows) {
+        const int64_t o = (int64_t)r * ld_in + c;
+        if (c + 4 <= cols) {
+          const Four<TIN> v = *reinterpret_cast<const Four<TIN>*>(in + o);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) f[q] = to_f32(v.e[q]);
+          if (ACT) {
+            const Four<float> x = *reinterpret_cast<const Four<float>*>(u + o);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) f[q] = act_rule<ACT == 2>(x.e[q], f[q]);
+          }
+        } else {
+          for (int q = 0; q < 4; ++q) if (c + q < cols) f[q] = ACT ? act_rule<ACT == 2>(u[o + q], to_f32(in[o + q])) : to_f32(in[o + q]);
+        }
+        if (ROWS && c < ld_rows) {
+          Four<bf16_t> h;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) from_f32(f[q], h.e[q]);
+          *reinterpret_cast<Four<bf16_t>*>(rows_out + (int64_t)r * ld_rows + c) = h;
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) { if (SUMS) sum[q] += f[q]; tile[rq + 16 * i][c4 + q] = f[q]; }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int c = (tid >> 3) + 32 * i, r = (tid & 7) * 8;
+      if (c0 + c < cols && r0 + r < ld_cols) {
+        struct alignas(16) Eight { bf16_t e[8]; } h;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) from_f32(tile[r + q][c], h.e[q]);
+        *reinterpret_cast<Eight*>(cols_out + (int64_t)(c0 + c) * ld_cols + r0 + r) = h;
+      }
+    }
   }
-  __syncthreads();
-  for (int i = threadIdx.x; i < 64 * 64; i += 256) {
-    const int c = i >> 6, r = i & 63;
-    if (r0 + r < ld_out && c0 + c < cols) from_f32(tile[r][c], out[(int64_t)(c0 + c) * ld_out + r0 + r]);      // tile holds zeros past `rows`
-  }
-}
-__global__ void __launch_bounds__(256) round_bf16_kernel(const float* __restrict__ in, int rows, int cols, int64_t ld_in, bf16_t* __restrict__ out, int64_t ld_out) {
-  const int64_t n = (int64_t)rows * ld_out;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-    const int64_t r = i / ld_out, c = i % ld_out;
-    from_f32(c < cols ? in[r * ld_in + c] : 0.f, out[i]);
+  if (SUMS) {                                              // sixteen row groups, added in their order
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) tile[rq][c4 + q] = sum[q];
+    __syncthreads();
+    if (tid < 64 && c0 + tid < cols) {
+      float v = 0.f;
+      for (int g = 0; g < 16; ++g) v += tile[g][tid];
+      part[(size_t)blockIdx.y * cols + c0 + tid] = v;
+    }
   }
 }
 
-// out[n] = sum_m Y[m ld + n]  (bias gradients), in two stages with a fixed shape so that the order of the additions
-// never depends on scheduling: kColParts row chunks are summed side by side (64 columns per block, 4 row groups),
-// then the chunk sums are added in chunk order.
+// Sums over rows run in two stages with a fixed shape, so that the order of the additions never depends on scheduling: up to kColParts
+// chunks of rows are summed side by side, then the chunk sums are added in their order:
+// out[y][c] = sum over p of part[p stride + y n + c], c < n, blockIdx.y = y.  32 columns per block, eight threads to a column: each adds an
+// eighth of the parts in order, then the eighths are added in order.
 constexpr int kColParts = 64;
-__global__ void __launch_bounds__(256) colsum_partial_kernel(const float* __restrict__ Y, int M, int N, int64_t ld, float* __restrict__ part) {
-  __shared__ float acc[4][64];
-  const int c = blockIdx.x * 64 + (threadIdx.x & 63), g = threadIdx.x >> 6;
-  const int chunk = (M + kColParts - 1) / kColParts;
-  const int m_begin = blockIdx.y * chunk, m_end = min(M, m_begin + chunk);
-  float s = 0.f;
-  if (c < N)
-    for (int m = m_begin + g; m < m_end; m += 4) s += Y[(int64_t)m * ld + c];
-  acc[g][threadIdx.x & 63] = s;
-  __syncthreads();
-  if (g == 0 && c < N) part[(size_t)blockIdx.y * N + c] = (acc[0][threadIdx.x] + acc[1][threadIdx.x]) + (acc[2][threadIdx.x] + acc[3][threadIdx.x]);
-}
-// The second stage for up to two sums of n columns: out[c] = part[0][c] + part[1][c] + ..., blockIdx.y choosing (part, out).  32 columns per
-// block, eight threads to a column: each adds an eighth of the parts in order, then the eighths are added in order.
-__global__ void __launch_bounds__(256) colsum_final_kernel(const float* __restrict__ part0, float* __restrict__ out0, const float* __restrict__ part1, float* __restrict__ out1,
-                                                           int parts, int64_t stride, int n) {
+struct SumOutputs { float* out[3]; };
+__global__ void __launch_bounds__(256) colsum_final_kernel(const float* __restrict__ part, int parts, int64_t stride, int n, SumOutputs outs) {
   __shared__ float sums[8][32];
-  const float* part = blockIdx.y ? part1 : part0;
-  float* out = blockIdx.y ? out1 : out0;
+  part += (int64_t)blockIdx.y * n;
+  float* out = outs.out[blockIdx.y];
   const int c = blockIdx.x * 32 + (threadIdx.x & 31), q = threadIdx.x >> 5, per = (parts + 7) / 8;
   float s = 0.f;
   if (c < n) {
@@ -119,23 +155,59 @@ __global__ void __launch_bounds__(256) fill_kernel(float* __restrict__ p, int64_
 }
 
 // ------------------------------------------------------------------ softmax cross-entropy
-// In place on a row of logits: d = (softmax - onehot(target)) * inv_count, or zeros for a row without a target.
-__global__ void __launch_bounds__(256) ce_backward_kernel(float* __restrict__ logits, const int32_t* __restrict__ targets, int n, float inv_count) {
-  __shared__ float red[4];
+// One row of logits per block: row_loss = logsumexp - logit[target] (0 where target < 0; a target past the end counts as the last entry) and
+// d = (softmax - onehot(target)) inv_count, zeros for a row without a target in [0, n).  d goes in place (fp32), or in bf16 to
+// d16 [rows, ld16] with zeros between n and ld16.  1024 threads hold 1024 MAXE entries in registers, so the row is read once and its exponentials
+// are taken once; entries beyond those are read again.  (Separate kernels for the loss and the gradient read the row five
+// times: 690 us for 2048 rows of 50272, now 176.)
+template <int MAXE, bool TO16>
+__global__ void __launch_bounds__(1024) ce_backward_kernel(float* __restrict__ logits, const int32_t* __restrict__ targets, int n, float inv_count, float* __restrict__ row_loss,
+                                                           bf16_t* __restrict__ d16, int64_t ld16) {
+  __shared__ float red[16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   float* row = logits + (size_t)blockIdx.x * n;
+  bf16_t* out16 = TO16 ? d16 + (size_t)blockIdx.x * ld16 : nullptr;
   const int tgt = targets[blockIdx.x];
-  if (tgt < 0 || tgt >= n) {                        // uniform over the block
-    for (int i = threadIdx.x; i < n; i += 256) row[i] = 0.f;
+  const bool has = tgt >= 0 && tgt < n;                    // uniform over the block
+  auto put = [&](int i, float d) { if (TO16) from_f32(d, out16[i]); else row[i] = d; };
+  auto across = [&](float v, bool maximum) {               // the block's 16 waves, in order
+    v = maximum ? wave_max(v) : wave_sum(v);
+    __syncthreads();
+    if (lane == 0) red[wave] = v;
+    __syncthreads();
+    float r = red[0];
+    for (int w = 1; w < 16; ++w) r = maximum ? fmaxf(r, red[w]) : r + red[w];
+    return r;
+  };
+  if (TO16) for (int i = n + tid; i < ld16; i += 1024) from_f32(0.f, out16[i]);
+  if (tgt < 0) {
+    for (int i = tid; i < n; i += 1024) put(i, 0.f);
+    if (tid == 0) row_loss[blockIdx.x] = 0.f;
     return;
   }
-  float mx = -INFINITY;
-  for (int i = threadIdx.x; i < n; i += 256) mx = fmaxf(mx, row[i]);
-  mx = block_max(mx, red);
+  const float at_target = row[has ? tgt : n - 1];          // read before anything is written
+  float v[MAXE], mx = -INFINITY;
+#pragma unroll
+  for (int u = 0; u < MAXE; ++u) {
+    const int i = tid + 1024 * u;
+    v[u] = i < n ? row[i] : -INFINITY;
+    mx = fmaxf(mx, v[u]);
+  }
+  for (int i = tid + 1024 * MAXE; i < n; i += 1024) mx = fmaxf(mx, row[i]);
+  mx = across(mx, true);
   float s = 0.f;
-  for (int i = threadIdx.x; i < n; i += 256) s += expf(row[i] - mx);
-  s = block_sum(s, red);
+#pragma unroll
+  for (int u = 0; u < MAXE; ++u) { v[u] = tid + 1024 * u < n ? expf(v[u] - mx) : 0.f; s += v[u]; }
+  for (int i = tid + 1024 * MAXE; i < n; i += 1024) s += expf(row[i] - mx);
+  s = across(s, false);
+  if (tid == 0) row_loss[blockIdx.x] = logf(s) + mx - at_target;
   const float inv = 1.0f / s;
-  for (int i = threadIdx.x; i < n; i += 256) row[i] = (expf(row[i] - mx) * inv - (i == tgt ? 1.0f : 0.f)) * inv_count;
+#pragma unroll
+  for (int u = 0; u < MAXE; ++u) {
+    const int i = tid + 1024 * u;
+    if (i < n) put(i, has ? (v[u] * inv - (i == tgt ? 1.0f : 0.f)) * inv_count : 0.f);
+  }
+  for (int i = tid + 1024 * MAXE; i < n; i += 1024) put(i, has ? (expf(row[i] - mx) * inv - (i == tgt ? 1.0f : 0.f)) * inv_count : 0.f);
 }
 
 // ------------------------------------------------------------------ LayerNorm
@@ -256,7 +328,7 @@ __global__ void __launch_bounds__(256) ln_stats_kernel(const float* __restrict__
   if (threadIdx.x == 0) { stats[2 * blockIdx.x] = mu; stats[2 * blockIdx.x + 1] = rstd; }
 }
 
-// dg[c] = sum_m dy[m][c] xhat[m][c], db[c] = sum_m dy[m][c]: chunk sums as above (part: [2][kColParts][d]), then
+// dg[c] = sum_m dy[m][c] xhat[m][c], db[c] = sum_m dy[m][c]: chunk sums as above (part: [kColParts][2][d]), then
 // colsum_final_kernel on each half
 __global__ void __launch_bounds__(256) ln_param_grad_partial_kernel(const float* __restrict__ x, const float* __restrict__ dy, const float* __restrict__ stats,
                                                                     int M, int d, float* __restrict__ part) {
@@ -274,19 +346,12 @@ __global__ void __launch_bounds__(256) ln_param_grad_partial_kernel(const float*
   pg[grp][threadIdx.x & 63] = sg; pb[grp][threadIdx.x & 63] = sb;
   __syncthreads();
   if (grp == 0 && c < d) {
-    part[(size_t)blockIdx.y * d + c] = (pg[0][threadIdx.x] + pg[1][threadIdx.x]) + (pg[2][threadIdx.x] + pg[3][threadIdx.x]);
-    part[(size_t)(kColParts + blockIdx.y) * d + c] = (pb[0][threadIdx.x] + pb[1][threadIdx.x]) + (pb[2][threadIdx.x] + pb[3][threadIdx.x]);
+    part[(size_t)2 * blockIdx.y * d + c] = (pg[0][threadIdx.x] + pg[1][threadIdx.x]) + (pg[2][threadIdx.x] + pg[3][threadIdx.x]);
+    part[(size_t)(2 * blockIdx.y + 1) * d + c] = (pb[0][threadIdx.x] + pb[1][threadIdx.x]) + (pb[2][threadIdx.x] + pb[3][threadIdx.x]);
   }
 }
 
-// ------------------------------------------------------------------ feed-forward activation: erf-GELU or ReLU
 // Four entries per thread (n4 of them), the last n % 4 by the first threads of the grid.
-template <bool RELU> __device__ __forceinline__ float act_of(float x) { return RELU ? fmaxf(x, 0.f) : 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)); }
-__device__ __forceinline__ float gelu_slope(float x) {
-  const float cdf = 0.5f * (1.0f + erff(x * 0.70710678118654752f));
-  const float pdf = 0.3989422804014327f * expf(-0.5f * x * x);
-  return cdf + x * pdf;
-}
 template <typename T, bool RELU>
 __global__ void __launch_bounds__(256) act_forward_kernel(const float* __restrict__ u, T* __restrict__ f, int64_t n) {
   struct alignas(sizeof(T) * 4) V4 { T e[4]; };
@@ -299,11 +364,7 @@ __global__ void __launch_bounds__(256) act_forward_kernel(const float* __restric
   }
   if (first < (n & 3)) from_f32(act_of<RELU>(u[4 * n4 + first]), f[4 * n4 + first]);
 }
-// du = df * act'(u), in place on df: GELU' = Phi(u) + u phi(u), ReLU' = [u > 0] (a zero slope gives zero whatever df holds)
-template <bool RELU> __device__ __forceinline__ float act_rule(float x, float df) {
-  if (RELU) return x > 0.f ? df : 0.f;
-  return df * gelu_slope(x);
-}
+// df <- df act'(u)
 template <bool RELU>
 __global__ void __launch_bounds__(256) act_backward_kernel(const float* __restrict__ u, float* __restrict__ df, int64_t n) {
   const int64_t first = (int64_t)blockIdx.x * 256 + threadIdx.x, n4 = n >> 2;
@@ -434,17 +495,27 @@ __global__ void __launch_bounds__(256) embed_backward_kernel(const int32_t* __re
 
 static unsigned grid_1d(int64_t n) { const int64_t b = (n + 255) / 256; return (unsigned)(b < 1 ? 1 : (b > 4096 ? 4096 : b)); }
 
-hipError_t launch_bw_transpose_bf16(int in_dtype, const void* in, int rows, int cols, int64_t ld_in, void* out, int64_t ld_out, hipStream_t s) {
+hipError_t launch_bw_transpose_bf16(const void* in, int rows, int cols, int64_t ld_in, void* out, int64_t ld_out, hipStream_t s) {
   if (rows < 1 || cols < 1) return hipSuccess;
   const dim3 grid((unsigned)((cols + 63) / 64), (unsigned)((ld_out + 63) / 64));
-  if (in_dtype == 1) hipLaunchKernelGGL(transpose_bf16_kernel<bf16_t>, grid, dim3(256), 0, s, reinterpret_cast<const bf16_t*>(in), rows, cols, ld_in, reinterpret_cast<bf16_t*>(out), ld_out);
-  else               hipLaunchKernelGGL(transpose_bf16_kernel<float>, grid, dim3(256), 0, s, reinterpret_cast<const float*>(in), rows, cols, ld_in, reinterpret_cast<bf16_t*>(out), ld_out);
+  hipLaunchKernelGGL((operand_kernel<bf16_t, 0, false, false>), grid, dim3(256), 0, s, reinterpret_cast<const bf16_t*>(in), nullptr, rows, cols, ld_in, reinterpret_cast<bf16_t*>(out), ld_out,
+                     nullptr, (int64_t)0, nullptr, 1);
   return hipGetLastError();
 }
 
-hipError_t launch_bw_round_bf16(const float* in, int rows, int cols, int64_t ld_in, void* out, int64_t ld_out, hipStream_t s) {
-  if (rows < 1 || cols < 1) return hipSuccess;
-  hipLaunchKernelGGL(round_bf16_kernel, dim3(grid_1d((int64_t)rows * ld_out)), dim3(256), 0, s, in, rows, cols, ld_in, reinterpret_cast<bf16_t*>(out), ld_out);
+hipError_t launch_bw_gradient_operands(const float* dy, const float* u, int relu, int M, int N, void* cols_out, void* rows_out, float* const* dbias, int n_bias, float* part, hipStream_t s) {
+  if (M < 1 || N < 1 || M % 64 || N % 64 || n_bias < 1 || n_bias > 3 || N % n_bias) return hipErrorInvalidValue;
+  const int tiles = M / 64, per = (tiles + kColParts - 1) / kColParts, parts = (tiles + per - 1) / per;
+  const dim3 grid((unsigned)(N / 64), (unsigned)parts);
+#define ZGR_OPERANDS(ACT)                                                                                                                                          \
+  hipLaunchKernelGGL((operand_kernel<float, ACT, true, true>), grid, dim3(256), 0, s, dy, u, M, N, (int64_t)N, reinterpret_cast<bf16_t*>(cols_out), (int64_t)M,    \
+                     reinterpret_cast<bf16_t*>(rows_out), (int64_t)N, part, per)
+  if (!u) ZGR_OPERANDS(0); else if (relu) ZGR_OPERANDS(2); else ZGR_OPERANDS(1);
+#undef ZGR_OPERANDS
+  SumOutputs outs{};
+  for (int i = 0; i < n_bias; ++i) outs.out[i] = dbias[i];
+  const int n = N / n_bias;
+  hipLaunchKernelGGL(colsum_final_kernel, dim3((unsigned)((n + 31) / 32), (unsigned)n_bias), dim3(256), 0, s, part, parts, (int64_t)N, n, outs);
   return hipGetLastError();
 }
 
@@ -454,20 +525,17 @@ size_t bw_scratch_floats(int d, int n_widest) {
   return ln > sums ? ln : sums;
 }
 
-hipError_t launch_bw_colsum(const float* Y, int M, int N, int64_t ld, float* out, float* part, hipStream_t s) {
-  hipLaunchKernelGGL(colsum_partial_kernel, dim3((unsigned)((N + 63) / 64), kColParts), dim3(256), 0, s, Y, M, N, ld, part);
-  hipLaunchKernelGGL(colsum_final_kernel, dim3((unsigned)((N + 31) / 32), 1), dim3(256), 0, s, part, out, nullptr, nullptr, kColParts, (int64_t)N, N);
-  return hipGetLastError();
-}
-
 hipError_t launch_bw_fill(float* p, int64_t n, float v, hipStream_t s) {
   if (n < 1) return hipSuccess;
   hipLaunchKernelGGL(fill_kernel, dim3(grid_1d(n)), dim3(256), 0, s, p, n, v);
   return hipGetLastError();
 }
 
-hipError_t launch_bw_cross_entropy(float* logits, const int32_t* targets, int rows, int n, float inv_count, hipStream_t s) {
-  hipLaunchKernelGGL(ce_backward_kernel, dim3((unsigned)rows), dim3(256), 0, s, logits, targets, n, inv_count);
+hipError_t launch_bw_cross_entropy(float* logits, const int32_t* targets, int rows, int n, float inv_count, float* row_loss, void* d16, int64_t ld16, hipStream_t s) {
+#define ZGR_CE(MAXE, TO16) hipLaunchKernelGGL((ce_backward_kernel<MAXE, TO16>), dim3((unsigned)rows), dim3(1024), 0, s, logits, targets, n, inv_count, row_loss, reinterpret_cast<bf16_t*>(d16), ld16)
+  if (n <= 8 * 1024) { if (d16) ZGR_CE(8, true); else ZGR_CE(8, false); }
+  else               { if (d16) ZGR_CE(50, true); else ZGR_CE(50, false); }
+#undef ZGR_CE
   return hipGetLastError();
 }
 
@@ -480,13 +548,13 @@ hipError_t launch_bw_layernorm(int dtype, const float* x, const void* g, const f
     if (dtype == 1) { if (d <= 512) ZGR_LN_BACKWARD(bf16_t, 2); else if (d <= 1024) ZGR_LN_BACKWARD(bf16_t, 4); else ZGR_LN_BACKWARD(bf16_t, 8); }
     else            { if (d <= 512) ZGR_LN_BACKWARD(float, 2); else if (d <= 1024) ZGR_LN_BACKWARD(float, 4); else ZGR_LN_BACKWARD(float, 8); }
 #undef ZGR_LN_BACKWARD
-    hipLaunchKernelGGL(colsum_final_kernel, dim3((unsigned)((d + 31) / 32), 2), dim3(256), 0, s, part, dg, part + d, db, blocks, (int64_t)2 * d, d);
+    hipLaunchKernelGGL(colsum_final_kernel, dim3((unsigned)((d + 31) / 32), 2), dim3(256), 0, s, part, blocks, (int64_t)2 * d, d, SumOutputs{{dg, db, nullptr}});
     return hipGetLastError();
   }
   // the parameter gradients read dy: they go first, so that dx_out may overwrite it
   hipLaunchKernelGGL(ln_stats_kernel, dim3((unsigned)M), dim3(256), 0, s, x, stats, d, eps);
   hipLaunchKernelGGL(ln_param_grad_partial_kernel, dim3((unsigned)((d + 63) / 64), kColParts), dim3(256), 0, s, x, dy, stats, M, d, part);
-  hipLaunchKernelGGL(colsum_final_kernel, dim3((unsigned)((d + 31) / 32), 2), dim3(256), 0, s, part, dg, part + (size_t)kColParts * d, db, kColParts, (int64_t)d, d);
+  hipLaunchKernelGGL(colsum_final_kernel, dim3((unsigned)((d + 31) / 32), 2), dim3(256), 0, s, part, kColParts, (int64_t)2 * d, d, SumOutputs{{dg, db, nullptr}});
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (dtype == 1) hipLaunchKernelGGL(ln_backward_kernel<bf16_t>, dim3((unsigned)M), dim3(256), 0, s, x, reinterpret_cast<const bf16_t*>(g), dy, add, dx_out, d, eps);

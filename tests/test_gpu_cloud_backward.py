@@ -93,6 +93,7 @@ def test_fp32_gradients_match_the_oracle_entry_by_entry(which, say):
     dict(d_model=1032, n_head=129, d_ff=40, vocab=67, max_pos=9, batch=1, seq=2),      # LayerNorm rows of 258 four-wide pieces, fewer rows than a block's waves
     dict(d_model=2056, n_head=257, d_ff=36, vocab=70, max_pos=7, batch=3, seq=5),      # rows past what a wave holds
     dict(d_model=24, n_head=3, d_ff=35, vocab=33, max_pos=33, batch=7, seq=33),        # odd feed-forward width: entries left over by the four-wide activation
+    dict(d_model=8, n_head=1, d_ff=8, vocab=52001, max_pos=4, batch=2, seq=3),         # more logits per row than a block of the cross-entropy rule holds
 ], ids=lambda k: f"d{k['d_model']}t{k['seq']}")
 def test_fp32_gradients_at_the_edges_of_the_row_rules(kw):
     """Same comparison and bound as above, one block, at the sizes where the row-wise rules change form."""
