@@ -363,13 +363,14 @@ zgr_status zgr_debug_cossin_table(int32_t gauss_bits, float* cos_out, float* sin
 zgr_status zgr_debug_gemm(int32_t dtype, const void* A, const void* W, const void* bias, void* out, int32_t epilogue,
                           int32_t M, int32_t N, int32_t K, void* hip_stream);
 
-/* One fp32 product of the cloud's backward pass as the library runs it, all DEVICE: C[i][j] = alpha sum_k A[i][k] B[k][j] in
+/* One fp32 product (of the cloud's backward pass, or a small projection of an fp32 model) as the library runs it, all DEVICE: C[i][j] = epilogue(alpha sum_k A[i][k] B[k][j] + bias[j]) in
  * `batches` batches (batch z starts z * a_batch, b_batch, c_batch elements further).  *_dtype: 0 fp32, 1 bf16; *_k: contiguous along
  * k (ld strides the other index) or along the other index (ld strides k).  a_sums (may be NULL): a_sums[i] = sum_k A[i][k] for an
- * fp32 A that is not contiguous along k, one batch.  scratch (may be NULL): floats for the parts of a split sum.        */
+ * fp32 A that is not contiguous along k, one batch.  scratch (may be NULL): floats for the parts of a split sum.
+ * epilogue: 0 store, 1 GELU, 2 add into C, 5 ReLU; bias (fp32) may be NULL.  */
 zgr_status zgr_debug_product(const void* A, int32_t a_dtype, int32_t a_k, int64_t lda, int64_t a_batch, const void* B, int32_t b_dtype, int32_t b_k,
                              int64_t ldb, int64_t b_batch, float* C, int64_t ldc, int64_t c_batch, int32_t M, int32_t N, int32_t K, float alpha,
-                             int32_t batches, float* a_sums, float* scratch, size_t scratch_floats, void* hip_stream);
+                             int32_t batches, float* a_sums, int32_t epilogue, const float* bias, float* scratch, size_t scratch_floats, void* hip_stream);
 
 /* Plain device-to-device copy of `bytes` bytes (a multiple of 16) by a simple kernel: the known-size
  * reference that hardware traffic counters are calibrated against.                                      */

@@ -526,6 +526,9 @@ zgr_status forward_loss(zgr_ctx* c, const zgr_batch* b, int slot) {
   const bool lm = m.arch == ZGR_ARCH_DECODER_LM;
   { ProfScope ps(c, ZGR_K_EMBED); HIP_TRY(c, launch_embed(dt, tok, T(c, c->tok_emb), T(c, c->pos_emb), x, M, b->seq, d, m.vocab, s)); }
   const int act_epi = m.act == ZGR_ACT_RELU ? EPI_RELU : EPI_GELU;
+  // fp32 models: a buffer whose contents a product neither reads nor still has use for holds the parts of its split sum
+  float* ff_scratch = dt == ZGR_F32 ? reinterpret_cast<float*>(ffb) : nullptr;
+  float* qkv_scratch = dt == ZGR_F32 ? reinterpret_cast<float*>(qkv) : nullptr;
   // post_ln: the residual stream x is itself normalised after every sum (and after the embeddings), and h is its copy
   // in the storage type; otherwise h = LN(x) feeds each sublayer and x stays the raw sum.
   float* xn = m.post_ln ? x : nullptr;
@@ -533,14 +536,14 @@ zgr_status forward_loss(zgr_ctx* c, const zgr_batch* b, int slot) {
   for (int l = 0; l < m.n_layer; ++l) {
     const Layer& L = c->layers[l];
     if (!m.post_ln) { ProfScope ps(c, ZGR_K_NORM); HIP_TRY(c, launch_layernorm(dt, x, T(c, L.ln1_g), T(c, L.ln1_b), h, M, d, m.ln_eps, s)); }
-    { ProfScope ps(c, ZGR_K_GEMM); HIP_TRY(c, launch_gemm(dt, h, T(c, L.wq), T(c, L.bq), qkv, EPI_STORE, M, 3 * d, d, s)); }
+    { ProfScope ps(c, ZGR_K_GEMM); HIP_TRY(c, launch_gemm(dt, h, T(c, L.wq), T(c, L.bq), qkv, EPI_STORE, M, 3 * d, d, s, ff_scratch, (size_t)M * ff)); }
     { ProfScope ps(c, ZGR_K_ATTN); HIP_TRY(c, launch_attention(dt, qkv, ctx, lm ? nullptr : b->lengths, b->batch, b->seq, d, m.n_head, lm ? 1 : 0, s)); }
-    { ProfScope ps(c, ZGR_K_GEMM); HIP_TRY(c, launch_gemm(dt, ctx, T(c, L.wo), T(c, L.bo), x, EPI_RESID, M, d, d, s)); }
+    { ProfScope ps(c, ZGR_K_GEMM); HIP_TRY(c, launch_gemm(dt, ctx, T(c, L.wo), T(c, L.bo), x, EPI_RESID, M, d, d, s, qkv_scratch, (size_t)3 * M * d)); }
     { ProfScope ps(c, ZGR_K_NORM);
       HIP_TRY(c, m.post_ln ? launch_layernorm(dt, x, T(c, L.ln1_g), T(c, L.ln1_b), h, M, d, m.ln_eps, s, xn)
                            : launch_layernorm(dt, x, T(c, L.ln2_g), T(c, L.ln2_b), h, M, d, m.ln_eps, s)); }
-    { ProfScope ps(c, ZGR_K_GEMM); HIP_TRY(c, launch_gemm(dt, h, T(c, L.w1), T(c, L.b1), ffb, act_epi, M, ff, d, s)); }
-    { ProfScope ps(c, ZGR_K_GEMM); HIP_TRY(c, launch_gemm(dt, ffb, T(c, L.w2), T(c, L.b2), x, EPI_RESID, M, d, ff, s)); }
+    { ProfScope ps(c, ZGR_K_GEMM); HIP_TRY(c, launch_gemm(dt, h, T(c, L.w1), T(c, L.b1), ffb, act_epi, M, ff, d, s, qkv_scratch, (size_t)3 * M * d)); }
+    { ProfScope ps(c, ZGR_K_GEMM); HIP_TRY(c, launch_gemm(dt, ffb, T(c, L.w2), T(c, L.b2), x, EPI_RESID, M, d, ff, s, qkv_scratch, (size_t)3 * M * d)); }
     if (m.post_ln) { ProfScope ps(c, ZGR_K_NORM); HIP_TRY(c, launch_layernorm(dt, x, T(c, L.ln2_g), T(c, L.ln2_b), h, M, d, m.ln_eps, s, xn)); }
   }
   if (!m.post_ln) { ProfScope ps(c, ZGR_K_NORM); HIP_TRY(c, launch_layernorm(dt, x, T(c, c->lnf_g), T(c, c->lnf_b), h, M, d, m.ln_eps, s)); }
@@ -1410,15 +1413,15 @@ zgr_status zgr_debug_gemm(int32_t dtype, const void* A, const void* W, const voi
 }
 
 zgr_status zgr_debug_product(const void* A, int32_t a_dtype, int32_t a_k, int64_t lda, int64_t a_batch, const void* B, int32_t b_dtype, int32_t b_k, int64_t ldb, int64_t b_batch,
-                             float* C, int64_t ldc, int64_t c_batch, int32_t M, int32_t N, int32_t K, float alpha, int32_t batches, float* a_sums, float* scratch, size_t scratch_floats,
-                             void* hip_stream) {
+                             float* C, int64_t ldc, int64_t c_batch, int32_t M, int32_t N, int32_t K, float alpha, int32_t batches, float* a_sums, int32_t epilogue, const float* bias, float* scratch,
+                             size_t scratch_floats, void* hip_stream) {
   if (!A || !B || !C) return fail(nullptr, ZGR_ERR_NULL, "a pointer is NULL");
   if (M < 1 || N < 1 || K < 1 || batches < 1 || batches > 65535) return fail(nullptr, ZGR_ERR_SHAPE, "bad shape");
   ProductArgs p;
   p.A = A; p.a_dtype = a_dtype; p.a_k = a_k != 0; p.lda = lda; p.a_outer = a_batch;
   p.B = B; p.b_dtype = b_dtype; p.b_k = b_k != 0; p.ldb = ldb; p.b_outer = b_batch;
   p.C = C; p.ldc = ldc; p.c_outer = c_batch; p.M = M; p.N = N; p.K = K; p.alpha = alpha; p.batches = batches;
-  p.a_sums = a_sums; p.scratch = scratch; p.scratch_floats = scratch_floats;
+  p.a_sums = a_sums; p.epilogue = epilogue; p.bias = bias; p.scratch = scratch; p.scratch_floats = scratch_floats;
   HIP_TRY(nullptr, launch_product(p, reinterpret_cast<hipStream_t>(hip_stream)));
   return ZGR_OK;
 }

@@ -7,6 +7,7 @@
 // Storage type T of weights and GEMM inputs is fp32 or bf16; accumulation, the
 // residual stream, LayerNorm, softmax and the loss are fp32, the final mean fp64.
 #include "forward.h"
+#include "product.h"
 #include <atomic>
 
 namespace zgr {
@@ -1098,13 +1099,21 @@ hipError_t launch_layernorm(int dtype, const float* x, const void* g, const void
   return hipGetLastError();
 }
 
-hipError_t launch_gemm(int dtype, const void* A, const void* W, const void* bias, void* out, int epi, int M, int N, int K, hipStream_t s) {
+hipError_t launch_gemm(int dtype, const void* A, const void* W, const void* bias, void* out, int epi, int M, int N, int K, hipStream_t s, float* scratch, size_t scratch_floats) {
   GemmEpi ep{epi, out, bias};
   if (dtype == 0) {
     const bool mfma_ok = K % 4 == 0 && (((uintptr_t)A | (uintptr_t)W) & 15) == 0;
     const long t128 = (long)((M + 127) / 128) * ((N + 127) / 128);
     if (mfma_ok && t128 >= 512)   // enough 128 x 128 tiles for two blocks on every CU
       hipLaunchKernelGGL((gemm_f32_mfma_kernel<2, 16>), dim3((N + 127) / 128, (M + 127) / 128), dim3(256), 0, s, (const float*)A, (const float*)W, M, N, K, ep);
+    else if (mfma_ok && (long)((M + 63) / 64) * ((N + 63) / 64) < 512) {
+      // too few 64 x 64 tiles to fill the chip: sums split among waves and blocks (1000^3: 28 us against 44, 1024 x 768 x 3072: 57 against 88;
+      // from about 512 tiles on the LDS-tiled kernel is the faster one: 2048 x 2304 x 768, 1152 tiles, 81 us against 93)
+      ProductArgs p;
+      p.A = A; p.lda = K; p.B = W; p.b_k = true; p.ldb = K; p.C = (float*)out; p.ldc = N; p.M = M; p.N = N; p.K = K;
+      p.epilogue = epi; p.bias = (const float*)bias; p.scratch = scratch; p.scratch_floats = scratch_floats;
+      return launch_product(p, s);
+    }
     else if (mfma_ok)
       hipLaunchKernelGGL((gemm_f32_mfma_kernel<1, 16>), dim3((N + 63) / 64, (M + 63) / 64), dim3(256), 0, s, (const float*)A, (const float*)W, M, N, K, ep);
     else

@@ -1,12 +1,12 @@
 // Matrix products with fp32 accumulation on operands as they lie in memory (product.hip): the fp32 and the
-// odd-sized products of the cloud's backward pass.
+// odd-sized products of the cloud's backward pass, and the small projections of fp32 models.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 namespace zgr {
 
-// C[i][j] = alpha sum_k A[i][k] B[k][j] for every batch z: operand X of batch z starts at X + (z / zdiv) x_outer + (z % zdiv) x_inner elements.
+// C[i][j] = epilogue(alpha sum_k A[i][k] B[k][j] + bias[j]) for every batch z: operand X of batch z starts at X + (z / zdiv) x_outer + (z % zdiv) x_inner elements.
 // An operand is fp32 or bf16 (dtype 0 / 1) and contiguous along k or along its other index; ld is the stride of the one that is not.
 struct ProductArgs {
   const void* A = nullptr; int a_dtype = 0; bool a_k = true; int64_t lda = 0;       // a_k: A[i][k] at A + i lda + k, else A + k lda + i
@@ -14,6 +14,8 @@ struct ProductArgs {
   float* C = nullptr; int64_t ldc = 0;
   int M = 0, N = 0, K = 0;
   float alpha = 1.0f;
+  int epilogue = 0;                 // forward.h: EPI_STORE (or EPI_F32), EPI_GELU, EPI_RELU, EPI_RESID (C += ...)
+  const float* bias = nullptr;      // fp32 [N], may be NULL
   float* a_sums = nullptr;          // when not NULL: a_sums[i] = sum_k A[i][k] (fp32 A contiguous along i, one batch)
   int batches = 1, zdiv = 1;
   int64_t a_outer = 0, a_inner = 0, b_outer = 0, b_inner = 0, c_outer = 0, c_inner = 0;

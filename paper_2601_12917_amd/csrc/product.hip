@@ -1,6 +1,7 @@
-// C = alpha A B with fp32 products and sums on the matrix cores (v_mfma_f32_16x16x4_f32), for operands as they lie: fp32 or bf16,
+// C = epilogue(alpha A B + bias) with fp32 products and sums on the matrix cores (v_mfma_f32_16x16x4_f32), for operands as they lie: fp32 or bf16,
 // contiguous along the summed index or along the other one, any sizes.  These are the backward products of fp32 models and of
-// bf16 models whose token count is no multiple of 64, and the five products per head of the attention rule.
+// bf16 models whose token count is no multiple of 64, the five products per head of the attention rule, and the projections of fp32
+// models that are too small for forward.hip's tiles to fill the chip.
 //
 // A wave owns a 64 x 64 piece of C and loads its operands from global memory straight into the instruction's layout: lane
 // (i = lane % 16, kg = lane / 16) supplies element i of the free index and kg of the summed one.  A step takes 16 terms,
@@ -13,6 +14,7 @@
 // instructions of the SIMD's other waves).  The LDS-tiled vector kernel this replaces reached 5 TFLOP/s on 231 tokens of a
 // 1024-wide model, where its grid left most of the chip idle (54 of the pass's 60 ms; the whole pass now takes 10).
 #include "product.h"
+#include "forward.h"
 
 namespace zgr {
 
@@ -64,7 +66,7 @@ template <> struct Raw4<bf16_t> {
   }
 };
 
-constexpr int kTile = 64, kStep = 16, kWaves = 2048;
+constexpr int kStep = 16, kWaves = 2048;
 struct Yes { static constexpr bool value = true; };
 struct No { static constexpr bool value = false; };
 
@@ -73,32 +75,46 @@ struct KernelArgs {
   int64_t lda, ldb, ldc;
   int M, N, K;
   float alpha;
+  int epilogue; const float* bias;
   int split;                 // waves that share a piece of C, each taking every split-th step: 1 (a block is 2 x 2 pieces), 4 or 8 (one piece)
-  int k_part;                // terms of one part of the sum: part z writes its result at C + z c_part (a_sums + z M), batches = 1
+  int k_part;                // terms of one part of the sum: part z writes its result at C + z c_part (a_sums + z M) when batches = 1
   int64_t c_part;
   int batched, zdiv;
   int64_t a_outer, a_inner, b_outer, b_inner, c_outer, c_inner;
 };
 
+__device__ __forceinline__ void finish(float* c, float v, int epilogue, const float* bias, int j) {
+  if (bias) v += bias[j];
+  switch (epilogue) {                                            // uniform
+    case EPI_GELU:  *c = 0.5f * v * (1.0f + erff(v * 0.70710678118654752f)); break;
+    case EPI_RELU:  *c = fmaxf(v, 0.f); break;
+    case EPI_RESID: *c += v; break;
+    default:        *c = v; break;
+  }
+}
+
 // NEAR: the byte offsets of a step fit 32 bits, an operand contiguous along its free index has at least four entries of it, and bf16
 // operands lie on 4 bytes; the other form loads element by element.
-template <typename TA, typename TB, bool AK, bool BK, bool NEAR>
+template <typename TA, typename TB, bool AK, bool BK, bool NEAR, int TT>
 __global__ void __launch_bounds__(512, 2) product_kernel(KernelArgs p) {
+  static_assert(TT == 4 || (AK && BK), "an operand contiguous along its free index brings four tiles per load");
+  constexpr int kTile = 16 * TT, TILES = TT * TT;
   extern __shared__ __attribute__((aligned(16))) float lds[];
   const int lane = threadIdx.x & 63, wave = uniform((int)threadIdx.x >> 6), il = lane & 15, kg = lane >> 4;
   const TA* A = reinterpret_cast<const TA*>(p.A);
   const TB* B = reinterpret_cast<const TB*>(p.B);
   float* C = p.C;
   int k_begin = 0, k_end = p.K;
+  const int z = (int)blockIdx.z;
   if (p.batched) {
-    const int zo = uniform((int)blockIdx.z / p.zdiv), zi = (int)blockIdx.z - zo * p.zdiv;
+    const int zo = uniform(z / p.zdiv), zi = z - zo * p.zdiv;
     A += zo * p.a_outer + zi * p.a_inner;
     B += zo * p.b_outer + zi * p.b_inner;
     C += zo * p.c_outer + zi * p.c_inner;
   } else {
-    k_begin = (int)blockIdx.z * p.k_part;
+    k_begin = z * p.k_part;
     k_end = p.K < k_begin + p.k_part ? p.K : k_begin + p.k_part;
-    C += blockIdx.z * p.c_part;
+    C += z * p.c_part;
   }
   const bool alone = p.split == 1;
   const int tm = alone ? (int)blockIdx.y * 2 + (wave >> 1) : (int)blockIdx.y, tn = alone ? (int)blockIdx.x * 2 + (wave & 1) : (int)blockIdx.x;
@@ -111,48 +127,55 @@ __global__ void __launch_bounds__(512, 2) product_kernel(KernelArgs p) {
   auto first_j = [&](int q) { const int j = j0 + 4 * q; return NEAR && j > p.N - 4 ? p.N - 4 : j; };
   auto row_i = [&](int t, int q) { const int i = AK ? i0 + 16 * t + q : first_i(q) + t; return i < p.M ? i : p.M - 1; };
   auto row_j = [&](int t, int q) { const int j = BK ? j0 + 16 * t + q : first_j(q) + t; return j < p.N ? j : p.N - 1; };
-  uint32_t ao[4], bo[4];
+  constexpr int LA = AK ? TT : 4, LB = BK ? TT : 4;              // loads per step
+  uint32_t ao[LA], bo[LB];
 #pragma unroll
-  for (int t = 0; t < 4; ++t) {
+  for (int t = 0; t < LA; ++t)
     ao[t] = (uint32_t)sizeof(TA) * (AK ? (uint32_t)(row_i(t, il) - i0) * (uint32_t)p.lda + 4u * kg : (uint32_t)(4 * kg + t) * (uint32_t)p.lda + (uint32_t)first_i(il));
+#pragma unroll
+  for (int t = 0; t < LB; ++t)
     bo[t] = (uint32_t)sizeof(TB) * (BK ? (uint32_t)(row_j(t, il) - j0) * (uint32_t)p.ldb + 4u * kg : (uint32_t)(4 * kg + t) * (uint32_t)p.ldb + (uint32_t)first_j(il));
-  }
   const TA* a_base = AK ? A + (int64_t)i0 * p.lda : A;
   const TB* b_base = BK ? B + (int64_t)j0 * p.ldb : B;
   auto a_at = [&](int i, int k) { return to_f32(AK ? A[(int64_t)i * p.lda + k] : A[(int64_t)k * p.lda + i]); };
   auto b_at = [&](int j, int k) { return to_f32(BK ? B[(int64_t)j * p.ldb + k] : B[(int64_t)k * p.ldb + j]); };
-  f32x4 acc[4][4], sums[4];
+  f32x4 acc[TT][TT], sums[TT];
 #pragma unroll
-  for (int t = 0; t < 4; ++t) {
+  for (int t = 0; t < TT; ++t) {
     sums[t] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int n = 0; n < 4; ++n) acc[t][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int n = 0; n < TT; ++n) acc[t][n] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  struct Operands { Raw4<TA> a[4]; Raw4<TB> b[4]; };
+  struct Operands { Raw4<TA> a[LA]; Raw4<TB> b[LB]; };
   auto fetch = [&](int k0, Operands& o) {
     if constexpr (NEAR) {
       const TA* ak = a_base + (AK ? (int64_t)k0 : k0 * p.lda);
       const TB* bk = b_base + (BK ? (int64_t)k0 : k0 * p.ldb);
 #pragma unroll
-      for (int t = 0; t < 4; ++t) { o.a[t].load(ak, ao[t]); o.b[t].load(bk, bo[t]); }
+      for (int t = 0; t < LA; ++t) o.a[t].load(ak, ao[t]);
+#pragma unroll
+      for (int t = 0; t < LB; ++t) o.b[t].load(bk, bo[t]);
     }
   };
   // x[t] holds what load t brought: tile t, terms s (contiguous along k) or term t, tiles s
-  auto multiply4 = [&](const f32x4 (&a)[4], const f32x4 (&b)[4], auto with_sums) {
+  auto multiply4 = [&](const f32x4 (&a)[LA], const f32x4 (&b)[LB], auto with_sums) {
 #pragma unroll
     for (int s = 0; s < 4; ++s)
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
+      for (int t = 0; t < TT; ++t) {
         const float av = AK ? a[t][s] : a[s][t];
 #pragma unroll
-        for (int n = 0; n < 4; ++n) acc[t][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, BK ? b[n][s] : b[s][n], acc[t][n], 0, 0, 0);
+        for (int n = 0; n < TT; ++n) acc[t][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, BK ? b[n][s] : b[s][n], acc[t][n], 0, 0, 0);
         if (decltype(with_sums)::value) sums[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, 1.0f, sums[t], 0, 0, 0);
       }
   };
   auto loop = [&](auto with_sums) {
     auto multiply = [&](const Operands& o) {
-      const f32x4 a[4] = {o.a[0].widen(), o.a[1].widen(), o.a[2].widen(), o.a[3].widen()};
-      const f32x4 b[4] = {o.b[0].widen(), o.b[1].widen(), o.b[2].widen(), o.b[3].widen()};
+      f32x4 a[LA], b[LB];
+#pragma unroll
+      for (int t = 0; t < LA; ++t) a[t] = o.a[t].widen();
+#pragma unroll
+      for (int t = 0; t < LB; ++t) b[t] = o.b[t].widen();
       multiply4(a, b, with_sums);
     };
     const int stride = p.split * kStep, full = k_begin + (k_end - k_begin) / kStep * kStep;
@@ -178,15 +201,14 @@ __global__ void __launch_bounds__(512, 2) product_kernel(KernelArgs p) {
     }
     // the terms left over (the wave whose turn it is; every step in the element-by-element form): zeros past the end
     for (; k0 < k_end; k0 += stride) {
-      f32x4 a[4], b[4];
+      f32x4 a[LA], b[LB];
 #pragma unroll
-      for (int t = 0; t < 4; ++t)
+      for (int s = 0; s < 4; ++s) {
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-          const int ka = k0 + 4 * kg + (AK ? s : t), kb = k0 + 4 * kg + (BK ? s : t);
-          a[t][s] = ka < k_end ? a_at(row_i(AK ? t : s, il), ka) : 0.f;
-          b[t][s] = kb < k_end ? b_at(row_j(BK ? t : s, il), kb) : 0.f;
-        }
+        for (int t = 0; t < LA; ++t) { const int k = k0 + 4 * kg + (AK ? s : t); a[t][s] = k < k_end ? a_at(row_i(AK ? t : s, il), k) : 0.f; }
+#pragma unroll
+        for (int t = 0; t < LB; ++t) { const int k = k0 + 4 * kg + (BK ? s : t); b[t][s] = k < k_end ? b_at(row_j(BK ? t : s, il), k) : 0.f; }
+      }
       multiply4(a, b, with_sums);
     }
   };
@@ -199,72 +221,108 @@ __global__ void __launch_bounds__(512, 2) product_kernel(KernelArgs p) {
       __syncthreads();
       if (wave >= half && wave < 2 * half)
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
+        for (int t = 0; t < TT; ++t)
 #pragma unroll
-          for (int n = 0; n < 4; ++n) *reinterpret_cast<f32x4*>(lds + (((wave - half) * 16 + t * 4 + n) * 64 + lane) * 4) = acc[t][n];
+          for (int n = 0; n < TT; ++n) *reinterpret_cast<f32x4*>(lds + (((wave - half) * TILES + t * TT + n) * 64 + lane) * 4) = acc[t][n];
       __syncthreads();
       if (wave < half)
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
+        for (int t = 0; t < TT; ++t)
 #pragma unroll
-          for (int n = 0; n < 4; ++n) acc[t][n] += *reinterpret_cast<const f32x4*>(lds + ((wave * 16 + t * 4 + n) * 64 + lane) * 4);
+          for (int n = 0; n < TT; ++n) acc[t][n] += *reinterpret_cast<const f32x4*>(lds + ((wave * TILES + t * TT + n) * 64 + lane) * 4);
       if (want_sums) {                                           // uniform over the block
         __syncthreads();
         if (wave >= half && wave < 2 * half)
 #pragma unroll
-          for (int t = 0; t < 4; ++t) *reinterpret_cast<f32x4*>(lds + (((wave - half) * 4 + t) * 64 + lane) * 4) = sums[t];
+          for (int t = 0; t < TT; ++t) *reinterpret_cast<f32x4*>(lds + (((wave - half) * TT + t) * 64 + lane) * 4) = sums[t];
         __syncthreads();
         if (wave < half)
 #pragma unroll
-          for (int t = 0; t < 4; ++t) sums[t] += *reinterpret_cast<const f32x4*>(lds + ((wave * 4 + t) * 64 + lane) * 4);
+          for (int t = 0; t < TT; ++t) sums[t] += *reinterpret_cast<const f32x4*>(lds + ((wave * TT + t) * 64 + lane) * 4);
       }
     }
-    if (wave != 0) return;
   }
   // lane (il, kg) holds column il of a tile and its rows 4 kg + v.  A lane that took entries before its own stores its own only.
-  const float alpha = p.alpha;
-  if (want_sums && il == 0)
+  if (want_sums && il == 0 && share == 0)
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
+    for (int t = 0; t < TT; ++t)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int i = first_i(4 * kg + v) + t;
-        if (i >= i0 + 4 * (4 * kg + v) && i < p.M) p.a_sums[(int64_t)blockIdx.z * p.M + i] = sums[t][v];
+        if (i >= i0 + 4 * (4 * kg + v) && i < p.M) p.a_sums[(int64_t)z * p.M + i] = sums[t][v];
       }
+  // Rows 4 kg + v0 .. 4 kg + v0 + count - 1 of the tiles (t, 0 .. TT - 1).  A whole piece without an epilogue takes no condition per
+  // entry, and 16-byte stores where a lane's columns are consecutive.
+  const float alpha = p.alpha;
+  const bool plain = !p.bias && (p.epilogue == EPI_STORE || p.epilogue == EPI_F32) && i0 + kTile <= p.M && j0 + kTile <= p.N;
+  auto row_of = [&](int t, int v) { return AK ? i0 + 16 * t + 4 * kg + v : first_i(4 * kg + v) + t; };
+  auto store = [&](int t, int v, const float (&x)[TT]) {
+    const int i = row_of(t, v);
+    if (plain) {
+      float* c = C + (int64_t)i * p.ldc + j0;
+      if constexpr (BK) {
 #pragma unroll
-  for (int t = 0; t < 4; ++t)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int i = AK ? i0 + 16 * t + 4 * kg + v : first_i(4 * kg + v) + t;
-      if (i >= p.M || (!AK && i < i0 + 4 * (4 * kg + v))) continue;
-      float* row = C + (int64_t)i * p.ldc;
-#pragma unroll
-      for (int n = 0; n < 4; ++n) {
-        const int j = BK ? j0 + 16 * n + il : first_j(il) + n;
-        if (j < p.N && (BK || j >= j0 + 4 * il)) row[j] = alpha * acc[t][n][v];
+        for (int n = 0; n < TT; ++n) c[16 * n + il] = alpha * x[n];
+      } else {
+        typedef f32x4 __attribute__((aligned(4))) f32x4_u;
+        *reinterpret_cast<f32x4_u*>(c + 4 * il) = f32x4{alpha * x[0], alpha * x[1], alpha * x[2], alpha * x[3]};
       }
+      return;
     }
+    if (i >= p.M || (!AK && i < i0 + 4 * (4 * kg + v))) return;
+#pragma unroll
+    for (int n = 0; n < TT; ++n) {
+      const int j = BK ? j0 + 16 * n + il : first_j(il) + n;
+      if (j < p.N && (BK || j >= j0 + 4 * il)) finish(C + (int64_t)i * p.ldc + j, alpha * x[n], p.epilogue, p.bias, j);
+    }
+  };
+  if (alone) {
+#pragma unroll
+    for (int t = 0; t < TT; ++t)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        float x[TT];
+#pragma unroll
+        for (int n = 0; n < TT; ++n) x[n] = acc[t][n][v];
+        store(t, v, x);
+      }
+  } else {                                                       // the waves share out the rows
+    __syncthreads();
+    if (wave == 0)
+#pragma unroll
+      for (int t = 0; t < TT; ++t)
+#pragma unroll
+        for (int n = 0; n < TT; ++n) *reinterpret_cast<f32x4*>(lds + ((t * TT + n) * 64 + lane) * 4) = acc[t][n];
+    __syncthreads();
+    const int count = 4 * TT / p.split;
+    for (int r = wave * count; r < (wave + 1) * count; ++r) {
+      float x[TT];
+#pragma unroll
+      for (int n = 0; n < TT; ++n) x[n] = lds[(((r >> 2) * TT + n) * 64 + lane) * 4 + (r & 3)];
+      store(r >> 2, r & 3, x);
+    }
+  }
 }
 
-// C[i][j] = alpha (part 0 + part 1 + ...)[i][j], a_sums likewise without alpha: the parts in their order
+// C[i][j] = epilogue(alpha (part 0 + part 1 + ...)[i][j] + bias[j]), a_sums likewise without alpha: the parts in their order
 __global__ void __launch_bounds__(256) product_sum_kernel(const float* __restrict__ part, int parts, int64_t n, int N, float* __restrict__ C, int64_t ldc, float alpha,
-                                                          const float* __restrict__ sum_part, int M, float* __restrict__ a_sums) {
+                                                          const float* __restrict__ sum_part, int M, float* __restrict__ a_sums, int epilogue, const float* __restrict__ bias) {
   for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < n + (a_sums ? M : 0); e += (int64_t)gridDim.x * 256) {
     const float* src = e < n ? part + e : sum_part + (e - n);
     const int64_t stride = e < n ? n : M;
     float v = 0.f;
 #pragma unroll 4
     for (int z = 0; z < parts; ++z) v += src[(int64_t)z * stride];
-    if (e < n) C[e / N * ldc + e % N] = alpha * v; else a_sums[e - n] = v;
+    if (e < n) finish(C + e / N * ldc + e % N, alpha * v, epilogue, bias, (int)(e % N)); else a_sums[e - n] = v;
   }
 }
 
-template <typename TA, typename TB, bool AK, bool BK>
+template <typename TA, typename TB, bool AK, bool BK, int TT = 4>
 hipError_t launch_t(const KernelArgs& k, bool near, dim3 grid, hipStream_t s) {
   const unsigned threads = k.split == 8 ? 512 : 256;
-  const size_t lds = k.split == 1 ? 0 : (size_t)(k.split / 2) * 16 * 64 * 16;       // 64 KB at most
-  if (near) hipLaunchKernelGGL((product_kernel<TA, TB, AK, BK, true>), grid, dim3(threads), lds, s, k);
-  else      hipLaunchKernelGGL((product_kernel<TA, TB, AK, BK, false>), grid, dim3(threads), lds, s, k);
+  const size_t lds = k.split == 1 ? 0 : (size_t)(k.split / 2) * TT * TT * 64 * 16;       // 64 KB at most
+  if (near) hipLaunchKernelGGL((product_kernel<TA, TB, AK, BK, true, TT>), grid, dim3(threads), lds, s, k);
+  else      hipLaunchKernelGGL((product_kernel<TA, TB, AK, BK, false, TT>), grid, dim3(threads), lds, s, k);
   return hipGetLastError();
 }
 
@@ -282,21 +340,28 @@ bool near_operand(const void* p, int dtype, bool along_k, int64_t ld, int n, int
 hipError_t launch_product(const ProductArgs& p, hipStream_t s) {
   if (p.M < 1 || p.N < 1 || p.batches < 1) return hipSuccess;
   if (p.K < 0 || p.batches > 65535 || p.zdiv < 1 || (p.a_sums && (p.a_k || p.a_dtype != 0 || p.batches != 1))) return hipErrorInvalidValue;
-  const int64_t tm = ((int64_t)p.M + kTile - 1) / kTile, tn = ((int64_t)p.N + kTile - 1) / kTile, pieces = tm * tn * p.batches;
-  if (tm > 65535) return hipErrorInvalidValue;
+  const int64_t tiles = (((int64_t)p.M + 63) / 64) * (((int64_t)p.N + 63) / 64) * p.batches;
   const int steps = (p.K + kStep - 1) / kStep;
   // Two waves per SIMD hide each other's loads (one: 10.35 ms for the backward pass of a 24-block, 1024-wide encoder on 231 tokens, two:
-  // 10.06).  Fewer pieces than that: four or eight waves share each, and
-  // where that still leaves SIMDs empty the sum is also split over blocks, each share at least eight steps.
-  const int split = pieces >= kWaves || steps < 4 ? 1 : (pieces * 4 >= kWaves || steps < 32 ? 4 : 8);
+  // 10.06).  With fewer pieces than that four waves share each, or eight where blocks of four would leave CUs with one (385 x 768 x 768:
+  // 20.4 us with eight, 385 x 3072 x 768: 36 with four, 40 with eight).  Where that is still too few the sum is split over
+  // blocks as well, each share at least eight steps (385 x 768 x 3072: 55 us undivided, 33 in three parts).
+  int split = tiles >= kWaves || steps < 4 ? 1 : (tiles >= 320 || steps < 32 ? 4 : 8);
   int parts = 1;
-  if (p.batches == 1 && p.scratch) {
-    int64_t z = kWaves / (pieces * split);
+  if (p.batches == 1 && p.scratch && split > 1) {
+    int64_t z = kWaves / (tiles * split);
     const int64_t room = (int64_t)(p.scratch_floats / ((size_t)p.M * ((size_t)p.N + 1)));
     if (z > steps / (8 * split)) z = steps / (8 * split);
     if (z > room) z = room;
     if (z > 1) parts = (int)z;
   }
+  // What is left with few pieces and an undivided sum takes 32 x 32 pieces, four times the blocks (512 x 128 x 512: 8.0 us against 16.6,
+  // 385 x 768 x 768: 15.9 against 20.4; at 252 pieces, 385 x 2304 x 768, they are slower: 28 against 22).
+  const bool small = p.a_k && p.b_k && p.a_dtype == 0 && p.b_dtype == 0 && p.batches == 1 && tiles <= 128 && parts == 1;
+  if (small && split > 1) split = 4;
+  const int tile = small ? 32 : 64;
+  const int64_t tm = ((int64_t)p.M + tile - 1) / tile, tn = ((int64_t)p.N + tile - 1) / tile;
+  if (tm > 65535) return hipErrorInvalidValue;
   KernelArgs k{};
   k.A = p.A; k.B = p.B; k.lda = p.lda; k.ldb = p.ldb; k.M = p.M; k.N = p.N; k.K = p.K; k.split = split;
   k.batched = p.batches > 1; k.zdiv = p.zdiv;
@@ -305,8 +370,8 @@ hipError_t launch_product(const ProductArgs& p, hipStream_t s) {
   if (k.k_part < 1) k.k_part = 1;
   const int64_t n = (int64_t)p.M * p.N;
   float* sum_part = p.scratch + (int64_t)parts * n;
-  if (parts > 1) { k.C = p.scratch; k.ldc = p.N; k.alpha = 1.0f; k.c_part = n; k.a_sums = p.a_sums ? sum_part : nullptr; }
-  else           { k.C = p.C; k.ldc = p.ldc; k.alpha = p.alpha; k.a_sums = p.a_sums; }
+  if (parts > 1) { k.C = p.scratch; k.ldc = p.N; k.alpha = 1.0f; k.epilogue = EPI_STORE; k.c_part = n; k.a_sums = p.a_sums ? sum_part : nullptr; }
+  else           { k.C = p.C; k.ldc = p.ldc; k.alpha = p.alpha; k.epilogue = p.epilogue; k.bias = p.bias; k.a_sums = p.a_sums; }
   const bool near = near_operand(p.A, p.a_dtype, p.a_k, p.lda, p.M, p.a_outer, p.a_inner) && near_operand(p.B, p.b_dtype, p.b_k, p.ldb, p.N, p.b_outer, p.b_inner);
   const dim3 grid((unsigned)(split == 1 ? (tn + 1) / 2 : tn), (unsigned)(split == 1 ? (tm + 1) / 2 : tm), (unsigned)(p.batches > 1 ? p.batches : parts));
   hipError_t e = hipErrorInvalidValue;
@@ -316,14 +381,14 @@ hipError_t launch_product(const ProductArgs& p, hipStream_t s) {
     case 0b0110: e = launch_t<float, bf16_t, true, false>(k, near, grid, s); break;
     case 0b0000: e = launch_t<float, float, false, false>(k, near, grid, s); break;
     case 0b0100: e = launch_t<float, bf16_t, false, false>(k, near, grid, s); break;
-    case 0b0011: e = launch_t<float, float, true, true>(k, near, grid, s); break;
+    case 0b0011: e = small ? launch_t<float, float, true, true, 2>(k, near, grid, s) : launch_t<float, float, true, true>(k, near, grid, s); break;
     case 0b0111: e = launch_t<float, bf16_t, true, true>(k, near, grid, s); break;
     case 0b1111: e = launch_t<bf16_t, bf16_t, true, true>(k, near, grid, s); break;
     default: break;
   }
   if (e != hipSuccess || parts == 1) return e;
   const int64_t total = n + (p.a_sums ? p.M : 0);
-  hipLaunchKernelGGL(product_sum_kernel, dim3((unsigned)(total / 256 + 1 < 2048 ? total / 256 + 1 : 2048)), dim3(256), 0, s, p.scratch, parts, n, p.N, p.C, p.ldc, p.alpha, sum_part, p.M, p.a_sums);
+  hipLaunchKernelGGL(product_sum_kernel, dim3((unsigned)(total / 256 + 1 < 2048 ? total / 256 + 1 : 2048)), dim3(256), 0, s, p.scratch, parts, n, p.N, p.C, p.ldc, p.alpha, sum_part, p.M, p.a_sums, p.epilogue, p.bias);
   return hipGetLastError();
 }
 

@@ -40,7 +40,7 @@ def test_product_matches_fp64(form, M, N, K, batches, pad):
     want, mag = -0.5 * torch.stack([x @ y for x, y in zip(ad, bd)]), 0.5 * torch.stack([x.abs() @ y.abs() for x, y in zip(ad, bd)])
     for use_scratch in (True, False):
         B.check(B.lib().zgr_debug_product(A.data_ptr(), int(a_t == "bf16"), a_k, A.shape[2], A[0].numel(), Bm.data_ptr(), int(b_t == "bf16"), b_k, Bm.shape[2], Bm[0].numel(),
-                                          out.data_ptr(), ldc, M * ldc, M, N, K, -0.5, batches, sums.data_ptr() if sums is not None else None,
+                                          out.data_ptr(), ldc, M * ldc, M, N, K, -0.5, batches, sums.data_ptr() if sums is not None else None, 0, None,
                                           scratch.data_ptr() if use_scratch else None, scratch.numel() if use_scratch else 0, torch.cuda.current_stream().cuda_stream))
         torch.cuda.synchronize()
         got = out.double().cpu()
@@ -49,3 +49,25 @@ def test_product_matches_fp64(form, M, N, K, batches, pad):
         assert torch.all((got[:, :, :N] - want).abs() <= bound * mag), float(((got[:, :, :N] - want).abs() / mag).max() / bound)
         if sums is not None:
             assert torch.all((sums.double().cpu() - ad[0].sum(1)).abs() <= bound * ad[0].abs().sum(1))
+
+
+@pytest.mark.parametrize("epilogue", [0, 1, 2, 5], ids=["store", "gelu", "add", "relu"])
+@pytest.mark.parametrize("M,N,K", [(5, 7, 12), (33, 95, 200), (70, 190, 1030), (130, 100, 4096), (300, 1100, 260), (2049, 4130, 36)])
+def test_product_epilogues(M, N, K, epilogue):
+    """The projections of fp32 models: out = act(A W^T + b) or out += A W^T + b, whole and split sums, both piece sizes.  |act'| <= 1.13."""
+    import torch
+    from paper_2601_12917_amd import binding as B
+    dev = "cuda:0"
+    gen = torch.Generator().manual_seed(M + N + K)
+    A, W, b, old = (torch.randn(*s, generator=gen) * f for s, f in (((M, K), 1.0), ((N, K), K ** -0.5), ((N,), 1.0), ((M, N), 1.0)))
+    x = A.double() @ W.double().T + b.double()
+    want = {0: x, 1: 0.5 * x * (1 + torch.erf(x / 2 ** 0.5)), 2: old.double() + x, 5: x.clamp(min=0)}[epilogue]
+    bound = 4 * np.sqrt(K + 16) * 2.0 ** -24 * 1.13 * (A.double().abs() @ W.double().abs().T + b.double().abs() + 1.0)
+    Ad, Wd, bd = A.to(dev), W.to(dev), b.to(dev)
+    scratch = torch.full((1 << 21,), float("nan"), device=dev)
+    for n in (scratch.numel(), 0):
+        out = old.to(dev).clone()
+        B.check(B.lib().zgr_debug_product(Ad.data_ptr(), 0, 1, K, 0, Wd.data_ptr(), 0, 1, K, 0, out.data_ptr(), N, 0, M, N, K, 1.0, 1, None, epilogue, bd.data_ptr(),
+                                          scratch.data_ptr() if n else None, n, torch.cuda.current_stream().cuda_stream))
+        torch.cuda.synchronize()
+        assert torch.all((out.double().cpu() - want).abs() <= bound)
