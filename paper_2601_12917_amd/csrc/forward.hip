@@ -788,56 +788,102 @@ hipError_t launch_gemm_bf16_t(const bf16_t* A, const bf16_t* W, const bf16_t* bi
 }
 
 // ------------------------------------------------------------------ attention
-// One thread per query row, one block per (batch, head, 256-query chunk); keys/values
-// stream through LDS in chunks of 32; online softmax in fp32.
+// fp32 on the matrix cores (v_mfma_f32_32x32x2_f32), for fp32 storage and for the head sizes the bf16 kernel below does not take.  One wave
+// per 32 queries of a head, keys in blocks of 32: S^T = K Q^T, then O^T += V^T P^T, everything in registers.  A lane supplies
+// half a row of K and of Q (the contraction index is split as d = half DH/2 + s), holds 16 keys of one query column of S^T, and its
+// probabilities are the second product's operand as they are: instruction v sums over the keys 8 (v / 4) + 4 half + v % 4, in which order
+// the rows of V are loaded.  Operands come straight from global memory: V while S^T is formed, the next block's K behind it.
+// Bound by load latency on short sequences and by the fp32 matrix rate on long ones.  (One thread per query with its row in registers left
+// 51 of 64 lanes idle at 77 tokens and walked the keys one by one: 75 us per layer for 60 heads of 64, now 11;
+// 8 x 4 heads of 32 at 64 tokens: 34 us, now 6.)
+template <typename T> struct alignas(sizeof(T) * 4) Quad { T e[4]; };
+template <typename T, int N> __device__ __forceinline__ void load_row(const T* p, float (&f)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; i += 4) {
+    const Quad<T> q = *reinterpret_cast<const Quad<T>*>(p + i);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) f[i + j] = to_f32(q.e[j]);
+  }
+}
 template <typename T, int DH>
-__global__ void __launch_bounds__(256) attention_kernel(const T* __restrict__ qkv, T* __restrict__ ctx, const int32_t* __restrict__ lengths,
-                                                        int seq, int d, int n_head, int causal) {
-  constexpr int KC = 32;
-  __shared__ float Ks[KC][DH], Vs[KC][DH];
-  const int chunks = (seq + 255) / 256;
-  const int qc = blockIdx.x % chunks, h = (blockIdx.x / chunks) % n_head, b = blockIdx.x / (chunks * n_head);
-  const int qi = qc * 256 + threadIdx.x;
-  const bool active = qi < seq;
-  const int len = lengths ? lengths[b] : seq;
+__global__ void __launch_bounds__(64, 2) attention_f32_kernel(const T* __restrict__ qkv, T* __restrict__ ctx, const int32_t* __restrict__ lengths,
+                                                           int seq, int d, int n_head, int causal, int heads) {
+  constexpr int HK = DH / 2, F = DH > 32 ? DH / 32 : 1;
+  const int lane = threadIdx.x, l32 = lane & 31, half = lane >> 5;
+  // causal: the last query blocks have the most keys and are handed out first
+  const int qblocks = (seq + 31) / 32, bh = (int)blockIdx.x % heads, qi0 = (int)blockIdx.x / heads;
+  const int q0 = 32 * (causal ? qblocks - 1 - qi0 : qi0), qi = q0 + l32;
+  const int h = bh % n_head, b = bh / n_head;
   const size_t ld = (size_t)3 * d;
   const T* base = qkv + (size_t)b * seq * ld + (size_t)h * DH;
-  float q[DH], acc[DH];
-  const float scale = 1.0f / sqrtf((float)DH);
+  int kend = lengths ? lengths[b] : seq;                             // visible to every query; then the causal mask
+  kend = kend < seq ? kend : seq;
+  const int last = causal && q0 + 32 < kend ? q0 + 32 : kend;        // keys of this wave
+  float q[HK], k[HK];
+  load_row(base + (size_t)(qi < seq ? qi : seq - 1) * ld + half * HK, q);
+  f32x16 o[F];
 #pragma unroll
-  for (int i = 0; i < DH; ++i) { q[i] = active ? to_f32(base[(size_t)qi * ld + i]) * scale : 0.f; acc[i] = 0.f; }
+  for (int f = 0; f < F; ++f)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) o[f][v] = 0.f;
   float mx = -INFINITY, den = 0.f;
-  int kend = len < seq ? len : seq;
-  if (causal) { const int last = qc * 256 + 255; kend = kend < last + 1 ? kend : last + 1; }
-  for (int k0 = 0; k0 < kend; k0 += KC) {
-    __syncthreads();
-    for (int i = threadIdx.x; i < KC * DH; i += 256) {
-      const int r = i / DH, c = i - r * DH;
-      const int kj = k0 + r;
-      Ks[r][c] = kj < seq ? to_f32(base[(size_t)kj * ld + d + c]) : 0.f;
-      Vs[r][c] = kj < seq ? to_f32(base[(size_t)kj * ld + 2 * d + c]) : 0.f;
-    }
-    __syncthreads();
-    if (!active) continue;
-    for (int r = 0; r < KC; ++r) {
-      const int kj = k0 + r;
-      if (kj >= kend || (causal && kj > qi)) break;
-      float s = 0.f;
+  const float scale_log2 = 1.44269504088896341f / sqrtf((float)DH);
+  // a key past the end repeats the last one: its probability is zero
+  auto k_row = [&](int k0) { const int key = k0 + l32; return base + (size_t)(key < last ? key : last - 1) * ld + d + half * HK; };
+  if (last > 0) load_row(k_row(0), k);
+  for (int k0 = 0; k0 < last; k0 += 32) {
+    float vv[16][F];
 #pragma unroll
-      for (int i = 0; i < DH; ++i) s = __builtin_fmaf(q[i], Ks[r][i], s);
-      const float nm = fmaxf(mx, s);
-      const float corr = __expf(mx - nm), p = __expf(s - nm);
-      den = den * corr + p;
+    for (int v = 0; v < 16; ++v) {
+      const int key = k0 + 8 * (v >> 2) + 4 * half + (v & 3);
+      const T* vr = base + (size_t)(key < last ? key : last - 1) * ld + 2 * d;
 #pragma unroll
-      for (int i = 0; i < DH; ++i) acc[i] = __builtin_fmaf(p, Vs[r][i], acc[i] * corr);
-      mx = nm;
+      for (int f = 0; f < F; ++f) vv[v][f] = DH >= 32 || l32 < DH ? to_f32(vr[32 * f + l32]) : 0.f;
     }
+    f32x16 s;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) s[v] = 0.f;
+#pragma unroll
+    for (int i = 0; i < HK; ++i) s = __builtin_amdgcn_mfma_f32_32x32x2f32(k[i], q[i], s, 0, 0, 0);
+    if (k0 + 32 < last) load_row(k_row(k0 + 32), k);
+    float mloc = -INFINITY;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int key = k0 + 8 * (v >> 2) + 4 * half + (v & 3);
+      s[v] = key < last && (!causal || key <= qi) ? s[v] * scale_log2 : -INFINITY;
+      mloc = fmaxf(mloc, s[v]);
+    }
+    mloc = fmaxf(mloc, __shfl_xor(mloc, 32, 64));
+    const float mnew = fmaxf(mx, mloc), msafe = mnew == -INFINITY ? 0.f : mnew;
+    const float corr = __builtin_amdgcn_exp2f(mx - msafe);           // mx = -inf -> 0
+    float sum = 0.f;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) { s[v] = __builtin_amdgcn_exp2f(s[v] - msafe); sum += s[v]; }
+    den = den * corr + sum;
+    mx = mnew;
+#pragma unroll
+    for (int f = 0; f < F; ++f)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) o[f][v] *= corr;
+#pragma unroll
+    for (int v = 0; v < 16; ++v)
+#pragma unroll
+      for (int f = 0; f < F; ++f) o[f] = __builtin_amdgcn_mfma_f32_32x32x2f32(vv[v][f], s[v], o[f], 0, 0, 0);
   }
-  if (active) {
-    T* o = ctx + ((size_t)b * seq + qi) * d + (size_t)h * DH;
+  den += __shfl_xor(den, 32, 64);
+  if (qi < seq) {
     const float inv = den > 0.f ? 1.0f / den : 0.f;
+    T* orow = ctx + ((size_t)b * seq + qi) * d + (size_t)h * DH;
 #pragma unroll
-    for (int i = 0; i < DH; ++i) from_f32(acc[i] * inv, o[i]);
+    for (int f = 0; f < F; ++f)
+#pragma unroll
+      for (int v4 = 0; v4 < 4; ++v4) {
+        const int c = 32 * f + 8 * v4 + 4 * half;                    // lane holds four consecutive entries of its query's row
+        Quad<T> r;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) from_f32(o[f][4 * v4 + i] * inv, r.e[i]);
+        if (c < DH) *reinterpret_cast<Quad<T>*>(orow + c) = r;
+      }
   }
 }
 
@@ -1159,12 +1205,13 @@ hipError_t launch_gemm_ce_bf16(const void* A, const void* W, const int32_t* targ
 template <typename T>
 static hipError_t launch_attention_t(const T* qkv, T* ctx, const int32_t* lengths, int batch, int seq, int d, int n_head, int causal, hipStream_t s) {
   const int dh = d / n_head;
-  const int grid = batch * n_head * ((seq + 255) / 256);
+  const int heads = batch * n_head;
+  const dim3 grid((unsigned)heads * (unsigned)((seq + 31) / 32));
   switch (dh) {
-    case 8:   hipLaunchKernelGGL((attention_kernel<T, 8>), dim3(grid), dim3(256), 0, s, qkv, ctx, lengths, seq, d, n_head, causal); break;
-    case 16:  hipLaunchKernelGGL((attention_kernel<T, 16>), dim3(grid), dim3(256), 0, s, qkv, ctx, lengths, seq, d, n_head, causal); break;
-    case 32:  hipLaunchKernelGGL((attention_kernel<T, 32>), dim3(grid), dim3(256), 0, s, qkv, ctx, lengths, seq, d, n_head, causal); break;
-    case 64:  hipLaunchKernelGGL((attention_kernel<T, 64>), dim3(grid), dim3(256), 0, s, qkv, ctx, lengths, seq, d, n_head, causal); break;
+    case 8:   hipLaunchKernelGGL((attention_f32_kernel<T, 8>), grid, dim3(64), 0, s, qkv, ctx, lengths, seq, d, n_head, causal, heads); break;
+    case 16:  hipLaunchKernelGGL((attention_f32_kernel<T, 16>), grid, dim3(64), 0, s, qkv, ctx, lengths, seq, d, n_head, causal, heads); break;
+    case 32:  hipLaunchKernelGGL((attention_f32_kernel<T, 32>), grid, dim3(64), 0, s, qkv, ctx, lengths, seq, d, n_head, causal, heads); break;
+    case 64:  hipLaunchKernelGGL((attention_f32_kernel<T, 64>), grid, dim3(64), 0, s, qkv, ctx, lengths, seq, d, n_head, causal, heads); break;
     default:  return hipErrorInvalidValue;
   }
   return hipGetLastError();
