@@ -1042,15 +1042,15 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
       const BwCarve::PerLayer& W = v.layer[l];
       float* xnext = F(l + 1 < m.n_layer ? v.layer[l + 1].xin : v.xfin);
       HIP_TRY(c, launch_layernorm(dt, F(W.xin), T(c, L.ln1_g), T(c, L.ln1_b), ws + W.h1, M, d, m.ln_eps, s));
-      HIP_TRY(c, launch_gemm(dt, ws + W.h1, T(c, L.wq), T(c, L.bq), ws + W.qkv, EPI_STORE, M, 3 * d, d, s));
-      HIP_TRY(c, launch_attention(dt, ws + W.qkv, ws + W.ctx, lengths, B, Tn, d, H, lm ? 1 : 0, s));
+      HIP_TRY(c, launch_gemm(dt, ws + W.h1, T(c, L.wq), T(c, L.bq), ws + W.qkv, EPI_STORE, M, 3 * d, d, s, nullptr, 0, true));
+      HIP_TRY(c, launch_attention(dt, ws + W.qkv, ws + W.ctx, lengths, B, Tn, d, H, lm ? 1 : 0, s, true));
       HIP_TRY(c, hipMemcpyAsync(F(W.xmid), F(W.xin), xbytes, hipMemcpyDeviceToDevice, s));
-      HIP_TRY(c, launch_gemm(dt, ws + W.ctx, T(c, L.wo), T(c, L.bo), F(W.xmid), EPI_RESID, M, d, d, s));
+      HIP_TRY(c, launch_gemm(dt, ws + W.ctx, T(c, L.wo), T(c, L.bo), F(W.xmid), EPI_RESID, M, d, d, s, nullptr, 0, true));
       HIP_TRY(c, launch_layernorm(dt, F(W.xmid), T(c, L.ln2_g), T(c, L.ln2_b), ws + W.h2, M, d, m.ln_eps, s));
-      HIP_TRY(c, launch_gemm(dt, ws + W.h2, T(c, L.w1), T(c, L.b1), F(W.u), EPI_F32, M, ff, d, s));
+      HIP_TRY(c, launch_gemm(dt, ws + W.h2, T(c, L.w1), T(c, L.b1), F(W.u), EPI_F32, M, ff, d, s, nullptr, 0, true));
       HIP_TRY(c, launch_bw_act_forward(dt, relu, F(W.u), ws + W.f, (int64_t)M * ff, s));
       HIP_TRY(c, hipMemcpyAsync(xnext, F(W.xmid), xbytes, hipMemcpyDeviceToDevice, s));
-      HIP_TRY(c, launch_gemm(dt, ws + W.f, T(c, L.w2), T(c, L.b2), xnext, EPI_RESID, M, d, ff, s));
+      HIP_TRY(c, launch_gemm(dt, ws + W.f, T(c, L.w2), T(c, L.b2), xnext, EPI_RESID, M, d, ff, s, nullptr, 0, true));
     }
     HIP_TRY(c, launch_layernorm(dt, F(v.xfin), T(c, c->lnf_g), T(c, c->lnf_b), ws + v.hf, M, d, m.ln_eps, s));
   } else {
@@ -1062,15 +1062,15 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
       const Layer& L = c->layers[l];
       const BwCarve::PerLayer& W = v.layer[l];
       const bool last = l + 1 == m.n_layer;
-      HIP_TRY(c, launch_gemm(dt, ws + W.h1, T(c, L.wq), T(c, L.bq), ws + W.qkv, EPI_STORE, M, 3 * d, d, s));
-      HIP_TRY(c, launch_attention(dt, ws + W.qkv, ws + W.ctx, lengths, B, Tn, d, H, lm ? 1 : 0, s));
+      HIP_TRY(c, launch_gemm(dt, ws + W.h1, T(c, L.wq), T(c, L.bq), ws + W.qkv, EPI_STORE, M, 3 * d, d, s, nullptr, 0, true));
+      HIP_TRY(c, launch_attention(dt, ws + W.qkv, ws + W.ctx, lengths, B, Tn, d, H, lm ? 1 : 0, s, true));
       HIP_TRY(c, hipMemcpyAsync(F(W.xmid), F(W.xin), xbytes, hipMemcpyDeviceToDevice, s));
-      HIP_TRY(c, launch_gemm(dt, ws + W.ctx, T(c, L.wo), T(c, L.bo), F(W.xmid), EPI_RESID, M, d, d, s));
+      HIP_TRY(c, launch_gemm(dt, ws + W.ctx, T(c, L.wo), T(c, L.bo), F(W.xmid), EPI_RESID, M, d, d, s, nullptr, 0, true));
       HIP_TRY(c, launch_layernorm(dt, F(W.xmid), T(c, L.ln1_g), T(c, L.ln1_b), ws + W.h2, M, d, m.ln_eps, s, F(W.x1n)));
-      HIP_TRY(c, launch_gemm(dt, ws + W.h2, T(c, L.w1), T(c, L.b1), F(W.u), EPI_F32, M, ff, d, s));
+      HIP_TRY(c, launch_gemm(dt, ws + W.h2, T(c, L.w1), T(c, L.b1), F(W.u), EPI_F32, M, ff, d, s, nullptr, 0, true));
       HIP_TRY(c, launch_bw_act_forward(dt, relu, F(W.u), ws + W.f, (int64_t)M * ff, s));
       HIP_TRY(c, hipMemcpyAsync(F(W.y2), F(W.x1n), xbytes, hipMemcpyDeviceToDevice, s));
-      HIP_TRY(c, launch_gemm(dt, ws + W.f, T(c, L.w2), T(c, L.b2), F(W.y2), EPI_RESID, M, d, ff, s));
+      HIP_TRY(c, launch_gemm(dt, ws + W.f, T(c, L.w2), T(c, L.b2), F(W.y2), EPI_RESID, M, d, ff, s, nullptr, 0, true));
       HIP_TRY(c, launch_layernorm(dt, F(W.y2), T(c, L.ln2_g), T(c, L.ln2_b), last ? ws + v.hf : ws + v.layer[l + 1].h1, M, d, m.ln_eps, s,
                                   F(last ? v.xout : v.layer[l + 1].xin)));
     }
@@ -1084,7 +1084,7 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
     int32_t* tgt = reinterpret_cast<int32_t*>(ws + v.targets);
     const double inv_n = 1.0 / ((double)B * (Tn - 1));
     HIP_TRY(c, launch_lm_targets(tok, tgt, M, Tn, m.vocab, s));
-    HIP_TRY(c, launch_gemm(dt, ws + v.hf, T(c, c->tok_emb), nullptr, logits, EPI_F32, M, m.vocab, d, s));
+    HIP_TRY(c, launch_gemm(dt, ws + v.hf, T(c, c->tok_emb), nullptr, logits, EPI_F32, M, m.vocab, d, s, nullptr, 0, true));
     // tied head: logits = hf E^T, so dE = dlogits^T hf (the embedding rule adds its share below), dhf = dlogits E
     const void* E = T(c, c->tok_emb);
     float* dE = grads[c->tok_emb];

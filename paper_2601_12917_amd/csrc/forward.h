@@ -11,13 +11,18 @@ enum { EPI_STORE = 0, EPI_GELU = 1, EPI_RESID = 2, EPI_F32 = 3, EPI_CE = 4, EPI_
 hipError_t launch_embed(int dtype, const int32_t* tok, const void* E, const void* Pe, float* x, int M, int seq, int d, int vocab, hipStream_t s);
 // out (storage type) = LayerNorm(x) g + b; xout, when not NULL, receives the same values in fp32 (it may be x itself)
 hipError_t launch_layernorm(int dtype, const float* x, const void* g, const void* b, void* out, int M, int d, float eps, hipStream_t s, float* xout = nullptr);
+// keep_order (launch_gemm, launch_attention): sums in the order in which the large tiles, and attention key by key, take them at every size.
+// The forward half of the cloud's backward pass asks for it: a ReLU's slope jumps where its argument changes sign, so sums taken in
+// another order there move the gradients by far more than their rounding (4e-3 of their norm on a 13-block bf16 model with head size
+// 32), while a loss, which is all the client's forward returns, follows smoothly.
 // out = epilogue(A[M,K] W[N,K]^T + bias); bf16 storage needs K % 64 == 0.  scratch (may be NULL): floats a split sum may be kept in meanwhile.
 hipError_t launch_gemm(int dtype, const void* A, const void* W, const void* bias, void* out, int epi, int M, int N, int K, hipStream_t s, float* scratch = nullptr,
-                       size_t scratch_floats = 0);
+                       size_t scratch_floats = 0, bool keep_order = false);
 // bf16 vocabulary projection fused with cross-entropy: row_loss[m] = logsumexp(A[m] W^T) - (A[m] W^T)[targets[m]] (0 where targets[m] < 0).
 int        ce_partials_per_row(int N);
 hipError_t launch_gemm_ce_bf16(const void* A, const void* W, const int32_t* targets, void* part, float* tlogit, float* row_loss, int M, int N, int K, hipStream_t s);
-hipError_t launch_attention(int dtype, const void* qkv, void* ctx, const int32_t* lengths, int batch, int seq, int d, int n_head, int causal, hipStream_t s);
+hipError_t launch_attention(int dtype, const void* qkv, void* ctx, const int32_t* lengths, int batch, int seq, int d, int n_head, int causal, hipStream_t s,
+                            bool keep_order = false);
 bool       attention_head_dim_supported(int dh);
 hipError_t launch_lm_targets(const int32_t* tok, int32_t* tgt, int M, int seq, int vocab, hipStream_t s);
 hipError_t launch_ce_rows(const float* logits, const int32_t* targets, float* row_loss, int M, int n, hipStream_t s);

@@ -887,6 +887,59 @@ __global__ void __launch_bounds__(64, 2) attention_f32_kernel(const T* __restric
   }
 }
 
+// The same attention key by key on the vector unit: one thread per query row, one block per (batch, head, 256-query chunk), keys and
+// values through LDS in chunks of 32.  The forward half of the cloud's backward pass keeps it (keep_order below).
+template <typename T, int DH>
+__global__ void __launch_bounds__(256) attention_kernel(const T* __restrict__ qkv, T* __restrict__ ctx, const int32_t* __restrict__ lengths,
+                                                        int seq, int d, int n_head, int causal) {
+  constexpr int KC = 32;
+  __shared__ float Ks[KC][DH], Vs[KC][DH];
+  const int chunks = (seq + 255) / 256;
+  const int qc = blockIdx.x % chunks, h = (blockIdx.x / chunks) % n_head, b = blockIdx.x / (chunks * n_head);
+  const int qi = qc * 256 + threadIdx.x;
+  const bool active = qi < seq;
+  const int len = lengths ? lengths[b] : seq;
+  const size_t ld = (size_t)3 * d;
+  const T* base = qkv + (size_t)b * seq * ld + (size_t)h * DH;
+  float q[DH], acc[DH];
+  const float scale = 1.0f / sqrtf((float)DH);
+#pragma unroll
+  for (int i = 0; i < DH; ++i) { q[i] = active ? to_f32(base[(size_t)qi * ld + i]) * scale : 0.f; acc[i] = 0.f; }
+  float mx = -INFINITY, den = 0.f;
+  int kend = len < seq ? len : seq;
+  if (causal) { const int last = qc * 256 + 255; kend = kend < last + 1 ? kend : last + 1; }
+  for (int k0 = 0; k0 < kend; k0 += KC) {
+    __syncthreads();
+    for (int i = threadIdx.x; i < KC * DH; i += 256) {
+      const int r = i / DH, c = i - r * DH;
+      const int kj = k0 + r;
+      Ks[r][c] = kj < seq ? to_f32(base[(size_t)kj * ld + d + c]) : 0.f;
+      Vs[r][c] = kj < seq ? to_f32(base[(size_t)kj * ld + 2 * d + c]) : 0.f;
+    }
+    __syncthreads();
+    if (!active) continue;
+    for (int r = 0; r < KC; ++r) {
+      const int kj = k0 + r;
+      if (kj >= kend || (causal && kj > qi)) break;
+      float s = 0.f;
+#pragma unroll
+      for (int i = 0; i < DH; ++i) s = __builtin_fmaf(q[i], Ks[r][i], s);
+      const float nm = fmaxf(mx, s);
+      const float corr = __expf(mx - nm), p = __expf(s - nm);
+      den = den * corr + p;
+#pragma unroll
+      for (int i = 0; i < DH; ++i) acc[i] = __builtin_fmaf(p, Vs[r][i], acc[i] * corr);
+      mx = nm;
+    }
+  }
+  if (active) {
+    T* o = ctx + ((size_t)b * seq + qi) * d + (size_t)h * DH;
+    const float inv = den > 0.f ? 1.0f / den : 0.f;
+#pragma unroll
+    for (int i = 0; i < DH; ++i) from_f32(acc[i] * inv, o[i]);
+  }
+}
+
 // MFMA attention for bf16 storage and head size 64.  One block = 128 queries of one (batch, head):
 // K [keys][64] and V^T [64][keys] are staged in LDS (all keys at once up to AT_KCH of them, chunk after chunk of
 // AT_KCH beyond: the online softmax carries over); each wave owns 32 queries and walks the keys in
@@ -1164,14 +1217,14 @@ hipError_t launch_layernorm(int dtype, const float* x, const void* g, const void
   return hipGetLastError();
 }
 
-hipError_t launch_gemm(int dtype, const void* A, const void* W, const void* bias, void* out, int epi, int M, int N, int K, hipStream_t s, float* scratch, size_t scratch_floats) {
+hipError_t launch_gemm(int dtype, const void* A, const void* W, const void* bias, void* out, int epi, int M, int N, int K, hipStream_t s, float* scratch, size_t scratch_floats, bool keep_order) {
   GemmEpi ep{epi, out, bias};
   if (dtype == 0) {
     const bool mfma_ok = K % 4 == 0 && (((uintptr_t)A | (uintptr_t)W) & 15) == 0;
     const long t128 = (long)((M + 127) / 128) * ((N + 127) / 128);
     if (mfma_ok && t128 >= 512)   // enough 128 x 128 tiles for two blocks on every CU
       hipLaunchKernelGGL((gemm_f32_mfma_kernel<2, 16>), dim3((N + 127) / 128, (M + 127) / 128), dim3(256), 0, s, (const float*)A, (const float*)W, M, N, K, ep);
-    else if (mfma_ok && (long)((M + 63) / 64) * ((N + 63) / 64) < 512) {
+    else if (mfma_ok && !keep_order && (long)((M + 63) / 64) * ((N + 63) / 64) < 512) {
       // too few 64 x 64 tiles to fill the chip: sums split among waves and blocks (1000^3: 28 us against 44, 1024 x 768 x 3072: 57 against 88;
       // from about 512 tiles on the LDS-tiled kernel is the faster one: 2048 x 2304 x 768, 1152 tiles, 81 us against 93)
       ProductArgs p;
@@ -1222,9 +1275,20 @@ hipError_t launch_gemm_ce_bf16(const void* A, const void* W, const int32_t* targ
 }
 
 template <typename T>
-static hipError_t launch_attention_t(const T* qkv, T* ctx, const int32_t* lengths, int batch, int seq, int d, int n_head, int causal, hipStream_t s) {
+static hipError_t launch_attention_t(const T* qkv, T* ctx, const int32_t* lengths, int batch, int seq, int d, int n_head, int causal, hipStream_t s, bool keep_order) {
   const int dh = d / n_head;
   const int heads = batch * n_head;
+  if (keep_order) {
+    const dim3 grid((unsigned)heads * (unsigned)((seq + 255) / 256));
+    switch (dh) {
+      case 8:   hipLaunchKernelGGL((attention_kernel<T, 8>), grid, dim3(256), 0, s, qkv, ctx, lengths, seq, d, n_head, causal); break;
+      case 16:  hipLaunchKernelGGL((attention_kernel<T, 16>), grid, dim3(256), 0, s, qkv, ctx, lengths, seq, d, n_head, causal); break;
+      case 32:  hipLaunchKernelGGL((attention_kernel<T, 32>), grid, dim3(256), 0, s, qkv, ctx, lengths, seq, d, n_head, causal); break;
+      case 64:  hipLaunchKernelGGL((attention_kernel<T, 64>), grid, dim3(256), 0, s, qkv, ctx, lengths, seq, d, n_head, causal); break;
+      default:  return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+  }
   const dim3 grid((unsigned)heads * (unsigned)((seq + 31) / 32));
   switch (dh) {
     case 8:   hipLaunchKernelGGL((attention_f32_kernel<T, 8>), grid, dim3(64), 0, s, qkv, ctx, lengths, seq, d, n_head, causal, heads); break;
@@ -1236,7 +1300,7 @@ static hipError_t launch_attention_t(const T* qkv, T* ctx, const int32_t* length
   return hipGetLastError();
 }
 
-hipError_t launch_attention(int dtype, const void* qkv, void* ctx, const int32_t* lengths, int batch, int seq, int d, int n_head, int causal, hipStream_t s) {
+hipError_t launch_attention(int dtype, const void* qkv, void* ctx, const int32_t* lengths, int batch, int seq, int d, int n_head, int causal, hipStream_t s, bool keep_order) {
   if (dtype == 1 && d / n_head == 64 && d % 8 == 0) {
     const int kpad = seq < AT_KCH ? (seq + 31) / 32 * 32 : AT_KCH;          // keys resident in LDS at a time
     const size_t lds = sizeof(bf16_t) * ((size_t)kpad * AT_LDK + (size_t)64 * (kpad + 8));
@@ -1257,8 +1321,8 @@ hipError_t launch_attention(int dtype, const void* qkv, void* ctx, const int32_t
     }
     return hipGetLastError();
   }
-  if (dtype == 0) return launch_attention_t<float>((const float*)qkv, (float*)ctx, lengths, batch, seq, d, n_head, causal, s);
-  return launch_attention_t<bf16_t>((const bf16_t*)qkv, (bf16_t*)ctx, lengths, batch, seq, d, n_head, causal, s);
+  if (dtype == 0) return launch_attention_t<float>((const float*)qkv, (float*)ctx, lengths, batch, seq, d, n_head, causal, s, keep_order);
+  return launch_attention_t<bf16_t>((const bf16_t*)qkv, (bf16_t*)ctx, lengths, batch, seq, d, n_head, causal, s, keep_order);
 }
 
 bool attention_head_dim_supported(int dh) { return dh == 8 || dh == 16 || dh == 32 || dh == 64; }
