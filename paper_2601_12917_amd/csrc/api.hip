@@ -44,6 +44,7 @@ struct Layer {
 struct Carve {                 // workspace layout (byte offsets)
   size_t descs = 0, flat = 0, tiles = 0, dbg = 0;
   size_t cap_flat = 0, cap_tiles = 0, cap_dbg = 0;   // capacities in items
+  bool few_tiles = false;      // small row tiles (kFewTiles)
   size_t x = 0, h = 0, qkv = 0, ctx = 0, ff = 0, logits = 0, row_loss = 0, targets = 0, loss = 0;
   size_t row_loss_stride = 0;                  // floats between the row losses of L+ (slot 0) and L- (slot 1)
   size_t spc[kSpcSlots] = {}, spc_bytes = 0;   // staging slots for the bases of one layer each (streamed bases)
@@ -135,19 +136,22 @@ size_t flat_items_of(int64_t numel, int P, int dtype) {
 }
 // Row tiles of 128 rows: fine enough that a launch over one layer's matrices (a stage of the layer pipeline) still
 // gives every block several tiles; the slice of R is shared by the consecutive row tiles of a strip, so small tiles cost nothing.
-int tile_rows_of(int64_t) { return kTileRowsPerIter; }
-size_t tile_items_of(int64_t rows, int64_t cols, int P) {
-  const int64_t tr = tile_rows_of(rows), tc = 32 * P;
+// A model with few of them altogether (kFewTiles: a quarter of the CUs with a block each) takes tiles of 8 rows, or of the 64 rows
+// the matrix-core kernel covers at a time.
+constexpr size_t kFewTiles = 64;
+int tile_rows_of(bool few, int k) { return !few ? kTileRowsPerIter : (k >= kMfmaMinK ? 64 : kSmallTileRows); }
+size_t tile_items_of(int64_t rows, int64_t cols, int P, int64_t tr = kTileRowsPerIter) {
+  const int64_t tc = 32 * P;
   return (size_t)(((rows + tr - 1) / tr) * ((cols + tc - 1) / tc));
 }
 
-void append_items(const zgr_tensor& t, int index, bool guided, int P, std::vector<WorkItem>& flat, std::vector<WorkItem>& tiles) {
+void append_items(const zgr_tensor& t, int index, bool guided, int P, bool few, std::vector<WorkItem>& flat, std::vector<WorkItem>& tiles) {
   if (!guided) {
     const int64_t groups = (t.rows * t.cols + P - 1) / P, per = flat_groups_per_item((int)elem_size(t.dtype), P);
     for (int64_t g0 = 0; g0 < groups; g0 += per)
       flat.push_back({index, (int32_t)std::min<int64_t>(per, groups - g0), g0});
   } else {
-    const int64_t tr = tile_rows_of(t.rows), tc = 32 * P;
+    const int64_t tr = tile_rows_of(few, t.k), tc = 32 * P;
     // column strips outermost: the kernels keep a strip's slice of R in LDS across its consecutive row tiles
     for (int64_t c0 = 0; c0 < t.cols; c0 += tc)
       for (int64_t r0 = 0; r0 < t.rows; r0 += tr)
@@ -247,7 +251,7 @@ void build_lists(zgr_ctx* c) {
       cls[k_class].begin = c->tiles.size();
       for (int i : members) {
         if (!is_guided(c, (size_t)i) || (c->t[i].k >= kMfmaMinK ? 0 : 1) != k_class) continue;
-        append_items(c->t[i], i, true, P, c->flat, c->tiles);
+        append_items(c->t[i], i, true, P, c->cv.few_tiles, c->flat, c->tiles);
         cls[k_class].max_k = std::max(cls[k_class].max_k, c->t[i].k);
         cls[k_class].min_k = std::min(cls[k_class].min_k, c->t[i].k);
       }
@@ -259,7 +263,7 @@ void build_lists(zgr_ctx* c) {
     if (is_streamed(c, i)) continue;
     describe(i, 0);
     if (is_guided(c, i)) resident.push_back((int)i);
-    else append_items(c->t[i], (int)i, false, P, c->flat, c->tiles);
+    else append_items(c->t[i], (int)i, false, P, c->cv.few_tiles, c->flat, c->tiles);
   }
   tile_ranges(resident, c->res);
   for (size_t gi = 0; gi < c->groups.size(); ++gi) {
@@ -317,9 +321,12 @@ Carve carve(const zgr_model& m, const zgr_tensor* t, int n_t, int max_batch, int
   const int P = group_size(bits);
   size_t nf = 0, nt = 0, nd = 0;
   int dtype = n_t > 0 ? t[0].dtype : 0;
+  size_t whole = 0;            // tiles of 128 rows if every matrix that could be guided were (any may be, later)
+  for (int i = 0; i < n_t; ++i) if (t[i].cols % P == 0 && t[i].rows > 1) whole += tile_items_of(t[i].rows, t[i].cols, P);
+  cv.few_tiles = whole <= kFewTiles;
   for (int i = 0; i < n_t; ++i) {
     const size_t f = flat_items_of(t[i].rows * t[i].cols, P, t[i].dtype);
-    const size_t tl = (t[i].cols % P == 0) ? tile_items_of(t[i].rows, t[i].cols, P) : 0;
+    const size_t tl = (t[i].cols % P == 0) ? tile_items_of(t[i].rows, t[i].cols, P, cv.few_tiles ? kSmallTileRows : kTileRowsPerIter) : 0;
     nf += f; nt += tl;
     nd = std::max(nd, std::max(f, tl));
   }
@@ -427,6 +434,7 @@ PerturbArgs perturb_args(zgr_ctx* c, uint64_t step) {
   a.n_flat = (int32_t)c->flat.size(); a.n_tiles = (int32_t)c->tiles.size();
   a.k0 = (uint32_t)c->cfg.seed; a.k1 = (uint32_t)(c->cfg.seed >> 32);
   a.step = (uint32_t)step; a.bits = c->cfg.gauss_bits; a.dtype = c->dtype; a.max_k = c->max_k; a.min_k = c->min_k;
+  a.tile_rows = tile_rows_of(c->cv.few_tiles, 0);
   return a;
 }
 
@@ -1340,7 +1348,7 @@ zgr_status zgr_debug_fill_z(zgr_ctx* c, int32_t idx, uint64_t step, float* Z) {
   zgr_status st = upload_lists(c);
   if (st != ZGR_OK) return st;
   std::vector<WorkItem> fl, tl;
-  append_items(c->t[idx], idx, is_guided(c, (size_t)idx), group_size(c->cfg.gauss_bits), fl, tl);
+  append_items(c->t[idx], idx, is_guided(c, (size_t)idx), group_size(c->cfg.gauss_bits), c->cv.few_tiles, fl, tl);
   std::vector<WorkItem>& items = fl.empty() ? tl : fl;
   if (items.size() > c->cv.cap_dbg) return fail(c, ZGR_ERR_WORKSPACE, "debug list outgrew the workspace");
   HIP_TRY(c, hipMemcpyAsync(c->ws + c->cv.dbg, items.data(), sizeof(WorkItem) * items.size(), hipMemcpyHostToDevice, c->stream));

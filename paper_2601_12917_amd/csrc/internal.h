@@ -35,6 +35,7 @@ struct WorkItem {
 constexpr int flat_slots(int elem_bytes, int P) { return 64 / (elem_bytes * P) < 1 ? 1 : 64 / (elem_bytes * P); }
 constexpr int flat_groups_per_item(int elem_bytes, int P) { return 256 * flat_slots(elem_bytes, P); }
 constexpr int kTileRowsPerIter   = 128;    // rows one block covers per iteration (4 waves x 32)
+constexpr int kSmallTileRows     = 8;      // and where the whole model has few tiles (vector kernel)
 constexpr int kMaxK              = 64;
 constexpr int kMfmaMinK          = 16;     // from this rank on the U R contraction of a tile runs on the matrix cores
 constexpr int kMaxBatch          = 8;      // perturbations summed in one pass (zgr_apply_updates)
@@ -59,6 +60,7 @@ struct PerturbArgs {
   int32_t           dtype;
   int32_t           max_k;     // largest k among tiled tensors
   int32_t           min_k;     // smallest k among tiled tensors
+  int32_t           tile_rows; // rows of a tile of the vector kernel: kTileRowsPerIter or kSmallTileRows
   // batched pass: theta += sum_i qcoef[i] Z(seed, qstep[i]); n_q == 0: the single pass theta += c Z(seed, step)
   int32_t           n_q;
   uint32_t          qstep[kMaxBatch];

@@ -293,17 +293,19 @@ __device__ __forceinline__ void finish_row(const TensorDesc& d, T* __restrict__ 
   }
 }
 
-// Lane layout inside a wave's 32-row slab: column group cg = lane % 32 owns P
-// consecutive columns; register v of the lane is row 8*(v/4) + 4*(lane/32) + v%4.
-template <typename T, int P, bool WRITE_Z, bool BATCH>
+// Lane layout: column group cg = lane % 32 owns P consecutive columns, each half of a wave RPL consecutive rows (a lane makes one
+// Philox call per row).  RPL = 16 is for passes that fill the chip; RPL = 1 spreads a small model's matrices over sixteen times the
+// blocks (least-squares layer of 256 x 512: 17 us with 8 blocks of 128 rows, 5.3 with 128 blocks of 8).
+template <typename T, int P, bool WRITE_Z, bool BATCH, int RPL>
 __global__ void __launch_bounds__(256) perturb_tile_kernel(PerturbArgs a, const TensorDesc* __restrict__ descs, const WorkItem* __restrict__ items,
                                                            float c, const RadiusEntry* __restrict__ gtab, float* __restrict__ zout, int kp) {
   extern __shared__ float smem[];
   RadiusEntry* tab = reinterpret_cast<RadiusEntry*>(smem);
-  float* Us = smem + kRadiusTabEntries * 3;          // [128][kp]
-  float* Rs = Us + kTileRowsPerIter * kp;            // [kp][TC]
+  constexpr int TR = 8 * RPL;                        // rows a block covers at a time
+  float* Us = smem + kRadiusTabEntries * 3;          // [TR][kp]
+  float* Rs = Us + TR * kp;                          // [kp][TC]
   constexpr int TC = 32 * P;
-  constexpr int RB = (P == 4) ? 16 : 8;              // rows a lane holds at once
+  constexpr int RB = RPL < 8 ? RPL : (P == 4 ? 16 : 8);   // rows a lane holds at once
   const int nblk = (int)gridDim.x - a.pull_blocks;               // computing blocks
   if ((int)blockIdx.x >= nblk) { pull_next_stage(a, (int)blockIdx.x - nblk, a.pull_blocks); return; }
   load_radius_table(tab, gtab);
@@ -341,9 +343,9 @@ __global__ void __launch_bounds__(256) perturb_tile_kernel(PerturbArgs a, const 
 #pragma unroll
       for (int j = 0; j < P; ++j) Rs[l * TC + g * P + j] = r[j];
     }
-    for (int r0 = 0; r0 < nrows; r0 += kTileRowsPerIter) {
+    for (int r0 = 0; r0 < nrows; r0 += TR) {
       __syncthreads();                               // Rs written / previous row block's readers of Us done
-      for (int idx = tid; idx < kTileRowsPerIter * kpt; idx += 256) {
+      for (int idx = tid; idx < TR * kpt; idx += 256) {
         const int r = idx / kpt, l = idx - r * kpt;
         const int64_t row = row0 + r0 + r;
         Us[r * kp + l] = (l < k && r0 + r < nrows && row < d.rows) ? basis_at(d, row, l) : 0.f;
@@ -351,7 +353,7 @@ __global__ void __launch_bounds__(256) perturb_tile_kernel(PerturbArgs a, const 
       __syncthreads();
       const int64_t col = col0 + (int64_t)cg * P;
 #pragma unroll 1
-      for (int vb = 0; vb < 16; vb += RB) {
+      for (int vb = 0; vb < RPL; vb += RB) {
         float acc[RB][P];
 #pragma unroll
         for (int v = 0; v < RB; ++v)
@@ -366,7 +368,7 @@ __global__ void __launch_bounds__(256) perturb_tile_kernel(PerturbArgs a, const 
 #pragma unroll
           for (int v = 0; v < RB; ++v) {
             const int vv = vb + v;
-            const int rloc = 32 * wave + 8 * (vv >> 2) + 4 * rh + (vv & 3);
+            const int rloc = (2 * wave + rh) * RPL + vv;
             const float* u = Us + rloc * kp + l0;
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
@@ -380,7 +382,7 @@ __global__ void __launch_bounds__(256) perturb_tile_kernel(PerturbArgs a, const 
 #pragma unroll
           for (int v = 0; v < RB; ++v) {
             const int vv = vb + v;
-            const int rloc = 32 * wave + 8 * (vv >> 2) + 4 * rh + (vv & 3);
+            const int rloc = (2 * wave + rh) * RPL + vv;
             const int64_t row = row0 + r0 + rloc;
             if (r0 + rloc < nrows && row < d.rows) finish_row<T, P, WRITE_Z, BATCH>(d, th, zout, row * d.cols + col, acc[v], c, a, tab);
           }
@@ -648,7 +650,7 @@ __global__ void __launch_bounds__(256) copy_kernel(uint4* __restrict__ dst, cons
 }
 
 // The table lives in static device memory: the library allocates nothing.
-__device__ RadiusEntry g_radius_table[kRadiusTabEntries];
+__device__ __align__(16) RadiusEntry g_radius_table[kRadiusTabEntries];
 
 }  // namespace
 
@@ -756,7 +758,6 @@ template <typename T, int P>
 hipError_t launch_tile_t(const PerturbArgs& a_in, float c, float* zout, hipStream_t s, int n_cu, const RadiusEntry* tab) {
   PerturbArgs a = a_in;
   const int kp = (a.max_k + 7) & ~7;
-  const size_t lds = sizeof(float) * ((size_t)kRadiusTabEntries * 3 + (size_t)kTileRowsPerIter * kp + (size_t)kp * 32 * P);
   if (a.min_k >= kMfmaMinK) {
     const size_t lds_m = sizeof(float) * ((size_t)kRadiusTabEntries * 3 + (size_t)kp * 32 * P);
     const int variant = zout ? 1 : (a.n_q > 0 ? 2 : 0);
@@ -769,9 +770,13 @@ hipError_t launch_tile_t(const PerturbArgs& a_in, float c, float* zout, hipStrea
     hipLaunchKernelGGL(km, dim3(grid_m), dim3(256), lds_m, s, a, a.descs, a.tiles, c, tab, zout, kp);
     return hipGetLastError();
   }
-  const int variant = zout ? 1 : (a.n_q > 0 ? 2 : 0);
-  auto kern = zout ? perturb_tile_kernel<T, P, true, false> : (a.n_q > 0 ? perturb_tile_kernel<T, P, false, true> : perturb_tile_kernel<T, P, false, false>);
-  static TileLaunchCache cache_v[3];
+  const bool small = a.tile_rows < kTileRowsPerIter;
+  const size_t lds = sizeof(float) * ((size_t)kRadiusTabEntries * 3 + (size_t)(small ? kSmallTileRows : kTileRowsPerIter) * kp + (size_t)kp * 32 * P);
+  const int variant = (zout ? 1 : (a.n_q > 0 ? 2 : 0)) + (small ? 3 : 0);
+  constexpr int RS = kSmallTileRows / 8, RL = kTileRowsPerIter / 8;
+  auto kern = small ? (zout ? perturb_tile_kernel<T, P, true, false, RS> : (a.n_q > 0 ? perturb_tile_kernel<T, P, false, true, RS> : perturb_tile_kernel<T, P, false, false, RS>))
+                    : (zout ? perturb_tile_kernel<T, P, true, false, RL> : (a.n_q > 0 ? perturb_tile_kernel<T, P, false, true, RL> : perturb_tile_kernel<T, P, false, false, RL>));
+  static TileLaunchCache cache_v[6];
   int per_cu = 1;
   hipError_t e = tile_launch_setup(kern, lds, 4, cache_v[variant], &per_cu);
   if (e != hipSuccess) return e;

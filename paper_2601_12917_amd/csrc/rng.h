@@ -153,11 +153,20 @@ __device__ __forceinline__ void gauss8(const u32x4 w, const RadiusEntry* __restr
     box_muller((((ww[p] & 0xFFFFu) << 1) | 1u) << 7, (ww[p] >> 16) << 8, tab, g[2 * p], g[2 * p + 1]);
 }
 
-// Block-wide copy of the radius table from global memory into LDS.
+// Copy of the radius table (16-byte aligned) from global memory into LDS by a block of 256 threads.
 __device__ __forceinline__ void load_radius_table(RadiusEntry* lds, const RadiusEntry* __restrict__ glob) {
-  const float* s = reinterpret_cast<const float*>(glob);
+  // every load is under way before the first is waited for: a small launch spends most of its time here otherwise
+  constexpr int kVectors = kRadiusTabEntries * 3 / 4, kPerThread = (kVectors + 255) / 256;
+  const float4* s = reinterpret_cast<const float4*>(glob);
   float* d = reinterpret_cast<float*>(lds);
-  for (int i = threadIdx.x; i < kRadiusTabEntries * 3; i += blockDim.x) d[i] = s[i];
+  float4 v[kPerThread];
+#pragma unroll
+  for (int u = 0; u < kPerThread; ++u) { const int i = (int)threadIdx.x + 256 * u; v[u] = s[i < kVectors ? i : kVectors - 1]; }
+#pragma unroll
+  for (int u = 0; u < kPerThread; ++u) {
+    const int i = (int)threadIdx.x + 256 * u;
+    if (i < kVectors) { d[4 * i] = v[u].x; d[4 * i + 1] = v[u].y; d[4 * i + 2] = v[u].z; d[4 * i + 3] = v[u].w; }
+  }
 }
 
 }  // namespace zgr

@@ -62,6 +62,23 @@ SHAPES = [
 ]
 
 
+@pytest.mark.parametrize("rows,cols,k,bits", [
+    (1021, 1016, 5, 32),     # 8 strips x 8 row tiles of 128: the most tiles that still take 8 rows each, the last with five
+    (1025, 1024, 5, 32),     # one row more: tiles of 128 rows, the last with one
+    (1100, 2056, 8, 16),     # the same with eight Gaussians per call, a ragged strip
+    (1021, 1016, 18, 32),    # matrix-core kernel on tiles of 64 rows
+])
+def test_z_on_either_side_of_the_small_tiles(rows, cols, k, bits):
+    sess, cfg, W, U = _session_for(rows, cols, k, bits=bits)
+    got = sess.fill_z(0, 7)
+    G, R, Z = P.hybrid_z(cfg.seed, 7, 3, rows, cols, U, k, cfg.alpha, 0, bits, parts=True)
+    assert np.all(np.abs(got.astype(np.float64) - Z) <= _z_bound(cfg, G, R, U, k, rows, cols, 0))
+    c = np.float32(1e-3)                      # and the pass itself: one fp32 FMA per entry
+    sess.perturb(7, float(c))
+    want = W.astype(np.float64) + float(c) * Z
+    assert np.all(np.abs(sess.get_theta(0) - want) <= F32_RTOL * (np.abs(want) + PARAM_SCALE))
+
+
 @pytest.mark.parametrize("bits", [32, 16])
 @pytest.mark.parametrize("rows,cols,k,ldu", SHAPES)
 def test_z_matches_oracle(rows, cols, k, ldu, bits):
