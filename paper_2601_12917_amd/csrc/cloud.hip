@@ -328,8 +328,9 @@ __global__ void __launch_bounds__(256) gram_kernel(const float* __restrict__ Y, 
     for (int b = 0; b <= a; ++b) acc[a][b] = 0.0;
   for (int64_t r0 = r_begin; r0 < r_end; r0 += kGramRows) {
     __syncthreads();
-    for (int i = tid; i < kGramRows * NT * 16; i += 256) {
-      const int rr = i / (NT * 16), c = i % (NT * 16);
+#pragma unroll
+    for (int u = 0; u < kGramRows * NT * 16 / 256; ++u) {
+      const int i = tid + 256 * u, rr = i / (NT * 16), c = i % (NT * 16);
       Ys[rr][c] = (r0 + rr < r_end && c < k) ? Y[(r0 + rr) * k + c] : 0.f;
     }
     __syncthreads();
@@ -446,9 +447,9 @@ __global__ void __launch_bounds__(256) apply_factor_kernel(float* __restrict__ Y
   const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
   const int64_t r0 = (int64_t)blockIdx.x * kApplyRows;
 #pragma unroll
-  for (int e = tid; e < KP * KP; e += 256) { const int i = e / KP, j = e % KP; F[i][j] = (i < k && j < k) ? fac[i * k + j] : 0.0; }
+  for (int u = 0; u < KP * KP / 256; ++u) { const int e = tid + 256 * u, i = e / KP, j = e % KP; F[i][j] = (i < k && j < k) ? fac[i * k + j] : 0.0; }
 #pragma unroll
-  for (int e = tid; e < kApplyRows * KP; e += 256) { const int r = e / KP, c = e % KP; Ys[r][c] = (r0 + r < rows && c < k) ? Y[(r0 + r) * k + c] : 0.f; }
+  for (int u = 0; u < kApplyRows * KP / 256; ++u) { const int e = tid + 256 * u, r = e / KP, c = e % KP; Ys[r][c] = (r0 + r < rows && c < k) ? Y[(r0 + r) * k + c] : 0.f; }
   __syncthreads();
   double acc[2][NT];
 #pragma unroll
