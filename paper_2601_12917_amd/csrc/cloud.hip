@@ -102,7 +102,7 @@ __global__ void __launch_bounds__(64 * kWaves, 2) gt_q_kernel(CloudSnaps g, int 
   T += (int64_t)(snap * gridDim.z + blockIdx.z) * t_part;
   // a lane past the last column (of G or of Q) repeats columns that exist: its results are not stored
   auto first_col = [&](int i) { const int64_t c = c0 + 4 * i; return NEAR && c > cols - 4 ? cols - 4 : c; };
-  const int64_t cl = first_col(i16);
+  const int64_t cl = first_col(i16), cb = first_col(0);      // cb <= cl: in a last strip of one to three columns the lanes start before c0
   int64_t cm[4];
 #pragma unroll
   for (int m = 0; m < 4; ++m) cm[m] = cl + m < cols ? cl + m : cols - 1;
@@ -118,12 +118,12 @@ __global__ void __launch_bounds__(64 * kWaves, 2) gt_q_kernel(CloudSnaps g, int 
   uint32_t go[kStep / 4], qo[kStep / 4][NT];            // byte offsets from the step's first row of G and of Q
 #pragma unroll
   for (int s = 0; s < kStep / 4; ++s) {
-    go[s] = (uint32_t)(4 * s + kg) * (uint32_t)ldg * 4u + (uint32_t)(cl - c0) * 4u;
+    go[s] = (uint32_t)(4 * s + kg) * (uint32_t)ldg * 4u + (uint32_t)(cl - cb) * 4u;
 #pragma unroll
     for (int t = 0; t < NT; ++t) qo[s][t] = ((uint32_t)(4 * s + kg) * (uint32_t)ldq + (uint32_t)jq[t]) * 4u;
   }
   auto fetch = [&](int64_t r0, Operands& o) {
-    const float* gr = G + r0 * ldg + c0;
+    const float* gr = G + r0 * ldg + cb;
     const float* qr = Q + r0 * ldq;
 #pragma unroll
     for (int s = 0; s < kStep / 4; ++s) {

@@ -89,6 +89,14 @@ def test_basis_without_sweeps_is_the_orthonormalised_product(rows, cols, s, k):
     assert np.abs(Uk.T @ Uk - np.eye(k)).max() <= 2e-6
 
 
+@pytest.mark.parametrize("rows,cols,s,k", [(130, 65, 1, 5), (96, 66, 2, 8), (200, 131, 1, 16), (270, 1281, 2, 5)])
+def test_sweeps_with_one_to_three_columns_in_the_last_strip(rows, cols, s, k):
+    """G^T Q takes 64 columns per workgroup and a lane's four columns end at the last: in a strip of one to three columns the
+    lanes start before the strip."""
+    snaps = _low_rank_snapshots(rows, cols, s, rank=max(k, 6), noise=1e-3, seed=rows + k)
+    _check_basis(snaps, k, n_iter=3)
+
+
 def test_lsq_gradient_and_basis_of_the_gradients_along_a_descent():
     """The cloud trains the least-squares model by gradient descent and keeps its last four gradients."""
     from paper_2601_12917_amd.session import cloud_lsq_gradient
