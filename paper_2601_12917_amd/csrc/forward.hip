@@ -831,6 +831,7 @@ __global__ void __launch_bounds__(64, 2) attention_f32_kernel(const T* __restric
   // a key past the end repeats the last one: its probability is zero
   auto k_row = [&](int k0) { const int key = k0 + l32; return base + (size_t)(key < last ? key : last - 1) * ld + d + half * HK; };
   if (last > 0) load_row(k_row(0), k);
+  uint32_t wild = 0;                                                 // bit v F + f: vv[v][f] of the block on the diagonal is infinite or NaN
   for (int k0 = 0; k0 < last; k0 += 32) {
     float vv[16][F];
 #pragma unroll
@@ -861,6 +862,14 @@ __global__ void __launch_bounds__(64, 2) attention_f32_kernel(const T* __restric
     for (int v = 0; v < 16; ++v) { s[v] = __builtin_amdgcn_exp2f(s[v] - msafe); sum += s[v]; }
     den = den * corr + sum;
     mx = mnew;
+    // The block on the diagonal (the wave's last) holds keys that some of its queries do not see.  Their probability is zero, but zero
+    // times an infinite V would be NaN: such entries go into the product as zeros, and what the queries that do see the key get is made infinite after the loop.
+    if (causal && k0 == q0) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v)
+#pragma unroll
+        for (int f = 0; f < F; ++f) if (!__builtin_isfinite(vv[v][f])) { wild |= 1u << (v * F + f); vv[v][f] = 0.f; }
+    }
 #pragma unroll
     for (int f = 0; f < F; ++f)
 #pragma unroll
@@ -869,6 +878,15 @@ __global__ void __launch_bounds__(64, 2) attention_f32_kernel(const T* __restric
     for (int v = 0; v < 16; ++v)
 #pragma unroll
       for (int f = 0; f < F; ++f) o[f] = __builtin_amdgcn_mfma_f32_32x32x2f32(vv[v][f], s[v], o[f], 0, 0, 0);
+  }
+  if (__ballot(wild != 0)) {                                         // 3e38 times 3e38 is infinite, and 0 times it is 0
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int key = q0 + 8 * (v >> 2) + 4 * half + (v & 3);
+      const float sees = key < last && key <= qi ? 3e38f : 0.f;
+#pragma unroll
+      for (int f = 0; f < F; ++f) o[f] = __builtin_amdgcn_mfma_f32_32x32x2f32((wild >> (v * F + f)) & 1u ? 3e38f : 0.f, sees, o[f], 0, 0, 0);
+    }
   }
   den += __shfl_xor(den, 32, 64);
   if (qi < seq) {

@@ -1,0 +1,46 @@
+"""Client forward passes (Session.loss, row losses) through the attention kernels at the edges of their blocks of 32 queries and keys."""
+import numpy as np
+import pytest
+
+import zgr_inputs as I
+from tests.util import inputs_of, make_batch_arrays, make_session, session_batch
+
+pytestmark = pytest.mark.gpu
+
+
+def _model(arch, dtype, head, batch, seq, **kw):
+    n_head = max(1, 64 // head) if dtype == "bf16" else 2
+    base = dict(name="attention", arch=arch, dtype=dtype, n_class=3 if arch == I.ARCH_ENCODER_CLS else 0, n_layer=2, d_model=head * n_head, n_head=n_head,
+                d_ff=128, vocab=307, max_pos=seq + 3, batch=batch, seq=seq, k=4, k_full=4, tokens="uniform")
+    return I.shrink(I.CONFIGS["cfg2"], **dict(base, **kw))
+
+
+@pytest.mark.parametrize("dtype,head,batch,seq", [
+    ("f32", 8, 2, 20), ("f32", 16, 2, 33), ("f32", 32, 1, 64), ("f32", 64, 2, 45), ("f32", 64, 1, 96),
+    ("bf16", 8, 2, 40), ("bf16", 16, 2, 40), ("bf16", 32, 1, 71)])
+def test_a_query_does_not_see_what_a_later_position_holds(dtype, head, batch, seq):
+    """Causal mask: a position whose activations are not finite leaves the losses of earlier ones as they are, bit for bit, and with
+    them the whole loss when it is the last position, which carries no target."""
+    from paper_2601_12917_amd import binding as B
+    cfg = _model(I.ARCH_DECODER_LM, dtype, head, batch, seq)
+    specs, values, bases = inputs_of(cfg)
+    sess = make_session(cfg, specs, values, bases)
+    b = session_batch(sess, cfg, make_batch_arrays(cfg))
+    pos = next(i for i, s in enumerate(specs) if s.role == I.ROLE_POS_EMB)
+    clean = sess.loss(b)
+    rows = sess.last_row_losses(batch * seq).reshape(batch, seq)
+    for p in sorted({seq - 1, seq - 2, seq // 2, 1}):
+        for bad in (np.inf, np.nan):
+            wild = np.array(values[pos], dtype=np.float32)
+            wild[p, 3] = bad
+            sess.set_theta(pos, wild)
+            if p == seq - 1:
+                assert sess.loss(b) == clean
+            else:
+                with pytest.raises(B.ZgrError) as e:
+                    sess.loss(b)
+                assert e.value.status == B.ZGR_ERR_NONFINITE
+            got = sess.last_row_losses(batch * seq).reshape(batch, seq)
+            assert np.array_equal(got[:, :p], rows[:, :p]), (p, bad)
+            assert np.all(np.isnan(got[:, p:seq - 1])), (p, bad)
+    sess.close()
