@@ -44,3 +44,25 @@ def test_a_query_does_not_see_what_a_later_position_holds(dtype, head, batch, se
             assert np.array_equal(got[:, :p], rows[:, :p]), (p, bad)
             assert np.all(np.isnan(got[:, p:seq - 1])), (p, bad)
     sess.close()
+
+
+@pytest.mark.parametrize("dtype,seq,batch,heads", [("f32", 1030, 32, 6), ("f32", 1024, 36, 6), ("bf16", 70, 5, 8), ("bf16", 33, 40, 8)])
+def test_heads_of_eight_by_either_kernel(dtype, seq, batch, heads):
+    """Heads of 8 take one of two kernels by storage type, mask, length and how many there are: a sequence's loss is the same alone and among
+    others (the sums run in another order: 2^-24 per term of a few hundred, amplified by 1 / sigma of two LayerNorms), and the oracle's."""
+    from oracle import forward as F
+    from tests.test_gpu_step import LOSS_RTOL
+    cfg = _model(I.ARCH_ENCODER_CLS, dtype, 8, batch, seq, n_layer=1, d_model=8 * heads, n_head=heads, d_ff=64)
+    specs, values, bases = inputs_of(cfg)
+    arrays = make_batch_arrays(cfg)
+    sess = make_session(cfg, specs, values, bases)
+    sess.loss(session_batch(sess, cfg, arrays))
+    together = sess.last_row_losses(batch)
+    P = {s.name: np.asarray(v, dtype=np.float64) for s, v in zip(specs, values)}
+    for i in (0, batch // 2, batch - 1):
+        one = {k: v[i:i + 1] for k, v in arrays.items()}
+        alone = sess.loss(sess.make_batch(one["x"], one["y"], one["lengths"], seq))
+        want = F.cls_loss(P, one["x"], one["lengths"], one["y"], cfg.n_layer, cfg.n_head, cfg.ln_eps, cfg.act, cfg.post_ln)
+        assert abs(alone - together[i]) <= (1e-5 if dtype == "f32" else 0.0) * abs(alone), (i, alone, together[i])
+        assert abs(alone - want) <= LOSS_RTOL[dtype] * abs(want), (i, alone, want)
+    sess.close()
