@@ -846,8 +846,8 @@ zgr_status zgr_cloud_basis(const float* const* snapshots, int32_t n_snap, int64_
   float* T = reinterpret_cast<float*>(ws + 2 * yb + align_up((size_t)cols * k * 4) + 256);
   float* part = T + kCloudSnaps * longer;
   const int64_t part_floats = (int64_t)((kCloudUnits - kCloudSnaps) * longer);
-  // the orthonormalisation's partial sums live there too, between the products: (ceil(rows / 64) + 2) k^2 doubles are at most
-  // 8 rows k + 24 k^2 <= 32 rows k bytes (k <= rows, k <= 64) of the region's 64 rows k
+  // the orthonormalisation's partial sums live there too, between the products: (2 ceil(rows / 64) + 3) k^2 doubles are at most
+  // 16 rows k + 40 k^2 <= 56 rows k bytes (k <= rows, k <= 64) of the region's 64 rows k
   double* orth = reinterpret_cast<double*>(T);
   auto batch_of = [&](int t0) {
     CloudSnaps g{};

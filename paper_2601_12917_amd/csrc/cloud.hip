@@ -300,32 +300,58 @@ __global__ void __launch_bounds__(64 * kWaves, 2) g_t_kernel(CloudSnaps g, int64
 
 // In-place orthonormalisation of the k columns of Y [rows, k] (row stride k), in the order of the columns: Gram-Schmidt in its
 // matrix form, Cholesky-QR, taken twice.  One round is
-//     W = Y^T Y        (fp64 sums, one partial W per block of rows: gram_kernel)
-//     W = L L^T        (sum_gram_kernel adds the partial W in their order, cholesky_kernel factorises: fp64, one workgroup)
+//     W = Y^T Y        (one partial W per block of rows: gram_kernel)
+//     W = L L^T        (sum_gram_kernel adds the partial W in their order, cholesky_kernel factorises: one workgroup)
 //     Y <- Y L^-T      (fp64: apply_factor_kernel)
-// Column j becomes y_j minus its projection on the earlier columns, divided by the norm that is left.  The second round takes
-// out what the first left of the earlier columns (at most cond(Y)^2 2^-53, 1e-4 at the dependence threshold), so the result is
-// orthonormal to the rounding of its fp32 entries.  A column that the earlier ones already span (norm below 1e-6 of what it
-// started with) is stored as zeros and counted in *dependent.
+// Column j becomes y_j minus its projection on the earlier columns, divided by the norm that is left.  A column of which the earlier
+// ones leave less than 1e-6 of its norm is stored as zeros and counted in *dependent.
+// The pivot of column j is the square of what is left of it, a difference of sums c^2 times as large, c being the size of the
+// coefficients with which the earlier columns make up y_j.  With columns that resemble each other c reaches 1e5 and more while each
+// column still leaves 1e-3 of itself: in fp64 the difference is rounding then, and whole columns were taken for dependent (64
+// overlapping bumps: 40 columns lost).  So the first round forms W and its pivots in pairs of doubles (106 bits: exact products of
+// fp32 entries, two-term sums), which decides as the residuals themselves do up to c of 1e8.  At 8192 x 64 that costs 20 us instead of
+// 10 for W and 40 instead of 25 for the factor.  The second round takes out what rounding of the coefficients and of Y to fp32 left of the earlier columns; its
+// columns are orthonormal to a few per cent already, and fp64 is enough: the result is orthonormal to the rounding of its entries.
 // The column-by-column form needs 3 k dependent sweeps over the rows, which one workgroup has to make: 33 ms for
 // 8192 x 64, waiting for the L2 in every sweep.  This form reads the block twice per round, spread over all the rows'
 // blocks, and what is serial (k pivots, one barrier each) stays inside one workgroup.
 constexpr int kGramRows = 64;        // rows staged at a time
 constexpr int kGramMaxParts = 128;   // partial W at most
 
-// part[p][i k + j] = sum over the rows of part p of Y[r][i] Y[r][j], for every i >= j (16 x 16 tiles on and below the diagonal).
+// A number as the sum of two doubles, |lo| <= ulp(hi).  The operations follow Knuth's two-sum and the exact product by fma; nothing in them
+// may be contracted or reordered.
+struct Pair { double hi, lo; };
+__device__ __forceinline__ Pair add_exact(double a, double b) {       // a + b = hi + lo
+#pragma clang fp contract(off)
+  const double s = a + b, t = s - a;
+  return {s, (a - (s - t)) + (b - t)};
+}
+__device__ __forceinline__ Pair add_pair(Pair a, Pair b) {
+#pragma clang fp contract(off)
+  const Pair s = add_exact(a.hi, b.hi);
+  const double lo = s.lo + (a.lo + b.lo), hi = s.hi + lo;
+  return {hi, lo - (hi - s.hi)};
+}
+__device__ __forceinline__ Pair mul_pair(Pair a, Pair b) {
+#pragma clang fp contract(off)
+  const double p = a.hi * b.hi;
+  return {p, __builtin_fma(a.lo, b.hi, __builtin_fma(a.hi, b.lo, __builtin_fma(a.hi, b.hi, -p)))};
+}
+
+// part[p][i k + j] = sum over the rows of part p of Y[r][i] Y[r][j], for every i >= j (16 x 16 tiles on and below the diagonal); with PAIRS
+// the low halves follow in the part's next k^2 entries.
 // Thread (tx, ty) holds element (16 a + ty, 16 b + tx) of each tile (a, b).  NT = ceil(k / 16) tiles.
-template <int NT>
+template <int NT, bool PAIRS>
 __global__ void __launch_bounds__(256) gram_kernel(const float* __restrict__ Y, int64_t rows, int k, int64_t rows_per_part, double* __restrict__ part) {
   __shared__ float Ys[kGramRows][NT * 16 + 1];
   const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
   const int64_t r_begin = (int64_t)blockIdx.x * rows_per_part;
   const int64_t r_end = rows < r_begin + rows_per_part ? rows : r_begin + rows_per_part;
-  double acc[NT][NT];
+  Pair acc[NT][NT];
 #pragma unroll
   for (int a = 0; a < NT; ++a)
 #pragma unroll
-    for (int b = 0; b <= a; ++b) acc[a][b] = 0.0;
+    for (int b = 0; b <= a; ++b) acc[a][b] = {0.0, 0.0};
   for (int64_t r0 = r_begin; r0 < r_end; r0 += kGramRows) {
     __syncthreads();
 #pragma unroll
@@ -342,53 +368,81 @@ __global__ void __launch_bounds__(256) gram_kernel(const float* __restrict__ Y, 
 #pragma unroll
       for (int a = 0; a < NT; ++a)
 #pragma unroll
-        for (int b = 0; b <= a; ++b) acc[a][b] = __builtin_fma(yi[a], yj[b], acc[a][b]);
+        for (int b = 0; b <= a; ++b) {
+          if (PAIRS) {
+#pragma clang fp contract(off)
+            const Pair s = add_exact(acc[a][b].hi, yi[a] * yj[b]);     // the product of two fp32 numbers is exact
+            acc[a][b] = {s.hi, acc[a][b].lo + s.lo};
+          } else {
+            acc[a][b].hi = __builtin_fma(yi[a], yj[b], acc[a][b].hi);
+          }
+        }
     }
   }
-  double* out = part + (int64_t)blockIdx.x * k * k;
+  const int n = k * k;
+  double* out = part + (int64_t)blockIdx.x * n * (PAIRS ? 2 : 1);
 #pragma unroll
   for (int a = 0; a < NT; ++a)
 #pragma unroll
     for (int b = 0; b <= a; ++b) {
       const int i = 16 * a + ty, j = 16 * b + tx;
-      if (i < k && j <= i) out[i * k + j] = acc[a][b];
+      if (i < k && j <= i) { out[i * k + j] = acc[a][b].hi; if (PAIRS) out[n + i * k + j] = acc[a][b].lo; }
     }
 }
 
-// W[e] = sum over p of part[p][e]: 64 entries per block, four threads per entry, each adding a quarter of the parts in order.
+// W[e] = sum over p of part[p][e] (n entries each, or n high and n low halves): 64 entries per block, four threads per entry, each
+// adding a quarter of the parts in order.
+template <bool PAIRS>
 __global__ void __launch_bounds__(256) sum_gram_kernel(const double* __restrict__ part, int n_parts, int n, double* __restrict__ W) {
-  __shared__ double sums[4][64];
-  const int e = blockIdx.x * 64 + (threadIdx.x & 63), q = threadIdx.x >> 6, per = (n_parts + 3) / 4;
-  double v = 0.0;
+  __shared__ double sums[PAIRS ? 2 : 1][4][64];
+  const int i64 = threadIdx.x & 63, e = blockIdx.x * 64 + i64, q = threadIdx.x >> 6, per = (n_parts + 3) / 4;
+  const int64_t stride = (int64_t)n * (PAIRS ? 2 : 1);
+  Pair v{0.0, 0.0};
   if (e < n) {
     const int end = n_parts < (q + 1) * per ? n_parts : (q + 1) * per;
 #pragma unroll 8
-    for (int p = q * per; p < end; ++p) v += part[(int64_t)p * n + e];
+    for (int p = q * per; p < end; ++p) {
+      if (PAIRS) v = add_pair(v, {part[p * stride + e], part[p * stride + n + e]});
+      else v.hi += part[p * stride + e];
+    }
   }
-  sums[q][threadIdx.x & 63] = v;
+  sums[0][q][i64] = v.hi;
+  if (PAIRS) sums[PAIRS ? 1 : 0][q][i64] = v.lo;
   __syncthreads();
-  if (q == 0 && e < n) W[e] = (sums[0][threadIdx.x] + sums[1][threadIdx.x]) + (sums[2][threadIdx.x] + sums[3][threadIdx.x]);
+  if (q != 0 || e >= n) return;
+  if (PAIRS) {
+    auto of = [&](int i) { return Pair{sums[0][i][i64], sums[PAIRS ? 1 : 0][i][i64]}; };
+    v = add_pair(add_pair(of(0), of(1)), add_pair(of(2), of(3)));
+    W[e] = v.hi;
+    W[n + e] = v.lo;
+  } else {
+    W[e] = (sums[0][0][i64] + sums[0][1][i64]) + (sums[0][2][i64] + sums[0][3][i64]);
+  }
 }
 
 // Factorises W [k][k] (its lower triangle is read) and inverts the factor: fac[i k + j] = (L^-1)_ji for i <= j, 0 otherwise and for
 // a dependent column j.  W = U D U^T with U unit lower triangular; X = U^-1 grows row by row under the same eliminations.
-// Thread (tx, ty) keeps the entries (16 a + ty, 16 b + tx) of what is left of W in registers, all of them updated at every pivot
-// (those of finished rows and columns are never read again), and those of X; the pivot's column and X's row go round through LDS, one barrier per pivot.
-// What bounds it is that chain of k barriers, LDS reads and reciprocals (about 0.35 us each).
-template <int NT>
+// Thread (tx, ty) keeps the entries (16 a + ty, 16 b + tx) of what is left of W in registers (W in pairs when PAIRS, X in fp64: the second round
+// takes up what that rounds), those of the tiles a pivot still reaches being updated; the pivot's column and X's row go round through
+// LDS, one barrier per pivot.
+// What bounds it is that chain of k barriers, LDS reads and reciprocals (0.4 us each at k = 64, 0.6 with pairs).
+template <int NT, bool PAIRS>
 __global__ void __launch_bounds__(256) cholesky_kernel(const double* __restrict__ W, int k, double* __restrict__ fac, int* __restrict__ dependent) {
-  __shared__ double col[2][NT * 16], row[2][NT * 16], pivots[NT * 16], norm0[NT * 16], inv[NT * 16];
+  __shared__ double col[2][PAIRS ? 2 : 1][NT * 16], row[2][NT * 16], pivots[NT * 16], norm0[NT * 16], inv[NT * 16];
   __shared__ int n_dep;
+  constexpr int LO = PAIRS ? 1 : 0;
   const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  double w[NT][NT], x[NT][NT];
+  Pair w[NT][NT];
+  double x[NT][NT];
 #pragma unroll
   for (int a = 0; a < NT; ++a)
 #pragma unroll
     for (int b = 0; b < NT; ++b) {
-      const int i = 16 * a + ty, j = 16 * b + tx;
+      const int i = 16 * a + ty, j = 16 * b + tx, e = i >= j ? i * k + j : j * k + i;
+      const bool inside = i < k && j < k;
       x[a][b] = i == j ? 1.0 : 0.0;
-      w[a][b] = (i < k && j < k) ? W[i >= j ? i * k + j : j * k + i] : 0.0;
-      if (i == j) norm0[j] = w[a][b];                 // the column's size before anything is taken out
+      w[a][b] = {inside ? W[e] : 0.0, PAIRS && inside ? W[k * k + e] : 0.0};
+      if (i == j) norm0[j] = w[a][b].hi;              // the column's size before anything is taken out
     }
   if (tid == 0) n_dep = 0;
 #pragma unroll
@@ -398,26 +452,40 @@ __global__ void __launch_bounds__(256) cholesky_kernel(const double* __restrict_
       if (j >= k) break;                              // uniform
       if (tx == jj)
 #pragma unroll
-        for (int a = 0; a < NT; ++a) col[j & 1][16 * a + ty] = w[a][b];
+        for (int a = b; a < NT; ++a) { col[j & 1][0][16 * a + ty] = w[a][b].hi; if (PAIRS) col[j & 1][LO][16 * a + ty] = w[a][b].lo; }
       if (ty == jj)
 #pragma unroll
-        for (int c = 0; c < NT; ++c) row[j & 1][16 * c + tx] = x[b][c];
+        for (int c = 0; c <= b; ++c) row[j & 1][16 * c + tx] = x[b][c];
       __syncthreads();
-      const double pivot = col[j & 1][j];
-      const bool dep = !(pivot > 1e-12 * norm0[j]) || !(pivot > 0.0);
-      if (tid == 0) pivots[j] = dep ? 0.0 : pivot;
-      double ip = __builtin_amdgcn_rcp(pivot);        // two Newton steps take the estimate to fp64 rounding
-      ip = __builtin_fma(__builtin_fma(-pivot, ip, 1.0), ip, ip);
-      ip = __builtin_fma(__builtin_fma(-pivot, ip, 1.0), ip, ip);
-      if (dep) ip = 0.0;
-      double g[NT], h[NT];
+      auto col_at = [&](int i) { return Pair{col[j & 1][0][i], PAIRS ? col[j & 1][LO][i] : 0.0}; };
+      const Pair pivot = col_at(j);
+      const bool dep = !(pivot.hi > 1e-12 * norm0[j]) || !(pivot.hi > 0.0);
+      if (tid == 0) pivots[j] = dep ? 0.0 : pivot.hi;
+      Pair ip{__builtin_amdgcn_rcp(pivot.hi), 0.0};   // two Newton steps take the estimate to fp64 rounding, a third gives the low half
+      ip.hi = __builtin_fma(__builtin_fma(-pivot.hi, ip.hi, 1.0), ip.hi, ip.hi);
+      ip.hi = __builtin_fma(__builtin_fma(-pivot.hi, ip.hi, 1.0), ip.hi, ip.hi);
+      if (PAIRS) ip.lo = __builtin_fma(-pivot.lo, ip.hi, __builtin_fma(-pivot.hi, ip.hi, 1.0)) * ip.hi;
+      if (dep) ip = {0.0, 0.0};
+      Pair g[NT];
+      double h[NT];
 #pragma unroll
-      for (int c = 0; c < NT; ++c) { g[c] = col[j & 1][16 * c + tx]; h[c] = row[j & 1][16 * c + tx]; }
+      for (int c = b; c < NT; ++c) g[c] = col_at(16 * c + tx);
 #pragma unroll
-      for (int a = 0; a < NT; ++a) {
-        const double f = 16 * a + ty > j ? -col[j & 1][16 * a + ty] * ip : 0.0;
+      for (int c = 0; c <= b; ++c) h[c] = row[j & 1][16 * c + tx];
 #pragma unroll
-        for (int c = 0; c < NT; ++c) { w[a][c] = __builtin_fma(f, g[c], w[a][c]); x[a][c] = __builtin_fma(f, h[c], x[a][c]); }
+      for (int a = b; a < NT; ++a) {                  // rows behind the pivot's
+        Pair f{0.0, 0.0};
+        if (16 * a + ty > j) {
+          f = col_at(16 * a + ty);
+          if (PAIRS) { f = mul_pair({-f.hi, -f.lo}, ip); } else f.hi = -f.hi * ip.hi;
+        }
+#pragma unroll
+        for (int c = b; c < NT; ++c) {
+          if (PAIRS) w[a][c] = add_pair(w[a][c], mul_pair(f, g[c]));
+          else w[a][c].hi = __builtin_fma(f.hi, g[c].hi, w[a][c].hi);
+        }
+#pragma unroll
+        for (int c = 0; c <= b; ++c) x[a][c] = __builtin_fma(f.hi, h[c], x[a][c]);
       }
     }
   __syncthreads();
@@ -573,32 +641,34 @@ hipError_t launch_cloud_g_t_all(const CloudSnaps& g, int n_snap, int64_t rows, i
 }
 #undef ZGR_CLOUD_LAUNCH
 
-template <int NT>
+template <int NT, bool PAIRS>
 static hipError_t orth_round(float* Y, int64_t rows, int k, int* dependent, double* scratch, hipStream_t s) {
   const int64_t chunks = (rows + kGramRows - 1) / kGramRows;
   const int64_t per = (chunks + kGramMaxParts - 1) / kGramMaxParts, parts = (chunks + per - 1) / per;
   const int n = k * k;
-  double* W = scratch + parts * n;
-  double* fac = W + n;
-  hipLaunchKernelGGL(gram_kernel<NT>, dim3((unsigned)parts), dim3(256), 0, s, Y, rows, k, per * kGramRows, scratch);
-  hipLaunchKernelGGL(sum_gram_kernel, dim3((unsigned)((n + 63) / 64)), dim3(256), 0, s, scratch, (int)parts, n, W);
-  hipLaunchKernelGGL(cholesky_kernel<NT>, dim3(1), dim3(256), 0, s, W, k, fac, dependent);
+  constexpr int halves = PAIRS ? 2 : 1;
+  double* W = scratch + parts * n * halves;
+  double* fac = W + n * halves;
+  hipLaunchKernelGGL((gram_kernel<NT, PAIRS>), dim3((unsigned)parts), dim3(256), 0, s, Y, rows, k, per * kGramRows, scratch);
+  hipLaunchKernelGGL(sum_gram_kernel<PAIRS>, dim3((unsigned)((n + 63) / 64)), dim3(256), 0, s, scratch, (int)parts, n, W);
+  hipLaunchKernelGGL((cholesky_kernel<NT, PAIRS>), dim3(1), dim3(256), 0, s, W, k, fac, dependent);
   hipLaunchKernelGGL(apply_factor_kernel<NT>, dim3((unsigned)((rows + kApplyRows - 1) / kApplyRows)), dim3(256), 0, s, Y, rows, k, fac);
   return hipGetLastError();
 }
 
+template <int NT>
+static hipError_t orth(float* Y, int64_t rows, int k, int* dependent, double* scratch, hipStream_t s) {
+  const hipError_t e = orth_round<NT, true>(Y, rows, k, dependent, scratch, s);
+  return e != hipSuccess ? e : orth_round<NT, false>(Y, rows, k, dependent, scratch, s);      // its count includes the first round's zero columns
+}
+
 hipError_t launch_cloud_orth(float* Y, int64_t rows, int k, int* dependent, double* scratch, hipStream_t s) {
-  for (int round = 0; round < 2; ++round) {                 // the count of the second round includes the first one's zero columns
-    hipError_t e;
-    switch ((k + 15) / 16) {
-      case 1:  e = orth_round<1>(Y, rows, k, dependent, scratch, s); break;
-      case 2:  e = orth_round<2>(Y, rows, k, dependent, scratch, s); break;
-      case 3:  e = orth_round<3>(Y, rows, k, dependent, scratch, s); break;
-      default: e = orth_round<4>(Y, rows, k, dependent, scratch, s); break;
-    }
-    if (e != hipSuccess) return e;
+  switch ((k + 15) / 16) {
+    case 1:  return orth<1>(Y, rows, k, dependent, scratch, s);
+    case 2:  return orth<2>(Y, rows, k, dependent, scratch, s);
+    case 3:  return orth<3>(Y, rows, k, dependent, scratch, s);
+    default: return orth<4>(Y, rows, k, dependent, scratch, s);
   }
-  return hipSuccess;
 }
 
 hipError_t launch_cloud_copy_basis(const float* Q, int64_t rows, int k, float* U, int ldu, hipStream_t s) {

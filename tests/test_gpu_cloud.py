@@ -97,6 +97,68 @@ def test_sweeps_with_one_to_three_columns_in_the_last_strip(rows, cols, s, k):
     _check_basis(snaps, k, n_iter=3)
 
 
+def _bumps(rows, k, width):
+    """Overlapping Gaussian bumps: neighbours resemble each other, the coefficients of one in the others grow far past 1."""
+    return np.exp(-((np.linspace(0, 1, rows)[:, None] - np.linspace(0, 1, k)[None]) / width) ** 2)
+
+
+def _kahan(rows, k, angle):
+    """Kahan's triangle (columns of norm 1) on random orthonormal rows: coefficients grow like 1 / sin^k though every column leaves much of itself."""
+    s, c = np.sin(angle), np.cos(angle)
+    K = np.diag(s ** np.arange(k)) @ (np.eye(k) - c * np.triu(np.ones((k, k)), 1))
+    return np.linalg.qr(np.random.default_rng(k).standard_normal((rows, k)))[0] @ (K / np.linalg.norm(K, axis=0))
+
+
+def _decaying(rows, k, ratio):
+    rng = np.random.default_rng(k + rows)
+    return np.linalg.qr(rng.standard_normal((rows, k)))[0] * ratio ** np.arange(k) @ np.linalg.qr(rng.standard_normal((k, k)))[0].T
+
+
+def _gram_schmidt(Y):
+    """Column by column in long double, each projected three times: (Q, R^-1 of the kept columns, what each column leaves of its norm)."""
+    Y = Y.astype(np.longdouble)
+    k = Y.shape[1]
+    Q, left, kept = np.zeros_like(Y), np.zeros(k), []
+    for j in range(k):
+        y, n0 = Y[:, j].copy(), np.sqrt((Y[:, j] ** 2).sum())
+        for _ in range(3):
+            y -= Q[:, :j] @ (Q[:, :j].T @ y)
+        n = np.sqrt((y ** 2).sum())
+        left[j] = n / n0 if n0 > 0 else 0.0
+        if left[j] > 1e-6:
+            Q[:, j] = y / n
+            kept.append(j)
+    R = (Q[:, kept].T @ Y[:, kept]).astype(np.float64)
+    return Q.astype(np.float64), np.linalg.inv(np.triu(R)), left, kept
+
+
+@pytest.mark.parametrize("name,Y", [
+    ("bumps8", _bumps(512, 8, 1.0)), ("bumps8 wider", _bumps(512, 8, 1.6)), ("bumps16", _bumps(512, 16, 0.3)), ("bumps24", _bumps(700, 24, 0.2)),
+    ("bumps32", _bumps(512, 32, 0.15)), ("bumps64", _bumps(8200, 64, 0.06)), ("kahan24", _kahan(300, 24, 0.6)), ("kahan48", _kahan(300, 48, 0.9)),
+    ("kahan64", _kahan(300, 64, 1.2)), ("decay16", _decaying(600, 16, 0.5)), ("decay64", _decaying(600, 64, 0.85)),
+    ("dependent", np.concatenate([_bumps(256, 12, 0.2), _bumps(256, 12, 0.2)[:, :5] * 3, np.zeros((256, 1)), _bumps(256, 12, 0.2)[:, 2:4] + _bumps(256, 12, 0.2)[:, 5:7]], axis=1)),
+], ids=lambda v: v.replace(" ", "_") if isinstance(v, str) else "")
+def test_columns_that_resemble_each_other_stay_in_the_basis(name, Y, say):
+    """One snapshot Y, omega the identity, no sweeps: U is Gram-Schmidt of Y itself.  A column counts as dependent when it leaves less than
+    1e-6 of its norm, whatever the others' coefficients in it.  A kept column is q_j = sum_i (R^-1)_ij y_i, taken in fp64 from coefficients of
+    that precision and rounded to fp32 twice: |error| <= 2^-22 + 8 2^-53 sum_i |R^-1|_ij |y_i|."""
+    from paper_2601_12917_amd.session import cloud_basis
+    Y = Y.astype(np.float32)
+    rows, k = Y.shape
+    Q, Rinv, left, kept = _gram_schmidt(Y)
+    assert not np.any((left > 0.8e-6) & (left < 1.25e-6))                 # none so close to the line that rounding may decide
+    U, dep = cloud_basis([Y], k, np.eye(k, dtype=np.float32), 0)
+    U = U.astype(np.float64)
+    zero = ~np.any(U, axis=0)
+    assert dep == zero.sum() == k - len(kept)
+    assert np.array_equal(np.flatnonzero(~zero), kept)
+    tol = 2.0 ** -22 + 8 * 2.0 ** -53 * (np.abs(Rinv) * np.linalg.norm(Y[:, kept].astype(np.float64), axis=0)[:, None]).sum(axis=0)
+    err = np.linalg.norm(U[:, kept] - Q[:, kept], axis=0)
+    say(f"{name}: least left of a kept column {left[kept].min():.1e}, largest coefficient {np.abs(Rinv).max():.0e}, error {(err / tol).max():.2f} of its bound")
+    assert np.all(err <= tol), (err / tol).max()
+    assert np.abs(U[:, kept].T @ U[:, kept] - np.eye(len(kept))).max() <= 2e-6
+
+
 def test_lsq_gradient_and_basis_of_the_gradients_along_a_descent():
     """The cloud trains the least-squares model by gradient descent and keeps its last four gradients."""
     from paper_2601_12917_amd.session import cloud_lsq_gradient
