@@ -473,12 +473,10 @@ __global__ void __launch_bounds__(256) cholesky_kernel(const double* __restrict_
 #pragma unroll
       for (int c = 0; c <= b; ++c) h[c] = row[j & 1][16 * c + tx];
 #pragma unroll
-      for (int a = b; a < NT; ++a) {                  // rows behind the pivot's
-        Pair f{0.0, 0.0};
-        if (16 * a + ty > j) {
-          f = col_at(16 * a + ty);
-          if (PAIRS) { f = mul_pair({-f.hi, -f.lo}, ip); } else f.hi = -f.hi * ip.hi;
-        }
+      for (int a = b; a < NT; ++a) {
+        if (a == b && ty <= jj) continue;             // rows up to the pivot's are finished (and a factor of zero would not spare them a NaN)
+        Pair f = col_at(16 * a + ty);
+        if (PAIRS) f = mul_pair({-f.hi, -f.lo}, ip); else f.hi = -f.hi * ip.hi;
 #pragma unroll
         for (int c = b; c < NT; ++c) {
           if (PAIRS) w[a][c] = add_pair(w[a][c], mul_pair(f, g[c]));
@@ -529,11 +527,13 @@ __global__ void __launch_bounds__(256) apply_factor_kernel(float* __restrict__ Y
 #pragma unroll 4
     for (int i = 16 * t; i < 16 * t + 16; ++i) {
       const double y0 = (double)Ys[ty][i], y1 = (double)Ys[16 + ty][i];
+      // in the tile on the diagonal the factor's zeros are skipped: a later column that is not finite must not reach an earlier one
+      const bool up = i <= 16 * t + tx;
 #pragma unroll
       for (int b = t; b < NT; ++b) {
         const double f = F[i][16 * b + tx];
-        acc[0][b] = __builtin_fma(y0, f, acc[0][b]);
-        acc[1][b] = __builtin_fma(y1, f, acc[1][b]);
+        acc[0][b] = __builtin_fma(b > t || up ? y0 : 0.0, f, acc[0][b]);
+        acc[1][b] = __builtin_fma(b > t || up ? y1 : 0.0, f, acc[1][b]);
       }
     }
 #pragma unroll

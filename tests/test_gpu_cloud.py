@@ -159,6 +159,22 @@ def test_columns_that_resemble_each_other_stay_in_the_basis(name, Y, say):
     assert np.abs(U[:, kept].T @ U[:, kept] - np.eye(len(kept))).max() <= 2e-6
 
 
+@pytest.mark.parametrize("rows,k,bad,n_iter", [(96, 20, 7, 0), (130, 64, 33, 1), (64, 16, 15, 2), (70, 5, 0, 1)])
+def test_a_column_that_is_not_finite_leaves_the_earlier_ones_alone(rows, k, bad, n_iter):
+    """The columns before it come out bit for bit as without it; it and those after it count as dependent."""
+    from paper_2601_12917_amd.session import cloud_basis
+    rng = np.random.default_rng(rows + k)
+    G = rng.standard_normal((rows, 80)).astype(np.float32)
+    omega = rng.standard_normal((80, k)).astype(np.float32)
+    clean, dep = cloud_basis([G], k, omega, n_iter)
+    assert dep == 0
+    for value in (np.nan, np.inf):
+        omega[3, bad] = value
+        U, dep = cloud_basis([G], k, omega, n_iter)
+        assert np.array_equal(U[:, :bad], clean[:, :bad])
+        assert dep == k - bad
+
+
 def test_lsq_gradient_and_basis_of_the_gradients_along_a_descent():
     """The cloud trains the least-squares model by gradient descent and keeps its last four gradients."""
     from paper_2601_12917_amd.session import cloud_lsq_gradient
