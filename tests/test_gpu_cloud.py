@@ -57,6 +57,7 @@ def test_basis_of_snapshots_with_a_spectral_gap(rows, cols, s, k, ldu):
 
 @pytest.mark.parametrize("rows,cols,s,k", [
     (1, 1, 1, 1),                # a single entry
+    (300, 70, 2, 1),             # a single column: one round of the orthonormalisation
     (5, 3, 2, 3),                # fewer than four columns: the general form of the products
     (64, 18, 13, 16),            # columns no multiple of four, several launches of four snapshots, one whole column tile
     (65, 63, 5, 17),             # one row past a tile, one column past a tile of the block
