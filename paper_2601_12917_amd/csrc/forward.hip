@@ -1235,6 +1235,19 @@ hipError_t launch_layernorm(int dtype, const float* x, const void* g, const void
   return hipGetLastError();
 }
 
+// Whether an fp32 projection goes to product.hip, which splits its sums among waves and blocks, rather than to the 64 x 64 tiles through LDS.
+// That pays where the tiles leave CUs idle and the sum is long enough to share out; times of a product against those of the tiles, with GELU:
+//   up to 128 tiles      0.8 at K = 128, 0.4 - 0.7 at 1024; even at 64, 1.1 below
+//   129 to 256 tiles     3.2 at K = 32 (4096 x 256: 25 us against 8), 1.2 at 192, 1.03 at 384, 0.85 - 0.99 at 512, 0.65 at 4096
+//   257 to 319 tiles     1.1 - 1.2 at K = 768, 1.05 - 1.08 at 1024, 0.95 at 2048 (eight waves a tile, a few CUs with a second round of them)
+//   320 to 511 tiles     2.7 at K = 32, 1.2 at 128, 1.0 at 768, 0.91 - 0.97 at 1024
+// From 512 on the tiles are the faster form (2048 x 2304 x 768, 1152 tiles: 81 us against 93).
+static bool product_is_faster(int M, int N, int K) {
+  const int64_t tiles = (((int64_t)M + 63) / 64) * (((int64_t)N + 63) / 64);
+  if (tiles >= 512) return false;
+  return K >= (tiles <= 128 ? 64 : tiles <= 256 ? 512 : tiles < 320 ? 2048 : 1024);
+}
+
 hipError_t launch_gemm(int dtype, const void* A, const void* W, const void* bias, void* out, int epi, int M, int N, int K, hipStream_t s, float* scratch, size_t scratch_floats, bool keep_order) {
   GemmEpi ep{epi, out, bias};
   if (dtype == 0) {
@@ -1242,9 +1255,7 @@ hipError_t launch_gemm(int dtype, const void* A, const void* W, const void* bias
     const long t128 = (long)((M + 127) / 128) * ((N + 127) / 128);
     if (mfma_ok && t128 >= 512)   // enough 128 x 128 tiles for two blocks on every CU
       hipLaunchKernelGGL((gemm_f32_mfma_kernel<2, 16>), dim3((N + 127) / 128, (M + 127) / 128), dim3(256), 0, s, (const float*)A, (const float*)W, M, N, K, ep);
-    else if (mfma_ok && !keep_order && (long)((M + 63) / 64) * ((N + 63) / 64) < 512) {
-      // too few 64 x 64 tiles to fill the chip: sums split among waves and blocks (1000^3: 28 us against 44, 1024 x 768 x 3072: 57 against 88;
-      // from about 512 tiles on the LDS-tiled kernel is the faster one: 2048 x 2304 x 768, 1152 tiles, 81 us against 93)
+    else if (mfma_ok && !keep_order && product_is_faster(M, N, K)) {
       ProductArgs p;
       p.A = A; p.lda = K; p.B = W; p.b_k = true; p.ldb = K; p.C = (float*)out; p.ldc = N; p.M = M; p.N = N; p.K = K;
       p.epilogue = epi; p.bias = (const float*)bias; p.scratch = scratch; p.scratch_floats = scratch_floats;

@@ -88,6 +88,15 @@ F32_SHAPES = [
     (300, 200, 40, "64x64 matrix-core tiles, ragged both, k-tail"),
     (64, 64, 4, "one tile, a single quarter-filled k-tile"),
     (130, 70, 37, "K no multiple of 4: the vector-ALU kernel"),
+    (1000, 500, 60, "128 tiles of 64x64, the longest sum that stays with them"),
+    (1000, 500, 64, "the same tiles, sums split among waves"),
+    (4090, 250, 508, "256 tiles, the longest sum that stays with them"),
+    (490, 1900, 512, "240 tiles, sums split among eight waves"),
+    (1100, 1010, 1028, "288 tiles, a sum that stays with them"),
+    (1100, 1010, 2052, "288 tiles, sums split among eight waves"),
+    (1280, 1000, 1024, "320 tiles, sums split among four waves"),
+    (1280, 1020, 1020, "320 tiles, the longest sum that stays with them"),
+    (450, 4088, 1024, "512 tiles: no sums split"),
 ]
 
 
