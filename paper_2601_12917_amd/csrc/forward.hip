@@ -1113,39 +1113,40 @@ __global__ void __launch_bounds__(64 * NW) attention_mfma_kernel(const bf16_t* _
 }
 
 // ------------------------------------------------------------------ losses
-// Cross-entropy of one row of fp32 logits [n]: loss = logsumexp - logit[target]; target < 0: row skipped (loss 0).  1024 threads hold
-// 1024 MAXE entries in registers, so the row is read once (256 threads reading it twice: 135 us for 385 rows of 50272, now 26);
+// Cross-entropy of one row of fp32 logits [n]: loss = logsumexp - logit[target]; target < 0: row skipped (loss 0).  A block holds
+// THREADS MAXE entries in registers, so the row is read once (256 threads reading it twice: 135 us for 385 rows of 50272, now 26);
 // entries beyond those are read again.
-template <int MAXE>
-__global__ void __launch_bounds__(1024) ce_rows_kernel(const float* __restrict__ logits, const int32_t* __restrict__ targets, float* __restrict__ row_loss, int n) {
-  __shared__ float red[16];
+template <int THREADS, int MAXE>
+__global__ void __launch_bounds__(THREADS) ce_rows_kernel(const float* __restrict__ logits, const int32_t* __restrict__ targets, float* __restrict__ row_loss, int n) {
+  constexpr int WAVES = THREADS / 64;
+  __shared__ float red[WAVES];
   const int m = blockIdx.x, tid = threadIdx.x;
   int tgt = targets[m];
   if (tgt < 0) { if (tid == 0) row_loss[m] = 0.f; return; }          // uniform over the block
   tgt = tgt >= n ? n - 1 : tgt;
   const float* row = logits + (size_t)m * n;
-  auto across = [&](float v, bool maximum) {                          // the block's 16 waves, in order
+  auto across = [&](float v, bool maximum) {                          // the block's waves, in order
     v = maximum ? wave_max(v) : wave_sum(v);
     __syncthreads();
     if ((tid & 63) == 0) red[tid >> 6] = v;
     __syncthreads();
     float r = red[0];
-    for (int w = 1; w < 16; ++w) r = maximum ? fmaxf(r, red[w]) : r + red[w];
+    for (int w = 1; w < WAVES; ++w) r = maximum ? fmaxf(r, red[w]) : r + red[w];
     return r;
   };
   float v[MAXE], mx = -INFINITY;
 #pragma unroll
   for (int u = 0; u < MAXE; ++u) {
-    const int i = tid + 1024 * u;
+    const int i = tid + THREADS * u;
     v[u] = i < n ? row[i] : -INFINITY;
     mx = fmaxf(mx, v[u]);
   }
-  for (int i = tid + 1024 * MAXE; i < n; i += 1024) mx = fmaxf(mx, row[i]);
+  for (int i = tid + THREADS * MAXE; i < n; i += THREADS) mx = fmaxf(mx, row[i]);
   mx = across(mx, true);
   float s = 0.f;
 #pragma unroll
-  for (int u = 0; u < MAXE; ++u) s += tid + 1024 * u < n ? expf(v[u] - mx) : 0.f;
-  for (int i = tid + 1024 * MAXE; i < n; i += 1024) s += expf(row[i] - mx);
+  for (int u = 0; u < MAXE; ++u) s += tid + THREADS * u < n ? expf(v[u] - mx) : 0.f;
+  for (int i = tid + THREADS * MAXE; i < n; i += THREADS) s += expf(row[i] - mx);
   s = across(s, false);
   if (tid == 0) row_loss[m] = logf(s) + mx - row[tgt];
 }
@@ -1377,9 +1378,18 @@ hipError_t launch_lm_targets(const int32_t* tok, int32_t* tgt, int M, int seq, i
   return hipGetLastError();
 }
 
+// The smallest block that holds the row: threads without an entry, and iterations without one, cost as much as those with (2048 rows of 33 / 4097 /
+// 10000 / 20000, with the target and mean launches: 28 / 88 / 88 / 91 us when every row took 1024 threads of 4 or 50, now 20 / 28 / 37 / 58; 256
+// threads reading the row twice: 20 / 31 / 48 / 76).
 hipError_t launch_ce_rows(const float* logits, const int32_t* targets, float* row_loss, int M, int n, hipStream_t s) {
-  if (n <= 4 * 1024) hipLaunchKernelGGL(ce_rows_kernel<4>, dim3(M), dim3(1024), 0, s, logits, targets, row_loss, n);
-  else               hipLaunchKernelGGL(ce_rows_kernel<50>, dim3(M), dim3(1024), 0, s, logits, targets, row_loss, n);
+#define ZGR_CE_ROWS(THREADS, MAXE) hipLaunchKernelGGL((ce_rows_kernel<THREADS, MAXE>), dim3(M), dim3(THREADS), 0, s, logits, targets, row_loss, n)
+  if (n <= 1024)       ZGR_CE_ROWS(256, 4);
+  else if (n <= 4096)  ZGR_CE_ROWS(256, 16);
+  else if (n <= 8192)  ZGR_CE_ROWS(512, 16);
+  else if (n <= 16384) ZGR_CE_ROWS(512, 32);
+  else if (n <= 32768) ZGR_CE_ROWS(512, 64);
+  else                 ZGR_CE_ROWS(1024, 50);
+#undef ZGR_CE_ROWS
   return hipGetLastError();
 }
 

@@ -66,3 +66,21 @@ def test_heads_of_eight_by_either_kernel(dtype, seq, batch, heads):
         assert abs(alone - together[i]) <= (1e-5 if dtype == "f32" else 0.0) * abs(alone), (i, alone, together[i])
         assert abs(alone - want) <= LOSS_RTOL[dtype] * abs(want), (i, alone, want)
     sess.close()
+
+
+@pytest.mark.parametrize("vocab", [2, 1024, 1025, 4096, 4097, 8192, 8193, 16384, 16385, 32768, 32769, 51200, 51201])
+def test_row_losses_at_the_edges_of_the_cross_entropy_forms(vocab):
+    """fp32 logits: each row's loss against the oracle's at vocabularies where the block or the number of entries it holds changes
+    (sums of `vocab` exponentials in fp32: 2^-24 sqrt(vocab) of the loss at most, and a few roundings of the model's own)."""
+    from oracle import forward as F
+    cfg = _model(I.ARCH_DECODER_LM, "f32", 8, 2, 5, n_layer=1, d_model=16, n_head=2, d_ff=32, vocab=vocab)
+    specs, values, bases = inputs_of(cfg)
+    values = [v * np.float32(20) if s.role == I.ROLE_TOK_EMB else v for s, v in zip(specs, values)]          # logits of a few units
+    arrays = make_batch_arrays(cfg)
+    sess = make_session(cfg, specs, values, bases)
+    sess.loss(session_batch(sess, cfg, arrays))
+    got = sess.last_row_losses(10).reshape(2, 5)
+    want = F.lm_token_losses({s.name: np.asarray(v, dtype=np.float64) for s, v in zip(specs, values)}, arrays["x"], cfg.n_layer, cfg.n_head, cfg.ln_eps, cfg.act, cfg.post_ln)
+    assert np.all(got[:, 4] == 0)
+    assert np.abs(got[:, :4] - want.reshape(2, 4)).max() <= (2.0 ** -24 * np.sqrt(vocab) + 4e-6) * np.abs(want).max()
+    sess.close()
