@@ -1298,15 +1298,17 @@ int ce_partials_per_row(int N) { return ((N + 255) / 256) * 2; }
 hipError_t launch_gemm_ce_bf16(const void* A, const void* W, const int32_t* targets, void* part, float* tlogit, float* row_loss, int M, int N, int K, hipStream_t s) {
   if (K % GB_K != 0 || (size_t)M * K >= ((size_t)1 << 31) || (size_t)N * K >= ((size_t)1 << 31)) return hipErrorInvalidValue;
   // transposed product: the kernel's rows are the N vocabulary entries, its columns the M tokens.  The tile of 256 x 256 multiplies mostly
-  // nothing for a short prompt: up to 64 or 128 tokens take 128 vocabulary entries and no more tokens than that, with one wave
-  // across the entries, so that there is one partial per 128 entries as well (33 tokens, 50272 x 768: 98 us against 55).
+  // nothing for a short prompt: up to 128 tokens take tiles of 128 vocabulary entries x 64 tokens with one wave across the entries, so that
+  // there is one partial per 128 entries as well (50272 x 768, with the layer's own projections: 33 tokens 138 -> 94 us, 128 tokens 135 -> 91;
+  // 9000 x 2048: 102 -> 85).
+  // (One tile of 128 x 128 for 65 to 128 tokens reads the weights once instead of twice and was slower than the
+  // large tile on wide models: 50272 x 2048 247 us against 232, now 160.)
   const bf16_t* w = (const bf16_t*)W; const bf16_t* a = (const bf16_t*)A;
   hipError_t e;
   int n_part = ce_partials_per_row(N);
   if (M <= 128) {
     n_part = (N + 127) / 128;
-    e = M <= 64 ? launch_gemm_bf16_t<128, 64, 1, 2, 64, 3>(w, a, nullptr, part, EPI_CE, N, M, K, s, targets, tlogit)
-                : launch_gemm_bf16_t<128, 128, 1, 4, 64, 3>(w, a, nullptr, part, EPI_CE, N, M, K, s, targets, tlogit);
+    e = launch_gemm_bf16_t<128, 64, 1, 2, 64, 3>(w, a, nullptr, part, EPI_CE, N, M, K, s, targets, tlogit);
   } else {
     e = launch_gemm_bf16_t<256, 256, 2, 4, 64, 20, 1>(w, a, nullptr, part, EPI_CE, N, M, K, s, targets, tlogit);
   }

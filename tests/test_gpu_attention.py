@@ -84,3 +84,21 @@ def test_row_losses_at_the_edges_of_the_cross_entropy_forms(vocab):
     assert np.all(got[:, 4] == 0)
     assert np.abs(got[:, :4] - want.reshape(2, 4)).max() <= (2.0 ** -24 * np.sqrt(vocab) + 4e-6) * np.abs(want).max()
     sess.close()
+
+
+@pytest.mark.parametrize("vocab,batch,seq", [(307, 1, 2), (1000, 1, 64), (1025, 1, 65), (127, 2, 64), (4000, 1, 128), (300, 1, 129), (129, 3, 43)])
+def test_bf16_row_losses_of_short_prompts(vocab, batch, seq):
+    """The vocabulary product on tiles for up to 64, up to 128 and more tokens, vocabularies on either side of a tile of 128."""
+    from oracle import forward as F
+    from tests.test_gpu_step import LOSS_RTOL
+    cfg = _model(I.ARCH_DECODER_LM, "bf16", 64, batch, seq, n_layer=1, d_model=128, n_head=2, vocab=vocab)
+    specs, values, bases = inputs_of(cfg)
+    arrays = make_batch_arrays(cfg)
+    sess = make_session(cfg, specs, values, bases)
+    sess.loss(session_batch(sess, cfg, arrays))
+    got = sess.last_row_losses(batch * seq).reshape(batch, seq)
+    P = {s.name: sess.get_theta(i).astype(np.float64) for i, s in enumerate(specs)}
+    want = F.lm_token_losses(P, arrays["x"], cfg.n_layer, cfg.n_head, cfg.ln_eps, cfg.act, cfg.post_ln)
+    assert np.all(got[:, -1] == 0)
+    assert np.abs(got[:, :-1] - want).max() <= LOSS_RTOL["bf16"] * np.abs(want).max()
+    sess.close()
