@@ -15,6 +15,56 @@ def _model(arch, dtype, head, batch, seq, **kw):
     return I.shrink(I.CONFIGS["cfg2"], **dict(base, **kw))
 
 
+LN_GAINS = (I.ROLE_LN1_G, I.ROLE_LN2_G, I.ROLE_LNF_G)
+
+
+def _check_row_losses(cfg, lengths=None):
+    """Row losses of one client forward against the oracle's, matrices scaled up so that the softmax is far from uniform.  fp32: a few hundred
+    roundings of 2^-24 through two blocks, amplified by the 1 / sigma of the LayerNorms; bf16: the tolerance of the step tests."""
+    from oracle import forward as F
+    from tests.test_gpu_step import LOSS_RTOL
+    specs, values, bases = inputs_of(cfg)
+    values = [v if s.role in LN_GAINS else v * np.float32(4) for s, v in zip(specs, values)]
+    arrays = make_batch_arrays(cfg)
+    if lengths is not None:
+        arrays["lengths"] = np.asarray(lengths, dtype=np.int32)
+    sess = make_session(cfg, specs, values, bases)
+    sess.loss(session_batch(sess, cfg, arrays))
+    P = {s.name: sess.get_theta(i).astype(np.float64).reshape(s.rows, s.cols) for i, s in enumerate(specs)}
+    if cfg.arch == I.ARCH_DECODER_LM:
+        got = sess.last_row_losses(cfg.batch * cfg.seq).reshape(cfg.batch, cfg.seq)
+        assert np.all(got[:, -1] == 0)
+        got = got[:, :-1]
+        want = F.lm_token_losses(P, arrays["x"], cfg.n_layer, cfg.n_head, cfg.ln_eps, cfg.act, cfg.post_ln)
+    else:
+        got = sess.last_row_losses(cfg.batch)
+        want = F.cls_row_losses(P, arrays["x"], arrays["lengths"], arrays["y"], cfg.n_layer, cfg.n_head, cfg.ln_eps, cfg.act, cfg.post_ln)
+    sess.close()
+    tol = 2e-5 if cfg.dtype == "f32" else LOSS_RTOL["bf16"]
+    assert np.abs(got - want).max() <= tol * np.abs(want).max(), np.abs(got - want).max() / np.abs(want).max()
+
+
+@pytest.mark.parametrize("seq", [1 + 1, 31, 32, 33, 64, 65, 77, 128])
+@pytest.mark.parametrize("dtype,head", [("f32", 8), ("f32", 16), ("f32", 32), ("f32", 64), ("bf16", 8), ("bf16", 16), ("bf16", 32)])
+def test_decoder_rows_at_the_edges_of_the_attention_blocks(dtype, head, seq):
+    _check_row_losses(_model(I.ARCH_DECODER_LM, dtype, head, 3, seq))
+
+
+@pytest.mark.parametrize("seq,lengths", [(33, [1, 31, 32, 33]), (64, [32, 33, 63, 64]), (65, [1, 32, 64, 65]), (77, [33, 64, 65, 77]), (100, [96, 97, 2, 100])])
+@pytest.mark.parametrize("dtype,head", [("f32", 8), ("f32", 16), ("f32", 32), ("f32", 64), ("bf16", 8), ("bf16", 16), ("bf16", 32)])
+def test_encoder_rows_with_lengths_inside_and_at_the_edges_of_key_blocks(dtype, head, seq, lengths):
+    _check_row_losses(_model(I.ARCH_ENCODER_CLS, dtype, head, len(lengths), seq), lengths)
+
+
+@pytest.mark.parametrize("arch", [I.ARCH_DECODER_LM, I.ARCH_ENCODER_CLS], ids=["decoder", "encoder"])
+@pytest.mark.parametrize("act,post_ln", [("gelu", False), ("relu", True)])
+@pytest.mark.parametrize("batch,seq,d_ff", [(1, 29, 2048), (3, 21, 2052), (2, 64, 4096)])
+def test_long_feed_forward_sums_split_over_blocks(arch, act, post_ln, batch, seq, d_ff):
+    """fp32 projections back from a feed-forward width of 2048 and more: the sum is split over blocks and its parts lie in an activation
+    buffer that the pass has no use for at that moment."""
+    _check_row_losses(_model(arch, "f32", 32, batch, seq, d_model=96, n_head=3, d_ff=d_ff, act=act, post_ln=post_ln))
+
+
 @pytest.mark.parametrize("dtype,head,batch,seq", [
     ("f32", 8, 2, 20), ("f32", 16, 2, 33), ("f32", 32, 1, 64), ("f32", 64, 2, 45), ("f32", 64, 1, 96),
     ("bf16", 8, 2, 40), ("bf16", 16, 2, 40), ("bf16", 32, 1, 71)])

@@ -94,12 +94,13 @@ def test_fp32_gradients_match_the_oracle_entry_by_entry(which, say):
     dict(d_model=2056, n_head=257, d_ff=36, vocab=70, max_pos=7, batch=3, seq=5),      # rows past what a wave holds
     dict(d_model=24, n_head=3, d_ff=35, vocab=33, max_pos=33, batch=7, seq=33),        # odd feed-forward width: entries left over by the four-wide activation
     dict(d_model=8, n_head=1, d_ff=8, vocab=52001, max_pos=4, batch=2, seq=3),         # more logits per row than a block of the cross-entropy rule holds
-    dict(d_model=64, n_head=1, d_ff=32, vocab=90, max_pos=66, batch=3, seq=33),        # one query past a wave's 32, head size 64
+    dict(d_model=64, n_head=1, d_ff=32, vocab=90, max_pos=66, batch=3, seq=33),        # head size 64: the attention rule's products over 33, 64 and 65 keys
     dict(d_model=128, n_head=2, d_ff=32, vocab=90, max_pos=66, batch=2, seq=64),
-    dict(arch=I.ARCH_ENCODER_CLS, n_class=3, d_model=64, n_head=1, d_ff=32, vocab=90, max_pos=66, batch=6, seq=65),   # padded keys, no causal mask
+    dict(arch=I.ARCH_ENCODER_CLS, n_class=3, d_model=64, n_head=1, d_ff=32, vocab=90, max_pos=66, batch=6, seq=65),   # and with padded keys, no causal mask
 ], ids=lambda k: f"d{k['d_model']}h{k['n_head']}t{k['seq']}")
 def test_fp32_gradients_at_the_edges_of_the_row_rules(kw):
-    """Same comparison and bound as above, one block, at the sizes where the row-wise rules change form."""
+    """Same comparison and bound as above, one block, at the sizes where the row-wise rules change form.  (The forward half of this pass takes
+    attention key by key; test_gpu_attention.py has the client's attention kernels.)"""
     cfg = I.shrink(I.CONFIGS["cfg2"], **dict(TINY_LM, name="bw_rows", n_layer=1, **kw))
     sess, specs, P = _setup(cfg)
     arrays = _batch(cfg, 3)

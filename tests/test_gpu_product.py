@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 # (a dtype, a along k, b dtype, b along k)
 FORMS = [("f32", 1, "f32", 0), ("f32", 1, "bf16", 0), ("f32", 0, "f32", 0), ("f32", 0, "bf16", 0), ("f32", 1, "f32", 1), ("f32", 1, "bf16", 1), ("bf16", 1, "bf16", 1)]
 #        M     N    K  batches pad
-SIZES = [(1, 1, 1, 1, 0), (3, 2, 5, 3, 0), (4, 4, 16, 2, 4), (63, 65, 17, 1, 1), (64, 64, 64, 5, 0), (65, 130, 15, 2, 2), (130, 66, 1040, 1, 0), (77, 100, 4100, 1, 4), (2100, 2050, 40, 1, 6)]
+SIZES = [(1, 1, 1, 1, 0), (3, 2, 5, 3, 0), (4, 4, 16, 2, 4), (63, 65, 17, 1, 1), (64, 64, 64, 5, 0), (65, 130, 15, 2, 2), (130, 66, 1040, 1, 0), (77, 100, 4100, 1, 4), (5, 36, 35001, 1, 3), (2100, 2050, 40, 1, 6)]
 
 
 @pytest.mark.parametrize("form", FORMS, ids=lambda f: f"{f[0]}{'k' if f[1] else 'i'}-{f[2]}{'k' if f[3] else 'j'}")
@@ -31,14 +31,15 @@ def test_product_matches_fp64(form, M, N, K, batches, pad):
     A = operand(*((M, K) if a_k else (K, M)), a_t)
     Bm = operand(*((N, K) if b_k else (K, N)), b_t)
     ldc = N + pad
-    out = torch.full((batches, M, ldc), 7.0, device=dev)
-    sums = torch.full((M,), 7.0, device=dev) if not a_k and batches == 1 else None
     scratch = torch.full((1 << 20,), float("nan"), device=dev)
     ad = A[:, :, :K if a_k else M].double()
     bd = Bm[:, :, :K if b_k else N].double()
     ad, bd = (ad if a_k else ad.transpose(1, 2)).cpu(), (bd.transpose(1, 2) if b_k else bd).cpu()
     want, mag = -0.5 * torch.stack([x @ y for x, y in zip(ad, bd)]), 0.5 * torch.stack([x.abs() @ y.abs() for x, y in zip(ad, bd)])
     for use_scratch in (True, False):
+        out = torch.full((batches, M, ldc), 7.0, device=dev)
+        out[:, :, :N] = float("nan")                       # every entry has to be written, each time
+        sums = torch.full((M,), float("nan"), device=dev) if not a_k and batches == 1 else None
         B.check(B.lib().zgr_debug_product(A.data_ptr(), int(a_t == "bf16"), a_k, A.shape[2], A[0].numel(), Bm.data_ptr(), int(b_t == "bf16"), b_k, Bm.shape[2], Bm[0].numel(),
                                           out.data_ptr(), ldc, M * ldc, M, N, K, -0.5, batches, sums.data_ptr() if sums is not None else None, 0, None,
                                           scratch.data_ptr() if use_scratch else None, scratch.numel() if use_scratch else 0, torch.cuda.current_stream().cuda_stream))
