@@ -908,7 +908,7 @@ struct BwCarve {
   size_t split = 0;                  // parts of split sums
   size_t total = 0;
 };
-constexpr size_t kProductScratch = ((size_t)1 << 21) + ((size_t)1 << 17);      // floats: 2048 waves, four to a 64 x 64 result, and row sums
+constexpr size_t kProductScratch = ((size_t)1 << 20) + ((size_t)1 << 14);      // floats: split sums take 2048 waves at most, eight to a 64 x 64 result, and 64 row sums each
 
 BwCarve bw_carve(const zgr_ctx* c, int batch, int seq) {
   BwCarve v;
