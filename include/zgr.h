@@ -250,8 +250,9 @@ zgr_status zgr_cloud_lsq_gradient(const float* W, const float* X, const float* Y
  * Algorithm 1): *loss_out (HOST) = L(theta; batch) as zgr_loss defines it, and grads[i] (HOST array of n_grads = n_t
  * DEVICE pointers, caller-owned, each rows_i * cols_i fp32 row-major, overwritten) = dL/dtheta_i for every tensor the
  * context was created with, in fp32 whatever the storage type; theta itself is left untouched.  The forward half runs
- * the client's own kernels (so a bf16 model's intermediate results are bf16-rounded exactly as in zgr_loss, except
- * that the activation is evaluated from the fp32 pre-activation, GELU by its erf form) and keeps every layer's results
+ * the client's kernels, fp32 products and attention in their undivided forms (so a bf16 model's intermediate results are bf16-rounded
+ * as in zgr_loss, the losses agree to the rounding of sums in another order, and the activation is evaluated from the fp32
+ * pre-activation, GELU by its erf form) and keeps every layer's results
  * in `workspace` (DEVICE, 256-byte aligned, zgr_cloud_backward_workspace(ctx, batch, seq) bytes: it grows with
  * n_layer * batch * seq * (d_model + d_ff)); both activations and both LayerNorm placements of zgr_model are covered.
  * The backward half is deterministic (no atomics).  Runs on the context's stream and returns after it has finished.

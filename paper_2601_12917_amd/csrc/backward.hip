@@ -1,11 +1,11 @@
 // Backward pass of the cloud block of Algorithm 1 (back-propagation on the public dataset with the current weights,
 // whose gradients build the basis; Sec. 3.2, paragraph on guided perturbation sampling on the cloud): dL/dtheta of the loss of forward.hip, by the chain rule
-// layer by layer, in fp32.  The forward pass that precedes it runs the client's own kernels and keeps every layer's
-// intermediate results; these kernels take them back in reverse order.
+// layer by layer, in fp32.  The forward pass that precedes it runs the client's kernels (fp32 products and attention in their undivided
+// forms, forward.h) and keeps every layer's intermediate results; these kernels take them back in reverse order.
 //
 // This runs on the cloud once per stored gradient snapshot, not on the client's step.  The products run on the matrix cores (forward.hip
-// for bf16 operands, product.hip for the others); the row-wise rules take one workgroup per row.  Deterministic: no atomics, every
-// sum has a fixed order.
+// for bf16 operands, product.hip for the others); LayerNorm and attention's softmax take a wave per row (LayerNorm rows of more than 2048
+// entries a workgroup), cross-entropy a workgroup.  Deterministic: no atomics, every sum has a fixed order.
 #include "backward.h"
 #include "product.h"
 

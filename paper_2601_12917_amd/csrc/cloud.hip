@@ -9,7 +9,7 @@
 //     Q = orth(Y)
 //     n_iter times:  T_t = G_t^T Q,  Y = sum_t G_t T_t,  Q = orth(Y)
 // Each sweep reads every snapshot twice and is a pair of tall-skinny products (2 rows cols 4 bytes per
-// snapshot and sweep); orth is Gram-Schmidt in matrix form (Cholesky-QR) in fp64, taken twice.  The subspace converges like
+// snapshot and sweep); orth is Gram-Schmidt in matrix form (Cholesky-QR), taken twice, in pairs of doubles and in fp64.  The subspace converges like
 // (sigma_{k+1} / sigma_k)^(2 n): the caller picks n_iter for the gap it expects.
 #include "internal.h"
 

@@ -13,8 +13,9 @@ hipError_t launch_embed(int dtype, const int32_t* tok, const void* E, const void
 hipError_t launch_layernorm(int dtype, const float* x, const void* g, const void* b, void* out, int M, int d, float eps, hipStream_t s, float* xout = nullptr);
 // keep_order (launch_gemm, launch_attention): sums in the order in which the large tiles, and attention key by key, take them at every size.
 // The forward half of the cloud's backward pass asks for it: a ReLU's slope jumps where its argument changes sign, so sums taken in
-// another order there move the gradients by far more than their rounding (4e-3 of their norm on a 13-block bf16 model with head size
-// 32), while a loss, which is all the client's forward returns, follows smoothly.
+// another order there move the gradients of bf16 ReLU models by far more than their rounding (4e-3 of their norm on a 13-block model with head
+// size 32), while a loss, which is all the client's forward returns, follows smoothly.  Neither order is the more accurate one: what this keeps is
+// that gradients stay as they were.  It is asked for with every model, though fp32 and GELU models have no such jump.
 // out = epilogue(A[M,K] W[N,K]^T + bias); bf16 storage needs K % 64 == 0.  scratch (may be NULL): floats a split sum may be kept in meanwhile.
 hipError_t launch_gemm(int dtype, const void* A, const void* W, const void* bias, void* out, int epi, int M, int N, int K, hipStream_t s, float* scratch = nullptr,
                        size_t scratch_floats = 0, bool keep_order = false);
