@@ -162,6 +162,23 @@ def test_cloud_entry_points_validate_their_arguments_without_a_gpu():
     assert lib.zgr_cloud_backward(None, None, None, 0, C.byref(v), None, 0) == B.ZGR_ERR_NULL
 
 
+def test_the_counter_digest_covers_what_the_step_kernels_are_built_from():
+    """profiles/cfg5_hbm_traffic.json is used only while the digest of the step's kernel sources matches: every file that the two
+    kernel files of the step include, and the source behind each header that declares kernels of its own, has to be part of it."""
+    from paper_2601_12917_amd import build
+    seen, todo = set(), ["perturb.hip", "forward.hip"]
+    while todo:
+        name = todo.pop()
+        if name in seen:
+            continue
+        seen.add(name)
+        todo += re.findall(r'#include "([^"]+)"', open(os.path.join(build.CSRC, name)).read())
+        source = name.replace(".h", ".hip")
+        if name.endswith(".h") and source in build.SOURCES:
+            todo.append(source)
+    assert seen <= set(build.STEP_KERNEL_SOURCES), seen - set(build.STEP_KERNEL_SOURCES)
+
+
 def test_bench_refuses_more_than_one_gpu():
     """One GPU is all the library runs on: the benchmark says so instead of starting ranks."""
     import subprocess
