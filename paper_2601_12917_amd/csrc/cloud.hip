@@ -12,6 +12,7 @@
 // snapshot and sweep); orth is Gram-Schmidt in matrix form (Cholesky-QR), taken twice, in pairs of doubles and in fp64.  The subspace converges like
 // (sigma_{k+1} / sigma_k)^(2 n): the caller picks n_iter for the gap it expects.
 #include "internal.h"
+#include <type_traits>
 
 namespace zgr {
 
@@ -309,7 +310,7 @@ __global__ void __launch_bounds__(64 * kWaves, 2) g_t_kernel(CloudSnaps g, int64
 // coefficients with which the earlier columns make up y_j.  With columns that resemble each other c reaches 1e5 and more while each
 // column still leaves 1e-3 of itself: in fp64 the difference is rounding then, and whole columns were taken for dependent (64
 // overlapping bumps: 40 columns lost).  So the first round forms W and its pivots in pairs of doubles (106 bits: exact products of
-// fp32 entries, two-term sums), which decides as the residuals themselves do up to c of 1e8.  At 8192 x 64 that costs 20 us instead of
+// fp32 entries, two-term sums), which decides as the residuals themselves do up to c of 1e8.  At 8192 x 64 that costs 15 us instead of
 // 10 for W and 40 instead of 25 for the factor.  The second round takes out what rounding of the coefficients and of Y to fp32 left of the earlier columns; its
 // columns are orthonormal to a few per cent already, and fp64 is enough: the result is orthonormal to the rounding of its entries.
 // The column-by-column form needs 3 k dependent sweeps over the rows, which one workgroup has to make: 33 ms for
@@ -340,7 +341,9 @@ __device__ __forceinline__ Pair mul_pair(Pair a, Pair b) {
 
 // part[p][i k + j] = sum over the rows of part p of Y[r][i] Y[r][j], for every i >= j (16 x 16 tiles on and below the diagonal); with PAIRS
 // the low halves follow in the part's next k^2 entries.
-// Thread (tx, ty) holds element (16 a + ty, 16 b + tx) of each tile (a, b).  NT = ceil(k / 16) tiles.
+// Thread (tx, ty) holds element (16 a + ty, 16 b + tx) of each tile (a, b).  NT = ceil(k / 16) tiles.  With PAIRS the arithmetic is what bounds it (seven
+// operations an entry and row), and the rows of tiles are shared between two blocks of equal work: blockIdx.y = 0 takes those of first_half.
+template <int NT> constexpr bool first_half(int a) { return a == NT - 1 || (NT == 4 && a == 0); }
 template <int NT, bool PAIRS>
 __global__ void __launch_bounds__(256) gram_kernel(const float* __restrict__ Y, int64_t rows, int k, int64_t rows_per_part, double* __restrict__ part) {
   __shared__ float Ys[kGramRows][NT * 16 + 1];
@@ -360,24 +363,28 @@ __global__ void __launch_bounds__(256) gram_kernel(const float* __restrict__ Y, 
       Ys[rr][c] = (r0 + rr < r_end && c < k) ? Y[(r0 + rr) * k + c] : 0.f;
     }
     __syncthreads();
+    auto add_rows = [&](auto half) {
 #pragma unroll 2
-    for (int rr = 0; rr < kGramRows; ++rr) {
-      double yi[NT], yj[NT];
+      for (int rr = 0; rr < kGramRows; ++rr) {
+        double yi[NT], yj[NT];
 #pragma unroll
-      for (int a = 0; a < NT; ++a) { yi[a] = (double)Ys[rr][16 * a + ty]; yj[a] = (double)Ys[rr][16 * a + tx]; }
+        for (int a = 0; a < NT; ++a) { yi[a] = (double)Ys[rr][16 * a + ty]; yj[a] = (double)Ys[rr][16 * a + tx]; }
 #pragma unroll
-      for (int a = 0; a < NT; ++a)
+        for (int a = 0; a < NT; ++a)
 #pragma unroll
-        for (int b = 0; b <= a; ++b) {
-          if (PAIRS) {
+          for (int b = 0; b <= a; ++b) {
+            if (PAIRS) {
 #pragma clang fp contract(off)
-            const Pair s = add_exact(acc[a][b].hi, yi[a] * yj[b]);     // the product of two fp32 numbers is exact
-            acc[a][b] = {s.hi, acc[a][b].lo + s.lo};
-          } else {
-            acc[a][b].hi = __builtin_fma(yi[a], yj[b], acc[a][b].hi);
+              if (first_half<NT>(a) != decltype(half)::value) continue;
+              const Pair s = add_exact(acc[a][b].hi, yi[a] * yj[b]);     // the product of two fp32 numbers is exact
+              acc[a][b] = {s.hi, acc[a][b].lo + s.lo};
+            } else {
+              acc[a][b].hi = __builtin_fma(yi[a], yj[b], acc[a][b].hi);
+            }
           }
-        }
-    }
+      }
+    };
+    if (PAIRS && blockIdx.y) add_rows(std::false_type{}); else add_rows(std::true_type{});
   }
   const int n = k * k;
   double* out = part + (int64_t)blockIdx.x * n * (PAIRS ? 2 : 1);
@@ -386,7 +393,8 @@ __global__ void __launch_bounds__(256) gram_kernel(const float* __restrict__ Y, 
 #pragma unroll
     for (int b = 0; b <= a; ++b) {
       const int i = 16 * a + ty, j = 16 * b + tx;
-      if (i < k && j <= i) { out[i * k + j] = acc[a][b].hi; if (PAIRS) out[n + i * k + j] = acc[a][b].lo; }
+      const bool here = !PAIRS || first_half<NT>(a) == (blockIdx.y == 0);
+      if (here && i < k && j <= i) { out[i * k + j] = acc[a][b].hi; if (PAIRS) out[n + i * k + j] = acc[a][b].lo; }
     }
 }
 
@@ -478,7 +486,7 @@ __global__ void __launch_bounds__(256) cholesky_kernel(const double* __restrict_
         Pair f = col_at(16 * a + ty);
         if (PAIRS) f = mul_pair({-f.hi, -f.lo}, ip); else f.hi = -f.hi * ip.hi;
 #pragma unroll
-        for (int c = b; c < NT; ++c) {
+        for (int c = b; c <= a; ++c) {                // on and below the diagonal: nothing above it is read
           if (PAIRS) w[a][c] = add_pair(w[a][c], mul_pair(f, g[c]));
           else w[a][c].hi = __builtin_fma(f.hi, g[c].hi, w[a][c].hi);
         }
@@ -649,7 +657,7 @@ static hipError_t orth_round(float* Y, int64_t rows, int k, int* dependent, doub
   constexpr int halves = PAIRS ? 2 : 1;
   double* W = scratch + parts * n * halves;
   double* fac = W + n * halves;
-  hipLaunchKernelGGL((gram_kernel<NT, PAIRS>), dim3((unsigned)parts), dim3(256), 0, s, Y, rows, k, per * kGramRows, scratch);
+  hipLaunchKernelGGL((gram_kernel<NT, PAIRS>), dim3((unsigned)parts, PAIRS && NT > 1 ? 2 : 1), dim3(256), 0, s, Y, rows, k, per * kGramRows, scratch);
   hipLaunchKernelGGL(sum_gram_kernel<PAIRS>, dim3((unsigned)((n + 63) / 64)), dim3(256), 0, s, scratch, (int)parts, n, W);
   hipLaunchKernelGGL((cholesky_kernel<NT, PAIRS>), dim3(1), dim3(256), 0, s, W, k, fac, dependent);
   hipLaunchKernelGGL(apply_factor_kernel<NT>, dim3((unsigned)((rows + kApplyRows - 1) / kApplyRows)), dim3(256), 0, s, Y, rows, k, fac);
