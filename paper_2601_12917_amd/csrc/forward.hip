@@ -1241,12 +1241,12 @@ hipError_t launch_layernorm(int dtype, const float* x, const void* g, const void
 //   up to 128 tiles      0.8 at K = 128, 0.4 - 0.7 at 1024; even at 64, 1.1 below
 //   129 to 256 tiles     3.2 at K = 32 (4096 x 256: 25 us against 8), 1.2 at 192, 1.03 at 384, 0.85 - 0.99 at 512, 0.65 at 4096
 //   257 to 319 tiles     1.1 - 1.2 at K = 768, 1.05 - 1.08 at 1024, 0.95 at 2048 (eight waves a tile, a few CUs with a second round of them)
-//   320 to 511 tiles     2.7 at K = 32, 1.2 at 128, 1.0 at 768, 0.91 - 0.97 at 1024
+//   320 to 511 tiles     2.7 at K = 32, 1.2 at 128, 1.00 - 1.06 at 512, 0.94 - 1.01 at 768, 0.91 - 0.97 at 1024
 // From 512 on the tiles are the faster form (2048 x 2304 x 768, 1152 tiles: 81 us against 93).
 static bool product_is_faster(int M, int N, int K) {
   const int64_t tiles = (((int64_t)M + 63) / 64) * (((int64_t)N + 63) / 64);
   if (tiles >= 512) return false;
-  return K >= (tiles <= 128 ? 64 : tiles <= 256 ? 512 : tiles < 320 ? 2048 : 1024);
+  return K >= (tiles <= 128 ? 64 : tiles <= 256 ? 512 : tiles < 320 ? 2048 : 768);
 }
 
 hipError_t launch_gemm(int dtype, const void* A, const void* W, const void* bias, void* out, int epi, int M, int N, int K, hipStream_t s, float* scratch, size_t scratch_floats, bool keep_order) {

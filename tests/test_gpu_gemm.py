@@ -94,8 +94,8 @@ F32_SHAPES = [
     (490, 1900, 512, "240 tiles, sums split among eight waves"),
     (1100, 1010, 1028, "288 tiles, a sum that stays with them"),
     (1100, 1010, 2052, "288 tiles, sums split among eight waves"),
-    (1280, 1000, 1024, "320 tiles, sums split among four waves"),
-    (1280, 1020, 1020, "320 tiles, the longest sum that stays with them"),
+    (1280, 1000, 768, "320 tiles, sums split among four waves"),
+    (1280, 1020, 764, "320 tiles, the longest sum that stays with them"),
     (450, 4088, 1024, "512 tiles: no sums split"),
 ]
 
