@@ -865,10 +865,17 @@ __global__ void __launch_bounds__(64, 2) attention_f32_kernel(const T* __restric
     // The block on the diagonal (the wave's last) holds keys that some of its queries do not see.  Their probability is zero, but zero
     // times an infinite V would be NaN: such entries go into the product as zeros, and what the queries that do see the key get is made infinite after the loop.
     if (causal && k0 == q0) {
+      float zero = 0.f;                                              // stays zero while every entry is finite
 #pragma unroll
       for (int v = 0; v < 16; ++v)
 #pragma unroll
-        for (int f = 0; f < F; ++f) if (!__builtin_isfinite(vv[v][f])) { wild |= 1u << (v * F + f); vv[v][f] = 0.f; }
+        for (int f = 0; f < F; ++f) zero = __builtin_fmaf(vv[v][f], 0.f, zero);
+      if (__ballot(!(zero == 0.f))) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+#pragma unroll
+          for (int f = 0; f < F; ++f) if (!__builtin_isfinite(vv[v][f])) { wild |= 1u << (v * F + f); vv[v][f] = 0.f; }
+      }
     }
 #pragma unroll
     for (int f = 0; f < F; ++f)
