@@ -788,8 +788,8 @@ hipError_t launch_gemm_bf16_t(const bf16_t* A, const bf16_t* W, const bf16_t* bi
 }
 
 // ------------------------------------------------------------------ attention
-// fp32 on the matrix cores (v_mfma_f32_32x32x2_f32), for fp32 storage and for the head sizes the bf16 kernel below does not take.  One wave
-// per 32 queries of a head, keys in blocks of 32: S^T = K Q^T, then O^T += V^T P^T, everything in registers.  A lane supplies
+// fp32 on the matrix cores (v_mfma_f32_32x32x2_f32), for fp32 storage and for the head sizes the bf16 kernel below does not take (heads
+// of 8 in part only, see launch_attention_t).  One wave per 32 queries of a head, keys in blocks of 32: S^T = K Q^T, then O^T += V^T P^T, everything in registers.  A lane supplies
 // half a row of K and of Q (the contraction index is split as d = half DH/2 + s), holds 16 keys of one query column of S^T, and its
 // probabilities are the second product's operand as they are: instruction v sums over the keys 8 (v / 4) + 4 half + v % 4, in which order
 // the rows of V are loaded.  Operands come straight from global memory: V while S^T is formed, the next block's K behind it.
