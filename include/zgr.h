@@ -145,6 +145,16 @@ typedef struct {           /* HOST */
 size_t zgr_workspace_bytes(const zgr_model* model, const zgr_tensor* tensors, int32_t n_t,
                            int32_t max_batch, int32_t max_seq);
 
+/* The same with room for two copies of the parameters.  A workspace of at least
+ * this size lets zgr_step keep W + eps Z and W - eps Z side by side: Z is then
+ * generated once for the two forward passes and the restoration instead of
+ * three times, with the same results bit for bit.  What zgr_workspace_bytes
+ * asks for is enough for every call; with less than this the perturbations are
+ * applied in place one after the other.  Without a model (ZGR_ARCH_NONE) the
+ * two sizes are equal.                                                         */
+size_t zgr_workspace_bytes_copies(const zgr_model* model, const zgr_tensor* tensors, int32_t n_t,
+                                  int32_t max_batch, int32_t max_seq);
+
 /* Creates a context over n_t caller-owned tensors.  Copies the tensor table
  * and validates it against the model (every role present once per layer,
  * shapes consistent).  hip_stream is a hipStream_t (NULL = default stream).

@@ -50,6 +50,7 @@ class zgr_result(C.Structure):
 # every symbol include/zgr.h declares: name -> (restype, argtypes)
 SYMBOLS = {
     "zgr_workspace_bytes": (C.c_size_t, [C.POINTER(zgr_model), C.POINTER(zgr_tensor), C.c_int32, C.c_int32, C.c_int32]),
+    "zgr_workspace_bytes_copies": (C.c_size_t, [C.POINTER(zgr_model), C.POINTER(zgr_tensor), C.c_int32, C.c_int32, C.c_int32]),
     "zgr_init": (C.c_int, [C.POINTER(C.c_void_p), C.POINTER(zgr_model), C.POINTER(zgr_tensor), C.c_int32, C.POINTER(zgr_config),
                            C.c_void_p, C.c_size_t, C.c_int32, C.c_int32, C.c_void_p]),
     "zgr_set_basis": (C.c_int, [C.c_void_p, C.c_int32, C.c_void_p, C.c_int32, C.c_int32]),

@@ -49,6 +49,8 @@ struct Carve {                 // workspace layout (byte offsets)
   size_t row_loss_stride = 0;                  // floats between the row losses of L+ (slot 0) and L- (slot 1)
   size_t spc[kSpcSlots] = {}, spc_bytes = 0;   // staging slots for the bases of one layer each (streamed bases)
   size_t total = 0;
+  size_t copies = 0, copy_bytes = 0;           // two copies of the parameters, copy_bytes apart; past `total`, only where the workspace has room for them
+  size_t total_with_copies = 0;
 };
 
 struct Prof {
@@ -80,6 +82,8 @@ struct zgr_ctx {
   TileRange res[2];            // tiles of the resident guided tensors, by class
   size_t min_stage_tiles = kMinStageTiles;   // consecutive layers share a stage until it holds this many tiles
   std::vector<TensorDesc> descs;
+  std::vector<size_t> copy_off;              // of each tensor in a copy of the parameters
+  bool copies = false;                       // the workspace holds the two copies
   std::vector<WorkItem> flat, tiles;
   bool lists_dirty = true;
   int max_k = 0, min_k = 0;
@@ -236,6 +240,7 @@ void build_lists(zgr_ctx* c) {
     d.theta = t.theta; d.U = guided ? t.U : nullptr; d.rows = t.rows; d.cols = t.cols; d.id = t.tensor_id;
     d.Uq = q4 ? c->qb[i].q : nullptr; d.qlambda = q4 ? c->qb[i].lambda : 0.f; d.qdelta = q4 ? c->qb[i].delta : 0.f;
     d.k = guided ? t.k : 0; d.ldu = t.ldu; d.dtype = t.dtype;
+    d.copy = (int64_t)c->copy_off[i];
     if (streamed) {
       // the basis of a streamed tensor is read from the staging slot its group rotates into, compact rows
       unsigned char* slot = c->ws + c->cv.spc[group_index % kSpcSlots] + c->hb[i].slot_off;
@@ -318,6 +323,27 @@ zgr_status check_model(zgr_ctx* c, const zgr_model& m, int dtype) {
   return ZGR_OK;
 }
 
+// Offsets of the tensors in a copy of the parameters.  What the forward pass reads as one matrix (Wq, Wk, Wv of a layer and their biases)
+// lies in one piece there as well, every other tensor on a multiple of 256 bytes.
+std::vector<size_t> copy_layout(const zgr_tensor* t, int n_t, size_t* bytes) {
+  std::vector<size_t> off((size_t)n_t, 0);
+  size_t end = 0;
+  auto bytes_of = [&](int i) { return (size_t)t[i].rows * (size_t)t[i].cols * elem_size(t[i].dtype); };
+  for (int i = 0; i < n_t; ++i) {
+    if (t[i].role == ZGR_ROLE_WK || t[i].role == ZGR_ROLE_WV || t[i].role == ZGR_ROLE_BK || t[i].role == ZGR_ROLE_BV) continue;
+    off[i] = end;
+    size_t next = end + bytes_of(i);
+    const int follow[2] = {t[i].role == ZGR_ROLE_WQ ? ZGR_ROLE_WK : ZGR_ROLE_BK, t[i].role == ZGR_ROLE_WQ ? ZGR_ROLE_WV : ZGR_ROLE_BV};
+    if (t[i].role == ZGR_ROLE_WQ || t[i].role == ZGR_ROLE_BQ)
+      for (int role : follow)
+        for (int j = 0; j < n_t; ++j)
+          if (t[j].role == role && t[j].layer == t[i].layer) { off[j] = next; next += bytes_of(j); }
+    end = align_up(next);
+  }
+  *bytes = end;
+  return off;
+}
+
 Carve carve(const zgr_model& m, const zgr_tensor* t, int n_t, int max_batch, int max_seq, int bits) {
   Carve cv;
   const int P = group_size(bits);
@@ -384,6 +410,12 @@ Carve carve(const zgr_model& m, const zgr_tensor* t, int n_t, int max_batch, int
     cv.row_loss = take(2 * cv.row_loss_stride * 4);
   }
   cv.total = off;
+  cv.total_with_copies = off;
+  if (m.arch != ZGR_ARCH_NONE) {               // a context without a model takes no step
+    copy_layout(t, n_t, &cv.copy_bytes);
+    cv.copies = off;
+    cv.total_with_copies = off + 2 * cv.copy_bytes;
+  }
   return cv;
 }
 
@@ -437,6 +469,7 @@ PerturbArgs perturb_args(zgr_ctx* c, uint64_t step) {
   a.k0 = (uint32_t)c->cfg.seed; a.k1 = (uint32_t)(c->cfg.seed >> 32);
   a.step = (uint32_t)step; a.bits = c->cfg.gauss_bits; a.dtype = c->dtype; a.max_k = c->max_k; a.min_k = c->min_k;
   a.tile_rows = tile_rows_of(c->cv.few_tiles, 0);
+  if (c->copies) for (int i = 0; i < 2; ++i) a.copy[i] = c->ws + c->cv.copies + (size_t)i * c->cv.copy_bytes;
   return a;
 }
 
@@ -492,11 +525,23 @@ zgr_status run_pass(zgr_ctx* c, PerturbArgs a, float coef) {
   return ZGR_OK;
 }
 
-zgr_status perturb_pass(zgr_ctx* c, uint64_t step, float coef) {
+zgr_status perturb_pass(zgr_ctx* c, uint64_t step, float coef, bool from_copy = false) {
   if (step >> 32) return fail(c, ZGR_ERR_CONFIG, "step must be < 2^32");
   zgr_status st = upload_lists(c);
   if (st != ZGR_OK) return st;
-  return run_pass(c, perturb_args(c, step), coef);
+  PerturbArgs a = perturb_args(c, step);
+  a.from_copy = from_copy ? 1 : 0;
+  return run_pass(c, a, coef);
+}
+
+// The passes + coef, - 2 coef and (restore) + coef of a step in one: the parameters of the two forward passes go into the copies.
+zgr_status spread_pass(zgr_ctx* c, uint64_t step, float coef, bool restore) {
+  if (step >> 32) return fail(c, ZGR_ERR_CONFIG, "step must be < 2^32");
+  zgr_status st = upload_lists(c);
+  if (st != ZGR_OK) return st;
+  PerturbArgs a = perturb_args(c, step);
+  a.spread = 1; a.restore = restore ? 1 : 0;
+  return run_pass(c, a, coef);
 }
 
 // One pass theta += sum_i coef[i] Z(seed, steps[i]), n <= kMaxBatch.
@@ -512,7 +557,11 @@ zgr_status perturb_pass_batched(zgr_ctx* c, int n, const uint64_t* steps, const 
 // ---------------------------------------------------------------- forward
 const void* T(zgr_ctx* c, int idx) { return c->t[idx].theta; }
 
-zgr_status forward_loss(zgr_ctx* c, const zgr_batch* b, int slot) {
+// The loss of the caller's parameters, or (from_copy) of copy `slot` of them.
+zgr_status forward_loss(zgr_ctx* c, const zgr_batch* b, int slot, bool from_copy = false) {
+  auto T = [&](zgr_ctx* ctx, int idx) -> const void* {
+    return from_copy ? ctx->ws + ctx->cv.copies + (size_t)slot * ctx->cv.copy_bytes + ctx->copy_off[idx] : ctx->t[idx].theta;
+  };
   const zgr_model& m = c->model;
   hipStream_t s = c->stream;
   unsigned char* ws = c->ws;
@@ -522,7 +571,7 @@ zgr_status forward_loss(zgr_ctx* c, const zgr_batch* b, int slot) {
   const int dt = c->dtype;
   if (m.arch == ZGR_ARCH_LINEAR_LSQ) {
     const zgr_tensor& w = c->t[c->lsq_w];
-    { ProfScope ps(c, ZGR_K_GEMM); HIP_TRY(c, launch_gemm(0, b->x, w.theta, nullptr, logits, EPI_F32, b->batch, (int)w.rows, (int)w.cols, s)); }
+    { ProfScope ps(c, ZGR_K_GEMM); HIP_TRY(c, launch_gemm(0, b->x, T(c, c->lsq_w), nullptr, logits, EPI_F32, b->batch, (int)w.rows, (int)w.cols, s)); }
     { ProfScope ps(c, ZGR_K_LOSS);
       HIP_TRY(c, launch_lsq_rows(logits, reinterpret_cast<const float*>(b->y), row_loss, b->batch, (int)w.rows, s));
       HIP_TRY(c, launch_mean_f64(row_loss, b->batch, 1.0 / b->batch, loss_dev, s)); }
@@ -662,6 +711,13 @@ size_t zgr_workspace_bytes(const zgr_model* model, const zgr_tensor* tensors, in
   return std::max(a, b);
 }
 
+size_t zgr_workspace_bytes_copies(const zgr_model* model, const zgr_tensor* tensors, int32_t n_t, int32_t max_batch, int32_t max_seq) {
+  if (zgr_workspace_bytes(model, tensors, n_t, max_batch, max_seq) == 0) return 0;
+  const size_t a = carve(*model, tensors, n_t, max_batch, max_seq, 32).total_with_copies;
+  const size_t b = carve(*model, tensors, n_t, max_batch, max_seq, 16).total_with_copies;
+  return std::max(a, b);
+}
+
 zgr_status zgr_init(zgr_ctx** out, const zgr_model* model, const zgr_tensor* tensors, int32_t n_t, const zgr_config* config,
                     void* workspace, size_t workspace_bytes, int32_t max_batch, int32_t max_seq, void* hip_stream) {
   if (!out) return fail(nullptr, ZGR_ERR_NULL, "out is NULL");
@@ -691,6 +747,9 @@ zgr_status zgr_init(zgr_ctx** out, const zgr_model* model, const zgr_tensor* ten
     delete c; return st;
   }
   c->ws = reinterpret_cast<unsigned char*>(workspace); c->ws_bytes = workspace_bytes;
+  size_t copy_bytes = 0;
+  c->copy_off = copy_layout(tensors, n_t, &copy_bytes);
+  c->copies = model->arch != ZGR_ARCH_NONE && workspace_bytes >= c->cv.total_with_copies;
   st = bind_model(c);
   if (st != ZGR_OK) { delete c; return st; }
   int dev = 0, n_cu = 0;
@@ -1232,16 +1291,24 @@ zgr_status zgr_step(zgr_ctx* c, uint64_t step, const zgr_batch* b, zgr_result* o
   zgr_status st = check_batch(c, b);
   if (st != ZGR_OK) return st;
   const float eps = c->cfg.eps;
-  if ((st = perturb_pass(c, step, eps)) != ZGR_OK) return st;                 // W + eps Z
-  st = forward_loss(c, b, 0);
-  zgr_status st2 = perturb_pass(c, step, -2.0f * eps);                        // W - eps Z
-  if (st == ZGR_OK && st2 == ZGR_OK) st = forward_loss(c, b, 1);
   const bool fuse = c->cfg.fuse_restore_update != 0;
-  zgr_status st3 = ZGR_OK;
-  if (!fuse || st != ZGR_OK || st2 != ZGR_OK) {
-    st3 = perturb_pass(c, step, eps);                                         // restore
-    if (st == ZGR_OK) st = st2 != ZGR_OK ? st2 : st3;
+  if (c->copies) {
+    // W + eps Z and W - eps Z as copies, W restored at once (a fused last pass restores from the second copy)
+    if ((st = spread_pass(c, step, eps, !fuse)) != ZGR_OK) return st;
+    st = forward_loss(c, b, 0, true);
+    if (st == ZGR_OK) st = forward_loss(c, b, 1, true);
     if (st != ZGR_OK) return st;
+  } else {
+    if ((st = perturb_pass(c, step, eps)) != ZGR_OK) return st;                 // W + eps Z
+    st = forward_loss(c, b, 0);
+    zgr_status st2 = perturb_pass(c, step, -2.0f * eps);                        // W - eps Z
+    if (st == ZGR_OK && st2 == ZGR_OK) st = forward_loss(c, b, 1);
+    zgr_status st3 = ZGR_OK;
+    if (!fuse || st != ZGR_OK || st2 != ZGR_OK) {
+      st3 = perturb_pass(c, step, eps);                                         // restore
+      if (st == ZGR_OK) st = st2 != ZGR_OK ? st2 : st3;
+      if (st != ZGR_OK) return st;
+    }
   }
   HIP_TRY(c, hipMemcpyAsync(c->host_loss, c->ws + c->cv.loss, 2 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
@@ -1253,7 +1320,7 @@ zgr_status zgr_step(zgr_ctx* c, uint64_t step, const zgr_batch* b, zgr_result* o
     // restore and update in one pass: + eps Z - lr g Z; a non-finite loss only restores
     const float lg = c->cfg.lr * out->g;
     const float coef = finite ? eps - lg : eps;
-    if ((st = perturb_pass(c, step, coef)) != ZGR_OK) return st;
+    if ((st = perturb_pass(c, step, coef, c->copies)) != ZGR_OK) return st;
     if (c->prof.on) HIP_TRY(c, hipStreamSynchronize(c->stream));
   }
   if (c->prof.on) prof_harvest(c);

@@ -19,6 +19,7 @@ struct TensorDesc {
   int32_t      k, ldu;   // ldu: row stride of U in floats, of Uq in bytes
   float        a, b;     // Z = a G + b U R   (a = 1, b = 0 when isotropic)
   int32_t      dtype;    // 0 fp32, 1 bf16
+  int64_t      copy;     // byte offset of the tensor in each of the two copies of the parameters (a multiple of 16)
 };
 
 // One unit of work of the perturbation kernels.
@@ -65,6 +66,10 @@ struct PerturbArgs {
   int32_t           n_q;
   uint32_t          qstep[kMaxBatch];
   float             qcoef[kMaxBatch];
+  // spread: the pass leaves theta + c Z in copy[0], that minus 2 c Z in copy[1] and, with restore, that plus c Z in theta, each
+  // rounded to the storage type.  from_copy: theta <- copy[1] + c Z.
+  unsigned char*    copy[2];
+  int32_t           spread, restore, from_copy;
   // bases of the NEXT launch's tensors, pulled over the host link by this launch while it computes
   int32_t           n_stage;
   int32_t           pull_blocks;   // set by the launchers: the last pull_blocks blocks of the grid only copy, the others only compute

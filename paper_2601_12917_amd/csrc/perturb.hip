@@ -132,12 +132,21 @@ __device__ __forceinline__ void pull_next_stage(const PerturbArgs& a, int part, 
 
 __global__ void __launch_bounds__(256) stage_only_kernel(PerturbArgs a) { pull_next_stage(a, blockIdx.x, gridDim.x); }
 
-// The P Gaussians of Philox call q of one stream.  BATCH: instead the combination sum_i qcoef[i] * (those of step
+// What a pass does with Z.
+//   kOne:    theta <- rnd(theta + c Z), theta read from the second copy instead when a.from_copy is set
+//   kBatch:  the same with a sum of perturbations in place of Z
+//   kSpread: what three passes with c, -2c and c leave behind, from one generation of Z and one read of theta: copy 0 <- rnd(theta + c Z),
+//            copy 1 <- rnd(copy 0 - 2c Z), theta <- rnd(copy 1 + c Z) (theta stays as it is when a.restore is 0)
+// The generator is what bounds kOne (466 cycles a call against 420 for the bytes); kSpread calls it once for four times a value's bytes and is
+// bound by those.  Steps of 1.3B bf16 parameters 29.0 -> 26.1 ms, of 350M 10.0 -> 9.1, of 125M 3.30 -> 3.21.
+enum { kOne = 0, kBatch = 1, kSpread = 2 };
+
+// The P Gaussians of Philox call q of one stream.  kBatch: instead the combination sum_i qcoef[i] * (those of step
 // qstep[i]), accumulated in the order of the list; since Z is linear in (G, R), a batched pass is the single
 // pass with this combination in place of G and of R and the coefficient 1.
-template <int P, bool BATCH>
+template <int P, int MODE>
 __device__ __forceinline__ void draw(uint64_t q, uint32_t id_stream, const PerturbArgs& a, const RadiusEntry* tab, float* g) {
-  if (!BATCH) {
+  if (MODE != kBatch) {
     gaussP<P>(philox_call(q, id_stream, a.step, a.k0, a.k1), tab, g);
   } else {
 #pragma unroll
@@ -150,6 +159,44 @@ __device__ __forceinline__ void draw(uint64_t q, uint32_t id_stream, const Pertu
       for (int j = 0; j < P; ++j) g[j] = __builtin_fmaf(ci, t[j], g[j]);
     }
   }
+}
+
+// Where the parameters of one tensor are read and written.
+template <typename T> struct Places { const T* src; T* theta; T* copy0; T* copy1; };
+template <typename T, int MODE> __device__ __forceinline__ Places<T> places_of(const TensorDesc& d, const PerturbArgs& a) {
+  Places<T> w;
+  w.theta = reinterpret_cast<T*>(d.theta);
+  w.copy0 = MODE == kSpread ? reinterpret_cast<T*>(a.copy[0] + d.copy) : nullptr;
+  w.copy1 = MODE == kSpread ? reinterpret_cast<T*>(a.copy[1] + d.copy) : nullptr;
+  w.src = MODE == kOne && a.from_copy ? reinterpret_cast<const T*>(a.copy[1] + d.copy) : w.theta;
+  return w;
+}
+
+// P parameters x (elements e0 .. e0 + P - 1) and their Z: every result rounded to the storage type before the next is taken from it.
+template <typename T, int P, int MODE>
+__device__ __forceinline__ void apply_z(const Places<T>& w, const PerturbArgs& a, int64_t e0, Vec<T, P> x, const float* z, float c) {
+  auto add = [&](float coef) {
+    float f[P];
+#pragma unroll
+    for (int j = 0; j < P; ++j) f[j] = __builtin_fmaf(coef, z[j], to_f32(x.v[j]));
+    round_into<P>(x, f);
+  };
+  add(c);
+  if (MODE != kSpread) { store_global(w.theta + e0, x); return; }
+  store_global(w.copy0 + e0, x);
+  add(-2.0f * c);
+  store_global(w.copy1 + e0, x);
+  if (a.restore) { add(c); store_global(w.theta + e0, x); }
+}
+template <typename T, int MODE>
+__device__ __forceinline__ void apply_z_elem(const Places<T>& w, const PerturbArgs& a, int64_t e, float z, float c) {
+  T x = load_global_elem(w.src + e);
+  from_f32(__builtin_fmaf(c, z, to_f32(x)), x);
+  if (MODE != kSpread) { store_global_elem(w.theta + e, x); return; }
+  store_global_elem(w.copy0 + e, x);
+  from_f32(__builtin_fmaf(-2.0f * c, z, to_f32(x)), x);
+  store_global_elem(w.copy1 + e, x);
+  if (a.restore) { from_f32(__builtin_fmaf(c, z, to_f32(x)), x); store_global_elem(w.theta + e, x); }
 }
 
 // The work list and the tensor descriptors are separate __restrict__ kernel parameters (besides being members
@@ -171,7 +218,7 @@ __global__ void __launch_bounds__(256) fill_flat_kernel(PerturbArgs a, const Ten
     for (int g = threadIdx.x; g < it.count; g += 256) {
       const int64_t q = it.first + g;
       float G[P];
-      draw<P, false>((uint64_t)q, d.id, a, tab, G);
+      draw<P, kOne>((uint64_t)q, d.id, a, tab, G);
       for (int j = 0; j < P; ++j) if (q * P + j < n) zout[q * P + j] = G[j];
     }
   }
@@ -196,7 +243,7 @@ template <typename V> __device__ __forceinline__ void wait_here_for(const V& v) 
 // block are requested before the generator runs for the current one, so kFlatSlots vectors per lane are in
 // flight under a whole item's arithmetic: the pass needs about 20 KB of reads in flight per compute unit to
 // keep HBM busy, and one 8-byte request per lane at a time, waited for after one call, supplies less than that.
-template <typename T, int P, bool BATCH>
+template <typename T, int P, int MODE>
 __global__ void __launch_bounds__(256) perturb_flat_kernel(PerturbArgs a, const TensorDesc* __restrict__ descs, const WorkItem* __restrict__ items,
                                                            float c, const RadiusEntry* __restrict__ gtab) {
   __shared__ RadiusEntry tab[kRadiusTabEntries];
@@ -215,7 +262,7 @@ __global__ void __launch_bounds__(256) perturb_flat_kernel(PerturbArgs a, const 
     const TensorDesc d = load_const(descs + it.tensor);
     const int64_t n = d.rows * d.cols;
     const int64_t last = n >= P ? (n - P) / P * P : 0;
-    const T* th = n >= P ? reinterpret_cast<const T*>(d.theta) : reinterpret_cast<const T*>(descs);
+    const T* th = n >= P ? places_of<T, MODE>(d, a).src : reinterpret_cast<const T*>(descs);
 #pragma unroll
     for (int j = 0; j < kFlatSlots; ++j) {
       int64_t e0 = (it.first + tid + 256 * j) * P;
@@ -232,7 +279,7 @@ __global__ void __launch_bounds__(256) perturb_flat_kernel(PerturbArgs a, const 
     const WorkItem it = load_const(items + w);
     const TensorDesc d = load_const(descs + it.tensor);
     const int64_t n = d.rows * d.cols;
-    T* __restrict__ th = reinterpret_cast<T*>(d.theta);
+    const Places<T> at = places_of<T, MODE>(d, a);
 #pragma unroll
     for (int j = 0; j < kFlatSlots; ++j) {
       const int g = tid + 256 * j;
@@ -244,22 +291,13 @@ __global__ void __launch_bounds__(256) perturb_flat_kernel(PerturbArgs a, const 
       if (g < it.count) {
         const int64_t q = it.first + g, e0 = q * P;
         float G[P];
-        draw<P, BATCH>((uint64_t)q, d.id, a, tab, G);
+        draw<P, MODE>((uint64_t)q, d.id, a, tab, G);
         if (e0 + P <= n) {
-          Vec<T, P> x = cur[j];
-          float f[P];
-#pragma unroll
-          for (int i = 0; i < P; ++i) f[i] = __builtin_fmaf(c, G[i], to_f32(x.v[i]));
-          round_into<P>(x, f);
-          store_global(th + e0, x);
+          apply_z<T, P, MODE>(at, a, e0, cur[j], G, c);
         } else {
           // ragged end of a tensor: element by element
           for (int i = 0; i < P; ++i)
-            if (e0 + i < n) {
-              T x = load_global_elem(th + e0 + i);
-              from_f32(__builtin_fmaf(c, G[i], to_f32(x)), x);
-              store_global_elem(th + e0 + i, x);
-            }
+            if (e0 + i < n) apply_z_elem<T, MODE>(at, a, e0 + i, G[i], c);
         }
       }
     }
@@ -272,31 +310,27 @@ __global__ void __launch_bounds__(256) perturb_flat_kernel(PerturbArgs a, const 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 // One lane's P consecutive elements starting at flat index e0: G from the seed, Z = a G + (b U R), axpy.
-template <typename T, int P, bool WRITE_Z, bool BATCH>
-__device__ __forceinline__ void finish_row(const TensorDesc& d, T* __restrict__ th, float* __restrict__ zout, int64_t e0, const float* ur,
+template <typename T, int P, bool WRITE_Z, int MODE>
+__device__ __forceinline__ void finish_row(const TensorDesc& d, const Places<T>& at, float* __restrict__ zout, int64_t e0, const float* ur,
                                            float c, const PerturbArgs& a, const RadiusEntry* tab) {
   float G[P];
-  draw<P, BATCH>((uint64_t)e0 / P, d.id, a, tab, G);
+  draw<P, MODE>((uint64_t)e0 / P, d.id, a, tab, G);
   if (WRITE_Z) {
 #pragma unroll
     for (int j = 0; j < P; ++j) zout[e0 + j] = __builtin_fmaf(d.a, G[j], ur[j]);
   } else {
-    Vec<T, P> x = load_global<Vec<T, P>>(th + e0);
-    float f[P];
+    const Vec<T, P> x = load_global<Vec<T, P>>(at.src + e0);
+    float z[P];
 #pragma unroll
-    for (int j = 0; j < P; ++j) {
-      const float z = __builtin_fmaf(d.a, G[j], ur[j]);
-      f[j] = __builtin_fmaf(c, z, to_f32(x.v[j]));
-    }
-    round_into<P>(x, f);
-    store_global(th + e0, x);
+    for (int j = 0; j < P; ++j) z[j] = __builtin_fmaf(d.a, G[j], ur[j]);
+    apply_z<T, P, MODE>(at, a, e0, x, z, c);
   }
 }
 
 // Lane layout: column group cg = lane % 32 owns P consecutive columns, each half of a wave RPL consecutive rows (a lane makes one
 // Philox call per row).  RPL = 16 is for passes that fill the chip; RPL = 1 spreads a small model's matrices over sixteen times the
 // blocks (least-squares layer of 256 x 512: 17 us with 8 blocks of 128 rows, 5.3 with 128 blocks of 8).
-template <typename T, int P, bool WRITE_Z, bool BATCH, int RPL>
+template <typename T, int P, bool WRITE_Z, int MODE, int RPL>
 __global__ void __launch_bounds__(256) perturb_tile_kernel(PerturbArgs a, const TensorDesc* __restrict__ descs, const WorkItem* __restrict__ items,
                                                            float c, const RadiusEntry* __restrict__ gtab, float* __restrict__ zout, int kp) {
   extern __shared__ float smem[];
@@ -323,7 +357,7 @@ __global__ void __launch_bounds__(256) perturb_tile_kernel(PerturbArgs a, const 
     const TensorDesc d = descs[it.tensor];
     const int64_t row0 = it.first >> 32, col0 = it.first & 0xFFFFFFFFll;
     const int nrows = it.count, k = d.k, kpt = (k + 7) & ~7;
-    T* __restrict__ th = reinterpret_cast<T*>(d.theta);
+    const Places<T> at = places_of<T, MODE>(d, a);
     const bool same_strip = it.tensor == prev_tensor && col0 == prev_col0;
     prev_tensor = it.tensor; prev_col0 = col0;
     if (!same_strip) __syncthreads();                // table loaded / previous strip's readers of Rs done
@@ -336,7 +370,7 @@ __global__ void __launch_bounds__(256) perturb_tile_kernel(PerturbArgs a, const 
       for (int j = 0; j < P; ++j) r[j] = 0.f;
       if (l < k && col < d.cols) {
         const uint64_t q = (uint64_t)((int64_t)l * d.cols + col) / P;
-        draw<P, BATCH>(q, d.id | 0x80000000u, a, tab, r);
+        draw<P, MODE>(q, d.id | 0x80000000u, a, tab, r);
 #pragma unroll
         for (int j = 0; j < P; ++j) r[j] *= d.b;
       }
@@ -384,7 +418,7 @@ __global__ void __launch_bounds__(256) perturb_tile_kernel(PerturbArgs a, const 
             const int vv = vb + v;
             const int rloc = (2 * wave + rh) * RPL + vv;
             const int64_t row = row0 + r0 + rloc;
-            if (r0 + rloc < nrows && row < d.rows) finish_row<T, P, WRITE_Z, BATCH>(d, th, zout, row * d.cols + col, acc[v], c, a, tab);
+            if (r0 + rloc < nrows && row < d.rows) finish_row<T, P, WRITE_Z, MODE>(d, at, zout, row * d.cols + col, acc[v], c, a, tab);
           }
         }
       }
@@ -401,9 +435,9 @@ __global__ void __launch_bounds__(256) perturb_tile_kernel(PerturbArgs a, const 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kTilePasses = 3;      // runs of the tile list per block of the matrix-core kernel
 
-template <typename T, int P, bool WRITE_Z, bool BATCH, bool FULL>
+template <typename T, int P, bool WRITE_Z, int MODE, bool FULL>
 __device__ __forceinline__ void mfma_row_block(const TensorDesc& d, const PerturbArgs& a, float c, const RadiusEntry* tab, const float* Rs,
-                                               T* __restrict__ th, float* __restrict__ zout, int64_t row0, int64_t col0, int r0, int nrows,
+                                               float* __restrict__ zout, int64_t row0, int64_t col0, int r0, int nrows,
                                                int k, int kq4, int wave, int n16, int rg) {
   constexpr int TC = 32 * P, GC = 16 * P;                     // tile columns, columns per group
   const int mrow = r0 + 16 * wave + n16;                      // A operand: this lane feeds row (lane % 16) of the slab
@@ -412,6 +446,7 @@ __device__ __forceinline__ void mfma_row_block(const TensorDesc& d, const Pertur
   const int ucol = rg * kq4;
   const int rbase = r0 + 16 * wave + 4 * rg;                  // first of this lane's 4 rows (tile-relative)
   const int64_t ebase = (row0 + rbase) * d.cols + col0 + (int64_t)P * n16;
+  const Places<T> at = places_of<T, MODE>(d, a);
   f32x4 acc[2 * P];
 #pragma unroll
   for (int j = 0; j < 2 * P; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -434,29 +469,24 @@ __device__ __forceinline__ void mfma_row_block(const TensorDesc& d, const Pertur
     // vector is used is a full one (loads and stores share one counter, and with both kinds in flight it cannot
     // be a partial wait), so whatever was requested last sets its length: with the request a whole call old it
     // has landed, with the request placed a third of a call earlier, as the scheduler does by itself, it has not.
-    Vec<T, P> xn = load_global<Vec<T, P>>(th + ebase);
+    Vec<T, P> xn = load_global<Vec<T, P>>(at.src + ebase);
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
       const int v = t >> 1, g = t & 1;
       const int64_t e0 = ebase + (int64_t)v * d.cols + g * GC;
       const Vec<T, P> xc = xn;
       if (t + 1 < 8) {
-        xn = load_global<Vec<T, P>>(th + ebase + (int64_t)((t + 1) >> 1) * d.cols + ((t + 1) & 1) * GC);
+        xn = load_global<Vec<T, P>>(at.src + ebase + (int64_t)((t + 1) >> 1) * d.cols + ((t + 1) & 1) * GC);
 #if defined(__HIP_DEVICE_COMPILE__)
         __builtin_amdgcn_sched_barrier(0);
 #endif
       }
       float G[P];
-      draw<P, BATCH>((uint64_t)e0 / P, d.id, a, tab, G);
-      Vec<T, P> xv = xc;
-      float f[P];
+      draw<P, MODE>((uint64_t)e0 / P, d.id, a, tab, G);
+      float z[P];
 #pragma unroll
-      for (int j = 0; j < P; ++j) {
-        const float z = __builtin_fmaf(d.a, G[j], acc[g * P + j][v]);
-        f[j] = __builtin_fmaf(c, z, to_f32(xv.v[j]));
-      }
-      round_into<P>(xv, f);
-      store_global(th + e0, xv);
+      for (int j = 0; j < P; ++j) z[j] = __builtin_fmaf(d.a, G[j], acc[g * P + j][v]);
+      apply_z<T, P, MODE>(at, a, e0, xc, z, c);
     }
     return;
   }
@@ -467,26 +497,22 @@ __device__ __forceinline__ void mfma_row_block(const TensorDesc& d, const Pertur
       if (FULL || (rbase + v < nrows && row0 + rbase + v < d.rows && col0 + g * GC + P * n16 < d.cols)) {
         const int64_t e0 = ebase + (int64_t)v * d.cols + g * GC;
         Vec<T, P> xv;
-        if (!WRITE_Z) xv = load_global<Vec<T, P>>(th + e0);
+        if (!WRITE_Z) xv = load_global<Vec<T, P>>(at.src + e0);
         float G[P];
-        draw<P, BATCH>((uint64_t)e0 / P, d.id, a, tab, G);
+        draw<P, MODE>((uint64_t)e0 / P, d.id, a, tab, G);
         if (WRITE_Z) {
 #pragma unroll
           for (int j = 0; j < P; ++j) zout[e0 + j] = __builtin_fmaf(d.a, G[j], acc[g * P + j][v]);
         } else {
-          float f[P];
+          float z[P];
 #pragma unroll
-          for (int j = 0; j < P; ++j) {
-            const float z = __builtin_fmaf(d.a, G[j], acc[g * P + j][v]);
-            f[j] = __builtin_fmaf(c, z, to_f32(xv.v[j]));
-          }
-          round_into<P>(xv, f);
-          store_global(th + e0, xv);
+          for (int j = 0; j < P; ++j) z[j] = __builtin_fmaf(d.a, G[j], acc[g * P + j][v]);
+          apply_z<T, P, MODE>(at, a, e0, xv, z, c);
         }
       }
 }
 
-template <typename T, int P, bool WRITE_Z, bool BATCH>
+template <typename T, int P, bool WRITE_Z, int MODE>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) perturb_tile_mfma_kernel(PerturbArgs a, const TensorDesc* __restrict__ descs, const WorkItem* __restrict__ items,
                                                                 float c, const RadiusEntry* __restrict__ gtab, float* __restrict__ zout, int kp) {
   extern __shared__ float smem[];
@@ -520,7 +546,6 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))
       const TensorDesc d = descs[it.tensor];
       const int64_t row0 = it.first >> 32, col0 = it.first & 0xFFFFFFFFll;
       const int nrows = it.count, k = d.k, kpt = (k + 7) & ~7, kq4 = kpt >> 2;
-      T* __restrict__ th = reinterpret_cast<T*>(d.theta);
       const bool same_strip = it.tensor == prev_tensor && col0 == prev_col0;
       prev_tensor = it.tensor; prev_col0 = col0;
       if (!same_strip) __syncthreads();                // table loaded / previous strip's readers of Rs done
@@ -531,7 +556,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))
 #pragma unroll
         for (int j = 0; j < P; ++j) r[j] = 0.f;
         if (l < k && col < d.cols) {
-          draw<P, BATCH>((uint64_t)((int64_t)l * d.cols + col) / P, d.id | 0x80000000u, a, tab, r);
+          draw<P, MODE>((uint64_t)((int64_t)l * d.cols + col) / P, d.id | 0x80000000u, a, tab, r);
 #pragma unroll
           for (int j = 0; j < P; ++j) r[j] *= d.b;
         }
@@ -541,8 +566,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))
       if (!same_strip) __syncthreads();
       const bool full = (nrows % 64 == 0) && row0 + nrows <= d.rows && col0 + TC <= d.cols && k == kpt;
       for (int r0 = 0; r0 < nrows; r0 += 64) {
-        if (full) mfma_row_block<T, P, WRITE_Z, BATCH, true>(d, a, c, tab, Rs, th, zout, row0, col0, r0, nrows, k, kq4, wave, n16, rg);
-        else      mfma_row_block<T, P, WRITE_Z, BATCH, false>(d, a, c, tab, Rs, th, zout, row0, col0, r0, nrows, k, kq4, wave, n16, rg);
+        if (full) mfma_row_block<T, P, WRITE_Z, MODE, true>(d, a, c, tab, Rs, zout, row0, col0, r0, nrows, k, kq4, wave, n16, rg);
+        else      mfma_row_block<T, P, WRITE_Z, MODE, false>(d, a, c, tab, Rs, zout, row0, col0, r0, nrows, k, kq4, wave, n16, rg);
       }
     }
   }
@@ -737,6 +762,8 @@ int split_grid(PerturbArgs& a, int items, int capacity) {
   return compute + a.pull_blocks;
 }
 
+int mode_of(const PerturbArgs& a) { return a.n_q > 0 ? kBatch : (a.spread ? kSpread : kOne); }
+
 template <typename T, int P>
 hipError_t launch_flat_t(const PerturbArgs& a_in, float c, float* zout, hipStream_t s, int n_cu, const RadiusEntry* tab) {
   PerturbArgs a = a_in;
@@ -745,9 +772,10 @@ hipError_t launch_flat_t(const PerturbArgs& a_in, float c, float* zout, hipStrea
     hipLaunchKernelGGL((fill_flat_kernel<T, P>), dim3(grid), dim3(256), 0, s, a, a.descs, a.flat, tab, zout);
     return hipGetLastError();
   }
-  auto kern = a.n_q > 0 ? perturb_flat_kernel<T, P, true> : perturb_flat_kernel<T, P, false>;
-  static std::atomic<int> per[2];                        // zero-initialised; racing threads compute the same value
-  std::atomic<int>& slot = per[a.n_q > 0 ? 1 : 0];
+  const int mode = mode_of(a);
+  auto kern = mode == kBatch ? perturb_flat_kernel<T, P, kBatch> : (mode == kSpread ? perturb_flat_kernel<T, P, kSpread> : perturb_flat_kernel<T, P, kOne>);
+  static std::atomic<int> per[3];                        // zero-initialised; racing threads compute the same value
+  std::atomic<int>& slot = per[mode];
   int nb = slot.load(std::memory_order_relaxed);
   if (nb == 0) { nb = resident_blocks_per_cu(kern, 0, 8); slot.store(nb, std::memory_order_relaxed); }
   const int grid = split_grid(a, a.n_flat, n_cu * nb);
@@ -760,9 +788,10 @@ hipError_t launch_tile_t(const PerturbArgs& a_in, float c, float* zout, hipStrea
   const int kp = (a.max_k + 7) & ~7;
   if (a.min_k >= kMfmaMinK) {
     const size_t lds_m = sizeof(float) * ((size_t)kRadiusTabEntries * 3 + (size_t)kp * 32 * P);
-    const int variant = zout ? 1 : (a.n_q > 0 ? 2 : 0);
-    auto km = zout ? perturb_tile_mfma_kernel<T, P, true, false> : (a.n_q > 0 ? perturb_tile_mfma_kernel<T, P, false, true> : perturb_tile_mfma_kernel<T, P, false, false>);
-    static TileLaunchCache cache_m[3];
+    const int variant = zout ? 3 : mode_of(a);
+    auto km = zout ? perturb_tile_mfma_kernel<T, P, true, kOne>
+                   : (variant == kBatch ? perturb_tile_mfma_kernel<T, P, false, kBatch> : (variant == kSpread ? perturb_tile_mfma_kernel<T, P, false, kSpread> : perturb_tile_mfma_kernel<T, P, false, kOne>));
+    static TileLaunchCache cache_m[4];
     int per_cu = 1;
     hipError_t e = tile_launch_setup(km, lds_m, 8, cache_m[variant], &per_cu);
     if (e != hipSuccess) return e;
@@ -772,11 +801,20 @@ hipError_t launch_tile_t(const PerturbArgs& a_in, float c, float* zout, hipStrea
   }
   const bool small = a.tile_rows < kTileRowsPerIter;
   const size_t lds = sizeof(float) * ((size_t)kRadiusTabEntries * 3 + (size_t)(small ? kSmallTileRows : kTileRowsPerIter) * kp + (size_t)kp * 32 * P);
-  const int variant = (zout ? 1 : (a.n_q > 0 ? 2 : 0)) + (small ? 3 : 0);
+  const int variant = (zout ? 3 : mode_of(a)) + (small ? 4 : 0);
   constexpr int RS = kSmallTileRows / 8, RL = kTileRowsPerIter / 8;
-  auto kern = small ? (zout ? perturb_tile_kernel<T, P, true, false, RS> : (a.n_q > 0 ? perturb_tile_kernel<T, P, false, true, RS> : perturb_tile_kernel<T, P, false, false, RS>))
-                    : (zout ? perturb_tile_kernel<T, P, true, false, RL> : (a.n_q > 0 ? perturb_tile_kernel<T, P, false, true, RL> : perturb_tile_kernel<T, P, false, false, RL>));
-  static TileLaunchCache cache_v[6];
+  decltype(&perturb_tile_kernel<T, P, false, kOne, RL>) kern = nullptr;
+  switch (variant) {
+    case kOne:        kern = perturb_tile_kernel<T, P, false, kOne, RL>; break;
+    case kBatch:      kern = perturb_tile_kernel<T, P, false, kBatch, RL>; break;
+    case kSpread:     kern = perturb_tile_kernel<T, P, false, kSpread, RL>; break;
+    case 3:           kern = perturb_tile_kernel<T, P, true, kOne, RL>; break;
+    case 4 + kOne:    kern = perturb_tile_kernel<T, P, false, kOne, RS>; break;
+    case 4 + kBatch:  kern = perturb_tile_kernel<T, P, false, kBatch, RS>; break;
+    case 4 + kSpread: kern = perturb_tile_kernel<T, P, false, kSpread, RS>; break;
+    default:          kern = perturb_tile_kernel<T, P, true, kOne, RS>; break;
+  }
+  static TileLaunchCache cache_v[8];
   int per_cu = 1;
   hipError_t e = tile_launch_setup(kern, lds, 4, cache_v[variant], &per_cu);
   if (e != hipSuccess) return e;
@@ -789,6 +827,7 @@ hipError_t launch_tile_t(const PerturbArgs& a_in, float c, float* zout, hipStrea
 hipError_t launch_perturb_flat(const PerturbArgs& a, float c, float* zout, hipStream_t s, int n_cu) {
   if (a.n_flat <= 0) return hipSuccess;
   if (a.n_q < 0 || a.n_q > kMaxBatch || (a.n_q > 0 && zout)) return hipErrorInvalidValue;
+  if ((a.spread && (a.n_q > 0 || a.from_copy || zout)) || ((a.spread || a.from_copy) && !(a.copy[0] && a.copy[1])) || (a.from_copy && a.n_q > 0)) return hipErrorInvalidValue;
   if (a.n_stage < 0 || a.n_stage > kMaxStage) return hipErrorInvalidValue;
   const RadiusEntry* tab = nullptr;
   hipError_t e = ensure_radius_table(&tab, s);
@@ -801,6 +840,7 @@ hipError_t launch_perturb_tile(const PerturbArgs& a, float c, float* zout, hipSt
   if (a.n_tiles <= 0) return hipSuccess;
   if (a.max_k < 1 || a.max_k > kMaxK) return hipErrorInvalidValue;
   if (a.n_q < 0 || a.n_q > kMaxBatch || (a.n_q > 0 && zout)) return hipErrorInvalidValue;
+  if ((a.spread && (a.n_q > 0 || a.from_copy || zout)) || ((a.spread || a.from_copy) && !(a.copy[0] && a.copy[1])) || (a.from_copy && a.n_q > 0)) return hipErrorInvalidValue;
   if (a.n_stage < 0 || a.n_stage > kMaxStage) return hipErrorInvalidValue;
   if (a.n_stage < 0 || a.n_stage > kMaxStage) return hipErrorInvalidValue;
   const RadiusEntry* tab = nullptr;

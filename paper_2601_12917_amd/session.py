@@ -26,6 +26,8 @@ def _align(x, a=256):
 
 
 class Session:
+    COPIES_SHARE = 0.25        # of the free device memory: the most that the copies zgr_step works faster with may take
+
     def __init__(self, arch, dtype, params: Sequence[ParamSpec], seed, eps, alpha, scale_mode=B.ZGR_SCALE_UNIT,
                  gauss_bits=32, n_layer=0, d_model=0, n_head=0, d_ff=0, vocab=0, max_pos=0, n_class=0, ln_eps=1e-5,
                  max_batch=1, max_seq=2, device="cuda:0", pack_after=(), fuse_lr=None, act="gelu", post_ln=False):
@@ -71,6 +73,10 @@ class Session:
         nbytes = self.lib.zgr_workspace_bytes(C.byref(self.model), self.table, len(self.params), max_batch, max_seq)
         if nbytes == 0:
             raise B.ZgrError(B.ZGR_ERR_SHAPE, "zgr_workspace_bytes rejected the arguments")
+        # room for the step's two copies of the parameters where they are a small part of what the device has left (asking costs 1 ms)
+        larger = self.lib.zgr_workspace_bytes_copies(C.byref(self.model), self.table, len(self.params), max_batch, max_seq)
+        if self.COPIES_SHARE > 0 and (larger - nbytes < 1 << 26 or larger - nbytes <= self.COPIES_SHARE * torch.cuda.mem_get_info(self.dev)[0]):
+            nbytes = larger
         self.workspace = torch.empty(nbytes, dtype=torch.uint8, device=self.dev)
         self.stream = torch.cuda.current_stream(self.dev)
         self.ctx = C.c_void_p()

@@ -1,0 +1,70 @@
+"""zgr_step with room for two copies of the parameters (Z generated once for both forward passes and the restoration) against
+the same step with the smallest workspace, where the three perturbations are applied in place one after the other: the
+parameters come out the same bit for bit, and the losses within the order of their sums."""
+import numpy as np
+import pytest
+
+import zgr_inputs as I
+from paper_2601_12917_amd.session import Session
+from tests.util import inputs_of, make_batch_arrays, make_session, session_batch
+
+pytestmark = pytest.mark.gpu
+
+_SMALL = dict(n_layer=3, vocab=211, max_pos=40, batch=3, seq=17)
+CASES = {
+    # few tiles: blocks of 8 rows, a column strip that ends early, a rank below the matrix-core kernel's
+    "linear": (I.shrink(I.CONFIGS["cfg1"], lsq_out=37, lsq_in=132, batch=5), 32),
+    "f32 rank 5": (I.shrink(I.CONFIGS["cfg2"], d_model=96, n_head=3, d_ff=200, k=5, k_full=9, **_SMALL), 32),
+    # matrix-core kernel: whole and ragged tiles, both group sizes, both types
+    "f32 rank 20": (I.shrink(I.CONFIGS["cfg2"], d_model=160, n_head=5, d_ff=328, k=20, k_full=20, **_SMALL), 16),
+    "bf16 rank 16": (I.shrink(I.CONFIGS["cfg3"], d_model=256, n_head=4, d_ff=576, k=16, k_full=24, **_SMALL), 32),
+    "bf16 rank 16 by 8": (I.shrink(I.CONFIGS["cfg3"], d_model=256, n_head=4, d_ff=576, k=16, k_full=16, **_SMALL), 16),
+    "bf16 many tiles": (I.shrink(I.CONFIGS["cfg3"], d_model=512, n_head=8, d_ff=1088, k=8, k_full=8, **_SMALL), 32),
+    "encoder post-LN": (I.shrink(I.CONFIGS["cfg4"], d_model=128, n_head=2, d_ff=192, k=16, k_full=16, post_ln=True, act="relu", **_SMALL), 32),
+}
+
+
+def _sessions(monkeypatch, cfg, bits, fuse_lr=None, stream=False):
+    specs, values, bases = inputs_of(cfg)
+    arrays = make_batch_arrays(cfg)
+    out = []
+    for share in (0.25, 0.0):
+        monkeypatch.setattr(Session, "COPIES_SHARE", share)
+        sess = make_session(cfg, specs, values, bases, bits=bits, fuse_lr=fuse_lr)
+        if stream:
+            sess.set_stage_tiles(1)
+            for i, u in enumerate(bases):
+                if u is not None:
+                    sess.set_basis_host(i, u, cfg.k)
+        out.append((sess, session_batch(sess, cfg, arrays)))
+    assert out[0][0].workspace.numel() > out[1][0].workspace.numel()
+    return out
+
+
+@pytest.mark.parametrize("stream", [False, True])
+@pytest.mark.parametrize("name", list(CASES))
+def test_step_with_copies_equals_step_in_place(monkeypatch, name, stream):
+    cfg, bits = CASES[name]
+    (a, ba), (b, bb) = _sessions(monkeypatch, cfg, bits, stream=stream)
+    tol = 1e-5 if cfg.dtype == "f32" else 2e-3          # losses: order of fp32 sums, and where bf16 activations round after it
+    for step in range(2):
+        ra, rb = a.step(step, ba), b.step(step, bb)
+        assert abs(ra[0] - rb[0]) <= tol * abs(rb[0]) and abs(ra[1] - rb[1]) <= tol * abs(rb[1]), (ra, rb)
+        for i in range(len(a.params)):
+            assert np.array_equal(a.get_theta(i), b.get_theta(i)), (step, a.params[i].name)
+        a.apply_update(step, 0.7, 1e-3), b.apply_update(step, 0.7, 1e-3)
+    # what reads the caller's parameters between the steps reads the restored ones
+    assert abs(a.loss(ba) - b.loss(bb)) <= tol * abs(b.loss(bb))
+    a.close(); b.close()
+
+
+@pytest.mark.parametrize("name", ["linear", "f32 rank 20", "bf16 rank 16"])
+def test_fused_step_with_copies(monkeypatch, name):
+    """Learning rate 0 makes the fused last pass, which starts from the second copy, independent of g: the same bits."""
+    cfg, bits = CASES[name]
+    (a, ba), (b, bb) = _sessions(monkeypatch, cfg, bits, fuse_lr=0.0)
+    for step in range(2):
+        a.step(step, ba), b.step(step, bb)
+        for i in range(len(a.params)):
+            assert np.array_equal(a.get_theta(i), b.get_theta(i)), (step, a.params[i].name)
+    a.close(); b.close()
