@@ -49,8 +49,7 @@ struct Carve {                 // workspace layout (byte offsets)
   size_t row_loss_stride = 0;                  // floats between the row losses of L+ (slot 0) and L- (slot 1)
   size_t spc[kSpcSlots] = {}, spc_bytes = 0;   // staging slots for the bases of one layer each (streamed bases)
   size_t total = 0;
-  size_t copies = 0, copy_bytes = 0;           // two copies of the parameters, copy_bytes apart; past `total`, only where the workspace has room for them
-  size_t total_with_copies = 0;
+  size_t copies = 0, copy_bytes = 0;           // two copies of the parameters, copy_bytes apart (0: none)
 };
 
 struct Prof {
@@ -101,6 +100,7 @@ struct zgr_ctx {
   int64_t last_rows = 0;       // rows of the last forward's row_loss
   int last_slot = 0;           // which of the two row-loss buffers the last forward wrote
   int64_t slot_rows[2] = {0, 0};
+  size_t slot_first[2] = {0, 0};   // where in row_loss it lies (floats)
   double host_loss[2] = {0, 0};
 };
 
@@ -344,7 +344,8 @@ std::vector<size_t> copy_layout(const zgr_tensor* t, int n_t, size_t* bytes) {
   return off;
 }
 
-Carve carve(const zgr_model& m, const zgr_tensor* t, int n_t, int max_batch, int max_seq, int bits) {
+// with_copies: room for two copies of the parameters, and for the activations of two models at once
+Carve carve(const zgr_model& m, const zgr_tensor* t, int n_t, int max_batch, int max_seq, int bits, bool with_copies) {
   Carve cv;
   const int P = group_size(bits);
   size_t nf = 0, nt = 0, nd = 0;
@@ -387,9 +388,9 @@ Carve carve(const zgr_model& m, const zgr_tensor* t, int n_t, int max_batch, int
     }
     for (int i = 0; i < kSpcSlots; ++i) cv.spc[i] = take(cv.spc_bytes);
   }
-  const size_t es = elem_size(dtype);
+  const size_t es = elem_size(dtype), models = with_copies ? 2 : 1;
   if (is_transformer(m.arch)) {
-    const size_t M = (size_t)max_batch * max_seq, d = m.d_model;
+    const size_t rows = (size_t)max_batch * max_seq, M = rows * models, d = m.d_model;
     cv.x = take(M * d * 4);
     cv.h = take(M * d * es);
     cv.qkv = take(M * 3 * d * es);
@@ -398,24 +399,22 @@ Carve carve(const zgr_model& m, const zgr_tensor* t, int n_t, int max_batch, int
     // fp32 storage: full fp32 logits; bf16: only the softmax partials (float2 per 128-row strip of the vocabulary
     // and token) and the target logits of the fused cross-entropy
     const size_t lm_logits = dtype == ZGR_BF16 ? M * ((size_t)2 * ce_partials_per_row(m.vocab) + 1) * 4 : M * (size_t)m.vocab * 4;
-    cv.logits = take(m.arch == ZGR_ARCH_DECODER_LM ? lm_logits : (size_t)max_batch * m.n_class * 4);
-    cv.row_loss_stride = align_up(M * 4) / 4;
+    cv.logits = take(m.arch == ZGR_ARCH_DECODER_LM ? lm_logits : (size_t)max_batch * models * m.n_class * 4);
+    cv.row_loss_stride = align_up(rows * 4) / 4;
     cv.row_loss = take(2 * cv.row_loss_stride * 4);
-    cv.targets = take(M * 4);
+    cv.targets = take(rows * 4);
   } else if (m.arch == ZGR_ARCH_LINEAR_LSQ) {
     size_t out = 0;
     for (int i = 0; i < n_t; ++i) if (t[i].role == ZGR_ROLE_LSQ_W) out = (size_t)t[i].rows;
-    cv.logits = take((size_t)max_batch * out * 4);
+    cv.logits = take((size_t)max_batch * models * out * 4);
     cv.row_loss_stride = align_up((size_t)max_batch * 4) / 4;
     cv.row_loss = take(2 * cv.row_loss_stride * 4);
   }
-  cv.total = off;
-  cv.total_with_copies = off;
-  if (m.arch != ZGR_ARCH_NONE) {               // a context without a model takes no step
+  if (with_copies && m.arch != ZGR_ARCH_NONE) {   // a context without a model takes no step
     copy_layout(t, n_t, &cv.copy_bytes);
-    cv.copies = off;
-    cv.total_with_copies = off + 2 * cv.copy_bytes;
+    cv.copies = take(2 * cv.copy_bytes);
   }
+  cv.total = off;
   return cv;
 }
 
@@ -557,10 +556,15 @@ zgr_status perturb_pass_batched(zgr_ctx* c, int n, const uint64_t* steps, const 
 // ---------------------------------------------------------------- forward
 const void* T(zgr_ctx* c, int idx) { return c->t[idx].theta; }
 
-// The loss of the caller's parameters, or (from_copy) of copy `slot` of them.
-zgr_status forward_loss(zgr_ctx* c, const zgr_batch* b, int slot, bool from_copy = false) {
-  auto T = [&](zgr_ctx* ctx, int idx) -> const void* {
-    return from_copy ? ctx->ws + ctx->cv.copies + (size_t)slot * ctx->cv.copy_bytes + ctx->copy_off[idx] : ctx->t[idx].theta;
+// The loss of the caller's parameters into `slot`, or (both) those of the two copies into slots 0 and 1: every launch then takes both models,
+// half the launches and twice the blocks of two passes one after the other.
+zgr_status forward_loss(zgr_ctx* c, const zgr_batch* b, int slot, bool both = false) {
+  auto T = [&](zgr_ctx* ctx, int idx) -> const void* { return both ? ctx->ws + ctx->cv.copies + ctx->copy_off[idx] : ctx->t[idx].theta; };
+  Twin tw;
+  if (both) { tw.models = 2; tw.w = (int64_t)c->cv.copy_bytes; }
+  auto wrote = [&](size_t rows) {                        // the second model's rows lie behind the first's
+    for (int i = both ? 0 : slot; i <= (both ? 1 : slot); ++i) { c->slot_rows[i] = (int64_t)rows; c->slot_first[i] = both ? i * rows : i * c->cv.row_loss_stride; }
+    c->last_rows = (int64_t)rows; c->last_slot = both ? 1 : slot;
   };
   const zgr_model& m = c->model;
   hipStream_t s = c->stream;
@@ -571,19 +575,20 @@ zgr_status forward_loss(zgr_ctx* c, const zgr_batch* b, int slot, bool from_copy
   const int dt = c->dtype;
   if (m.arch == ZGR_ARCH_LINEAR_LSQ) {
     const zgr_tensor& w = c->t[c->lsq_w];
-    { ProfScope ps(c, ZGR_K_GEMM); HIP_TRY(c, launch_gemm(0, b->x, T(c, c->lsq_w), nullptr, logits, EPI_F32, b->batch, (int)w.rows, (int)w.cols, s)); }
+    { ProfScope ps(c, ZGR_K_GEMM); HIP_TRY(c, launch_gemm(0, b->x, T(c, c->lsq_w), nullptr, logits, EPI_F32, b->batch, (int)w.rows, (int)w.cols, s, nullptr, 0, false, tw, true)); }
     { ProfScope ps(c, ZGR_K_LOSS);
-      HIP_TRY(c, launch_lsq_rows(logits, reinterpret_cast<const float*>(b->y), row_loss, b->batch, (int)w.rows, s));
-      HIP_TRY(c, launch_mean_f64(row_loss, b->batch, 1.0 / b->batch, loss_dev, s)); }
-    c->last_rows = c->slot_rows[slot] = b->batch; c->last_slot = slot;
+      HIP_TRY(c, launch_lsq_rows(logits, reinterpret_cast<const float*>(b->y), row_loss, b->batch, (int)w.rows, s, tw.models));
+      HIP_TRY(c, launch_mean_f64(row_loss, b->batch, 1.0 / b->batch, loss_dev, s, tw.models)); }
+    wrote((size_t)b->batch);
     return ZGR_OK;
   }
   const int M = b->batch * b->seq, d = m.d_model, ff = m.d_ff;
+  const size_t rows = (size_t)M * tw.models;
   float* x = reinterpret_cast<float*>(ws + c->cv.x);
   void* h = ws + c->cv.h; void* qkv = ws + c->cv.qkv; void* ctx = ws + c->cv.ctx; void* ffb = ws + c->cv.ff;
   const int32_t* tok = reinterpret_cast<const int32_t*>(b->x);
   const bool lm = m.arch == ZGR_ARCH_DECODER_LM;
-  { ProfScope ps(c, ZGR_K_EMBED); HIP_TRY(c, launch_embed(dt, tok, T(c, c->tok_emb), T(c, c->pos_emb), x, M, b->seq, d, m.vocab, s)); }
+  { ProfScope ps(c, ZGR_K_EMBED); HIP_TRY(c, launch_embed(dt, tok, T(c, c->tok_emb), T(c, c->pos_emb), x, M, b->seq, d, m.vocab, s, tw)); }
   const int act_epi = m.act == ZGR_ACT_RELU ? EPI_RELU : EPI_GELU;
   // fp32 models: a buffer whose contents a product neither reads nor still has use for holds the parts of its split sum
   float* ff_scratch = dt == ZGR_F32 ? reinterpret_cast<float*>(ffb) : nullptr;
@@ -591,43 +596,43 @@ zgr_status forward_loss(zgr_ctx* c, const zgr_batch* b, int slot, bool from_copy
   // post_ln: the residual stream x is itself normalised after every sum (and after the embeddings), and h is its copy
   // in the storage type; otherwise h = LN(x) feeds each sublayer and x stays the raw sum.
   float* xn = m.post_ln ? x : nullptr;
-  if (m.post_ln) { ProfScope ps(c, ZGR_K_NORM); HIP_TRY(c, launch_layernorm(dt, x, T(c, c->lnf_g), T(c, c->lnf_b), h, M, d, m.ln_eps, s, xn)); }
+  if (m.post_ln) { ProfScope ps(c, ZGR_K_NORM); HIP_TRY(c, launch_layernorm(dt, x, T(c, c->lnf_g), T(c, c->lnf_b), h, M, d, m.ln_eps, s, xn, tw)); }
   for (int l = 0; l < m.n_layer; ++l) {
     const Layer& L = c->layers[l];
-    if (!m.post_ln) { ProfScope ps(c, ZGR_K_NORM); HIP_TRY(c, launch_layernorm(dt, x, T(c, L.ln1_g), T(c, L.ln1_b), h, M, d, m.ln_eps, s)); }
-    { ProfScope ps(c, ZGR_K_GEMM); HIP_TRY(c, launch_gemm(dt, h, T(c, L.wq), T(c, L.bq), qkv, EPI_STORE, M, 3 * d, d, s, ff_scratch, (size_t)M * ff)); }
-    { ProfScope ps(c, ZGR_K_ATTN); HIP_TRY(c, launch_attention(dt, qkv, ctx, lm ? nullptr : b->lengths, b->batch, b->seq, d, m.n_head, lm ? 1 : 0, s)); }
-    { ProfScope ps(c, ZGR_K_GEMM); HIP_TRY(c, launch_gemm(dt, ctx, T(c, L.wo), T(c, L.bo), x, EPI_RESID, M, d, d, s, qkv_scratch, (size_t)3 * M * d)); }
+    if (!m.post_ln) { ProfScope ps(c, ZGR_K_NORM); HIP_TRY(c, launch_layernorm(dt, x, T(c, L.ln1_g), T(c, L.ln1_b), h, M, d, m.ln_eps, s, nullptr, tw)); }
+    { ProfScope ps(c, ZGR_K_GEMM); HIP_TRY(c, launch_gemm(dt, h, T(c, L.wq), T(c, L.bq), qkv, EPI_STORE, M, 3 * d, d, s, ff_scratch, rows * ff, false, tw)); }
+    { ProfScope ps(c, ZGR_K_ATTN); HIP_TRY(c, launch_attention(dt, qkv, ctx, lm ? nullptr : b->lengths, b->batch, b->seq, d, m.n_head, lm ? 1 : 0, s, false, tw.models)); }
+    { ProfScope ps(c, ZGR_K_GEMM); HIP_TRY(c, launch_gemm(dt, ctx, T(c, L.wo), T(c, L.bo), x, EPI_RESID, M, d, d, s, qkv_scratch, 3 * rows * d, false, tw)); }
     { ProfScope ps(c, ZGR_K_NORM);
-      HIP_TRY(c, m.post_ln ? launch_layernorm(dt, x, T(c, L.ln1_g), T(c, L.ln1_b), h, M, d, m.ln_eps, s, xn)
-                           : launch_layernorm(dt, x, T(c, L.ln2_g), T(c, L.ln2_b), h, M, d, m.ln_eps, s)); }
-    { ProfScope ps(c, ZGR_K_GEMM); HIP_TRY(c, launch_gemm(dt, h, T(c, L.w1), T(c, L.b1), ffb, act_epi, M, ff, d, s, qkv_scratch, (size_t)3 * M * d)); }
-    { ProfScope ps(c, ZGR_K_GEMM); HIP_TRY(c, launch_gemm(dt, ffb, T(c, L.w2), T(c, L.b2), x, EPI_RESID, M, d, ff, s, qkv_scratch, (size_t)3 * M * d)); }
-    if (m.post_ln) { ProfScope ps(c, ZGR_K_NORM); HIP_TRY(c, launch_layernorm(dt, x, T(c, L.ln2_g), T(c, L.ln2_b), h, M, d, m.ln_eps, s, xn)); }
+      HIP_TRY(c, m.post_ln ? launch_layernorm(dt, x, T(c, L.ln1_g), T(c, L.ln1_b), h, M, d, m.ln_eps, s, xn, tw)
+                           : launch_layernorm(dt, x, T(c, L.ln2_g), T(c, L.ln2_b), h, M, d, m.ln_eps, s, nullptr, tw)); }
+    { ProfScope ps(c, ZGR_K_GEMM); HIP_TRY(c, launch_gemm(dt, h, T(c, L.w1), T(c, L.b1), ffb, act_epi, M, ff, d, s, qkv_scratch, 3 * rows * d, false, tw)); }
+    { ProfScope ps(c, ZGR_K_GEMM); HIP_TRY(c, launch_gemm(dt, ffb, T(c, L.w2), T(c, L.b2), x, EPI_RESID, M, d, ff, s, qkv_scratch, 3 * rows * d, false, tw)); }
+    if (m.post_ln) { ProfScope ps(c, ZGR_K_NORM); HIP_TRY(c, launch_layernorm(dt, x, T(c, L.ln2_g), T(c, L.ln2_b), h, M, d, m.ln_eps, s, xn, tw)); }
   }
-  if (!m.post_ln) { ProfScope ps(c, ZGR_K_NORM); HIP_TRY(c, launch_layernorm(dt, x, T(c, c->lnf_g), T(c, c->lnf_b), h, M, d, m.ln_eps, s)); }
+  if (!m.post_ln) { ProfScope ps(c, ZGR_K_NORM); HIP_TRY(c, launch_layernorm(dt, x, T(c, c->lnf_g), T(c, c->lnf_b), h, M, d, m.ln_eps, s, nullptr, tw)); }
   if (lm) {
     int32_t* tgt = reinterpret_cast<int32_t*>(ws + c->cv.targets);
     { ProfScope ps(c, ZGR_K_LOSS); HIP_TRY(c, launch_lm_targets(tok, tgt, M, b->seq, m.vocab, s)); }
     if (dt == ZGR_BF16) {
       // the logits region holds the cross-entropy partials and, behind them, the target logits
-      float* tlogit = logits + (size_t)2 * ce_partials_per_row(m.vocab) * M;
+      float* tlogit = logits + 2 * ce_partials_per_row(m.vocab) * rows;
       ProfScope ps(c, ZGR_K_GEMM);
-      HIP_TRY(c, launch_gemm_ce_bf16(h, T(c, c->tok_emb), tgt, logits, tlogit, row_loss, M, m.vocab, d, s));
+      HIP_TRY(c, launch_gemm_ce_bf16(h, T(c, c->tok_emb), tgt, logits, tlogit, row_loss, M, m.vocab, d, s, tw));
     } else {
-      { ProfScope ps(c, ZGR_K_GEMM); HIP_TRY(c, launch_gemm(dt, h, T(c, c->tok_emb), nullptr, logits, EPI_F32, M, m.vocab, d, s)); }
+      { ProfScope ps(c, ZGR_K_GEMM); HIP_TRY(c, launch_gemm(dt, h, T(c, c->tok_emb), nullptr, logits, EPI_F32, M, m.vocab, d, s, nullptr, 0, false, tw)); }
       ProfScope ps(c, ZGR_K_LOSS);
-      HIP_TRY(c, launch_ce_rows(logits, tgt, row_loss, M, m.vocab, s));
+      HIP_TRY(c, launch_ce_rows(logits, tgt, row_loss, M, m.vocab, s, tw.models));
     }
     { ProfScope ps(c, ZGR_K_LOSS);
-      HIP_TRY(c, launch_mean_f64(row_loss, M, 1.0 / ((double)b->batch * (b->seq - 1)), loss_dev, s)); }
-    c->last_rows = c->slot_rows[slot] = M; c->last_slot = slot;
+      HIP_TRY(c, launch_mean_f64(row_loss, M, 1.0 / ((double)b->batch * (b->seq - 1)), loss_dev, s, tw.models)); }
+    wrote((size_t)M);
   } else {
     { ProfScope ps(c, ZGR_K_LOSS);
-      HIP_TRY(c, launch_cls_head(dt, h, T(c, c->cls_w), T(c, c->cls_b), logits, b->batch, b->seq, d, m.n_class, s));
-      HIP_TRY(c, launch_ce_rows(logits, reinterpret_cast<const int32_t*>(b->y), row_loss, b->batch, m.n_class, s));
-      HIP_TRY(c, launch_mean_f64(row_loss, b->batch, 1.0 / b->batch, loss_dev, s)); }
-    c->last_rows = c->slot_rows[slot] = b->batch; c->last_slot = slot;
+      HIP_TRY(c, launch_cls_head(dt, h, T(c, c->cls_w), T(c, c->cls_b), logits, b->batch, b->seq, d, m.n_class, s, tw));
+      HIP_TRY(c, launch_ce_rows(logits, reinterpret_cast<const int32_t*>(b->y), row_loss, b->batch, m.n_class, s, tw.models));
+      HIP_TRY(c, launch_mean_f64(row_loss, b->batch, 1.0 / b->batch, loss_dev, s, tw.models)); }
+    wrote((size_t)b->batch);
   }
   return ZGR_OK;
 }
@@ -706,15 +711,15 @@ size_t zgr_workspace_bytes(const zgr_model* model, const zgr_tensor* tensors, in
   if (!model || (n_t > 0 && !tensors) || n_t < 0 || max_batch < 0 || max_seq < 0) return 0;
   for (int i = 0; i < n_t; ++i) if (tensors[i].rows < 1 || tensors[i].cols < 1) return 0;
   // sized for the finer of the two Philox groupings so that either gauss_bits fits
-  const size_t a = carve(*model, tensors, n_t, max_batch, max_seq, 32).total;
-  const size_t b = carve(*model, tensors, n_t, max_batch, max_seq, 16).total;
+  const size_t a = carve(*model, tensors, n_t, max_batch, max_seq, 32, false).total;
+  const size_t b = carve(*model, tensors, n_t, max_batch, max_seq, 16, false).total;
   return std::max(a, b);
 }
 
 size_t zgr_workspace_bytes_copies(const zgr_model* model, const zgr_tensor* tensors, int32_t n_t, int32_t max_batch, int32_t max_seq) {
   if (zgr_workspace_bytes(model, tensors, n_t, max_batch, max_seq) == 0) return 0;
-  const size_t a = carve(*model, tensors, n_t, max_batch, max_seq, 32).total_with_copies;
-  const size_t b = carve(*model, tensors, n_t, max_batch, max_seq, 16).total_with_copies;
+  const size_t a = carve(*model, tensors, n_t, max_batch, max_seq, 32, true).total;
+  const size_t b = carve(*model, tensors, n_t, max_batch, max_seq, 16, true).total;
   return std::max(a, b);
 }
 
@@ -741,7 +746,9 @@ zgr_status zgr_init(zgr_ctx** out, const zgr_model* model, const zgr_tensor* ten
   if (!c) return fail(nullptr, ZGR_ERR_DEVICE, "out of host memory");
   c->model = *model; c->cfg = *config; c->t.assign(tensors, tensors + n_t); c->qb.assign((size_t)n_t, zgr_ctx::QBasis{}); c->hb.assign((size_t)n_t, zgr_ctx::HostBasis{}); c->dtype = tensors[0].dtype;
   c->max_batch = max_batch; c->max_seq = max_seq; c->stream = reinterpret_cast<hipStream_t>(hip_stream);
-  c->cv = carve(*model, tensors, n_t, max_batch, max_seq, config->gauss_bits);
+  c->cv = carve(*model, tensors, n_t, max_batch, max_seq, config->gauss_bits, true);
+  c->copies = c->cv.copy_bytes > 0 && workspace_bytes >= c->cv.total;
+  if (!c->copies) c->cv = carve(*model, tensors, n_t, max_batch, max_seq, config->gauss_bits, false);
   if (workspace_bytes < c->cv.total) {
     st = fail(nullptr, ZGR_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, c->cv.total);
     delete c; return st;
@@ -749,7 +756,6 @@ zgr_status zgr_init(zgr_ctx** out, const zgr_model* model, const zgr_tensor* ten
   c->ws = reinterpret_cast<unsigned char*>(workspace); c->ws_bytes = workspace_bytes;
   size_t copy_bytes = 0;
   c->copy_off = copy_layout(tensors, n_t, &copy_bytes);
-  c->copies = model->arch != ZGR_ARCH_NONE && workspace_bytes >= c->cv.total_with_copies;
   st = bind_model(c);
   if (st != ZGR_OK) { delete c; return st; }
   int dev = 0, n_cu = 0;
@@ -1295,9 +1301,7 @@ zgr_status zgr_step(zgr_ctx* c, uint64_t step, const zgr_batch* b, zgr_result* o
   if (c->copies) {
     // W + eps Z and W - eps Z as copies, W restored at once (a fused last pass restores from the second copy)
     if ((st = spread_pass(c, step, eps, !fuse)) != ZGR_OK) return st;
-    st = forward_loss(c, b, 0, true);
-    if (st == ZGR_OK) st = forward_loss(c, b, 1, true);
-    if (st != ZGR_OK) return st;
+    if ((st = forward_loss(c, b, 0, true)) != ZGR_OK) return st;
   } else {
     if ((st = perturb_pass(c, step, eps)) != ZGR_OK) return st;                 // W + eps Z
     st = forward_loss(c, b, 0);
@@ -1451,7 +1455,7 @@ zgr_status zgr_debug_last_row_losses(zgr_ctx* c, float* out, int64_t n) {
   if (!c) return ZGR_ERR_NULL;
   if (!out) return fail(c, ZGR_ERR_NULL, "out is NULL");
   if (c->model.arch == ZGR_ARCH_NONE || n != c->last_rows) return fail(c, ZGR_ERR_SHAPE, "n = %lld, the last forward produced %lld rows", (long long)n, (long long)c->last_rows);
-  HIP_TRY(c, hipMemcpyAsync(out, c->ws + c->cv.row_loss + sizeof(float) * (size_t)c->last_slot * c->cv.row_loss_stride, sizeof(float) * (size_t)n, hipMemcpyDeviceToHost, c->stream));
+  HIP_TRY(c, hipMemcpyAsync(out, c->ws + c->cv.row_loss + sizeof(float) * c->slot_first[c->last_slot], sizeof(float) * (size_t)n, hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   return ZGR_OK;
 }
@@ -1461,7 +1465,7 @@ zgr_status zgr_debug_step_row_losses(zgr_ctx* c, int32_t which, float* out, int6
   if (!out) return fail(c, ZGR_ERR_NULL, "out is NULL");
   if (which != 0 && which != 1) return fail(c, ZGR_ERR_CONFIG, "which must be 0 (L+) or 1 (L-)");
   if (c->model.arch == ZGR_ARCH_NONE || n != c->slot_rows[which]) return fail(c, ZGR_ERR_SHAPE, "n = %lld, that forward produced %lld rows", (long long)n, (long long)c->slot_rows[which]);
-  HIP_TRY(c, hipMemcpyAsync(out, c->ws + c->cv.row_loss + sizeof(float) * (size_t)which * c->cv.row_loss_stride, sizeof(float) * (size_t)n, hipMemcpyDeviceToHost, c->stream));
+  HIP_TRY(c, hipMemcpyAsync(out, c->ws + c->cv.row_loss + sizeof(float) * c->slot_first[which], sizeof(float) * (size_t)n, hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   return ZGR_OK;
 }

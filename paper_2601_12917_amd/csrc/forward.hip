@@ -51,23 +51,36 @@ __device__ __forceinline__ float block_max(float v, float* red) {
 
 __device__ __forceinline__ float gelu_erf(float x) { return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)); }
 
+// A parameter of the model a row belongs to: with two models (Twin) the second one's parameters lie w bytes behind the first's.
+template <typename T> __device__ __forceinline__ const T* of_model(const T* p, bool second, int64_t w) {
+  return reinterpret_cast<const T*>(reinterpret_cast<const unsigned char*>(p) + (second ? w : 0));
+}
+__device__ __forceinline__ int uniform_of(int v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_readfirstlane(v);
+#else
+  return v;
+#endif
+}
+
 // ------------------------------------------------------------------ embedding
 template <typename T>
 __global__ void __launch_bounds__(256) embed_kernel(const int32_t* __restrict__ tok, const T* __restrict__ E, const T* __restrict__ Pe,
-                                                    float* __restrict__ x, int M, int seq, int d, int vocab) {
-  const int m = blockIdx.x;
-  int t = tok[m];
+                                                    float* __restrict__ x, int M, int seq, int d, int vocab, int64_t w) {
+  const int m = blockIdx.x, mt = m < M ? m : m - M;
+  int t = tok[mt];
   t = t < 0 ? 0 : (t >= vocab ? vocab - 1 : t);
-  const T* e = E + (size_t)t * d;
-  const T* p = Pe + (size_t)(m % seq) * d;
+  const T* e = of_model(E, m >= M, w) + (size_t)t * d;
+  const T* p = of_model(Pe, m >= M, w) + (size_t)(mt % seq) * d;
   for (int i = threadIdx.x; i < d; i += 256) x[(size_t)m * d + i] = to_f32(e[i]) + to_f32(p[i]);
 }
 
 // ------------------------------------------------------------------ LayerNorm (one block per row)
 template <typename T>
 __global__ void __launch_bounds__(256) layernorm_kernel(const float* x, const T* __restrict__ g, const T* __restrict__ b,
-                                                        T* __restrict__ out, int d, float eps, float* xout) {
+                                                        T* __restrict__ out, int d, float eps, float* xout, int M, int64_t w) {
   __shared__ float red[4];
+  g = of_model(g, (int)blockIdx.x >= M, w); b = of_model(b, (int)blockIdx.x >= M, w);
   const float* row = x + (size_t)blockIdx.x * d;
   float s = 0.f;
   for (int i = threadIdx.x; i < d; i += 256) s += row[i];
@@ -87,8 +100,9 @@ __global__ void __launch_bounds__(256) layernorm_kernel(const float* x, const T*
 // Row held in registers (d % 4 == 0, d <= 8192): one read of x, float4 loads, packed stores.
 template <typename T>
 __global__ void __launch_bounds__(256) layernorm_reg_kernel(const float* x, const T* __restrict__ g, const T* __restrict__ b,
-                                                            T* __restrict__ out, int d, float eps, float* xout) {
+                                                            T* __restrict__ out, int d, float eps, float* xout, int M, int64_t w) {
   __shared__ float red[4];
+  g = of_model(g, (int)blockIdx.x >= M, w); b = of_model(b, (int)blockIdx.x >= M, w);
   constexpr int MAXV = 8;
   const float4* row = reinterpret_cast<const float4*>(x + (size_t)blockIdx.x * d);
   const int nv = d >> 2;
@@ -132,11 +146,12 @@ __global__ void __launch_bounds__(256) layernorm_reg_kernel(const float* x, cons
 // and both reductions stay inside the wave: no LDS, no workgroup barrier.  Four rows per block.
 template <typename T>
 __global__ void __launch_bounds__(256) layernorm_wave_kernel(const float* x, const T* __restrict__ g, const T* __restrict__ b,
-                                                             T* __restrict__ out, int M, int d, float eps, float* xout) {
+                                                             T* __restrict__ out, int rows, int d, float eps, float* xout, int M, int64_t w) {
   constexpr int MAXV = 8;
   const int lane = threadIdx.x & 63;
-  const int row_i = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row_i >= M) return;                                          // whole waves leave: no barrier below
+  const int row_i = uniform_of(blockIdx.x * 4 + (threadIdx.x >> 6));
+  if (row_i >= rows) return;                                       // whole waves leave: no barrier below
+  g = of_model(g, row_i >= M, w); b = of_model(b, row_i >= M, w);
   const float4* row = reinterpret_cast<const float4*>(x + (size_t)row_i * d);
   const int nv = d >> 2;
   float4 v[MAXV];
@@ -182,6 +197,31 @@ __global__ void __launch_bounds__(256) layernorm_wave_kernel(const float* x, con
 //   EPI_RESID: xres fp32 [M,N] += acc + bias
 //   EPI_F32  : outf fp32 [M,N] = acc + bias (bias may be null)
 struct GemmEpi { int mode; void* out; const void* bias; };
+// Bytes from the first model's operands to the second's (Twin); which of the two a block works on is a dimension of the grid.
+struct GemmTwin { int64_t a, w, out, bias, tlogit; };
+// The tile of a block (and, returned, its model; -1: none).  Consecutive block ids go round-robin to the 8 XCDs, each with its own L2 and about 32
+// blocks in flight.  Every XCD gets an equal run of the tiles, which go through each model in bands of four rows of tiles, column by column, so that the
+// blocks resident in one L2 share 4 row panels of A and 8 of W.  (Whole super-tiles of 4 x 8 dealt out to the XCDs left half of them idle where there
+// are few: 16 x 6 tiles are four of them.  2 x 2048 x 768 x 768 and x 3072 with the residual: 47.6 us -> 26.7 on average, 2 x 4096 x 6144 x 2048:
+// 216 -> 173.)
+__device__ __forceinline__ int tile_of_block(int tiles_m, int tiles_n, int models, int& tm, int& tn) {
+  constexpr int GM = 4;
+  const int per_model = tiles_m * tiles_n, total = per_model * models;
+  const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3, q = total >> 3, rem = total & 7;
+  if (local >= q + (xcd < rem ? 1 : 0)) return -1;
+  const int idx = xcd * q + (xcd < rem ? xcd : rem) + local;
+  const int model = idx / per_model, r = idx - model * per_model, band = r / (GM * tiles_n), at = r - band * (GM * tiles_n);
+  const int rows = tiles_m - band * GM < GM ? tiles_m - band * GM : GM;
+  tn = at / rows;
+  tm = band * GM + (at - tn * rows);
+  return model;
+}
+template <typename T> __device__ __forceinline__ const T* ahead(const T* p, int64_t bytes) {
+  return p ? reinterpret_cast<const T*>(reinterpret_cast<const unsigned char*>(p) + bytes) : p;
+}
+template <typename T> __device__ __forceinline__ T* ahead(T* p, int64_t bytes) {
+  return p ? reinterpret_cast<T*>(reinterpret_cast<unsigned char*>(p) + bytes) : p;
+}
 
 template <typename T>
 __device__ __forceinline__ void epilogue_store(const GemmEpi& ep, int m, int n, int N, float v) {
@@ -197,7 +237,8 @@ __device__ __forceinline__ void epilogue_store(const GemmEpi& ep, int m, int n, 
 }
 
 // fp32 path: 64x64 tile, BK = 16, each thread 4x4 outputs; any M, N, K.
-__global__ void __launch_bounds__(256) gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ W, int M, int N, int K, GemmEpi ep) {
+__global__ void __launch_bounds__(256) gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ W, int M, int N, int K, GemmEpi ep, GemmTwin tw) {
+  A = ahead(A, blockIdx.z * tw.a); W = ahead(W, blockIdx.z * tw.w); ep.out = ahead(ep.out, blockIdx.z * tw.out); ep.bias = ahead(ep.bias, blockIdx.z * tw.bias);
   __shared__ float As[16][64 + 4], Ws[16][64 + 4];
   const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
   const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
@@ -243,7 +284,8 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // which the MFMA reads and writes directly.  (Allowed 512, the compiler multiplies in the accumulation registers, carries
 // the sums round the loop in vector registers and moves all 64 of them back and forth in every k-tile.)
 template <int F, int BK>
-__global__ void __launch_bounds__(256, 2) gemm_f32_mfma_kernel(const float* __restrict__ A, const float* __restrict__ W, int M, int N, int K, GemmEpi ep) {
+__global__ void __launch_bounds__(256, 2) gemm_f32_mfma_kernel(const float* __restrict__ A, const float* __restrict__ W, int M, int N, int K, GemmEpi ep, GemmTwin tw) {
+  A = ahead(A, blockIdx.z * tw.a); W = ahead(W, blockIdx.z * tw.w); ep.out = ahead(ep.out, blockIdx.z * tw.out); ep.bias = ahead(ep.bias, blockIdx.z * tw.bias);
   constexpr int BT = 64 * F, LD = BK + 4, KQ = BK / 4, NV = BT * KQ / 256, HK = BK / 2;
   __shared__ __attribute__((aligned(16))) float As[2][BT][LD], Ws[2][BT][LD];
   const int m0 = blockIdx.y * BT, n0 = blockIdx.x * BT;
@@ -433,7 +475,7 @@ template <int N> __device__ __forceinline__ void wait_vmem_upto() {   // at most
 template <int BM, int BN, int WM, int WN, int BK, int STAGES, int MODE, int PP = 0>
 __global__ void __launch_bounds__(64 * WM * WN) gemm_bf16_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, int M, int N, int K,
                                                                  void* __restrict__ out, const bf16_t* __restrict__ bias,
-                                                                 const int32_t* __restrict__ targets, float* __restrict__ tlogit) {
+                                                                 const int32_t* __restrict__ targets, float* __restrict__ tlogit, GemmTwin tw, int models) {
   constexpr int NW = WM * WN;
   constexpr int FM = BM / (32 * WM), FN = BN / (32 * WN);      // 32x32 fragments per wave
   constexpr int CPR = BK / 8;                                  // 16-byte chunks per LDS row
@@ -455,15 +497,12 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_bf16_kernel(const bf16_t* _
   const int wave = tid >> 6;
 #endif
   const int wm = wave / WN, wn = wave % WN;
-  // XCD-aware tile order.  Consecutive block ids go round-robin to the 8 XCDs, each with its own L2 and
-  // about 32 blocks in flight.  Give XCD x the super-tiles x, x+8, ... of GM x GN = 4 x 8 tiles, walked in
-  // order inside the XCD, so that the blocks resident in one L2 share 4 row panels of A and 8 of W.
-  constexpr int GM = 4, GN = 8;
   const int tiles_n = (N + BN - 1) / BN, tiles_m = (M + BM - 1) / BM;
-  const int stn = (tiles_n + GN - 1) / GN;
-  const int local = blockIdx.x >> 3, st = (local / (GM * GN)) * 8 + (blockIdx.x & 7), w = local % (GM * GN);
-  const int tm = (st / stn) * GM + w / GN, tn = (st % stn) * GN + w % GN;
-  if (tm >= tiles_m || tn >= tiles_n) return;
+  int tm, tn;
+  const int model = tile_of_block(tiles_m, tiles_n, models, tm, tn);
+  if (model < 0) return;
+  A = ahead(A, model * tw.a); W = ahead(W, model * tw.w); out = ahead(out, model * tw.out); bias = ahead(bias, model * tw.bias);
+  if (MODE == EPI_CE) tlogit = ahead(tlogit, model * tw.tlogit);
   const int m0 = tm * BM, n0 = tn * BN;
   f32x16 acc[FM][FN];
 #pragma unroll
@@ -734,6 +773,23 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_bf16_kernel(const bf16_t* _
 #pragma unroll
         for (int v = 0; v < 16; ++v)
           op[(size_t)(i * 32 + 8 * (v >> 2) + (v & 3)) * N + j * 32] = res[(i * FN + j) * 16 + v] + (acc[i][j][v] + bv[j]);
+  } else if (MODE == EPI_RESID && m0 + BM <= M && n0 + BN <= N) {
+    // larger tiles: the residual of the next fragment is requested before this one's sum is stored (one value after the other, each waiting for
+    // the store before it: 2 x 4096 x 2048 x 2048 and x 8192 took 355 us on average, now 147)
+    float* op = reinterpret_cast<float*>(out) + (size_t)mbase * N + nbase;
+    float old[2][16];
+    auto request = [&](int f) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) old[f & 1][v] = op[(size_t)((f / FN) * 32 + 8 * (v >> 2) + (v & 3)) * N + (f % FN) * 32];
+    };
+    request(0);
+#pragma unroll
+    for (int f = 0; f < FM * FN; ++f) {
+      if (f + 1 < FM * FN) request(f + 1);
+#pragma unroll
+      for (int v = 0; v < 16; ++v)
+        op[(size_t)((f / FN) * 32 + 8 * (v >> 2) + (v & 3)) * N + (f % FN) * 32] = old[f & 1][v] + (acc[f / FN][f % FN][v] + bv[f % FN]);
+    }
   } else if (m0 + BM <= M && n0 + BN <= N) {
 #pragma unroll
     for (int i = 0; i < FM; ++i)
@@ -748,6 +804,15 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_bf16_kernel(const bf16_t* _
 #pragma unroll
       for (int j = 0; j < FN; ++j) {
         const int n = nbase + j * 32;
+        if (MODE == EPI_RESID) {                                   // all of the fragment's values, then its stores
+          float* op = reinterpret_cast<float*>(out) + n;
+          float old[16];
+#pragma unroll
+          for (int v = 0; v < 16; ++v) { const int m = mbase + i * 32 + 8 * (v >> 2) + (v & 3); old[v] = op[(size_t)(m < M ? m : M - 1) * N - (n < N ? 0 : n - (N - 1))]; }
+#pragma unroll
+          for (int v = 0; v < 16; ++v) { const int m = mbase + i * 32 + 8 * (v >> 2) + (v & 3); if (m < M && n < N) op[(size_t)m * N] = old[v] + (acc[i][j][v] + bv[j]); }
+          continue;
+        }
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           const int m = mbase + i * 32 + 8 * (v >> 2) + (v & 3);
@@ -758,12 +823,10 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_bf16_kernel(const bf16_t* _
 }
 
 template <int BM, int BN, int WM, int WN, int BK, int STAGES, int PP = 0>
-hipError_t launch_gemm_bf16_t(const bf16_t* A, const bf16_t* W, const bf16_t* bias, void* out, int epi, int M, int N, int K, hipStream_t s,
+hipError_t launch_gemm_bf16_t(const bf16_t* A, const bf16_t* W, const bf16_t* bias, void* out, int epi, int M, int N, int K, hipStream_t s, int models, const GemmTwin& tw,
                               const int32_t* targets = nullptr, float* tlogit = nullptr) {
   const size_t lds = PP ? (size_t)STAGES * 8192 : (size_t)STAGES * (BM + BN) * BK * sizeof(bf16_t);   // ping-pong: STAGES counts 8 KiB ring units
-  // super-tiles of 4 x 8 tiles, rounded up to a multiple of 8 super-tiles (one per XCD)
-  const int stm = ((M + BM - 1) / BM + 3) / 4, stn = ((N + BN - 1) / BN + 7) / 8;
-  const int grid = ((stm * stn + 7) / 8 * 8) * 32;
+  const int grid = (((M + BM - 1) / BM) * ((N + BN - 1) / BN) * models + 7) / 8 * 8;
 #define ZGR_GEMM_LAUNCH(MODE)                                                                                           \
   {                                                                                                                     \
     static std::atomic<bool> attr_set{false};   /* set twice by racing threads at worst: the call is idempotent */         \
@@ -773,7 +836,7 @@ hipError_t launch_gemm_bf16_t(const bf16_t* A, const bf16_t* W, const bf16_t* bi
       if (e != hipSuccess) return e;                                                                                    \
       attr_set = true;                                                                                                  \
     }                                                                                                                   \
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * WM * WN), lds, s, A, W, M, N, K, out, bias, targets, tlogit);        \
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * WM * WN), lds, s, A, W, M, N, K, out, bias, targets, tlogit, tw, models); \
   }
   switch (epi) {
     case EPI_STORE: ZGR_GEMM_LAUNCH(EPI_STORE) break;
@@ -807,7 +870,7 @@ template <typename T, int N> __device__ __forceinline__ void load_row(const T* p
 }
 template <typename T, int DH>
 __global__ void __launch_bounds__(64, 2) attention_f32_kernel(const T* __restrict__ qkv, T* __restrict__ ctx, const int32_t* __restrict__ lengths,
-                                                           int seq, int d, int n_head, int causal, int heads) {
+                                                           int seq, int d, int n_head, int causal, int heads, int n_len) {
   constexpr int HK = DH / 2, F = DH > 32 ? DH / 32 : 1;
   const int lane = threadIdx.x, l32 = lane & 31, half = lane >> 5;
   // causal: the last query blocks have the most keys and are handed out first
@@ -816,7 +879,7 @@ __global__ void __launch_bounds__(64, 2) attention_f32_kernel(const T* __restric
   const int h = bh % n_head, b = bh / n_head;
   const size_t ld = (size_t)3 * d;
   const T* base = qkv + (size_t)b * seq * ld + (size_t)h * DH;
-  int kend = lengths ? lengths[b] : seq;                             // visible to every query; then the causal mask
+  int kend = lengths ? lengths[b % n_len] : seq;                     // visible to every query; then the causal mask
   kend = kend < seq ? kend : seq;
   const int last = causal && q0 + 32 < kend ? q0 + 32 : kend;        // keys of this wave
   float q[HK], k[HK];
@@ -916,14 +979,14 @@ __global__ void __launch_bounds__(64, 2) attention_f32_kernel(const T* __restric
 // values through LDS in chunks of 32.  The forward half of the cloud's backward pass keeps it (keep_order below), and small heads where it is the faster one.
 template <typename T, int DH>
 __global__ void __launch_bounds__(256) attention_kernel(const T* __restrict__ qkv, T* __restrict__ ctx, const int32_t* __restrict__ lengths,
-                                                        int seq, int d, int n_head, int causal) {
+                                                        int seq, int d, int n_head, int causal, int n_len) {
   constexpr int KC = 32;
   __shared__ float Ks[KC][DH], Vs[KC][DH];
   const int chunks = (seq + 255) / 256;
   const int qc = blockIdx.x % chunks, h = (blockIdx.x / chunks) % n_head, b = blockIdx.x / (chunks * n_head);
   const int qi = qc * 256 + threadIdx.x;
   const bool active = qi < seq;
-  const int len = lengths ? lengths[b] : seq;
+  const int len = lengths ? lengths[b % n_len] : seq;
   const size_t ld = (size_t)3 * d;
   const T* base = qkv + (size_t)b * seq * ld + (size_t)h * DH;
   float q[DH], acc[DH];
@@ -979,7 +1042,7 @@ constexpr int AT_KCH = 512;             // keys staged at a time: 72 KB of K row
 // 256-token sequence are staged once per head instead of once per 128 queries.
 template <int DH, int NW>
 __global__ void __launch_bounds__(64 * NW) attention_mfma_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ ctx, const int32_t* __restrict__ lengths,
-                                                                 int seq, int d, int n_head, int causal, int kpad) {
+                                                                 int seq, int d, int n_head, int causal, int kpad, int n_len) {
   static_assert(DH == 64, "head size 64");
   constexpr int QB = 32 * NW, NT = 64 * NW;                     // queries and threads per block
   extern __shared__ __attribute__((aligned(16))) unsigned char asm_[];
@@ -994,7 +1057,7 @@ __global__ void __launch_bounds__(64 * NW) attention_mfma_kernel(const bf16_t* _
   const int bh = (causal && qblocks > 1) ? (int)blockIdx.x % heads : (int)blockIdx.x / qblocks;
   const int h = bh % n_head, b = bh / n_head;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, half = lane >> 5;
-  const int len = lengths ? min(lengths[b], seq) : seq;
+  const int len = lengths ? min(lengths[b % n_len], seq) : seq;
   const size_t ld = (size_t)3 * d;
   const bf16_t* base = qkv + (size_t)b * seq * ld + (size_t)h * DH;
   // keys this block can need, rounded up to 32
@@ -1124,11 +1187,11 @@ __global__ void __launch_bounds__(64 * NW) attention_mfma_kernel(const bf16_t* _
 // THREADS MAXE entries in registers, so the row is read once (256 threads reading it twice: 135 us for 385 rows of 50272, now 26);
 // entries beyond those are read again.
 template <int THREADS, int MAXE>
-__global__ void __launch_bounds__(THREADS) ce_rows_kernel(const float* __restrict__ logits, const int32_t* __restrict__ targets, float* __restrict__ row_loss, int n) {
+__global__ void __launch_bounds__(THREADS) ce_rows_kernel(const float* __restrict__ logits, const int32_t* __restrict__ targets, float* __restrict__ row_loss, int n, int M) {
   constexpr int WAVES = THREADS / 64;
   __shared__ float red[WAVES];
   const int m = blockIdx.x, tid = threadIdx.x;
-  int tgt = targets[m];
+  int tgt = targets[m < M ? m : m - M];                              // two models: the same targets
   if (tgt < 0) { if (tid == 0) row_loss[m] = 0.f; return; }          // uniform over the block
   tgt = tgt >= n ? n - 1 : tgt;
   const float* row = logits + (size_t)m * n;
@@ -1160,10 +1223,10 @@ __global__ void __launch_bounds__(THREADS) ce_rows_kernel(const float* __restric
 
 // Combines the cross-entropy partials of one row: loss = log(sum_i s_i exp(m_i - M)) + M - logit[target].
 __global__ void __launch_bounds__(256) ce_combine_kernel(const float2* __restrict__ part, int n_part, const int32_t* __restrict__ targets,
-                                                         const float* __restrict__ tlogit, float* __restrict__ row_loss) {
+                                                         const float* __restrict__ tlogit, float* __restrict__ row_loss, int M) {
   __shared__ float red[4];
   const int m = blockIdx.x;
-  if (targets[m] < 0) { if (threadIdx.x == 0) row_loss[m] = 0.f; return; }
+  if (targets[m < M ? m : m - M] < 0) { if (threadIdx.x == 0) row_loss[m] = 0.f; return; }
   const float2* row = part + (size_t)m * n_part;
   float mx = -INFINITY;
   for (int i = threadIdx.x; i < n_part; i += 256) mx = fmaxf(mx, row[i].x);
@@ -1183,36 +1246,37 @@ __global__ void lm_targets_kernel(const int32_t* __restrict__ tok, int32_t* __re
   tgt[m] = t;
 }
 
-// mean of n_rows losses (ignoring the skipped ones by dividing by `count`), accumulated in fp64
+// mean of n_rows losses (ignoring the skipped ones by dividing by `count`), accumulated in fp64; a block per model
 __global__ void __launch_bounds__(256) mean_f64_kernel(const float* __restrict__ v, int n, double inv_count, double* __restrict__ out) {
   __shared__ double red[256];
+  v += (size_t)blockIdx.x * n;
   double s = 0.0;
   for (int i = threadIdx.x; i < n; i += 256) s += (double)v[i];
   red[threadIdx.x] = s;
   __syncthreads();
   for (int o = 128; o > 0; o >>= 1) { if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o]; __syncthreads(); }
-  if (threadIdx.x == 0) *out = red[0] * inv_count;
+  if (threadIdx.x == 0) out[blockIdx.x] = red[0] * inv_count;
 }
 
 // classification head on token 0 of every sequence: logits[b][c] = h[b*seq] . Wc[c] + bc[c]
 template <typename T>
 __global__ void __launch_bounds__(64) cls_head_kernel(const T* __restrict__ h, const T* __restrict__ Wc, const T* __restrict__ bc, float* __restrict__ logits,
-                                                      int seq, int d, int n_class) {
+                                                      int seq, int d, int n_class, int batch, int64_t wb) {
   const int b = blockIdx.x / n_class, c = blockIdx.x % n_class;
   const T* x = h + (size_t)b * seq * d;
-  const T* w = Wc + (size_t)c * d;
+  const T* w = of_model(Wc, b >= batch, wb) + (size_t)c * d;
   float s = 0.f;
   for (int i = threadIdx.x; i < d; i += 64) s = __builtin_fmaf(to_f32(x[i]), to_f32(w[i]), s);
   s = wave_sum(s);
-  if (threadIdx.x == 0) logits[b * n_class + c] = s + to_f32(bc[c]);
+  if (threadIdx.x == 0) logits[b * n_class + c] = s + to_f32(of_model(bc, b >= batch, wb)[c]);
 }
 
 // least squares: row_loss[b] = sum_o (pred[b][o] - Y[b][o])^2 / 2
-__global__ void __launch_bounds__(256) lsq_rows_kernel(const float* __restrict__ pred, const float* __restrict__ Y, float* __restrict__ row_loss, int n_out) {
+__global__ void __launch_bounds__(256) lsq_rows_kernel(const float* __restrict__ pred, const float* __restrict__ Y, float* __restrict__ row_loss, int n_out, int batch) {
   __shared__ float red[4];
-  const int b = blockIdx.x;
+  const int b = blockIdx.x, by = b < batch ? b : b - batch;
   float s = 0.f;
-  for (int i = threadIdx.x; i < n_out; i += 256) { const float r = pred[(size_t)b * n_out + i] - Y[(size_t)b * n_out + i]; s = __builtin_fmaf(r, r, s); }
+  for (int i = threadIdx.x; i < n_out; i += 256) { const float r = pred[(size_t)b * n_out + i] - Y[(size_t)by * n_out + i]; s = __builtin_fmaf(r, r, s); }
   s = block_sum(s, red);
   if (threadIdx.x == 0) row_loss[b] = 0.5f * s;
 }
@@ -1220,26 +1284,27 @@ __global__ void __launch_bounds__(256) lsq_rows_kernel(const float* __restrict__
 }  // namespace
 
 // ------------------------------------------------------------------ host launchers
-hipError_t launch_embed(int dtype, const int32_t* tok, const void* E, const void* Pe, float* x, int M, int seq, int d, int vocab, hipStream_t s) {
-  if (dtype == 0) hipLaunchKernelGGL(embed_kernel<float>, dim3(M), dim3(256), 0, s, tok, (const float*)E, (const float*)Pe, x, M, seq, d, vocab);
-  else            hipLaunchKernelGGL(embed_kernel<bf16_t>, dim3(M), dim3(256), 0, s, tok, (const bf16_t*)E, (const bf16_t*)Pe, x, M, seq, d, vocab);
+hipError_t launch_embed(int dtype, const int32_t* tok, const void* E, const void* Pe, float* x, int M, int seq, int d, int vocab, hipStream_t s, Twin tw) {
+  if (dtype == 0) hipLaunchKernelGGL(embed_kernel<float>, dim3(M * tw.models), dim3(256), 0, s, tok, (const float*)E, (const float*)Pe, x, M, seq, d, vocab, tw.w);
+  else            hipLaunchKernelGGL(embed_kernel<bf16_t>, dim3(M * tw.models), dim3(256), 0, s, tok, (const bf16_t*)E, (const bf16_t*)Pe, x, M, seq, d, vocab, tw.w);
   return hipGetLastError();
 }
 
-hipError_t launch_layernorm(int dtype, const float* x, const void* g, const void* b, void* out, int M, int d, float eps, hipStream_t s, float* xout) {
-  if (d % 4 == 0 && d <= 2048 && (((uintptr_t)g | (uintptr_t)b | (uintptr_t)out | (uintptr_t)xout) & 15) == 0) {
-    const dim3 grid((unsigned)((M + 3) / 4));
-    if (dtype == 0) hipLaunchKernelGGL(layernorm_wave_kernel<float>, grid, dim3(256), 0, s, x, (const float*)g, (const float*)b, (float*)out, M, d, eps, xout);
-    else            hipLaunchKernelGGL(layernorm_wave_kernel<bf16_t>, grid, dim3(256), 0, s, x, (const bf16_t*)g, (const bf16_t*)b, (bf16_t*)out, M, d, eps, xout);
+hipError_t launch_layernorm(int dtype, const float* x, const void* g, const void* b, void* out, int M, int d, float eps, hipStream_t s, float* xout, Twin tw) {
+  const int rows = M * tw.models;
+  if (d % 4 == 0 && d <= 2048 && (((uintptr_t)g | (uintptr_t)b | (uintptr_t)out | (uintptr_t)xout | (uintptr_t)tw.w) & 15) == 0) {
+    const dim3 grid((unsigned)((rows + 3) / 4));
+    if (dtype == 0) hipLaunchKernelGGL(layernorm_wave_kernel<float>, grid, dim3(256), 0, s, x, (const float*)g, (const float*)b, (float*)out, rows, d, eps, xout, M, tw.w);
+    else            hipLaunchKernelGGL(layernorm_wave_kernel<bf16_t>, grid, dim3(256), 0, s, x, (const bf16_t*)g, (const bf16_t*)b, (bf16_t*)out, rows, d, eps, xout, M, tw.w);
     return hipGetLastError();
   }
-  if (d % 4 == 0 && d <= 8192 && (((uintptr_t)g | (uintptr_t)b | (uintptr_t)out | (uintptr_t)xout) & 15) == 0) {
-    if (dtype == 0) hipLaunchKernelGGL(layernorm_reg_kernel<float>, dim3(M), dim3(256), 0, s, x, (const float*)g, (const float*)b, (float*)out, d, eps, xout);
-    else            hipLaunchKernelGGL(layernorm_reg_kernel<bf16_t>, dim3(M), dim3(256), 0, s, x, (const bf16_t*)g, (const bf16_t*)b, (bf16_t*)out, d, eps, xout);
+  if (d % 4 == 0 && d <= 8192 && (((uintptr_t)g | (uintptr_t)b | (uintptr_t)out | (uintptr_t)xout | (uintptr_t)tw.w) & 15) == 0) {
+    if (dtype == 0) hipLaunchKernelGGL(layernorm_reg_kernel<float>, dim3(rows), dim3(256), 0, s, x, (const float*)g, (const float*)b, (float*)out, d, eps, xout, M, tw.w);
+    else            hipLaunchKernelGGL(layernorm_reg_kernel<bf16_t>, dim3(rows), dim3(256), 0, s, x, (const bf16_t*)g, (const bf16_t*)b, (bf16_t*)out, d, eps, xout, M, tw.w);
     return hipGetLastError();
   }
-  if (dtype == 0) hipLaunchKernelGGL(layernorm_kernel<float>, dim3(M), dim3(256), 0, s, x, (const float*)g, (const float*)b, (float*)out, d, eps, xout);
-  else            hipLaunchKernelGGL(layernorm_kernel<bf16_t>, dim3(M), dim3(256), 0, s, x, (const bf16_t*)g, (const bf16_t*)b, (bf16_t*)out, d, eps, xout);
+  if (dtype == 0) hipLaunchKernelGGL(layernorm_kernel<float>, dim3(rows), dim3(256), 0, s, x, (const float*)g, (const float*)b, (float*)out, d, eps, xout, M, tw.w);
+  else            hipLaunchKernelGGL(layernorm_kernel<bf16_t>, dim3(rows), dim3(256), 0, s, x, (const bf16_t*)g, (const bf16_t*)b, (bf16_t*)out, d, eps, xout, M, tw.w);
   return hipGetLastError();
 }
 
@@ -1250,50 +1315,53 @@ hipError_t launch_layernorm(int dtype, const float* x, const void* g, const void
 //   257 to 319 tiles     1.1 - 1.2 at K = 768, 1.05 - 1.08 at 1024, 0.95 at 2048 (eight waves a tile, a few CUs with a second round of them)
 //   320 to 511 tiles     2.7 at K = 32, 1.2 at 128, 1.00 - 1.06 at 512, 0.94 - 1.01 at 768, 0.91 - 0.97 at 1024
 // From 512 on the tiles are the faster form (2048 x 2304 x 768, 1152 tiles: 81 us against 93).
-static bool product_is_faster(int M, int N, int K) {
-  const int64_t tiles = (((int64_t)M + 63) / 64) * (((int64_t)N + 63) / 64);
+static bool product_is_faster(int M, int N, int K, int models) {
+  const int64_t tiles = (((int64_t)M + 63) / 64) * (((int64_t)N + 63) / 64) * models;
   if (tiles >= 512) return false;
   return K >= (tiles <= 128 ? 64 : tiles <= 256 ? 512 : tiles < 320 ? 2048 : 768);
 }
 
-hipError_t launch_gemm(int dtype, const void* A, const void* W, const void* bias, void* out, int epi, int M, int N, int K, hipStream_t s, float* scratch, size_t scratch_floats, bool keep_order) {
+hipError_t launch_gemm(int dtype, const void* A, const void* W, const void* bias, void* out, int epi, int M, int N, int K, hipStream_t s, float* scratch, size_t scratch_floats, bool keep_order, Twin tw, bool shared_a) {
   GemmEpi ep{epi, out, bias};
+  const int es = dtype == 0 ? 4 : 2, n = tw.models;
+  const GemmTwin gt{shared_a ? 0 : (int64_t)M * K * es, tw.w, (int64_t)M * N * (epi == EPI_RESID || epi == EPI_F32 ? 4 : es), tw.w, 0};
   if (dtype == 0) {
-    const bool mfma_ok = K % 4 == 0 && (((uintptr_t)A | (uintptr_t)W) & 15) == 0;
-    const long t128 = (long)((M + 127) / 128) * ((N + 127) / 128);
+    const bool mfma_ok = K % 4 == 0 && (((uintptr_t)A | (uintptr_t)W | (uintptr_t)tw.w) & 15) == 0;
+    const long t128 = (long)((M + 127) / 128) * ((N + 127) / 128) * n;
     if (mfma_ok && t128 >= 512)   // enough 128 x 128 tiles for two blocks on every CU
-      hipLaunchKernelGGL((gemm_f32_mfma_kernel<2, 16>), dim3((N + 127) / 128, (M + 127) / 128), dim3(256), 0, s, (const float*)A, (const float*)W, M, N, K, ep);
-    else if (mfma_ok && !keep_order && product_is_faster(M, N, K)) {
+      hipLaunchKernelGGL((gemm_f32_mfma_kernel<2, 16>), dim3((N + 127) / 128, (M + 127) / 128, n), dim3(256), 0, s, (const float*)A, (const float*)W, M, N, K, ep, gt);
+    else if (mfma_ok && !keep_order && product_is_faster(M, N, K, n)) {
       ProductArgs p;
       p.A = A; p.lda = K; p.B = W; p.b_k = true; p.ldb = K; p.C = (float*)out; p.ldc = N; p.M = M; p.N = N; p.K = K;
       p.epilogue = epi; p.bias = (const float*)bias; p.scratch = scratch; p.scratch_floats = scratch_floats;
+      p.batches = n; p.a_outer = gt.a / 4; p.b_outer = p.bias_outer = tw.w / 4; p.c_outer = (int64_t)M * N;
       return launch_product(p, s);
     }
     else if (mfma_ok)
-      hipLaunchKernelGGL((gemm_f32_mfma_kernel<1, 16>), dim3((N + 63) / 64, (M + 63) / 64), dim3(256), 0, s, (const float*)A, (const float*)W, M, N, K, ep);
+      hipLaunchKernelGGL((gemm_f32_mfma_kernel<1, 16>), dim3((N + 63) / 64, (M + 63) / 64, n), dim3(256), 0, s, (const float*)A, (const float*)W, M, N, K, ep, gt);
     else
-      hipLaunchKernelGGL(gemm_f32_kernel, dim3((N + 63) / 64, (M + 63) / 64), dim3(256), 0, s, (const float*)A, (const float*)W, M, N, K, ep);
+      hipLaunchKernelGGL(gemm_f32_kernel, dim3((N + 63) / 64, (M + 63) / 64, n), dim3(256), 0, s, (const float*)A, (const float*)W, M, N, K, ep, gt);
   } else {
     if (K % GB_K != 0) return hipErrorInvalidValue;
     const bf16_t* a = (const bf16_t*)A; const bf16_t* w = (const bf16_t*)W; const bf16_t* b = (const bf16_t*)bias;
     // largest tile that still gives every CU a block
-    const long t256 = (long)((M + 255) / 256) * ((N + 255) / 256), t128x256 = (long)((M + 127) / 128) * ((N + 255) / 256);
+    const long t256 = (long)((M + 255) / 256) * ((N + 255) / 256) * n, t128x256 = (long)((M + 127) / 128) * ((N + 255) / 256) * n;
     if ((size_t)M * K >= ((size_t)1 << 31) || (size_t)N * K >= ((size_t)1 << 31)) return hipErrorInvalidValue;   // 32-bit byte offsets
     // 256 x 256 tiles unless their count leaves the last round of 256 CUs less than ~85 % full and 256 x 192 tiles fill it better
-    const long t192 = (long)((M + 255) / 256) * ((N + 191) / 192);
+    const long t192 = (long)((M + 255) / 256) * ((N + 191) / 192) * n;
     auto fill = [](long t) { const long rounds = (t + 255) / 256; return (double)t / (double)(rounds * 256); };
-    if (t256 >= 256 && (fill(t256) >= 0.85 || fill(t192) <= fill(t256))) return launch_gemm_bf16_t<256, 256, 2, 4, 64, 20, 1>(a, w, b, out, epi, M, N, K, s);
-    if (t192 >= 256 && N % 192 == 0) return launch_gemm_bf16_t<256, 192, 4, 2, 64, 20, 1>(a, w, b, out, epi, M, N, K, s);
-    if (t256 >= 256) return launch_gemm_bf16_t<256, 256, 2, 4, 64, 20, 1>(a, w, b, out, epi, M, N, K, s);
-    if (t128x256 >= 200) return launch_gemm_bf16_t<128, 256, 2, 4, 64, 20, 1>(a, w, b, out, epi, M, N, K, s);
+    if (t256 >= 256 && (fill(t256) >= 0.85 || fill(t192) <= fill(t256))) return launch_gemm_bf16_t<256, 256, 2, 4, 64, 20, 1>(a, w, b, out, epi, M, N, K, s, n, gt);
+    if (t192 >= 256 && N % 192 == 0) return launch_gemm_bf16_t<256, 192, 4, 2, 64, 20, 1>(a, w, b, out, epi, M, N, K, s, n, gt);
+    if (t256 >= 256) return launch_gemm_bf16_t<256, 256, 2, 4, 64, 20, 1>(a, w, b, out, epi, M, N, K, s, n, gt);
+    if (t128x256 >= 200) return launch_gemm_bf16_t<128, 256, 2, 4, 64, 20, 1>(a, w, b, out, epi, M, N, K, s, n, gt);
     // small problems.  More 128 x 128 tiles than CUs: the ping-pong loop on a short ring (64 KB, two blocks per CU, one block's
     // epilogue under the other's loop).  Fewer than half the CUs would get such a tile: 64 x 64 tiles with the plain loop
     // (four times the blocks, two of them per CU; 64 x 128 tiles were a few per cent slower).
     // In between (about one tile per CU): the ping-pong loop on the full ring.
-    const long t128 = (long)((M + 127) / 128) * ((N + 127) / 128);
-    if (t128 > 256) return launch_gemm_bf16_t<128, 128, 2, 4, 64, 8, 1>(a, w, b, out, epi, M, N, K, s);
-    if (t128 <= 128) return launch_gemm_bf16_t<64, 64, 2, 2, 64, 4>(a, w, b, out, epi, M, N, K, s);
-    return launch_gemm_bf16_t<128, 128, 2, 4, 64, 20, 1>(a, w, b, out, epi, M, N, K, s);
+    const long t128 = (long)((M + 127) / 128) * ((N + 127) / 128) * n;
+    if (t128 > 256) return launch_gemm_bf16_t<128, 128, 2, 4, 64, 8, 1>(a, w, b, out, epi, M, N, K, s, n, gt);
+    if (t128 <= 128) return launch_gemm_bf16_t<64, 64, 2, 2, 64, 4>(a, w, b, out, epi, M, N, K, s, n, gt);
+    return launch_gemm_bf16_t<128, 128, 2, 4, 64, 20, 1>(a, w, b, out, epi, M, N, K, s, n, gt);
   }
   return hipGetLastError();
 }
@@ -1302,7 +1370,7 @@ hipError_t launch_gemm(int dtype, const void* A, const void* W, const void* bias
 // part: float2 scratch of ce_partials_per_row(N) entries per row; tlogit: float [M].
 int ce_partials_per_row(int N) { return ((N + 255) / 256) * 2; }
 
-hipError_t launch_gemm_ce_bf16(const void* A, const void* W, const int32_t* targets, void* part, float* tlogit, float* row_loss, int M, int N, int K, hipStream_t s) {
+hipError_t launch_gemm_ce_bf16(const void* A, const void* W, const int32_t* targets, void* part, float* tlogit, float* row_loss, int M, int N, int K, hipStream_t s, Twin tw) {
   if (K % GB_K != 0 || (size_t)M * K >= ((size_t)1 << 31) || (size_t)N * K >= ((size_t)1 << 31)) return hipErrorInvalidValue;
   // transposed product: the kernel's rows are the N vocabulary entries, its columns the M tokens.  The tile of 256 x 256 multiplies mostly
   // nothing for a short prompt: up to 128 tokens take tiles of 128 vocabulary entries x 64 tokens with one wave across the entries, so that
@@ -1313,21 +1381,23 @@ hipError_t launch_gemm_ce_bf16(const void* A, const void* W, const int32_t* targ
   const bf16_t* w = (const bf16_t*)W; const bf16_t* a = (const bf16_t*)A;
   hipError_t e;
   int n_part = ce_partials_per_row(N);
+  // the kernel's first operand is the parameters here, its second the tokens
+  auto twin = [&](int parts) { return GemmTwin{tw.w, (int64_t)M * K * 2, (int64_t)M * parts * (int64_t)sizeof(float2), 0, (int64_t)M * 4}; };
   if (M <= 128) {
     n_part = (N + 127) / 128;
-    e = launch_gemm_bf16_t<128, 64, 1, 2, 64, 3>(w, a, nullptr, part, EPI_CE, N, M, K, s, targets, tlogit);
+    e = launch_gemm_bf16_t<128, 64, 1, 2, 64, 3>(w, a, nullptr, part, EPI_CE, N, M, K, s, tw.models, twin(n_part), targets, tlogit);
   } else {
-    e = launch_gemm_bf16_t<256, 256, 2, 4, 64, 20, 1>(w, a, nullptr, part, EPI_CE, N, M, K, s, targets, tlogit);
+    e = launch_gemm_bf16_t<256, 256, 2, 4, 64, 20, 1>(w, a, nullptr, part, EPI_CE, N, M, K, s, tw.models, twin(n_part), targets, tlogit);
   }
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(ce_combine_kernel, dim3(M), dim3(256), 0, s, (const float2*)part, n_part, targets, tlogit, row_loss);
+  hipLaunchKernelGGL(ce_combine_kernel, dim3(M * tw.models), dim3(256), 0, s, (const float2*)part, n_part, targets, tlogit, row_loss, M);
   return hipGetLastError();
 }
 
 template <typename T>
-static hipError_t launch_attention_t(const T* qkv, T* ctx, const int32_t* lengths, int batch, int seq, int d, int n_head, int causal, hipStream_t s, bool keep_order) {
+static hipError_t launch_attention_t(const T* qkv, T* ctx, const int32_t* lengths, int batch, int seq, int d, int n_head, int causal, hipStream_t s, bool keep_order, int models) {
   const int dh = d / n_head;
-  const int heads = batch * n_head;
+  const int heads = batch * models * n_head;
   // Heads of 8 leave the matrix instructions three quarters empty.  bf16: key by key is the faster form nearly everywhere (1 x 2048 tokens of
   // 32 heads, no causal mask: 174 us against 188, 4 x 2047: 180 against 334, 128 x 33: 21 against 28; only with few waves, 64 x 128, does it lose,
   // 65 against 57).  fp32: only on long sequences without a causal mask that fill the chip (3 x 2047: 175 against 181, 4 x 2047: 182 against
@@ -1336,26 +1406,26 @@ static hipError_t launch_attention_t(const T* qkv, T* ctx, const int32_t* length
   if (keep_order || by_key) {
     const dim3 grid((unsigned)heads * (unsigned)((seq + 255) / 256));
     switch (dh) {
-      case 8:   hipLaunchKernelGGL((attention_kernel<T, 8>), grid, dim3(256), 0, s, qkv, ctx, lengths, seq, d, n_head, causal); break;
-      case 16:  hipLaunchKernelGGL((attention_kernel<T, 16>), grid, dim3(256), 0, s, qkv, ctx, lengths, seq, d, n_head, causal); break;
-      case 32:  hipLaunchKernelGGL((attention_kernel<T, 32>), grid, dim3(256), 0, s, qkv, ctx, lengths, seq, d, n_head, causal); break;
-      case 64:  hipLaunchKernelGGL((attention_kernel<T, 64>), grid, dim3(256), 0, s, qkv, ctx, lengths, seq, d, n_head, causal); break;
+      case 8:   hipLaunchKernelGGL((attention_kernel<T, 8>), grid, dim3(256), 0, s, qkv, ctx, lengths, seq, d, n_head, causal, batch); break;
+      case 16:  hipLaunchKernelGGL((attention_kernel<T, 16>), grid, dim3(256), 0, s, qkv, ctx, lengths, seq, d, n_head, causal, batch); break;
+      case 32:  hipLaunchKernelGGL((attention_kernel<T, 32>), grid, dim3(256), 0, s, qkv, ctx, lengths, seq, d, n_head, causal, batch); break;
+      case 64:  hipLaunchKernelGGL((attention_kernel<T, 64>), grid, dim3(256), 0, s, qkv, ctx, lengths, seq, d, n_head, causal, batch); break;
       default:  return hipErrorInvalidValue;
     }
     return hipGetLastError();
   }
   const dim3 grid((unsigned)heads * (unsigned)((seq + 31) / 32));
   switch (dh) {
-    case 8:   if constexpr (sizeof(T) == 4) hipLaunchKernelGGL((attention_f32_kernel<T, 8>), grid, dim3(64), 0, s, qkv, ctx, lengths, seq, d, n_head, causal, heads); break;
-    case 16:  hipLaunchKernelGGL((attention_f32_kernel<T, 16>), grid, dim3(64), 0, s, qkv, ctx, lengths, seq, d, n_head, causal, heads); break;
-    case 32:  hipLaunchKernelGGL((attention_f32_kernel<T, 32>), grid, dim3(64), 0, s, qkv, ctx, lengths, seq, d, n_head, causal, heads); break;
-    case 64:  hipLaunchKernelGGL((attention_f32_kernel<T, 64>), grid, dim3(64), 0, s, qkv, ctx, lengths, seq, d, n_head, causal, heads); break;
+    case 8:   if constexpr (sizeof(T) == 4) hipLaunchKernelGGL((attention_f32_kernel<T, 8>), grid, dim3(64), 0, s, qkv, ctx, lengths, seq, d, n_head, causal, heads, batch); break;
+    case 16:  hipLaunchKernelGGL((attention_f32_kernel<T, 16>), grid, dim3(64), 0, s, qkv, ctx, lengths, seq, d, n_head, causal, heads, batch); break;
+    case 32:  hipLaunchKernelGGL((attention_f32_kernel<T, 32>), grid, dim3(64), 0, s, qkv, ctx, lengths, seq, d, n_head, causal, heads, batch); break;
+    case 64:  hipLaunchKernelGGL((attention_f32_kernel<T, 64>), grid, dim3(64), 0, s, qkv, ctx, lengths, seq, d, n_head, causal, heads, batch); break;
     default:  return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
-hipError_t launch_attention(int dtype, const void* qkv, void* ctx, const int32_t* lengths, int batch, int seq, int d, int n_head, int causal, hipStream_t s, bool keep_order) {
+hipError_t launch_attention(int dtype, const void* qkv, void* ctx, const int32_t* lengths, int batch, int seq, int d, int n_head, int causal, hipStream_t s, bool keep_order, int models) {
   if (dtype == 1 && d / n_head == 64 && d % 8 == 0) {
     const int kpad = seq < AT_KCH ? (seq + 31) / 32 * 32 : AT_KCH;          // keys resident in LDS at a time
     const size_t lds = sizeof(bf16_t) * ((size_t)kpad * AT_LDK + (size_t)64 * (kpad + 8));
@@ -1368,16 +1438,16 @@ hipError_t launch_attention(int dtype, const void* qkv, void* ctx, const int32_t
       attr_set = true;
     }
     if (seq > 128) {      // 256 queries per block: the keys of a head are staged once per 256 queries
-      const int grid = batch * n_head * ((seq + 255) / 256);
-      hipLaunchKernelGGL((attention_mfma_kernel<64, 8>), dim3(grid), dim3(512), lds, s, (const bf16_t*)qkv, (bf16_t*)ctx, lengths, seq, d, n_head, causal, kpad);
+      const int grid = batch * models * n_head * ((seq + 255) / 256);
+      hipLaunchKernelGGL((attention_mfma_kernel<64, 8>), dim3(grid), dim3(512), lds, s, (const bf16_t*)qkv, (bf16_t*)ctx, lengths, seq, d, n_head, causal, kpad, batch);
     } else {
-      const int grid = batch * n_head * ((seq + 127) / 128);
-      hipLaunchKernelGGL((attention_mfma_kernel<64, 4>), dim3(grid), dim3(256), lds, s, (const bf16_t*)qkv, (bf16_t*)ctx, lengths, seq, d, n_head, causal, kpad);
+      const int grid = batch * models * n_head * ((seq + 127) / 128);
+      hipLaunchKernelGGL((attention_mfma_kernel<64, 4>), dim3(grid), dim3(256), lds, s, (const bf16_t*)qkv, (bf16_t*)ctx, lengths, seq, d, n_head, causal, kpad, batch);
     }
     return hipGetLastError();
   }
-  if (dtype == 0) return launch_attention_t<float>((const float*)qkv, (float*)ctx, lengths, batch, seq, d, n_head, causal, s, keep_order);
-  return launch_attention_t<bf16_t>((const bf16_t*)qkv, (bf16_t*)ctx, lengths, batch, seq, d, n_head, causal, s, keep_order);
+  if (dtype == 0) return launch_attention_t<float>((const float*)qkv, (float*)ctx, lengths, batch, seq, d, n_head, causal, s, keep_order, models);
+  return launch_attention_t<bf16_t>((const bf16_t*)qkv, (bf16_t*)ctx, lengths, batch, seq, d, n_head, causal, s, keep_order, models);
 }
 
 bool attention_head_dim_supported(int dh) { return dh == 8 || dh == 16 || dh == 32 || dh == 64; }
@@ -1390,8 +1460,8 @@ hipError_t launch_lm_targets(const int32_t* tok, int32_t* tgt, int M, int seq, i
 // The smallest block that holds the row: threads without an entry, and iterations without one, cost as much as those with (2048 rows of 33 / 4097 /
 // 10000 / 20000, with the target and mean launches: 28 / 88 / 88 / 91 us when every row took 1024 threads of 4 or 50, now 20 / 28 / 37 / 58; 256
 // threads reading the row twice: 20 / 31 / 48 / 76).
-hipError_t launch_ce_rows(const float* logits, const int32_t* targets, float* row_loss, int M, int n, hipStream_t s) {
-#define ZGR_CE_ROWS(THREADS, MAXE) hipLaunchKernelGGL((ce_rows_kernel<THREADS, MAXE>), dim3(M), dim3(THREADS), 0, s, logits, targets, row_loss, n)
+hipError_t launch_ce_rows(const float* logits, const int32_t* targets, float* row_loss, int M, int n, hipStream_t s, int models) {
+#define ZGR_CE_ROWS(THREADS, MAXE) hipLaunchKernelGGL((ce_rows_kernel<THREADS, MAXE>), dim3(M * models), dim3(THREADS), 0, s, logits, targets, row_loss, n, M)
   if (n <= 1024)       ZGR_CE_ROWS(256, 4);
   else if (n <= 4096)  ZGR_CE_ROWS(256, 16);
   else if (n <= 8192)  ZGR_CE_ROWS(512, 16);
@@ -1402,19 +1472,19 @@ hipError_t launch_ce_rows(const float* logits, const int32_t* targets, float* ro
   return hipGetLastError();
 }
 
-hipError_t launch_mean_f64(const float* v, int n, double inv_count, double* out, hipStream_t s) {
-  hipLaunchKernelGGL(mean_f64_kernel, dim3(1), dim3(256), 0, s, v, n, inv_count, out);
+hipError_t launch_mean_f64(const float* v, int n, double inv_count, double* out, hipStream_t s, int models) {
+  hipLaunchKernelGGL(mean_f64_kernel, dim3(models), dim3(256), 0, s, v, n, inv_count, out);
   return hipGetLastError();
 }
 
-hipError_t launch_cls_head(int dtype, const void* h, const void* Wc, const void* bc, float* logits, int batch, int seq, int d, int n_class, hipStream_t s) {
-  if (dtype == 0) hipLaunchKernelGGL(cls_head_kernel<float>, dim3(batch * n_class), dim3(64), 0, s, (const float*)h, (const float*)Wc, (const float*)bc, logits, seq, d, n_class);
-  else            hipLaunchKernelGGL(cls_head_kernel<bf16_t>, dim3(batch * n_class), dim3(64), 0, s, (const bf16_t*)h, (const bf16_t*)Wc, (const bf16_t*)bc, logits, seq, d, n_class);
+hipError_t launch_cls_head(int dtype, const void* h, const void* Wc, const void* bc, float* logits, int batch, int seq, int d, int n_class, hipStream_t s, Twin tw) {
+  if (dtype == 0) hipLaunchKernelGGL(cls_head_kernel<float>, dim3(batch * tw.models * n_class), dim3(64), 0, s, (const float*)h, (const float*)Wc, (const float*)bc, logits, seq, d, n_class, batch, tw.w);
+  else            hipLaunchKernelGGL(cls_head_kernel<bf16_t>, dim3(batch * tw.models * n_class), dim3(64), 0, s, (const bf16_t*)h, (const bf16_t*)Wc, (const bf16_t*)bc, logits, seq, d, n_class, batch, tw.w);
   return hipGetLastError();
 }
 
-hipError_t launch_lsq_rows(const float* pred, const float* Y, float* row_loss, int batch, int n_out, hipStream_t s) {
-  hipLaunchKernelGGL(lsq_rows_kernel, dim3(batch), dim3(256), 0, s, pred, Y, row_loss, n_out);
+hipError_t launch_lsq_rows(const float* pred, const float* Y, float* row_loss, int batch, int n_out, hipStream_t s, int models) {
+  hipLaunchKernelGGL(lsq_rows_kernel, dim3(batch * models), dim3(256), 0, s, pred, Y, row_loss, n_out, batch);
   return hipGetLastError();
 }
 

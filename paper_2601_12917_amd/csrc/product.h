@@ -15,7 +15,8 @@ struct ProductArgs {
   int M = 0, N = 0, K = 0;
   float alpha = 1.0f;
   int epilogue = 0;                 // forward.h: EPI_STORE (or EPI_F32), EPI_GELU, EPI_RELU, EPI_RESID (C += ...)
-  const float* bias = nullptr;      // fp32 [N], may be NULL
+  const float* bias = nullptr;      // fp32 [N], may be NULL; bias_outer floats further on for each next batch (per outer step)
+  int64_t bias_outer = 0;
   float* a_sums = nullptr;          // when not NULL: a_sums[i] = sum_k A[i][k] (fp32 A contiguous along i, one batch)
   int batches = 1, zdiv = 1;
   int64_t a_outer = 0, a_inner = 0, b_outer = 0, b_inner = 0, c_outer = 0, c_inner = 0;

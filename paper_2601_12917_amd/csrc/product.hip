@@ -77,9 +77,10 @@ struct KernelArgs {
   float alpha;
   int epilogue; const float* bias;
   int split;                 // waves that share a piece of C, each taking every split-th step: 1 (a block is 2 x 2 pieces), 4 or 8 (one piece)
-  int k_part;                // terms of one part of the sum: part z writes its result at C + z c_part (a_sums + z M) when batches = 1
+  int k_part;                // terms of one part of the sum: part z of a batch writes its result at C + z c_part (a_sums + z M)
   int64_t c_part;
-  int batched, zdiv;
+  int parts, zdiv;           // a block's z: batch z / parts, part z % parts
+  int64_t bias_outer;
   int64_t a_outer, a_inner, b_outer, b_inner, c_outer, c_inner;
 };
 
@@ -104,18 +105,13 @@ __global__ void __launch_bounds__(512, 2) product_kernel(KernelArgs p) {
   const TA* A = reinterpret_cast<const TA*>(p.A);
   const TB* B = reinterpret_cast<const TB*>(p.B);
   float* C = p.C;
-  int k_begin = 0, k_end = p.K;
-  const int z = (int)blockIdx.z;
-  if (p.batched) {
-    const int zo = uniform(z / p.zdiv), zi = z - zo * p.zdiv;
-    A += zo * p.a_outer + zi * p.a_inner;
-    B += zo * p.b_outer + zi * p.b_inner;
-    C += zo * p.c_outer + zi * p.c_inner;
-  } else {
-    k_begin = z * p.k_part;
-    k_end = p.K < k_begin + p.k_part ? p.K : k_begin + p.k_part;
-    C += z * p.c_part;
-  }
+  const int zb = uniform((int)blockIdx.z / p.parts), z = (int)blockIdx.z - zb * p.parts;
+  const int zo = uniform(zb / p.zdiv), zi = zb - zo * p.zdiv;
+  A += zo * p.a_outer + zi * p.a_inner;
+  B += zo * p.b_outer + zi * p.b_inner;
+  C += zo * p.c_outer + zi * p.c_inner + z * p.c_part;
+  const float* const bias = p.bias ? p.bias + zo * p.bias_outer : nullptr;
+  const int k_begin = z * p.k_part, k_end = p.K < k_begin + p.k_part ? p.K : k_begin + p.k_part;
   const bool alone = p.split == 1;
   const int tm = alone ? (int)blockIdx.y * 2 + (wave >> 1) : (int)blockIdx.y, tn = alone ? (int)blockIdx.x * 2 + (wave & 1) : (int)blockIdx.x;
   const int i0 = tm * kTile, j0 = tn * kTile;
@@ -254,7 +250,7 @@ __global__ void __launch_bounds__(512, 2) product_kernel(KernelArgs p) {
   // Rows 4 kg + v0 .. 4 kg + v0 + count - 1 of the tiles (t, 0 .. TT - 1).  A whole piece without an epilogue takes no condition per
   // entry, and 16-byte stores where a lane's columns are consecutive.
   const float alpha = p.alpha;
-  const bool plain = !p.bias && (p.epilogue == EPI_STORE || p.epilogue == EPI_F32) && i0 + kTile <= p.M && j0 + kTile <= p.N;
+  const bool plain = !bias && (p.epilogue == EPI_STORE || p.epilogue == EPI_F32) && i0 + kTile <= p.M && j0 + kTile <= p.N;
   auto row_of = [&](int t, int v) { return AK ? i0 + 16 * t + 4 * kg + v : first_i(4 * kg + v) + t; };
   auto store = [&](int t, int v, const float (&x)[TT]) {
     const int i = row_of(t, v);
@@ -273,7 +269,7 @@ __global__ void __launch_bounds__(512, 2) product_kernel(KernelArgs p) {
 #pragma unroll
     for (int n = 0; n < TT; ++n) {
       const int j = BK ? j0 + 16 * n + il : first_j(il) + n;
-      if (j < p.N && (BK || j >= j0 + 4 * il)) finish(C + (int64_t)i * p.ldc + j, alpha * x[n], p.epilogue, p.bias, j);
+      if (j < p.N && (BK || j >= j0 + 4 * il)) finish(C + (int64_t)i * p.ldc + j, alpha * x[n], p.epilogue, bias, j);
     }
   };
   if (alone) {
@@ -304,9 +300,12 @@ __global__ void __launch_bounds__(512, 2) product_kernel(KernelArgs p) {
   }
 }
 
-// C[i][j] = epilogue(alpha (part 0 + part 1 + ...)[i][j] + bias[j]), a_sums likewise without alpha: the parts in their order
+// C[i][j] = epilogue(alpha (part 0 + part 1 + ...)[i][j] + bias[j]), a_sums likewise without alpha: the parts in their order; a row of blocks per batch
 __global__ void __launch_bounds__(256) product_sum_kernel(const float* __restrict__ part, int parts, int64_t n, int N, float* __restrict__ C, int64_t ldc, float alpha,
-                                                          const float* __restrict__ sum_part, int M, float* __restrict__ a_sums, int epilogue, const float* __restrict__ bias) {
+                                                          const float* __restrict__ sum_part, int M, float* __restrict__ a_sums, int epilogue, const float* __restrict__ bias, int64_t c_outer, int64_t bias_outer) {
+  part += (int64_t)blockIdx.y * parts * n;
+  C += (int64_t)blockIdx.y * c_outer;
+  if (bias) bias += (int64_t)blockIdx.y * bias_outer;
   for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < n + (a_sums ? M : 0); e += (int64_t)gridDim.x * 256) {
     const float* src = e < n ? part + e : sum_part + (e - n);
     const int64_t stride = e < n ? n : M;
@@ -348,32 +347,33 @@ hipError_t launch_product(const ProductArgs& p, hipStream_t s) {
   // blocks as well, each share at least eight steps (385 x 768 x 3072: 55 us undivided, 33 in three parts).
   int split = tiles >= kWaves || steps < 4 ? 1 : (tiles >= 320 || steps < 32 ? 4 : 8);
   int parts = 1;
-  if (p.batches == 1 && p.scratch && split > 1) {
+  const bool few = p.batches == 1 || (p.batches == 2 && p.zdiv == 1);      // one product, or that of two models
+  if (few && p.scratch && split > 1) {
     int64_t z = kWaves / (tiles * split);
-    const int64_t room = (int64_t)(p.scratch_floats / ((size_t)p.M * ((size_t)p.N + 1)));
+    const int64_t room = (int64_t)(p.scratch_floats / ((size_t)p.M * ((size_t)p.N + 1) * (size_t)p.batches));
     if (z > steps / (8 * split)) z = steps / (8 * split);
     if (z > room) z = room;
     if (z > 1) parts = (int)z;
   }
   // What is left with few pieces and an undivided sum takes 32 x 32 pieces, four times the blocks (512 x 128 x 512: 8.0 us against 16.6,
   // 385 x 768 x 768: 15.9 against 20.4; at 252 pieces, 385 x 2304 x 768, they are slower: 28 against 22).
-  const bool small = p.a_k && p.b_k && p.a_dtype == 0 && p.b_dtype == 0 && p.batches == 1 && tiles <= 128 && parts == 1;
+  const bool small = p.a_k && p.b_k && p.a_dtype == 0 && p.b_dtype == 0 && few && tiles <= 128 && parts == 1;
   if (small && split > 1) split = 4;
   const int tile = small ? 32 : 64;
   const int64_t tm = ((int64_t)p.M + tile - 1) / tile, tn = ((int64_t)p.N + tile - 1) / tile;
   if (tm > 65535) return hipErrorInvalidValue;
   KernelArgs k{};
   k.A = p.A; k.B = p.B; k.lda = p.lda; k.ldb = p.ldb; k.M = p.M; k.N = p.N; k.K = p.K; k.split = split;
-  k.batched = p.batches > 1; k.zdiv = p.zdiv;
+  k.parts = parts; k.zdiv = p.zdiv; k.bias_outer = p.bias_outer;
   k.a_outer = p.a_outer; k.a_inner = p.a_inner; k.b_outer = p.b_outer; k.b_inner = p.b_inner; k.c_outer = p.c_outer; k.c_inner = p.c_inner;
   k.k_part = (steps + parts - 1) / parts * kStep;
   if (k.k_part < 1) k.k_part = 1;
   const int64_t n = (int64_t)p.M * p.N;
-  float* sum_part = p.scratch + (int64_t)parts * n;
-  if (parts > 1) { k.C = p.scratch; k.ldc = p.N; k.alpha = 1.0f; k.epilogue = EPI_STORE; k.c_part = n; k.a_sums = p.a_sums ? sum_part : nullptr; }
+  float* sum_part = p.scratch + (int64_t)parts * p.batches * n;
+  if (parts > 1) { k.C = p.scratch; k.ldc = p.N; k.alpha = 1.0f; k.epilogue = EPI_STORE; k.c_part = n; k.c_outer = parts * n; k.c_inner = 0; k.a_sums = p.a_sums ? sum_part : nullptr; }
   else           { k.C = p.C; k.ldc = p.ldc; k.alpha = p.alpha; k.epilogue = p.epilogue; k.bias = p.bias; k.a_sums = p.a_sums; }
   const bool near = near_operand(p.A, p.a_dtype, p.a_k, p.lda, p.M, p.a_outer, p.a_inner) && near_operand(p.B, p.b_dtype, p.b_k, p.ldb, p.N, p.b_outer, p.b_inner);
-  const dim3 grid((unsigned)(split == 1 ? (tn + 1) / 2 : tn), (unsigned)(split == 1 ? (tm + 1) / 2 : tm), (unsigned)(p.batches > 1 ? p.batches : parts));
+  const dim3 grid((unsigned)(split == 1 ? (tn + 1) / 2 : tn), (unsigned)(split == 1 ? (tm + 1) / 2 : tm), (unsigned)(p.batches * parts));
   hipError_t e = hipErrorInvalidValue;
   const int form = (p.a_dtype << 3) | (p.b_dtype << 2) | ((p.a_k ? 1 : 0) << 1) | (p.b_k ? 1 : 0);
   switch (form) {
@@ -388,7 +388,7 @@ hipError_t launch_product(const ProductArgs& p, hipStream_t s) {
   }
   if (e != hipSuccess || parts == 1) return e;
   const int64_t total = n + (p.a_sums ? p.M : 0);
-  hipLaunchKernelGGL(product_sum_kernel, dim3((unsigned)(total / 256 + 1 < 2048 ? total / 256 + 1 : 2048)), dim3(256), 0, s, p.scratch, parts, n, p.N, p.C, p.ldc, p.alpha, sum_part, p.M, p.a_sums, p.epilogue, p.bias);
+  hipLaunchKernelGGL(product_sum_kernel, dim3((unsigned)(total / 256 + 1 < 2048 ? total / 256 + 1 : 2048), (unsigned)p.batches), dim3(256), 0, s, p.scratch, parts, n, p.N, p.C, p.ldc, p.alpha, sum_part, p.M, p.a_sums, p.epilogue, p.bias, p.c_outer, p.bias_outer);
   return hipGetLastError();
 }
 
