@@ -1104,7 +1104,9 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
       HIP_TRY(c, launch_gemm(ZGR_BF16, ws + v.tA, ws + v.tW, nullptr, da, EPI_F32, M, Kp, Np, s));
     } else {
       if (u) HIP_TRY(c, launch_bw_act(relu, u, dy, (int64_t)M * Np, s));
-      for (int p = 0; p < blocks; ++p) HIP_TRY(c, product(dy + (size_t)p * n, false, Np, a, Kp, grads[wi[p]], Kp, n, Kp, M, db[p]));
+      bool whole = true;                                 // the blocks' gradients in one piece, weights and biases: one product
+      for (int p = 1; p < blocks; ++p) whole = whole && grads[wi[p]] == grads[wi[0]] + (size_t)p * n * Kp && db[p] == db[0] + (size_t)p * n;
+      for (int p = 0; p < (whole ? 1 : blocks); ++p) HIP_TRY(c, product(dy + (size_t)p * n, false, Np, a, Kp, grads[wi[p]], Kp, whole ? Np : n, Kp, M, db[p]));
       HIP_TRY(c, product(dy, true, Np, W, Kp, da, Kp, M, Kp, Np, nullptr));
     }
     return ZGR_OK;
