@@ -7,6 +7,8 @@
 // Storage type T of weights and GEMM inputs is fp32 or bf16; accumulation, the
 // residual stream, LayerNorm, softmax and the loss are fp32, the final mean fp64.
 #include "forward.h"
+#include "act.h"
+#include "planes.h"
 #include "product.h"
 #include <atomic>
 
@@ -48,8 +50,6 @@ __device__ __forceinline__ float block_max(float v, float* red) {
   __syncthreads();
   return fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
 }
-
-__device__ __forceinline__ float gelu_erf(float x) { return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)); }
 
 // A parameter of the model a row belongs to: with two models (Twin) the second one's parameters lie w bytes behind the first's.
 template <typename T> __device__ __forceinline__ const T* of_model(const T* p, bool second, int64_t w) {
@@ -229,7 +229,7 @@ __device__ __forceinline__ void epilogue_store(const GemmEpi& ep, int m, int n, 
   const size_t o = (size_t)m * N + n;
   switch (ep.mode) {
     case EPI_STORE: from_f32(v, reinterpret_cast<T*>(ep.out)[o]); break;
-    case EPI_GELU:  from_f32(gelu_erf(v), reinterpret_cast<T*>(ep.out)[o]); break;
+    case EPI_GELU:  from_f32(gelu_f32(v), reinterpret_cast<T*>(ep.out)[o]); break;
     case EPI_RELU:  from_f32(fmaxf(v, 0.f), reinterpret_cast<T*>(ep.out)[o]); break;
     case EPI_RESID: reinterpret_cast<float*>(ep.out)[o] += v; break;
     default:        reinterpret_cast<float*>(ep.out)[o] = v; break;
@@ -279,6 +279,8 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const float* __restrict__
 // conflict-free at a row stride of 20 floats.
 // Any M, N; K % 4 == 0 and 16-byte aligned rows (the 64 x 64 kernel above takes what is left).
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4v __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 // At least two waves per SIMD, i.e. at most 256 registers per lane: the accumulators then live in ordinary vector registers,
 // which the MFMA reads and writes directly.  (Allowed 512, the compiler multiplies in the accumulation registers, carries
@@ -417,19 +419,276 @@ __global__ void __launch_bounds__(256, 2) gemm_f32_mfma_kernel(const float* __re
       }
 }
 
-// bf16 path: MFMA 32x32x16.  Block tile BM x BN, BK = 64, WM x WN waves, each owning (BM / WM) x (BN / WN) of
-// the output as FM x FN accumulator fragments of 32 x 32.  Operands go from global memory straight into LDS
-// (no register staging).  Two main loops: the ping-pong pipeline (PP = 1, eight waves, large tiles) and a plain
-// multi-stage loop with one barrier per k-tile (PP = 0, the 128 x 128 tile of small problems).
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-constexpr int GB_K = 64;
-
 __device__ __forceinline__ void wait_vmem() {   // all outstanding global -> LDS transfers of this wave have landed
 #if defined(__HIP_DEVICE_COMPILE__)
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #endif
 }
+
+template <int N> __device__ __forceinline__ void wait_vmem_upto() {   // at most N global -> LDS transfers of this wave still in flight
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+#endif
+}
+
+// Bare workgroup barrier.  __syncthreads() also fences memory, which makes the compiler drain every
+// outstanding global -> LDS transfer (vmcnt(0)) and so serialises a multi-stage pipeline; the main loop
+// orders its LDS traffic itself (wait_vmem_upto before the barrier, data-dependent waits on its own reads).
+__device__ __forceinline__ void block_barrier() {
+#if defined(__HIP_DEVICE_COMPILE__)
+  __builtin_amdgcn_s_barrier();
+#endif
+}
+
+// fp32 path on the bf16 matrix instructions (planes.h).  A wave owns 64 x 64 of the result, 2 x 2 accumulator fragments of 32 x 32, and takes k-tiles of
+// 32 terms.  SHARED: the block's four waves lie 2 x 2 on 128 x 128 and share the operands of every k-tile; otherwise all four own the
+// same 64 x 64 and each takes every fourth k-tile, with a part of LDS of its own and no barrier in its loop.
+// Operands go from global memory straight into LDS (as in the bf16 kernel below: 8 rows of 128 bytes an instruction, the 16-byte chunk c of row r in
+// slot c ^ ((r / 2) % 8)).  The half-wave h takes the chunks 4 ks + 2 h and the next as its eight terms of instruction ks, in both operands alike.
+// Cutting costs 5.5 vector instructions an entry, 176 per k-step against 24 matrix instructions of 32 cycles, whose shadow they just fit: eleven of the
+// next step's behind each of this step's.  (A 64 x 64 tile shared the usual way, 32 x 32 a wave, would cut every entry twice.)
+// The product of the first planes has a set of accumulators of its own: the other five terms are at most 2^-8 of it and round in a sum as
+// small, which leaves one rounding of the large sum per sixteen terms.
+// The shared form has two blocks a CU and no registers for that.  Off from fp64 by 1.1e-7 of the norm at K = 768 and 1.2e-7 at 1024 (the fp32 kernels: 1.8e-7 to
+// 5.0e-7, 5.7e-7), shared 4.3e-7 and 4.9e-7.
+// What bounds it: the chip's power at large sizes (4096 x 2048 x 8192 185 TFLOP/s, six times that on the matrix cores; the fp32 instruction 140), the wave's
+// issue at small ones (2400 cycles a k-tile for 1536 of matrix instructions; 2900 with the reads and transfers in a row).
+// K % 32 == 0 and 16-byte aligned rows; any M, N.
+constexpr int kPlaneK = 32;
+template <bool SHARED>
+__global__ void __launch_bounds__(256, SHARED ? 2 : 1) gemm_planes_kernel(const float* __restrict__ A, const float* __restrict__ W, int M, int N, int K, GemmEpi ep, GemmTwin tw, int models) {
+  constexpr int BT = SHARED ? 128 : 64;
+  constexpr int STAGE = 2 * BT * kPlaneK * 4;                  // bytes of a k-tile: A's rows, then W's
+  constexpr int LOADS = SHARED ? 8 : 16;                       // transfers of a wave per k-tile
+  extern __shared__ __attribute__((aligned(1024))) unsigned char gsm[];
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
+  const int wave = uniform_of(tid >> 6);
+  const int tiles_n = (N + BT - 1) / BT, tiles_m = (M + BT - 1) / BT;
+  int tm, tn;
+  const int model = tile_of_block(tiles_m, tiles_n, models, tm, tn);
+  if (model < 0) return;
+  A = ahead(A, model * tw.a); W = ahead(W, model * tw.w); ep.out = ahead(ep.out, model * tw.out); ep.bias = ahead(ep.bias, model * tw.bias);
+  const int mb = tm * BT, nb = tn * BT;                        // of the block's tile
+  const int m0 = SHARED ? mb + 64 * (wave >> 1) : mb, n0 = SHARED ? nb + 64 * (wave & 1) : nb;
+  // lane L supplies row L / 8 of a transfer's eight rows, slot L % 8; rows past the matrix are its last row (not stored).  Byte offsets from the
+  // tile's first row.  Shared tiles: wave w transfers rows 32 w .. 32 w + 31 of either operand.
+  uint32_t off[LOADS];
+#pragma unroll
+  for (int g = 0; g < LOADS; ++g) {
+    const int rl = (SHARED ? wave * 4 + (g & 3) : (g & 7)) * 8 + (lane >> 3), c = ((lane & 7) ^ ((rl >> 1) & 7)) * 16;
+    off[g] = (uint32_t)(g < LOADS / 2 ? min(rl, M - 1 - mb) : min(rl, N - 1 - nb)) * (uint32_t)K * 4u + (uint32_t)c;
+  }
+  const int nk = K / kPlaneK, steps = SHARED ? nk : (wave < nk ? (nk - wave + 3) / 4 : 0);
+  auto ktile = [&](int i) { const int j = i < steps ? i : steps - 1; return SHARED ? j : wave + 4 * j; };     // of step i
+#if defined(__HIP_DEVICE_COMPILE__)
+  const __amdgpu_buffer_rsrc_t rsA = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(A + (size_t)mb * K), 0, 0xFFFFFFFFu, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rsW = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(W + (size_t)nb * K), 0, 0xFFFFFFFFu, 0x00020000);
+#endif
+  const uint32_t own = SHARED ? 0u : (uint32_t)wave * 2 * STAGE;      // this wave's part of LDS
+  // Transfer g of step i's k-tile into place pos, unconditionally, so that every step is the same: past the last step that one is read again into a
+  // place nobody reads any more.
+  auto transfer = [&](int i, int pos, int g) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    const int rows8 = SHARED ? (g < 4 ? wave * 4 + g : 16 + wave * 4 + g - 4) : g;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(g < LOADS / 2 ? rsA : rsW, (__attribute__((address_space(3))) void*)(gsm + own + pos * STAGE + rows8 * 1024), 16, off[g], ktile(i) * (kPlaneK * 4), 0, 0);
+#endif
+  };
+  f32x16 acc[2][2], low_[SHARED ? 1 : 2][2];
+  f32x16 (&low)[2][2] = *reinterpret_cast<f32x16 (*)[2][2]>(SHARED ? &acc[0][0] : &low_[0][0]);
+  auto clear = [&]() {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[i][j][v] = low[i][j][v] = 0.f;
+  };
+  clear();
+  struct Frags { PlanesOf<3> f[4]; };                          // A's two, W's two
+  struct Raw { f32x4v lo[4], hi[4]; };
+  typedef __attribute__((address_space(3))) unsigned char lds_byte;
+  typedef __attribute__((address_space(3))) const f32x4v lds_f32x4;
+  const int swz = (l32 >> 1) & 7, rowA = SHARED ? 64 * (wave >> 1) : 0, rowW = BT + (SHARED ? 64 * (wave & 1) : 0);
+  uint32_t ra[2][2];                                           // LDS addresses of a lane's two chunks of row l32, k-step ks
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+    for (int u = 0; u < 2; ++u) ra[ks][u] = (uint32_t)(uintptr_t)(lds_byte*)gsm + own + (uint32_t)l32 * 128 + (uint32_t)(((4 * ks + 2 * half + u) ^ swz) * 16);
+  auto read = [&](int pos, int ks, int q, Raw& o) {
+    const int f = q >> 1;
+    const f32x4v v = *(lds_f32x4*)(uintptr_t)(ra[ks][q & 1] + (uint32_t)(pos * STAGE + ((f < 2 ? rowA : rowW) + 32 * (f & 1)) * 128));
+    if (q & 1) o.hi[f] = v; else o.lo[f] = v;
+  };
+  auto mfma = [&](const Frags& o, int x, int y, int q, f32x16 (&to)[2][2]) {
+    f32x16& t = to[q >> 1][q & 1];
+    t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, o.f[q >> 1].p[x]), __builtin_bit_cast(bf16x8, o.f[2 + (q & 1)].p[y]), t, 0, 0, 0);
+  };
+  auto in_this_order = [&]() {
+#if defined(__HIP_DEVICE_COMPILE__)
+    __builtin_amdgcn_sched_barrier(0);
+#endif
+  };
+  // The products of one k-step, the cuts of the next (from place pos) and the transfers of step `fetch` (none if negative) into place `to`.  A read or
+  // transfer holds the wave's issue up for 25 to 35 cycles, so none stands without a matrix instruction before it: two terms with a read behind each
+  // instruction, then a fragment under each term, eleven vector instructions behind a matrix instruction, and the transfers.
+  auto step = [&](const Frags& cur, int pos, int ks, Frags& next, int fetch, int to) {
+    constexpr int X[6] = {2, 1, 0, 1, 0, 0}, Y[6] = {0, 1, 2, 0, 1, 0};        // the smallest first
+    Raw r;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      read(pos, ks, q, r);
+      in_this_order();
+      mfma(cur, X[q >> 2], Y[q >> 2], q & 3, low);
+      in_this_order();
+    }
+#pragma unroll
+    for (int f = 0; f < 4; ++f) {
+      f32x16 (&sum)[2][2] = f == 3 ? acc : low;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        mfma(cur, X[2 + f], Y[2 + f], q, sum);
+        if (fetch >= 0 && 4 * f + q < LOADS) transfer(fetch, to, 4 * f + q);
+        const f32x4v& v = q < 2 ? r.lo[f] : r.hi[f];
+        cut_pair(v[2 * (q & 1)], v[2 * (q & 1) + 1], q, next.f[f]);
+        in_this_order();
+      }
+    }
+  };
+  if (steps > 0) {                                             // SHARED: the same for every wave of the block
+    Frags f0, f1;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int g = 0; g < LOADS; ++g) transfer(i, i, g);
+    wait_vmem_upto<LOADS>();
+    if (SHARED) block_barrier();
+    {
+      Raw r;
+#pragma unroll
+      for (int q = 0; q < 8; ++q) read(0, 0, q, r);
+#pragma unroll
+      for (int f = 0; f < 4; ++f) {
+        cut_pair(r.lo[f][0], r.lo[f][1], 0, f0.f[f]); cut_pair(r.lo[f][2], r.lo[f][3], 1, f0.f[f]);
+        cut_pair(r.hi[f][0], r.hi[f][1], 2, f0.f[f]); cut_pair(r.hi[f][2], r.hi[f][3], 3, f0.f[f]);
+      }
+    }
+    for (int i = 0; i < steps; ++i) {
+      step(f0, i & 1, 1, f1, -1, 0);
+      // this k-tile's values are in registers: its place may be overwritten once every wave that reads it is here, and the next one has
+      // landed once every wave's share of it has
+#if defined(__HIP_DEVICE_COMPILE__)
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#endif
+      wait_vmem();
+      if (SHARED) block_barrier();
+      in_this_order();
+      step(f1, (i + 1) & 1, 0, f0, i + 2, i & 1);              // behind the last step the cuts are of no use
+    }
+    wait_vmem();                                               // nothing on its way into LDS when it is used for the sums
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) if (!SHARED) acc[i][j] += low[i][j];
+  }
+  // a sum that is not finite: this wave's share of it again, by the fp32 instructions (planes.h)
+  {
+    float zero = 0.f;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) zero = __builtin_fmaf(acc[i][j][v], 0.f, zero);
+    if (__ballot(!(zero == 0.f))) {
+      clear();
+      for (int i = 0; i < steps; ++i)
+#pragma unroll 1
+        for (int k = ktile(i) * kPlaneK; k < (ktile(i) + 1) * kPlaneK; k += 2) {
+          float a[2], w[2];
+#pragma unroll
+          for (int f = 0; f < 2; ++f) { a[f] = A[(size_t)min(m0 + 32 * f + l32, M - 1) * K + k + half]; w[f] = W[(size_t)min(n0 + 32 * f + l32, N - 1) * K + k + half]; }
+#pragma unroll
+          for (int f = 0; f < 2; ++f)
+#pragma unroll
+            for (int g = 0; g < 2; ++g) acc[f][g] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[f], w[g], acc[f][g], 0, 0, 0);
+        }
+    }
+  }
+  // One fragment's rows 8 q + 4 half + v and column l32 from (m, n); the values a residual is added to are requested before anything is stored.
+  auto store = [&](const float (&r)[16], int m, int n) {
+    if (n >= N) return;
+    const float b = ep.bias ? reinterpret_cast<const float*>(ep.bias)[n] : 0.f;
+    float* o = reinterpret_cast<float*>(ep.out) + (size_t)m * N + n;
+    const int rows = M - m;                                    // may be negative
+    auto each = [&](auto f) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) { const int i = 8 * (v >> 2) + (v & 3); if (i < rows) f(v, o + (size_t)i * N); }
+    };
+    float old[16];
+    switch (ep.mode) {                                         // uniform
+      case EPI_GELU:  each([&](int v, float* p) { *p = gelu_f32(r[v] + b); }); break;
+      case EPI_RELU:  each([&](int v, float* p) { *p = fmaxf(r[v] + b, 0.f); }); break;
+      case EPI_RESID:
+        each([&](int v, float* p) { old[v] = *p; });
+        each([&](int v, float* p) { *p = old[v] + (r[v] + b); });
+        break;
+      default:        each([&](int v, float* p) { *p = r[v] + b; }); break;
+    }
+  };
+  if constexpr (SHARED) {
+#pragma unroll
+    for (int f = 0; f < 4; ++f) {
+      float r[16];
+#pragma unroll
+      for (int v = 0; v < 16; ++v) r[v] = acc[f >> 1][f & 1][v];
+      store(r, m0 + 32 * (f >> 1) + 4 * half, n0 + 32 * (f & 1) + l32);
+    }
+  } else {
+    // the waves' sums in the order ((0 + 1) + (2 + 3)); wave w adds up and stores fragment w
+    __syncthreads();
+    f32x4v* parts = reinterpret_cast<f32x4v*>(gsm);            // [wave][fragment][4][lane]
+#pragma unroll
+    for (int f = 0; f < 4; ++f)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const f32x16& a = acc[f >> 1][f & 1];
+        parts[((wave * 4 + f) * 4 + q) * 64 + lane] = f32x4v{a[4 * q], a[4 * q + 1], a[4 * q + 2], a[4 * q + 3]};
+      }
+    __syncthreads();
+    float r[16];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      f32x4v p[4];
+#pragma unroll
+      for (int w = 0; w < 4; ++w) p[w] = parts[((w * 4 + wave) * 4 + q) * 64 + lane];
+      const f32x4v t = (p[0] + p[1]) + (p[2] + p[3]);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) r[4 * q + v] = t[v];
+    }
+    store(r, m0 + 32 * (wave >> 1) + 4 * half, n0 + 32 * (wave & 1) + l32);
+  }
+}
+
+template <bool SHARED>
+static hipError_t launch_gemm_planes(const float* A, const float* W, int M, int N, int K, const GemmEpi& ep, const GemmTwin& gt, int models, hipStream_t s) {
+  constexpr int BT = SHARED ? 128 : 64, lds = SHARED ? 2 * 2 * 128 * kPlaneK * 4 : 4 * 2 * 2 * 64 * kPlaneK * 4;
+  static std::atomic<bool> attr_set{false};       // set twice by racing threads at worst: the call is idempotent
+  auto kern = gemm_planes_kernel<SHARED>;
+  if (!attr_set) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return e;
+    attr_set = true;
+  }
+  const int64_t tiles = (int64_t)((M + BT - 1) / BT) * ((N + BT - 1) / BT) * models;
+  hipLaunchKernelGGL(kern, dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(256), lds, s, A, W, M, N, K, ep, gt, models);
+  return hipGetLastError();
+}
+
+// bf16 path: MFMA 32x32x16.  Block tile BM x BN, BK = 64, WM x WN waves, each owning (BM / WM) x (BN / WN) of
+// the output as FM x FN accumulator fragments of 32 x 32.  Operands go from global memory straight into LDS
+// (no register staging).  Two main loops: the ping-pong pipeline (PP = 1, eight waves, large tiles) and a plain
+// multi-stage loop with one barrier per k-tile (PP = 0, the 128 x 128 tile of small problems).
+constexpr int GB_K = 64;
 
 // erf-GELU, x Phi(x) = max(x, 0) - |x|/2 erfc(|x| / sqrt 2), with erfc(|x| / sqrt 2) = exp2(q(|x|)): q is a
 // degree-6 fit of log2 erfc on [0, 6] (beyond 6 the term is below 1e-8 and |x| is clamped).  Absolute error of
@@ -455,21 +714,6 @@ __device__ __forceinline__ void epilogue_bf16(void* out, size_t o, float v) {
   else if (MODE == EPI_RELU) from_f32(fmaxf(v, 0.f), reinterpret_cast<bf16_t*>(out)[o]);
   else if (MODE == EPI_RESID) reinterpret_cast<float*>(out)[o] += v;
   else reinterpret_cast<float*>(out)[o] = v;
-}
-
-// Bare workgroup barrier.  __syncthreads() also fences memory, which makes the compiler drain every
-// outstanding global -> LDS transfer (vmcnt(0)) and so serialises a multi-stage pipeline; the main loop
-// orders its LDS traffic itself (wait_vmem_upto before the barrier, data-dependent waits on its own reads).
-__device__ __forceinline__ void block_barrier() {
-#if defined(__HIP_DEVICE_COMPILE__)
-  __builtin_amdgcn_s_barrier();
-#endif
-}
-
-template <int N> __device__ __forceinline__ void wait_vmem_upto() {   // at most N global -> LDS transfers of this wave still in flight
-#if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-#endif
 }
 
 template <int BM, int BN, int WM, int WN, int BK, int STAGES, int MODE, int PP = 0>
@@ -1321,6 +1565,16 @@ static bool product_is_faster(int M, int N, int K, int models) {
   return K >= (tiles <= 128 ? 64 : tiles <= 256 ? 512 : tiles < 320 ? 2048 : 768);
 }
 
+// Which fp32 projections (K a multiple of 32) go to the bf16 instructions' planes, by tiles of 128 x 128 and of 64 x 64 over both models; the kernels below
+// are the faster ones elsewhere (us with GELU, then those of the planes):
+//   shared:   2048 x 4096 (512 tiles) at K = 64 35 / 24, at 512 86 / 63; 2048 x 2048 (256) at 128 19.6 / 22.6, at 256 28.4 / 27.8, at 512 46 / 39;
+//             2048 x 1024 (128) at 512 26 / 33; 385 x 50272 x 768 (1572) 335 / 252, 4096 x 2048 x 8192 980 / 743
+//   private:  1024 x 1024 (256 tiles) at K = 128 10.1 / 9.8, at 512 17.1 / 14.2; 512 x 1024 (128) at 256 8.8 / 10.4, at 512 12.3 / 12.7; 1280 x 1280 (400) at 256
+//             17.1 / 19.7, at 512 25.9 / 24.7; 2048 x 1024 (512) at 512 26.0 / 27.6, with the residual at 1024 48 / 33; 385 x 768 (84) at 768 15.8 / 12.4, at 3072
+//             46 / 32; 231 x 1024 (64) at 1024 12.0 / 15.1
+static bool planes_shared(int64_t t128, int K) { return t128 >= 512 || (t128 >= 256 && K >= 256); }
+static bool planes_private(int64_t t64, int K) { return t64 >= 72 && K >= (t64 > 128 && t64 <= 256 ? 192 : 640); }
+
 hipError_t launch_gemm(int dtype, const void* A, const void* W, const void* bias, void* out, int epi, int M, int N, int K, hipStream_t s, float* scratch, size_t scratch_floats, bool keep_order, Twin tw, bool shared_a) {
   GemmEpi ep{epi, out, bias};
   const int es = dtype == 0 ? 4 : 2, n = tw.models;
@@ -1328,6 +1582,11 @@ hipError_t launch_gemm(int dtype, const void* A, const void* W, const void* bias
   if (dtype == 0) {
     const bool mfma_ok = K % 4 == 0 && (((uintptr_t)A | (uintptr_t)W | (uintptr_t)tw.w) & 15) == 0;
     const long t128 = (long)((M + 127) / 128) * ((N + 127) / 128) * n;
+    if (mfma_ok && !keep_order && K % kPlaneK == 0) {
+      const int64_t t64 = (int64_t)((M + 63) / 64) * ((N + 63) / 64) * n;
+      if (planes_shared(t128, K)) return launch_gemm_planes<true>((const float*)A, (const float*)W, M, N, K, ep, gt, n, s);
+      if (planes_private(t64, K)) return launch_gemm_planes<false>((const float*)A, (const float*)W, M, N, K, ep, gt, n, s);
+    }
     if (mfma_ok && t128 >= 512)   // enough 128 x 128 tiles for two blocks on every CU
       hipLaunchKernelGGL((gemm_f32_mfma_kernel<2, 16>), dim3((N + 127) / 128, (M + 127) / 128, n), dim3(256), 0, s, (const float*)A, (const float*)W, M, N, K, ep, gt);
     else if (mfma_ok && !keep_order && product_is_faster(M, N, K, n)) {

@@ -18,6 +18,7 @@
 // 1024-wide model, where its grid left most of the chip idle (54 of the pass's 60 ms; the whole pass now takes 10).
 #include "product.h"
 #include "forward.h"
+#include "act.h"
 #include "planes.h"
 
 namespace zgr {
@@ -126,7 +127,7 @@ struct KernelArgs {
 __device__ __forceinline__ void finish(float* c, float v, int epilogue, const float* bias, int j) {
   if (bias) v += bias[j];
   switch (epilogue) {                                            // uniform
-    case EPI_GELU:  *c = 0.5f * v * (1.0f + erff(v * 0.70710678118654752f)); break;
+    case EPI_GELU:  *c = gelu_f32(v); break;
     case EPI_RELU:  *c = fmaxf(v, 0.f); break;
     case EPI_RESID: *c += v; break;
     default:        *c = v; break;

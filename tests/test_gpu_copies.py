@@ -17,6 +17,8 @@ CASES = {
     "f32 rank 5": (I.shrink(I.CONFIGS["cfg2"], d_model=96, n_head=3, d_ff=200, k=5, k_full=9, **_SMALL), 32),
     # matrix-core kernel: whole and ragged tiles, both group sizes, both types
     "f32 rank 20": (I.shrink(I.CONFIGS["cfg2"], d_model=160, n_head=5, d_ff=328, k=20, k_full=20, **_SMALL), 16),
+    # both models' projections on the bf16 instructions' planes (160 tiles of 64 x 64 at K = 256)
+    "f32 planes": (I.shrink(I.CONFIGS["cfg2"], d_model=256, n_head=4, d_ff=1024, k=16, k_full=16, n_layer=2, vocab=900, max_pos=40, batch=8, seq=40), 32),
     "bf16 rank 16": (I.shrink(I.CONFIGS["cfg3"], d_model=256, n_head=4, d_ff=576, k=16, k_full=24, **_SMALL), 32),
     "bf16 rank 16 by 8": (I.shrink(I.CONFIGS["cfg3"], d_model=256, n_head=4, d_ff=576, k=16, k_full=16, **_SMALL), 16),
     "bf16 many tiles": (I.shrink(I.CONFIGS["cfg3"], d_model=512, n_head=8, d_ff=1088, k=8, k_full=8, **_SMALL), 32),

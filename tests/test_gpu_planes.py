@@ -1,0 +1,82 @@
+"""fp32 products taken on the bf16 matrix instructions (an fp32 number as three bf16 numbers): both tile forms of the projections at
+the edges of their tiles, k-tiles and dispatch rules, against fp64, and operands that are infinite, NaN or next to the largest number, which
+have to give what fp32 products give."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+#          M     N     K
+PRIVATE = [(575, 513, 192), (1024, 1024, 192), (320, 900, 640), (65, 4600, 672), (777, 770, 768), (1281, 1279, 640), (64, 4608, 3104)]      # 64 x 64 tiles, sums shared by four waves
+SHARED = [(2048, 2048, 256), (1921, 2047, 288), (2048, 4096, 32), (129, 32769, 64), (4000, 2049, 96)]      # 128 x 128 tiles
+
+
+@pytest.mark.parametrize("M,N,K", PRIVATE + SHARED)
+@pytest.mark.parametrize("epi", [1, 2, 3], ids=["gelu", "add", "fp32"])
+def test_projection_matches_fp64(M, N, K, epi):
+    import torch
+    from paper_2601_12917_amd import binding as B
+    gen = torch.Generator().manual_seed(M + N + K + epi)
+    A, W, b, old = (torch.randn(*s, generator=gen) * f for s, f in (((M, K), 1.0), ((N, K), K ** -0.5), ((N,), 1.0), ((M, N), 1.0)))
+    x = A.double() @ W.double().T + b.double()
+    want = {1: 0.5 * x * (1 + torch.erf(x / 2 ** 0.5)), 2: old.double() + x, 3: x}[epi]
+    # a sum of K products, each step rounding to 2^-24 of it, a random walk over at most K steps; |gelu'| <= 1.13
+    bound = 4 * np.sqrt(K + 16) * 2.0 ** -24 * 1.13 * (A.double().abs() @ W.double().abs().T + b.double().abs() + 1.0)
+    Ad, Wd, bd, out = A.cuda(), W.cuda(), b.cuda(), old.cuda()
+    B.check(B.lib().zgr_debug_gemm(0, Ad.data_ptr(), Wd.data_ptr(), bd.data_ptr(), out.data_ptr(), epi, M, N, K, torch.cuda.current_stream().cuda_stream))
+    torch.cuda.synchronize()
+    assert torch.all((out.double().cpu() - want).abs() <= bound)
+
+
+def _wild(x, gen):
+    """Entries that are infinite, NaN or close to the largest number, a few in a row of their own each."""
+    import torch
+    n = x.shape[0]
+    for i, v in enumerate((float("inf"), float("-inf"), float("nan"), 3.4e38, -3.3e38, 1e-40)):
+        x[(7 * i + 3) % n, int(torch.randint(x.shape[1], (1,), generator=gen))] = v
+    x[(7 * 6 + 3) % n, 0], x[(7 * 6 + 3) % n, 1] = float("inf"), float("-inf")
+    return x
+
+
+def _same(got, want):
+    """Finite where fp32 is, and the same kind of infinity or NaN where it is not."""
+    import torch
+    assert torch.equal(torch.isnan(got), torch.isnan(want))
+    big = want.abs() > 3.4e38                                       # past the largest fp32 number: sums may or may not reach it on the way
+    inf = torch.isinf(want)
+    assert torch.equal(got[inf].double(), want[inf])
+    ok = ~(torch.isnan(want) | big)
+    assert torch.all((got[ok].double() - want[ok]).abs() <= 1e-5 * (1.0 + want[ok].abs()))
+
+
+@pytest.mark.parametrize("M,N,K", [(577, 513, 256), (2048, 2048, 256)], ids=["private", "shared"])
+def test_projection_of_wild_operands(M, N, K):
+    import torch
+    from paper_2601_12917_amd import binding as B
+    gen = torch.Generator().manual_seed(K)
+    A, W = _wild(torch.randn(M, K, generator=gen), gen), torch.randn(N, K, generator=gen).clamp(-3, 3) * 0.01
+    want = A.double() @ W.double().T
+    Ad, Wd, out = A.cuda(), W.cuda(), torch.zeros(M, N, device="cuda")
+    B.check(B.lib().zgr_debug_gemm(0, Ad.data_ptr(), Wd.data_ptr(), None, out.data_ptr(), 3, M, N, K, torch.cuda.current_stream().cuda_stream))
+    torch.cuda.synchronize()
+    _same(out.cpu(), want)
+
+
+@pytest.mark.parametrize("a_k", [1, 0])
+@pytest.mark.parametrize("K", [77, 256])
+def test_product_of_wild_operands_with_bf16(a_k, K):
+    import torch
+    from paper_2601_12917_amd import binding as B
+    gen = torch.Generator().manual_seed(K + a_k)
+    M, N = 130, 200
+    A, Bm = _wild(torch.randn(M, K, generator=gen), gen), (torch.randn(K, N, generator=gen).clamp(-3, 3) * 0.01).bfloat16()
+    want = A.double() @ Bm.double()
+    Ad, Bd, out = (A if a_k else A.T.contiguous()).cuda(), Bm.cuda(), torch.zeros(M, N, device="cuda")
+    sums = None if a_k else torch.zeros(M, device="cuda")
+    B.check(B.lib().zgr_debug_product(Ad.data_ptr(), 0, a_k, Ad.shape[1], 0, Bd.data_ptr(), 1, 0, N, 0, out.data_ptr(), N, 0, M, N, K, 1.0, 1,
+                                      sums.data_ptr() if sums is not None else None, 0, None, None, 0, torch.cuda.current_stream().cuda_stream))
+    torch.cuda.synchronize()
+    _same(out.cpu(), want)
+    if sums is not None:
+        s = A.double().sum(1)
+        assert torch.equal(torch.isnan(sums.cpu()), torch.isnan(s))
