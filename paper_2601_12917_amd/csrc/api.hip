@@ -1007,8 +1007,9 @@ BwCarve bw_carve(const zgr_ctx* c, int batch, int seq) {
   v.dt = take(M * d * 4);
   v.dff = take(M * ff * 4);
   v.dqkv = take(M * 3 * d * 4);
-  v.P = take((size_t)batch * m.n_head * seq * seq * 4);
-  v.dS = take((size_t)batch * m.n_head * seq * seq * 4);
+  const bool pairs = bw_attention_buffers((int)d, m.n_head);       // [T, T] per head, or three numbers per query
+  v.P = take((size_t)batch * m.n_head * (pairs ? (size_t)seq * seq : 3 * align_up((size_t)seq, 32)) * 4);
+  v.dS = take(pairs ? (size_t)batch * m.n_head * seq * seq * 4 : 0);
   v.stats = take(M * 2 * 4);
   v.part = take(4 * bw_scratch_floats((int)d, (int)std::max(std::max(ff, 3 * d), (size_t)m.n_class)));
   v.split = take(kProductScratch * 4);

@@ -27,7 +27,9 @@ hipError_t launch_bw_layernorm(int dtype, const float* x, const void* g, const f
 hipError_t launch_bw_act_forward(int dtype, int relu, const float* u, void* f, int64_t n, hipStream_t s);
 hipError_t launch_bw_act(int relu, const float* u, float* df, int64_t n, hipStream_t s);
 hipError_t launch_bw_add(float* dst, const float* src, int64_t n, hipStream_t s);
-// dqkv [B T, 3 d] from dctx [B T, d]; P, dS: scratch of B n_head T T floats each
+// dqkv [B T, 3 d] from dctx [B T, d]; scratch: P of 3 B n_head floats for T rounded up to a multiple of 32, or, where the rule needs [T, T] buffers (heads of 8), P and dS of B n_head T T
+// floats each
+bool       bw_attention_buffers(int d, int n_head);
 hipError_t launch_bw_attention(int dtype, const void* qkv, const float* dctx, const int32_t* lengths, int batch, int seq, int d, int n_head, int causal,
                                float* P, float* dS, float* dqkv, hipStream_t s);
 // dE [vocab, d] += rows of dx by token, dPe [max_pos, d] = sums of dx by position

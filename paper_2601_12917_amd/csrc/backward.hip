@@ -7,6 +7,7 @@
 // for bf16 operands, product.hip for the others); LayerNorm and attention's softmax take a wave per row (LayerNorm rows of more than 2048
 // entries a workgroup), cross-entropy a workgroup.  Deterministic: no atomics, every sum has a fixed order.
 #include "backward.h"
+#include "planes.h"
 #include "product.h"
 
 namespace zgr {
@@ -428,6 +429,278 @@ __global__ void __launch_bounds__(256) attn_backward_rows_kernel(const int32_t* 
   }
 }
 
+// The same rule for heads of 16, 32 and 64 without the [T, T] buffers, in two kernels of one wave per 32 rows.  The first has 32 queries in its lanes and
+// walks the keys in blocks of 32 twice: S^T = K Q^T and dP^T = V dctx^T give the maximum, the sum of exponentials and p . dP of each query (stats), then
+// again dS and with it dQ^T += K^T dS^T.  The second has 32 keys in its lanes and walks the queries that see them: S, dP, P and dS from the stats,
+// dK^T += Q^T dS, dV^T += dctx^T P.  A lane holds 16 rows of one column of these 32 x 32 pieces, which are the next product's operand as they
+// are: its terms are taken in the order 8 (v / 4) + 4 half + v % 4, in which the other operand's rows are loaded.  Probabilities and dS stay in fp32: bf16
+// models take the products with dS and dctx on the bf16 instruction in three planes (planes.h), those of two fp32 operands are fp32 instructions.
+// Bound by load latency on short sequences, by the vector unit (exponentials, planes) on long ones.  Five batched products and the row rule with their
+// [T, T] buffers took 67 us for 192 heads of 64 at 128 tokens and 46 for 48 at 77.
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+constexpr float kLog2e = 1.44269504088896341f;
+
+// A lane's part of the 32 rows of an operand contracted over the head: row l32 (lane % 32).  fp32: entries half DH / 2 .. of it; bf16: eight
+// entries from 16 s + 8 half on for every instruction s.
+template <typename T, int DH> struct HeadRow;
+template <int DH> struct HeadRow<float, DH> {
+  float v[DH / 2];
+  __device__ __forceinline__ void load(const float* row, int half) {
+#pragma unroll
+    for (int i = 0; i < DH / 2; i += 4) {
+      const float4 t = *reinterpret_cast<const float4*>(row + half * (DH / 2) + i);
+      v[i] = t.x; v[i + 1] = t.y; v[i + 2] = t.z; v[i + 3] = t.w;
+    }
+  }
+};
+template <int DH> struct HeadRow<bf16_t, DH> {
+  bf16x8 v[DH / 16];
+  __device__ __forceinline__ void load(const bf16_t* row, int half) {
+#pragma unroll
+    for (int s = 0; s < DH / 16; ++s) v[s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(row + 16 * s + 8 * half));
+  }
+};
+// The fp32 rows that meet rows of storage type T: as they are, or cut into planes (ready()) once they have arrived.
+template <typename T, int DH> struct GradRow : HeadRow<float, DH> { __device__ __forceinline__ void ready() {} };
+template <int DH> struct GradRow<bf16_t, DH> {
+  float4 raw[DH / 16][2];
+  PlanesOf<3> v[DH / 16];
+  __device__ __forceinline__ void load(const float* row, int half) {
+#pragma unroll
+    for (int s = 0; s < DH / 16; ++s)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) raw[s][q] = *reinterpret_cast<const float4*>(row + 16 * s + 8 * half + 4 * q);
+  }
+  __device__ __forceinline__ void ready() {
+#pragma unroll
+    for (int s = 0; s < DH / 16; ++s)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) { cut_pair(raw[s][q].x, raw[s][q].y, 2 * q, v[s]); cut_pair(raw[s][q].z, raw[s][q].w, 2 * q + 1, v[s]); }
+  }
+};
+__device__ __forceinline__ f32x16 zeros16() {
+  f32x16 z;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) z[v] = 0.f;
+  return z;
+}
+template <int DH> __device__ __forceinline__ f32x16 rows_product(const HeadRow<float, DH>& a, const HeadRow<float, DH>& b) {
+  f32x16 s = zeros16();
+#pragma unroll
+  for (int i = 0; i < DH / 2; ++i) s = __builtin_amdgcn_mfma_f32_32x32x2f32(a.v[i], b.v[i], s, 0, 0, 0);
+  return s;
+}
+template <int DH> __device__ __forceinline__ f32x16 rows_product(const HeadRow<bf16_t, DH>& a, const HeadRow<bf16_t, DH>& b) {
+  f32x16 s = zeros16();
+#pragma unroll
+  for (int i = 0; i < DH / 16; ++i) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.v[i], b.v[i], s, 0, 0, 0);
+  return s;
+}
+template <int DH> __device__ __forceinline__ f32x16 rows_product(const HeadRow<bf16_t, DH>& a, const GradRow<bf16_t, DH>& b) {
+  f32x16 s = zeros16();
+#pragma unroll
+  for (int x = 2; x >= 0; --x)
+#pragma unroll
+    for (int i = 0; i < DH / 16; ++i) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.v[i], __builtin_bit_cast(bf16x8, b.v[i].p[x]), s, 0, 0, 0);
+  return s;
+}
+template <int DH> __device__ __forceinline__ f32x16 rows_product(const GradRow<bf16_t, DH>& a, const HeadRow<bf16_t, DH>& b) {
+  f32x16 s = zeros16();
+#pragma unroll
+  for (int x = 2; x >= 0; --x)
+#pragma unroll
+    for (int i = 0; i < DH / 16; ++i) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a.v[i].p[x]), b.v[i], s, 0, 0, 0);
+  return s;
+}
+// Entry 32 f + l32 of the 16 rows that meet a lane's 16 values: rows(v) is where row 8 (v / 4) + 4 half + v % 4 of the operand starts.  Requested ahead
+// of what they are multiplied with.
+template <typename T, int DH> struct Columns {
+  static constexpr int F = DH > 32 ? DH / 32 : 1;
+  T c[16][F];
+  template <typename R> __device__ __forceinline__ void load(R rows, int l32) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const T* r = rows(v);
+#pragma unroll
+      for (int f = 0; f < F; ++f) { c[v][f] = T{}; if (DH >= 32 || l32 < DH) c[v][f] = r[32 * f + l32]; }
+    }
+  }
+};
+// o[f][t][column] += sum over v of c[v][f] (of lane t) x[v]
+template <int DH> __device__ __forceinline__ void add_columns(f32x16* o, const Columns<float, DH>& a, const f32x16& x) {
+#pragma unroll
+  for (int v = 0; v < 16; ++v)
+#pragma unroll
+    for (int f = 0; f < Columns<float, DH>::F; ++f) o[f] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.c[v][f], x[v], o[f], 0, 0, 0);
+}
+template <int DH> __device__ __forceinline__ void add_columns(f32x16* o, const Columns<bf16_t, DH>& a, const f32x16& x) {
+  constexpr int F = Columns<bf16_t, DH>::F;
+  PlanesOf<3> p[2];
+#pragma unroll
+  for (int v = 0; v < 16; v += 2) cut_pair(x[v], x[v + 1], (v & 7) >> 1, p[v >> 3]);
+#pragma unroll
+  for (int st = 0; st < 2; ++st)
+#pragma unroll
+    for (int f = 0; f < F; ++f) {
+      planes_u32x4 w;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) w[i] = (uint32_t)a.c[8 * st + 2 * i][f].bits | ((uint32_t)a.c[8 * st + 2 * i + 1][f].bits << 16);
+#pragma unroll
+      for (int y = 2; y >= 0; --y) o[f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, p[st].p[y]), o[f], 0, 0, 0);
+    }
+}
+// the rows of a transposed result: lane (l32, half) holds four consecutive entries of row l32 at a time
+template <int DH> __device__ __forceinline__ void store_head_row(float* row, const f32x16* o, int half, float scale) {
+  constexpr int F = DH > 32 ? DH / 32 : 1;
+#pragma unroll
+  for (int f = 0; f < F; ++f)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int t = 32 * f + 8 * q + 4 * half;
+      if (t < DH) *reinterpret_cast<float4*>(row + t) = make_float4(o[f][4 * q] * scale, o[f][4 * q + 1] * scale, o[f][4 * q + 2] * scale, o[f][4 * q + 3] * scale);
+    }
+}
+
+// stats: [3][heads][T rounded up to 32], the maximum of the scaled scores in log2 units, 1 / (sum of exponentials) and p . dP.  The last query blocks come first:
+// under the causal mask they have the most keys.  The next block's rows are requested before this one's are used.
+template <typename T, int DH>
+__global__ void __launch_bounds__(64, 1) attn_backward_q_kernel(const T* __restrict__ qkv, const float* __restrict__ dctx, const int32_t* __restrict__ lengths, int seq, int d, int n_head, int causal,
+                                                                int heads, float* __restrict__ stats, float* __restrict__ dqkv) {
+  constexpr int F = DH > 32 ? DH / 32 : 1;
+  const int lane = threadIdx.x, l32 = lane & 31, half = lane >> 5;
+  const int blocks = (seq + 31) / 32, bh = (int)blockIdx.x % heads, q0 = 32 * (blocks - 1 - (int)blockIdx.x / heads), qi = q0 + l32, qr = qi < seq ? qi : seq - 1;
+  const int h = bh % n_head, b = bh / n_head;
+  const int64_t ld = (int64_t)3 * d;
+  const T* base = qkv + (int64_t)b * seq * ld + (int64_t)h * DH;
+  const float scale = 1.0f / sqrtf((float)DH), scale_log2 = kLog2e * scale;
+  int kend = lengths ? lengths[b] : seq;
+  kend = kend < seq ? kend : seq;
+  const int last = causal && q0 + 32 < kend ? q0 + 32 : kend;        // keys of this wave
+  HeadRow<T, DH> q, k, vv;
+  GradRow<T, DH> g;
+  q.load(base + qr * ld, half);
+  g.load(dctx + ((int64_t)b * seq + qr) * d + (int64_t)h * DH, half);
+  auto sees = [&](int key) { return key < last && (!causal || key <= qi); };
+  auto key_of = [&](int k0, int v) { return k0 + 8 * (v >> 2) + 4 * half + (v & 3); };
+  auto request = [&](int k0) {                                       // a key past the end repeats the last one
+    const T* row = base + (int64_t)(k0 + l32 < last ? k0 + l32 : last - 1) * ld + d;
+    k.load(row, half);
+    vv.load(row + d, half);
+  };
+  f32x16 s, dp;
+  auto scores = [&](int k0, int next) {                              // scaled, in log2 units, and dP
+    s = rows_product(k, q);
+    dp = rows_product(vv, g);
+    request(next);
+#pragma unroll
+    for (int v = 0; v < 16; ++v) s[v] = sees(key_of(k0, v)) ? s[v] * scale_log2 : -INFINITY;
+  };
+  float mx = -INFINITY, den = 0.f, dot = 0.f;
+  if (last > 0) request(0);
+  g.ready();
+  for (int k0 = 0; k0 < last; k0 += 32) {
+    scores(k0, k0 + 32 < last ? k0 + 32 : 0);                        // behind the last block, the first one for the second walk
+    float m = mx;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) m = fmaxf(m, s[v]);
+    m = fmaxf(m, __shfl_xor(m, 32, 64));
+    const float safe = m == -INFINITY ? 0.f : m, corr = __builtin_amdgcn_exp2f(mx - safe);
+    den *= corr; dot *= corr;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const float p = __builtin_amdgcn_exp2f(s[v] - safe);
+      den += p;
+      dot += sees(key_of(k0, v)) ? p * dp[v] : 0.f;
+    }
+    mx = m;
+  }
+  den += __shfl_xor(den, 32, 64);
+  dot += __shfl_xor(dot, 32, 64);
+  const float inv = den > 0.f ? 1.0f / den : 0.f, safe = mx == -INFINITY ? 0.f : mx;
+  dot *= inv;
+  if (qi < seq && half == 0) {
+    const int64_t i = (int64_t)bh * (32 * blocks) + qi, n = (int64_t)heads * (32 * blocks);
+    stats[i] = safe; stats[n + i] = inv; stats[2 * n + i] = dot;
+  }
+  f32x16 o[F];
+#pragma unroll
+  for (int f = 0; f < F; ++f) o[f] = zeros16();
+  for (int k0 = 0; k0 < last; k0 += 32) {
+    Columns<T, DH> kc;
+    kc.load([&](int v) { const int key = key_of(k0, v); return base + (int64_t)(key < last ? key : last - 1) * ld + d; }, l32);
+    scores(k0, k0 + 32 < last ? k0 + 32 : k0);
+#pragma unroll
+    for (int v = 0; v < 16; ++v) s[v] = sees(key_of(k0, v)) ? __builtin_amdgcn_exp2f(s[v] - safe) * inv * (dp[v] - dot) : 0.f;
+    add_columns<DH>(o, kc, s);
+  }
+  if (qi < seq) store_head_row<DH>(dqkv + ((int64_t)b * seq + qi) * ld + (int64_t)h * DH, o, half, scale);
+}
+
+template <typename T, int DH>
+__global__ void __launch_bounds__(64, 1) attn_backward_kv_kernel(const T* __restrict__ qkv, const float* __restrict__ dctx, const int32_t* __restrict__ lengths, int seq, int d, int n_head, int causal,
+                                                                 int heads, const float* __restrict__ stats, float* __restrict__ dqkv) {
+  constexpr int F = DH > 32 ? DH / 32 : 1;
+  const int lane = threadIdx.x, l32 = lane & 31, half = lane >> 5;
+  const int blocks = (seq + 31) / 32, bh = (int)blockIdx.x % heads, k0 = 32 * ((int)blockIdx.x / heads), kj = k0 + l32, kr = kj < seq ? kj : seq - 1;
+  const int h = bh % n_head, b = bh / n_head;
+  const int64_t ld = (int64_t)3 * d;
+  const T* base = qkv + (int64_t)b * seq * ld + (int64_t)h * DH;
+  const float* dbase = dctx + (int64_t)b * seq * d + (int64_t)h * DH;
+  const float scale = 1.0f / sqrtf((float)DH), scale_log2 = kLog2e * scale;
+  const float* mx = stats + (int64_t)bh * (32 * blocks);
+  const float* inv = mx + (int64_t)heads * (32 * blocks);
+  const float* dot = inv + (int64_t)heads * (32 * blocks);
+  int kend = lengths ? lengths[b] : seq;
+  kend = kend < seq ? kend : seq;
+  HeadRow<T, DH> k, vv, q;
+  GradRow<T, DH> g;
+  auto request = [&](int q0) {
+    const int qr = q0 + l32 < seq ? q0 + l32 : seq - 1;
+    q.load(base + qr * ld, half);
+    g.load(dbase + (int64_t)qr * d, half);
+  };
+  const int first = k0 >= kend ? seq : (causal ? k0 : 0);            // no query sees keys past the end
+  if (first < seq) request(first);
+  k.load(base + kr * ld + d, half);
+  vv.load(base + kr * ld + 2 * d, half);
+  f32x16 dk[F], dv[F];
+#pragma unroll
+  for (int f = 0; f < F; ++f) dk[f] = dv[f] = zeros16();
+  for (int q0 = first; q0 < seq; q0 += 32) {
+    auto query = [&](int v) { const int i = q0 + 8 * (v >> 2) + 4 * half + (v & 3); return i < seq ? i : seq - 1; };      // one past the end repeats the last: its P and dS are zero
+    Columns<float, DH> dc;
+    Columns<T, DH> qc;
+    float4 stat[3][4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int i = q0 + 8 * u + 4 * half;
+      stat[0][u] = *reinterpret_cast<const float4*>(mx + i); stat[1][u] = *reinterpret_cast<const float4*>(inv + i); stat[2][u] = *reinterpret_cast<const float4*>(dot + i);
+    }
+    dc.load([&](int v) { return dbase + (int64_t)query(v) * d; }, l32);
+    qc.load([&](int v) { return base + (int64_t)query(v) * ld; }, l32);
+    g.ready();
+    f32x16 p = rows_product(q, k), ds = rows_product(g, vv);
+    request(q0 + 32 < seq ? q0 + 32 : q0);
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int i = q0 + 8 * (v >> 2) + 4 * half + (v & 3);
+      const bool seen = i < seq && kj < kend && (!causal || kj <= i);
+      const float m = reinterpret_cast<const float*>(&stat[0][v >> 2])[v & 3], w = reinterpret_cast<const float*>(&stat[1][v >> 2])[v & 3], t = reinterpret_cast<const float*>(&stat[2][v >> 2])[v & 3];
+      const float e = seen ? __builtin_amdgcn_exp2f(p[v] * scale_log2 - m) * w : 0.f;
+      p[v] = e;
+      ds[v] = seen ? e * (ds[v] - t) : 0.f;
+    }
+    add_columns<DH>(dv, dc, p);
+    add_columns<DH>(dk, qc, ds);
+  }
+  if (kj < seq) {
+    float* row = dqkv + ((int64_t)b * seq + kj) * ld + (int64_t)h * DH;
+    store_head_row<DH>(row + d, dk, half, scale);
+    store_head_row<DH>(row + 2 * d, dv, half, 1.0f);
+  }
+}
+
 // ------------------------------------------------------------------ embeddings
 // x0[m] = E[tok[m]] + Pe[m mod seq].  dE accumulates (the tied head has written it), dPe is overwritten; the rows that share a token or a
 // position are added in the order of the rows, so the result is reproducible.
@@ -586,10 +859,30 @@ hipError_t launch_bw_add(float* dst, const float* src, int64_t n, hipStream_t s)
   return hipGetLastError();
 }
 
+bool bw_attention_buffers(int d, int n_head) { const int dh = d / n_head; return !((dh == 16 || dh == 32 || dh == 64) && d % 8 == 0); }
+
 hipError_t launch_bw_attention(int dtype, const void* qkv, const float* dctx, const int32_t* lengths, int batch, int seq, int d, int n_head, int causal,
                                float* P, float* dS, float* dqkv, hipStream_t s) {
   if (batch < 1 || seq < 1 || n_head < 1 || seq > kBackwardMaxSeq || d % n_head != 0) return hipErrorInvalidValue;
   const int dh = d / n_head, heads = batch * n_head;
+  if (!bw_attention_buffers(d, n_head)) {
+    const dim3 grid((unsigned)heads * (unsigned)((seq + 31) / 32));
+#define ZGR_ATTENTION(T, DH)                                                                                                                                              \
+    {                                                                                                                                                                     \
+      hipLaunchKernelGGL((attn_backward_q_kernel<T, DH>), grid, dim3(64), 0, s, reinterpret_cast<const T*>(qkv), dctx, lengths, seq, d, n_head, causal, heads, P, dqkv);  \
+      hipLaunchKernelGGL((attn_backward_kv_kernel<T, DH>), grid, dim3(64), 0, s, reinterpret_cast<const T*>(qkv), dctx, lengths, seq, d, n_head, causal, heads, P, dqkv); \
+      return hipGetLastError();                                                                                                                                           \
+    }
+    switch (dh | (dtype == 1 ? 256 : 0)) {
+      case 16: ZGR_ATTENTION(float, 16)
+      case 32: ZGR_ATTENTION(float, 32)
+      case 64: ZGR_ATTENTION(float, 64)
+      case 256 | 16: ZGR_ATTENTION(bf16_t, 16)
+      case 256 | 32: ZGR_ATTENTION(bf16_t, 32)
+      default: ZGR_ATTENTION(bf16_t, 64)
+    }
+#undef ZGR_ATTENTION
+  }
   // head z = (b, h): the [T, T] buffers are consecutive in z; q, k, v of the head are the columns h dh, d + h dh, 2 d + h dh of
   // the [T, 3 d] rows of sequence b, dctx its columns h dh of [T, d] rows
   const int64_t tt = (int64_t)seq * seq, ld = (int64_t)3 * d;
