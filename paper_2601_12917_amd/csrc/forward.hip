@@ -197,6 +197,15 @@ __global__ void __launch_bounds__(256) layernorm_wave_kernel(const float* x, con
 //   EPI_RESID: xres fp32 [M,N] += acc + bias
 //   EPI_F32  : outf fp32 [M,N] = acc + bias (bias may be null)
 struct GemmEpi { int mode; void* out; const void* bias; };
+// The values are waited for here, once.  In front of stores under a condition each the compiler waits anew inside every one of them, which then
+// sits out the store before it: 16 round trips to memory for a fragment at the ragged edge (the loss of a prompt of 33 tokens, 125M parameters, 24 such
+// launches: 721 us, now 691; the fp32 step on 5 x 77 tokens 3.07 ms, now 2.93).
+__device__ __forceinline__ void arrived(float (&v)[16]) {
+#if defined(__HIP_DEVICE_COMPILE__)
+#pragma unroll
+  for (int i = 0; i < 16; ++i) asm volatile("" : "+v"(v[i]));
+#endif
+}
 // Bytes from the first model's operands to the second's (Twin); which of the two a block works on is a dimension of the grid.
 struct GemmTwin { int64_t a, w, out, bias, tlogit; };
 // The tile of a block (and, returned, its model; -1: none).  Consecutive block ids go round-robin to the 8 XCDs, each with its own L2 and about 32
@@ -629,7 +638,9 @@ __global__ void __launch_bounds__(256, SHARED ? 2 : 1) gemm_planes_kernel(const 
       case EPI_GELU:  each([&](int v, float* p) { *p = gelu_f32(r[v] + b); }); break;
       case EPI_RELU:  each([&](int v, float* p) { *p = fmaxf(r[v] + b, 0.f); }); break;
       case EPI_RESID:
-        each([&](int v, float* p) { old[v] = *p; });
+#pragma unroll
+        for (int v = 0; v < 16; ++v) { const int i = 8 * (v >> 2) + (v & 3); old[v] = o[((ptrdiff_t)(i < rows ? i : rows - 1)) * N]; }
+        arrived(old);
         each([&](int v, float* p) { *p = old[v] + (r[v] + b); });
         break;
       default:        each([&](int v, float* p) { *p = r[v] + b; }); break;
@@ -1053,6 +1064,7 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_bf16_kernel(const bf16_t* _
           float old[16];
 #pragma unroll
           for (int v = 0; v < 16; ++v) { const int m = mbase + i * 32 + 8 * (v >> 2) + (v & 3); old[v] = op[(size_t)(m < M ? m : M - 1) * N - (n < N ? 0 : n - (N - 1))]; }
+          arrived(old);
 #pragma unroll
           for (int v = 0; v < 16; ++v) { const int m = mbase + i * 32 + 8 * (v >> 2) + (v & 3); if (m < M && n < N) op[(size_t)m * N] = old[v] + (acc[i][j][v] + bv[j]); }
           continue;
