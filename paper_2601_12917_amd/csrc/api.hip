@@ -969,12 +969,13 @@ struct BwCarve {
   std::vector<PerLayer> layer;
   size_t xfin = 0, hf = 0, logits = 0, targets = 0, row_loss = 0, loss = 0;
   size_t dx = 0, dt = 0, dff = 0, dqkv = 0, P = 0, dS = 0, stats = 0;
-  size_t part = 0;                   // chunk sums of the column reductions
+  size_t part = 0, part_floats = 0;  // chunk sums of the column reductions until they are added up
   size_t tA = 0, tB = 0, tC = 0, tW = 0;     // bf16 operands of the matrix-core products (bf16 models with a token count that is a multiple of 64)
   bool mfma = false;
   size_t split = 0;                  // parts of split sums
   size_t total = 0;
 };
+constexpr size_t kSumArena = (size_t)1 << 23;          // floats: the chunk sums of 8 blocks of the 125M model, 2 of the 1.3B model
 constexpr size_t kProductScratch = ((size_t)1 << 20) + ((size_t)1 << 14);      // floats: split sums take 2048 waves at most, eight to a 64 x 64 result, and 64 row sums each
 
 BwCarve bw_carve(const zgr_ctx* c, int batch, int seq) {
@@ -1011,7 +1012,8 @@ BwCarve bw_carve(const zgr_ctx* c, int batch, int seq) {
   v.P = take((size_t)batch * m.n_head * (pairs ? (size_t)seq * seq : 3 * align_up((size_t)seq, 32)) * 4);
   v.dS = take(pairs ? (size_t)batch * m.n_head * seq * seq * 4 : 0);
   v.stats = take(M * 2 * 4);
-  v.part = take(4 * bw_scratch_floats((int)d, (int)std::max(std::max(ff, 3 * d), (size_t)m.n_class)));
+  v.part_floats = std::max(kSumArena, bw_scratch_floats((int)d, (int)std::max(std::max(ff, 3 * d), (size_t)m.n_class)));
+  v.part = take(4 * v.part_floats);
   v.split = take(kProductScratch * 4);
   v.mfma = c->dtype == ZGR_BF16 && M % 64 == 0;
   if (v.mfma) {
@@ -1082,6 +1084,7 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
     return launch_product(p, s);
   };
   const int relu = m.act == ZGR_ACT_RELU ? 1 : 0;
+  SumQueue sums(F(v.part), v.part_floats, s);
   // whether the GEMM's 32-bit offsets reach the operands of the products with dy [M, Np] and W [Np, Kp]
   auto on_bf16 = [&](int Np, int Kp) {
     const size_t lim = (size_t)1 << 31, Npad = ((size_t)Np + 63) / 64 * 64;
@@ -1095,7 +1098,7 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
     const int n = Np / blocks;
     if (on_bf16(Np, Kp)) {
       unsigned char* tC = ws + v.tC;
-      HIP_TRY(c, launch_bw_gradient_operands(dy, u, relu, M, Np, tC, ws + v.tA, db, blocks, F(v.part), s));
+      HIP_TRY(c, launch_bw_gradient_operands(dy, u, relu, M, Np, tC, ws + v.tA, db, blocks, sums, s));
       HIP_TRY(c, launch_bw_transpose_bf16(a, M, Kp, Kp, ws + v.tB, M, s));
       bool whole = true;                                 // the blocks' weight gradients in one piece: one product
       for (int p = 1; p < blocks; ++p) whole = whole && grads[wi[p]] == grads[wi[0]] + (size_t)p * n * Kp;
@@ -1122,13 +1125,11 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
       HIP_TRY(c, launch_layernorm(dt, F(W.xin), T(c, L.ln1_g), T(c, L.ln1_b), ws + W.h1, M, d, m.ln_eps, s));
       HIP_TRY(c, launch_gemm(dt, ws + W.h1, T(c, L.wq), T(c, L.bq), ws + W.qkv, EPI_STORE, M, 3 * d, d, s, nullptr, 0, true));
       HIP_TRY(c, launch_attention(dt, ws + W.qkv, ws + W.ctx, lengths, B, Tn, d, H, lm ? 1 : 0, s, true));
-      HIP_TRY(c, hipMemcpyAsync(F(W.xmid), F(W.xin), xbytes, hipMemcpyDeviceToDevice, s));
-      HIP_TRY(c, launch_gemm(dt, ws + W.ctx, T(c, L.wo), T(c, L.bo), F(W.xmid), EPI_RESID, M, d, d, s, nullptr, 0, true));
+      HIP_TRY(c, launch_gemm(dt, ws + W.ctx, T(c, L.wo), T(c, L.bo), F(W.xmid), EPI_RESID, M, d, d, s, nullptr, 0, true, {}, false, F(W.xin)));
       HIP_TRY(c, launch_layernorm(dt, F(W.xmid), T(c, L.ln2_g), T(c, L.ln2_b), ws + W.h2, M, d, m.ln_eps, s));
       HIP_TRY(c, launch_gemm(dt, ws + W.h2, T(c, L.w1), T(c, L.b1), F(W.u), EPI_F32, M, ff, d, s, nullptr, 0, true));
       HIP_TRY(c, launch_bw_act_forward(dt, relu, F(W.u), ws + W.f, (int64_t)M * ff, s));
-      HIP_TRY(c, hipMemcpyAsync(xnext, F(W.xmid), xbytes, hipMemcpyDeviceToDevice, s));
-      HIP_TRY(c, launch_gemm(dt, ws + W.f, T(c, L.w2), T(c, L.b2), xnext, EPI_RESID, M, d, ff, s, nullptr, 0, true));
+      HIP_TRY(c, launch_gemm(dt, ws + W.f, T(c, L.w2), T(c, L.b2), xnext, EPI_RESID, M, d, ff, s, nullptr, 0, true, {}, false, F(W.xmid)));
     }
     HIP_TRY(c, launch_layernorm(dt, F(v.xfin), T(c, c->lnf_g), T(c, c->lnf_b), ws + v.hf, M, d, m.ln_eps, s));
   } else {
@@ -1142,13 +1143,11 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
       const bool last = l + 1 == m.n_layer;
       HIP_TRY(c, launch_gemm(dt, ws + W.h1, T(c, L.wq), T(c, L.bq), ws + W.qkv, EPI_STORE, M, 3 * d, d, s, nullptr, 0, true));
       HIP_TRY(c, launch_attention(dt, ws + W.qkv, ws + W.ctx, lengths, B, Tn, d, H, lm ? 1 : 0, s, true));
-      HIP_TRY(c, hipMemcpyAsync(F(W.xmid), F(W.xin), xbytes, hipMemcpyDeviceToDevice, s));
-      HIP_TRY(c, launch_gemm(dt, ws + W.ctx, T(c, L.wo), T(c, L.bo), F(W.xmid), EPI_RESID, M, d, d, s, nullptr, 0, true));
+      HIP_TRY(c, launch_gemm(dt, ws + W.ctx, T(c, L.wo), T(c, L.bo), F(W.xmid), EPI_RESID, M, d, d, s, nullptr, 0, true, {}, false, F(W.xin)));
       HIP_TRY(c, launch_layernorm(dt, F(W.xmid), T(c, L.ln1_g), T(c, L.ln1_b), ws + W.h2, M, d, m.ln_eps, s, F(W.x1n)));
       HIP_TRY(c, launch_gemm(dt, ws + W.h2, T(c, L.w1), T(c, L.b1), F(W.u), EPI_F32, M, ff, d, s, nullptr, 0, true));
       HIP_TRY(c, launch_bw_act_forward(dt, relu, F(W.u), ws + W.f, (int64_t)M * ff, s));
-      HIP_TRY(c, hipMemcpyAsync(F(W.y2), F(W.x1n), xbytes, hipMemcpyDeviceToDevice, s));
-      HIP_TRY(c, launch_gemm(dt, ws + W.f, T(c, L.w2), T(c, L.b2), F(W.y2), EPI_RESID, M, d, ff, s, nullptr, 0, true));
+      HIP_TRY(c, launch_gemm(dt, ws + W.f, T(c, L.w2), T(c, L.b2), F(W.y2), EPI_RESID, M, d, ff, s, nullptr, 0, true, {}, false, F(W.x1n)));
       HIP_TRY(c, launch_layernorm(dt, F(W.y2), T(c, L.ln2_g), T(c, L.ln2_b), last ? ws + v.hf : ws + v.layer[l + 1].h1, M, d, m.ln_eps, s,
                                   F(last ? v.xout : v.layer[l + 1].xin)));
     }
@@ -1196,14 +1195,14 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
   // ---- the blocks in reverse; dx holds dL/d(residual stream) at the block's output
   const int64_t nx = (int64_t)M * d;
   if (m.post_ln) HIP_TRY(c, hipMemcpyAsync(dx, dtb, xbytes, hipMemcpyDeviceToDevice, s));       // the head reads the last LN2's output itself
-  else HIP_TRY(c, launch_bw_layernorm(dt, F(v.xfin), T(c, c->lnf_g), dtb, nullptr, dx, F(v.stats), grads[c->lnf_g], grads[c->lnf_b], F(v.part), M, d, m.ln_eps, s));
+  else HIP_TRY(c, launch_bw_layernorm(dt, F(v.xfin), T(c, c->lnf_g), dtb, nullptr, dx, F(v.stats), grads[c->lnf_g], grads[c->lnf_b], sums, M, d, m.ln_eps, s));
   for (int l = m.n_layer - 1; l >= 0; --l) {
     const Layer& L = c->layers[l];
     const BwCarve::PerLayer& W = v.layer[l];
     float* dff = F(v.dff);
     float* dqkv = F(v.dqkv);
     // post-LN: x_out = LN2(y2), dx <- dL/dy2
-    if (m.post_ln) HIP_TRY(c, launch_bw_layernorm(dt, F(W.y2), T(c, L.ln2_g), dx, nullptr, dx, F(v.stats), grads[L.ln2_g], grads[L.ln2_b], F(v.part), M, d, m.ln_eps, s));
+    if (m.post_ln) HIP_TRY(c, launch_bw_layernorm(dt, F(W.y2), T(c, L.ln2_g), dx, nullptr, dx, F(v.stats), grads[L.ln2_g], grads[L.ln2_b], sums, M, d, m.ln_eps, s));
     // x_out (or y2) = x_mid (or x1n) + f W2^T + b2
     if ((st = linear_backward(dx, nullptr, d, T(c, L.w2), ff, ws + W.f, 1, &L.w2, &L.b2, dff)) != ZGR_OK) return st;
     // f = act(u), u = h2 W1^T + b1
@@ -1211,10 +1210,10 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
     if (m.post_ln) {
       // h2 = x1n = LN1(y1): dL/dx1n = dx + dh2, then dx <- dL/dy1
       HIP_TRY(c, launch_bw_add(dtb, dx, nx, s));
-      HIP_TRY(c, launch_bw_layernorm(dt, F(W.xmid), T(c, L.ln1_g), dtb, nullptr, dx, F(v.stats), grads[L.ln1_g], grads[L.ln1_b], F(v.part), M, d, m.ln_eps, s));
+      HIP_TRY(c, launch_bw_layernorm(dt, F(W.xmid), T(c, L.ln1_g), dtb, nullptr, dx, F(v.stats), grads[L.ln1_g], grads[L.ln1_b], sums, M, d, m.ln_eps, s));
     } else {
       // h2 = LN2(x_mid): dx <- dx + LN2'(dh2)
-      HIP_TRY(c, launch_bw_layernorm(dt, F(W.xmid), T(c, L.ln2_g), dtb, dx, dx, F(v.stats), grads[L.ln2_g], grads[L.ln2_b], F(v.part), M, d, m.ln_eps, s));
+      HIP_TRY(c, launch_bw_layernorm(dt, F(W.xmid), T(c, L.ln2_g), dtb, dx, dx, F(v.stats), grads[L.ln2_g], grads[L.ln2_b], sums, M, d, m.ln_eps, s));
     }
     // x_mid (or y1) = x_in + ctx Wo^T + bo
     if ((st = linear_backward(dx, nullptr, d, T(c, L.wo), d, ws + W.ctx, 1, &L.wo, &L.bo, dtb)) != ZGR_OK) return st;
@@ -1223,10 +1222,11 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
     const int wi[3] = {L.wq, L.wk, L.wv}, bi[3] = {L.bq, L.bk, L.bv};
     if ((st = linear_backward(dqkv, nullptr, 3 * d, T(c, L.wq), d, ws + W.h1, 3, wi, bi, dtb)) != ZGR_OK) return st;
     if (m.post_ln) HIP_TRY(c, launch_bw_add(dx, dtb, nx, s));                                    // h1 = x_in
-    else HIP_TRY(c, launch_bw_layernorm(dt, F(W.xin), T(c, L.ln1_g), dtb, dx, dx, F(v.stats), grads[L.ln1_g], grads[L.ln1_b], F(v.part), M, d, m.ln_eps, s));
+    else HIP_TRY(c, launch_bw_layernorm(dt, F(W.xin), T(c, L.ln1_g), dtb, dx, dx, F(v.stats), grads[L.ln1_g], grads[L.ln1_b], sums, M, d, m.ln_eps, s));
   }
   // post-LN: x_0 = LNF(embedding sum)
-  if (m.post_ln) HIP_TRY(c, launch_bw_layernorm(dt, F(v.xfin), T(c, c->lnf_g), dx, nullptr, dx, F(v.stats), grads[c->lnf_g], grads[c->lnf_b], F(v.part), M, d, m.ln_eps, s));
+  if (m.post_ln) HIP_TRY(c, launch_bw_layernorm(dt, F(v.xfin), T(c, c->lnf_g), dx, nullptr, dx, F(v.stats), grads[c->lnf_g], grads[c->lnf_b], sums, M, d, m.ln_eps, s));
+  HIP_TRY(c, sums.flush());
   HIP_TRY(c, launch_bw_embedding(tok, dx, M, Tn, d, m.vocab, grads[c->tok_emb], grads[c->pos_emb], m.max_pos, s));
   HIP_TRY(c, hipMemcpyAsync(c->host_loss, loss_dev, sizeof(double), hipMemcpyDeviceToHost, s));
   HIP_TRY(c, hipStreamSynchronize(s));

@@ -8,13 +8,31 @@ namespace zgr {
 
 constexpr int kBackwardMaxSeq = 2048;      // keys one wave of the attention rule holds
 
+// Sums over rows (bias and LayerNorm gradients) run in two stages: their kernels leave chunk sums in an arena, and one launch adds up those of
+// many, a row of blocks each (one launch per sum: 73 of 3.9 us in the backward pass of a 12-block decoder).  flush() before the results are read.
+constexpr int kSumJobs = 64;
+struct SumJob { const float* part; float* out; int64_t stride; int parts, n; };      // out[c] = sum over p of part[p stride + c], c < n
+struct SumJobs { SumJob job[kSumJobs]; };
+class SumQueue {
+ public:
+  SumQueue(float* arena, size_t floats, hipStream_t s) : arena_(arena), floats_(floats), s_(s) {}
+  hipError_t take(size_t floats, int n_jobs, float** part);      // room for the chunk sums of the next n_jobs sums
+  void add(const SumJob& j) { if (j.n > widest_) widest_ = j.n; jobs_.job[count_++] = j; }
+  hipError_t flush();
+ private:
+  float* arena_; size_t floats_, used_ = 0;
+  hipStream_t s_;
+  SumJobs jobs_{};
+  int count_ = 0, widest_ = 0;
+};
+
 // bf16 operands for the matrix-core products: out [cols, rows] (row stride ld_out, a multiple of 64) = in [rows, cols]^T in bf16 (row
 // stride ld_in, a multiple of 4), zeros between rows and ld_out
 hipError_t launch_bw_transpose_bf16(const void* in, int rows, int cols, int64_t ld_in, void* out, int64_t ld_out, hipStream_t s);
 // a gradient dy [M, N] (both multiples of 64) as both operands, cols_out [N, M] and rows_out [M, N] in bf16, and its column sums: dbias[i] gets
 // those of the i-th of n_bias equal column blocks.  With u != NULL it is dy act'(u) that is taken.
-hipError_t launch_bw_gradient_operands(const float* dy, const float* u, int relu, int M, int N, void* cols_out, void* rows_out, float* const* dbias, int n_bias, float* part, hipStream_t s);
-// `part` of the column sums and of the LayerNorm rule: scratch of bw_scratch_floats(d, widest N) floats
+hipError_t launch_bw_gradient_operands(const float* dy, const float* u, int relu, int M, int N, void* cols_out, void* rows_out, float* const* dbias, int n_bias, SumQueue& sums, hipStream_t s);
+// the largest room one column sum or LayerNorm rule takes of the arena, floats
 size_t     bw_scratch_floats(int d, int n_widest);
 hipError_t launch_bw_fill(float* p, int64_t n, float v, hipStream_t s);
 // row_loss of logits [rows, n] (0 where the target is negative), and (softmax - onehot(target)) inv_count in place of the logits or, with d16,
@@ -22,7 +40,7 @@ hipError_t launch_bw_fill(float* p, int64_t n, float v, hipStream_t s);
 hipError_t launch_bw_cross_entropy(float* logits, const int32_t* targets, int rows, int n, float inv_count, float* row_loss, void* d16, int64_t ld16, hipStream_t s);
 // y = LayerNorm(x) g + b: dx_out = (add ? add : 0) + dL/dx (dx_out may be add or dy), dg, db from dy; stats: 2 M floats of scratch
 hipError_t launch_bw_layernorm(int dtype, const float* x, const void* g, const float* dy, const float* add, float* dx_out, float* stats, float* dg, float* db,
-                               float* part, int M, int d, float eps, hipStream_t s);
+                               SumQueue& sums, int M, int d, float eps, hipStream_t s);
 // f = act(u) in the storage type (erf-GELU, or ReLU when relu != 0); df <- df act'(u); dst += src
 hipError_t launch_bw_act_forward(int dtype, int relu, const float* u, void* f, int64_t n, hipStream_t s);
 hipError_t launch_bw_act(int relu, const float* u, float* df, int64_t n, hipStream_t s);

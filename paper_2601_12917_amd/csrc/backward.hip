@@ -128,26 +128,25 @@ __global__ void __launch_bounds__(256) operand_kernel(const TIN* __restrict__ in
 
 // Sums over rows run in two stages with a fixed shape, so that the order of the additions never depends on scheduling: up to kColParts
 // chunks of rows are summed side by side, then the chunk sums are added in their order:
-// out[y][c] = sum over p of part[p stride + y n + c], c < n, blockIdx.y = y.  32 columns per block, eight threads to a column: each adds an
+// blockIdx.y = job: out[c] = sum over p of part[p stride + c], c < n.  32 columns per block, eight threads to a column: each adds an
 // eighth of the parts in order, then the eighths are added in order.
 constexpr int kColParts = 64;
-struct SumOutputs { float* out[3]; };
-__global__ void __launch_bounds__(256) colsum_final_kernel(const float* __restrict__ part, int parts, int64_t stride, int n, SumOutputs outs) {
+__global__ void __launch_bounds__(256) colsum_final_kernel(SumJobs jobs) {
   __shared__ float sums[8][32];
-  part += (int64_t)blockIdx.y * n;
-  float* out = outs.out[blockIdx.y];
-  const int c = blockIdx.x * 32 + (threadIdx.x & 31), q = threadIdx.x >> 5, per = (parts + 7) / 8;
+  const SumJob j = jobs.job[blockIdx.y];
+  const int c = blockIdx.x * 32 + (threadIdx.x & 31), q = threadIdx.x >> 5, per = (j.parts + 7) / 8;
+  if ((int)blockIdx.x * 32 >= j.n) return;                 // the whole block
   float s = 0.f;
-  if (c < n) {
-    const int end = parts < (q + 1) * per ? parts : (q + 1) * per;
+  if (c < j.n) {
+    const int end = j.parts < (q + 1) * per ? j.parts : (q + 1) * per;
 #pragma unroll 8
-    for (int p = q * per; p < end; ++p) s += part[p * stride + c];
+    for (int p = q * per; p < end; ++p) s += j.part[p * j.stride + c];
   }
   sums[q][threadIdx.x & 31] = s;
   __syncthreads();
-  if (q == 0 && c < n) {
+  if (q == 0 && c < j.n) {
     for (int i = 1; i < 8; ++i) s += sums[i][threadIdx.x];
-    out[c] = s;
+    j.out[c] = s;
   }
 }
 
@@ -768,6 +767,24 @@ __global__ void __launch_bounds__(256) embed_backward_kernel(const int32_t* __re
 
 static unsigned grid_1d(int64_t n) { const int64_t b = (n + 255) / 256; return (unsigned)(b < 1 ? 1 : (b > 4096 ? 4096 : b)); }
 
+hipError_t SumQueue::flush() {
+  if (count_ == 0) return hipSuccess;
+  hipLaunchKernelGGL(colsum_final_kernel, dim3((unsigned)((widest_ + 31) / 32), (unsigned)count_), dim3(256), 0, s_, jobs_);
+  used_ = 0; count_ = 0; widest_ = 0;
+  return hipGetLastError();
+}
+hipError_t SumQueue::take(size_t floats, int n_jobs, float** part) {
+  const size_t room = (floats + 63) / 64 * 64;
+  if (floats > floats_) return hipErrorInvalidValue;
+  if (count_ + n_jobs > kSumJobs || used_ + floats > floats_) {
+    const hipError_t e = flush();
+    if (e != hipSuccess) return e;
+  }
+  *part = arena_ + used_;
+  used_ += room;
+  return hipSuccess;
+}
+
 hipError_t launch_bw_transpose_bf16(const void* in, int rows, int cols, int64_t ld_in, void* out, int64_t ld_out, hipStream_t s) {
   if (rows < 1 || cols < 1) return hipSuccess;
   const dim3 grid((unsigned)((cols + 63) / 64), (unsigned)((ld_out + 63) / 64));
@@ -776,19 +793,20 @@ hipError_t launch_bw_transpose_bf16(const void* in, int rows, int cols, int64_t 
   return hipGetLastError();
 }
 
-hipError_t launch_bw_gradient_operands(const float* dy, const float* u, int relu, int M, int N, void* cols_out, void* rows_out, float* const* dbias, int n_bias, float* part, hipStream_t s) {
+hipError_t launch_bw_gradient_operands(const float* dy, const float* u, int relu, int M, int N, void* cols_out, void* rows_out, float* const* dbias, int n_bias, SumQueue& sums, hipStream_t s) {
   if (M < 1 || N < 1 || M % 64 || N % 64 || n_bias < 1 || n_bias > 3 || N % n_bias) return hipErrorInvalidValue;
   const int tiles = M / 64, per = (tiles + kColParts - 1) / kColParts, parts = (tiles + per - 1) / per;
   const dim3 grid((unsigned)(N / 64), (unsigned)parts);
+  float* part = nullptr;
+  const hipError_t e = sums.take((size_t)parts * N, n_bias, &part);
+  if (e != hipSuccess) return e;
 #define ZGR_OPERANDS(ACT)                                                                                                                                          \
   hipLaunchKernelGGL((operand_kernel<float, ACT, true, true>), grid, dim3(256), 0, s, dy, u, M, N, (int64_t)N, reinterpret_cast<bf16_t*>(cols_out), (int64_t)M,    \
                      reinterpret_cast<bf16_t*>(rows_out), (int64_t)N, part, per)
   if (!u) ZGR_OPERANDS(0); else if (relu) ZGR_OPERANDS(2); else ZGR_OPERANDS(1);
 #undef ZGR_OPERANDS
-  SumOutputs outs{};
-  for (int i = 0; i < n_bias; ++i) outs.out[i] = dbias[i];
   const int n = N / n_bias;
-  hipLaunchKernelGGL(colsum_final_kernel, dim3((unsigned)((n + 31) / 32), (unsigned)n_bias), dim3(256), 0, s, part, parts, (int64_t)N, n, outs);
+  for (int i = 0; i < n_bias; ++i) sums.add(SumJob{part + (size_t)i * n, dbias[i], (int64_t)N, parts, n});
   return hipGetLastError();
 }
 
@@ -813,22 +831,28 @@ hipError_t launch_bw_cross_entropy(float* logits, const int32_t* targets, int ro
 }
 
 hipError_t launch_bw_layernorm(int dtype, const float* x, const void* g, const float* dy, const float* add, float* dx_out, float* stats, float* dg, float* db,
-                               float* part, int M, int d, float eps, hipStream_t s) {
+                               SumQueue& sums, int M, int d, float eps, hipStream_t s) {
+  float* part = nullptr;
+  auto queue = [&](int parts) { sums.add(SumJob{part, dg, (int64_t)2 * d, parts, d}); sums.add(SumJob{part + d, db, (int64_t)2 * d, parts, d}); };
   if (d % 4 == 0 && d <= 2048) {
     const int blocks = M < 4 * kLnBlocks ? (M + 3) / 4 : kLnBlocks;
     const dim3 grid((unsigned)blocks);
+    const hipError_t e = sums.take((size_t)2 * blocks * d, 2, &part);
+    if (e != hipSuccess) return e;
 #define ZGR_LN_BACKWARD(T, MAXV) hipLaunchKernelGGL((ln_backward_wave_kernel<T, MAXV>), grid, dim3(256), 0, s, x, reinterpret_cast<const T*>(g), dy, add, dx_out, part, M, d, eps)
     if (dtype == 1) { if (d <= 512) ZGR_LN_BACKWARD(bf16_t, 2); else if (d <= 1024) ZGR_LN_BACKWARD(bf16_t, 4); else ZGR_LN_BACKWARD(bf16_t, 8); }
     else            { if (d <= 512) ZGR_LN_BACKWARD(float, 2); else if (d <= 1024) ZGR_LN_BACKWARD(float, 4); else ZGR_LN_BACKWARD(float, 8); }
 #undef ZGR_LN_BACKWARD
-    hipLaunchKernelGGL(colsum_final_kernel, dim3((unsigned)((d + 31) / 32), 2), dim3(256), 0, s, part, blocks, (int64_t)2 * d, d, SumOutputs{{dg, db, nullptr}});
+    queue(blocks);
     return hipGetLastError();
   }
   // the parameter gradients read dy: they go first, so that dx_out may overwrite it
+  hipError_t e = sums.take((size_t)2 * kColParts * d, 2, &part);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(ln_stats_kernel, dim3((unsigned)M), dim3(256), 0, s, x, stats, d, eps);
   hipLaunchKernelGGL(ln_param_grad_partial_kernel, dim3((unsigned)((d + 63) / 64), kColParts), dim3(256), 0, s, x, dy, stats, M, d, part);
-  hipLaunchKernelGGL(colsum_final_kernel, dim3((unsigned)((d + 31) / 32), 2), dim3(256), 0, s, part, kColParts, (int64_t)2 * d, d, SumOutputs{{dg, db, nullptr}});
-  hipError_t e = hipGetLastError();
+  queue(kColParts);
+  e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (dtype == 1) hipLaunchKernelGGL(ln_backward_kernel<bf16_t>, dim3((unsigned)M), dim3(256), 0, s, x, reinterpret_cast<const bf16_t*>(g), dy, add, dx_out, d, eps);
   else            hipLaunchKernelGGL(ln_backward_kernel<float>, dim3((unsigned)M), dim3(256), 0, s, x, reinterpret_cast<const float*>(g), dy, add, dx_out, d, eps);

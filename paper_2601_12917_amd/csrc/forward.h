@@ -22,9 +22,9 @@ hipError_t launch_layernorm(int dtype, const float* x, const void* g, const void
 // size 32), while a loss, which is all the client's forward returns, follows smoothly.  Neither order is the more accurate one: what this keeps is
 // that gradients stay as they were.  It is asked for with every model, though fp32 and GELU models have no such jump.
 // out = epilogue(A[M,K] W[N,K]^T + bias); bf16 storage needs K % 64 == 0.  scratch (may be NULL): floats a split sum may be kept in meanwhile.
-// shared_a: both models read the same A.
+// shared_a: both models read the same A.  resid: what EPI_RESID adds to, where that is not out itself (sums in the order of the tiles then).
 hipError_t launch_gemm(int dtype, const void* A, const void* W, const void* bias, void* out, int epi, int M, int N, int K, hipStream_t s, float* scratch = nullptr,
-                       size_t scratch_floats = 0, bool keep_order = false, Twin tw = {}, bool shared_a = false);
+                       size_t scratch_floats = 0, bool keep_order = false, Twin tw = {}, bool shared_a = false, const float* resid = nullptr);
 // bf16 vocabulary projection fused with cross-entropy: row_loss[m] = logsumexp(A[m] W^T) - (A[m] W^T)[targets[m]] (0 where targets[m] < 0).
 int        ce_partials_per_row(int N);
 hipError_t launch_gemm_ce_bf16(const void* A, const void* W, const int32_t* targets, void* part, float* tlogit, float* row_loss, int M, int N, int K, hipStream_t s, Twin tw = {});

@@ -196,7 +196,7 @@ __global__ void __launch_bounds__(256) layernorm_wave_kernel(const float* x, con
 //   EPI_GELU : out T [M,N] = gelu(acc + bias);  EPI_RELU: out T [M,N] = max(acc + bias, 0)
 //   EPI_RESID: xres fp32 [M,N] += acc + bias
 //   EPI_F32  : outf fp32 [M,N] = acc + bias (bias may be null)
-struct GemmEpi { int mode; void* out; const void* bias; };
+struct GemmEpi { int mode; void* out; const void* bias; const float* resid; };      // resid: what EPI_RESID adds to (out, or another place)
 // The values are waited for here, once.  In front of stores under a condition each the compiler waits anew inside every one of them, which then
 // sits out the store before it: 16 round trips to memory for a fragment at the ragged edge (the loss of a prompt of 33 tokens, 125M parameters, 24 such
 // launches: 721 us, now 691; the fp32 step on 5 x 77 tokens 3.07 ms, now 2.93).
@@ -240,14 +240,14 @@ __device__ __forceinline__ void epilogue_store(const GemmEpi& ep, int m, int n, 
     case EPI_STORE: from_f32(v, reinterpret_cast<T*>(ep.out)[o]); break;
     case EPI_GELU:  from_f32(gelu_f32(v), reinterpret_cast<T*>(ep.out)[o]); break;
     case EPI_RELU:  from_f32(fmaxf(v, 0.f), reinterpret_cast<T*>(ep.out)[o]); break;
-    case EPI_RESID: reinterpret_cast<float*>(ep.out)[o] += v; break;
+    case EPI_RESID: reinterpret_cast<float*>(ep.out)[o] = ep.resid[o] + v; break;
     default:        reinterpret_cast<float*>(ep.out)[o] = v; break;
   }
 }
 
 // fp32 path: 64x64 tile, BK = 16, each thread 4x4 outputs; any M, N, K.
 __global__ void __launch_bounds__(256) gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ W, int M, int N, int K, GemmEpi ep, GemmTwin tw) {
-  A = ahead(A, blockIdx.z * tw.a); W = ahead(W, blockIdx.z * tw.w); ep.out = ahead(ep.out, blockIdx.z * tw.out); ep.bias = ahead(ep.bias, blockIdx.z * tw.bias);
+  A = ahead(A, blockIdx.z * tw.a); W = ahead(W, blockIdx.z * tw.w); ep.out = ahead(ep.out, blockIdx.z * tw.out); ep.resid = ahead(ep.resid, blockIdx.z * tw.out); ep.bias = ahead(ep.bias, blockIdx.z * tw.bias);
   __shared__ float As[16][64 + 4], Ws[16][64 + 4];
   const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
   const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
@@ -296,7 +296,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 // the sums round the loop in vector registers and moves all 64 of them back and forth in every k-tile.)
 template <int F, int BK>
 __global__ void __launch_bounds__(256, 2) gemm_f32_mfma_kernel(const float* __restrict__ A, const float* __restrict__ W, int M, int N, int K, GemmEpi ep, GemmTwin tw) {
-  A = ahead(A, blockIdx.z * tw.a); W = ahead(W, blockIdx.z * tw.w); ep.out = ahead(ep.out, blockIdx.z * tw.out); ep.bias = ahead(ep.bias, blockIdx.z * tw.bias);
+  A = ahead(A, blockIdx.z * tw.a); W = ahead(W, blockIdx.z * tw.w); ep.out = ahead(ep.out, blockIdx.z * tw.out); ep.resid = ahead(ep.resid, blockIdx.z * tw.out); ep.bias = ahead(ep.bias, blockIdx.z * tw.bias);
   constexpr int BT = 64 * F, LD = BK + 4, KQ = BK / 4, NV = BT * KQ / 256, HK = BK / 2;
   __shared__ __attribute__((aligned(16))) float As[2][BT][LD], Ws[2][BT][LD];
   const int m0 = blockIdx.y * BT, n0 = blockIdx.x * BT;
@@ -476,7 +476,7 @@ __global__ void __launch_bounds__(256, SHARED ? 2 : 1) gemm_planes_kernel(const 
   int tm, tn;
   const int model = tile_of_block(tiles_m, tiles_n, models, tm, tn);
   if (model < 0) return;
-  A = ahead(A, model * tw.a); W = ahead(W, model * tw.w); ep.out = ahead(ep.out, model * tw.out); ep.bias = ahead(ep.bias, model * tw.bias);
+  A = ahead(A, model * tw.a); W = ahead(W, model * tw.w); ep.out = ahead(ep.out, model * tw.out); ep.resid = ahead(ep.resid, model * tw.out); ep.bias = ahead(ep.bias, model * tw.bias);
   const int mb = tm * BT, nb = tn * BT;                        // of the block's tile
   const int m0 = SHARED ? mb + 64 * (wave >> 1) : mb, n0 = SHARED ? nb + 64 * (wave & 1) : nb;
   // lane L supplies row L / 8 of a transfer's eight rows, slot L % 8; rows past the matrix are its last row (not stored).  Byte offsets from the
@@ -628,6 +628,7 @@ __global__ void __launch_bounds__(256, SHARED ? 2 : 1) gemm_planes_kernel(const 
     if (n >= N) return;
     const float b = ep.bias ? reinterpret_cast<const float*>(ep.bias)[n] : 0.f;
     float* o = reinterpret_cast<float*>(ep.out) + (size_t)m * N + n;
+    const float* src = ep.resid + (size_t)m * N + n;
     const int rows = M - m;                                    // may be negative
     auto each = [&](auto f) {
 #pragma unroll
@@ -639,7 +640,7 @@ __global__ void __launch_bounds__(256, SHARED ? 2 : 1) gemm_planes_kernel(const 
       case EPI_RELU:  each([&](int v, float* p) { *p = fmaxf(r[v] + b, 0.f); }); break;
       case EPI_RESID:
 #pragma unroll
-        for (int v = 0; v < 16; ++v) { const int i = 8 * (v >> 2) + (v & 3); old[v] = o[((ptrdiff_t)(i < rows ? i : rows - 1)) * N]; }
+        for (int v = 0; v < 16; ++v) { const int i = 8 * (v >> 2) + (v & 3); old[v] = src[((ptrdiff_t)(i < rows ? i : rows - 1)) * N]; }
         arrived(old);
         each([&](int v, float* p) { *p = old[v] + (r[v] + b); });
         break;
@@ -730,7 +731,7 @@ __device__ __forceinline__ void epilogue_bf16(void* out, size_t o, float v) {
 template <int BM, int BN, int WM, int WN, int BK, int STAGES, int MODE, int PP = 0>
 __global__ void __launch_bounds__(64 * WM * WN) gemm_bf16_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, int M, int N, int K,
                                                                  void* __restrict__ out, const bf16_t* __restrict__ bias,
-                                                                 const int32_t* __restrict__ targets, float* __restrict__ tlogit, GemmTwin tw, int models) {
+                                                                 const int32_t* __restrict__ targets, float* __restrict__ tlogit, GemmTwin tw, int models, const float* resid) {
   constexpr int NW = WM * WN;
   constexpr int FM = BM / (32 * WM), FN = BN / (32 * WN);      // 32x32 fragments per wave
   constexpr int CPR = BK / 8;                                  // 16-byte chunks per LDS row
@@ -758,6 +759,7 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_bf16_kernel(const bf16_t* _
   if (model < 0) return;
   A = ahead(A, model * tw.a); W = ahead(W, model * tw.w); out = ahead(out, model * tw.out); bias = ahead(bias, model * tw.bias);
   if (MODE == EPI_CE) tlogit = ahead(tlogit, model * tw.tlogit);
+  if (MODE == EPI_RESID) resid = ahead(resid, model * tw.out);
   const int m0 = tm * BM, n0 = tn * BN;
   f32x16 acc[FM][FN];
 #pragma unroll
@@ -773,7 +775,7 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_bf16_kernel(const bf16_t* _
   const bool pre_res = PRE_RES && m0 + BM <= M && n0 + BN <= N;
   float res[PRE_RES ? FM * FN * 16 : 1];
   if (PRE_RES && pre_res) {
-    const float* rp = reinterpret_cast<const float*>(out) + (size_t)(m0 + wm * (BM / WM) + 4 * (lane >> 5)) * N + n0 + wn * (BN / WN) + (lane & 31);
+    const float* rp = resid + (size_t)(m0 + wm * (BM / WM) + 4 * (lane >> 5)) * N + n0 + wn * (BN / WN) + (lane & 31);
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -1032,10 +1034,11 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_bf16_kernel(const bf16_t* _
     // larger tiles: the residual of the next fragment is requested before this one's sum is stored (one value after the other, each waiting for
     // the store before it: 2 x 4096 x 2048 x 2048 and x 8192 took 355 us on average, now 147)
     float* op = reinterpret_cast<float*>(out) + (size_t)mbase * N + nbase;
+    const float* ip = resid + (size_t)mbase * N + nbase;
     float old[2][16];
     auto request = [&](int f) {
 #pragma unroll
-      for (int v = 0; v < 16; ++v) old[f & 1][v] = op[(size_t)((f / FN) * 32 + 8 * (v >> 2) + (v & 3)) * N + (f % FN) * 32];
+      for (int v = 0; v < 16; ++v) old[f & 1][v] = ip[(size_t)((f / FN) * 32 + 8 * (v >> 2) + (v & 3)) * N + (f % FN) * 32];
     };
     request(0);
 #pragma unroll
@@ -1061,9 +1064,10 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_bf16_kernel(const bf16_t* _
         const int n = nbase + j * 32;
         if (MODE == EPI_RESID) {                                   // all of the fragment's values, then its stores
           float* op = reinterpret_cast<float*>(out) + n;
+          const float* ip = resid + n;
           float old[16];
 #pragma unroll
-          for (int v = 0; v < 16; ++v) { const int m = mbase + i * 32 + 8 * (v >> 2) + (v & 3); old[v] = op[(size_t)(m < M ? m : M - 1) * N - (n < N ? 0 : n - (N - 1))]; }
+          for (int v = 0; v < 16; ++v) { const int m = mbase + i * 32 + 8 * (v >> 2) + (v & 3); old[v] = ip[(size_t)(m < M ? m : M - 1) * N - (n < N ? 0 : n - (N - 1))]; }
           arrived(old);
 #pragma unroll
           for (int v = 0; v < 16; ++v) { const int m = mbase + i * 32 + 8 * (v >> 2) + (v & 3); if (m < M && n < N) op[(size_t)m * N] = old[v] + (acc[i][j][v] + bv[j]); }
@@ -1080,7 +1084,7 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_bf16_kernel(const bf16_t* _
 
 template <int BM, int BN, int WM, int WN, int BK, int STAGES, int PP = 0>
 hipError_t launch_gemm_bf16_t(const bf16_t* A, const bf16_t* W, const bf16_t* bias, void* out, int epi, int M, int N, int K, hipStream_t s, int models, const GemmTwin& tw,
-                              const int32_t* targets = nullptr, float* tlogit = nullptr) {
+                              const float* resid, const int32_t* targets = nullptr, float* tlogit = nullptr) {
   const size_t lds = PP ? (size_t)STAGES * 8192 : (size_t)STAGES * (BM + BN) * BK * sizeof(bf16_t);   // ping-pong: STAGES counts 8 KiB ring units
   const int grid = (((M + BM - 1) / BM) * ((N + BN - 1) / BN) * models + 7) / 8 * 8;
 #define ZGR_GEMM_LAUNCH(MODE)                                                                                           \
@@ -1092,7 +1096,7 @@ hipError_t launch_gemm_bf16_t(const bf16_t* A, const bf16_t* W, const bf16_t* bi
       if (e != hipSuccess) return e;                                                                                    \
       attr_set = true;                                                                                                  \
     }                                                                                                                   \
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * WM * WN), lds, s, A, W, M, N, K, out, bias, targets, tlogit, tw, models); \
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * WM * WN), lds, s, A, W, M, N, K, out, bias, targets, tlogit, tw, models, resid); \
   }
   switch (epi) {
     case EPI_STORE: ZGR_GEMM_LAUNCH(EPI_STORE) break;
@@ -1587,8 +1591,10 @@ static bool product_is_faster(int M, int N, int K, int models) {
 static bool planes_shared(int64_t t128, int K) { return t128 >= 512 || (t128 >= 256 && K >= 256); }
 static bool planes_private(int64_t t64, int K) { return t64 >= 72 && K >= (t64 > 128 && t64 <= 256 ? 192 : 640); }
 
-hipError_t launch_gemm(int dtype, const void* A, const void* W, const void* bias, void* out, int epi, int M, int N, int K, hipStream_t s, float* scratch, size_t scratch_floats, bool keep_order, Twin tw, bool shared_a) {
-  GemmEpi ep{epi, out, bias};
+hipError_t launch_gemm(int dtype, const void* A, const void* W, const void* bias, void* out, int epi, int M, int N, int K, hipStream_t s, float* scratch, size_t scratch_floats, bool keep_order, Twin tw, bool shared_a, const float* resid) {
+  const float* from = resid ? resid : (const float*)out;
+  GemmEpi ep{epi, out, bias, from};
+  if (resid && resid != out) keep_order = true;          // the kernels that split sums add to out itself
   const int es = dtype == 0 ? 4 : 2, n = tw.models;
   const GemmTwin gt{shared_a ? 0 : (int64_t)M * K * es, tw.w, (int64_t)M * N * (epi == EPI_RESID || epi == EPI_F32 ? 4 : es), tw.w, 0};
   if (dtype == 0) {
@@ -1621,18 +1627,18 @@ hipError_t launch_gemm(int dtype, const void* A, const void* W, const void* bias
     // 256 x 256 tiles unless their count leaves the last round of 256 CUs less than ~85 % full and 256 x 192 tiles fill it better
     const long t192 = (long)((M + 255) / 256) * ((N + 191) / 192) * n;
     auto fill = [](long t) { const long rounds = (t + 255) / 256; return (double)t / (double)(rounds * 256); };
-    if (t256 >= 256 && (fill(t256) >= 0.85 || fill(t192) <= fill(t256))) return launch_gemm_bf16_t<256, 256, 2, 4, 64, 20, 1>(a, w, b, out, epi, M, N, K, s, n, gt);
-    if (t192 >= 256 && N % 192 == 0) return launch_gemm_bf16_t<256, 192, 4, 2, 64, 20, 1>(a, w, b, out, epi, M, N, K, s, n, gt);
-    if (t256 >= 256) return launch_gemm_bf16_t<256, 256, 2, 4, 64, 20, 1>(a, w, b, out, epi, M, N, K, s, n, gt);
-    if (t128x256 >= 200) return launch_gemm_bf16_t<128, 256, 2, 4, 64, 20, 1>(a, w, b, out, epi, M, N, K, s, n, gt);
+    if (t256 >= 256 && (fill(t256) >= 0.85 || fill(t192) <= fill(t256))) return launch_gemm_bf16_t<256, 256, 2, 4, 64, 20, 1>(a, w, b, out, epi, M, N, K, s, n, gt, from);
+    if (t192 >= 256 && N % 192 == 0) return launch_gemm_bf16_t<256, 192, 4, 2, 64, 20, 1>(a, w, b, out, epi, M, N, K, s, n, gt, from);
+    if (t256 >= 256) return launch_gemm_bf16_t<256, 256, 2, 4, 64, 20, 1>(a, w, b, out, epi, M, N, K, s, n, gt, from);
+    if (t128x256 >= 200) return launch_gemm_bf16_t<128, 256, 2, 4, 64, 20, 1>(a, w, b, out, epi, M, N, K, s, n, gt, from);
     // small problems.  More 128 x 128 tiles than CUs: the ping-pong loop on a short ring (64 KB, two blocks per CU, one block's
     // epilogue under the other's loop).  Fewer than half the CUs would get such a tile: 64 x 64 tiles with the plain loop
     // (four times the blocks, two of them per CU; 64 x 128 tiles were a few per cent slower).
     // In between (about one tile per CU): the ping-pong loop on the full ring.
     const long t128 = (long)((M + 127) / 128) * ((N + 127) / 128) * n;
-    if (t128 > 256) return launch_gemm_bf16_t<128, 128, 2, 4, 64, 8, 1>(a, w, b, out, epi, M, N, K, s, n, gt);
-    if (t128 <= 128) return launch_gemm_bf16_t<64, 64, 2, 2, 64, 4>(a, w, b, out, epi, M, N, K, s, n, gt);
-    return launch_gemm_bf16_t<128, 128, 2, 4, 64, 20, 1>(a, w, b, out, epi, M, N, K, s, n, gt);
+    if (t128 > 256) return launch_gemm_bf16_t<128, 128, 2, 4, 64, 8, 1>(a, w, b, out, epi, M, N, K, s, n, gt, from);
+    if (t128 <= 128) return launch_gemm_bf16_t<64, 64, 2, 2, 64, 4>(a, w, b, out, epi, M, N, K, s, n, gt, from);
+    return launch_gemm_bf16_t<128, 128, 2, 4, 64, 20, 1>(a, w, b, out, epi, M, N, K, s, n, gt, from);
   }
   return hipGetLastError();
 }
@@ -1656,9 +1662,9 @@ hipError_t launch_gemm_ce_bf16(const void* A, const void* W, const int32_t* targ
   auto twin = [&](int parts) { return GemmTwin{tw.w, (int64_t)M * K * 2, (int64_t)M * parts * (int64_t)sizeof(float2), 0, (int64_t)M * 4}; };
   if (M <= 128) {
     n_part = (N + 127) / 128;
-    e = launch_gemm_bf16_t<128, 64, 1, 2, 64, 3>(w, a, nullptr, part, EPI_CE, N, M, K, s, tw.models, twin(n_part), targets, tlogit);
+    e = launch_gemm_bf16_t<128, 64, 1, 2, 64, 3>(w, a, nullptr, part, EPI_CE, N, M, K, s, tw.models, twin(n_part), nullptr, targets, tlogit);
   } else {
-    e = launch_gemm_bf16_t<256, 256, 2, 4, 64, 20, 1>(w, a, nullptr, part, EPI_CE, N, M, K, s, tw.models, twin(n_part), targets, tlogit);
+    e = launch_gemm_bf16_t<256, 256, 2, 4, 64, 20, 1>(w, a, nullptr, part, EPI_CE, N, M, K, s, tw.models, twin(n_part), nullptr, targets, tlogit);
   }
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(ce_combine_kernel, dim3(M * tw.models), dim3(256), 0, s, (const float2*)part, n_part, targets, tlogit, row_loss, M);
