@@ -970,7 +970,7 @@ struct BwCarve {
   size_t xfin = 0, hf = 0, logits = 0, targets = 0, row_loss = 0, loss = 0;
   size_t dx = 0, dt = 0, dff = 0, dqkv = 0, P = 0, dS = 0, stats = 0;
   size_t part = 0, part_floats = 0;  // chunk sums of the column reductions until they are added up
-  size_t tA = 0, tB = 0, tC = 0, tW = 0;     // bf16 operands of the matrix-core products (bf16 models with a token count that is a multiple of 64)
+  size_t tA = 0, tB = 0, tC = 0, tW = 0, tL[8] = {};     // bf16 operands of the matrix-core products (bf16 models with a token count that is a multiple of 64)
   bool mfma = false;
   size_t split = 0;                  // parts of split sums
   size_t total = 0;
@@ -1021,9 +1021,12 @@ BwCarve bw_carve(const zgr_ctx* c, int batch, int seq) {
     // vocabulary, rounded up to the multiple of 64 the GEMM takes
     const size_t widest = std::max(std::max(ff, 3 * d), m.arch == ZGR_ARCH_DECODER_LM ? align_up((size_t)m.vocab, 64) : (size_t)0);
     v.tA = take(2 * M * widest);
-    v.tB = take(2 * M * std::max(ff, d));
+    v.tB = take(m.arch == ZGR_ARCH_DECODER_LM ? 2 * M * d : 0);
     v.tC = take(2 * M * std::max(ff, 3 * d));
-    v.tW = take(2 * d * widest);
+    v.tW = take(m.arch == ZGR_ARCH_DECODER_LM ? 2 * d * align_up((size_t)m.vocab, 64) : 0);
+    // the transposed operands of one block: of FC2, FC1, the attention output and Q, K, V the kept input and the weights
+    const size_t in[4] = {ff, d, d, d}, out[4] = {d, ff, d, 3 * d};
+    for (int i = 0; i < 4; ++i) { v.tL[2 * i] = take(2 * M * in[i]); v.tL[2 * i + 1] = take(2 * in[i] * out[i]); }
   }
   v.total = off;
   return v;
@@ -1092,20 +1095,20 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
   };
   // One linear layer y = a W^T + b, a [M, Kp] kept in the storage type, W [Np, Kp], with dL/dy = dy (act'(u) dy when u is given): dW = dy^T a, db = column
   // sums, da = dy W.  The layer's outputs may be up to three equal blocks with weights and biases of their own (W's rows in one piece).
-  auto linear_backward = [&](float* dy, const float* u, int Np, const void* W, int Kp, const void* a, int blocks, const int* wi, const int* bi, float* da) -> zgr_status {
+  auto linear_backward = [&](float* dy, const float* u, int Np, const void* W, int Kp, const void* a, int blocks, const int* wi, const int* bi, float* da, int which) -> zgr_status {
     float* db[3] = {};
     for (int p = 0; p < blocks; ++p) db[p] = grads[bi[p]];
     const int n = Np / blocks;
     if (on_bf16(Np, Kp)) {
       unsigned char* tC = ws + v.tC;
       HIP_TRY(c, launch_bw_gradient_operands(dy, u, relu, M, Np, tC, ws + v.tA, db, blocks, sums, s));
-      HIP_TRY(c, launch_bw_transpose_bf16(a, M, Kp, Kp, ws + v.tB, M, s));
+      const void* aT = ws + v.tL[2 * which];                  // a and W transposed, written at the start of the block
+      const void* wT = ws + v.tL[2 * which + 1];
       bool whole = true;                                 // the blocks' weight gradients in one piece: one product
       for (int p = 1; p < blocks; ++p) whole = whole && grads[wi[p]] == grads[wi[0]] + (size_t)p * n * Kp;
       for (int p = 0; p < (whole ? 1 : blocks); ++p)
-        HIP_TRY(c, launch_gemm(ZGR_BF16, tC + (size_t)p * n * M * 2, ws + v.tB, nullptr, grads[wi[p]], EPI_F32, whole ? Np : n, Kp, M, s));
-      HIP_TRY(c, launch_bw_transpose_bf16(W, Np, Kp, Kp, ws + v.tW, Np, s));
-      HIP_TRY(c, launch_gemm(ZGR_BF16, ws + v.tA, ws + v.tW, nullptr, da, EPI_F32, M, Kp, Np, s));
+        HIP_TRY(c, launch_gemm(ZGR_BF16, tC + (size_t)p * n * M * 2, aT, nullptr, grads[wi[p]], EPI_F32, whole ? Np : n, Kp, M, s));
+      HIP_TRY(c, launch_gemm(ZGR_BF16, ws + v.tA, wT, nullptr, da, EPI_F32, M, Kp, Np, s));
     } else {
       if (u) HIP_TRY(c, launch_bw_act(relu, u, dy, (int64_t)M * Np, s));
       bool whole = true;                                 // the blocks' gradients in one piece, weights and biases: one product
@@ -1201,12 +1204,22 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
     const BwCarve::PerLayer& W = v.layer[l];
     float* dff = F(v.dff);
     float* dqkv = F(v.dqkv);
+    {
+      const struct { int Np, Kp; const void* W; const void* a; } lin[4] = {{d, ff, T(c, L.w2), ws + W.f}, {ff, d, T(c, L.w1), ws + W.h2}, {d, d, T(c, L.wo), ws + W.ctx}, {3 * d, d, T(c, L.wq), ws + W.h1}};
+      TransposeJobs jobs;
+      for (int i = 0; i < 4; ++i) {
+        if (!on_bf16(lin[i].Np, lin[i].Kp)) continue;
+        jobs.job[jobs.count++] = TransposeJob{lin[i].a, ws + v.tL[2 * i], M, lin[i].Kp};
+        jobs.job[jobs.count++] = TransposeJob{lin[i].W, ws + v.tL[2 * i + 1], lin[i].Np, lin[i].Kp};
+      }
+      HIP_TRY(c, launch_bw_transposes_bf16(jobs, s));
+    }
     // post-LN: x_out = LN2(y2), dx <- dL/dy2
     if (m.post_ln) HIP_TRY(c, launch_bw_layernorm(dt, F(W.y2), T(c, L.ln2_g), dx, nullptr, dx, F(v.stats), grads[L.ln2_g], grads[L.ln2_b], sums, M, d, m.ln_eps, s));
     // x_out (or y2) = x_mid (or x1n) + f W2^T + b2
-    if ((st = linear_backward(dx, nullptr, d, T(c, L.w2), ff, ws + W.f, 1, &L.w2, &L.b2, dff)) != ZGR_OK) return st;
+    if ((st = linear_backward(dx, nullptr, d, T(c, L.w2), ff, ws + W.f, 1, &L.w2, &L.b2, dff, 0)) != ZGR_OK) return st;
     // f = act(u), u = h2 W1^T + b1
-    if ((st = linear_backward(dff, F(W.u), ff, T(c, L.w1), d, ws + W.h2, 1, &L.w1, &L.b1, dtb)) != ZGR_OK) return st;
+    if ((st = linear_backward(dff, F(W.u), ff, T(c, L.w1), d, ws + W.h2, 1, &L.w1, &L.b1, dtb, 1)) != ZGR_OK) return st;
     if (m.post_ln) {
       // h2 = x1n = LN1(y1): dL/dx1n = dx + dh2, then dx <- dL/dy1
       HIP_TRY(c, launch_bw_add(dtb, dx, nx, s));
@@ -1216,11 +1229,11 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
       HIP_TRY(c, launch_bw_layernorm(dt, F(W.xmid), T(c, L.ln2_g), dtb, dx, dx, F(v.stats), grads[L.ln2_g], grads[L.ln2_b], sums, M, d, m.ln_eps, s));
     }
     // x_mid (or y1) = x_in + ctx Wo^T + bo
-    if ((st = linear_backward(dx, nullptr, d, T(c, L.wo), d, ws + W.ctx, 1, &L.wo, &L.bo, dtb)) != ZGR_OK) return st;
+    if ((st = linear_backward(dx, nullptr, d, T(c, L.wo), d, ws + W.ctx, 1, &L.wo, &L.bo, dtb, 2)) != ZGR_OK) return st;
     HIP_TRY(c, launch_bw_attention(dt, ws + W.qkv, dtb, lengths, B, Tn, d, H, lm ? 1 : 0, F(v.P), F(v.dS), dqkv, s));
     // q, k, v = h1 W{q,k,v}^T + b{q,k,v}: three column blocks of dqkv; Wq, Wk, Wv are adjacent, one [3 d, d] matrix
     const int wi[3] = {L.wq, L.wk, L.wv}, bi[3] = {L.bq, L.bk, L.bv};
-    if ((st = linear_backward(dqkv, nullptr, 3 * d, T(c, L.wq), d, ws + W.h1, 3, wi, bi, dtb)) != ZGR_OK) return st;
+    if ((st = linear_backward(dqkv, nullptr, 3 * d, T(c, L.wq), d, ws + W.h1, 3, wi, bi, dtb, 3)) != ZGR_OK) return st;
     if (m.post_ln) HIP_TRY(c, launch_bw_add(dx, dtb, nx, s));                                    // h1 = x_in
     else HIP_TRY(c, launch_bw_layernorm(dt, F(W.xin), T(c, L.ln1_g), dtb, dx, dx, F(v.stats), grads[L.ln1_g], grads[L.ln1_b], sums, M, d, m.ln_eps, s));
   }

@@ -29,6 +29,11 @@ class SumQueue {
 // bf16 operands for the matrix-core products: out [cols, rows] (row stride ld_out, a multiple of 64) = in [rows, cols]^T in bf16 (row
 // stride ld_in, a multiple of 4), zeros between rows and ld_out
 hipError_t launch_bw_transpose_bf16(const void* in, int rows, int cols, int64_t ld_in, void* out, int64_t ld_out, hipStream_t s);
+// several whole matrices at once, in [rows, cols] and out [cols, rows] (rows and cols multiples of 64)
+constexpr int kTransposeJobs = 8;
+struct TransposeJob { const void* in; void* out; int rows, cols; };
+struct TransposeJobs { TransposeJob job[kTransposeJobs]; int count = 0; };
+hipError_t launch_bw_transposes_bf16(const TransposeJobs& jobs, hipStream_t s);
 // a gradient dy [M, N] (both multiples of 64) as both operands, cols_out [N, M] and rows_out [M, N] in bf16, and its column sums: dbias[i] gets
 // those of the i-th of n_bias equal column blocks.  With u != NULL it is dy act'(u) that is taken.
 hipError_t launch_bw_gradient_operands(const float* dy, const float* u, int relu, int M, int N, void* cols_out, void* rows_out, float* const* dbias, int n_bias, SumQueue& sums, hipStream_t s);
