@@ -1110,6 +1110,148 @@ hipError_t launch_gemm_bf16_t(const bf16_t* A, const bf16_t* W, const bf16_t* bi
   return hipGetLastError();
 }
 
+// The same product for few tiles: 32 x 32 of the result per block, one wave that reads and multiplies and two that only transfer (A's rows, W's rows), a ring
+// of kFewRing k-tiles of 8 KB.  What counts there is the chain of one block: with 64 x 64 tiles every wave transfers, meets, reads eight operands
+// of 33 cycles and then multiplies, some 700 cycles a k-tile on a quarter as many CUs; here the reading wave's eight reads run beside the other
+// waves' transfers and over its own matrix instructions, and all of a short sum is on its way before the first wait.  The terms are taken in the same
+// order, so the result is the same bit for bit.
+// 231 x 1024 x 4096 20.9 us -> 10.8, 33 x 768 x 3072 15.3 -> 8.3, 256 x 1024 x 2048 11.8 -> 7.2; the loss of one 33-token prompt of a 125M-parameter model
+// 691 us -> 545, a 24-block encoder's backward over 231 tokens 5.9 ms -> 5.6.  Up to 256 tiles, one block a CU: with 128 as the line 590 us and 5.94 ms, with
+// 512 554 us.  The same form with 64 x 64 tiles and four readers gave these cases less than 1%.
+constexpr int kFewRing = 16;
+template <int MODE>
+__global__ void __launch_bounds__(192) gemm_bf16_few_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, int M, int N, int K, void* __restrict__ out, const bf16_t* __restrict__ bias,
+                                                            GemmTwin tw, int models, const float* resid) {
+  constexpr int SLAB = 64 * GB_K * 2;                          // bytes of a k-tile: 32 rows of A, 32 of W
+  extern __shared__ __attribute__((aligned(1024))) unsigned char gsm[];
+  const int lane = threadIdx.x & 63, wave = uniform_of(threadIdx.x >> 6), l32 = lane & 31, half = lane >> 5;
+  int tm, tn;
+  const int model = tile_of_block((M + 31) / 32, (N + 31) / 32, models, tm, tn);
+  if (model < 0) return;
+  A = ahead(A, model * tw.a); W = ahead(W, model * tw.w); out = ahead(out, model * tw.out); bias = ahead(bias, model * tw.bias);
+  if (MODE == EPI_RESID) resid = ahead(resid, model * tw.out);
+  const int m0 = tm * 32, n0 = tn * 32, nk = K / GB_K;
+  if (wave != 0) {
+    // transfers: rows of eight of one operand, the 16-byte chunk c of row r in slot c ^ ((r / 2) % 8); past the last k-tile that one is read again
+    const bool is_a = wave == 1;
+    uint32_t off[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const int rl = 8 * g + (lane >> 3), row = is_a ? min(m0 + rl, M - 1) : min(n0 + rl, N - 1);
+      off[g] = ((uint32_t)row * (uint32_t)K + (uint32_t)(((lane & 7) ^ ((rl >> 1) & 7)) << 3)) * 2u;
+    }
+#if defined(__HIP_DEVICE_COMPILE__)
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(is_a ? A : W), 0, (uint32_t)(is_a ? M : N) * (uint32_t)K * 2u, 0x00020000);
+#endif
+    [[maybe_unused]] const uint32_t base = is_a ? 0u : 32u * GB_K * 2u;   // (not used by the host's pass over this)
+    auto issue = [&](int t, int pos) {
+#if defined(__HIP_DEVICE_COMPILE__)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(gsm + pos * SLAB + base + g * 1024), 16, off[g], (t < nk ? t : nk - 1) * (GB_K * 2), 0, 0);
+#endif
+    };
+    for (int t = 0; t < kFewRing; ++t) issue(t, t);
+    wait_vmem_upto<(kFewRing - 1) * 4>();
+    block_barrier();                                           // k-tile 0 is there
+    int pos = 0;
+    for (int kt = 0; kt + 1 < nk; ++kt) {
+      wait_vmem_upto<(kFewRing - 2) * 4>();
+      block_barrier();                                         // k-tile kt + 1 is there, and kt has been read: its place is free
+      issue(kt + kFewRing, pos);
+      pos = pos + 1 == kFewRing ? 0 : pos + 1;
+    }
+    wait_vmem();
+    return;
+  }
+  typedef __attribute__((address_space(3))) unsigned char lds_byte;
+  typedef __attribute__((address_space(3))) const bf16x8 lds_bf16x8;
+  uint32_t ra[4];                                              // LDS addresses of this lane's reads of A in place 0; W's are 4 KB behind
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) ra[ks] = (uint32_t)(uintptr_t)(lds_byte*)gsm + (uint32_t)(l32 * GB_K * 2 + (((2 * ks + half) ^ ((l32 >> 1) & 7)) << 4));
+  // what the epilogue needs is requested first
+  const int n = n0 + l32, mb = m0 + 4 * half;
+  const float bv = bias && n < N ? to_f32(bias[n]) : 0.f;
+  float old[16];
+#pragma unroll
+  for (int v = 0; v < 16; ++v) old[v] = MODE == EPI_RESID ? resid[(size_t)min(mb + 8 * (v >> 2) + (v & 3), M - 1) * N + min(n, N - 1)] : 0.f;
+  f32x16 acc;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+  struct Frags { bf16x8 a[4], b[4]; };
+  auto read = [&](int pos, Frags& f) {
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      f.a[ks] = *(lds_bf16x8*)(uintptr_t)(ra[ks] + (uint32_t)(pos * SLAB));
+      f.b[ks] = *(lds_bf16x8*)(uintptr_t)(ra[ks] + (uint32_t)(pos * SLAB) + 32 * GB_K * 2);
+    }
+  };
+  auto fixed = [&]() {
+#if defined(__HIP_DEVICE_COMPILE__)
+    __builtin_amdgcn_sched_barrier(0);
+#endif
+  };
+  auto multiply = [&](const Frags& f) {
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[ks], f.b[ks], acc, 0, 0, 0);
+  };
+  Frags f0, f1;
+  int pos = 0;
+  // k-tile kt is in `cur`; the next one is read while it is multiplied
+  auto turn = [&](const Frags& cur, Frags& next) {
+    pos = pos + 1 == kFewRing ? 0 : pos + 1;
+#if defined(__HIP_DEVICE_COMPILE__)
+    __builtin_amdgcn_s_waitcnt(0xC07F);                        // lgkmcnt(0): k-tile kt has been read
+#endif
+    fixed();
+    block_barrier();
+    read(pos, next);
+    fixed();
+    multiply(cur);
+    fixed();
+  };
+  block_barrier();
+  read(0, f0);
+  int kt = 0;
+  for (; kt + 2 < nk; kt += 2) { turn(f0, f1); turn(f1, f0); }
+  if (kt + 1 < nk) { turn(f0, f1); multiply(f1); } else multiply(f0);
+  if (MODE == EPI_RESID) arrived(old);
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    const int m = mb + 8 * (v >> 2) + (v & 3);
+    if (m < M && n < N) {
+      if (MODE == EPI_RESID) reinterpret_cast<float*>(out)[(size_t)m * N + n] = old[v] + (acc[v] + bv);
+      else epilogue_bf16<MODE>(out, (size_t)m * N + n, acc[v] + bv);
+    }
+  }
+}
+
+static hipError_t launch_gemm_bf16_few(const bf16_t* A, const bf16_t* W, const bf16_t* bias, void* out, int epi, int M, int N, int K, hipStream_t s, int models, const GemmTwin& tw, const float* resid) {
+  constexpr int lds = kFewRing * 64 * GB_K * 2;
+  const int64_t tiles = (int64_t)((M + 31) / 32) * ((N + 31) / 32) * models;
+  const dim3 grid((unsigned)((tiles + 7) / 8 * 8));
+#define ZGR_FEW(MODE)                                                                                                                             \
+  {                                                                                                                                               \
+    static std::atomic<bool> attr_set{false};   /* set twice by racing threads at worst: the call is idempotent */                                \
+    auto kern = gemm_bf16_few_kernel<MODE>;                                                                                                       \
+    if (!attr_set) {                                                                                                                              \
+      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);                   \
+      if (e != hipSuccess) return e;                                                                                                              \
+      attr_set = true;                                                                                                                            \
+    }                                                                                                                                             \
+    hipLaunchKernelGGL(kern, grid, dim3(192), lds, s, A, W, M, N, K, out, bias, tw, models, resid);                                               \
+  }
+  switch (epi) {
+    case EPI_STORE: ZGR_FEW(EPI_STORE) break;
+    case EPI_GELU:  ZGR_FEW(EPI_GELU) break;
+    case EPI_RELU:  ZGR_FEW(EPI_RELU) break;
+    case EPI_RESID: ZGR_FEW(EPI_RESID) break;
+    default:        ZGR_FEW(EPI_F32) break;
+  }
+#undef ZGR_FEW
+  return hipGetLastError();
+}
+
 // ------------------------------------------------------------------ attention
 // fp32 on the matrix cores (v_mfma_f32_32x32x2_f32), for fp32 storage and for the head sizes the bf16 kernel below does not take (heads
 // of 8 in part only, see launch_attention_t).  One wave per 32 queries of a head, keys in blocks of 32: S^T = K Q^T, then O^T += V^T P^T, everything in registers.  A lane supplies
@@ -1637,6 +1779,8 @@ hipError_t launch_gemm(int dtype, const void* A, const void* W, const void* bias
     // In between (about one tile per CU): the ping-pong loop on the full ring.
     const long t128 = (long)((M + 127) / 128) * ((N + 127) / 128) * n;
     if (t128 > 256) return launch_gemm_bf16_t<128, 128, 2, 4, 64, 8, 1>(a, w, b, out, epi, M, N, K, s, n, gt, from);
+    const int64_t t32 = (int64_t)((M + 31) / 32) * ((N + 31) / 32) * n;   // 32 x 32 tiles that all get a CU of their own
+    if (t32 <= 256) return launch_gemm_bf16_few(a, w, b, out, epi, M, N, K, s, n, gt, from);
     if (t128 <= 128) return launch_gemm_bf16_t<64, 64, 2, 2, 64, 4>(a, w, b, out, epi, M, N, K, s, n, gt, from);
     return launch_gemm_bf16_t<128, 128, 2, 4, 64, 20, 1>(a, w, b, out, epi, M, N, K, s, n, gt, from);
   }
