@@ -925,7 +925,7 @@ zgr_status zgr_cloud_basis(const float* const* snapshots, int32_t n_snap, int64_
   // Q = orth(sum_t G_t Omega)
   for (int t = 0; t < n_snap; t += kCloudSnaps)
     HIP_TRY(nullptr, launch_cloud_g_t_all(batch_of(t), in_batch(t), rows, cols, omega, 0, k, Q, t > 0, part, part_floats, s));
-  HIP_TRY(nullptr, launch_cloud_orth(Q, rows, k, dep, orth, s));
+  HIP_TRY(nullptr, launch_cloud_orth(Q, rows, k, n_iter == 0, dep, orth, s));
   // sweeps Q <- orth(sum_t G_t (G_t^T Q))
   for (int it = 0; it < n_iter; ++it) {
     for (int t = 0; t < n_snap; t += kCloudSnaps) {
@@ -933,7 +933,7 @@ zgr_status zgr_cloud_basis(const float* const* snapshots, int32_t n_snap, int64_
       HIP_TRY(nullptr, launch_cloud_g_t_all(batch_of(t), in_batch(t), rows, cols, T, cols * k, k, Y, t > 0, part, part_floats, s));
     }
     float* tmp = Q; Q = Y; Y = tmp;
-    HIP_TRY(nullptr, launch_cloud_orth(Q, rows, k, dep, orth, s));
+    HIP_TRY(nullptr, launch_cloud_orth(Q, rows, k, it + 1 == n_iter, dep, orth, s));
   }
   HIP_TRY(nullptr, launch_cloud_copy_basis(Q, rows, k, U, ldu, s));
   if (dependent_out) {

@@ -114,7 +114,7 @@ hipError_t launch_cloud_gt_q_all(const CloudSnaps& g, int n_snap, int64_t rows, 
 hipError_t launch_cloud_g_t_all(const CloudSnaps& g, int n_snap, int64_t rows, int64_t cols, const float* T, int64_t t_snap, int k, float* Y, int accumulate, float* part, int64_t part_floats,
                                 hipStream_t s);
 // scratch: (2 min(ceil(rows / 64), 128) + 3) k^2 doubles
-hipError_t launch_cloud_orth(float* Y, int64_t rows, int k, int* dependent, double* scratch, hipStream_t s);
+hipError_t launch_cloud_orth(float* Y, int64_t rows, int k, bool last, int* dependent, double* scratch, hipStream_t s);
 hipError_t launch_cloud_copy_basis(const float* Q, int64_t rows, int k, float* U, int ldu, hipStream_t s);
 hipError_t launch_cloud_residual(float* R, const float* Y, int64_t n, hipStream_t s);
 
