@@ -1430,27 +1430,38 @@ __global__ void __launch_bounds__(256) attention_kernel(const T* __restrict__ qk
   }
 }
 
-// MFMA attention for bf16 storage and head size 64.  One block = 128 queries of one (batch, head):
-// K [keys][64] and V^T [64][keys] are staged in LDS (all keys at once up to AT_KCH of them, chunk after chunk of
-// AT_KCH beyond: the online softmax carries over); each wave owns 32 queries and walks the keys in
-// blocks of 32, computing S^T = K Q^T and O^T += V^T P^T with v_mfma_f32_32x32x16_bf16.  In the S^T
+// MFMA attention for bf16 storage and head size 64.  One block = 32 NW queries of one (batch, head), 32 per wave; the keys come in stages
+// through two LDS buffers: the next stage's K and V rows are on their way to registers while this one's are multiplied, one barrier a stage.
+// A wave walks the keys in blocks of 32, computing S^T = K Q^T and O^T += V^T P^T with v_mfma_f32_32x32x16_bf16.  In the S^T
 // result a lane holds one query column and 16 keys in registers, so the softmax reductions run over
 // registers plus one exchange with the partner lane (lane ^ 32); P goes straight from the accumulator
 // registers into the B operand of the second product (the contraction order of that product is the
-// accumulator's key order, which the V^T operand is read in as well).
+// accumulator's key order, which the V^T operand is read in as well).  V stays in rows: ds_read_b64_tr_b16 hands 16 lanes the columns of a
+// 4 x 16 piece.  Bound by the vector unit (exponentials, masks) on long sequences, by the transfer of q, k, v on short ones.
+// 128 heads at 2047 tokens 165 -> 119 us (512 keys staged at a time, V transposed by 2-byte stores, no load under the products), 96 heads at 513 tokens
+// 20.5 -> 17.4, 512 heads at 256 tokens 20.7 -> 19.0, 384 at 128 tokens 10.6 -> 9.1; the results keep their bits.  Stages of 128 keys under eight
+// waves: with 64 the two stages that are requested ahead are half of a 256-token sequence (46.5 us for 2048 heads, 42.2 with all its keys).
 constexpr int AT_LDK = 64 + 8;          // K row stride (bf16): 144 B
-constexpr int AT_KCH = 512;             // keys staged at a time: 72 KB of K rows + 65 KB of V^T
-// NW waves per block, 32 queries each: with NW = 8 one block covers 256 queries of a head, so K and V^T of a
+typedef short i16x4 __attribute__((ext_vector_type(4)));
+// columns of a piece of 4 rows of 16 entries: lane i of 16 supplies where entries 4 (i % 4) .. + 4 of row i / 4 lie and receives entry i of each row
+__device__ __forceinline__ uint2 lds_columns(const bf16_t* p) {
+  return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)const_cast<bf16_t*>(p)));
+}
+// the larger of a lane's value and its partner's (lane ^ 32)
+__device__ __forceinline__ float max_of_halves(float v) {
+  const auto w = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(w[0]), __uint_as_float(w[1]));
+}
+// NW waves per block, 32 queries each: with NW = 8 one block covers 256 queries of a head, so K and V of a
 // 256-token sequence are staged once per head instead of once per 128 queries.
 template <int DH, int NW>
-__global__ void __launch_bounds__(64 * NW) attention_mfma_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ ctx, const int32_t* __restrict__ lengths,
-                                                                 int seq, int d, int n_head, int causal, int kpad, int n_len) {
+__global__ void __launch_bounds__(64 * NW, 4) attention_mfma_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ ctx, const int32_t* __restrict__ lengths,
+                                                                    int seq, int d, int n_head, int causal, int n_len) {
   static_assert(DH == 64, "head size 64");
   constexpr int QB = 32 * NW, NT = 64 * NW;                     // queries and threads per block
-  extern __shared__ __attribute__((aligned(16))) unsigned char asm_[];
-  bf16_t* Ks = reinterpret_cast<bf16_t*>(asm_);                 // [kpad][AT_LDK]
-  bf16_t* Vt = Ks + (size_t)kpad * AT_LDK;                      // [DH][kpad + 8]
-  const int ldv = kpad + 8;
+  constexpr int AT_KEYS = 16 * NW, PER = AT_KEYS * 8 / NT;      // keys of a stage, 16-byte pieces of its K (and V) per thread
+  __shared__ __attribute__((aligned(16))) bf16_t Ks[2][AT_KEYS * AT_LDK];
+  __shared__ __attribute__((aligned(16))) bf16_t Vs[2][AT_KEYS * DH];      // row r's halves are exchanged where r / 2 is odd: four rows of 16 entries then lie in 64 different banks
   const int qblocks = (seq + QB - 1) / QB;
   // Under the causal mask a query block's work grows with its position: the blocks are handed out longest first (all heads'
   // last query blocks, then the ones before, ...), so that the short ones fill the gaps at the end of the launch.
@@ -1475,9 +1486,7 @@ __global__ void __launch_bounds__(64 * NW) attention_mfma_kernel(const bf16_t* _
   bf16x8 qf[DH / 16];
 #pragma unroll
   for (int s4 = 0; s4 < DH / 16; ++s4) {
-    uint4 t = make_uint4(0, 0, 0, 0);
-    if (qi < seq) t = *reinterpret_cast<const uint4*>(base + (size_t)qi * ld + s4 * 16 + half * 8);
-    qf[s4] = *reinterpret_cast<bf16x8*>(&t);
+    qf[s4] = *reinterpret_cast<const bf16x8*>(base + (size_t)min(qi, seq - 1) * ld + s4 * 16 + half * 8);
   }
   f32x16 o[DH / 32];
 #pragma unroll
@@ -1489,31 +1498,47 @@ __global__ void __launch_bounds__(64 * NW) attention_mfma_kernel(const bf16_t* _
   int wave_kblocks = kblocks;
   if (causal) wave_kblocks = min(kblocks, (q0 + 31) / 32 + 1);
   if (q0 >= seq) wave_kblocks = 0;
-  for (int c0 = 0; c0 < kblocks; c0 += AT_KCH / 32) {                 // key chunks: the same trip count for every wave of the block
-    const int c_end = min(kblocks, c0 + AT_KCH / 32);
-    if (c0 > 0) __syncthreads();                                         // every wave is done with the previous chunk
-    // stage K and V^T of key blocks [c0, c_end) (zero beyond seq so masked products stay finite)
-    for (int i = tid; i < (c_end - c0) * 32 * 8; i += NT) {
-      const int r = i >> 3, c = (i & 7) * 8, key = c0 * 32 + r;
-      uint4 kv = make_uint4(0, 0, 0, 0), vv = make_uint4(0, 0, 0, 0);
-      if (key < seq) {
-        kv = *reinterpret_cast<const uint4*>(base + (size_t)key * ld + d + c);
-        vv = *reinterpret_cast<const uint4*>(base + (size_t)key * ld + 2 * d + c);
-      }
-      *reinterpret_cast<uint4*>(Ks + r * AT_LDK + c) = kv;
-      const uint16_t* ve = reinterpret_cast<const uint16_t*>(&vv);
+  struct Pieces { planes_u32x4 k[PER], v[PER]; };
+  auto request = [&](Pieces& t, int stage) {                            // without branches: the waits for these loads are then counted; beyond seq the last row again (masked)
 #pragma unroll
-      for (int j = 0; j < 8; ++j) Vt[(c + j) * ldv + r].bits = ve[j];
+    for (int p = 0; p < PER; ++p) {
+      const int i = tid + p * NT, key = min(stage * AT_KEYS + (i >> 3), seq - 1);
+      const bf16_t* row = base + (size_t)key * ld + d + (i & 7) * 8;
+      t.k[p] = *reinterpret_cast<const planes_u32x4*>(row);
+      t.v[p] = *reinterpret_cast<const planes_u32x4*>(row + d);
     }
-    __syncthreads();
-    for (int kb = c0; kb < min(c_end, wave_kblocks); ++kb) {
-      const int kl = (kb - c0) * 32;                                      // the block's first key within the staged chunk
+  };
+  auto put = [&](const Pieces& t, int buf) {
+#pragma unroll
+    for (int p = 0; p < PER; ++p) {
+      const int i = tid + p * NT, r = i >> 3, c = (i & 7) * 8;
+      *reinterpret_cast<planes_u32x4*>(Ks[buf] + r * AT_LDK + c) = t.k[p];
+      *reinterpret_cast<planes_u32x4*>(Vs[buf] + r * DH + (c ^ ((r & 2) << 4))) = t.v[p];
+    }
+  };
+  const int i16 = lane & 15, v_row = ((i16 >> 2) + 4 * half) * DH + (lane & 16) + 4 * (i16 & 3), v_swap = (i16 & 8) << 2;
+  const int stages = max(1, (kblocks * 32 + AT_KEYS - 1) / AT_KEYS);    // the same for every wave of the block; one that no wave needs where no key is visible, so that no path leaves q's loads pending
+  // The first two stages are requested together (the second may be past the last one: its rows are not used); from then on the one after next is
+  // requested as soon as the one before it lies in LDS.
+  Pieces next;
+  {
+    Pieces first;
+    request(first, 0);
+    request(next, 1);
+    put(first, 0);
+  }
+  __syncthreads();
+  for (int st = 0; st < stages; ++st) {
+    const bf16_t* K = Ks[st & 1];
+    const bf16_t* V = Vs[st & 1] + v_row;
+    for (int kb = st * (AT_KEYS / 32); kb < min((st + 1) * (AT_KEYS / 32), wave_kblocks); ++kb) {
+      const int kl = kb * 32 - st * AT_KEYS;                              // the block's first key within the stage
       f32x16 sacc;
 #pragma unroll
       for (int v = 0; v < 16; ++v) sacc[v] = 0.f;
 #pragma unroll
       for (int s4 = 0; s4 < DH / 16; ++s4) {
-        const bf16x8 kf = *reinterpret_cast<const bf16x8*>(Ks + (kl + l32) * AT_LDK + s4 * 16 + half * 8);
+        const bf16x8 kf = *reinterpret_cast<const bf16x8*>(K + (kl + l32) * AT_LDK + s4 * 16 + half * 8);
         sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[s4], sacc, 0, 0, 0);
       }
       // lane: query qi, keys kb*32 + 8*(v/4) + 4*half + v%4; scores in log2 units
@@ -1530,7 +1555,7 @@ __global__ void __launch_bounds__(64 * NW) attention_mfma_kernel(const bf16_t* _
           mloc = fmaxf(mloc, sv[v]);
         }
       }
-      mloc = fmaxf(mloc, __shfl_xor(mloc, 32, 64));
+      mloc = max_of_halves(mloc);
       const float mnew = fmaxf(mx, mloc);
       const float msafe = mnew == -INFINITY ? 0.f : mnew;
       // v_exp_f32 directly: the arguments are <= 0 (or -inf, which gives 0), so the library routine's range handling is not needed
@@ -1557,16 +1582,20 @@ __global__ void __launch_bounds__(64 * NW) attention_mfma_kernel(const bf16_t* _
       }
       // O^T += V^T P^T: A operand lane (dh row 32 f + l32, half) reads the keys in the accumulator's order
 #pragma unroll
-      for (int st = 0; st < 2; ++st) {
+      for (int ks = 0; ks < 2; ++ks) {
 #pragma unroll
         for (int f = 0; f < DH / 32; ++f) {
-          const bf16_t* vr = Vt + (f * 32 + l32) * ldv + kl + st * 16 + 4 * half;
-          const uint2 lo = *reinterpret_cast<const uint2*>(vr), hi = *reinterpret_cast<const uint2*>(vr + 8);
+          const bf16_t* vr = V + (kl + ks * 16) * DH + ((f * 32) ^ v_swap);
+          const uint2 lo = lds_columns(vr), hi = lds_columns(vr + 8 * DH);
           uint4 t = make_uint4(lo.x, lo.y, hi.x, hi.y);
-          o[f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<bf16x8*>(&t), pf[st], o[f], 0, 0, 0);
+          o[f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<bf16x8*>(&t), pf[ks], o[f], 0, 0, 0);
         }
       }
     }
+    if (st + 1 == stages) break;
+    put(next, (st + 1) & 1);                        // its readers of two stages ago are behind the last barrier
+    request(next, st + 2);
+    __syncthreads();
   }
   lsum += __shfl_xor(lsum, 32, 64);
   if (qi < seq) {
@@ -1848,22 +1877,12 @@ static hipError_t launch_attention_t(const T* qkv, T* ctx, const int32_t* length
 
 hipError_t launch_attention(int dtype, const void* qkv, void* ctx, const int32_t* lengths, int batch, int seq, int d, int n_head, int causal, hipStream_t s, bool keep_order, int models) {
   if (dtype == 1 && d / n_head == 64 && d % 8 == 0) {
-    const int kpad = seq < AT_KCH ? (seq + 31) / 32 * 32 : AT_KCH;          // keys resident in LDS at a time
-    const size_t lds = sizeof(bf16_t) * ((size_t)kpad * AT_LDK + (size_t)64 * (kpad + 8));
-    static std::atomic<bool> attr_set{false};     // set twice by racing threads at worst: the calls are idempotent
-    if (!attr_set) {
-      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(attention_mfma_kernel<64, 4>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-      if (e != hipSuccess) return e;
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(attention_mfma_kernel<64, 8>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-      if (e != hipSuccess) return e;
-      attr_set = true;
-    }
     if (seq > 128) {      // 256 queries per block: the keys of a head are staged once per 256 queries
       const int grid = batch * models * n_head * ((seq + 255) / 256);
-      hipLaunchKernelGGL((attention_mfma_kernel<64, 8>), dim3(grid), dim3(512), lds, s, (const bf16_t*)qkv, (bf16_t*)ctx, lengths, seq, d, n_head, causal, kpad, batch);
+      hipLaunchKernelGGL((attention_mfma_kernel<64, 8>), dim3(grid), dim3(512), 0, s, (const bf16_t*)qkv, (bf16_t*)ctx, lengths, seq, d, n_head, causal, batch);
     } else {
       const int grid = batch * models * n_head * ((seq + 127) / 128);
-      hipLaunchKernelGGL((attention_mfma_kernel<64, 4>), dim3(grid), dim3(256), lds, s, (const bf16_t*)qkv, (bf16_t*)ctx, lengths, seq, d, n_head, causal, kpad, batch);
+      hipLaunchKernelGGL((attention_mfma_kernel<64, 4>), dim3(grid), dim3(256), 0, s, (const bf16_t*)qkv, (bf16_t*)ctx, lengths, seq, d, n_head, causal, batch);
     }
     return hipGetLastError();
   }

@@ -56,6 +56,13 @@ def test_encoder_rows_with_lengths_inside_and_at_the_edges_of_key_blocks(dtype, 
     _check_row_losses(_model(I.ARCH_ENCODER_CLS, dtype, head, len(lengths), seq), lengths)
 
 
+@pytest.mark.parametrize("seq", [2, 33, 63, 64, 65, 127, 128, 129, 160, 255, 256, 257, 384, 385])
+@pytest.mark.parametrize("arch", [I.ARCH_DECODER_LM, I.ARCH_ENCODER_CLS], ids=["decoder", "encoder"])
+def test_heads_of_64_in_bf16_at_the_edges_of_the_key_stages(arch, seq):
+    """Keys arrive in stages of 64 (up to 128 tokens) or 128: sequences and padding lengths that end inside, at and just behind one."""
+    _check_row_losses(_model(arch, "bf16", 64, 4, seq), [max(1, seq // 2), max(1, min(seq, 64)), max(1, seq - 1), seq] if arch == I.ARCH_ENCODER_CLS else None)
+
+
 @pytest.mark.parametrize("arch", [I.ARCH_DECODER_LM, I.ARCH_ENCODER_CLS], ids=["decoder", "encoder"])
 @pytest.mark.parametrize("act,post_ln", [("gelu", False), ("relu", True)])
 @pytest.mark.parametrize("batch,seq,d_ff", [(1, 29, 2048), (3, 21, 2052), (2, 64, 4096)])

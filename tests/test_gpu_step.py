@@ -23,8 +23,8 @@ SMALL_BF16_LM = I.shrink(I.CONFIGS["cfg3"], name="small_bf16_lm", n_layer=2, d_m
                          max_pos=64, batch=3, seq=40, k=16, k_full=16)
 SMALL_BF16_CLS = I.shrink(I.CONFIGS["cfg4"], name="small_bf16_cls", n_layer=2, d_model=128, n_head=2, d_ff=192, vocab=777,
                           max_pos=64, batch=5, seq=33, k=32, k_full=32)
-# sequences past the 512 keys the matrix-core attention kernel holds in LDS at a time: three key chunks with a ragged last one
-# (decoder, causal), two chunks with padded sequences that end in the first or the second (encoder)
+# sequences of many of the 128-key stages of the matrix-core attention kernel: nine with a ragged last one
+# (decoder, causal), six with padded sequences that end in one of them (encoder)
 LONG_BF16_LM = I.shrink(SMALL_BF16_LM, name="long_bf16_lm", max_pos=1100, batch=1, seq=1100)
 LONG_BF16_CLS = I.shrink(SMALL_BF16_CLS, name="long_bf16_cls", max_pos=700, batch=4, seq=700)
 # the two model families of the paper's experiments: ReLU feed-forward (decoder), post-LayerNorm blocks (encoder), and both
