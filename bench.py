@@ -3,8 +3,9 @@
 
 One step = the whole hot path on one synthetic batch already resident in HBM:
 perturb +eps Z, forward, perturb -2 eps Z, forward, restore +eps Z, form g,
-update theta <- theta - lr g Z (four streaming passes over all parameters and
-two forward passes).  Prints one JSON line with the throughput, the roofline
+update theta <- theta - lr g Z (two forward passes and two passes over all
+parameters: one writes both perturbed copies and the restored values, one
+updates; four in place where the workspace has no room for the copies).  Prints one JSON line with the throughput, the roofline
 of the dominant kernel (HIP-event timed inside the timed region) and the CPU
 oracle timed on a bounded sample of the same workload.
 """
@@ -329,23 +330,26 @@ def main():
         "last_losses": None if last is None else [last[0], last[1], last[2]],
         "setup_s": setup_s, "profiled_steps": profiled_steps,
     }
+    with_copies = sess.with_copies
     if prof:
         kern = {}
         for name, (ms, n) in prof.items():
             if n:
                 kern[name] = {"ms_total": ms, "launches": int(n), "ms_avg": ms / n}
         out["kernel_ms"] = kern
-        # perturbation pass over the guided matrices: read + write every element once, plus one read of U
+        # perturbation pass over the guided matrices, plus one read of U: read + write every element once; of a step's two launches
+        # with the copies one reads it once and writes it three times, which makes three transfers each on average
+        moves = 3.0 if with_copies else 2.0
         if "perturb_tile" in kern:
             k1 = kern["perturb_tile"]
-            bytes_per_launch = 2.0 * guided_elems * es + u_bytes
+            bytes_per_launch = moves * guided_elems * es + u_bytes
             gbs = bytes_per_launch / (k1["ms_avg"] * 1e-3) / 1e9
             out["roofline_perturb"] = {"bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": gbs / HBM_PEAK_GBS,
                                        "traffic": kernel_traffic(traffic, "perturb_tile"), "kernel": "perturb_tile_mfma_kernel" if cfg.k >= 16 else "perturb_tile_kernel",
                                        "bytes_per_launch": bytes_per_launch}
         if "perturb_flat" in kern:
             k1 = kern["perturb_flat"]
-            gbs = 2.0 * flat_elems * es / (k1["ms_avg"] * 1e-3) / 1e9
+            gbs = moves * flat_elems * es / (k1["ms_avg"] * 1e-3) / 1e9
             out["roofline_perturb_flat"] = {"bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": gbs / HBM_PEAK_GBS,
                                             "traffic": kernel_traffic(traffic, "perturb_flat"), "kernel": "perturb_flat_kernel"}
         # What really bounds the perturbation passes: vector-ALU issue.  Achieved = vector instructions executed (the
@@ -436,7 +440,7 @@ def main():
     sess.close()
     del sess, batch
     if not args.no_fused_line:
-        # the same step with the restoring pass and the update fused into one pass (3 instead of 4 passes over theta);
+        # the same step with the restoring pass and the update fused into one pass (that starts from the second copy where there is one);
         # reported beside the headline value, which keeps the client block and the edge-server update separate
         fs = make_session(cfg, specs, values, bases, bits=args.gauss_bits, fuse_lr=cfg.lr)
         fb = session_batch(fs, cfg, arrays)
@@ -449,7 +453,7 @@ def main():
         torch.cuda.synchronize()
         fe = time.perf_counter() - t0
         out["fused_restore_update"] = {"value": args.steps / fe, "unit": "steps/s", "ms_per_step": 1e3 * fe / args.steps,
-                                       "passes_over_parameters": 3}
+                                       "passes_over_parameters": 2 if with_copies else 3}
         fs.close()
         del fs, fb
     del values

@@ -77,6 +77,7 @@ class Session:
         larger = self.lib.zgr_workspace_bytes_copies(C.byref(self.model), self.table, len(self.params), max_batch, max_seq)
         if self.COPIES_SHARE > 0 and (larger - nbytes < 1 << 26 or larger - nbytes <= self.COPIES_SHARE * torch.cuda.mem_get_info(self.dev)[0]):
             nbytes = larger
+        self.with_copies = nbytes == larger
         self.workspace = torch.empty(nbytes, dtype=torch.uint8, device=self.dev)
         self.stream = torch.cuda.current_stream(self.dev)
         self.ctx = C.c_void_p()
