@@ -1440,7 +1440,8 @@ __global__ void __launch_bounds__(256) attention_kernel(const T* __restrict__ qk
 // 4 x 16 piece.  Bound by the vector unit (exponentials, masks) on long sequences, by the transfer of q, k, v on short ones.
 // 128 heads at 2047 tokens 165 -> 119 us (512 keys staged at a time, V transposed by 2-byte stores, no load under the products), 96 heads at 513 tokens
 // 20.5 -> 17.4, 512 heads at 256 tokens 20.7 -> 19.0, 384 at 128 tokens 10.6 -> 9.1; the results keep their bits.  Stages of 128 keys under eight
-// waves: with 64 the two stages that are requested ahead are half of a 256-token sequence (46.5 us for 2048 heads, 42.2 with all its keys).
+// waves: the two that are requested at the start hold a 256-token sequence (2048 heads of it 42.2 -> 37.4 us; a first form with stages of 64, one requested at
+// a time and waited for in front of the products, 46.5).
 constexpr int AT_LDK = 64 + 8;          // K row stride (bf16): 144 B
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 // columns of a piece of 4 rows of 16 entries: lane i of 16 supplies where entries 4 (i % 4) .. + 4 of row i / 4 lie and receives entry i of each row
