@@ -323,22 +323,27 @@ zgr_status check_model(zgr_ctx* c, const zgr_model& m, int dtype) {
   return ZGR_OK;
 }
 
-// Offsets of the tensors in a copy of the parameters.  What the forward pass reads as one matrix (Wq, Wk, Wv of a layer and their biases)
-// lies in one piece there as well, every other tensor on a multiple of 256 bytes.
-std::vector<size_t> copy_layout(const zgr_tensor* t, int n_t, size_t* bytes) {
+// Offsets of the tensors in a copy of the parameters.  What a transformer's forward pass reads as one matrix (Wq, Wk, Wv of a layer and their biases)
+// lies in one piece there as well, every other tensor on a multiple of 256 bytes.  A context of another kind may hold tensors of any role: each by itself.
+std::vector<size_t> copy_layout(const zgr_model& m, const zgr_tensor* t, int n_t, size_t* bytes) {
   std::vector<size_t> off((size_t)n_t, 0);
+  std::vector<bool> placed((size_t)n_t, false);
   size_t end = 0;
-  auto bytes_of = [&](int i) { return (size_t)t[i].rows * (size_t)t[i].cols * elem_size(t[i].dtype); };
-  for (int i = 0; i < n_t; ++i) {
-    if (t[i].role == ZGR_ROLE_WK || t[i].role == ZGR_ROLE_WV || t[i].role == ZGR_ROLE_BK || t[i].role == ZGR_ROLE_BV) continue;
-    off[i] = end;
-    size_t next = end + bytes_of(i);
-    const int follow[2] = {t[i].role == ZGR_ROLE_WQ ? ZGR_ROLE_WK : ZGR_ROLE_BK, t[i].role == ZGR_ROLE_WQ ? ZGR_ROLE_WV : ZGR_ROLE_BV};
-    if (t[i].role == ZGR_ROLE_WQ || t[i].role == ZGR_ROLE_BQ)
-      for (int role : follow)
+  auto place = [&](int i) { off[i] = end; end += (size_t)t[i].rows * (size_t)t[i].cols * elem_size(t[i].dtype); placed[i] = true; };
+  if (is_transformer(m.arch))
+    for (int i = 0; i < n_t; ++i) {
+      if (placed[i] || (t[i].role != ZGR_ROLE_WQ && t[i].role != ZGR_ROLE_BQ)) continue;
+      const bool weight = t[i].role == ZGR_ROLE_WQ;
+      place(i);
+      for (int role : {weight ? ZGR_ROLE_WK : ZGR_ROLE_BK, weight ? ZGR_ROLE_WV : ZGR_ROLE_BV})
         for (int j = 0; j < n_t; ++j)
-          if (t[j].role == role && t[j].layer == t[i].layer) { off[j] = next; next += bytes_of(j); }
-    end = align_up(next);
+          if (!placed[j] && t[j].role == role && t[j].layer == t[i].layer) place(j);
+      end = align_up(end);
+    }
+  for (int i = 0; i < n_t; ++i) {
+    if (placed[i]) continue;
+    place(i);
+    end = align_up(end);
   }
   *bytes = end;
   return off;
@@ -411,7 +416,7 @@ Carve carve(const zgr_model& m, const zgr_tensor* t, int n_t, int max_batch, int
     cv.row_loss = take(2 * cv.row_loss_stride * 4);
   }
   if (with_copies && m.arch != ZGR_ARCH_NONE) {   // a context without a model takes no step
-    copy_layout(t, n_t, &cv.copy_bytes);
+    copy_layout(m, t, n_t, &cv.copy_bytes);
     cv.copies = take(2 * cv.copy_bytes);
   }
   cv.total = off;
@@ -755,7 +760,7 @@ zgr_status zgr_init(zgr_ctx** out, const zgr_model* model, const zgr_tensor* ten
   }
   c->ws = reinterpret_cast<unsigned char*>(workspace); c->ws_bytes = workspace_bytes;
   size_t copy_bytes = 0;
-  c->copy_off = copy_layout(tensors, n_t, &copy_bytes);
+  c->copy_off = copy_layout(*model, tensors, n_t, &copy_bytes);
   st = bind_model(c);
   if (st != ZGR_OK) { delete c; return st; }
   int dev = 0, n_cu = 0;

@@ -111,6 +111,16 @@ def test_workspace_bytes_and_null_context_calls(lib):
     lib.zgr_destroy(None)
 
 
+@pytest.mark.parametrize("role", [7, 8, 9, 10, 5, 15], ids=["WK", "BK", "WV", "BV", "WQ", "W1"])
+def test_copies_hold_every_tensor_whatever_its_role(lib, role):
+    """A least-squares context takes further tensors of any role; each needs its room in the two copies of the parameters."""
+    model = B.zgr_model(B.ZGR_ARCH_LINEAR_LSQ, 0, 0, 0, 0, 0, 0, 0, 1e-5)
+    shapes = [(16, 16, 0), (2048, 2048, role), (33, 7, role), (5, 3, 5), (5, 3, 7)]
+    arr = (B.zgr_tensor * len(shapes))(*[_tensor(rows=r, cols=c, role=ro, tid=i) for i, (r, c, ro) in enumerate(shapes)])
+    small, large = (f(C.byref(model), arr, len(shapes), 1, 2) for f in (lib.zgr_workspace_bytes, lib.zgr_workspace_bytes_copies))
+    assert large - small >= 2 * sum(-(-4 * r * c // 256) * 256 for r, c, _ in shapes)
+
+
 def test_compression_share_matches_the_oracle(lib):
     """zgr_dtc_omega / zgr_dtc_memory_factor are host arithmetic: checked here against the oracle's search."""
     import numpy as np

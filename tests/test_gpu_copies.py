@@ -5,7 +5,8 @@ import numpy as np
 import pytest
 
 import zgr_inputs as I
-from paper_2601_12917_amd.session import Session
+from paper_2601_12917_amd import binding as B
+from paper_2601_12917_amd.session import ParamSpec, Session
 from tests.util import inputs_of, make_batch_arrays, make_session, session_batch
 
 pytestmark = pytest.mark.gpu
@@ -70,3 +71,27 @@ def test_fused_step_with_copies(monkeypatch, name):
         for i in range(len(a.params)):
             assert np.array_equal(a.get_theta(i), b.get_theta(i)), (step, a.params[i].name)
     a.close(); b.close()
+
+
+def test_least_squares_context_with_tensors_of_other_roles(monkeypatch):
+    """Tensors the model does not read, of roles that a transformer's copies keep behind Wq and bq: each has a place of its own in the copies."""
+    rng = np.random.default_rng(5)
+    table = [("w", I.ROLE_LSQ_W, (24, 40)), ("k", I.ROLE_WK, (64, 48)), ("v", I.ROLE_WV, (33, 20)), ("bk", I.ROLE_BK, (1, 13)), ("q", I.ROLE_WQ, (5, 3)), ("k2", I.ROLE_WK, (5, 3))]
+    params = [ParamSpec(n, r, 0, i, rng.standard_normal(s).astype(np.float32)) for i, (n, r, s) in enumerate(table)]
+    x, y = rng.standard_normal((6, 40)).astype(np.float32), rng.standard_normal((6, 24)).astype(np.float32)
+    out = []
+    for share in (0.25, 0.0):
+        monkeypatch.setattr(Session, "COPIES_SHARE", share)
+        sess = Session(B.ZGR_ARCH_LINEAR_LSQ, "f32", params, seed=9, eps=1e-2, alpha=1.0, max_batch=6)
+        batch = sess.make_batch(x, y)
+        losses = []
+        for step in range(2):
+            losses.append(sess.step(step, batch)[:2])
+            sess.apply_update(step, 0.7, 1e-2)
+        out.append((losses, [sess.get_theta(i) for i in range(len(params))], sess.workspace.numel()))
+        sess.close()
+    (la, ta, na), (lb, tb, nb) = out
+    assert na > nb
+    assert np.allclose(la, lb, rtol=1e-5), (la, lb)
+    for a, b, (name, _, _) in zip(ta, tb, table):
+        assert np.array_equal(a, b), name
