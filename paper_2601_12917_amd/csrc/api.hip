@@ -100,7 +100,6 @@ struct zgr_ctx {
   int64_t last_rows = 0;       // rows of the last forward's row_loss
   int last_slot = 0;           // which of the two row-loss buffers the last forward wrote
   int64_t slot_rows[2] = {0, 0};
-  size_t slot_first[2] = {0, 0};   // where in row_loss it lies (floats)
   double host_loss[2] = {0, 0};
 };
 
@@ -566,9 +565,9 @@ const void* T(zgr_ctx* c, int idx) { return c->t[idx].theta; }
 zgr_status forward_loss(zgr_ctx* c, const zgr_batch* b, int slot, bool both = false) {
   auto T = [&](zgr_ctx* ctx, int idx) -> const void* { return both ? ctx->ws + ctx->cv.copies + ctx->copy_off[idx] : ctx->t[idx].theta; };
   Twin tw;
-  if (both) { tw.models = 2; tw.w = (int64_t)c->cv.copy_bytes; }
-  auto wrote = [&](size_t rows) {                        // the second model's rows lie behind the first's
-    for (int i = both ? 0 : slot; i <= (both ? 1 : slot); ++i) { c->slot_rows[i] = (int64_t)rows; c->slot_first[i] = both ? i * rows : i * c->cv.row_loss_stride; }
+  if (both) { tw.models = 2; tw.w = (int64_t)c->cv.copy_bytes; tw.row_loss = (int64_t)c->cv.row_loss_stride; }
+  auto wrote = [&](size_t rows) {
+    for (int i = both ? 0 : slot; i <= (both ? 1 : slot); ++i) c->slot_rows[i] = (int64_t)rows;
     c->last_rows = (int64_t)rows; c->last_slot = both ? 1 : slot;
   };
   const zgr_model& m = c->model;
@@ -582,8 +581,8 @@ zgr_status forward_loss(zgr_ctx* c, const zgr_batch* b, int slot, bool both = fa
     const zgr_tensor& w = c->t[c->lsq_w];
     { ProfScope ps(c, ZGR_K_GEMM); HIP_TRY(c, launch_gemm(0, b->x, T(c, c->lsq_w), nullptr, logits, EPI_F32, b->batch, (int)w.rows, (int)w.cols, s, nullptr, 0, false, tw, true)); }
     { ProfScope ps(c, ZGR_K_LOSS);
-      HIP_TRY(c, launch_lsq_rows(logits, reinterpret_cast<const float*>(b->y), row_loss, b->batch, (int)w.rows, s, tw.models));
-      HIP_TRY(c, launch_mean_f64(row_loss, b->batch, 1.0 / b->batch, loss_dev, s, tw.models)); }
+      HIP_TRY(c, launch_lsq_rows(logits, reinterpret_cast<const float*>(b->y), row_loss, b->batch, (int)w.rows, s, tw));
+      HIP_TRY(c, launch_mean_f64(row_loss, b->batch, 1.0 / b->batch, loss_dev, s, tw)); }
     wrote((size_t)b->batch);
     return ZGR_OK;
   }
@@ -627,16 +626,16 @@ zgr_status forward_loss(zgr_ctx* c, const zgr_batch* b, int slot, bool both = fa
     } else {
       { ProfScope ps(c, ZGR_K_GEMM); HIP_TRY(c, launch_gemm(dt, h, T(c, c->tok_emb), nullptr, logits, EPI_F32, M, m.vocab, d, s, nullptr, 0, false, tw)); }
       ProfScope ps(c, ZGR_K_LOSS);
-      HIP_TRY(c, launch_ce_rows(logits, tgt, row_loss, M, m.vocab, s, tw.models));
+      HIP_TRY(c, launch_ce_rows(logits, tgt, row_loss, M, m.vocab, s, tw));
     }
     { ProfScope ps(c, ZGR_K_LOSS);
-      HIP_TRY(c, launch_mean_f64(row_loss, M, 1.0 / ((double)b->batch * (b->seq - 1)), loss_dev, s, tw.models)); }
+      HIP_TRY(c, launch_mean_f64(row_loss, M, 1.0 / ((double)b->batch * (b->seq - 1)), loss_dev, s, tw)); }
     wrote((size_t)M);
   } else {
     { ProfScope ps(c, ZGR_K_LOSS);
       HIP_TRY(c, launch_cls_head(dt, h, T(c, c->cls_w), T(c, c->cls_b), logits, b->batch, b->seq, d, m.n_class, s, tw));
-      HIP_TRY(c, launch_ce_rows(logits, reinterpret_cast<const int32_t*>(b->y), row_loss, b->batch, m.n_class, s, tw.models));
-      HIP_TRY(c, launch_mean_f64(row_loss, b->batch, 1.0 / b->batch, loss_dev, s, tw.models)); }
+      HIP_TRY(c, launch_ce_rows(logits, reinterpret_cast<const int32_t*>(b->y), row_loss, b->batch, m.n_class, s, tw));
+      HIP_TRY(c, launch_mean_f64(row_loss, b->batch, 1.0 / b->batch, loss_dev, s, tw)); }
     wrote((size_t)b->batch);
   }
   return ZGR_OK;
@@ -1476,7 +1475,7 @@ zgr_status zgr_debug_last_row_losses(zgr_ctx* c, float* out, int64_t n) {
   if (!c) return ZGR_ERR_NULL;
   if (!out) return fail(c, ZGR_ERR_NULL, "out is NULL");
   if (c->model.arch == ZGR_ARCH_NONE || n != c->last_rows) return fail(c, ZGR_ERR_SHAPE, "n = %lld, the last forward produced %lld rows", (long long)n, (long long)c->last_rows);
-  HIP_TRY(c, hipMemcpyAsync(out, c->ws + c->cv.row_loss + sizeof(float) * c->slot_first[c->last_slot], sizeof(float) * (size_t)n, hipMemcpyDeviceToHost, c->stream));
+  HIP_TRY(c, hipMemcpyAsync(out, c->ws + c->cv.row_loss + sizeof(float) * (size_t)c->last_slot * c->cv.row_loss_stride, sizeof(float) * (size_t)n, hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   return ZGR_OK;
 }
@@ -1486,7 +1485,7 @@ zgr_status zgr_debug_step_row_losses(zgr_ctx* c, int32_t which, float* out, int6
   if (!out) return fail(c, ZGR_ERR_NULL, "out is NULL");
   if (which != 0 && which != 1) return fail(c, ZGR_ERR_CONFIG, "which must be 0 (L+) or 1 (L-)");
   if (c->model.arch == ZGR_ARCH_NONE || n != c->slot_rows[which]) return fail(c, ZGR_ERR_SHAPE, "n = %lld, that forward produced %lld rows", (long long)n, (long long)c->slot_rows[which]);
-  HIP_TRY(c, hipMemcpyAsync(out, c->ws + c->cv.row_loss + sizeof(float) * c->slot_first[which], sizeof(float) * (size_t)n, hipMemcpyDeviceToHost, c->stream));
+  HIP_TRY(c, hipMemcpyAsync(out, c->ws + c->cv.row_loss + sizeof(float) * (size_t)which * c->cv.row_loss_stride, sizeof(float) * (size_t)n, hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   return ZGR_OK;
 }

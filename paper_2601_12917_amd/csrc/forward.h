@@ -9,9 +9,9 @@ namespace zgr {
 enum { EPI_STORE = 0, EPI_GELU = 1, EPI_RESID = 2, EPI_F32 = 3, EPI_CE = 4, EPI_RELU = 5 };
 
 // Two models on the same batch in one launch (the two loss evaluations of a step): the second's parameters lie w bytes behind the first's, and
-// in every activation, row loss and loss its rows follow the first's.  M and batch below count one model's rows.  Half the launches, each with twice the blocks: steps of
+// in every activation and loss its rows follow the first's; its row losses start row_loss floats behind the first's.  M and batch below count one model's rows.  Half the launches, each with twice the blocks: steps of
 // 125M parameters 3.21 -> 2.45 ms (with the tiles' order below), in fp32 4.46 -> 3.56, of 350M 9.07 -> 7.83, of 1.3B 26.1 -> 24.4, of a small decoder 245 -> 164 us.
-struct Twin { int models = 1; int64_t w = 0; };
+struct Twin { int models = 1; int64_t w = 0; int64_t row_loss = 0; };
 
 hipError_t launch_embed(int dtype, const int32_t* tok, const void* E, const void* Pe, float* x, int M, int seq, int d, int vocab, hipStream_t s, Twin tw = {});
 // out (storage type) = LayerNorm(x) g + b; xout, when not NULL, receives the same values in fp32 (it may be x itself)
@@ -32,9 +32,9 @@ hipError_t launch_attention(int dtype, const void* qkv, void* ctx, const int32_t
                             bool keep_order = false, int models = 1);
 bool       attention_head_dim_supported(int dh);
 hipError_t launch_lm_targets(const int32_t* tok, int32_t* tgt, int M, int seq, int vocab, hipStream_t s);
-hipError_t launch_ce_rows(const float* logits, const int32_t* targets, float* row_loss, int M, int n, hipStream_t s, int models = 1);
-hipError_t launch_mean_f64(const float* v, int n, double inv_count, double* out, hipStream_t s, int models = 1);
+hipError_t launch_ce_rows(const float* logits, const int32_t* targets, float* row_loss, int M, int n, hipStream_t s, Twin tw = {});
+hipError_t launch_mean_f64(const float* row_loss, int n, double inv_count, double* out, hipStream_t s, Twin tw = {});
 hipError_t launch_cls_head(int dtype, const void* h, const void* Wc, const void* bc, float* logits, int batch, int seq, int d, int n_class, hipStream_t s, Twin tw = {});
-hipError_t launch_lsq_rows(const float* pred, const float* Y, float* row_loss, int batch, int n_out, hipStream_t s, int models = 1);
+hipError_t launch_lsq_rows(const float* pred, const float* Y, float* row_loss, int batch, int n_out, hipStream_t s, Twin tw = {});
 
 }  // namespace zgr

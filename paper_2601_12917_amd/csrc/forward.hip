@@ -1619,12 +1619,13 @@ __global__ void __launch_bounds__(64 * NW, 4) attention_mfma_kernel(const bf16_t
 // THREADS MAXE entries in registers, so the row is read once (256 threads reading it twice: 135 us for 385 rows of 50272, now 26);
 // entries beyond those are read again.
 template <int THREADS, int MAXE>
-__global__ void __launch_bounds__(THREADS) ce_rows_kernel(const float* __restrict__ logits, const int32_t* __restrict__ targets, float* __restrict__ row_loss, int n, int M) {
+__global__ void __launch_bounds__(THREADS) ce_rows_kernel(const float* __restrict__ logits, const int32_t* __restrict__ targets, float* __restrict__ row_loss, int n, int M, int64_t second) {
   constexpr int WAVES = THREADS / 64;
   __shared__ float red[WAVES];
   const int m = blockIdx.x, tid = threadIdx.x;
-  int tgt = targets[m < M ? m : m - M];                              // two models: the same targets
-  if (tgt < 0) { if (tid == 0) row_loss[m] = 0.f; return; }          // uniform over the block
+  int tgt = targets[m < M ? m : m - M];                              // two models: the same targets, row losses `second` floats further on
+  row_loss += m < M ? m : m - M + second;
+  if (tgt < 0) { if (tid == 0) *row_loss = 0.f; return; }          // uniform over the block
   tgt = tgt >= n ? n - 1 : tgt;
   const float* row = logits + (size_t)m * n;
   auto across = [&](float v, bool maximum) {                          // the block's waves, in order
@@ -1650,15 +1651,16 @@ __global__ void __launch_bounds__(THREADS) ce_rows_kernel(const float* __restric
   for (int u = 0; u < MAXE; ++u) s += tid + THREADS * u < n ? expf(v[u] - mx) : 0.f;
   for (int i = tid + THREADS * MAXE; i < n; i += THREADS) s += expf(row[i] - mx);
   s = across(s, false);
-  if (tid == 0) row_loss[m] = logf(s) + mx - row[tgt];
+  if (tid == 0) *row_loss = logf(s) + mx - row[tgt];
 }
 
 // Combines the cross-entropy partials of one row: loss = log(sum_i s_i exp(m_i - M)) + M - logit[target].
 __global__ void __launch_bounds__(256) ce_combine_kernel(const float2* __restrict__ part, int n_part, const int32_t* __restrict__ targets,
-                                                         const float* __restrict__ tlogit, float* __restrict__ row_loss, int M) {
+                                                         const float* __restrict__ tlogit, float* __restrict__ row_loss, int M, int64_t second) {
   __shared__ float red[4];
   const int m = blockIdx.x;
-  if (targets[m < M ? m : m - M] < 0) { if (threadIdx.x == 0) row_loss[m] = 0.f; return; }
+  row_loss += m < M ? m : m - M + second;
+  if (targets[m < M ? m : m - M] < 0) { if (threadIdx.x == 0) *row_loss = 0.f; return; }
   const float2* row = part + (size_t)m * n_part;
   float mx = -INFINITY;
   for (int i = threadIdx.x; i < n_part; i += 256) mx = fmaxf(mx, row[i].x);
@@ -1666,7 +1668,7 @@ __global__ void __launch_bounds__(256) ce_combine_kernel(const float2* __restric
   float s = 0.f;
   for (int i = threadIdx.x; i < n_part; i += 256) s += row[i].y * expf(row[i].x - mx);
   s = block_sum(s, red);
-  if (threadIdx.x == 0) row_loss[m] = logf(s) + mx - tlogit[m];
+  if (threadIdx.x == 0) *row_loss = logf(s) + mx - tlogit[m];
 }
 
 // next-token targets: row m = b*seq + t predicts tok[m+1] for t < seq-1, else -1
@@ -1679,9 +1681,9 @@ __global__ void lm_targets_kernel(const int32_t* __restrict__ tok, int32_t* __re
 }
 
 // mean of n_rows losses (ignoring the skipped ones by dividing by `count`), accumulated in fp64; a block per model
-__global__ void __launch_bounds__(256) mean_f64_kernel(const float* __restrict__ v, int n, double inv_count, double* __restrict__ out) {
+__global__ void __launch_bounds__(256) mean_f64_kernel(const float* __restrict__ v, int n, double inv_count, double* __restrict__ out, int64_t second) {
   __shared__ double red[256];
-  v += (size_t)blockIdx.x * n;
+  v += blockIdx.x * second;
   double s = 0.0;
   for (int i = threadIdx.x; i < n; i += 256) s += (double)v[i];
   red[threadIdx.x] = s;
@@ -1704,13 +1706,13 @@ __global__ void __launch_bounds__(64) cls_head_kernel(const T* __restrict__ h, c
 }
 
 // least squares: row_loss[b] = sum_o (pred[b][o] - Y[b][o])^2 / 2
-__global__ void __launch_bounds__(256) lsq_rows_kernel(const float* __restrict__ pred, const float* __restrict__ Y, float* __restrict__ row_loss, int n_out, int batch) {
+__global__ void __launch_bounds__(256) lsq_rows_kernel(const float* __restrict__ pred, const float* __restrict__ Y, float* __restrict__ row_loss, int n_out, int batch, int64_t second) {
   __shared__ float red[4];
   const int b = blockIdx.x, by = b < batch ? b : b - batch;
   float s = 0.f;
   for (int i = threadIdx.x; i < n_out; i += 256) { const float r = pred[(size_t)b * n_out + i] - Y[(size_t)by * n_out + i]; s = __builtin_fmaf(r, r, s); }
   s = block_sum(s, red);
-  if (threadIdx.x == 0) row_loss[b] = 0.5f * s;
+  if (threadIdx.x == 0) row_loss[b < batch ? b : by + second] = 0.5f * s;
 }
 
 }  // namespace
@@ -1841,7 +1843,7 @@ hipError_t launch_gemm_ce_bf16(const void* A, const void* W, const int32_t* targ
     e = launch_gemm_bf16_t<256, 256, 2, 4, 64, 20, 1>(w, a, nullptr, part, EPI_CE, N, M, K, s, tw.models, twin(n_part), nullptr, targets, tlogit);
   }
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(ce_combine_kernel, dim3(M * tw.models), dim3(256), 0, s, (const float2*)part, n_part, targets, tlogit, row_loss, M);
+  hipLaunchKernelGGL(ce_combine_kernel, dim3(M * tw.models), dim3(256), 0, s, (const float2*)part, n_part, targets, tlogit, row_loss, M, tw.row_loss);
   return hipGetLastError();
 }
 
@@ -1901,8 +1903,8 @@ hipError_t launch_lm_targets(const int32_t* tok, int32_t* tgt, int M, int seq, i
 // The smallest block that holds the row: threads without an entry, and iterations without one, cost as much as those with (2048 rows of 33 / 4097 /
 // 10000 / 20000, with the target and mean launches: 28 / 88 / 88 / 91 us when every row took 1024 threads of 4 or 50, now 20 / 28 / 37 / 58; 256
 // threads reading the row twice: 20 / 31 / 48 / 76).
-hipError_t launch_ce_rows(const float* logits, const int32_t* targets, float* row_loss, int M, int n, hipStream_t s, int models) {
-#define ZGR_CE_ROWS(THREADS, MAXE) hipLaunchKernelGGL((ce_rows_kernel<THREADS, MAXE>), dim3(M * models), dim3(THREADS), 0, s, logits, targets, row_loss, n, M)
+hipError_t launch_ce_rows(const float* logits, const int32_t* targets, float* row_loss, int M, int n, hipStream_t s, Twin tw) {
+#define ZGR_CE_ROWS(THREADS, MAXE) hipLaunchKernelGGL((ce_rows_kernel<THREADS, MAXE>), dim3(M * tw.models), dim3(THREADS), 0, s, logits, targets, row_loss, n, M, tw.row_loss)
   if (n <= 1024)       ZGR_CE_ROWS(256, 4);
   else if (n <= 4096)  ZGR_CE_ROWS(256, 16);
   else if (n <= 8192)  ZGR_CE_ROWS(512, 16);
@@ -1913,8 +1915,8 @@ hipError_t launch_ce_rows(const float* logits, const int32_t* targets, float* ro
   return hipGetLastError();
 }
 
-hipError_t launch_mean_f64(const float* v, int n, double inv_count, double* out, hipStream_t s, int models) {
-  hipLaunchKernelGGL(mean_f64_kernel, dim3(models), dim3(256), 0, s, v, n, inv_count, out);
+hipError_t launch_mean_f64(const float* row_loss, int n, double inv_count, double* out, hipStream_t s, Twin tw) {
+  hipLaunchKernelGGL(mean_f64_kernel, dim3(tw.models), dim3(256), 0, s, row_loss, n, inv_count, out, tw.row_loss);
   return hipGetLastError();
 }
 
@@ -1924,8 +1926,8 @@ hipError_t launch_cls_head(int dtype, const void* h, const void* Wc, const void*
   return hipGetLastError();
 }
 
-hipError_t launch_lsq_rows(const float* pred, const float* Y, float* row_loss, int batch, int n_out, hipStream_t s, int models) {
-  hipLaunchKernelGGL(lsq_rows_kernel, dim3(batch * models), dim3(256), 0, s, pred, Y, row_loss, n_out, batch);
+hipError_t launch_lsq_rows(const float* pred, const float* Y, float* row_loss, int batch, int n_out, hipStream_t s, Twin tw) {
+  hipLaunchKernelGGL(lsq_rows_kernel, dim3(batch * tw.models), dim3(256), 0, s, pred, Y, row_loss, n_out, batch, tw.row_loss);
   return hipGetLastError();
 }
 

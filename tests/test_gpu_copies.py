@@ -95,3 +95,22 @@ def test_least_squares_context_with_tensors_of_other_roles(monkeypatch):
     assert np.allclose(la, lb, rtol=1e-5), (la, lb)
     for a, b, (name, _, _) in zip(ta, tb, table):
         assert np.array_equal(a, b), name
+
+
+@pytest.mark.parametrize("name", ["linear", "f32 rank 20", "bf16 rank 16", "encoder post-LN"])
+def test_row_losses_of_a_step_outlive_a_later_loss(name):
+    """A loss of more rows than the step's writes to the first forward's row losses alone: those of L- stay."""
+    cfg, bits = CASES[name]
+    specs, values, bases = inputs_of(cfg)
+    sess, a = make_session(cfg, specs, values, bases, bits=bits), make_batch_arrays(cfg)
+    assert sess.with_copies
+    one = sess.make_batch(a["x"][:1], None if a["y"] is None else a["y"][:1], None if a["lengths"] is None else a["lengths"][:1], cfg.seq)
+    keep = sess._batch_keep
+    n = cfg.seq if cfg.arch == I.ARCH_DECODER_LM else 1
+    sess.step(0, one)
+    before = sess.step_row_losses(1, n)
+    assert np.all(before[:max(1, n - 1)] > 0)
+    sess.loss(session_batch(sess, cfg, a))
+    assert np.array_equal(sess.step_row_losses(1, n), before)
+    del keep
+    sess.close()
