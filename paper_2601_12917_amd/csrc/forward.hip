@@ -730,7 +730,7 @@ __device__ __forceinline__ void epilogue_bf16(void* out, size_t o, float v) {
 
 template <int BM, int BN, int WM, int WN, int BK, int STAGES, int MODE, int PP = 0>
 __global__ void __launch_bounds__(64 * WM * WN) gemm_bf16_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, int M, int N, int K,
-                                                                 void* __restrict__ out, const bf16_t* __restrict__ bias,
+                                                                 void* out, const bf16_t* __restrict__ bias,      // resid may be out
                                                                  const int32_t* __restrict__ targets, float* __restrict__ tlogit, GemmTwin tw, int models, const float* resid) {
   constexpr int NW = WM * WN;
   constexpr int FM = BM / (32 * WM), FN = BN / (32 * WN);      // 32x32 fragments per wave
@@ -1120,7 +1120,7 @@ hipError_t launch_gemm_bf16_t(const bf16_t* A, const bf16_t* W, const bf16_t* bi
 // 512 554 us.  The same form with 64 x 64 tiles and four readers gave these cases less than 1%.
 constexpr int kFewRing = 16;
 template <int MODE>
-__global__ void __launch_bounds__(192) gemm_bf16_few_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, int M, int N, int K, void* __restrict__ out, const bf16_t* __restrict__ bias,
+__global__ void __launch_bounds__(192) gemm_bf16_few_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, int M, int N, int K, void* out, const bf16_t* __restrict__ bias,      // resid may be out
                                                             GemmTwin tw, int models, const float* resid) {
   constexpr int SLAB = 64 * GB_K * 2;                          // bytes of a k-tile: 32 rows of A, 32 of W
   extern __shared__ __attribute__((aligned(1024))) unsigned char gsm[];
