@@ -455,11 +455,11 @@ __device__ __forceinline__ void block_barrier() {
 // Operands go from global memory straight into LDS (as in the bf16 kernel below: 8 rows of 128 bytes an instruction, the 16-byte chunk c of row r in
 // slot c ^ ((r / 2) % 8)).  The half-wave h takes the chunks 4 ks + 2 h and the next as its eight terms of instruction ks, in both operands alike.
 // Cutting costs 5.5 vector instructions an entry, 176 per k-step against 24 matrix instructions of 32 cycles, whose shadow they just fit: eleven of the
-// next step's behind each of this step's.  (A 64 x 64 tile shared the usual way, 32 x 32 a wave, would cut every entry twice.)
+// next step's behind each of this step's (two of them, the roundings, at half rate: 125M fp32 step 2964 us, 2940 with planes cut by truncation, planes.h).  (A 64 x 64 tile shared the usual way, 32 x 32 a wave, would cut every entry twice.)
 // The product of the first planes has a set of accumulators of its own: the other five terms are at most 2^-8 of it and round in a sum as
 // small, which leaves one rounding of the large sum per sixteen terms.
-// The shared form has two blocks a CU and no registers for that.  Off from fp64 by 1.1e-7 of the norm at K = 768 and 1.2e-7 at 1024 (the fp32 kernels: 1.8e-7 to
-// 5.0e-7, 5.7e-7), shared 4.3e-7 and 4.9e-7.
+// The shared form has two blocks a CU and no registers for that.  Off from fp64 by 0.9e-7 of the norm at K = 768 and 1.0e-7 at 1024 (the fp32 kernels: 1.8e-7 to
+// 5.0e-7, 2.9e-7 to 5.7e-7), shared 4.2e-7 at 768, 7.0e-7 at 2048 (8.1e-7), 14e-7 at 8192 (16e-7).
 // What bounds it: the chip's power at large sizes (4096 x 2048 x 8192 185 TFLOP/s, six times that on the matrix cores; the fp32 instruction 140), the wave's
 // issue at small ones (2400 cycles a k-tile for 1536 of matrix instructions; 2900 with the reads and transfers in a row).
 // K % 32 == 0 and 16-byte aligned rows; any M, N.
@@ -558,7 +558,7 @@ __global__ void __launch_bounds__(256, SHARED ? 2 : 1) gemm_planes_kernel(const 
         mfma(cur, X[2 + f], Y[2 + f], q, sum);
         if (fetch >= 0 && 4 * f + q < LOADS) transfer(fetch, to, 4 * f + q);
         const f32x4v& v = q < 2 ? r.lo[f] : r.hi[f];
-        cut_pair(v[2 * (q & 1)], v[2 * (q & 1) + 1], q, next.f[f]);
+        cut_pair_rounded(v[2 * (q & 1)], v[2 * (q & 1) + 1], q, next.f[f]);
         in_this_order();
       }
     }
@@ -577,8 +577,8 @@ __global__ void __launch_bounds__(256, SHARED ? 2 : 1) gemm_planes_kernel(const 
       for (int q = 0; q < 8; ++q) read(0, 0, q, r);
 #pragma unroll
       for (int f = 0; f < 4; ++f) {
-        cut_pair(r.lo[f][0], r.lo[f][1], 0, f0.f[f]); cut_pair(r.lo[f][2], r.lo[f][3], 1, f0.f[f]);
-        cut_pair(r.hi[f][0], r.hi[f][1], 2, f0.f[f]); cut_pair(r.hi[f][2], r.hi[f][3], 3, f0.f[f]);
+        cut_pair_rounded(r.lo[f][0], r.lo[f][1], 0, f0.f[f]); cut_pair_rounded(r.lo[f][2], r.lo[f][3], 1, f0.f[f]);
+        cut_pair_rounded(r.hi[f][0], r.hi[f][1], 2, f0.f[f]); cut_pair_rounded(r.hi[f][2], r.hi[f][3], 3, f0.f[f]);
       }
     }
     for (int i = 0; i < steps; ++i) {

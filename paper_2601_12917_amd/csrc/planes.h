@@ -1,10 +1,17 @@
 // fp32 products on the bf16 matrix instructions.  An fp32 number is the sum of three bf16 numbers exactly: its mantissa cut into pieces of
-// eight bits ("planes", cut by truncation, so that no piece overflows).  The product of two bf16 numbers is exact in fp32, so a product of fp32 numbers is
-// the sum of nine such products, of which the three smallest are below 2^-24 of it and left out; with a bf16 factor three are all.  The sums are
-// the instruction's, in fp32.  Six bf16 instructions take 0.38 of the time of the fp32 ones they replace, three 0.19.
-// Against fp64 the results are as good as or better than those of the fp32 instructions, whose every fourth (16x16x4) or second (32x32x2) term is
+// eight bits ("planes").  The product of two bf16 numbers is exact in fp32, so with a bf16 factor three such products are the whole product,
+// and that of two fp32 numbers is the sum of nine, of which the three smallest are left out.  The sums are the instruction's, in fp32.  Six bf16
+// instructions take 0.38 of the time of the fp32 ones they replace, three 0.19.
+// Where products are left out the planes are cut by rounding: plane 1 of a number in [1, 2) is then at most 2^-8 and plane 2 at most 2^-17, what is left out at most
+// 2^-24 of the product, and its sign is anyone's.  (Cut by truncation it is up to 2^-21, always with the sign of the product: sums of positive products came
+// out 2^-24.5 too small, and where the sum has grown so large that a step's share of the smaller planes is under half its last place, all of that share was
+// lost: 2048 x 2048 x 2048 factors of [1, 2) were off by 48 2^-24 of the norm, 4096 x 1024 x 8192 by 269; the fp32 instruction 11 and 23.)  With a bf16
+// factor nothing is left out and truncation serves, under which no plane overflows.
+// Off from fp64 no further than the fp32 instructions, whose every fourth (16x16x4) or second (32x32x2) term is
 // followed by a rounding of the sum, here every thirty-second (sixteenth) of each plane (figures where it is used).
-// An infinite factor has NaN in its second plane; sums that come out not finite have to be taken again by the fp32 instructions.
+// An infinite factor has NaN in its second plane, one that rounds up to infinity (above 3.39e38) in its third; sums that come out not finite have to be
+// taken again by the fp32 instructions.  The instruction takes a subnormal plane as zero: entries are exact to 2^-126, so numbers below about 2^-110
+// lose their last plane (factors of 2^-115 times factors of 2^100: off by 37 2^-24).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -32,7 +39,7 @@ __device__ __forceinline__ uint32_t low_halves(uint32_t x1, uint32_t x0) {
   return (x1 << 16) | (x0 & 0xFFFFu);
 #endif
 }
-// words w of the planes: terms 2 w and 2 w + 1
+// words w of the planes: terms 2 w and 2 w + 1, cut by truncation
 __device__ __forceinline__ void cut_pair(float x0, float x1, int w, PlanesOf<3>& o) {
   const uint32_t u0 = __float_as_uint(x0), u1 = __float_as_uint(x1);
   const float r0 = x0 - __uint_as_float(u0 & 0xFFFF0000u), r1 = x1 - __uint_as_float(u1 & 0xFFFF0000u);
@@ -40,6 +47,20 @@ __device__ __forceinline__ void cut_pair(float x0, float x1, int w, PlanesOf<3>&
   const float s0 = r0 - __uint_as_float(v0 & 0xFFFF0000u), s1 = r1 - __uint_as_float(v1 & 0xFFFF0000u);
   o.p[0][w] = high_halves(u1, u0);
   o.p[1][w] = high_halves(v1, v0);
+  o.p[2][w] = high_halves(__float_as_uint(s1), __float_as_uint(s0));
+}
+
+// the same, cut by rounding: what is left after two planes fits the third
+typedef float planes_f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 planes_bf16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t round_pair(float x0, float x1) { return __builtin_bit_cast(uint32_t, __builtin_convertvector(planes_f32x2{x0, x1}, planes_bf16x2)); }
+__device__ __forceinline__ void cut_pair_rounded(float x0, float x1, int w, PlanesOf<3>& o) {
+  const uint32_t u = round_pair(x0, x1);
+  const float r0 = x0 - __uint_as_float(u << 16), r1 = x1 - __uint_as_float(u & 0xFFFF0000u);
+  const uint32_t v = round_pair(r0, r1);
+  const float s0 = r0 - __uint_as_float(v << 16), s1 = r1 - __uint_as_float(v & 0xFFFF0000u);
+  o.p[0][w] = u;
+  o.p[1][w] = v;
   o.p[2][w] = high_halves(__float_as_uint(s1), __float_as_uint(s0));
 }
 

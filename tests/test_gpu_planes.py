@@ -28,6 +28,25 @@ def test_projection_matches_fp64(M, N, K, epi):
     assert torch.all((out.double().cpu() - want).abs() <= bound)
 
 
+@pytest.mark.parametrize("M,N,K", [(1024, 1024, 192), (777, 770, 768), (2048, 4096, 32), (2048, 2048, 256), (2048, 2048, 2048), (4096, 1024, 8192)])
+@pytest.mark.parametrize("factors", ["gauss", "positive"])
+def test_projection_is_as_close_as_fp32_and_unbiased(M, N, K, factors):
+    """In the norm, where entry-wise bounds are far above what the planes lose.  Factors of one sign show what they leave out or let fall below the sum's last
+    place: nothing averages out.  A sum rounds 6 K / 16 times by at most 2^-24 of its final size (gauss: of its norm over the factors, which the sum's own is)."""
+    import torch
+    from paper_2601_12917_amd import binding as B
+    gen = torch.Generator(device="cuda").manual_seed(M + N + K)
+    draw = torch.randn if factors == "gauss" else lambda *s, **kw: torch.rand(*s, **kw) + 1
+    A, W = draw(M, K, generator=gen, device="cuda"), draw(N, K, generator=gen, device="cuda")
+    out = torch.empty(M, N, device="cuda")
+    B.check(B.lib().zgr_debug_gemm(0, A.data_ptr(), W.data_ptr(), None, out.data_ptr(), 3, M, N, K, torch.cuda.current_stream().cuda_stream))
+    want = A.double() @ W.double().T
+    off = out.double() - want
+    assert off.norm() <= 2.0 ** -24 * np.sqrt(K / 8) * want.norm()              # uniform roundings: 1 / sqrt(3) of their largest
+    if K <= 768:                                                                # what is left out averages 2^-38 of a product
+        assert abs((off * want.sign()).sum()) <= 0.2 * 2.0 ** -24 * want.abs().sum()
+
+
 def _wild(x, gen):
     """Entries that are infinite, NaN or close to the largest number, a few in a row of their own each."""
     import torch
