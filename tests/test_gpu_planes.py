@@ -82,6 +82,24 @@ def test_projection_of_wild_operands(M, N, K):
 
 
 @pytest.mark.parametrize("a_k", [1, 0])
+@pytest.mark.parametrize("M,N,K", [(231, 1024, 2047), (1024, 1024, 8190), (2048, 4096, 8191)])
+@pytest.mark.parametrize("factors", ["gauss", "positive"])
+def test_product_with_a_bf16_factor_is_as_close_as_fp32(M, N, K, a_k, factors):
+    """Nothing is left out; a sum rounds three times per 32 terms, by at most 2^-24 of its final size, here counted twice.  With factors of one sign the smallest
+    planes must not have one."""
+    import torch
+    from paper_2601_12917_amd import binding as B
+    gen = torch.Generator(device="cuda").manual_seed(M + N + K)
+    draw = torch.randn if factors == "gauss" else lambda *s, **kw: torch.rand(*s, **kw) + 1
+    A, Bm = draw(M, K, generator=gen, device="cuda"), draw(K, N, generator=gen, device="cuda").bfloat16()
+    Ad, out = A if a_k else A.T.contiguous(), torch.empty(M, N, device="cuda")
+    B.check(B.lib().zgr_debug_product(Ad.data_ptr(), 0, a_k, Ad.shape[1], 0, Bm.data_ptr(), 1, 0, N, 0, out.data_ptr(), N, 0, M, N, K, 1.0, 1,
+                                      None, 0, None, None, 0, torch.cuda.current_stream().cuda_stream))
+    want = A.double() @ Bm.double()
+    assert (out.double() - want).norm() <= 2.0 ** -24 * np.sqrt(K / 16) * want.norm()
+
+
+@pytest.mark.parametrize("a_k", [1, 0])
 @pytest.mark.parametrize("K", [77, 256])
 def test_product_of_wild_operands_with_bf16(a_k, K):
     import torch
