@@ -113,6 +113,20 @@ def test_fp32_gradients_at_the_edges_of_the_row_rules(kw):
         assert np.abs(grads[i] - want).max() <= 2e-4 * np.abs(want).max() + floor, s.name
 
 
+@pytest.mark.parametrize("n_head", [1, 2, 4], ids=["head64", "head32", "head16"])
+@pytest.mark.parametrize("seq", [257, 1100, 2047])
+def test_key_bias_gradient_is_zero_but_for_rounding(n_head, seq):
+    """Scores shifted by one number leave the softmax as it is, so the key bias has no gradient: what comes out is the rounding of dS and of the sums over it.  dK rows
+    meet LayerNorm rows of norm sqrt(d) in Wk's gradient, so sqrt(sum |dK_j|^2) is its norm / sqrt(d); four roundings an entry of dS (scores, exponential, 1 / sum,
+    dP - p dP), independent, and as much again at most for the sums, whose chains must not grow with the sequence."""
+    cfg = I.shrink(I.CONFIGS["cfg2"], name="bw_sums", n_layer=1, d_model=64, n_head=n_head, d_ff=64, vocab=101, max_pos=2048, batch=1, seq=seq, k=4, k_full=4, tokens="uniform")
+    sess, specs, _ = _setup(cfg, 1.0)
+    _, got = _device(sess, cfg, _batch(cfg, 0))
+    g = {s.role: x for s, x in zip(specs, got)}
+    assert np.linalg.norm(g[I.ROLE_BK]) <= 4.5 * 2.0 ** -24 * np.linalg.norm(g[I.ROLE_WK]) / 8
+    sess.close()
+
+
 @pytest.mark.parametrize("batch,seq,act,post_ln", [(4, 48, "gelu", False), (3, 37, "gelu", False), (4, 48, "relu", True)])
 def test_bf16_gradients_point_where_the_oracle_gradients_point(batch, seq, act, post_ln, say):
     """192 tokens: the backward products run on the matrix cores; 111 tokens (not a multiple of 64): on the fp32 kernel."""
