@@ -972,7 +972,7 @@ struct BwCarve {
   size_t xout = 0;
   std::vector<PerLayer> layer;
   size_t xfin = 0, hf = 0, logits = 0, targets = 0, row_loss = 0, loss = 0;
-  size_t dx = 0, dt = 0, dff = 0, dqkv = 0, P = 0, dS = 0, stats = 0;
+  size_t dx = 0, dt = 0, dff = 0, dqkv = 0, attn = 0, stats = 0;
   size_t part = 0, part_floats = 0;  // chunk sums of the column reductions until they are added up
   size_t tA = 0, tB = 0, tC = 0, tW = 0, tL[8] = {};     // bf16 operands of the matrix-core products (bf16 models with a token count that is a multiple of 64)
   bool mfma = false;
@@ -1012,9 +1012,7 @@ BwCarve bw_carve(const zgr_ctx* c, int batch, int seq) {
   v.dt = take(M * d * 4);
   v.dff = take(M * ff * 4);
   v.dqkv = take(M * 3 * d * 4);
-  const bool pairs = bw_attention_buffers((int)d, m.n_head);       // [T, T] per head, or three numbers per query
-  v.P = take((size_t)batch * m.n_head * (pairs ? (size_t)seq * seq : 3 * align_up((size_t)seq, 32)) * 4);
-  v.dS = take(pairs ? (size_t)batch * m.n_head * seq * seq * 4 : 0);
+  v.attn = take(4 * bw_attention_scratch(c->dtype, (int)d, m.n_head, batch, seq, m.arch == ZGR_ARCH_DECODER_LM ? 1 : 0));
   v.stats = take(M * 2 * 4);
   v.part_floats = std::max(kSumArena, bw_scratch_floats((int)d, (int)std::max(std::max(ff, 3 * d), (size_t)m.n_class)));
   v.part = take(4 * v.part_floats);
@@ -1234,7 +1232,7 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
     }
     // x_mid (or y1) = x_in + ctx Wo^T + bo
     if ((st = linear_backward(dx, nullptr, d, T(c, L.wo), d, ws + W.ctx, 1, &L.wo, &L.bo, dtb, 2)) != ZGR_OK) return st;
-    HIP_TRY(c, launch_bw_attention(dt, ws + W.qkv, dtb, lengths, B, Tn, d, H, lm ? 1 : 0, F(v.P), F(v.dS), dqkv, s));
+    HIP_TRY(c, launch_bw_attention(dt, ws + W.qkv, dtb, lengths, B, Tn, d, H, lm ? 1 : 0, F(v.attn), dqkv, s));
     // q, k, v = h1 W{q,k,v}^T + b{q,k,v}: three column blocks of dqkv; Wq, Wk, Wv are adjacent, one [3 d, d] matrix
     const int wi[3] = {L.wq, L.wk, L.wv}, bi[3] = {L.bq, L.bk, L.bv};
     if ((st = linear_backward(dqkv, nullptr, 3 * d, T(c, L.wq), d, ws + W.h1, 3, wi, bi, dtb, 3)) != ZGR_OK) return st;

@@ -50,11 +50,10 @@ hipError_t launch_bw_layernorm(int dtype, const float* x, const void* g, const f
 hipError_t launch_bw_act_forward(int dtype, int relu, const float* u, void* f, int64_t n, hipStream_t s);
 hipError_t launch_bw_act(int relu, const float* u, float* df, int64_t n, hipStream_t s);
 hipError_t launch_bw_add(float* dst, const float* src, int64_t n, hipStream_t s);
-// dqkv [B T, 3 d] from dctx [B T, d]; scratch: P of 3 B n_head floats for T rounded up to a multiple of 32, or, where the rule needs [T, T] buffers (heads of 8), P and dS of B n_head T T
-// floats each
-bool       bw_attention_buffers(int d, int n_head);
+// dqkv [B T, 3 d] from dctx [B T, d]; scratch: bw_attention_scratch floats, which grow with batch and with seq
+size_t     bw_attention_scratch(int dtype, int d, int n_head, int batch, int seq, int causal);
 hipError_t launch_bw_attention(int dtype, const void* qkv, const float* dctx, const int32_t* lengths, int batch, int seq, int d, int n_head, int causal,
-                               float* P, float* dS, float* dqkv, hipStream_t s);
+                               float* scratch, float* dqkv, hipStream_t s);
 // dE [vocab, d] += rows of dx by token, dPe [max_pos, d] = sums of dx by position
 hipError_t launch_bw_embedding(const int32_t* tok, const float* dx, int M, int seq, int d, int vocab, float* dE, float* dPe, int max_pos, hipStream_t s);
 

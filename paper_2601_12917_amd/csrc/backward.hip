@@ -9,6 +9,7 @@
 #include "backward.h"
 #include "planes.h"
 #include "product.h"
+#include <algorithm>
 
 namespace zgr {
 
@@ -459,7 +460,7 @@ __global__ void __launch_bounds__(256) attn_backward_rows_kernel(const int32_t* 
   }
 }
 
-// The same rule for heads of 16, 32 and 64 without the [T, T] buffers, in two kernels of one wave per 32 rows.  The first has 32 queries in its lanes and
+// The same rule for heads of 16, 32 and 64 without the [T, T] buffers, where there are enough rows (bw_attention_buffers), in two kernels of one wave per 32 rows.  The first has 32 queries in its lanes and
 // walks the keys in blocks of 32 twice: S^T = K Q^T and dP^T = V dctx^T give the maximum, the sum of exponentials and p . dP of each query (stats), then
 // again dS and with it dQ^T += K^T dS^T.  The second has 32 keys in its lanes and walks the queries that see them: S, dP, P and dS from the stats,
 // dK^T += Q^T dS, dV^T += dctx^T P.  A lane holds 16 rows of one column of these 32 x 32 pieces, which are the next product's operand as they
@@ -941,18 +942,45 @@ hipError_t launch_bw_add(float* dst, const float* src, int64_t n, hipStream_t s)
   return hipGetLastError();
 }
 
-bool bw_attention_buffers(int d, int n_head) { const int dh = d / n_head; return !((dh == 16 || dh == 32 || dh == 64) && d % 8 == 0); }
+// The kernels without the [T, T] buffers have a wave per 32 rows, which walks the whole sequence: with few of them most of the chip stands by. Longer than `after`
+// tokens and up to `waves` of them the five products with the buffers are the faster form.  Time with the buffers / without, of the whole pass of a 2-block model:
+//   fp32 64   4 heads at 64 tokens 0.98, 128 0.94, 512 0.84, 2048 0.80 (256 waves); 24 at 1024 (768) 0.95; 32 at 1024 (1024) 0.99; 24 at 2048 (1536) 1.06, without the causal mask 0.90;
+//             32 at 2048 (2048) 1.15 and 0.96; 96 at 1024 (3072) 1.18 and 1.00
+//   fp32 32   4 at 128 1.00, 256 0.94, 2048 0.83; 32 at 512 (512) 0.94; 48 at 512 (768) 0.98; 24 at 1024 (768) 1.05         fp32 16   4 at 192 0.99, 256 0.95, 2048 0.82; 32 at 512 0.95; 48 at 512 1.00
+//   bf16 64   16 at 128 1.07, 192 1.01, 256 0.97, 4 at 2048 0.67; 32 at 512 0.96; 48 at 384 (576) 1.04; 12 at 2048 (768) 1.15
+//   bf16 32   4 at 256 1.00, 16 at 300 1.02, 4 at 384 0.97, 2048 0.89; 32 at 512 1.00; 24 at 1024 1.07                                            bf16 16   4 at 256 0.99, 16 at 300 1.04, 4 at 384 0.93, 512 0.91, 2048 0.83; 32 at 512 0.97; 48 at 512 1.03
+static bool bw_attention_has_kernels(int d, int n_head) { const int dh = d / n_head; return (dh == 16 || dh == 32 || dh == 64) && d % 8 == 0; }
+struct FewWaves { int after, waves; };
+static FewWaves bw_attention_few_waves(int dtype, int dh, int seq, int causal) {
+  if (dtype == 0 && dh == 64) return {64, causal || seq <= 256 ? 1024 : 2048};
+  if (dtype == 0) return {dh == 32 ? 128 : 192, 512};
+  return {dh == 64 ? 192 : 320, 512};
+}
+static bool bw_attention_buffers(int dtype, int d, int n_head, int batch, int seq, int causal) {
+  if (!bw_attention_has_kernels(d, n_head)) return true;
+  const FewWaves f = bw_attention_few_waves(dtype, d / n_head, seq, causal);
+  return seq > f.after && (int64_t)batch * n_head * ((seq + 31) / 32) <= f.waves;
+}
+static size_t bw_attention_pair(int heads, int seq) { return ((size_t)heads * seq * seq + 63) / 64 * 64; }
+size_t bw_attention_scratch(int dtype, int d, int n_head, int batch, int seq, int causal) {
+  const size_t heads = (size_t)batch * n_head, stats = 3 * heads * (((size_t)seq + 31) / 32 * 32);
+  if (!bw_attention_has_kernels(d, n_head)) return 2 * bw_attention_pair((int)heads, seq);
+  // the largest that a smaller batch or a shorter sequence may ask for, so that room for the largest is room for all: up to `waves` blocks of 32 rows have buffers
+  const FewWaves f = bw_attention_few_waves(dtype, d / n_head, seq, causal);
+  const size_t rows = std::min(heads * (size_t)seq, (size_t)f.waves * 32);
+  return std::max(stats, seq > f.after ? 2 * (rows * (size_t)seq + 64) : (size_t)0);
+}
 
 hipError_t launch_bw_attention(int dtype, const void* qkv, const float* dctx, const int32_t* lengths, int batch, int seq, int d, int n_head, int causal,
-                               float* P, float* dS, float* dqkv, hipStream_t s) {
+                               float* scratch, float* dqkv, hipStream_t s) {
   if (batch < 1 || seq < 1 || n_head < 1 || seq > kBackwardMaxSeq || d % n_head != 0) return hipErrorInvalidValue;
   const int dh = d / n_head, heads = batch * n_head;
-  if (!bw_attention_buffers(d, n_head)) {
+  if (!bw_attention_buffers(dtype, d, n_head, batch, seq, causal)) {
     const dim3 grid((unsigned)heads * (unsigned)((seq + 31) / 32));
 #define ZGR_ATTENTION(T, DH)                                                                                                                                              \
     {                                                                                                                                                                     \
-      hipLaunchKernelGGL((attn_backward_q_kernel<T, DH>), grid, dim3(64), 0, s, reinterpret_cast<const T*>(qkv), dctx, lengths, seq, d, n_head, causal, heads, P, dqkv);  \
-      hipLaunchKernelGGL((attn_backward_kv_kernel<T, DH>), grid, dim3(64), 0, s, reinterpret_cast<const T*>(qkv), dctx, lengths, seq, d, n_head, causal, heads, P, dqkv); \
+      hipLaunchKernelGGL((attn_backward_q_kernel<T, DH>), grid, dim3(64), 0, s, reinterpret_cast<const T*>(qkv), dctx, lengths, seq, d, n_head, causal, heads, scratch, dqkv);  \
+      hipLaunchKernelGGL((attn_backward_kv_kernel<T, DH>), grid, dim3(64), 0, s, reinterpret_cast<const T*>(qkv), dctx, lengths, seq, d, n_head, causal, heads, scratch, dqkv); \
       return hipGetLastError();                                                                                                                                           \
     }
     switch (dh | (dtype == 1 ? 256 : 0)) {
@@ -965,6 +993,8 @@ hipError_t launch_bw_attention(int dtype, const void* qkv, const float* dctx, co
     }
 #undef ZGR_ATTENTION
   }
+  float* P = scratch;
+  float* dS = P + bw_attention_pair(heads, seq);
   // head z = (b, h): the [T, T] buffers are consecutive in z; q, k, v of the head are the columns h dh, d + h dh, 2 d + h dh of
   // the [T, 3 d] rows of sequence b, dctx its columns h dh of [T, d] rows
   const int64_t tt = (int64_t)seq * seq, ld = (int64_t)3 * d;

@@ -113,17 +113,60 @@ def test_fp32_gradients_at_the_edges_of_the_row_rules(kw):
         assert np.abs(grads[i] - want).max() <= 2e-4 * np.abs(want).max() + floor, s.name
 
 
-@pytest.mark.parametrize("n_head", [1, 2, 4], ids=["head64", "head32", "head16"])
-@pytest.mark.parametrize("seq", [257, 1100, 2047])
-def test_key_bias_gradient_is_zero_but_for_rounding(n_head, seq):
+# per head size: batches on either side of the line between attention's kernels and the products with [T, T] buffers (blocks of 32 rows x heads)
+LONG = [(1, 257, 113, 114), (1, 1100, 29, 30), (2, 257, 28, 29), (2, 1100, 7, 8), (4, 257, 14, 15), (4, 2047, 2, 3)]
+
+
+@pytest.mark.parametrize("few", [True, False], ids=["few", "many"])
+@pytest.mark.parametrize("n_head,seq,few_batch,many_batch", LONG)
+def test_key_bias_gradient_is_zero_but_for_rounding(n_head, seq, few_batch, many_batch, few):
     """Scores shifted by one number leave the softmax as it is, so the key bias has no gradient: what comes out is the rounding of dS and of the sums over it.  dK rows
     meet LayerNorm rows of norm sqrt(d) in Wk's gradient, so sqrt(sum |dK_j|^2) is its norm / sqrt(d); four roundings an entry of dS (scores, exponential, 1 / sum,
     dP - p dP), independent, and as much again at most for the sums, whose chains must not grow with the sequence."""
-    cfg = I.shrink(I.CONFIGS["cfg2"], name="bw_sums", n_layer=1, d_model=64, n_head=n_head, d_ff=64, vocab=101, max_pos=2048, batch=1, seq=seq, k=4, k_full=4, tokens="uniform")
+    cfg = I.shrink(I.CONFIGS["cfg2"], name="bw_sums", n_layer=1, d_model=64, n_head=n_head, d_ff=64, vocab=101, max_pos=2048, batch=few_batch if few else many_batch, seq=seq,
+                   k=4, k_full=4, tokens="uniform")
     sess, specs, _ = _setup(cfg, 1.0)
     _, got = _device(sess, cfg, _batch(cfg, 0))
     g = {s.role: x for s, x in zip(specs, got)}
     assert np.linalg.norm(g[I.ROLE_BK]) <= 4.5 * 2.0 ** -24 * np.linalg.norm(g[I.ROLE_WK]) / 8
+    sess.close()
+
+
+@pytest.mark.parametrize("few", [True, False], ids=["few", "many"])
+@pytest.mark.parametrize("dtype,arch", [("f32", "dec"), ("f32", "enc"), ("bf16", "dec"), ("bf16", "enc")])
+@pytest.mark.parametrize("n_head", [1, 2, 4], ids=["head64", "head32", "head16"])
+def test_attention_on_long_sequences_either_way(n_head, dtype, arch, few):
+    """330 tokens (bf16 models with heads of 16 or 32 have their line from 321 on), both sides of it; products of fp32 operands as above, of bf16 ones by direction."""
+    waves = 2048 if dtype == "f32" and n_head == 1 and arch == "enc" else 1024 if dtype == "f32" and n_head == 1 else 512
+    batch = waves // (11 * n_head) + (0 if few else 1)
+    cfg = I.shrink(I.CONFIGS["cfg2"], **dict(TINY_CLS if arch == "enc" else TINY_LM, name="bw_line", n_layer=1, d_model=64, n_head=n_head, d_ff=64, vocab=67, max_pos=332, batch=batch, seq=330, dtype=dtype))
+    sess, specs, P = _setup(cfg)
+    arrays = _batch(cfg, 5)
+    loss, grads = _device(sess, cfg, arrays)
+    loss_or, grads_or = _oracle(cfg, P, arrays)
+    floor = 1e-6 * max(np.abs(g).max() for g in grads_or.values())
+    for i, s in enumerate(specs):
+        want = grads_or[s.name]
+        if dtype == "f32":
+            assert np.abs(grads[i] - want).max() <= 2e-4 * np.abs(want).max() + floor, s.name
+        elif want.ndim == 2 and s.rows > 1:
+            assert (grads[i] * want).sum() >= 0.995 * np.linalg.norm(grads[i]) * np.linalg.norm(want), s.name
+    sess.close()
+
+
+@pytest.mark.parametrize("dtype,n_head", [("f32", 1), ("f32", 4), ("bf16", 1), ("bf16", 2), ("f32", 8)])
+@pytest.mark.parametrize("arch", [I.ARCH_DECODER_LM, I.ARCH_ENCODER_CLS], ids=["dec", "enc"])
+def test_workspace_of_a_batch_holds_every_smaller_one(dtype, n_head, arch):
+    cfg = I.shrink(I.CONFIGS["cfg2"], **dict(TINY_CLS if arch == I.ARCH_ENCODER_CLS else TINY_LM, arch=arch, name="bw_ws", n_layer=1, d_model=64, n_head=n_head, d_ff=64, max_pos=2048,
+                                             batch=64, seq=2048, dtype=dtype))
+    sess, _, _ = _setup(cfg)
+    need = lambda b, t: sess.lib.zgr_cloud_backward_workspace(sess.ctx, b, t)
+    for t in (64, 128, 192, 256, 320, 512, 1024, 2048):            # multiples of 64: bf16 models keep one form of the products
+        sizes = [need(b, t) for b in range(1, 65)]
+        assert all(0 < a <= b for a, b in zip(sizes, sizes[1:])), t
+    for b in (1, 5, 17, 64):
+        sizes = [need(b, t) for t in range(64, 2049, 64)]
+        assert all(0 < x <= y for x, y in zip(sizes, sizes[1:])), b
     sess.close()
 
 
