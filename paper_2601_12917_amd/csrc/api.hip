@@ -1082,10 +1082,10 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
   // The products of the backward half.  fp32 models and ragged token counts: fp32 products on the operands as they lie.  bf16 models
   // (token count a multiple of 64): the forward pass's matrix-core GEMM, which contracts along the rows of both
   // operands, on bf16 copies written out with the contraction index innermost.
-  auto product = [&](const void* A, bool a_k, int64_t lda, const void* B, int64_t ldb, float* C, int64_t ldc, int Mp, int Np, int Kp, float* a_sums) {
+  auto product = [&](const void* A, bool a_k, int64_t lda, const void* B, int64_t ldb, float* C, int64_t ldc, int Mp, int Np, int Kp, float* a_sums, int row_blocks = 1) {
     ProductArgs p;
     p.A = A; p.a_k = a_k; p.lda = lda; p.B = B; p.b_dtype = dt == ZGR_BF16 ? 1 : 0; p.b_k = false; p.ldb = ldb; p.C = C; p.ldc = ldc;
-    p.M = Mp; p.N = Np; p.K = Kp; p.a_sums = a_sums; p.scratch = F(v.split); p.scratch_floats = kProductScratch;
+    p.M = Mp; p.N = Np; p.K = Kp; p.a_sums = a_sums; p.row_blocks = row_blocks; p.scratch = F(v.split); p.scratch_floats = kProductScratch;
     return launch_product(p, s);
   };
   const int relu = m.act == ZGR_ACT_RELU ? 1 : 0;
@@ -1113,9 +1113,9 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
       HIP_TRY(c, launch_gemm(ZGR_BF16, ws + v.tA, wT, nullptr, da, EPI_F32, M, Kp, Np, s));
     } else {
       if (u) HIP_TRY(c, launch_bw_act(relu, u, dy, (int64_t)M * Np, s));
-      bool whole = true;                                 // the blocks' gradients in one piece, weights and biases: one product
+      bool whole = true;                                 // the blocks' gradients in one piece, weights and biases: one product, with the bits of one each
       for (int p = 1; p < blocks; ++p) whole = whole && grads[wi[p]] == grads[wi[0]] + (size_t)p * n * Kp && db[p] == db[0] + (size_t)p * n;
-      for (int p = 0; p < (whole ? 1 : blocks); ++p) HIP_TRY(c, product(dy + (size_t)p * n, false, Np, a, Kp, grads[wi[p]], Kp, whole ? Np : n, Kp, M, db[p]));
+      for (int p = 0; p < (whole ? 1 : blocks); ++p) HIP_TRY(c, product(dy + (size_t)p * n, false, Np, a, Kp, grads[wi[p]], Kp, whole ? Np : n, Kp, M, db[p], whole ? blocks : 1));
       HIP_TRY(c, product(dy, true, Np, W, Kp, da, Kp, M, Kp, Np, nullptr));
     }
     return ZGR_OK;

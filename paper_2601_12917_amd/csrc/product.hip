@@ -528,7 +528,9 @@ bool near_operand(const void* p, int dtype, bool along_k, int64_t ld, int n, int
 hipError_t launch_product(const ProductArgs& p, hipStream_t s) {
   if (p.M < 1 || p.N < 1 || p.batches < 1) return hipSuccess;
   if (p.K < 0 || p.batches > 65535 || p.zdiv < 1 || (p.a_sums && (p.a_k || p.a_dtype != 0 || p.batches != 1))) return hipErrorInvalidValue;
-  const int64_t tiles = (((int64_t)p.M + 63) / 64) * (((int64_t)p.N + 63) / 64) * p.batches;
+  if (p.row_blocks < 1 || p.M % p.row_blocks || (p.row_blocks > 1 && (p.batches != 1 || p.a_k))) return hipErrorInvalidValue;
+  const int rows = p.M / p.row_blocks;
+  const int64_t tiles = (((int64_t)rows + 63) / 64) * (((int64_t)p.N + 63) / 64) * p.batches;
   const int steps = (p.K + kStep - 1) / kStep;
   // Two fp32 operands.  Two waves per SIMD hide each other's loads (one: 10.35 ms for the backward pass of a 24-block, 1024-wide encoder on 231
   // tokens, two: 10.06).  With fewer pieces than that four waves share each, or eight where blocks of four would leave CUs with one (385 x 768 x 768:
@@ -542,10 +544,22 @@ hipError_t launch_product(const ProductArgs& p, hipStream_t s) {
   const bool few = p.batches == 1 || (p.batches == 2 && p.zdiv == 1);      // one product, or that of two models
   if (few && p.scratch && split > 1) {
     int64_t z = (planes ? kWaves / 2 : kWaves) / (tiles * split);
-    const int64_t room = (int64_t)(p.scratch_floats / ((size_t)p.M * ((size_t)p.N + 1) * (size_t)p.batches));
+    const int64_t room = (int64_t)(p.scratch_floats / ((size_t)rows * ((size_t)p.N + 1) * (size_t)p.batches));
     if (z > steps / (8 * split)) z = steps / (8 * split);
     if (z > room) z = room;
     if (z > 1) parts = (int)z;
+  }
+  if (p.row_blocks > 1 && parts > 1 && (size_t)parts * p.M * ((size_t)p.N + 1) > p.scratch_floats) {      // no room for all blocks' parts: one after the other
+    ProductArgs q = p;
+    q.M = rows; q.row_blocks = 1;
+    for (int b = 0; b < p.row_blocks; ++b) {
+      q.A = reinterpret_cast<const char*>(p.A) + (size_t)b * rows * (p.a_dtype == 1 ? 2 : 4);
+      q.C = p.C + (int64_t)b * rows * p.ldc;
+      q.a_sums = p.a_sums ? p.a_sums + (int64_t)b * rows : nullptr;
+      const hipError_t e = launch_product(q, s);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
   }
   // What is left with few pieces and an undivided sum takes 32 x 32 pieces, four times the blocks (512 x 128 x 512: 8.0 us against 16.6,
   // 385 x 768 x 768: 15.9 against 20.4; at 252 pieces, 385 x 2304 x 768, they are slower: 28 against 22).

@@ -230,6 +230,29 @@ def test_two_runs_agree_bit_for_bit(dtype):
         assert bool((a == b).all()), s_.name
 
 
+@pytest.mark.parametrize("dtype,d,n_head,batch,seq", [("f32", 768, 12, 4, 128), ("f32", 512, 8, 1, 2048), ("bf16", 512, 8, 1, 2047), ("bf16", 512, 8, 4, 128), ("f32", 40, 5, 2, 19)])
+def test_gradients_do_not_depend_on_where_they_are_written(dtype, d, n_head, batch, seq):
+    """Adjacent gradients of Wq, Wk, Wv (and of their biases) are one product: the sums take the order of three all the same.  (Undivided sums in one launch; parts that the
+    scratch has no room for all at once; bf16 operands.)"""
+    import ctypes
+    import torch
+    cfg = I.shrink(I.CONFIGS["cfg2"], name="bw_places", n_layer=1, d_model=d, n_head=n_head, d_ff=64, vocab=101, max_pos=2048, batch=batch, seq=seq, k=4, k_full=4, dtype=dtype)
+    from tests.util import session_batch
+    sess, specs, _ = _setup(cfg)
+    b = session_batch(sess, cfg, _batch(cfg, 0))
+    need = sess.lib.zgr_cloud_backward_workspace(sess.ctx, batch, seq)
+    work, out = torch.empty(need, dtype=torch.uint8, device="cuda"), []
+    for gap in (0, 64):
+        at = np.cumsum([0] + [s.numel + gap for s in specs])
+        slab, loss = torch.zeros(int(at[-1]), device="cuda"), ctypes.c_double()
+        ptrs = (ctypes.c_void_p * len(specs))(*[slab.data_ptr() + 4 * int(a) for a in at[:-1]])
+        assert sess.lib.zgr_cloud_backward(sess.ctx, ctypes.byref(b), ptrs, len(specs), ctypes.byref(loss), work.data_ptr(), need) == 0
+        out.append([slab[int(a):int(a) + s.numel].clone() for a, s in zip(at, specs)])
+    for x, y, s in zip(*out, specs):
+        assert torch.equal(x, y), s.name
+    sess.close()
+
+
 def test_lsq_gradient_through_the_same_entry_point():
     cfg = I.CONFIGS["cfg1"]
     sess, specs, P = _setup(cfg, scale=1.0)
