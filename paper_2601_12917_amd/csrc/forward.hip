@@ -1749,13 +1749,13 @@ hipError_t launch_layernorm(int dtype, const float* x, const void* g, const void
 //   257 to 319 tiles     1.1 - 1.2 at K = 768, 1.05 - 1.08 at 1024, 0.95 at 2048 (eight waves a tile, a few CUs with a second round of them)
 //   320 to 511 tiles     2.7 at K = 32, 1.2 at 128, 1.00 - 1.06 at 512, 0.94 - 1.01 at 768, 0.91 - 0.97 at 1024
 // From 512 on the tiles are the faster form (2048 x 2304 x 768, 1152 tiles: 81 us against 93).
-static bool product_is_faster(int M, int N, int K, int models) {
-  const int64_t tiles = (((int64_t)M + 63) / 64) * (((int64_t)N + 63) / 64) * models;
+static bool product_is_faster(int M, int N, int K) {
+  const int64_t tiles = (((int64_t)M + 63) / 64) * (((int64_t)N + 63) / 64);
   if (tiles >= 512) return false;
   return K >= (tiles <= 128 ? 64 : tiles <= 256 ? 512 : tiles < 320 ? 2048 : 768);
 }
 
-// Which fp32 projections (K a multiple of 32) go to the bf16 instructions' planes, by tiles of 128 x 128 and of 64 x 64 over both models; the kernels below
+// Which fp32 projections (K a multiple of 32) go to the bf16 instructions' planes, by one model's tiles of 128 x 128 and of 64 x 64; the kernels below
 // are the faster ones elsewhere (us with GELU, then those of the planes):
 //   shared:   2048 x 4096 (512 tiles) at K = 64 35 / 24, at 512 86 / 63; 2048 x 2048 (256) at 128 19.6 / 22.6, at 256 28.4 / 27.8, at 512 46 / 39;
 //             2048 x 1024 (128) at 512 26 / 33; 385 x 50272 x 768 (1572) 335 / 252, 4096 x 2048 x 8192 980 / 743
@@ -1773,19 +1773,19 @@ hipError_t launch_gemm(int dtype, const void* A, const void* W, const void* bias
   const GemmTwin gt{shared_a ? 0 : (int64_t)M * K * es, tw.w, (int64_t)M * N * (epi == EPI_RESID || epi == EPI_F32 ? 4 : es), tw.w, 0};
   if (dtype == 0) {
     const bool mfma_ok = K % 4 == 0 && (((uintptr_t)A | (uintptr_t)W | (uintptr_t)tw.w) & 15) == 0;
-    const long t128 = (long)((M + 127) / 128) * ((N + 127) / 128) * n;
+    const long t128 = (long)((M + 127) / 128) * ((N + 127) / 128);      // of one model
     if (mfma_ok && !keep_order && K % kPlaneK == 0) {
-      const int64_t t64 = (int64_t)((M + 63) / 64) * ((N + 63) / 64) * n;
+      const int64_t t64 = (int64_t)((M + 63) / 64) * ((N + 63) / 64);
       if (planes_shared(t128, K)) return launch_gemm_planes<true>((const float*)A, (const float*)W, M, N, K, ep, gt, n, s);
       if (planes_private(t64, K)) return launch_gemm_planes<false>((const float*)A, (const float*)W, M, N, K, ep, gt, n, s);
     }
     if (mfma_ok && t128 >= 512)   // enough 128 x 128 tiles for two blocks on every CU
       hipLaunchKernelGGL((gemm_f32_mfma_kernel<2, 16>), dim3((N + 127) / 128, (M + 127) / 128, n), dim3(256), 0, s, (const float*)A, (const float*)W, M, N, K, ep, gt);
-    else if (mfma_ok && !keep_order && product_is_faster(M, N, K, n)) {
+    else if (mfma_ok && !keep_order && product_is_faster(M, N, K)) {
       ProductArgs p;
       p.A = A; p.lda = K; p.B = W; p.b_k = true; p.ldb = K; p.C = (float*)out; p.ldc = N; p.M = M; p.N = N; p.K = K;
       p.epilogue = epi; p.bias = (const float*)bias; p.scratch = scratch; p.scratch_floats = scratch_floats;
-      p.batches = n; p.a_outer = gt.a / 4; p.b_outer = p.bias_outer = tw.w / 4; p.c_outer = (int64_t)M * N;
+      p.batches = p.models = n; p.a_outer = gt.a / 4; p.b_outer = p.bias_outer = tw.w / 4; p.c_outer = (int64_t)M * N;
       return launch_product(p, s);
     }
     else if (mfma_ok)
@@ -1855,7 +1855,7 @@ static hipError_t launch_attention_t(const T* qkv, T* ctx, const int32_t* length
   // 32 heads, no causal mask: 174 us against 188, 4 x 2047: 180 against 334, 128 x 33: 21 against 28; only with few waves, 64 x 128, does it lose,
   // 65 against 57).  fp32: only on long sequences without a causal mask that fill the chip (3 x 2047: 175 against 181, 4 x 2047: 182 against
   // 237; 8 x 1024: 151 against 144, 2 x 2047: 178 against 168).
-  const bool by_key = dh == 8 && (sizeof(T) == 2 || (!causal && seq > 1024 && (int64_t)heads * ((seq + 31) / 32) >= 6144));
+  const bool by_key = dh == 8 && (sizeof(T) == 2 || (!causal && seq > 1024 && (int64_t)batch * n_head * ((seq + 31) / 32) >= 6144));
   if (keep_order || by_key) {
     const dim3 grid((unsigned)heads * (unsigned)((seq + 255) / 256));
     switch (dh) {

@@ -20,6 +20,7 @@ struct ProductArgs {
   float* a_sums = nullptr;          // when not NULL: a_sums[i] = sum_k A[i][k] (fp32 A contiguous along i, one batch)
   int batches = 1, zdiv = 1;
   int64_t a_outer = 0, a_inner = 0, b_outer = 0, b_inner = 0, c_outer = 0, c_inner = 0;
+  int models = 1;                   // the batches are those of that many models on the same inputs; each one's sums take the order they take by themselves
   int row_blocks = 1;               // M is that many equal blocks of rows; each one's sums take the order they take in a product of its own
   float* scratch = nullptr; size_t scratch_floats = 0;    // for the parts of a split sum; without it sums are split inside workgroups only
 };

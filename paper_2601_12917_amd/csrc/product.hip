@@ -528,9 +528,9 @@ bool near_operand(const void* p, int dtype, bool along_k, int64_t ld, int n, int
 hipError_t launch_product(const ProductArgs& p, hipStream_t s) {
   if (p.M < 1 || p.N < 1 || p.batches < 1) return hipSuccess;
   if (p.K < 0 || p.batches > 65535 || p.zdiv < 1 || (p.a_sums && (p.a_k || p.a_dtype != 0 || p.batches != 1))) return hipErrorInvalidValue;
-  if (p.row_blocks < 1 || p.M % p.row_blocks || (p.row_blocks > 1 && (p.batches != 1 || p.a_k))) return hipErrorInvalidValue;
+  if (p.models < 1 || p.batches % p.models || p.row_blocks < 1 || p.M % p.row_blocks || (p.row_blocks > 1 && (p.batches != 1 || p.a_k))) return hipErrorInvalidValue;
   const int rows = p.M / p.row_blocks;
-  const int64_t tiles = (((int64_t)rows + 63) / 64) * (((int64_t)p.N + 63) / 64) * p.batches;
+  const int64_t tiles = (((int64_t)rows + 63) / 64) * (((int64_t)p.N + 63) / 64) * (p.batches / p.models);
   const int steps = (p.K + kStep - 1) / kStep;
   // Two fp32 operands.  Two waves per SIMD hide each other's loads (one: 10.35 ms for the backward pass of a 24-block, 1024-wide encoder on 231
   // tokens, two: 10.06).  With fewer pieces than that four waves share each, or eight where blocks of four would leave CUs with one (385 x 768 x 768:
@@ -541,7 +541,7 @@ hipError_t launch_product(const ProductArgs& p, hipStream_t s) {
   const bool planes = p.a_dtype == 1 || p.b_dtype == 1;
   int split = tiles >= kWaves || steps < 4 ? 1 : (planes || tiles >= 320 || steps < 32 ? 4 : 8);
   int parts = 1;
-  const bool few = p.batches == 1 || (p.batches == 2 && p.zdiv == 1);      // one product, or that of two models
+  const bool few = p.batches == p.models && p.zdiv == 1;      // one product, or that of two models
   if (few && p.scratch && split > 1) {
     int64_t z = (planes ? kWaves / 2 : kWaves) / (tiles * split);
     const int64_t room = (int64_t)(p.scratch_floats / ((size_t)rows * ((size_t)p.N + 1) * (size_t)p.batches));

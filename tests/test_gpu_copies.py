@@ -1,6 +1,6 @@
 """zgr_step with room for two copies of the parameters (Z generated once for both forward passes and the restoration) against
 the same step with the smallest workspace, where the three perturbations are applied in place one after the other: the
-parameters come out the same bit for bit, and the losses within the order of their sums."""
+parameters and the losses come out the same bit for bit, and a loss of the perturbed parameters is the step's."""
 import numpy as np
 import pytest
 
@@ -23,15 +23,20 @@ CASES = {
     "bf16 rank 16": (I.shrink(I.CONFIGS["cfg3"], d_model=256, n_head=4, d_ff=576, k=16, k_full=24, **_SMALL), 32),
     "bf16 rank 16 by 8": (I.shrink(I.CONFIGS["cfg3"], d_model=256, n_head=4, d_ff=576, k=16, k_full=16, **_SMALL), 16),
     "bf16 many tiles": (I.shrink(I.CONFIGS["cfg3"], d_model=512, n_head=8, d_ff=1088, k=8, k_full=8, **_SMALL), 32),
+    # sizes at which two models' tiles would cross a line of the fp32 projections that one's don't, sums split over blocks, and heads of 8
+    "f32 two products": (I.shrink(I.CONFIGS["cfg2"], d_model=96, n_head=12, d_ff=4096, k=4, k_full=4, n_layer=1, vocab=300, max_pos=40, batch=1, seq=29), 32),
+    "f32 shared": (I.shrink(I.CONFIGS["cfg2"], d_model=256, n_head=4, d_ff=768, k=4, k_full=4, n_layer=1, vocab=4500, max_pos=70, batch=16, seq=64), 32),
+    "f32 wide": (I.shrink(I.CONFIGS["cfg2"], d_model=768, n_head=12, d_ff=3072, k=4, k_full=4, n_layer=1, vocab=3000, max_pos=40, batch=2, seq=33), 32),
+    "f32 odd": (I.shrink(I.CONFIGS["cfg2"], d_model=72, n_head=9, d_ff=140, k=4, k_full=4, n_layer=2, vocab=300, max_pos=40, batch=7, seq=31), 32),
     "encoder post-LN": (I.shrink(I.CONFIGS["cfg4"], d_model=128, n_head=2, d_ff=192, k=16, k_full=16, post_ln=True, act="relu", **_SMALL), 32),
 }
 
 
-def _sessions(monkeypatch, cfg, bits, fuse_lr=None, stream=False):
+def _sessions(monkeypatch, cfg, bits, fuse_lr=None, stream=False, shares=(0.25, 0.0)):
     specs, values, bases = inputs_of(cfg)
     arrays = make_batch_arrays(cfg)
     out = []
-    for share in (0.25, 0.0):
+    for share in shares:
         monkeypatch.setattr(Session, "COPIES_SHARE", share)
         sess = make_session(cfg, specs, values, bases, bits=bits, fuse_lr=fuse_lr)
         if stream:
@@ -48,17 +53,22 @@ def _sessions(monkeypatch, cfg, bits, fuse_lr=None, stream=False):
 @pytest.mark.parametrize("name", list(CASES))
 def test_step_with_copies_equals_step_in_place(monkeypatch, name, stream):
     cfg, bits = CASES[name]
-    (a, ba), (b, bb) = _sessions(monkeypatch, cfg, bits, stream=stream)
-    tol = 1e-5 if cfg.dtype == "f32" else 2e-3          # losses: order of fp32 sums, and where bf16 activations round after it
+    (a, ba), (b, bb), (c, bc) = _sessions(monkeypatch, cfg, bits, stream=stream, shares=(0.25, 0.0, 0.25))
     for step in range(2):
         ra, rb = a.step(step, ba), b.step(step, bb)
-        assert abs(ra[0] - rb[0]) <= tol * abs(rb[0]) and abs(ra[1] - rb[1]) <= tol * abs(rb[1]), (ra, rb)
+        assert ra == rb
+        c.perturb(step, cfg.eps)                          # the step by hand
+        assert c.loss(bc) == ra[0]
+        c.perturb(step, -2 * np.float32(cfg.eps))
+        assert c.loss(bc) == ra[1]
+        c.perturb(step, cfg.eps)
         for i in range(len(a.params)):
             assert np.array_equal(a.get_theta(i), b.get_theta(i)), (step, a.params[i].name)
-        a.apply_update(step, 0.7, 1e-3), b.apply_update(step, 0.7, 1e-3)
+        for sess in (a, b, c):
+            sess.apply_update(step, 0.7, 1e-3)
     # what reads the caller's parameters between the steps reads the restored ones
-    assert abs(a.loss(ba) - b.loss(bb)) <= tol * abs(b.loss(bb))
-    a.close(); b.close()
+    assert a.loss(ba) == b.loss(bb) == c.loss(bc)
+    a.close(); b.close(); c.close()
 
 
 @pytest.mark.parametrize("name", ["linear", "f32 rank 20", "bf16 rank 16"])
