@@ -150,8 +150,10 @@ size_t zgr_workspace_bytes(const zgr_model* model, const zgr_tensor* tensors, in
  * generated once for the two forward passes and the restoration instead of
  * three times, with the same results bit for bit.  What zgr_workspace_bytes
  * asks for is enough for every call; with less than this the perturbations are
- * applied in place one after the other.  Without a model (ZGR_ARCH_NONE) the
- * two sizes are equal.                                                         */
+ * applied in place one after the other.  The larger size is the smaller one plus
+ * twice the parameters' bytes, each tensor rounded up to 256, and the
+ * activations of a second model.  Without a model (ZGR_ARCH_NONE) the two sizes
+ * are equal.                                                                   */
 size_t zgr_workspace_bytes_copies(const zgr_model* model, const zgr_tensor* tensors, int32_t n_t,
                                   int32_t max_batch, int32_t max_seq);
 

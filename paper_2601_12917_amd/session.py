@@ -26,14 +26,18 @@ def _align(x, a=256):
 
 
 class Session:
-    COPIES_SHARE = 0.25        # of the free device memory: the most that the copies zgr_step works faster with may take
+    COPIES_SHARE = 0.25        # of the free device memory: the most that the step's copies may take where the caller leaves the choice
 
     def __init__(self, arch, dtype, params: Sequence[ParamSpec], seed, eps, alpha, scale_mode=B.ZGR_SCALE_UNIT,
                  gauss_bits=32, n_layer=0, d_model=0, n_head=0, d_ff=0, vocab=0, max_pos=0, n_class=0, ln_eps=1e-5,
-                 max_batch=1, max_seq=2, device="cuda:0", pack_after=(), fuse_lr=None, act="gelu", post_ln=False):
+                 max_batch=1, max_seq=2, device="cuda:0", pack_after=(), fuse_lr=None, act="gelu", post_ln=False,
+                 copies: Optional[bool] = None):
         """pack_after: names of tensors that must start right where the previous one ends
         (Wk, Wv after Wq; bk, bv after bq).  fuse_lr: a learning rate makes step() end with the fused
-        restore + update pass (apply_update is then not to be called)."""
+        restore + update pass (apply_update is then not to be called).  copies: whether the workspace has room for two copies of
+        the parameters, and the activations of two models, with which step() is up to 1.8 times as fast and gives the same bits.  They take
+        2 x the parameters' bytes and more; None takes them up to COPIES_SHARE of the device memory that is free (and up to
+        64 MiB in any case), False saves them for a client that is short of memory."""
         self.lib = B.lib()
         self.dev = torch.device(device)
         torch.cuda.set_device(self.dev)
@@ -73,12 +77,18 @@ class Session:
         nbytes = self.lib.zgr_workspace_bytes(C.byref(self.model), self.table, len(self.params), max_batch, max_seq)
         if nbytes == 0:
             raise B.ZgrError(B.ZGR_ERR_SHAPE, "zgr_workspace_bytes rejected the arguments")
-        # room for the step's two copies of the parameters where they are a small part of what the device has left (asking costs 1 ms)
         larger = self.lib.zgr_workspace_bytes_copies(C.byref(self.model), self.table, len(self.params), max_batch, max_seq)
-        if self.COPIES_SHARE > 0 and (larger - nbytes < 1 << 26 or larger - nbytes <= self.COPIES_SHARE * torch.cuda.mem_get_info(self.dev)[0]):
-            nbytes = larger
+        want = copies
+        if want is None:                                  # asking for the free memory costs 1 ms
+            want = self.COPIES_SHARE > 0 and (larger - nbytes < 1 << 26 or larger - nbytes <= self.COPIES_SHARE * torch.cuda.mem_get_info(self.dev)[0])
+        try:
+            self.workspace = torch.empty(larger if want else nbytes, dtype=torch.uint8, device=self.dev)
+        except torch.cuda.OutOfMemoryError:
+            if copies or not want:
+                raise
+            self.workspace = torch.empty(nbytes, dtype=torch.uint8, device=self.dev)
+        nbytes = self.workspace.numel()
         self.with_copies = nbytes == larger
-        self.workspace = torch.empty(nbytes, dtype=torch.uint8, device=self.dev)
         self.stream = torch.cuda.current_stream(self.dev)
         self.ctx = C.c_void_p()
         st = self.lib.zgr_init(C.byref(self.ctx), C.byref(self.model), self.table, len(self.params), C.byref(self.config),

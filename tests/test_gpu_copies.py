@@ -124,3 +124,29 @@ def test_row_losses_of_a_step_outlive_a_later_loss(name):
     assert np.array_equal(sess.step_row_losses(1, n), before)
     del keep
     sess.close()
+
+
+def test_copies_are_the_callers_choice(monkeypatch):
+    """Asked for or refused by the caller; left to the session, a device too full for them is no error."""
+    import torch
+    params = [ParamSpec("w", I.ROLE_LSQ_W, 0, 0, np.ones((8, 12), np.float32))]
+    make = lambda **kw: Session(B.ZGR_ARCH_LINEAR_LSQ, "f32", params, seed=9, eps=1e-2, alpha=1.0, max_batch=6, **kw)
+    sizes = {}
+    for copies in (None, True, False):
+        sess = make(copies=copies)
+        sizes[copies] = sess.workspace.numel()
+        assert sess.with_copies == (copies is not False)
+        sess.close()
+    assert sizes[None] == sizes[True] > sizes[False]
+    empty = torch.empty
+
+    def full(n, *a, **kw):
+        if n == sizes[True]:
+            raise torch.cuda.OutOfMemoryError("full")
+        return empty(n, *a, **kw)
+    monkeypatch.setattr(torch, "empty", full)
+    sess = make()
+    assert not sess.with_copies and sess.workspace.numel() == sizes[False]
+    sess.close()
+    with pytest.raises(torch.cuda.OutOfMemoryError):
+        make(copies=True)
