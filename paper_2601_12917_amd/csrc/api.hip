@@ -979,7 +979,7 @@ struct BwCarve {
   size_t split = 0;                  // parts of split sums
   size_t total = 0;
 };
-constexpr size_t kSumArena = (size_t)1 << 23;          // floats: the chunk sums of 8 blocks of the 125M model, 2 of the 1.3B model
+constexpr size_t kSumArena = (size_t)1 << 23;          // floats at most: the chunk sums of 8 blocks of the 125M model, 2 of the 1.3B model
 constexpr size_t kProductScratch = ((size_t)1 << 20) + ((size_t)1 << 14);      // floats: split sums take 2048 waves at most, eight to a 64 x 64 result, and 64 row sums each
 
 BwCarve bw_carve(const zgr_ctx* c, int batch, int seq) {
@@ -1014,10 +1014,12 @@ BwCarve bw_carve(const zgr_ctx* c, int batch, int seq) {
   v.dqkv = take(M * 3 * d * 4);
   v.attn = take(4 * bw_attention_scratch(c->dtype, (int)d, m.n_head, batch, seq, m.arch == ZGR_ARCH_DECODER_LM ? 1 : 0));
   v.stats = take(M * 2 * 4);
-  v.part_floats = std::max(kSumArena, bw_scratch_floats((int)d, (int)std::max(std::max(ff, 3 * d), (size_t)m.n_class)));
+  v.mfma = c->dtype == ZGR_BF16 && M % 64 == 0;
+  // those of the whole pass where they are fewer: two LayerNorms a block and the last (or first) one, the biases of four products with bf16 operands
+  const size_t all_sums = (2 * (size_t)m.n_layer + 1) * bw_layernorm_floats((int)M, (int)d) + (v.mfma ? (size_t)m.n_layer * bw_bias_floats((int)M, (int)(5 * d + ff)) : 0);
+  v.part_floats = std::max(std::min(kSumArena, all_sums), bw_scratch_floats((int)d, (int)std::max(std::max(ff, 3 * d), (size_t)m.n_class)));
   v.part = take(4 * v.part_floats);
   v.split = take(kProductScratch * 4);
-  v.mfma = c->dtype == ZGR_BF16 && M % 64 == 0;
   if (v.mfma) {
     // widest contraction of a product: the feed-forward width, the three projections side by side, or (decoder) the
     // vocabulary, rounded up to the multiple of 64 the GEMM takes

@@ -39,6 +39,8 @@ hipError_t launch_bw_transposes_bf16(const TransposeJobs& jobs, hipStream_t s);
 hipError_t launch_bw_gradient_operands(const float* dy, const float* u, int relu, int M, int N, void* cols_out, void* rows_out, float* const* dbias, int n_bias, SumQueue& sums, hipStream_t s);
 // the largest room one column sum or LayerNorm rule takes of the arena, floats
 size_t     bw_scratch_floats(int d, int n_widest);
+size_t     bw_layernorm_floats(int M, int d);      // chunk sums that launch_bw_layernorm takes from the queue, and what launch_bw_gradient_operands takes for n columns in
+size_t     bw_bias_floats(int M, int n);           // up to four calls
 hipError_t launch_bw_fill(float* p, int64_t n, float v, hipStream_t s);
 // row_loss of logits [rows, n] (0 where the target is negative), and (softmax - onehot(target)) inv_count in place of the logits or, with d16,
 // in bf16 at d16 [rows, ld16] with zeros past n; rows with a target outside [0, n) become zeros

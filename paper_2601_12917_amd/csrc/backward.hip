@@ -889,12 +889,17 @@ hipError_t launch_bw_cross_entropy(float* logits, const int32_t* targets, int ro
   return hipGetLastError();
 }
 
+static bool ln_wave_form(int d) { return d % 4 == 0 && d <= 2048; }
+static int ln_blocks(int M) { return M < 4 * kLnBlocks ? (M + 3) / 4 : kLnBlocks; }
+size_t bw_layernorm_floats(int M, int d) { return ((size_t)2 * (ln_wave_form(d) ? ln_blocks(M) : kColParts) * d + 63) / 64 * 64; }
+size_t bw_bias_floats(int M, int n) { const size_t tiles = (size_t)(M + 63) / 64; return std::min(tiles, (size_t)kColParts) * n + 4 * 64; }
+
 hipError_t launch_bw_layernorm(int dtype, const float* x, const void* g, const float* dy, const float* add, float* dx_out, float* stats, float* dg, float* db,
                                SumQueue& sums, int M, int d, float eps, hipStream_t s) {
   float* part = nullptr;
   auto queue = [&](int parts) { sums.add(SumJob{part, dg, (int64_t)2 * d, parts, d}); sums.add(SumJob{part + d, db, (int64_t)2 * d, parts, d}); };
-  if (d % 4 == 0 && d <= 2048) {
-    const int blocks = M < 4 * kLnBlocks ? (M + 3) / 4 : kLnBlocks;
+  if (ln_wave_form(d)) {
+    const int blocks = ln_blocks(M);
     const dim3 grid((unsigned)blocks);
     const hipError_t e = sums.take((size_t)2 * blocks * d, 2, &part);
     if (e != hipSuccess) return e;

@@ -230,6 +230,37 @@ def test_two_runs_agree_bit_for_bit(dtype):
         assert bool((a == b).all()), s_.name
 
 
+@pytest.mark.parametrize("kw", [
+    dict(dtype="bf16", n_layer=8, d_model=64, n_head=1, d_ff=64, batch=4, seq=16),                       # ten sums a block: more than 64 of them
+    dict(dtype="bf16", n_layer=8, d_model=64, n_head=1, d_ff=128, batch=4, seq=16, post_ln=True, act="relu"),
+    dict(dtype="f32", n_layer=4, d_model=2048, n_head=32, d_ff=64, batch=64, seq=16),                    # few sums, whose chunks fill the arena (2^23 floats)
+], ids=["jobs", "jobs post-LN", "room"])
+def test_sums_over_rows_of_more_blocks_than_are_kept_back(kw):
+    """Bias and LayerNorm gradients of every block where their chunk sums are added up in the middle of the pass and the space used again."""
+    cfg = I.shrink(I.CONFIGS["cfg2"], **dict(TINY_LM, name="bw_sums_kept", vocab=37, max_pos=16, **kw))
+    sess, specs, P = _setup(cfg, scale=2.0)
+    arrays = _batch(cfg, 4)
+    _, grads = _device(sess, cfg, arrays)
+    _, want = _oracle(cfg, P, arrays)
+    floor = 1e-6 * max(np.abs(g).max() for g in want.values())
+    for g, s in zip(grads, specs):
+        w = want[s.name]
+        if s.rows > 1 or s.role == I.ROLE_BK:
+            continue
+        if cfg.dtype == "f32":
+            assert np.abs(g - w).max() <= 2e-4 * np.abs(w).max() + floor, s.name
+        else:
+            assert (g * w).sum() >= 0.99 * np.linalg.norm(g) * np.linalg.norm(w) and abs(np.linalg.norm(g) / np.linalg.norm(w) - 1) <= 0.1, s.name
+    sess.close()
+
+
+def test_workspace_of_a_small_model_is_small():
+    """Nothing in it is sized for large models: 3 x 37 tokens of a 2-block, 64-wide decoder, where split sums (4.3 MB) take the most."""
+    sess, _, _ = _setup(I.shrink(I.CONFIGS["cfg2"], **TINY_LM))
+    assert 0 < sess.lib.zgr_cloud_backward_workspace(sess.ctx, 3, 37) <= 6 << 20
+    sess.close()
+
+
 @pytest.mark.parametrize("dtype,d,n_head,batch,seq", [("f32", 768, 12, 4, 128), ("f32", 512, 8, 1, 2048), ("bf16", 512, 8, 1, 2047), ("bf16", 512, 8, 4, 128), ("f32", 40, 5, 2, 19)])
 def test_gradients_do_not_depend_on_where_they_are_written(dtype, d, n_head, batch, seq):
     """Adjacent gradients of Wq, Wk, Wv (and of their biases) are one product: the sums take the order of three all the same.  (Undivided sums in one launch; parts that the
