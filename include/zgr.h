@@ -376,6 +376,10 @@ zgr_status zgr_debug_cossin_table(int32_t gauss_bits, float* cos_out, float* sin
 zgr_status zgr_debug_gemm(int32_t dtype, const void* A, const void* W, const void* bias, void* out, int32_t epilogue,
                           int32_t M, int32_t N, int32_t K, void* hip_stream);
 
+/* The kernel that zgr_debug_gemm takes for fp32 operands of that size (rows 16-byte aligned): 0, 1 tiles of 128 x 128 and of 64 x 64 on the
+ * bf16 matrix instructions, 2, 3 the same on the fp32 ones, 4 the product below, 5 the vector unit; -1 for a size below 1.  For tests.   */
+int32_t zgr_debug_gemm_form(int32_t M, int32_t N, int32_t K);
+
 /* One fp32 product (of the cloud's backward pass, or a small projection of an fp32 model) as the library runs it, all DEVICE: C[i][j] = epilogue(alpha sum_k A[i][k] B[k][j] + bias[j]) in
  * `batches` batches (batch z starts z * a_batch, b_batch, c_batch elements further).  *_dtype: 0 fp32, 1 bf16; *_k: contiguous along
  * k (ld strides the other index) or along the other index (ld strides k).  a_sums (may be NULL): a_sums[i] = sum_k A[i][k] for an

@@ -1513,6 +1513,8 @@ zgr_status zgr_debug_gemm(int32_t dtype, const void* A, const void* W, const voi
   return ZGR_OK;
 }
 
+int32_t zgr_debug_gemm_form(int32_t M, int32_t N, int32_t K) { return M < 1 || N < 1 || K < 1 ? -1 : fp32_projection_form(M, N, K, K % 4 == 0, false); }
+
 zgr_status zgr_debug_product(const void* A, int32_t a_dtype, int32_t a_k, int64_t lda, int64_t a_batch, const void* B, int32_t b_dtype, int32_t b_k, int64_t ldb, int64_t b_batch,
                              float* C, int64_t ldc, int64_t c_batch, int32_t M, int32_t N, int32_t K, float alpha, int32_t batches, float* a_sums, int32_t epilogue, const float* bias, float* scratch,
                              size_t scratch_floats, void* hip_stream) {

@@ -27,6 +27,9 @@ hipError_t launch_layernorm(int dtype, const float* x, const void* g, const void
 // shared_a: both models read the same A.  resid: what EPI_RESID adds to, where that is not out itself (sums in the order of the tiles then).
 hipError_t launch_gemm(int dtype, const void* A, const void* W, const void* bias, void* out, int epi, int M, int N, int K, hipStream_t s, float* scratch = nullptr,
                        size_t scratch_floats = 0, bool keep_order = false, Twin tw = {}, bool shared_a = false, const float* resid = nullptr);
+// The kernel of an fp32 projection (zgr.h, zgr_debug_gemm_form).  whole_rows: K % 4 == 0 and 16-byte aligned operands.
+enum { F32_PLANES_128 = 0, F32_PLANES_64 = 1, F32_TILES_128 = 2, F32_TILES_64 = 3, F32_PRODUCT = 4, F32_VECTOR = 5 };
+int        fp32_projection_form(int M, int N, int K, bool whole_rows, bool keep_order);
 // bf16 vocabulary projection fused with cross-entropy: row_loss[m] = logsumexp(A[m] W^T) - (A[m] W^T)[targets[m]] (0 where targets[m] < 0).
 int        ce_partials_per_row(int N);
 hipError_t launch_gemm_ce_bf16(const void* A, const void* W, const int32_t* targets, void* part, float* tlogit, float* row_loss, int M, int N, int K, hipStream_t s, Twin tw = {});

@@ -1765,6 +1765,17 @@ static bool product_is_faster(int M, int N, int K) {
 static bool planes_shared(int64_t t128, int K) { return t128 >= 512 || (t128 >= 256 && K >= 256); }
 static bool planes_private(int64_t t64, int K) { return t64 >= 72 && K >= (t64 > 128 && t64 <= 256 ? 192 : 640); }
 
+int fp32_projection_form(int M, int N, int K, bool whole_rows, bool keep_order) {
+  const int64_t t128 = (int64_t)((M + 127) / 128) * ((N + 127) / 128), t64 = (int64_t)((M + 63) / 64) * ((N + 63) / 64);
+  if (!whole_rows) return F32_VECTOR;
+  if (!keep_order && K % kPlaneK == 0) {
+    if (planes_shared(t128, K)) return F32_PLANES_128;
+    if (planes_private(t64, K)) return F32_PLANES_64;
+  }
+  if (t128 >= 512) return F32_TILES_128;                 // enough 128 x 128 tiles for two blocks on every CU
+  return !keep_order && product_is_faster(M, N, K) ? F32_PRODUCT : F32_TILES_64;
+}
+
 hipError_t launch_gemm(int dtype, const void* A, const void* W, const void* bias, void* out, int epi, int M, int N, int K, hipStream_t s, float* scratch, size_t scratch_floats, bool keep_order, Twin tw, bool shared_a, const float* resid) {
   const float* from = resid ? resid : (const float*)out;
   GemmEpi ep{epi, out, bias, from};
@@ -1772,26 +1783,22 @@ hipError_t launch_gemm(int dtype, const void* A, const void* W, const void* bias
   const int es = dtype == 0 ? 4 : 2, n = tw.models;
   const GemmTwin gt{shared_a ? 0 : (int64_t)M * K * es, tw.w, (int64_t)M * N * (epi == EPI_RESID || epi == EPI_F32 ? 4 : es), tw.w, 0};
   if (dtype == 0) {
-    const bool mfma_ok = K % 4 == 0 && (((uintptr_t)A | (uintptr_t)W | (uintptr_t)tw.w) & 15) == 0;
-    const long t128 = (long)((M + 127) / 128) * ((N + 127) / 128);      // of one model
-    if (mfma_ok && !keep_order && K % kPlaneK == 0) {
-      const int64_t t64 = (int64_t)((M + 63) / 64) * ((N + 63) / 64);
-      if (planes_shared(t128, K)) return launch_gemm_planes<true>((const float*)A, (const float*)W, M, N, K, ep, gt, n, s);
-      if (planes_private(t64, K)) return launch_gemm_planes<false>((const float*)A, (const float*)W, M, N, K, ep, gt, n, s);
+    const float* a = (const float*)A; const float* w = (const float*)W;
+    const dim3 t64((N + 63) / 64, (M + 63) / 64, n), t128((N + 127) / 128, (M + 127) / 128, n);
+    switch (fp32_projection_form(M, N, K, K % 4 == 0 && (((uintptr_t)A | (uintptr_t)W | (uintptr_t)tw.w) & 15) == 0, keep_order)) {     // one model's sizes
+      case F32_PLANES_128: return launch_gemm_planes<true>(a, w, M, N, K, ep, gt, n, s);
+      case F32_PLANES_64:  return launch_gemm_planes<false>(a, w, M, N, K, ep, gt, n, s);
+      case F32_TILES_128:  hipLaunchKernelGGL((gemm_f32_mfma_kernel<2, 16>), t128, dim3(256), 0, s, a, w, M, N, K, ep, gt); break;
+      case F32_TILES_64:   hipLaunchKernelGGL((gemm_f32_mfma_kernel<1, 16>), t64, dim3(256), 0, s, a, w, M, N, K, ep, gt); break;
+      case F32_PRODUCT: {
+        ProductArgs p;
+        p.A = A; p.lda = K; p.B = W; p.b_k = true; p.ldb = K; p.C = (float*)out; p.ldc = N; p.M = M; p.N = N; p.K = K;
+        p.epilogue = epi; p.bias = (const float*)bias; p.scratch = scratch; p.scratch_floats = scratch_floats;
+        p.batches = p.models = n; p.a_outer = gt.a / 4; p.b_outer = p.bias_outer = tw.w / 4; p.c_outer = (int64_t)M * N;
+        return launch_product(p, s);
+      }
+      default: hipLaunchKernelGGL(gemm_f32_kernel, t64, dim3(256), 0, s, a, w, M, N, K, ep, gt); break;
     }
-    if (mfma_ok && t128 >= 512)   // enough 128 x 128 tiles for two blocks on every CU
-      hipLaunchKernelGGL((gemm_f32_mfma_kernel<2, 16>), dim3((N + 127) / 128, (M + 127) / 128, n), dim3(256), 0, s, (const float*)A, (const float*)W, M, N, K, ep, gt);
-    else if (mfma_ok && !keep_order && product_is_faster(M, N, K)) {
-      ProductArgs p;
-      p.A = A; p.lda = K; p.B = W; p.b_k = true; p.ldb = K; p.C = (float*)out; p.ldc = N; p.M = M; p.N = N; p.K = K;
-      p.epilogue = epi; p.bias = (const float*)bias; p.scratch = scratch; p.scratch_floats = scratch_floats;
-      p.batches = p.models = n; p.a_outer = gt.a / 4; p.b_outer = p.bias_outer = tw.w / 4; p.c_outer = (int64_t)M * N;
-      return launch_product(p, s);
-    }
-    else if (mfma_ok)
-      hipLaunchKernelGGL((gemm_f32_mfma_kernel<1, 16>), dim3((N + 63) / 64, (M + 63) / 64, n), dim3(256), 0, s, (const float*)A, (const float*)W, M, N, K, ep, gt);
-    else
-      hipLaunchKernelGGL(gemm_f32_kernel, dim3((N + 63) / 64, (M + 63) / 64, n), dim3(256), 0, s, (const float*)A, (const float*)W, M, N, K, ep, gt);
   } else {
     if (K % GB_K != 0) return hipErrorInvalidValue;
     const bf16_t* a = (const bf16_t*)A; const bf16_t* w = (const bf16_t*)W; const bf16_t* b = (const bf16_t*)bias;
