@@ -10,7 +10,7 @@ enum { EPI_STORE = 0, EPI_GELU = 1, EPI_RESID = 2, EPI_F32 = 3, EPI_CE = 4, EPI_
 
 // Two models on the same batch in one launch (the two loss evaluations of a step): the second's parameters lie w bytes behind the first's, and
 // in every activation and loss its rows follow the first's; its row losses start row_loss floats behind the first's.  M and batch below count one model's rows.  Half the launches, each with twice the blocks: steps of
-// 125M parameters 3.21 -> 2.45 ms (with the tiles' order below), in fp32 4.46 -> 3.56, of 350M 9.07 -> 7.83, of 1.3B 26.1 -> 24.4, of a small decoder 245 -> 164 us.
+// 125M parameters 3.21 -> 2.45 ms (with the tiles' order below), in fp32 4.46 -> 3.56 (kernels chosen by both models' tiles, as they no longer are), of 350M 9.07 -> 7.83, of 1.3B 26.1 -> 24.4, of a small decoder 245 -> 164 us.
 // Every result has the bits that one model's launch gives it: whatever decides the order of a sum looks at one model's sizes.  (bf16 tiles, all of which take the terms in the
 // same order, are chosen by the tiles of both.)
 struct Twin { int models = 1; int64_t w = 0; int64_t row_loss = 0; };

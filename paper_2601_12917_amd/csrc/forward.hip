@@ -1802,7 +1802,8 @@ hipError_t launch_gemm(int dtype, const void* A, const void* W, const void* bias
   } else {
     if (K % GB_K != 0) return hipErrorInvalidValue;
     const bf16_t* a = (const bf16_t*)A; const bf16_t* w = (const bf16_t*)W; const bf16_t* b = (const bf16_t*)bias;
-    // largest tile that still gives every CU a block
+    // largest tile that still gives every CU a block.  The tiles of both models count where there are two: their number is what fills the chip, and all forms
+    // take the terms of a sum in the same order.
     const long t256 = (long)((M + 255) / 256) * ((N + 255) / 256) * n, t128x256 = (long)((M + 127) / 128) * ((N + 255) / 256) * n;
     if ((size_t)M * K >= ((size_t)1 << 31) || (size_t)N * K >= ((size_t)1 << 31)) return hipErrorInvalidValue;   // 32-bit byte offsets
     // 256 x 256 tiles unless their count leaves the last round of 256 CUs less than ~85 % full and 256 x 192 tiles fill it better
