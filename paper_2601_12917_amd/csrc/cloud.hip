@@ -318,7 +318,9 @@ __global__ void __launch_bounds__(64 * kWaves, 2) g_t_kernel(CloudSnaps g, int64
 // blocks, and what is serial (k pivots, one barrier each) stays inside one workgroup.
 // Between sweeps the first round is enough: it fixes the span and which columns are dependent, and the next product takes columns that are orthonormal
 // to a few per cent as well as better ones (8192 x 64, three sweeps: four second rounds of 53 us each became one, the whole basis 1000 us -> 847;
-// the distance to an fp64 computation is the same over sizes, ranks and spectra decaying by up to 1e6).
+// the distance to an fp64 computation is the same over sizes, ranks and spectra decaying by up to 1e6).  Where a spectrum runs through the 1e-6 line rounding decides which of the
+// columns next to it count as dependent, here as with two rounds: of 160 such bases 28 differ by a column or two from fp64's count either way, 8 from each other.  (Second rounds
+// only where a column is left under 1e-4 agree in all 160, but cost 39 us of launches that leave at once, and let a later column decide on an earlier one's last bits.)
 constexpr int kGramRows = 64;        // rows staged at a time
 constexpr int kGramMaxParts = 128;   // partial W at most
 

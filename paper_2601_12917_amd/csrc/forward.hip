@@ -460,7 +460,7 @@ __device__ __forceinline__ void block_barrier() {
 // small, which leaves one rounding of the large sum per sixteen terms.
 // The shared form has two blocks a CU and no registers for that.  Off from fp64 by 0.9e-7 of the norm at K = 768 and 1.0e-7 at 1024 (the fp32 kernels: 1.8e-7 to
 // 5.0e-7, 2.9e-7 to 5.7e-7), shared 4.2e-7 at 768, 7.0e-7 at 2048 (8.1e-7), 14e-7 at 8192 (16e-7).
-// What bounds it: the chip's power at large sizes (4096 x 2048 x 8192 185 TFLOP/s, six times that on the matrix cores; the fp32 instruction 140), the wave's
+// What bounds it: the chip's power at large sizes (4096 x 2048 x 8192 176 TFLOP/s, 185 with planes cut by truncation, six times that on the matrix cores; the fp32 instruction 140), the wave's
 // issue at small ones (2400 cycles a k-tile for 1536 of matrix instructions; 2900 with the reads and transfers in a row).
 // K % 32 == 0 and 16-byte aligned rows; any M, N.
 constexpr int kPlaneK = 32;
