@@ -207,14 +207,14 @@ __global__ void __launch_bounds__(256) generator_kernel(int iters, uint32_t k0, 
       const u32x4 w = philox_call(q, 7, 3, k0, k1);
       acc ^= w.x ^ w.y ^ w.z ^ w.w;
     } else if (PART == 1) {
-      facc += radius_from_odd24((a >> 8) | 1u, tab) + radius_from_odd24((b >> 8) | 1u, tab);
+      facc += radius_from_odd24(odd24(a), tab) + radius_from_odd24(odd24(b), tab);
     } else if (PART == 2) {
-      const TrigHL t = trig_from_u24(a >> 8), u = trig_from_u24(b >> 8);
+      const TrigHL t = trig_from_u24(a), u = trig_from_u24(b);
       facc += t.ch + t.cl + t.sh + t.sl + u.ch + u.cl + u.sh + u.sl + __uint_as_float(t.sign ^ u.sign);
     } else if (PART == 3) {
       float g[4];
-      box_muller((a >> 8) | 1u, b >> 8, tab, g[0], g[1]);
-      box_muller((c >> 8) | 1u, d >> 8, tab, g[2], g[3]);
+      box_muller(odd24(a), b, tab, g[0], g[1]);
+      box_muller(odd24(c), d, tab, g[2], g[3]);
       facc += g[0] + g[1] + g[2] + g[3];
     } else if (PART == 4) {
       float g[4];

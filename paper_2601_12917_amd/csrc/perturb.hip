@@ -145,20 +145,24 @@ enum { kOne = 0, kBatch = 1, kSpread = 2 };
 // qstep[i]), accumulated in the order of the list; since Z is linear in (G, R), a batched pass is the single
 // pass with this combination in place of G and of R and the coefficient 1.
 template <int P, int MODE>
-__device__ __forceinline__ void draw(uint64_t q, uint32_t id_stream, const PerturbArgs& a, const RadiusEntry* tab, float* g) {
+__device__ __forceinline__ void draw(uint32_t q_lo, uint32_t q_hi, uint32_t id_stream, const PerturbArgs& a, const RadiusEntry* tab, float* g) {
   if (MODE != kBatch) {
-    gaussP<P>(philox_call(q, id_stream, a.step, a.k0, a.k1), tab, g);
+    gaussP<P>(philox4x32_10(q_lo, q_hi, id_stream, a.step, a.k0, a.k1), tab, g);
   } else {
 #pragma unroll
     for (int j = 0; j < P; ++j) g[j] = 0.f;
     for (int i = 0; i < a.n_q; ++i) {
       float t[P];
-      gaussP<P>(philox_call(q, id_stream, a.qstep[i], a.k0, a.k1), tab, t);
+      gaussP<P>(philox4x32_10(q_lo, q_hi, id_stream, a.qstep[i], a.k0, a.k1), tab, t);
       const float ci = a.qcoef[i];
 #pragma unroll
       for (int j = 0; j < P; ++j) g[j] = __builtin_fmaf(ci, t[j], g[j]);
     }
   }
+}
+template <int P, int MODE>
+__device__ __forceinline__ void draw(uint64_t q, uint32_t id_stream, const PerturbArgs& a, const RadiusEntry* tab, float* g) {
+  draw<P, MODE>((uint32_t)q, (uint32_t)(q >> 32), id_stream, a, tab, g);
 }
 
 // Where the parameters of one tensor are read and written.
@@ -280,24 +284,37 @@ __global__ void __launch_bounds__(256) perturb_flat_kernel(PerturbArgs a, const 
     const TensorDesc d = load_const(descs + it.tensor);
     const int64_t n = d.rows * d.cols;
     const Places<T> at = places_of<T, MODE>(d, a);
+    // an item starts at a multiple of its length, a power of two: its counters share their upper word
+    const uint32_t q_lo = (uint32_t)it.first, q_hi = (uint32_t)((uint64_t)it.first >> 32);
+    // the next item's vectors were requested a whole item ago and the youngest store is one call old: nothing to sit out
+    auto arrived = [&]() {
 #pragma unroll
-    for (int j = 0; j < kFlatSlots; ++j) {
-      const int g = tid + 256 * j;
-      if (j == kFlatSlots - 1) {
-        // the next item's vectors were requested a whole item ago and the youngest store is one call old: nothing to sit out
+      for (int i = 0; i < kFlatSlots; ++i) wait_here_for(nxt[i]);
+    };
+    if (it.count == 256 * kFlatSlots && (it.first + it.count) * P <= n) {
 #pragma unroll
-        for (int i = 0; i < kFlatSlots; ++i) wait_here_for(nxt[i]);
-      }
-      if (g < it.count) {
-        const int64_t q = it.first + g, e0 = q * P;
+      for (int j = 0; j < kFlatSlots; ++j) {
         float G[P];
-        draw<P, MODE>((uint64_t)q, d.id, a, tab, G);
-        if (e0 + P <= n) {
-          apply_z<T, P, MODE>(at, a, e0, cur[j], G, c);
-        } else {
-          // ragged end of a tensor: element by element
-          for (int i = 0; i < P; ++i)
-            if (e0 + i < n) apply_z_elem<T, MODE>(at, a, e0 + i, G[i], c);
+        draw<P, MODE>(q_lo + (uint32_t)(tid + 256 * j), q_hi, d.id, a, tab, G);
+        if (j == kFlatSlots - 1) arrived();
+        apply_z<T, P, MODE>(at, a, (it.first + tid + 256 * j) * P, cur[j], G, c);
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < kFlatSlots; ++j) {
+        const int g = tid + 256 * j;
+        if (j == kFlatSlots - 1) arrived();
+        if (g < it.count) {
+          const int64_t e0 = (it.first + g) * P;
+          float G[P];
+          draw<P, MODE>(q_lo + (uint32_t)g, q_hi, d.id, a, tab, G);
+          if (e0 + P <= n) {
+            apply_z<T, P, MODE>(at, a, e0, cur[j], G, c);
+          } else {
+            // ragged end of a tensor: element by element
+            for (int i = 0; i < P; ++i)
+              if (e0 + i < n) apply_z_elem<T, MODE>(at, a, e0 + i, G[i], c);
+          }
         }
       }
     }
@@ -653,20 +670,16 @@ __global__ void __launch_bounds__(256) debug_radius_kernel(int bits, const Radiu
   const uint32_t total = bits == 32 ? (1u << 23) : (1u << 16);
   for (uint32_t n = blockIdx.x * blockDim.x + threadIdx.x; n < total; n += gridDim.x * blockDim.x) {
     const uint32_t N = bits == 32 ? ((n << 1) | 1u) : (((n << 1) | 1u) << 7);
-    out[n] = radius_from_odd24(N, tab);
+    out[n] = radius_from_odd24(N << 8, tab);
   }
 }
 
 __global__ void __launch_bounds__(256) debug_cossin_kernel(int bits, float* __restrict__ co, float* __restrict__ so) {
-#pragma clang fp contract(off)
   const uint32_t total = bits == 32 ? (1u << 24) : (1u << 16);
   for (uint32_t n = blockIdx.x * blockDim.x + threadIdx.x; n < total; n += gridDim.x * blockDim.x) {
     const uint32_t m = bits == 32 ? n : (n << 8);
-    const TrigHL t = trig_from_u24(m);
     // the fused kernel multiplies (hi, lo) by the radius; with radius 1 the product is the rounded sum
-    const float one = __uint_as_float(0x3F800000u ^ t.sign);
-    co[n] = __builtin_fmaf(one, t.ch, one * t.cl);
-    so[n] = __builtin_fmaf(one, t.sh, one * t.sl);
+    times_radius(trig_from_u24(m << 8), 1.0f, co[n], so[n]);
   }
 }
 
@@ -699,7 +712,7 @@ hipError_t ensure_radius_table(const RadiusEntry** dev_ptr, hipStream_t s) {
           RadiusEntry& r = host[E * 64 + j];
           r.H = (float)hl;
           r.L = (float)(hl - (double)r.H);
-          r.C = (float)__builtin_ldexp(cj, -E);
+          r.C = (float)__builtin_ldexp(cj, -E - 8);
         }
       host_ready = true;
     }
