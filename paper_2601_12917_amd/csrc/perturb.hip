@@ -10,6 +10,7 @@
 //         generates its slice of R once into LDS, stages U row blocks in LDS,
 //         contracts U R in registers and fuses G, the mix and the axpy.
 #include "internal.h"
+#include "planes.h"
 
 #include <atomic>
 #include <mutex>
@@ -444,102 +445,176 @@ __global__ void __launch_bounds__(256) perturb_tile_kernel(PerturbArgs a, const 
 }
 
 // ------------------------------------------------------------------ tile, U R on the matrix cores (k >= 16)
-// fp32 MFMA 16x16x4.  A wave covers 16 rows x 32P columns per step: lane (n = lane % 16, rg = lane / 16)
-// ends up with rows 4 rg + v (v = 0..3) and, in each of the two column groups g, the P consecutive columns
-// g*16P + P n + j -- one Philox call per (row, group) -- so Z never leaves registers and a lane needs only
-// 2P x 4 accumulators.  The contraction index is l = rg * (kpt/4) + s: a lane reads kpt/4 consecutive floats
-// of its row of U from global memory and one row of the R slice from LDS per step.
+// v_mfma_f32_16x16x32_bf16 on the operands' planes (planes.h).  A wave covers 16 rows x 32P columns of a tile: lane (n = lane % 16,
+// rg = lane / 16) ends up with rows 4 rg + v (v = 0..3) and, in each of the two column groups g, the P consecutive columns
+// g*16P + P n + j -- one Philox call per (row, group) -- so Z never leaves registers.  Eight tiles of 16 columns are contracted at a time, both
+// groups with P = 4, one after the other with P = 8: 32 accumulators.  The lane feeds row n of the wave's slab: eight consecutive entries of U,
+// cut into planes once for the eight tiles.
+// The strip's slice of b R waits in LDS as planes: [plane][l / 8][column], 16 bytes of eight l each, the columns of a tile next to each other.
+// Instructions of a tile: six per 32 terms; 16 terms (or what is left of that many) take three, their six products side by side along
+// the instruction's index (the half-waves rg < 2 and rg >= 2 hold different planes).
+// Bound by the generator's vector instructions where one result is written (1.2e9 bf16 entries of rank 16 in 1.45 ms, 3.3 TB/s; four perturbations at
+// once 4.54 ms), by writes where three are (2.2 ms, 4.4 TB/s).  On v_mfma_f32_16x16x4f32, whose 32 (rank 32: 64) cycles per four terms the vector
+// instructions do not hide, with four waves to a radius table and theta requested one vector ahead, the same passes took 1.49, 4.6 and 2.3 ms, and
+// 302e6 entries of rank 32 487 and 660 us, now 382 and 534.  Z is off from fp64 by 0.7e-7 of its norm at rank 16, 1.1e-7 at 64 (1.0 and 1.6e-7
+// with the fp32 instruction).  Entries of U below 2^-110 lose their last plane.
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kTilePasses = 3;      // runs of the tile list per block of the matrix-core kernel
+constexpr int kTileWaves = 8;       // of 16 rows each, a tile's: one radius table and one slice of R serve them all
+static_assert(16 * kTileWaves == kTileRowsPerIter, "a wave has one slab of a tile");
 
-template <typename T, int P, bool WRITE_Z, int MODE, bool FULL>
-__device__ __forceinline__ void mfma_row_block(const TensorDesc& d, const PerturbArgs& a, float c, const RadiusEntry* tab, const float* Rs,
-                                               float* __restrict__ zout, int64_t row0, int64_t col0, int r0, int nrows,
-                                               int k, int kq4, int wave, int n16, int rg) {
-  constexpr int TC = 32 * P, GC = 16 * P;                     // tile columns, columns per group
-  const int mrow = r0 + 16 * wave + n16;                      // A operand: this lane feeds row (lane % 16) of the slab
-  const bool uvalid = FULL || (mrow < nrows && row0 + mrow < d.rows);
-  const int64_t urow = row0 + mrow;
-  const int ucol = rg * kq4;
-  const int rbase = r0 + 16 * wave + 4 * rg;                  // first of this lane's 4 rows (tile-relative)
-  const int64_t ebase = (row0 + rbase) * d.cols + col0 + (int64_t)P * n16;
-  const Places<T> at = places_of<T, MODE>(d, a);
-  f32x4 acc[2 * P];
-#pragma unroll
-  for (int j = 0; j < 2 * P; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int s0 = 0; s0 < kq4; s0 += 2) {
-    float ua[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) ua[i] = (uvalid && ucol + s0 + i < k) ? basis_at(d, urow, ucol + s0 + i) : 0.f;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const float* rrow = Rs + (rg * kq4 + s0 + i) * TC + P * n16;
-#pragma unroll
-      for (int g = 0; g < 2; ++g)
-#pragma unroll
-        for (int j = 0; j < P; ++j)
-          acc[g * P + j] = __builtin_amdgcn_mfma_f32_16x16x4f32(ua[i], rrow[g * GC + j], acc[g * P + j], 0, 0, 0);
-    }
-  }
-  if (FULL && !WRITE_Z) {
-    // Whole tile: the lane's eight vectors of theta are requested one generator call ahead.  The wait before a
-    // vector is used is a full one (loads and stores share one counter, and with both kinds in flight it cannot
-    // be a partial wait), so whatever was requested last sets its length: with the request a whole call old it
-    // has landed, with the request placed a third of a call earlier, as the scheduler does by itself, it has not.
-    Vec<T, P> xn = load_global<Vec<T, P>>(at.src + ebase);
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      const int v = t >> 1, g = t & 1;
-      const int64_t e0 = ebase + (int64_t)v * d.cols + g * GC;
-      const Vec<T, P> xc = xn;
-      if (t + 1 < 8) {
-        xn = load_global<Vec<T, P>>(at.src + ebase + (int64_t)((t + 1) >> 1) * d.cols + ((t + 1) & 1) * GC);
+__device__ __forceinline__ f32x4 mfma_planes(planes_u32x4 x, planes_u32x4 y, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(planes_bf16x8, x), __builtin_bit_cast(planes_bf16x8, y), c, 0, 0, 0);
+}
+__device__ __forceinline__ void in_this_order() {
 #if defined(__HIP_DEVICE_COMPILE__)
-        __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_sched_barrier(0);
 #endif
-      }
-      float G[P];
-      draw<P, MODE>((uint64_t)e0 / P, d.id, a, tab, G);
-      float z[P];
-#pragma unroll
-      for (int j = 0; j < P; ++j) z[j] = __builtin_fmaf(d.a, G[j], acc[g * P + j][v]);
-      apply_z<T, P, MODE>(at, a, e0, xc, z, c);
-    }
-    return;
-  }
-#pragma unroll
-  for (int v = 0; v < 4; ++v)
-#pragma unroll
-    for (int g = 0; g < 2; ++g)
-      if (FULL || (rbase + v < nrows && row0 + rbase + v < d.rows && col0 + g * GC + P * n16 < d.cols)) {
-        const int64_t e0 = ebase + (int64_t)v * d.cols + g * GC;
-        Vec<T, P> xv;
-        if (!WRITE_Z) xv = load_global<Vec<T, P>>(at.src + e0);
-        float G[P];
-        draw<P, MODE>((uint64_t)e0 / P, d.id, a, tab, G);
-        if (WRITE_Z) {
-#pragma unroll
-          for (int j = 0; j < P; ++j) zout[e0 + j] = __builtin_fmaf(d.a, G[j], acc[g * P + j][v]);
-        } else {
-          float z[P];
-#pragma unroll
-          for (int j = 0; j < P; ++j) z[j] = __builtin_fmaf(d.a, G[j], acc[g * P + j][v]);
-          apply_z<T, P, MODE>(at, a, e0, xv, z, c);
-        }
-      }
 }
 
+// One entry of the tile list, and where a lane's row of U and its part of theta start (rows and columns past the end: the last ones).
+struct Tile {
+  TensorDesc d;
+  int64_t row0, col0;
+  int nrows, n8;            // n8: eights of the rank
+  bool eights;              // the rank is a multiple of 8: rows of U are read eight entries at a time
+};
+__device__ __forceinline__ Tile tile_of(const TensorDesc* descs, const WorkItem* items, int w) {
+  const WorkItem it = load_const(items + w);
+  Tile t;
+  t.d = load_const(descs + it.tensor);
+  t.row0 = it.first >> 32; t.col0 = it.first & 0xFFFFFFFFll;
+  t.nrows = it.count; t.n8 = (t.d.k + 7) >> 3; t.eights = (t.d.k & 7) == 0;
+  return t;
+}
+
+// Eight entries of a lane's row of U as they lie: fp32 (16-byte loads aligned to 4) or 4-bit codes (one load of 4 bytes aligned to 1).
+typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32_a1 __attribute__((aligned(1)));
+struct RawEight { uint32_t w[8]; };
+__device__ __forceinline__ void request_eight(const TensorDesc& d, int64_t row, int c8, RawEight& o) {
+  if (d.Uq) {
+    typedef const u32_a1 __attribute__((address_space(1))) GW;
+    o.w[0] = *reinterpret_cast<GW*>(reinterpret_cast<uintptr_t>(d.Uq + row * d.ldu + 4 * c8));
+  } else {
+    typedef const u32x4_a4 __attribute__((address_space(1))) GV;
+    GV* p = reinterpret_cast<GV*>(reinterpret_cast<uintptr_t>(d.U + row * d.ldu + 8 * c8));
+    const planes_u32x4 lo = p[0], hi = p[1];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { o.w[i] = lo[i]; o.w[4 + i] = hi[i]; }
+  }
+}
+__device__ __forceinline__ void eight_of(const TensorDesc& d, const RawEight& r, float (&u)[8]) {
+  if (d.Uq) {
+    const uint32_t w = r.w[0];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) u[i] = d.qlambda * ((float)((w >> (4 * i)) & 15u) - d.qdelta);
+  } else {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) u[i] = __uint_as_float(r.w[i]);
+  }
+}
+
+// acc[t] = U R for the wave's 16 rows and the 16 columns of tile t, eight tiles from R's entries at Rs on; `first` holds the lane's first eight where t.eights.
+template <int P>
+__device__ __forceinline__ void contract(const Tile& tl, const RawEight& first, const planes_u32x4* Rs, int64_t urow, int n16, int rg, f32x4 (&acc)[8]) {
+  constexpr int TC = 32 * P;
+  const int n8 = tl.n8, plane = n8 * TC;                      // 16-byte entries of a plane of R
+#pragma unroll
+  for (int j = 0; j < 8; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float largest = 0.f;
+  auto cut_u = [&](int l8, int c8, bool in, PlanesOf<3>& o) {
+    float u[8];
+    if (tl.eights) {
+      RawEight r = first;
+      if (l8 > 0) request_eight(tl.d, urow, c8, r);
+      eight_of(tl.d, r, u);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) u[i] = 8 * c8 + i < tl.d.k ? basis_at(tl.d, urow, 8 * c8 + i) : 0.f;
+    }
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      u[2 * w] = in ? u[2 * w] : 0.f; u[2 * w + 1] = in ? u[2 * w + 1] : 0.f;         // past the end: zeros times R's last eight
+      cut_pair_rounded(u[2 * w], u[2 * w + 1], w, o);
+      largest = fmaxf(fmaxf(largest, __builtin_fabsf(u[2 * w])), __builtin_fabsf(u[2 * w + 1]));
+    }
+  };
+  PlanesOf<3> pu;
+  int l8 = 0;
+  for (; n8 - l8 > 2; l8 += 4) {                              // 32 terms
+    const bool in = l8 + rg < n8;
+    const int c8 = in ? l8 + rg : n8 - 1;
+    cut_u(l8, c8, in, pu);
+    const planes_u32x4* r = Rs + c8 * TC + n16;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      const planes_u32x4 q[3] = {r[16 * t], r[plane + 16 * t], r[2 * plane + 16 * t]};
+      for_terms<3, 3>([&](int x, int y) { acc[t] = mfma_planes(pu.p[x], q[y], acc[t]); });
+      if (t & 1) in_this_order();                             // the operands of two tiles at a time: those of all would take 96 registers
+    }
+  }
+  if (l8 < n8) {                                              // 16, or 8
+    const bool low = rg < 2, in = l8 + (rg & 1) < n8;
+    const int c8 = in ? l8 + (rg & 1) : n8 - 1;
+    cut_u(l8, c8, in, pu);
+#pragma unroll
+    for (int w = 0; w < 4; ++w) pu.p[2][w] = low ? pu.p[2][w] : pu.p[0][w];
+    const planes_u32x4* r = Rs + c8 * TC + n16;
+    const planes_u32x4* ra = r + (low ? 0 : 2 * plane);       // U2 R0 and U0 R2
+    const planes_u32x4* rb = r + (low ? plane : 0);           // U1 R1 and U1 R0, then U0 R1 and U0 R0
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      const planes_u32x4 b = rb[16 * t];
+      acc[t] = mfma_planes(pu.p[2], ra[16 * t], acc[t]);
+      acc[t] = mfma_planes(pu.p[1], b, acc[t]);
+      acc[t] = mfma_planes(pu.p[0], b, acc[t]);
+      if (t & 1) in_this_order();
+    }
+  }
+  if (__builtin_expect(__ballot(largest > 3.3e38f) != 0, 0)) {      // infinite or too large for bf16 (a NaN stays one): on the fp32 instruction
+#pragma unroll
+    for (int j = 0; j < 8; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const uint16_t* r = reinterpret_cast<const uint16_t*>(Rs);
+#pragma unroll 1
+    for (int l = rg; l < 8 * n8; l += 4) {
+      const float u = l < tl.d.k ? basis_at(tl.d, urow, l) : 0.f;
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        const int e = ((l >> 3) * TC + 16 * t + n16) * 8 + (l & 7);
+        const float x = low_float(r[e]) + (low_float(r[e + 8 * plane]) + low_float(r[e + 16 * plane]));
+        acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(u, x, acc[t], 0, 0, 0);
+        in_this_order();
+      }
+    }
+  }
+}
+
+// What a lane requests is used one round of calls later: kAhead vectors of theta (and, with a tile's last ones, the next tile's U) are under way while
+// those before them are worked on.  Requested one vector and one call ahead, the pass ran at the latency of the loads: a wait covers every load
+// and store issued before it, and some 10 KB in flight per compute unit are half of what HBM needs at this rate.
+template <typename T, int P> constexpr int vectors_ahead() { return 64 / (int)(sizeof(T) * P); }      // 16 registers
+
 template <typename T, int P, bool WRITE_Z, int MODE>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) perturb_tile_mfma_kernel(PerturbArgs a, const TensorDesc* __restrict__ descs, const WorkItem* __restrict__ items,
+__global__ void __launch_bounds__(64 * kTileWaves) __attribute__((amdgpu_waves_per_eu(4, 8))) perturb_tile_mfma_kernel(PerturbArgs a, const TensorDesc* __restrict__ descs, const WorkItem* __restrict__ items,
                                                                 float c, const RadiusEntry* __restrict__ gtab, float* __restrict__ zout, int kp) {
   extern __shared__ float smem[];
   RadiusEntry* tab = reinterpret_cast<RadiusEntry*>(smem);
-  float* Rs = smem + kRadiusTabEntries * 3;          // [kp][TC]
-  constexpr int TC = 32 * P;
+  planes_u32x4* Rs = reinterpret_cast<planes_u32x4*>(smem + kRadiusTabEntries * 3);      // [3][kp / 8][TC]
+  constexpr int TC = 32 * P, GC = 16 * P;            // tile columns, columns per group
+  constexpr int kAhead = vectors_ahead<T, P>(), kRounds = 8 / kAhead, kGroups = 8 / P;      // kGroups: column groups contracted at a time
+  // the row and the column group of a lane's vector number i
+  auto row_of = [](int i) { return kGroups == 2 ? i >> 1 : i & 3; };
+  auto group_of = [](int i) { return kGroups == 2 ? i & 1 : i >> 2; };
   const int nblk = (int)gridDim.x - a.pull_blocks;               // computing blocks
   if ((int)blockIdx.x >= nblk) { pull_next_stage(a, (int)blockIdx.x - nblk, a.pull_blocks); return; }
-  load_radius_table(tab, gtab);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  load_radius_table<64 * kTileWaves>(tab, gtab);
+#if defined(__HIP_DEVICE_COMPILE__)
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+#else
+  const int wave = (int)threadIdx.x >> 6;
+#endif
+  const int tid = threadIdx.x, lane = tid & 63;
   const int n16 = lane & 15, rg = lane >> 4;
   // Every block takes kTilePasses contiguous runs of the list; the R slice is regenerated only when the column strip
   // changes (see above).  Consecutive block ids go round-robin to the 8 XCDs, so the list is cut into 8 chunks, one
@@ -553,39 +628,149 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))
   const int n_pass = !by_xcd || by_len < 1 ? 1 : (by_len < kTilePasses ? by_len : kTilePasses);
   const int per_xcd = nblk >> 3;
   const int64_t n_runs = (int64_t)nblk * n_pass;          // run r is tiles [r n / R, (r + 1) n / R): lengths differ by at most one
+  int pass = -1, w = 0, w_end = 0;
+  auto advance = [&]() {                             // the block's next tile; false behind the last one
+    if (w + 1 < w_end) { ++w; return true; }
+    while (++pass < n_pass) {
+      const int run = by_xcd ? (((int)blockIdx.x & 7) * n_pass + pass) * per_xcd + ((int)blockIdx.x >> 3) : (int)blockIdx.x;
+      w = (int)((int64_t)run * a.n_tiles / n_runs);
+      w_end = (int)(((int64_t)run + 1) * a.n_tiles / n_runs);
+      if (w < w_end) return true;
+    }
+    return false;
+  };
+  auto u_row = [&](const Tile& t) { const int64_t r = t.row0 + 16 * wave + n16; return r < t.d.rows ? r : t.d.rows - 1; };
+  auto request_u = [&](const Tile& t, RawEight& o) {
+    if (!t.eights) return;
+    const int c8 = t.n8 > 2 ? rg : rg & 1;
+    request_eight(t.d, u_row(t), c8 < t.n8 ? c8 : t.n8 - 1, o);
+  };
+  auto request = [&](const Tile& t, int round, Vec<T, P>* buf) {
+    if (WRITE_Z) return;
+    const T* src = places_of<T, MODE>(t.d, a).src + (t.row0 * t.d.cols + t.col0);
+    const int64_t rows_left = t.d.rows - t.row0, cols_left = t.d.cols - t.col0;
+    const uint32_t last_row = rows_left < kTileRowsPerIter ? (uint32_t)rows_left - 1 : kTileRowsPerIter - 1, last_col = cols_left < TC ? (uint32_t)cols_left - P : TC - P;
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) {
+      const int v = row_of(round * kAhead + i), g = group_of(round * kAhead + i);
+      uint32_t r = 16 * wave + 4 * rg + v, k = g * GC + P * n16;
+      r = r < last_row ? r : last_row; k = k < last_col ? k : last_col;
+      buf[i] = load_global<Vec<T, P>>(src + ((uint64_t)r * (uint32_t)t.d.cols + k));
+    }
+  };
+  if (!advance()) return;                            // uniform over the block: no barrier follows
+  Tile t = tile_of(descs, items, w);
+  Vec<T, P> cur[kAhead], nxt[kAhead];
+  RawEight u8{};
+  request(t, 0, cur);
+  request_u(t, u8);
   int prev_tensor = -1;
   int64_t prev_col0 = -1;
-  for (int pass = 0; pass < n_pass; ++pass) {
-    const int run = by_xcd ? (((int)blockIdx.x & 7) * n_pass + pass) * per_xcd + ((int)blockIdx.x >> 3) : (int)blockIdx.x;
-    const int w_end = (int)(((int64_t)run + 1) * a.n_tiles / n_runs);
-    for (int w = (int)((int64_t)run * a.n_tiles / n_runs); w < w_end; ++w) {
-      const WorkItem it = items[w];
-      const TensorDesc d = descs[it.tensor];
-      const int64_t row0 = it.first >> 32, col0 = it.first & 0xFFFFFFFFll;
-      const int nrows = it.count, k = d.k, kpt = (k + 7) & ~7, kq4 = kpt >> 2;
-      const bool same_strip = it.tensor == prev_tensor && col0 == prev_col0;
-      prev_tensor = it.tensor; prev_col0 = col0;
-      if (!same_strip) __syncthreads();                // table loaded / previous strip's readers of Rs done
-      for (int idx = tid; idx < (same_strip ? 0 : kpt * 32); idx += 256) {
+  for (bool more = true; more;) {
+    const int tensor = load_const(items + w).tensor;
+    const bool same_strip = tensor == prev_tensor && t.col0 == prev_col0;
+    prev_tensor = tensor; prev_col0 = t.col0;
+    if (!same_strip) {
+      const int kpt = 8 * t.n8;
+      __syncthreads();                               // table loaded / previous strip's readers of Rs done
+      for (int idx = tid; idx < kpt * 32; idx += 64 * kTileWaves) {
         const int l = idx >> 5, g = idx & 31;
-        const int64_t col = col0 + (int64_t)g * P;
+        const int64_t col = t.col0 + (int64_t)g * P;
         float r[P];
 #pragma unroll
         for (int j = 0; j < P; ++j) r[j] = 0.f;
-        if (l < k && col < d.cols) {
-          draw<P, MODE>((uint64_t)((int64_t)l * d.cols + col) / P, d.id | 0x80000000u, a, tab, r);
+        if (l < t.d.k && col < t.d.cols) {
+          draw<P, MODE>((uint64_t)((int64_t)l * t.d.cols + col) / P, t.d.id | 0x80000000u, a, tab, r);
 #pragma unroll
-          for (int j = 0; j < P; ++j) r[j] *= d.b;
+          for (int j = 0; j < P; ++j) r[j] *= t.d.b;
         }
+        // column g P + j is column n = g % 16 of tile j of its group: entry 16 tile + n
+        uint16_t* o = reinterpret_cast<uint16_t*>(Rs + (l >> 3) * TC + (g >> 4) * 16 * P + (g & 15)) + (l & 7);
 #pragma unroll
-        for (int j = 0; j < P; ++j) Rs[l * TC + g * P + j] = r[j];
+        for (int j = 0; j < P; j += 2) {
+          PlanesOf<3> q;
+          cut_pair_rounded(r[j], r[j + 1], 0, q);
+#pragma unroll
+          for (int x = 0; x < 3; ++x) {
+            o[x * t.n8 * TC * 8 + 128 * j] = (uint16_t)q.p[x][0];
+            o[x * t.n8 * TC * 8 + 128 * (j + 1)] = (uint16_t)(q.p[x][0] >> 16);
+          }
+        }
       }
-      if (!same_strip) __syncthreads();
-      const bool full = (nrows % 64 == 0) && row0 + nrows <= d.rows && col0 + TC <= d.cols && k == kpt;
-      for (int r0 = 0; r0 < nrows; r0 += 64) {
-        if (full) mfma_row_block<T, P, WRITE_Z, MODE, true>(d, a, c, tab, Rs, zout, row0, col0, r0, nrows, k, kq4, wave, n16, rg);
-        else      mfma_row_block<T, P, WRITE_Z, MODE, false>(d, a, c, tab, Rs, zout, row0, col0, r0, nrows, k, kq4, wave, n16, rg);
+      __syncthreads();
+    }
+    f32x4 acc[8];
+    const Places<T> at = places_of<T, MODE>(t.d, a);
+    const int rbase = 16 * wave + 4 * rg;            // first of this lane's 4 rows (tile-relative)
+    const int64_t origin = t.row0 * t.d.cols + t.col0, ebase = origin + (int64_t)rbase * t.d.cols + (int64_t)P * n16;
+    // the calls' counters share their upper word in all but the tile that crosses 2^32 calls
+    const uint32_t q_hi = (uint32_t)((uint64_t)origin / P >> 32);
+    const bool full = 16 * wave + 16 <= t.nrows && t.row0 + t.nrows <= t.d.rows && t.col0 + TC <= t.d.cols &&
+                      q_hi == (uint32_t)((uint64_t)(origin + (int64_t)(t.nrows - 1) * t.d.cols + TC - 1) / P >> 32);
+    const bool any = 16 * wave < t.nrows;
+    const int nrows = t.nrows;
+    const TensorDesc d = t.d;
+    const int64_t row0 = t.row0, col0 = t.col0;
+    const uint32_t q0 = (uint32_t)((uint64_t)ebase / P), q_row = (uint32_t)((uint64_t)d.cols / P);
+    auto z_of = [&](int v, int g, float* z) {
+#pragma unroll
+      for (int j = 0; j < P; ++j) z[j] = __builtin_fmaf(d.a, z[j], acc[(g % kGroups) * P + j][v]);
+    };
+#pragma unroll
+    for (int round = 0; round < kRounds; ++round) {
+      const bool last = round + 1 == kRounds;
+      if (round * kAhead % (4 * kGroups) == 0) contract<P>(t, u8, Rs + group_of(round * kAhead) * GC, u_row(t), n16, rg, acc);
+      if (last) {
+        more = advance();
+        if (more) t = tile_of(descs, items, w);
+        request_u(t, u8);                            // behind the last tile it is requested again
       }
+      request(t, last ? 0 : round + 1, nxt);
+      in_this_order();
+      auto arrived = [&]() {                         // all that was requested, in front of the round's last store
+        if (WRITE_Z) return;
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i) wait_here_for(nxt[i]);
+        if (last) wait_here_for(u8);
+      };
+      if (full) {
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i) {
+          const int v = row_of(round * kAhead + i), g = group_of(round * kAhead + i);
+          float z[P];
+          draw<P, MODE>(q0 + (uint32_t)v * q_row + 16u * g, q_hi, d.id, a, tab, z);
+          z_of(v, g, z);
+          const int64_t e0 = ebase + (int64_t)v * d.cols + g * GC;
+          if (i + 1 == kAhead) arrived();
+          if (WRITE_Z) {
+#pragma unroll
+            for (int j = 0; j < P; ++j) zout[e0 + j] = z[j];
+          } else {
+            apply_z<T, P, MODE>(at, a, e0, cur[i], z, c);
+          }
+        }
+      } else {
+        arrived();
+        if (any) {
+#pragma unroll
+          for (int i = 0; i < kAhead; ++i) {
+            const int v = row_of(round * kAhead + i), g = group_of(round * kAhead + i);
+            if (rbase + v >= nrows || row0 + rbase + v >= d.rows || col0 + g * GC + P * n16 >= d.cols) continue;
+            const int64_t e0 = ebase + (int64_t)v * d.cols + g * GC;
+            float z[P];
+            draw<P, MODE>((uint64_t)e0 / P, d.id, a, tab, z);
+            z_of(v, g, z);
+            if (WRITE_Z) {
+#pragma unroll
+              for (int j = 0; j < P; ++j) zout[e0 + j] = z[j];
+            } else {
+              apply_z<T, P, MODE>(at, a, e0, cur[i], z, c);
+            }
+          }
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < kAhead; ++i) cur[i] = nxt[i];
     }
   }
 }
@@ -731,13 +916,13 @@ hipError_t ensure_radius_table(const RadiusEntry** dev_ptr, hipStream_t s) {
 }
 
 namespace {
-// Resident blocks of 256 threads per CU for a persistent kernel: the grid is sized to what the register and
+// Resident blocks per CU for a persistent kernel: the grid is sized to what the register and
 // LDS budget really admits, because a block that has to wait for a slot would start its share of the work
 // list only after another block has finished all of its own.
 template <typename K>
-int resident_blocks_per_cu(K kern, size_t dyn_lds, int cap) {
+int resident_blocks_per_cu(K kern, size_t dyn_lds, int cap, int threads = 256) {
   int nb = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kern, 256, dyn_lds) != hipSuccess || nb < 1) nb = 1;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kern, threads, dyn_lds) != hipSuccess || nb < 1) nb = 1;
   return nb < cap ? nb : cap;
 }
 
@@ -749,7 +934,7 @@ struct TileLaunchCache {
   int per_cu = 0;
 };
 template <typename K>
-hipError_t tile_launch_setup(K kern, size_t lds, int cap, TileLaunchCache& cache, int* per_cu) {
+hipError_t tile_launch_setup(K kern, size_t lds, int threads, int cap, TileLaunchCache& cache, int* per_cu) {
   static std::mutex mu;                                  // the caches are shared by every context of the process
   std::lock_guard<std::mutex> lock(mu);
   if (lds > cache.lds_limit) {
@@ -759,7 +944,7 @@ hipError_t tile_launch_setup(K kern, size_t lds, int cap, TileLaunchCache& cache
   }
   if (!(cache.per_cu > 0 && cache.lds == lds)) {
     cache.lds = lds;
-    cache.per_cu = resident_blocks_per_cu(kern, lds, cap);
+    cache.per_cu = resident_blocks_per_cu(kern, lds, cap, threads);
   }
   *per_cu = cache.per_cu;
   return hipSuccess;
@@ -800,16 +985,16 @@ hipError_t launch_tile_t(const PerturbArgs& a_in, float c, float* zout, hipStrea
   PerturbArgs a = a_in;
   const int kp = (a.max_k + 7) & ~7;
   if (a.min_k >= kMfmaMinK) {
-    const size_t lds_m = sizeof(float) * ((size_t)kRadiusTabEntries * 3 + (size_t)kp * 32 * P);
+    const size_t lds_m = sizeof(RadiusEntry) * (size_t)kRadiusTabEntries + 6 * (size_t)kp * 32 * P;      // three planes of two bytes
     const int variant = zout ? 3 : mode_of(a);
     auto km = zout ? perturb_tile_mfma_kernel<T, P, true, kOne>
                    : (variant == kBatch ? perturb_tile_mfma_kernel<T, P, false, kBatch> : (variant == kSpread ? perturb_tile_mfma_kernel<T, P, false, kSpread> : perturb_tile_mfma_kernel<T, P, false, kOne>));
     static TileLaunchCache cache_m[4];
     int per_cu = 1;
-    hipError_t e = tile_launch_setup(km, lds_m, 8, cache_m[variant], &per_cu);
+    hipError_t e = tile_launch_setup(km, lds_m, 64 * kTileWaves, 4, cache_m[variant], &per_cu);
     if (e != hipSuccess) return e;
     const int grid_m = split_grid(a, a.n_tiles, n_cu * per_cu);
-    hipLaunchKernelGGL(km, dim3(grid_m), dim3(256), lds_m, s, a, a.descs, a.tiles, c, tab, zout, kp);
+    hipLaunchKernelGGL(km, dim3(grid_m), dim3(64 * kTileWaves), lds_m, s, a, a.descs, a.tiles, c, tab, zout, kp);
     return hipGetLastError();
   }
   const bool small = a.tile_rows < kTileRowsPerIter;
@@ -829,7 +1014,7 @@ hipError_t launch_tile_t(const PerturbArgs& a_in, float c, float* zout, hipStrea
   }
   static TileLaunchCache cache_v[8];
   int per_cu = 1;
-  hipError_t e = tile_launch_setup(kern, lds, 4, cache_v[variant], &per_cu);
+  hipError_t e = tile_launch_setup(kern, lds, 256, 4, cache_v[variant], &per_cu);
   if (e != hipSuccess) return e;
   const int grid = split_grid(a, a.n_tiles, n_cu * per_cu);
   hipLaunchKernelGGL(kern, dim3(grid), dim3(256), lds, s, a, a.descs, a.tiles, c, tab, zout, kp);

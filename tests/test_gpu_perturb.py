@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 import zgr_inputs as I
+from oracle import dtc as D
 from oracle import perturbation as P
 from tests.util import make_session
 
@@ -185,4 +186,52 @@ def test_mixed_ranks_in_one_context(ranks, dtype):
             assert np.all(np.abs(got - want) <= BF16_RTOL * np.abs(want) + 1e-30) and np.mean(got == want) > 0.98, (j, k)
     want_b = P.axpy_inplace_value(b, c, P.gauss_field(cfg.seed, step, 20, 0, 1, 300), dtype)
     assert np.all(np.abs(sess.get_theta(len(ranks)) - want_b) <= (F32_RTOL if dtype == "f32" else BF16_RTOL) * (np.abs(want_b) + PARAM_SCALE))
+    sess.close()
+
+
+@pytest.mark.parametrize("rows,cols,k,ldu,bits,dtype", [
+    (17, 128, 16, 17, 32, "f32"),       # a second slab of one row; rows of U on 4-byte boundaries
+    (144, 132, 24, 24, 32, "bf16"),     # three eights (a step of 32 terms with eight zeros); a second tile of one whole slab, a strip of 4 columns
+    (129, 256, 40, 43, 16, "bf16"),     # a step of 32 terms and one of 8; eight Gaussians per call
+    (257, 264, 48, 48, 16, "f32"),      # steps of 32 and 16 terms, two vectors of theta per round
+    (256, 128, 56, 56, 32, "f32"),      # 32 and 24
+    (2304, 512, 32, 32, 32, "bf16"),    # several tiles of a strip per block
+])
+def test_matrix_core_tiles_at_their_edges(rows, cols, k, ldu, bits, dtype):
+    sess, cfg, W, U = _session_for(rows, cols, k, dtype=dtype, bits=bits, ldu=ldu)
+    step, c = 9, np.float32(1e-3)
+    for quantised in (False, True):
+        if quantised:
+            lam, delta = D.affine_params(U[:, :k], 4)
+            codes = D.quantize(U[:, :k], lam, delta, 4)
+            U = D.dequantize(codes, lam, delta)
+            sess.set_basis_q4(0, D.pack_nibbles(codes), k, lam, delta)
+        G, R, Z = P.hybrid_z(cfg.seed, step, 3, rows, cols, U, k, cfg.alpha, P.SCALE_UNIT, bits, parts=True)
+        assert np.all(np.abs(sess.fill_z(0, step).astype(np.float64) - Z) <= _z_bound(cfg, G, R, U, k, rows, cols, P.SCALE_UNIT))
+        before = sess.get_theta(0)
+        sess.perturb(step, float(c))
+        want, got = P.axpy_inplace_value(before, c, Z, dtype), sess.get_theta(0)
+        if dtype == "f32":
+            assert np.all(np.abs(got - want) <= F32_RTOL * (np.abs(want) + PARAM_SCALE))
+        else:
+            assert np.all(np.abs(got - want) <= BF16_RTOL * np.abs(want) + 1e-30) and np.mean(got == want) > 0.98
+    sess.close()
+
+
+@pytest.mark.parametrize("k", [16, 40])
+def test_basis_entries_beyond_bf16(k):
+    """Entries that bf16 does not hold, and an infinite one, give what fp32 products give; their rows alone are concerned."""
+    rows, cols = 160, 128
+    sess, cfg, W, U = _session_for(rows, cols, k, scale_mode=P.SCALE_PAPER)
+    U = U.copy()
+    U[5, 3], U[70, k - 1], U[130, 0] = 3.4e38, np.inf, -np.inf
+    sess.set_basis(0, U, k)
+    with np.errstate(invalid="ignore", over="ignore"):
+        G, R, Z = P.hybrid_z(cfg.seed, 1, 3, rows, cols, U, k, cfg.alpha, P.SCALE_PAPER, 32, parts=True)
+        bound = _z_bound(cfg, G, R, U, k, rows, cols, P.SCALE_PAPER)
+    got = sess.fill_z(0, 1).astype(np.float64)
+    for r, l, sign in ((70, k - 1, 1.0), (130, 0, -1.0)):
+        assert np.array_equal(got[r], sign * np.sign(R[l]) * np.inf)
+    rest = np.setdiff1d(np.arange(rows), [70, 130])
+    assert np.all(np.abs(got[rest] - Z[rest]) <= bound[rest])
     sess.close()
