@@ -389,6 +389,12 @@ zgr_status zgr_debug_product(const void* A, int32_t a_dtype, int32_t a_k, int64_
                              int64_t ldb, int64_t b_batch, float* C, int64_t ldc, int64_t c_batch, int32_t M, int32_t N, int32_t K, float alpha,
                              int32_t batches, float* a_sums, int32_t epilogue, const float* bias, float* scratch, size_t scratch_floats, void* hip_stream);
 
+/* The weight gradient of the cloud's backward pass for a bf16 model whose token count is no multiple of 64, all DEVICE: with dy <- dy act'(u) (u may be NULL; relu 0
+ * erf-GELU, 1 ReLU), dy fp32 [M, N] and x bf16 [M, K], dW[p] [N / parts, K] = rows p N / parts .. of dy^T x and db[p] the sums of those columns of dy (dW and db:
+ * HOST arrays of `parts` pointers, 1 to 3).  N and K multiples of 64.  scratch: 6 N Mp + 2 K Mp + 4 (N Mp / 64 + 512) bytes or more, Mp: M rounded up to a multiple of 64.  For tests.   */
+zgr_status zgr_debug_weight_gradient(float* dy, const float* u, int32_t relu, const void* x, int32_t M, int32_t N, int32_t K, int32_t parts, float* const* dW, float* const* db,
+                                     void* scratch, size_t scratch_bytes, void* hip_stream);
+
 /* Plain device-to-device copy of `bytes` bytes (a multiple of 16) by a simple kernel: the known-size
  * reference that hardware traffic counters are calibrated against.                                      */
 zgr_status zgr_debug_copy(void* dst, const void* src, size_t bytes, void* hip_stream);

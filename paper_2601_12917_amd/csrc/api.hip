@@ -974,8 +974,9 @@ struct BwCarve {
   size_t xfin = 0, hf = 0, logits = 0, targets = 0, row_loss = 0, loss = 0;
   size_t dx = 0, dt = 0, dff = 0, dqkv = 0, attn = 0, stats = 0;
   size_t part = 0, part_floats = 0;  // chunk sums of the column reductions until they are added up
-  size_t tA = 0, tB = 0, tC = 0, tW = 0, tL[8] = {};     // bf16 operands of the matrix-core products (bf16 models with a token count that is a multiple of 64)
-  bool mfma = false;
+  size_t tA = 0, tB = 0, tW = 0, tC[4] = {}, tL[8] = {};     // bf16 operands of the matrix-core products (bf16 models)
+  bool mfma = false;                 // a token count that is a multiple of 64: gradients are rounded to bf16 for the products
+  bool planes = false;               // any other: the weights' gradients are taken on the planes of fp32 gradients
   size_t split = 0;                  // parts of split sums
   size_t total = 0;
 };
@@ -1015,22 +1016,26 @@ BwCarve bw_carve(const zgr_ctx* c, int batch, int seq) {
   v.attn = take(4 * bw_attention_scratch(c->dtype, (int)d, m.n_head, batch, seq, m.arch == ZGR_ARCH_DECODER_LM ? 1 : 0));
   v.stats = take(M * 2 * 4);
   v.mfma = c->dtype == ZGR_BF16 && M % 64 == 0;
+  v.planes = c->dtype == ZGR_BF16 && M % 64 != 0;
   // those of the whole pass where they are fewer: two LayerNorms a block and the last (or first) one, the biases of four products with bf16 operands
-  const size_t all_sums = (2 * (size_t)m.n_layer + 1) * bw_layernorm_floats((int)M, (int)d) + (v.mfma ? (size_t)m.n_layer * bw_bias_floats((int)M, (int)(5 * d + ff)) : 0);
+  const size_t all_sums = (2 * (size_t)m.n_layer + 1) * bw_layernorm_floats((int)M, (int)d) + (v.mfma || v.planes ? (size_t)m.n_layer * bw_bias_floats((int)M, (int)(5 * d + ff)) : 0);
   v.part_floats = std::max(std::min(kSumArena, all_sums), bw_scratch_floats((int)d, (int)std::max(std::max(ff, 3 * d), (size_t)m.n_class)));
   v.part = take(4 * v.part_floats);
   v.split = take(kProductScratch * 4);
-  if (v.mfma) {
-    // widest contraction of a product: the feed-forward width, the three projections side by side, or (decoder) the
-    // vocabulary, rounded up to the multiple of 64 the GEMM takes
-    const size_t widest = std::max(std::max(ff, 3 * d), m.arch == ZGR_ARCH_DECODER_LM ? align_up((size_t)m.vocab, 64) : (size_t)0);
-    v.tA = take(2 * M * widest);
-    v.tB = take(m.arch == ZGR_ARCH_DECODER_LM ? 2 * M * d : 0);
-    v.tC = take(2 * M * std::max(ff, 3 * d));
-    v.tW = take(m.arch == ZGR_ARCH_DECODER_LM ? 2 * d * align_up((size_t)m.vocab, 64) : 0);
-    // the transposed operands of one block: of FC2, FC1, the attention output and Q, K, V the kept input and the weights
-    const size_t in[4] = {ff, d, d, d}, out[4] = {d, ff, d, 3 * d};
-    for (int i = 0; i < 4; ++i) { v.tL[2 * i] = take(2 * M * in[i]); v.tL[2 * i + 1] = take(2 * in[i] * out[i]); }
+  if (v.mfma || v.planes) {
+    // what the products of FC2, FC1, the attention output and Q, K, V take, until the end of a block: gradients transposed (three planes of them where
+    // they stay fp32), the kept input transposed
+    const size_t in[4] = {ff, d, d, d}, out[4] = {d, ff, d, 3 * d}, Mp = align_up(M, 64);
+    for (int i = 0; i < 4; ++i) { v.tC[i] = take(2 * Mp * out[i] * (v.planes ? 3 : 1)); v.tL[2 * i] = take(2 * Mp * in[i]); }
+    if (v.mfma) {
+      // widest contraction of a product: the feed-forward width, the three projections side by side, or (decoder) the
+      // vocabulary, rounded up to the multiple of 64 the GEMM takes
+      const size_t widest = std::max(std::max(ff, 3 * d), m.arch == ZGR_ARCH_DECODER_LM ? align_up((size_t)m.vocab, 64) : (size_t)0);
+      v.tA = take(2 * M * widest);
+      v.tB = take(m.arch == ZGR_ARCH_DECODER_LM ? 2 * M * d : 0);
+      v.tW = take(m.arch == ZGR_ARCH_DECODER_LM ? 2 * d * align_up((size_t)m.vocab, 64) : 0);
+      for (int i = 0; i < 4; ++i) v.tL[2 * i + 1] = take(2 * in[i] * out[i]);      // the weights transposed
+    }
   }
   v.total = off;
   return v;
@@ -1097,26 +1102,40 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
     const size_t lim = (size_t)1 << 31, Npad = ((size_t)Np + 63) / 64 * 64;
     return v.mfma && (size_t)M * Npad < lim && (size_t)Kp * Npad < lim && (size_t)M * Kp < lim;
   };
+  // and those of the planes of dy
+  auto on_planes = [&](int Np, int Kp) {
+    const size_t lim = (size_t)1 << 31, Mp = ((size_t)M + 63) / 64 * 64;
+    return v.planes && Np % 64 == 0 && Kp % 64 == 0 && 3 * Mp * Np < lim && 3 * Mp * Kp < lim;
+  };
+  // The weights' gradients of a block, which nothing waits for, in one launch at its end.
+  ProductGroup weights;
+  weights.fold = v.planes ? 3 : 1;
+  weights.K = (int)(((size_t)M + 63) / 64 * 64) * weights.fold;
   // One linear layer y = a W^T + b, a [M, Kp] kept in the storage type, W [Np, Kp], with dL/dy = dy (act'(u) dy when u is given): dW = dy^T a, db = column
   // sums, da = dy W.  The layer's outputs may be up to three equal blocks with weights and biases of their own (W's rows in one piece).
   auto linear_backward = [&](float* dy, const float* u, int Np, const void* W, int Kp, const void* a, int blocks, const int* wi, const int* bi, float* da, int which) -> zgr_status {
     float* db[3] = {};
     for (int p = 0; p < blocks; ++p) db[p] = grads[bi[p]];
     const int n = Np / blocks;
-    if (on_bf16(Np, Kp)) {
-      unsigned char* tC = ws + v.tC;
-      HIP_TRY(c, launch_bw_gradient_operands(dy, u, relu, M, Np, tC, ws + v.tA, db, blocks, sums, s));
-      const void* aT = ws + v.tL[2 * which];                  // a and W transposed, written at the start of the block
-      const void* wT = ws + v.tL[2 * which + 1];
-      bool whole = true;                                 // the blocks' weight gradients in one piece: one product
-      for (int p = 1; p < blocks; ++p) whole = whole && grads[wi[p]] == grads[wi[0]] + (size_t)p * n * Kp;
+    bool whole = true;                                   // the blocks' weight gradients in one piece: one product
+    for (int p = 1; p < blocks; ++p) whole = whole && grads[wi[p]] == grads[wi[0]] + (size_t)p * n * Kp;
+    auto queue_weights = [&]() {
+      const unsigned char* dyT = ws + v.tC[which];
       for (int p = 0; p < (whole ? 1 : blocks); ++p)
-        HIP_TRY(c, launch_gemm(ZGR_BF16, tC + (size_t)p * n * M * 2, aT, nullptr, grads[wi[p]], EPI_F32, whole ? Np : n, Kp, M, s));
-      HIP_TRY(c, launch_gemm(ZGR_BF16, ws + v.tA, wT, nullptr, da, EPI_F32, M, Kp, Np, s));
+        weights.job[weights.count++] = GroupedProduct{dyT + (size_t)p * n * weights.K * 2, ws + v.tL[2 * which], grads[wi[p]], whole ? Np : n, Kp};
+    };
+    if (on_bf16(Np, Kp)) {
+      // a and W transposed were written at the start of the block
+      HIP_TRY(c, launch_bw_gradient_operands(dy, u, relu, M, Np, ws + v.tC[which], ws + v.tA, db, blocks, sums, s));
+      queue_weights();
+      HIP_TRY(c, launch_gemm(ZGR_BF16, ws + v.tA, ws + v.tL[2 * which + 1], nullptr, da, EPI_F32, M, Kp, Np, s));
+    } else if (on_planes(Np, Kp)) {
+      HIP_TRY(c, launch_bw_gradient_planes(dy, u, relu, M, Np, ws + v.tC[which], a, Kp, ws + v.tL[2 * which], db, blocks, sums, s));
+      queue_weights();
+      HIP_TRY(c, product(dy, true, Np, W, Kp, da, Kp, M, Kp, Np, nullptr));
     } else {
       if (u) HIP_TRY(c, launch_bw_act(relu, u, dy, (int64_t)M * Np, s));
-      bool whole = true;                                 // the blocks' gradients in one piece, weights and biases: one product, with the bits of one each
-      for (int p = 1; p < blocks; ++p) whole = whole && grads[wi[p]] == grads[wi[0]] + (size_t)p * n * Kp && db[p] == db[0] + (size_t)p * n;
+      for (int p = 1; p < blocks; ++p) whole = whole && db[p] == db[0] + (size_t)p * n;      // and the biases': the bits of one product each
       for (int p = 0; p < (whole ? 1 : blocks); ++p) HIP_TRY(c, product(dy + (size_t)p * n, false, Np, a, Kp, grads[wi[p]], Kp, whole ? Np : n, Kp, M, db[p], whole ? blocks : 1));
       HIP_TRY(c, product(dy, true, Np, W, Kp, da, Kp, M, Kp, Np, nullptr));
     }
@@ -1238,6 +1257,8 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
     // q, k, v = h1 W{q,k,v}^T + b{q,k,v}: three column blocks of dqkv; Wq, Wk, Wv are adjacent, one [3 d, d] matrix
     const int wi[3] = {L.wq, L.wk, L.wv}, bi[3] = {L.bq, L.bk, L.bv};
     if ((st = linear_backward(dqkv, nullptr, 3 * d, T(c, L.wq), d, ws + W.h1, 3, wi, bi, dtb, 3)) != ZGR_OK) return st;
+    HIP_TRY(c, launch_product_group(weights, s));
+    weights.count = 0;
     if (m.post_ln) HIP_TRY(c, launch_bw_add(dx, dtb, nx, s));                                    // h1 = x_in
     else HIP_TRY(c, launch_bw_layernorm(dt, F(W.xin), T(c, L.ln1_g), dtb, dx, dx, F(v.stats), grads[L.ln1_g], grads[L.ln1_b], sums, M, d, m.ln_eps, s));
   }
@@ -1526,6 +1547,25 @@ zgr_status zgr_debug_product(const void* A, int32_t a_dtype, int32_t a_k, int64_
   p.C = C; p.ldc = ldc; p.c_outer = c_batch; p.M = M; p.N = N; p.K = K; p.alpha = alpha; p.batches = batches;
   p.a_sums = a_sums; p.epilogue = epilogue; p.bias = bias; p.scratch = scratch; p.scratch_floats = scratch_floats;
   HIP_TRY(nullptr, launch_product(p, reinterpret_cast<hipStream_t>(hip_stream)));
+  return ZGR_OK;
+}
+
+zgr_status zgr_debug_weight_gradient(float* dy, const float* u, int32_t relu, const void* x, int32_t M, int32_t N, int32_t K, int32_t parts, float* const* dW, float* const* db,
+                                     void* scratch, size_t scratch_bytes, void* hip_stream) {
+  if (!dy || !x || !dW || !db || !scratch) return fail(nullptr, ZGR_ERR_NULL, "NULL argument");
+  if (M < 1 || N < 64 || N % 64 || K < 64 || K % 64 || parts < 1 || parts > 3 || N % parts) return fail(nullptr, ZGR_ERR_SHAPE, "bad shape");
+  const size_t Mp = align_up((size_t)M, 64), planes = align_up(6 * Mp * (size_t)N), rows = align_up(2 * Mp * (size_t)K), floats = bw_bias_floats(M, N);
+  if (scratch_bytes < planes + rows + 4 * floats || ((uintptr_t)scratch & 255)) return fail(nullptr, ZGR_ERR_WORKSPACE, "scratch must hold %zu bytes on a multiple of 256", planes + rows + 4 * floats);
+  unsigned char* ws = reinterpret_cast<unsigned char*>(scratch);
+  hipStream_t s = reinterpret_cast<hipStream_t>(hip_stream);
+  SumQueue sums(reinterpret_cast<float*>(ws + planes + rows), floats, s);
+  HIP_TRY(nullptr, launch_bw_gradient_planes(dy, u, relu, M, N, ws, x, K, ws + planes, db, parts, sums, s));
+  ProductGroup g;
+  g.fold = 3;
+  g.K = (int)(3 * Mp);
+  for (int p = 0; p < parts; ++p) g.job[g.count++] = GroupedProduct{ws + (size_t)p * (N / parts) * g.K * 2, ws + planes, dW[p], N / parts, K};
+  HIP_TRY(nullptr, launch_product_group(g, s));
+  HIP_TRY(nullptr, sums.flush());
   return ZGR_OK;
 }
 

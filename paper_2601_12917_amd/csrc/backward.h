@@ -37,6 +37,10 @@ hipError_t launch_bw_transposes_bf16(const TransposeJobs& jobs, hipStream_t s);
 // a gradient dy [M, N] (both multiples of 64) as both operands, cols_out [N, M] and rows_out [M, N] in bf16, and its column sums: dbias[i] gets
 // those of the i-th of n_bias equal column blocks.  With u != NULL it is dy act'(u) that is taken.
 hipError_t launch_bw_gradient_operands(const float* dy, const float* u, int relu, int M, int N, void* cols_out, void* rows_out, float* const* dbias, int n_bias, SumQueue& sums, hipStream_t s);
+// A gradient dy [M, N] in fp32 (any M, N a multiple of 64) as the first operand of a product group with fold = 3, cols_out [N, 3 x M rounded up to a multiple
+// of 64], and its column sums as above.  With u != NULL dy <- dy act'(u) first.  The second operand as well: x [M, x_cols] in bf16, x_out [x_cols, M rounded up].
+hipError_t launch_bw_gradient_planes(float* dy, const float* u, int relu, int M, int N, void* cols_out, const void* x, int x_cols, void* x_out, float* const* dbias, int n_bias, SumQueue& sums,
+                                     hipStream_t s);
 // the largest room one column sum or LayerNorm rule takes of the arena, floats
 size_t     bw_scratch_floats(int d, int n_widest);
 size_t     bw_layernorm_floats(int M, int d);      // chunk sums that launch_bw_layernorm takes from the queue, and what launch_bw_gradient_operands takes for n columns in

@@ -127,11 +127,103 @@ __global__ void __launch_bounds__(256) operand_kernel(const TIN* __restrict__ in
   }
 }
 
-// The transposed operands of a whole block's products in one launch (whole 64 x 64 tiles, eight values a load and a store): the weights and kept
+// The operand of a weight's gradient from fp32 dy [rows, cols] (cols a multiple of 64) with any number of rows: its planes (planes.h, with a bf16 factor) as three runs of
+// ld terms a row, ld = rows rounded up to a multiple of 64, zeros past the rows: cols_out[c][run ld + r], the smallest plane first.  dy <- act'(u) dy where ACT
+// says so, and part[blockIdx.y][c] as above.  An infinite entry is its first plane and nothing else (Inf - Inf would make a NaN of it).
+// The blocks behind those (blockIdx.x >= cols / 64) write the product's other operand, x [rows, x_cols] transposed.
+// 231 tokens, 4096 columns: 8 us with the activation's slope, which a launch of its own took 5 for (x on its own: 6).
+__device__ __forceinline__ void transpose_tile(const uint16_t* in, int rows, int cols, int r0, int c0, uint16_t* out, int64_t ld, uint16_t (*tile)[72]);
+template <int ACT>
+__global__ void __launch_bounds__(256) gradient_planes_kernel(float* __restrict__ dy, const float* __restrict__ u, int rows, int cols, bf16_t* __restrict__ cols_out, int64_t ld, float* __restrict__ part,
+                                                              int tiles_per_block, const bf16_t* __restrict__ x, int x_cols, bf16_t* __restrict__ x_out) {
+  __shared__ __attribute__((aligned(16))) float tile[64][65];
+  const int tid = threadIdx.x, c4 = (tid & 15) * 4, rq = tid >> 4, c0 = blockIdx.x * 64;
+  if ((int)blockIdx.x >= cols >> 6) {
+    uint16_t (*half)[72] = reinterpret_cast<uint16_t(*)[72]>(tile);
+    const int x0 = ((int)blockIdx.x - (cols >> 6)) * 64;
+    for (int t = 0; t < tiles_per_block; ++t) {
+      const int r0 = ((int)blockIdx.y * tiles_per_block + t) * 64;
+      if (r0 >= ld) break;
+      transpose_tile(reinterpret_cast<const uint16_t*>(x), rows, x_cols, r0, x0, reinterpret_cast<uint16_t*>(x_out), ld, half);
+    }
+    return;
+  }
+  double sum[4] = {0., 0., 0., 0.};
+  for (int t = 0; t < tiles_per_block; ++t) {
+    const int r0 = ((int)blockIdx.y * tiles_per_block + t) * 64;
+    if (r0 >= ld) break;
+    __syncthreads();                                       // the previous tile has been read
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = r0 + rq + 16 * i;
+      Four<float> f{};
+      if (r < rows) {
+        const int64_t o = (int64_t)r * cols + c0 + c4;
+        f = *reinterpret_cast<const Four<float>*>(dy + o);
+        if (ACT) {
+          const Four<float> x = *reinterpret_cast<const Four<float>*>(u + o);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) f.e[q] = act_rule<ACT == 2>(x.e[q], f.e[q]);
+          *reinterpret_cast<Four<float>*>(dy + o) = f;
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) { sum[q] += f.e[q]; tile[rq + 16 * i][c4 + q] = f.e[q]; }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int c = (tid >> 3) + 32 * i, r = (tid & 7) * 8;
+      planes_u32x4 h[3];
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        const float x0 = tile[r + 2 * w][c], x1 = tile[r + 2 * w + 1][c];
+        const uint32_t u0 = __float_as_uint(x0), u1 = __float_as_uint(x1);
+        PlanesOf<3> o;
+        cut_rest(__builtin_fabsf(x0) == INFINITY ? 0.f : x0 - high_float(u0), __builtin_fabsf(x1) == INFINITY ? 0.f : x1 - high_float(u1), 0, o);
+        h[2][w] = high_halves(u1, u0); h[1][w] = o.p[1][0]; h[0][w] = o.p[2][0];
+      }
+#pragma unroll
+      for (int x = 0; x < 3; ++x) *reinterpret_cast<planes_u32x4*>(cols_out + (int64_t)(c0 + c) * 3 * ld + x * ld + r0 + r) = h[x];
+    }
+  }
+  __syncthreads();                                         // sixteen row groups, added in their order
+  double* all = reinterpret_cast<double*>(tile);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) all[rq * 64 + c4 + q] = sum[q];
+  __syncthreads();
+  if (tid < 64) {
+    double v = 0.;
+    for (int g = 0; g < 16; ++g) v += all[g * 64 + tid];
+    part[(size_t)blockIdx.y * cols + c0 + tid] = (float)v;
+  }
+}
+
+// out[c][r] = in[r][c] for the 64 x 64 entries from (r0, c0) on, zeros past the rows; a block of 256 threads, 16-byte loads and stores.
+__device__ __forceinline__ void transpose_tile(const uint16_t* in, int rows, int cols, int r0, int c0, uint16_t* out, int64_t ld, uint16_t (*tile)[72]) {
+  const int tid = threadIdx.x, q = (tid & 7) * 8, row = tid >> 3;
+  __syncthreads();                                         // the previous tile has been read
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int r = row + 32 * i;
+    const planes_u32x4 v = *reinterpret_cast<const planes_u32x4*>(in + (int64_t)min(r0 + r, rows - 1) * cols + c0 + q);
+    *reinterpret_cast<planes_u32x4*>(&tile[r][q]) = r0 + r < rows ? v : planes_u32x4{0, 0, 0, 0};
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int c = row + 32 * i;
+    struct alignas(16) Eight { uint16_t e[8]; } h;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) h.e[k] = tile[q + k][c];
+    *reinterpret_cast<Eight*>(out + (int64_t)(c0 + c) * ld + r0 + q) = h;
+  }
+}
+
+// The transposed operands of a whole block's products in one launch (whole 64 x 64 tiles): the weights and kept
 // activations of a 125M model's block are 72 MB in and out, 8 launches of 6.3 us one by one.
 __global__ void __launch_bounds__(256) transposes_kernel(TransposeJobs jobs) {
   __shared__ __attribute__((aligned(16))) uint16_t tile[64][72];
-  struct alignas(16) Eight { uint16_t e[8]; };
   int b = blockIdx.x, j = 0;
   for (; j + 1 < jobs.count; ++j) {
     const int n = (jobs.job[j].rows >> 6) * (jobs.job[j].cols >> 6);
@@ -139,23 +231,8 @@ __global__ void __launch_bounds__(256) transposes_kernel(TransposeJobs jobs) {
     b -= n;
   }
   const TransposeJob job = jobs.job[j];
-  const int ct = job.cols >> 6, r0 = b / ct * 64, c0 = (b - b / ct * ct) * 64, tid = threadIdx.x, q = (tid & 7) * 8, row = tid >> 3;
-  const uint16_t* in = reinterpret_cast<const uint16_t*>(job.in);
-  uint16_t* out = reinterpret_cast<uint16_t*>(job.out);
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int r = row + 32 * i;
-    *reinterpret_cast<Eight*>(&tile[r][q]) = *reinterpret_cast<const Eight*>(in + (int64_t)(r0 + r) * job.cols + c0 + q);
-  }
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int c = row + 32 * i;
-    Eight h;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) h.e[k] = tile[q + k][c];
-    *reinterpret_cast<Eight*>(out + (int64_t)(c0 + c) * job.rows + r0 + q) = h;
-  }
+  const int ct = job.cols >> 6, r = b / ct;
+  transpose_tile(reinterpret_cast<const uint16_t*>(job.in), job.rows, job.cols, r * 64, (b - r * ct) * 64, reinterpret_cast<uint16_t*>(job.out), job.rows, tile);
 }
 
 // Sums over rows run in two stages with a fixed shape, so that the order of the additions never depends on scheduling: up to kColParts
@@ -164,11 +241,11 @@ __global__ void __launch_bounds__(256) transposes_kernel(TransposeJobs jobs) {
 // eighth of the parts in order, then the eighths are added in order.
 constexpr int kColParts = 64;
 __global__ void __launch_bounds__(256) colsum_final_kernel(SumJobs jobs) {
-  __shared__ float sums[8][32];
+  __shared__ double sums[8][32];
   const SumJob j = jobs.job[blockIdx.y];
   const int c = blockIdx.x * 32 + (threadIdx.x & 31), q = threadIdx.x >> 5, per = (j.parts + 7) / 8;
   if ((int)blockIdx.x * 32 >= j.n) return;                 // the whole block
-  float s = 0.f;
+  double s = 0.;                                           // as free as fp32 here
   if (c < j.n) {
     const int end = j.parts < (q + 1) * per ? j.parts : (q + 1) * per;
 #pragma unroll 8
@@ -178,7 +255,7 @@ __global__ void __launch_bounds__(256) colsum_final_kernel(SumJobs jobs) {
   __syncthreads();
   if (q == 0 && c < j.n) {
     for (int i = 1; i < 8; ++i) s += sums[i][threadIdx.x];
-    j.out[c] = s;
+    j.out[c] = (float)s;
   }
 }
 
@@ -864,6 +941,22 @@ hipError_t launch_bw_gradient_operands(const float* dy, const float* u, int relu
                      reinterpret_cast<bf16_t*>(rows_out), (int64_t)N, part, per)
   if (!u) ZGR_OPERANDS(0); else if (relu) ZGR_OPERANDS(2); else ZGR_OPERANDS(1);
 #undef ZGR_OPERANDS
+  const int n = N / n_bias;
+  for (int i = 0; i < n_bias; ++i) sums.add(SumJob{part + (size_t)i * n, dbias[i], (int64_t)N, parts, n});
+  return hipGetLastError();
+}
+
+hipError_t launch_bw_gradient_planes(float* dy, const float* u, int relu, int M, int N, void* cols_out, const void* x, int x_cols, void* x_out, float* const* dbias, int n_bias, SumQueue& sums,
+                                     hipStream_t s) {
+  if (M < 1 || N < 64 || N % 64 || x_cols < 64 || x_cols % 64 || n_bias < 1 || n_bias > 3 || N % n_bias) return hipErrorInvalidValue;
+  const int tiles = (M + 63) / 64, per = (tiles + kColParts - 1) / kColParts, parts = (tiles + per - 1) / per;
+  const dim3 grid((unsigned)(N / 64 + x_cols / 64), (unsigned)parts);
+  float* part = nullptr;
+  const hipError_t e = sums.take((size_t)parts * N, n_bias, &part);
+  if (e != hipSuccess) return e;
+  auto kern = !u ? gradient_planes_kernel<0> : relu ? gradient_planes_kernel<2> : gradient_planes_kernel<1>;
+  hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, dy, u, M, N, reinterpret_cast<bf16_t*>(cols_out), (int64_t)tiles * 64, part, per, reinterpret_cast<const bf16_t*>(x), x_cols,
+                     reinterpret_cast<bf16_t*>(x_out));
   const int n = N / n_bias;
   for (int i = 0; i < n_bias; ++i) sums.add(SumJob{part + (size_t)i * n, dbias[i], (int64_t)N, parts, n});
   return hipGetLastError();

@@ -213,16 +213,22 @@ struct GemmTwin { int64_t a, w, out, bias, tlogit; };
 // blocks resident in one L2 share 4 row panels of A and 8 of W.  (Whole super-tiles of 4 x 8 dealt out to the XCDs left half of them idle where there
 // are few: 16 x 6 tiles are four of them.  2 x 2048 x 768 x 768 and x 3072 with the residual: 47.6 us -> 26.7 on average, 2 x 4096 x 6144 x 2048:
 // 216 -> 173.)
-__device__ __forceinline__ int tile_of_block(int tiles_m, int tiles_n, int models, int& tm, int& tn) {
-  constexpr int GM = 4;
-  const int per_model = tiles_m * tiles_n, total = per_model * models;
+__device__ __forceinline__ int place_of_block(int total) {
   const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3, q = total >> 3, rem = total & 7;
-  if (local >= q + (xcd < rem ? 1 : 0)) return -1;
-  const int idx = xcd * q + (xcd < rem ? xcd : rem) + local;
-  const int model = idx / per_model, r = idx - model * per_model, band = r / (GM * tiles_n), at = r - band * (GM * tiles_n);
+  return local >= q + (xcd < rem ? 1 : 0) ? -1 : xcd * q + (xcd < rem ? xcd : rem) + local;
+}
+__device__ __forceinline__ void tile_at(int place, int tiles_m, int tiles_n, int& tm, int& tn) {
+  constexpr int GM = 4;
+  const int band = place / (GM * tiles_n), at = place - band * (GM * tiles_n);
   const int rows = tiles_m - band * GM < GM ? tiles_m - band * GM : GM;
   tn = at / rows;
   tm = band * GM + (at - tn * rows);
+}
+__device__ __forceinline__ int tile_of_block(int tiles_m, int tiles_n, int models, int& tm, int& tn) {
+  const int per_model = tiles_m * tiles_n, place = place_of_block(per_model * models);
+  if (place < 0) return -1;
+  const int model = place / per_model;
+  tile_at(place - model * per_model, tiles_m, tiles_n, tm, tn);
   return model;
 }
 template <typename T> __device__ __forceinline__ const T* ahead(const T* p, int64_t bytes) {
@@ -728,10 +734,13 @@ __device__ __forceinline__ void epilogue_bf16(void* out, size_t o, float v) {
   else reinterpret_cast<float*>(out)[o] = v;
 }
 
-template <int BM, int BN, int WM, int WN, int BK, int STAGES, int MODE, int PP = 0>
-__global__ void __launch_bounds__(64 * WM * WN) gemm_bf16_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, int M, int N, int K,
-                                                                 void* out, const bf16_t* __restrict__ bias,      // resid may be out
-                                                                 const int32_t* __restrict__ targets, float* __restrict__ tlogit, GemmTwin tw, int models, const float* resid) {
+// Tile (tm, tn) of the product.  FOLD: A's rows hold FOLD runs of K / FOLD terms and W's one, which every run is multiplied with.  Those are sums that
+// stay fp32 throughout: they are taken in pieces of kPieceTiles k-tiles, so that the large sum rounds once a piece and not with every instruction
+// (the adding up hides behind the other group's memory phase).
+template <int BM, int BN, int WM, int WN, int BK, int STAGES, int MODE, int PP, int FOLD>
+__device__ __forceinline__ void gemm_bf16_tile(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, int M, int N, int K,
+                                               void* out, const bf16_t* __restrict__ bias,      // resid may be out
+                                               const int32_t* __restrict__ targets, float* __restrict__ tlogit, const float* resid, int tm, int tn) {
   constexpr int NW = WM * WN;
   constexpr int FM = BM / (32 * WM), FN = BN / (32 * WN);      // 32x32 fragments per wave
   constexpr int CPR = BK / 8;                                  // 16-byte chunks per LDS row
@@ -753,13 +762,9 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_bf16_kernel(const bf16_t* _
   const int wave = tid >> 6;
 #endif
   const int wm = wave / WN, wn = wave % WN;
-  const int tiles_n = (N + BN - 1) / BN, tiles_m = (M + BM - 1) / BM;
-  int tm, tn;
-  const int model = tile_of_block(tiles_m, tiles_n, models, tm, tn);
-  if (model < 0) return;
-  A = ahead(A, model * tw.a); W = ahead(W, model * tw.w); out = ahead(out, model * tw.out); bias = ahead(bias, model * tw.bias);
-  if (MODE == EPI_CE) tlogit = ahead(tlogit, model * tw.tlogit);
-  if (MODE == EPI_RESID) resid = ahead(resid, model * tw.out);
+  constexpr int kPieceTiles = 2;
+  constexpr bool PIECES = FOLD > 1;
+  [[maybe_unused]] const int tiles_m = (M + BM - 1) / BM;
   const int m0 = tm * BM, n0 = tn * BN;
   f32x16 acc[FM][FN];
 #pragma unroll
@@ -783,7 +788,24 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_bf16_kernel(const bf16_t* _
 #pragma unroll
         for (int v = 0; v < 16; ++v) res[(i * FN + j) * 16 + v] = rp[(size_t)(i * 32 + 8 * (v >> 2) + (v & 3)) * N + j * 32];
   }
-  const int nk = K / BK;
+  f32x16 total[PIECES ? FM : 1][PIECES ? FN : 1];
+  auto add_piece = [&](bool first) {
+    if constexpr (PIECES) {
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) { total[i][j][v] = first ? acc[i][j][v] : total[i][j][v] + acc[i][j][v]; acc[i][j][v] = 0.f; }
+    }
+  };
+  add_piece(true);
+  const int nk = K / BK, KW = K / FOLD, nkw = nk / FOLD;        // W's row stride and k-tiles
+  auto w_ktile = [&](int kt) {
+    if constexpr (FOLD == 1) return kt;
+    else { const int r = kt < nkw ? kt : kt - nkw; return FOLD == 2 || r < nkw ? r : r - nkw; }
+  };
+  static_assert(FOLD <= 3, "runs");
   // reader: lane (l32, half) reads row l32 of each fragment, logical chunk 2*ks + half
   const int l32 = lane & 31, half = lane >> 5, swz = (l32 / RPB) % CPR;
   int koff[BK / 16];
@@ -820,19 +842,19 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_bf16_kernel(const bf16_t* _
       int r = (is_a ? m0 : n0) + rl;
       const int lim = is_a ? M : N;
       r = r < lim ? r : lim - 1;
-      uo[u] = ((uint32_t)r * (uint32_t)K + (((lane & 7) ^ ((frow >> 1) & 7)) << 3)) * 2;   // bytes
+      uo[u] = ((uint32_t)r * (uint32_t)(is_a ? K : KW) + (((lane & 7) ^ ((frow >> 1) & 7)) << 3)) * 2;   // bytes
     }
 #if defined(__HIP_DEVICE_COMPILE__)
     // buffer addressing: per-lane byte offset in a register, the k-tile's offset in a scalar, bounds-checked
     const __amdgpu_buffer_rsrc_t rsA = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(A), 0, (uint32_t)M * (uint32_t)K * 2u, 0x00020000);
-    const __amdgpu_buffer_rsrc_t rsW = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(W), 0, (uint32_t)N * (uint32_t)K * 2u, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rsW = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(W), 0, (uint32_t)N * (uint32_t)KW * 2u, 0x00020000);
 #endif
     // Transfers are issued unconditionally, so that every wave's count of outstanding transfers is the same in
     // every k-tile: a unit past the last k-tile re-reads the last one into a ring slot nobody reads any more.
     auto issue_unit = [&](int u, int ktile, int pos) {           // u is a compile-time constant after unrolling
 #if defined(__HIP_DEVICE_COMPILE__)
       const int kc = ktile < nk ? ktile : nk - 1;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(u < UA ? rsA : rsW, (__attribute__((address_space(3))) void*)(gsm + pos * 8192 + wave * 1024), 16, uo[u], kc * (BK * 2), 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(u < UA ? rsA : rsW, (__attribute__((address_space(3))) void*)(gsm + pos * 8192 + wave * 1024), 16, uo[u], (u < UA ? kc : w_ktile(kc)) * (BK * 2), 0, 0);
 #endif
     };
     int wpos = 0;                                                // ring position of the next unit to issue
@@ -914,6 +936,7 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_bf16_kernel(const bf16_t* _
           for (int i = 0; i < FM; ++i)
 #pragma unroll
             for (int j = 0; j < FN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][i], b[ks][j], acc[i][j], 0, 0, 0);
+        if (h == 1 && PIECES && kt % kPieceTiles == kPieceTiles - 1) add_piece(false);
         if (h == 1 && !grp) wait_vmem_upto<Q0 - U>();
 #if defined(__HIP_DEVICE_COMPILE__)
         __builtin_amdgcn_sched_barrier(0);
@@ -938,7 +961,7 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_bf16_kernel(const bf16_t* _
   for (int g = 0; g < GW; ++g) {
     const int rl = (wave * GW + g) * RPI + lrow;
     int c = n0 + rl; c = c < N ? c : N - 1;
-    wo[g] = (uint32_t)c * (uint32_t)K + ((lslot ^ ((rl / RPB) % CPR)) << 3);
+    wo[g] = (uint32_t)c * (uint32_t)KW + ((lslot ^ ((rl / RPB) % CPR)) << 3);
   }
   auto issue = [&](int kt, int buf) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -947,7 +970,7 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_bf16_kernel(const bf16_t* _
       __builtin_amdgcn_global_load_lds(A + ao[g] + kt * BK, As + (buf * BM + (wave * GA + g) * RPI) * BK, 16, 0, 0);
 #pragma unroll
     for (int g = 0; g < GW; ++g)
-      __builtin_amdgcn_global_load_lds(W + wo[g] + kt * BK, Ws + (buf * BN + (wave * GW + g) * RPI) * BK, 16, 0, 0);
+      __builtin_amdgcn_global_load_lds(W + wo[g] + w_ktile(kt) * BK, Ws + (buf * BN + (wave * GW + g) * RPI) * BK, 16, 0, 0);
 #endif
   };
   // prologue: STAGES - 1 k-tiles in flight
@@ -974,8 +997,15 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_bf16_kernel(const bf16_t* _
 #pragma unroll
         for (int j = 0; j < FN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
     }
+    if (PIECES && kt % kPieceTiles == kPieceTiles - 1) add_piece(false);
     buf = buf + 1 == STAGES ? 0 : buf + 1;
   }
+  }
+  if constexpr (PIECES) {
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j) acc[i][j] += total[i][j];
   }
   if (MODE == EPI_CE) {
     // Cross-entropy partials instead of logits.  The product is taken transposed (rows = vocabulary entries,
@@ -1080,6 +1110,67 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_bf16_kernel(const bf16_t* _
         }
       }
   }
+}
+
+template <int BM, int BN, int WM, int WN, int BK, int STAGES, int MODE, int PP = 0>
+__global__ void __launch_bounds__(64 * WM * WN) gemm_bf16_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, int M, int N, int K,
+                                                                 void* out, const bf16_t* __restrict__ bias,
+                                                                 const int32_t* __restrict__ targets, float* __restrict__ tlogit, GemmTwin tw, int models, const float* resid) {
+  int tm, tn;
+  const int model = tile_of_block((M + BM - 1) / BM, (N + BN - 1) / BN, models, tm, tn);
+  if (model < 0) return;
+  A = ahead(A, model * tw.a); W = ahead(W, model * tw.w); out = ahead(out, model * tw.out); bias = ahead(bias, model * tw.bias);
+  if (MODE == EPI_CE) tlogit = ahead(tlogit, model * tw.tlogit);
+  if (MODE == EPI_RESID) resid = ahead(resid, model * tw.out);
+  gemm_bf16_tile<BM, BN, WM, WN, BK, STAGES, MODE, PP, 1>(A, W, M, N, K, out, bias, targets, tlogit, resid, tm, tn);
+}
+
+// Several products with the same K and fp32 results in one launch: the tiles of all of them, one after the other, dealt out as those of one product are.
+// The four weight gradients of a block of 768 columns have 144, 144, 36 and 108 tiles of 128 x 128: one by one they left up to six sevenths of the
+// chip idle (2048 tokens: 67 us in four launches, now 36, 0.8 PFLOP/s).
+// FOLD = 3, a block of 1024 columns and 231 tokens: 32 us, 50 MB of results among them; product.hip's kernel, which cuts planes from fp32 operands as they lie, took
+// 67 in four launches.  Off from fp64 by 0.7e-7 of the norm there (0.8e-7 in product.hip, which shares a sum among waves), 1.0e-7 at 2047 tokens (2.4e-7); with the sums in one
+// piece 0.8e-7 and 2.7e-7, and 2 us less.
+template <int BM, int BN, int WM, int WN, int BK, int STAGES, int PP, int FOLD>
+__global__ void __launch_bounds__(64 * WM * WN) gemm_bf16_group_kernel(ProductGroup g) {
+  auto tiles = [&](int j) { return ((g.job[j].M + BM - 1) / BM) * ((g.job[j].N + BN - 1) / BN); };
+  int total = 0;
+  for (int j = 0; j < g.count; ++j) total += tiles(j);
+  int place = place_of_block(total), j = 0, tm, tn;
+  if (place < 0) return;
+  for (; place >= tiles(j); ++j) place -= tiles(j);
+  const GroupedProduct p = g.job[j];
+  tile_at(place, (p.M + BM - 1) / BM, (p.N + BN - 1) / BN, tm, tn);
+  gemm_bf16_tile<BM, BN, WM, WN, BK, STAGES, EPI_F32, PP, FOLD>(reinterpret_cast<const bf16_t*>(p.A), reinterpret_cast<const bf16_t*>(p.W), p.M, p.N, g.K, p.out, nullptr, nullptr, nullptr, nullptr, tm, tn);
+}
+
+template <int BM, int BN, int WM, int WN, int BK, int STAGES, int PP, int FOLD>
+static hipError_t launch_group_t(const ProductGroup& g, int64_t tiles, hipStream_t s) {
+  const size_t lds = PP ? (size_t)STAGES * 8192 : (size_t)STAGES * (BM + BN) * BK * sizeof(bf16_t);
+  static std::atomic<bool> attr_set{false};   // set twice by racing threads at worst: the call is idempotent
+  auto kern = gemm_bf16_group_kernel<BM, BN, WM, WN, BK, STAGES, PP, FOLD>;
+  if (!attr_set) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    attr_set = true;
+  }
+  hipLaunchKernelGGL(kern, dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(64 * WM * WN), lds, s, g);
+  return hipGetLastError();
+}
+template <int FOLD>
+static hipError_t launch_group_f(const ProductGroup& g, hipStream_t s) {
+  auto tiles = [&](int bm, int bn) {
+    int64_t t = 0;
+    for (int j = 0; j < g.count; ++j) t += (int64_t)((g.job[j].M + bm - 1) / bm) * ((g.job[j].N + bn - 1) / bn);
+    return t;
+  };
+  const int64_t t256 = tiles(256, 256), t128 = tiles(128, 128);
+  if constexpr (FOLD == 1) {                               // (pieces of sums leave 256 x 256 tiles no registers)
+    if (t256 >= 512) return launch_group_t<256, 256, 2, 4, 64, 20, 1, FOLD>(g, t256, s);
+  }
+  if (t128 > 256) return launch_group_t<128, 128, 2, 4, 64, 8, 1, FOLD>(g, t128, s);
+  if (t128 > 128) return launch_group_t<128, 128, 2, 4, 64, 20, 1, FOLD>(g, t128, s);
+  return launch_group_t<64, 64, 2, 2, 64, 4, 0, FOLD>(g, tiles(64, 64), s);
 }
 
 template <int BM, int BN, int WM, int WN, int BK, int STAGES, int PP = 0>
@@ -1825,6 +1916,16 @@ hipError_t launch_gemm(int dtype, const void* A, const void* W, const void* bias
     return launch_gemm_bf16_t<128, 128, 2, 4, 64, 20, 1>(a, w, b, out, epi, M, N, K, s, n, gt, from);
   }
   return hipGetLastError();
+}
+
+hipError_t launch_product_group(const ProductGroup& g, hipStream_t s) {
+  if (g.count == 0) return hipSuccess;
+  if (g.count < 0 || g.count > kGroupedProducts || (g.fold != 1 && g.fold != 3) || g.K < 1 || g.K % (GB_K * g.fold)) return hipErrorInvalidValue;
+  for (int j = 0; j < g.count; ++j) {
+    const GroupedProduct& p = g.job[j];
+    if (p.M < 1 || p.N < 1 || (size_t)p.M * g.K >= ((size_t)1 << 31) || (size_t)p.N * g.K >= ((size_t)1 << 31)) return hipErrorInvalidValue;      // 32-bit byte offsets
+  }
+  return g.fold == 1 ? launch_group_f<1>(g, s) : launch_group_f<3>(g, s);
 }
 
 // Vocabulary projection fused with the row-wise cross-entropy (bf16 storage): logits are never stored.

@@ -123,3 +123,52 @@ def test_product_of_wild_operands_with_bf16(a_k, K):
     if sums is not None:
         s = A.double().sum(1)
         assert torch.equal(torch.isnan(sums.cpu()), torch.isnan(s))
+
+
+def _weight_gradient(dy, u, relu, x, parts):
+    """dW, db and dy act'(u) (in place of dy) of zgr_debug_weight_gradient, which has to write every entry."""
+    import ctypes as C
+    import torch
+    from paper_2601_12917_amd import binding as B
+    (M, N), K, Mp = dy.shape, x.shape[1], -(-dy.shape[0] // 64) * 64
+    dW = [torch.full((N // parts, K), float("nan"), device="cuda") for _ in range(parts)]
+    db = [torch.full((N // parts,), float("nan"), device="cuda") for _ in range(parts)]
+    scratch = torch.full((6 * N * Mp + 2 * K * Mp + 4 * (N * Mp // 64 + 512),), 0xFF, dtype=torch.uint8, device="cuda")      # NaN, if any of it is read first
+    ptrs = lambda t: (C.c_void_p * parts)(*[v.data_ptr() for v in t])
+    B.check(B.lib().zgr_debug_weight_gradient(dy.data_ptr(), u.data_ptr() if u is not None else None, relu, x.data_ptr(), M, N, K, parts, ptrs(dW), ptrs(db),
+                                              scratch.data_ptr(), scratch.numel(), torch.cuda.current_stream().cuda_stream))
+    torch.cuda.synchronize()
+    return torch.cat(dW), torch.cat(db)
+
+
+@pytest.mark.parametrize("M,N,K,parts", [(1, 64, 64, 1), (63, 192, 64, 3), (65, 1536, 1600, 1), (77, 2112, 2048, 3), (231, 3072, 2048, 3), (130, 5696, 6016, 1), (8191, 128, 192, 2)],
+                         ids=lambda v: str(v))
+def test_weight_gradient_is_as_close_as_fp32(M, N, K, parts):
+    """Each tile size of the group (64 x 64, 128 x 128 with one and two blocks a CU, 256 x 256), ragged tiles, tokens on either side of a multiple of 64.  Nothing is left
+    out; a sum rounds once per 16 terms of a plane, by at most 2^-24 of its size, here counted twice.  GELU's slope in fp32 is within 6 2^-24."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(M + N + K)
+    for draw in (torch.randn, lambda *s, **kw: torch.rand(*s, **kw) + 1):
+        dy, x = draw(M, N, generator=gen, device="cuda"), draw(M, K, generator=gen, device="cuda").bfloat16()
+        u = torch.randn(M, N, generator=gen, device="cuda") if N % 128 else None
+        exact = dy.double()
+        if u is not None:
+            v = u.double()
+            exact = exact * (0.5 * (1 + torch.erf(v / 2 ** 0.5)) + v * torch.exp(-0.5 * v * v) / (2 * np.pi) ** 0.5)
+        dW, db = _weight_gradient(dy, u, 0, x, parts)
+        if u is not None:
+            assert (dy.double() - exact).norm() <= 6 * 2.0 ** -24 * exact.norm()
+        want, wb = dy.double().T @ x.double(), dy.double().sum(0)
+        assert (dW.double() - want).norm() <= 2.0 ** -24 * np.sqrt(max(M, 16) / 8) * want.norm()
+        assert torch.all((db.double() - wb).abs() <= 2.0 ** -24 * 4 * np.sqrt(M + 64) * dy.double().abs().sum(0))
+
+
+@pytest.mark.parametrize("M", [33, 200])
+def test_weight_gradient_of_wild_operands(M):
+    import torch
+    gen = torch.Generator().manual_seed(M)
+    dy, x = _wild(torch.randn(M, 192, generator=gen), gen), (torch.randn(M, 320, generator=gen).clamp(-3, 3) * 0.01).bfloat16()
+    want, wb = dy.double().T @ x.double(), dy.double().sum(0)
+    dW, db = _weight_gradient(dy.cuda(), None, 0, x.cuda(), 1)
+    _same(dW.cpu(), want)
+    assert torch.equal(torch.isnan(db.cpu()), torch.isnan(wb))
