@@ -10,7 +10,7 @@ SOURCES = ["api.hip", "perturb.hip", "forward.hip", "ceilings.hip", "cloud.hip",
 FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-shared", "-Wall",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
-STEP_KERNEL_SOURCES = ("perturb.hip", "forward.hip", "forward.h", "product.hip", "product.h", "planes.h", "act.h", "rng.h", "internal.h")
+STEP_KERNEL_SOURCES = ("perturb.hip", "forward.hip", "forward.h", "product.hip", "product.h", "planes.h", "act.h", "rng.h", "wave.h", "internal.h")
 
 
 def source_digest() -> str:

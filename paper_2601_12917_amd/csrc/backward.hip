@@ -8,6 +8,7 @@
 // entries a workgroup), cross-entropy a workgroup.  Deterministic: no atomics, every sum has a fixed order.
 #include "backward.h"
 #include "planes.h"
+#include "wave.h"
 #include "product.h"
 #include <algorithm>
 
@@ -24,16 +25,6 @@ __device__ __forceinline__ void from_f32(float x, bf16_t& o) {
   o.bits = __builtin_bit_cast(uint16_t, h);
 }
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
-}
 // block of 256 threads
 __device__ __forceinline__ float block_sum(float v, float* red) {
   v = wave_sum(v);

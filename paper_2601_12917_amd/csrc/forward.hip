@@ -9,6 +9,7 @@
 #include "forward.h"
 #include "act.h"
 #include "planes.h"
+#include "wave.h"
 #include "product.h"
 #include <atomic>
 
@@ -25,16 +26,6 @@ __device__ __forceinline__ void from_f32(float x, bf16_t& o) {     // round to n
   o.bits = __builtin_bit_cast(uint16_t, h);
 }
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
-}
 // block of 256 threads: reduce across the 4 waves through LDS
 __device__ __forceinline__ float block_sum(float v, float* red) {
   v = wave_sum(v);
@@ -1779,8 +1770,11 @@ __global__ void __launch_bounds__(256) mean_f64_kernel(const float* __restrict__
   for (int i = threadIdx.x; i < n; i += 256) s += (double)v[i];
   red[threadIdx.x] = s;
   __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) { if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o]; __syncthreads(); }
-  if (threadIdx.x == 0) out[blockIdx.x] = red[0] * inv_count;
+  if (threadIdx.x >= 64) return;                                   // the first wave: the upper half onto the lower, again and again
+  s = (red[threadIdx.x] + red[threadIdx.x + 128]) + (red[threadIdx.x + 64] + red[threadIdx.x + 192]);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
+  if (threadIdx.x == 0) out[blockIdx.x] = s * inv_count;
 }
 
 // classification head on token 0 of every sequence: logits[b][c] = h[b*seq] . Wc[c] + bc[c]
