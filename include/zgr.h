@@ -16,7 +16,8 @@
  *     owned by the caller, and stays valid for the lifetime of the context.
  *     Pointers marked HOST are host memory.
  *   - The library allocates no device memory: parameters, bases, batch and
- *     workspace all come from the caller.
+ *     workspace all come from the caller.  A context with a model has 16 bytes
+ *     of pinned host memory, which its losses are written to.
  *   - All work is enqueued on the HIP stream given to zgr_init.  zgr_step
  *     synchronises that stream once (to read the two losses); the other calls
  *     return after enqueueing unless stated otherwise.

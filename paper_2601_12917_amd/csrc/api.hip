@@ -45,7 +45,7 @@ struct Carve {                 // workspace layout (byte offsets)
   size_t descs = 0, flat = 0, tiles = 0, dbg = 0;
   size_t cap_flat = 0, cap_tiles = 0, cap_dbg = 0;   // capacities in items
   bool few_tiles = false;      // small row tiles (kFewTiles)
-  size_t x = 0, h = 0, qkv = 0, ctx = 0, ff = 0, logits = 0, row_loss = 0, targets = 0, loss = 0;
+  size_t x = 0, h = 0, qkv = 0, ctx = 0, ff = 0, logits = 0, row_loss = 0, targets = 0;
   size_t row_loss_stride = 0;                  // floats between the row losses of L+ (slot 0) and L- (slot 1)
   size_t spc[kSpcSlots] = {}, spc_bytes = 0;   // staging slots for the bases of one layer each (streamed bases)
   size_t total = 0;
@@ -100,7 +100,9 @@ struct zgr_ctx {
   int64_t last_rows = 0;       // rows of the last forward's row_loss
   int last_slot = 0;           // which of the two row-loss buffers the last forward wrote
   int64_t slot_rows[2] = {0, 0};
-  double host_loss[2] = {0, 0};
+  // the losses, in pinned host memory that the kernels write themselves (a copy from the device is a launch of its own, 4 us, and a wait)
+  double* host_loss = nullptr;
+  double* loss_dev = nullptr;  // the same memory as the device sees it
 };
 
 namespace {
@@ -370,7 +372,6 @@ Carve carve(const zgr_model& m, const zgr_tensor* t, int n_t, int max_batch, int
   cv.flat = take(sizeof(WorkItem) * std::max<size_t>(nf, 1));
   cv.tiles = take(sizeof(WorkItem) * std::max<size_t>(nt, 1));
   cv.dbg = take(sizeof(WorkItem) * std::max<size_t>(nd, 1));
-  cv.loss = take(sizeof(double) * 2);
   {
     // A staging slot holds the fp32 bases (compact rows x k, ranks from the tensor table) of one stage: consecutive
     // layers packed until they hold kMinStageTiles tiles.  Sized as if every guidable tensor were streamed.
@@ -558,6 +559,36 @@ zgr_status perturb_pass_batched(zgr_ctx* c, int n, const uint64_t* steps, const 
 }
 
 // ---------------------------------------------------------------- forward
+// Places for the losses of contexts, of a cache line each, in pages of pinned memory: an allocation of its own takes every context 3 ms.  A page is taken when none has
+// room and given back when its last place is, but for one, which stays for the next context.
+struct LossPage { unsigned char* at; uint64_t used; };
+std::mutex g_loss_mu;
+std::vector<LossPage>& g_loss_pages = *new std::vector<LossPage>();      // never destroyed: contexts may outlast the library's statics
+constexpr size_t kLossPlace = 64, kLossPlaces = 64;
+
+double* take_loss_place() {
+  std::lock_guard<std::mutex> lock(g_loss_mu);
+  for (LossPage& p : g_loss_pages)
+    for (size_t i = 0; i < kLossPlaces; ++i)
+      if (!(p.used >> i & 1)) { p.used |= (uint64_t)1 << i; return reinterpret_cast<double*>(p.at + i * kLossPlace); }
+  void* at = nullptr;
+  if (hipHostMalloc(&at, kLossPlace * kLossPlaces, hipHostMallocMapped | hipHostMallocPortable) != hipSuccess) return nullptr;
+  g_loss_pages.push_back({reinterpret_cast<unsigned char*>(at), 1});
+  return reinterpret_cast<double*>(at);
+}
+void give_loss_place(double* place) {
+  if (!place) return;
+  std::lock_guard<std::mutex> lock(g_loss_mu);
+  for (size_t k = 0; k < g_loss_pages.size(); ++k) {
+    LossPage& p = g_loss_pages[k];
+    const size_t off = (size_t)(reinterpret_cast<unsigned char*>(place) - p.at);
+    if (reinterpret_cast<unsigned char*>(place) < p.at || off >= kLossPlace * kLossPlaces) continue;
+    p.used &= ~((uint64_t)1 << (off / kLossPlace));
+    if (p.used == 0 && g_loss_pages.size() > 1) { (void)hipHostFree(p.at); g_loss_pages.erase(g_loss_pages.begin() + (std::ptrdiff_t)k); }
+    return;
+  }
+}
+
 const void* T(zgr_ctx* c, int idx) { return c->t[idx].theta; }
 
 // The loss of the caller's parameters into `slot`, or (both) those of the two copies into slots 0 and 1: every launch then takes both models,
@@ -573,7 +604,7 @@ zgr_status forward_loss(zgr_ctx* c, const zgr_batch* b, int slot, bool both = fa
   const zgr_model& m = c->model;
   hipStream_t s = c->stream;
   unsigned char* ws = c->ws;
-  double* loss_dev = reinterpret_cast<double*>(ws + c->cv.loss) + slot;
+  double* loss_dev = c->loss_dev + slot;
   float* row_loss = reinterpret_cast<float*>(ws + c->cv.row_loss) + (size_t)slot * c->cv.row_loss_stride;
   float* logits = reinterpret_cast<float*>(ws + c->cv.logits);
   const int dt = c->dtype;
@@ -581,8 +612,7 @@ zgr_status forward_loss(zgr_ctx* c, const zgr_batch* b, int slot, bool both = fa
     const zgr_tensor& w = c->t[c->lsq_w];
     { ProfScope ps(c, ZGR_K_GEMM); HIP_TRY(c, launch_gemm(0, b->x, T(c, c->lsq_w), nullptr, logits, EPI_F32, b->batch, (int)w.rows, (int)w.cols, s, nullptr, 0, false, tw, true)); }
     { ProfScope ps(c, ZGR_K_LOSS);
-      HIP_TRY(c, launch_lsq_rows(logits, reinterpret_cast<const float*>(b->y), row_loss, b->batch, (int)w.rows, s, tw));
-      HIP_TRY(c, launch_mean_f64(row_loss, b->batch, 1.0 / b->batch, loss_dev, s, tw)); }
+      HIP_TRY(c, launch_lsq_loss(logits, reinterpret_cast<const float*>(b->y), row_loss, b->batch, (int)w.rows, loss_dev, s, tw)); }
     wrote((size_t)b->batch);
     return ZGR_OK;
   }
@@ -592,7 +622,8 @@ zgr_status forward_loss(zgr_ctx* c, const zgr_batch* b, int slot, bool both = fa
   void* h = ws + c->cv.h; void* qkv = ws + c->cv.qkv; void* ctx = ws + c->cv.ctx; void* ffb = ws + c->cv.ff;
   const int32_t* tok = reinterpret_cast<const int32_t*>(b->x);
   const bool lm = m.arch == ZGR_ARCH_DECODER_LM;
-  { ProfScope ps(c, ZGR_K_EMBED); HIP_TRY(c, launch_embed(dt, tok, T(c, c->tok_emb), T(c, c->pos_emb), x, M, b->seq, d, m.vocab, s, tw)); }
+  int32_t* tgt = lm ? reinterpret_cast<int32_t*>(ws + c->cv.targets) : nullptr;
+  { ProfScope ps(c, ZGR_K_EMBED); HIP_TRY(c, launch_embed(dt, tok, T(c, c->tok_emb), T(c, c->pos_emb), x, M, b->seq, d, m.vocab, tgt, s, tw)); }
   const int act_epi = m.act == ZGR_ACT_RELU ? EPI_RELU : EPI_GELU;
   // fp32 models: a buffer whose contents a product neither reads nor still has use for holds the parts of its split sum
   float* ff_scratch = dt == ZGR_F32 ? reinterpret_cast<float*>(ffb) : nullptr;
@@ -616,8 +647,6 @@ zgr_status forward_loss(zgr_ctx* c, const zgr_batch* b, int slot, bool both = fa
   }
   if (!m.post_ln) { ProfScope ps(c, ZGR_K_NORM); HIP_TRY(c, launch_layernorm(dt, x, T(c, c->lnf_g), T(c, c->lnf_b), h, M, d, m.ln_eps, s, nullptr, tw)); }
   if (lm) {
-    int32_t* tgt = reinterpret_cast<int32_t*>(ws + c->cv.targets);
-    { ProfScope ps(c, ZGR_K_LOSS); HIP_TRY(c, launch_lm_targets(tok, tgt, M, b->seq, m.vocab, s)); }
     if (dt == ZGR_BF16) {
       // the logits region holds the cross-entropy partials and, behind them, the target logits
       float* tlogit = logits + 2 * ce_partials_per_row(m.vocab) * rows;
@@ -769,6 +798,13 @@ zgr_status zgr_init(zgr_ctx** out, const zgr_model* model, const zgr_tensor* ten
   c->n_cu = n_cu;
   const RadiusEntry* tab = nullptr;
   if (ensure_radius_table(&tab, c->stream) != hipSuccess) { delete c; return fail(nullptr, ZGR_ERR_DEVICE, "could not set up the device tables"); }
+  if (model->arch != ZGR_ARCH_NONE) {
+    c->host_loss = take_loss_place();
+    if (!c->host_loss || hipHostGetDevicePointer(reinterpret_cast<void**>(&c->loss_dev), c->host_loss, 0) != hipSuccess) {
+      give_loss_place(c->host_loss);
+      delete c; return fail(nullptr, ZGR_ERR_DEVICE, "no pinned host memory for the losses");
+    }
+  }
   build_lists(c);
   *out = c;
   return ZGR_OK;
@@ -971,7 +1007,7 @@ struct BwCarve {
   struct PerLayer { size_t xin, h1, qkv, ctx, xmid, h2, u, f, x1n, y2; };   // x1n, y2: post-LayerNorm models only
   size_t xout = 0;
   std::vector<PerLayer> layer;
-  size_t xfin = 0, hf = 0, logits = 0, targets = 0, row_loss = 0, loss = 0;
+  size_t xfin = 0, hf = 0, logits = 0, targets = 0, row_loss = 0;
   size_t dx = 0, dt = 0, dff = 0, dqkv = 0, attn = 0, stats = 0;
   size_t part = 0, part_floats = 0;  // chunk sums of the column reductions until they are added up
   size_t tA = 0, tB = 0, tW = 0, tC[4] = {}, tL[8] = {};     // bf16 operands of the matrix-core products (bf16 models)
@@ -1008,7 +1044,6 @@ BwCarve bw_carve(const zgr_ctx* c, int batch, int seq) {
   v.logits = take(m.arch == ZGR_ARCH_DECODER_LM ? M * (size_t)m.vocab * 4 : (size_t)batch * m.n_class * 4);
   v.targets = take(M * 4);
   v.row_loss = take(M * 4);
-  v.loss = take(sizeof(double));
   v.dx = take(M * d * 4);
   v.dt = take(M * d * 4);
   v.dff = take(M * ff * 4);
@@ -1074,7 +1109,6 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
     HIP_TRY(c, launch_gemm(0, X, w.theta, nullptr, R, EPI_F32, b->batch, (int)w.rows, (int)w.cols, s));
     HIP_TRY(c, launch_cloud_residual(R, reinterpret_cast<const float*>(b->y), (int64_t)b->batch * w.rows, s));
     HIP_TRY(c, launch_cloud_gt_q(R, b->batch, w.rows, w.rows, X, (int)w.cols, w.cols, grads[c->lsq_w], w.cols, 1.0f / (float)b->batch, 0, s));
-    HIP_TRY(c, hipMemcpyAsync(c->host_loss, c->ws + c->cv.loss, sizeof(double), hipMemcpyDeviceToHost, s));
     HIP_TRY(c, hipStreamSynchronize(s));
     *loss_out = c->host_loss[0];
     return std::isfinite(*loss_out) ? ZGR_OK : fail(c, ZGR_ERR_NONFINITE, "loss is not finite");
@@ -1142,8 +1176,9 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
     return ZGR_OK;
   };
   // ---- forward, every layer's intermediate results kept
+  int32_t* tgt = lm ? reinterpret_cast<int32_t*>(ws + v.targets) : nullptr;
   if (!m.post_ln) {
-    HIP_TRY(c, launch_embed(dt, tok, T(c, c->tok_emb), T(c, c->pos_emb), F(v.layer[0].xin), M, Tn, d, m.vocab, s));
+    HIP_TRY(c, launch_embed(dt, tok, T(c, c->tok_emb), T(c, c->pos_emb), F(v.layer[0].xin), M, Tn, d, m.vocab, tgt, s));
     for (int l = 0; l < m.n_layer; ++l) {
       const Layer& L = c->layers[l];
       const BwCarve::PerLayer& W = v.layer[l];
@@ -1161,7 +1196,7 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
   } else {
     // post-LayerNorm blocks: xfin holds the raw embedding sum, a layer's xin / h1 its normalised input (fp32 / storage type),
     // xmid and y2 the raw sums in front of LN1 and LN2, x1n / h2 the output of LN1
-    HIP_TRY(c, launch_embed(dt, tok, T(c, c->tok_emb), T(c, c->pos_emb), F(v.xfin), M, Tn, d, m.vocab, s));
+    HIP_TRY(c, launch_embed(dt, tok, T(c, c->tok_emb), T(c, c->pos_emb), F(v.xfin), M, Tn, d, m.vocab, tgt, s));
     HIP_TRY(c, launch_layernorm(dt, F(v.xfin), T(c, c->lnf_g), T(c, c->lnf_b), ws + v.layer[0].h1, M, d, m.ln_eps, s, F(v.layer[0].xin)));
     for (int l = 0; l < m.n_layer; ++l) {
       const Layer& L = c->layers[l];
@@ -1182,11 +1217,9 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
   float* logits = F(v.logits);
   float* dx = F(v.dx);
   float* dtb = F(v.dt);
-  double* loss_dev = reinterpret_cast<double*>(ws + v.loss);
+  double* loss_dev = c->loss_dev;
   if (lm) {
-    int32_t* tgt = reinterpret_cast<int32_t*>(ws + v.targets);
     const double inv_n = 1.0 / ((double)B * (Tn - 1));
-    HIP_TRY(c, launch_lm_targets(tok, tgt, M, Tn, m.vocab, s));
     HIP_TRY(c, launch_gemm(dt, ws + v.hf, T(c, c->tok_emb), nullptr, logits, EPI_F32, M, m.vocab, d, s, nullptr, 0, true));
     // tied head: logits = hf E^T, so dE = dlogits^T hf (the embedding rule adds its share below), dhf = dlogits E
     const void* E = T(c, c->tok_emb);
@@ -1266,7 +1299,6 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
   if (m.post_ln) HIP_TRY(c, launch_bw_layernorm(dt, F(v.xfin), T(c, c->lnf_g), dx, nullptr, dx, F(v.stats), grads[c->lnf_g], grads[c->lnf_b], sums, M, d, m.ln_eps, s));
   HIP_TRY(c, sums.flush());
   HIP_TRY(c, launch_bw_embedding(tok, dx, M, Tn, d, m.vocab, grads[c->tok_emb], grads[c->pos_emb], m.max_pos, s));
-  HIP_TRY(c, hipMemcpyAsync(c->host_loss, loss_dev, sizeof(double), hipMemcpyDeviceToHost, s));
   HIP_TRY(c, hipStreamSynchronize(s));
   *loss_out = c->host_loss[0];
   return std::isfinite(*loss_out) ? ZGR_OK : fail(c, ZGR_ERR_NONFINITE, "loss is not finite");
@@ -1284,7 +1316,6 @@ zgr_status zgr_loss(zgr_ctx* c, const zgr_batch* b, double* loss_out) {
   if (st != ZGR_OK) return st;
   st = forward_loss(c, b, 0);
   if (st != ZGR_OK) return st;
-  HIP_TRY(c, hipMemcpyAsync(c->host_loss, c->ws + c->cv.loss, sizeof(double), hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   if (c->prof.on) prof_harvest(c);
   *loss_out = c->host_loss[0];
@@ -1325,10 +1356,9 @@ zgr_status zgr_lsq_loss_static(const float* W, const float* X, const float* Y, i
   float* pred = reinterpret_cast<float*>(ptr);
   float* row_loss = pred + kStaticPredFloats;
   hipStream_t s = reinterpret_cast<hipStream_t>(hip_stream);
-  // the three launches of zgr_loss for this model; every word of scratch they read they have written in this call
+  // the launches of zgr_loss for this model; every word of scratch they read they have written in this call
   HIP_TRY(nullptr, launch_gemm(0, X, W, nullptr, pred, EPI_F32, batch, n_out, n_in, s));
-  HIP_TRY(nullptr, launch_lsq_rows(pred, Y, row_loss, batch, n_out, s));
-  HIP_TRY(nullptr, launch_mean_f64(row_loss, batch, 1.0 / batch, loss_out, s));
+  HIP_TRY(nullptr, launch_lsq_loss(pred, Y, row_loss, batch, n_out, loss_out, s));
   return ZGR_OK;
 }
 
@@ -1355,7 +1385,6 @@ zgr_status zgr_step(zgr_ctx* c, uint64_t step, const zgr_batch* b, zgr_result* o
       if (st != ZGR_OK) return st;
     }
   }
-  HIP_TRY(c, hipMemcpyAsync(c->host_loss, c->ws + c->cv.loss, 2 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   out->loss_plus = c->host_loss[0];
   out->loss_minus = c->host_loss[1];
@@ -1405,6 +1434,7 @@ void zgr_destroy(zgr_ctx* c) {
   if (!c) return;
   (void)hipStreamSynchronize(c->stream);
   for (hipEvent_t e : c->prof.ev) (void)hipEventDestroy(e);
+  give_loss_place(c->host_loss);
   delete c;
 }
 

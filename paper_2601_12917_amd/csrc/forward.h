@@ -15,7 +15,8 @@ enum { EPI_STORE = 0, EPI_GELU = 1, EPI_RESID = 2, EPI_F32 = 3, EPI_CE = 4, EPI_
 // same order, are chosen by the tiles of both.)
 struct Twin { int models = 1; int64_t w = 0; int64_t row_loss = 0; };
 
-hipError_t launch_embed(int dtype, const int32_t* tok, const void* E, const void* Pe, float* x, int M, int seq, int d, int vocab, hipStream_t s, Twin tw = {});
+// targets (may be NULL): the next token of each of the M rows, -1 at the end of a sequence
+hipError_t launch_embed(int dtype, const int32_t* tok, const void* E, const void* Pe, float* x, int M, int seq, int d, int vocab, int32_t* targets, hipStream_t s, Twin tw = {});
 // out (storage type) = LayerNorm(x) g + b; xout, when not NULL, receives the same values in fp32 (it may be x itself)
 hipError_t launch_layernorm(int dtype, const float* x, const void* g, const void* b, void* out, int M, int d, float eps, hipStream_t s, float* xout = nullptr, Twin tw = {});
 // keep_order (launch_gemm, launch_attention): sums in the order in which the large tiles, and attention key by key, take them at every size.
@@ -42,10 +43,10 @@ hipError_t launch_gemm_ce_bf16(const void* A, const void* W, const int32_t* targ
 hipError_t launch_attention(int dtype, const void* qkv, void* ctx, const int32_t* lengths, int batch, int seq, int d, int n_head, int causal, hipStream_t s,
                             bool keep_order = false, int models = 1);
 bool       attention_head_dim_supported(int dh);
-hipError_t launch_lm_targets(const int32_t* tok, int32_t* tgt, int M, int seq, int vocab, hipStream_t s);
 hipError_t launch_ce_rows(const float* logits, const int32_t* targets, float* row_loss, int M, int n, hipStream_t s, Twin tw = {});
 hipError_t launch_mean_f64(const float* row_loss, int n, double inv_count, double* out, hipStream_t s, Twin tw = {});
 hipError_t launch_cls_head(int dtype, const void* h, const void* Wc, const void* bc, float* logits, int batch, int seq, int d, int n_class, hipStream_t s, Twin tw = {});
-hipError_t launch_lsq_rows(const float* pred, const float* Y, float* row_loss, int batch, int n_out, hipStream_t s, Twin tw = {});
+// row losses and, at out (one per model), their mean
+hipError_t launch_lsq_loss(const float* pred, const float* Y, float* row_loss, int batch, int n_out, double* out, hipStream_t s, Twin tw = {});
 
 }  // namespace zgr

@@ -55,10 +55,16 @@ __device__ __forceinline__ int uniform_of(int v) {
 }
 
 // ------------------------------------------------------------------ embedding
+// With targets the rows' next tokens as well (those of one model): row m = b seq + t predicts tok[m + 1] for t < seq - 1, -1 otherwise.
 template <typename T>
 __global__ void __launch_bounds__(256) embed_kernel(const int32_t* __restrict__ tok, const T* __restrict__ E, const T* __restrict__ Pe,
-                                                    float* __restrict__ x, int M, int seq, int d, int vocab, int64_t w) {
+                                                    float* __restrict__ x, int M, int seq, int d, int vocab, int64_t w, int32_t* __restrict__ targets) {
   const int m = blockIdx.x, mt = m < M ? m : m - M;
+  if (targets && threadIdx.x == 0 && m < M) {
+    int t = -1;
+    if (m % seq < seq - 1) { t = tok[m + 1]; t = t < 0 ? 0 : (t >= vocab ? vocab - 1 : t); }   // the embedding's clamp
+    targets[m] = t;
+  }
   int t = tok[mt];
   t = t < 0 ? 0 : (t >= vocab ? vocab - 1 : t);
   const T* e = of_model(E, m >= M, w) + (size_t)t * d;
@@ -1753,15 +1759,6 @@ __global__ void __launch_bounds__(256) ce_combine_kernel(const float2* __restric
   if (threadIdx.x == 0) *row_loss = logf(s) + mx - tlogit[m];
 }
 
-// next-token targets: row m = b*seq + t predicts tok[m+1] for t < seq-1, else -1
-__global__ void lm_targets_kernel(const int32_t* __restrict__ tok, int32_t* __restrict__ tgt, int M, int seq, int vocab) {
-  const int m = blockIdx.x * blockDim.x + threadIdx.x;
-  if (m >= M) return;
-  int t = -1;
-  if ((m % seq) < seq - 1) { t = tok[m + 1]; t = t < 0 ? 0 : (t >= vocab ? vocab - 1 : t); }   // same clamp as the embedding
-  tgt[m] = t;
-}
-
 // mean of n_rows losses (ignoring the skipped ones by dividing by `count`), accumulated in fp64; a block per model
 __global__ void __launch_bounds__(256) mean_f64_kernel(const float* __restrict__ v, int n, double inv_count, double* __restrict__ out, int64_t second) {
   __shared__ double red[256];
@@ -1800,12 +1797,41 @@ __global__ void __launch_bounds__(256) lsq_rows_kernel(const float* __restrict__
   if (threadIdx.x == 0) row_loss[b < batch ? b : by + second] = 0.5f * s;
 }
 
+// The same rows and their mean in one launch, a block of sixteen waves per model, a wave per row at a time; each row summed in fp64 and rounded once.
+template <int THREADS>
+__global__ void __launch_bounds__(THREADS) lsq_loss_kernel(const float* __restrict__ pred, const float* __restrict__ Y, float* __restrict__ row_loss, int n_out, int batch, double inv_count,
+                                                           double* __restrict__ out, int64_t second) {
+  __shared__ double red[THREADS / 64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  pred += (size_t)blockIdx.x * batch * n_out;
+  row_loss += blockIdx.x * second;
+  double sum = 0.0;
+  for (int b = wave; b < batch; b += THREADS / 64) {
+    const float* p = pred + (size_t)b * n_out;
+    const float* y = Y + (size_t)b * n_out;
+    double s = 0.0;
+#pragma unroll 4
+    for (int i = lane; i < n_out; i += 64) { const float r = p[i] - y[i]; s = __builtin_fma((double)r, (double)r, s); }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    const float row = (float)(0.5 * s);
+    if (lane == 0) row_loss[b] = row;
+    sum += (double)row;
+  }
+  if (lane == 0) red[wave] = sum;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < THREADS / 64; ++w) sum += red[w];
+    out[blockIdx.x] = sum * inv_count;
+  }
+}
+
 }  // namespace
 
 // ------------------------------------------------------------------ host launchers
-hipError_t launch_embed(int dtype, const int32_t* tok, const void* E, const void* Pe, float* x, int M, int seq, int d, int vocab, hipStream_t s, Twin tw) {
-  if (dtype == 0) hipLaunchKernelGGL(embed_kernel<float>, dim3(M * tw.models), dim3(256), 0, s, tok, (const float*)E, (const float*)Pe, x, M, seq, d, vocab, tw.w);
-  else            hipLaunchKernelGGL(embed_kernel<bf16_t>, dim3(M * tw.models), dim3(256), 0, s, tok, (const bf16_t*)E, (const bf16_t*)Pe, x, M, seq, d, vocab, tw.w);
+hipError_t launch_embed(int dtype, const int32_t* tok, const void* E, const void* Pe, float* x, int M, int seq, int d, int vocab, int32_t* targets, hipStream_t s, Twin tw) {
+  if (dtype == 0) hipLaunchKernelGGL(embed_kernel<float>, dim3(M * tw.models), dim3(256), 0, s, tok, (const float*)E, (const float*)Pe, x, M, seq, d, vocab, tw.w, targets);
+  else            hipLaunchKernelGGL(embed_kernel<bf16_t>, dim3(M * tw.models), dim3(256), 0, s, tok, (const bf16_t*)E, (const bf16_t*)Pe, x, M, seq, d, vocab, tw.w, targets);
   return hipGetLastError();
 }
 
@@ -1998,11 +2024,6 @@ hipError_t launch_attention(int dtype, const void* qkv, void* ctx, const int32_t
 
 bool attention_head_dim_supported(int dh) { return dh == 8 || dh == 16 || dh == 32 || dh == 64; }
 
-hipError_t launch_lm_targets(const int32_t* tok, int32_t* tgt, int M, int seq, int vocab, hipStream_t s) {
-  hipLaunchKernelGGL(lm_targets_kernel, dim3((M + 255) / 256), dim3(256), 0, s, tok, tgt, M, seq, vocab);
-  return hipGetLastError();
-}
-
 // The smallest block that holds the row: threads without an entry, and iterations without one, cost as much as those with (2048 rows of 33 / 4097 /
 // 10000 / 20000, with the target and mean launches: 28 / 88 / 88 / 91 us when every row took 1024 threads of 4 or 50, now 20 / 28 / 37 / 58; 256
 // threads reading the row twice: 20 / 31 / 48 / 76).
@@ -2029,9 +2050,15 @@ hipError_t launch_cls_head(int dtype, const void* h, const void* Wc, const void*
   return hipGetLastError();
 }
 
-hipError_t launch_lsq_rows(const float* pred, const float* Y, float* row_loss, int batch, int n_out, hipStream_t s, Twin tw) {
+// One block a model while a wave has at most four rows and a lane sixteen entries (with a product of 64 columns in front: 32 rows of 256 7.2 us against 9.2 in two launches,
+// 64 of 256 8.6 against 9.0, 16 of 1024 7.8 against 9.2; 64 of 512 10.0 against 8.9, 128 of 128 13.1 against 9.2).
+hipError_t launch_lsq_loss(const float* pred, const float* Y, float* row_loss, int batch, int n_out, double* out, hipStream_t s, Twin tw) {
+  if (batch <= 64 && (int64_t)batch * n_out <= 16384) {
+    hipLaunchKernelGGL(lsq_loss_kernel<1024>, dim3(tw.models), dim3(1024), 0, s, pred, Y, row_loss, n_out, batch, 1.0 / batch, out, tw.row_loss);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(lsq_rows_kernel, dim3(batch * tw.models), dim3(256), 0, s, pred, Y, row_loss, n_out, batch, tw.row_loss);
-  return hipGetLastError();
+  return launch_mean_f64(row_loss, batch, 1.0 / batch, out, s, tw);
 }
 
 }  // namespace zgr

@@ -390,3 +390,59 @@ def test_non_finite_loss_is_reported_and_parameters_are_restored_lm(cfg, fused):
         # bf16 storage does not return to the starting values exactly (three roundings): the oracle's three passes do the same
         assert _close_params(got, t.theta, cfg.dtype, eps_z), t.name
     sess.close()
+
+
+@pytest.mark.parametrize("batch,n_out", [(1, 1), (1, 7), (5, 37), (16, 1024), (17, 65), (64, 256), (64, 257), (65, 252), (33, 497)])
+def test_least_squares_rows_and_mean_on_either_side_of_one_block(batch, n_out):
+    """Row losses and their mean in one launch (up to 64 rows and 16384 entries) and in two, for one model and for the step's two.  A prediction of 8 products is
+    off by at most 9 2^-24 of their magnitudes, a row of n squares by twice that and (two launches) by 2^-24 sqrt(n) more."""
+    cfg = I.shrink(I.CONFIGS["cfg1"], name=f"lsq{batch}x{n_out}", lsq_out=n_out, lsq_in=8, batch=batch, k=1, k_full=1)
+    specs, values, bases = inputs_of(cfg)
+    arrays = make_batch_arrays(cfg)
+    sess = make_session(cfg, specs, values, [None])
+    b = session_batch(sess, cfg, arrays)
+    X, Y, W = (np.asarray(a, np.float64) for a in (arrays["x"], arrays["y"], values[0]))
+    X, Y = X.reshape(batch, 8), Y.reshape(batch, n_out)
+    got = sess.loss(b)
+    rows = sess.last_row_losses(batch).astype(np.float64)
+    r, mag = X @ W.T - Y, np.abs(X) @ np.abs(W).T + np.abs(Y)
+    want, bound = 0.5 * (r ** 2).sum(1), 2.0 ** -24 * ((np.abs(r) * 9 * mag).sum(1) + (2 + np.sqrt(n_out)) * 0.5 * (r ** 2).sum(1)) + 1e-30
+    assert np.all(np.abs(rows - want) <= bound)
+    assert abs(got - rows.mean()) <= 1e-14 * abs(got)
+    lp, lm, _ = sess.step(3, b)
+    for which, loss in ((0, lp), (1, lm)):
+        rows = sess.step_row_losses(which, batch).astype(np.float64)
+        assert abs(loss - rows.mean()) <= 1e-14 * abs(loss)
+    sess.close()
+    fresh = make_session(cfg, specs, values, [None])
+    b = session_batch(fresh, cfg, arrays)
+    fresh.perturb(3, cfg.eps)
+    assert fresh.loss(b) == lp
+    fresh.close()
+
+
+def test_many_contexts_have_losses_of_their_own():
+    """More contexts than a page of loss places holds, ended out of order and replaced, from several threads."""
+    from concurrent.futures import ThreadPoolExecutor
+    cfg = I.shrink(I.CONFIGS["cfg1"], name="many", lsq_out=6, lsq_in=8, batch=3, k=1, k_full=1)
+    specs, values, _ = inputs_of(cfg)
+    arrays = make_batch_arrays(cfg)
+
+    def open_one(i):
+        sess = make_session(cfg, specs, [values[0] * (1 + i)], [None])
+        return i, sess, session_batch(sess, cfg, arrays)
+    with ThreadPoolExecutor(4) as pool:
+        live = [open_one(i) for i in range(70)]
+        want = {i: sess.loss(b) for i, sess, b in live}
+        assert len(set(want.values())) == 70
+        for i, sess, _ in live[:68:3]:
+            sess.close()
+        live = [x for j, x in enumerate(live) if j >= 68 or j % 3]
+        live += list(pool.map(open_one, range(70, 90)))
+        got = dict(pool.map(lambda x: (x[0], x[1].loss(x[2])), live))
+        assert len(set(got.values())) == len(live) and all(got[i] == want[i] for i, _, _ in live if i in want)
+    for _, sess, _ in live:
+        sess.close()
+    i, sess, b = open_one(0)
+    assert sess.loss(b) == want[0]
+    sess.close()
