@@ -1123,8 +1123,9 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
   // The products of the backward half.  fp32 models and ragged token counts: fp32 products on the operands as they lie.  bf16 models
   // (token count a multiple of 64): the forward pass's matrix-core GEMM, which contracts along the rows of both
   // operands, on bf16 copies written out with the contraction index innermost.
-  auto product = [&](const void* A, bool a_k, int64_t lda, const void* B, int64_t ldb, float* C, int64_t ldc, int Mp, int Np, int Kp, float* a_sums, int row_blocks = 1) {
+  auto product = [&](const void* A, bool a_k, int64_t lda, const void* B, int64_t ldb, float* C, int64_t ldc, int Mp, int Np, int Kp, float* a_sums, int row_blocks = 1, int* parts_left = nullptr) {
     ProductArgs p;
+    p.parts_left = parts_left;
     p.A = A; p.a_k = a_k; p.lda = lda; p.B = B; p.b_dtype = dt == ZGR_BF16 ? 1 : 0; p.b_k = false; p.ldb = ldb; p.C = C; p.ldc = ldc;
     p.M = Mp; p.N = Np; p.K = Kp; p.a_sums = a_sums; p.row_blocks = row_blocks; p.scratch = F(v.split); p.scratch_floats = kProductScratch;
     return launch_product(p, s);
@@ -1147,7 +1148,8 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
   weights.K = (int)(((size_t)M + 63) / 64 * 64) * weights.fold;
   // One linear layer y = a W^T + b, a [M, Kp] kept in the storage type, W [Np, Kp], with dL/dy = dy (act'(u) dy when u is given): dW = dy^T a, db = column
   // sums, da = dy W.  The layer's outputs may be up to three equal blocks with weights and biases of their own (W's rows in one piece).
-  auto linear_backward = [&](float* dy, const float* u, int Np, const void* W, int Kp, const void* a, int blocks, const int* wi, const int* bi, float* da, int which) -> zgr_status {
+  // parts_left: da may stay in parts at split (launch_product).
+  auto linear_backward = [&](float* dy, const float* u, int Np, const void* W, int Kp, const void* a, int blocks, const int* wi, const int* bi, float* da, int which, int* parts_left = nullptr) -> zgr_status {
     float* db[3] = {};
     for (int p = 0; p < blocks; ++p) db[p] = grads[bi[p]];
     const int n = Np / blocks;
@@ -1166,12 +1168,12 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
     } else if (on_planes(Np, Kp)) {
       HIP_TRY(c, launch_bw_gradient_planes(dy, u, relu, M, Np, ws + v.tC[which], a, Kp, ws + v.tL[2 * which], db, blocks, sums, s));
       queue_weights();
-      HIP_TRY(c, product(dy, true, Np, W, Kp, da, Kp, M, Kp, Np, nullptr));
+      HIP_TRY(c, product(dy, true, Np, W, Kp, da, Kp, M, Kp, Np, nullptr, 1, parts_left));
     } else {
       if (u) HIP_TRY(c, launch_bw_act(relu, u, dy, (int64_t)M * Np, s));
       for (int p = 1; p < blocks; ++p) whole = whole && db[p] == db[0] + (size_t)p * n;      // and the biases': the bits of one product each
       for (int p = 0; p < (whole ? 1 : blocks); ++p) HIP_TRY(c, product(dy + (size_t)p * n, false, Np, a, Kp, grads[wi[p]], Kp, whole ? Np : n, Kp, M, db[p], whole ? blocks : 1));
-      HIP_TRY(c, product(dy, true, Np, W, Kp, da, Kp, M, Kp, Np, nullptr));
+      HIP_TRY(c, product(dy, true, Np, W, Kp, da, Kp, M, Kp, Np, nullptr, 1, parts_left));
     }
     return ZGR_OK;
   };
@@ -1275,25 +1277,28 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
     // x_out (or y2) = x_mid (or x1n) + f W2^T + b2
     if ((st = linear_backward(dx, nullptr, d, T(c, L.w2), ff, ws + W.f, 1, &L.w2, &L.b2, dff, 0)) != ZGR_OK) return st;
     // f = act(u), u = h2 W1^T + b1
-    if ((st = linear_backward(dff, F(W.u), ff, T(c, L.w1), d, ws + W.h2, 1, &L.w1, &L.b1, dtb, 1)) != ZGR_OK) return st;
+    int parts = 1;
+    int* left = !m.post_ln && bw_layernorm_adds_parts(d) ? &parts : nullptr;      // the LayerNorm that follows adds up
+    if ((st = linear_backward(dff, F(W.u), ff, T(c, L.w1), d, ws + W.h2, 1, &L.w1, &L.b1, dtb, 1, left)) != ZGR_OK) return st;
     if (m.post_ln) {
       // h2 = x1n = LN1(y1): dL/dx1n = dx + dh2, then dx <- dL/dy1
       HIP_TRY(c, launch_bw_add(dtb, dx, nx, s));
       HIP_TRY(c, launch_bw_layernorm(dt, F(W.xmid), T(c, L.ln1_g), dtb, nullptr, dx, F(v.stats), grads[L.ln1_g], grads[L.ln1_b], sums, M, d, m.ln_eps, s));
     } else {
       // h2 = LN2(x_mid): dx <- dx + LN2'(dh2)
-      HIP_TRY(c, launch_bw_layernorm(dt, F(W.xmid), T(c, L.ln2_g), dtb, dx, dx, F(v.stats), grads[L.ln2_g], grads[L.ln2_b], sums, M, d, m.ln_eps, s));
+      HIP_TRY(c, launch_bw_layernorm(dt, F(W.xmid), T(c, L.ln2_g), parts > 1 ? F(v.split) : dtb, dx, dx, F(v.stats), grads[L.ln2_g], grads[L.ln2_b], sums, M, d, m.ln_eps, s, parts));
     }
     // x_mid (or y1) = x_in + ctx Wo^T + bo
     if ((st = linear_backward(dx, nullptr, d, T(c, L.wo), d, ws + W.ctx, 1, &L.wo, &L.bo, dtb, 2)) != ZGR_OK) return st;
     HIP_TRY(c, launch_bw_attention(dt, ws + W.qkv, dtb, lengths, B, Tn, d, H, lm ? 1 : 0, F(v.attn), dqkv, s));
     // q, k, v = h1 W{q,k,v}^T + b{q,k,v}: three column blocks of dqkv; Wq, Wk, Wv are adjacent, one [3 d, d] matrix
     const int wi[3] = {L.wq, L.wk, L.wv}, bi[3] = {L.bq, L.bk, L.bv};
-    if ((st = linear_backward(dqkv, nullptr, 3 * d, T(c, L.wq), d, ws + W.h1, 3, wi, bi, dtb, 3)) != ZGR_OK) return st;
+    parts = 1;
+    if ((st = linear_backward(dqkv, nullptr, 3 * d, T(c, L.wq), d, ws + W.h1, 3, wi, bi, dtb, 3, left)) != ZGR_OK) return st;
     HIP_TRY(c, launch_product_group(weights, s));
     weights.count = 0;
     if (m.post_ln) HIP_TRY(c, launch_bw_add(dx, dtb, nx, s));                                    // h1 = x_in
-    else HIP_TRY(c, launch_bw_layernorm(dt, F(W.xin), T(c, L.ln1_g), dtb, dx, dx, F(v.stats), grads[L.ln1_g], grads[L.ln1_b], sums, M, d, m.ln_eps, s));
+    else HIP_TRY(c, launch_bw_layernorm(dt, F(W.xin), T(c, L.ln1_g), parts > 1 ? F(v.split) : dtb, dx, dx, F(v.stats), grads[L.ln1_g], grads[L.ln1_b], sums, M, d, m.ln_eps, s, parts));
   }
   // post-LN: x_0 = LNF(embedding sum)
   if (m.post_ln) HIP_TRY(c, launch_bw_layernorm(dt, F(v.xfin), T(c, c->lnf_g), dx, nullptr, dx, F(v.stats), grads[c->lnf_g], grads[c->lnf_b], sums, M, d, m.ln_eps, s));

@@ -49,9 +49,11 @@ hipError_t launch_bw_fill(float* p, int64_t n, float v, hipStream_t s);
 // row_loss of logits [rows, n] (0 where the target is negative), and (softmax - onehot(target)) inv_count in place of the logits or, with d16,
 // in bf16 at d16 [rows, ld16] with zeros past n; rows with a target outside [0, n) become zeros
 hipError_t launch_bw_cross_entropy(float* logits, const int32_t* targets, int rows, int n, float inv_count, float* row_loss, void* d16, int64_t ld16, hipStream_t s);
-// y = LayerNorm(x) g + b: dx_out = (add ? add : 0) + dL/dx (dx_out may be add or dy), dg, db from dy; stats: 2 M floats of scratch
+// y = LayerNorm(x) g + b: dx_out = (add ? add : 0) + dL/dx (dx_out may be add or dy), dg, db from dy; stats: 2 M floats of scratch.  dy: the sum of dy_parts parts of M d
+// floats each, one behind the other (more than one where bw_layernorm_adds_parts).
+bool       bw_layernorm_adds_parts(int d);
 hipError_t launch_bw_layernorm(int dtype, const float* x, const void* g, const float* dy, const float* add, float* dx_out, float* stats, float* dg, float* db,
-                               SumQueue& sums, int M, int d, float eps, hipStream_t s);
+                               SumQueue& sums, int M, int d, float eps, hipStream_t s, int dy_parts = 1);
 // f = act(u) in the storage type (erf-GELU, or ReLU when relu != 0); df <- df act'(u); dst += src
 hipError_t launch_bw_act_forward(int dtype, int relu, const float* u, void* f, int64_t n, hipStream_t s);
 hipError_t launch_bw_act(int relu, const float* u, float* df, int64_t n, hipStream_t s);

@@ -347,8 +347,10 @@ __global__ void __launch_bounds__(256) ln_backward_kernel(const float* __restric
 // db[c] = sum_m dy[m][c] in registers too.  part[b][0 | 1][c]: the block's sums, its four waves added in order.  Bound by launch and
 // load latency at a few thousand rows: with a kernel each for the row statistics, the partial sums and the two final sums the rule
 // took five launches and three reads (27 us per LayerNorm of 2048 x 768, now 13).
-template <typename T, int MAXV>
-__global__ void __launch_bounds__(256) ln_backward_wave_kernel(const float* __restrict__ x, const T* __restrict__ g, const float* dy, const float* add, float* dx_out,
+// dy comes as dy_parts parts, dy_stride floats apart, which are added in their order: those of a product whose sums are split over blocks, whose adding up was a launch
+// of 4.4 us (four parts of 231 x 1024 7.9 us here, one 7.7; loaded one after the other 11).
+template <typename T, int MAXV, bool PARTS>
+__global__ void __launch_bounds__(256) ln_backward_wave_kernel(const float* __restrict__ x, const T* __restrict__ g, const float* dy, int dy_parts, int64_t dy_stride, const float* add, float* dx_out,
                                                                float* __restrict__ part, int M, int d, float eps) {            // add or dy may be dx_out
   __shared__ __attribute__((aligned(16))) float red[4][256 * MAXV];
   struct alignas(sizeof(T) * 4) V4 { T e[4]; };
@@ -370,8 +372,23 @@ __global__ void __launch_bounds__(256) ln_backward_wave_kernel(const float* __re
       const int i = lane + 64 * j;
       v[j] = w[j] = make_float4(0.f, 0.f, 0.f, 0.f);
       if (i < nv) { v[j] = xr[i]; w[j] = dr[i]; }
-      s += (v[j].x + v[j].y) + (v[j].z + v[j].w);
     }
+    constexpr int AHEAD = MAXV > 4 ? 1 : 3;                  // parts under way at a time (past the last one the first is read and left)
+    for (int p = 1; PARTS && p < dy_parts; p += AHEAD) {
+      float4 t[AHEAD][MAXV];
+#pragma unroll
+      for (int u = 0; u < AHEAD; ++u)
+#pragma unroll
+        for (int j = 0; j < MAXV; ++j) t[u][j] = reinterpret_cast<const float4*>(dy + (size_t)row * d + (p + u < dy_parts ? p + u : 0) * dy_stride)[min(lane + 64 * j, nv - 1)];
+#pragma unroll
+      for (int u = 0; u < AHEAD; ++u)
+        if (p + u < dy_parts)
+#pragma unroll
+          for (int j = 0; j < MAXV; ++j)
+            if (lane + 64 * j < nv) { w[j].x += t[u][j].x; w[j].y += t[u][j].y; w[j].z += t[u][j].z; w[j].w += t[u][j].w; }
+    }
+#pragma unroll
+    for (int j = 0; j < MAXV; ++j) s += (v[j].x + v[j].y) + (v[j].z + v[j].w);
     const float mu = wave_sum(s) / d;
     float q = 0.f;
 #pragma unroll
@@ -978,16 +995,19 @@ static int ln_blocks(int M) { return M < 4 * kLnBlocks ? (M + 3) / 4 : kLnBlocks
 size_t bw_layernorm_floats(int M, int d) { return ((size_t)2 * (ln_wave_form(d) ? ln_blocks(M) : kColParts) * d + 63) / 64 * 64; }
 size_t bw_bias_floats(int M, int n) { const size_t tiles = (size_t)(M + 63) / 64; return std::min(tiles, (size_t)kColParts) * n + 4 * 64; }
 
+bool bw_layernorm_adds_parts(int d) { return ln_wave_form(d); }
 hipError_t launch_bw_layernorm(int dtype, const float* x, const void* g, const float* dy, const float* add, float* dx_out, float* stats, float* dg, float* db,
-                               SumQueue& sums, int M, int d, float eps, hipStream_t s) {
+                               SumQueue& sums, int M, int d, float eps, hipStream_t s, int dy_parts) {
   float* part = nullptr;
+  if (dy_parts < 1 || (dy_parts > 1 && !ln_wave_form(d))) return hipErrorInvalidValue;
+  const int64_t dy_stride = (int64_t)M * d;
   auto queue = [&](int parts) { sums.add(SumJob{part, dg, (int64_t)2 * d, parts, d}); sums.add(SumJob{part + d, db, (int64_t)2 * d, parts, d}); };
   if (ln_wave_form(d)) {
     const int blocks = ln_blocks(M);
     const dim3 grid((unsigned)blocks);
     const hipError_t e = sums.take((size_t)2 * blocks * d, 2, &part);
     if (e != hipSuccess) return e;
-#define ZGR_LN_BACKWARD(T, MAXV) hipLaunchKernelGGL((ln_backward_wave_kernel<T, MAXV>), grid, dim3(256), 0, s, x, reinterpret_cast<const T*>(g), dy, add, dx_out, part, M, d, eps)
+#define ZGR_LN_BACKWARD(T, MAXV) hipLaunchKernelGGL((dy_parts > 1 ? ln_backward_wave_kernel<T, MAXV, true> : ln_backward_wave_kernel<T, MAXV, false>), grid, dim3(256), 0, s, x, reinterpret_cast<const T*>(g), dy, dy_parts, dy_stride, add, dx_out, part, M, d, eps)
     if (dtype == 1) { if (d <= 512) ZGR_LN_BACKWARD(bf16_t, 2); else if (d <= 1024) ZGR_LN_BACKWARD(bf16_t, 4); else ZGR_LN_BACKWARD(bf16_t, 8); }
     else            { if (d <= 512) ZGR_LN_BACKWARD(float, 2); else if (d <= 1024) ZGR_LN_BACKWARD(float, 4); else ZGR_LN_BACKWARD(float, 8); }
 #undef ZGR_LN_BACKWARD

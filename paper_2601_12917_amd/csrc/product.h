@@ -23,6 +23,8 @@ struct ProductArgs {
   int models = 1;                   // the batches are those of that many models on the same inputs; each one's sums take the order they take by themselves
   int row_blocks = 1;               // M is that many equal blocks of rows; each one's sums take the order they take in a product of its own
   float* scratch = nullptr; size_t scratch_floats = 0;    // for the parts of a split sum; without it sums are split inside workgroups only
+  int* parts_left = nullptr;        // when not NULL (one batch, EPI_STORE, alpha = 1, no bias): a sum in several parts is left to the reader, who adds parts of M N floats
+                                    // each from scratch on, in their order: *parts_left of them, or 1, and C holds the result
 };
 hipError_t launch_product(const ProductArgs& p, hipStream_t s);
 

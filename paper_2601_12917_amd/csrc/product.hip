@@ -528,6 +528,7 @@ bool near_operand(const void* p, int dtype, bool along_k, int64_t ld, int n, int
 hipError_t launch_product(const ProductArgs& p, hipStream_t s) {
   if (p.M < 1 || p.N < 1 || p.batches < 1) return hipSuccess;
   if (p.K < 0 || p.batches > 65535 || p.zdiv < 1 || (p.a_sums && (p.a_k || p.a_dtype != 0 || p.batches != 1))) return hipErrorInvalidValue;
+  if (p.parts_left && (p.batches != 1 || p.row_blocks != 1 || p.alpha != 1.0f || p.epilogue != EPI_STORE || p.bias || p.a_sums || p.ldc != p.N)) return hipErrorInvalidValue;
   if (p.models < 1 || p.batches % p.models || p.row_blocks < 1 || p.M % p.row_blocks || (p.row_blocks > 1 && (p.batches != 1 || p.a_k))) return hipErrorInvalidValue;
   const int rows = p.M / p.row_blocks;
   const int64_t tiles = (((int64_t)rows + 63) / 64) * (((int64_t)p.N + 63) / 64) * (p.batches / p.models);
@@ -537,7 +538,8 @@ hipError_t launch_product(const ProductArgs& p, hipStream_t s) {
   // 20.4 us with eight, 385 x 3072 x 768: 36 with four, 40 with eight).  Where that is still too few the sum is split over
   // blocks as well, each share at least eight steps (385 x 768 x 3072: 55 us undivided, 33 in three parts).
   // With planes a share of the sum takes a third of the time and adding up costs the same: four waves a piece, and half the blocks
-  // (231 x 1024 x 4096: 20 us with eight, 18 with four waves and four parts; 231 x 4096 x 1024: 24 in two parts, 16 undivided).
+  // (231 x 1024 x 4096: 20 us with eight, 18 with four waves and four parts; 231 x 4096 x 1024: 24 in two parts, 16 undivided).  (A reader that adds the parts up is
+  // no reason for more of them: eight of that first product 16 us, four 13.)
   const bool planes = p.a_dtype == 1 || p.b_dtype == 1;
   int split = tiles >= kWaves || steps < 4 ? 1 : (planes || tiles >= 320 || steps < 32 ? 4 : 8);
   int parts = 1;
@@ -593,7 +595,8 @@ hipError_t launch_product(const ProductArgs& p, hipStream_t s) {
     case 0b1111: e = launch_t<bf16_t, bf16_t, true, true>(k, near, grid, s); break;
     default: break;
   }
-  if (e != hipSuccess || parts == 1) return e;
+  if (p.parts_left) *p.parts_left = parts;
+  if (e != hipSuccess || parts == 1 || p.parts_left) return e;
   const int64_t total = n + (p.a_sums ? p.M : 0);
   hipLaunchKernelGGL(product_sum_kernel, dim3((unsigned)(total / 256 + 1 < 2048 ? total / 256 + 1 : 2048), (unsigned)p.batches), dim3(256), 0, s, p.scratch, parts, n, p.N, p.C, p.ldc, p.alpha, sum_part, p.M, p.a_sums, p.epilogue, p.bias, p.c_outer, p.bias_outer);
   return hipGetLastError();

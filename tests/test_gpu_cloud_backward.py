@@ -376,3 +376,31 @@ def test_argument_errors_are_reported_not_executed():
     assert lib.zgr_cloud_backward(sess.ctx, Ct.byref(batch), ptrs, len(grads), Ct.byref(v), ws.data_ptr() + 64, need) == B.ZGR_ERR_WORKSPACE
     ptrs[3] = None
     assert lib.zgr_cloud_backward(sess.ctx, Ct.byref(batch), ptrs, len(grads), Ct.byref(v), ws.data_ptr(), need) == B.ZGR_ERR_NULL
+
+
+@pytest.mark.parametrize("dtype,d,n_head,ff,batch,seq", [
+    ("f32", 128, 2, 2048, 1, 33),      # FC1's sum in two parts
+    ("f32", 704, 11, 5120, 2, 19),     # in several, rows of 704; Q, K, V's in two
+    ("bf16", 128, 2, 2048, 1, 33),     # four parts, all requested at once
+    ("bf16", 576, 9, 4608, 1, 70),     # nine of FC1's, three of Q, K, V's
+    ("bf16", 1088, 17, 2048, 1, 31),   # wide rows, where they are requested one by one; the weight gradients' third tile size
+])
+def test_layernorm_adds_the_parts_of_a_split_product(dtype, d, n_head, ff, batch, seq):
+    """Long sums over few rows: the products in front of the LayerNorm rules leave parts.  Bounds as above."""
+    cfg = I.shrink(I.CONFIGS["cfg3"], name="bw_parts", dtype=dtype, n_layer=2, d_model=d, n_head=n_head, d_ff=ff, vocab=203, max_pos=80, batch=batch, seq=seq, k=8, k_full=8)
+    sess, specs, P = _setup(cfg, scale=2.0)
+    arrays = _batch(cfg, 3)
+    loss, grads = _device(sess, cfg, arrays)
+    loss_or, grads_or = _oracle(cfg, P, arrays)
+    assert abs(loss - loss_or) <= (1e-4 if dtype == "f32" else 2e-2) * max(1.0, abs(loss_or))
+    for i, s in enumerate(specs):
+        want = grads_or[s.name]
+        if s.role == I.ROLE_BK:
+            continue
+        if dtype == "f32":
+            assert np.abs(grads[i] - want).max() <= 2e-4 * np.abs(want).max(), s.name
+        else:
+            cos = float((grads[i] * want).sum() / (np.linalg.norm(grads[i]) * np.linalg.norm(want)))
+            ratio = float(np.linalg.norm(grads[i]) / np.linalg.norm(want))
+            assert cos >= 0.995 and abs(ratio - 1.0) <= 0.05, (s.name, cos, ratio)
+    sess.close()
