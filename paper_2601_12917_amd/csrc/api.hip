@@ -1145,11 +1145,15 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
   // The weights' gradients of a block, which nothing waits for, in one launch at its end.
   ProductGroup weights;
   weights.fold = v.planes ? 3 : 1;
-  weights.K = (int)(((size_t)M + 63) / 64 * 64) * weights.fold;
+  const int Mp = (M + 63) / 64 * 64;
+  // What a LayerNorm rule reads: da, or the parts of it that the rule adds up itself.
+  struct Left { const float* at; int parts; };
   // One linear layer y = a W^T + b, a [M, Kp] kept in the storage type, W [Np, Kp], with dL/dy = dy (act'(u) dy when u is given): dW = dy^T a, db = column
   // sums, da = dy W.  The layer's outputs may be up to three equal blocks with weights and biases of their own (W's rows in one piece).
-  // parts_left: da may stay in parts at split (launch_product).
-  auto linear_backward = [&](float* dy, const float* u, int Np, const void* W, int Kp, const void* a, int blocks, const int* wi, const int* bi, float* da, int which, int* parts_left = nullptr) -> zgr_status {
+  // left: da may stay in parts (those of a product on bf16 operands in place of dy, which has been read by then).
+  auto linear_backward = [&](float* dy, const float* u, int Np, const void* W, int Kp, const void* a, int blocks, const int* wi, const int* bi, float* da, int which, Left* left = nullptr) -> zgr_status {
+    if (left) *left = Left{da, 1};
+    int in_split = 1;
     float* db[3] = {};
     for (int p = 0; p < blocks; ++p) db[p] = grads[bi[p]];
     const int n = Np / blocks;
@@ -1158,23 +1162,30 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
     auto queue_weights = [&]() {
       const unsigned char* dyT = ws + v.tC[which];
       for (int p = 0; p < (whole ? 1 : blocks); ++p)
-        weights.job[weights.count++] = GroupedProduct{dyT + (size_t)p * n * weights.K * 2, ws + v.tL[2 * which], grads[wi[p]], whole ? Np : n, Kp};
+        weights.job[weights.count++] = GroupedProduct{dyT + (size_t)p * n * Mp * weights.fold * 2, ws + v.tL[2 * which], grads[wi[p]], whole ? Np : n, Kp, Mp * weights.fold, Mp * weights.fold, Mp};
     };
     if (on_bf16(Np, Kp)) {
       // a and W transposed were written at the start of the block
       HIP_TRY(c, launch_bw_gradient_operands(dy, u, relu, M, Np, ws + v.tC[which], ws + v.tA, db, blocks, sums, s));
       queue_weights();
-      HIP_TRY(c, launch_gemm(ZGR_BF16, ws + v.tA, ws + v.tL[2 * which + 1], nullptr, da, EPI_F32, M, Kp, Np, s));
+      const int slices = left ? product_slices(M, Kp, Np, Np / Kp) : 1;
+      if (slices > 1) {
+        HIP_TRY(c, launch_product_slices(ws + v.tA, ws + v.tL[2 * which + 1], dy, M, Kp, Np, slices, s));
+        *left = Left{dy, slices};
+      } else {
+        HIP_TRY(c, launch_gemm(ZGR_BF16, ws + v.tA, ws + v.tL[2 * which + 1], nullptr, da, EPI_F32, M, Kp, Np, s));
+      }
     } else if (on_planes(Np, Kp)) {
       HIP_TRY(c, launch_bw_gradient_planes(dy, u, relu, M, Np, ws + v.tC[which], a, Kp, ws + v.tL[2 * which], db, blocks, sums, s));
       queue_weights();
-      HIP_TRY(c, product(dy, true, Np, W, Kp, da, Kp, M, Kp, Np, nullptr, 1, parts_left));
+      HIP_TRY(c, product(dy, true, Np, W, Kp, da, Kp, M, Kp, Np, nullptr, 1, left ? &in_split : nullptr));
     } else {
       if (u) HIP_TRY(c, launch_bw_act(relu, u, dy, (int64_t)M * Np, s));
       for (int p = 1; p < blocks; ++p) whole = whole && db[p] == db[0] + (size_t)p * n;      // and the biases': the bits of one product each
       for (int p = 0; p < (whole ? 1 : blocks); ++p) HIP_TRY(c, product(dy + (size_t)p * n, false, Np, a, Kp, grads[wi[p]], Kp, whole ? Np : n, Kp, M, db[p], whole ? blocks : 1));
-      HIP_TRY(c, product(dy, true, Np, W, Kp, da, Kp, M, Kp, Np, nullptr, 1, parts_left));
+      HIP_TRY(c, product(dy, true, Np, W, Kp, da, Kp, M, Kp, Np, nullptr, 1, left ? &in_split : nullptr));
     }
+    if (in_split > 1) *left = Left{F(v.split), in_split};
     return ZGR_OK;
   };
   // ---- forward, every layer's intermediate results kept
@@ -1220,6 +1231,7 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
   float* dx = F(v.dx);
   float* dtb = F(v.dt);
   double* loss_dev = c->loss_dev;
+  Left dhf{dtb, 1};
   if (lm) {
     const double inv_n = 1.0 / ((double)B * (Tn - 1));
     HIP_TRY(c, launch_gemm(dt, ws + v.hf, T(c, c->tok_emb), nullptr, logits, EPI_F32, M, m.vocab, d, s, nullptr, 0, true));
@@ -1234,7 +1246,14 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
       HIP_TRY(c, launch_bw_transpose_bf16(ws + v.hf, M, d, d, ws + v.tB, M, s));
       HIP_TRY(c, launch_gemm(ZGR_BF16, logits, ws + v.tB, nullptr, dE, EPI_F32, m.vocab, d, M, s));
       HIP_TRY(c, launch_bw_transpose_bf16(E, m.vocab, d, d, ws + v.tW, Vpad, s));
-      HIP_TRY(c, launch_gemm(ZGR_BF16, ws + v.tA, ws + v.tW, nullptr, dtb, EPI_F32, M, d, Vpad, s));
+      // the logits' place is free again
+      const int slices = !m.post_ln && bw_layernorm_adds_parts(d) ? product_slices(M, d, Vpad, m.vocab / d) : 1;
+      if (slices > 1) {
+        HIP_TRY(c, launch_product_slices(ws + v.tA, ws + v.tW, logits, M, d, Vpad, slices, s));
+        dhf = Left{logits, slices};
+      } else {
+        HIP_TRY(c, launch_gemm(ZGR_BF16, ws + v.tA, ws + v.tW, nullptr, dtb, EPI_F32, M, d, Vpad, s));
+      }
     } else {
       HIP_TRY(c, launch_bw_cross_entropy(logits, tgt, M, m.vocab, (float)inv_n, F(v.row_loss), nullptr, 0, s));
       HIP_TRY(c, product(logits, false, m.vocab, ws + v.hf, d, dE, d, m.vocab, d, M, nullptr));
@@ -1256,7 +1275,7 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
   // ---- the blocks in reverse; dx holds dL/d(residual stream) at the block's output
   const int64_t nx = (int64_t)M * d;
   if (m.post_ln) HIP_TRY(c, hipMemcpyAsync(dx, dtb, xbytes, hipMemcpyDeviceToDevice, s));       // the head reads the last LN2's output itself
-  else HIP_TRY(c, launch_bw_layernorm(dt, F(v.xfin), T(c, c->lnf_g), dtb, nullptr, dx, F(v.stats), grads[c->lnf_g], grads[c->lnf_b], sums, M, d, m.ln_eps, s));
+  else HIP_TRY(c, launch_bw_layernorm(dt, F(v.xfin), T(c, c->lnf_g), dhf.at, nullptr, dx, F(v.stats), grads[c->lnf_g], grads[c->lnf_b], sums, M, d, m.ln_eps, s, dhf.parts));
   for (int l = m.n_layer - 1; l >= 0; --l) {
     const Layer& L = c->layers[l];
     const BwCarve::PerLayer& W = v.layer[l];
@@ -1277,8 +1296,8 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
     // x_out (or y2) = x_mid (or x1n) + f W2^T + b2
     if ((st = linear_backward(dx, nullptr, d, T(c, L.w2), ff, ws + W.f, 1, &L.w2, &L.b2, dff, 0)) != ZGR_OK) return st;
     // f = act(u), u = h2 W1^T + b1
-    int parts = 1;
-    int* left = !m.post_ln && bw_layernorm_adds_parts(d) ? &parts : nullptr;      // the LayerNorm that follows adds up
+    Left dy{dtb, 1};
+    Left* left = !m.post_ln && bw_layernorm_adds_parts(d) ? &dy : nullptr;      // the LayerNorm that follows adds up
     if ((st = linear_backward(dff, F(W.u), ff, T(c, L.w1), d, ws + W.h2, 1, &L.w1, &L.b1, dtb, 1, left)) != ZGR_OK) return st;
     if (m.post_ln) {
       // h2 = x1n = LN1(y1): dL/dx1n = dx + dh2, then dx <- dL/dy1
@@ -1286,19 +1305,18 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
       HIP_TRY(c, launch_bw_layernorm(dt, F(W.xmid), T(c, L.ln1_g), dtb, nullptr, dx, F(v.stats), grads[L.ln1_g], grads[L.ln1_b], sums, M, d, m.ln_eps, s));
     } else {
       // h2 = LN2(x_mid): dx <- dx + LN2'(dh2)
-      HIP_TRY(c, launch_bw_layernorm(dt, F(W.xmid), T(c, L.ln2_g), parts > 1 ? F(v.split) : dtb, dx, dx, F(v.stats), grads[L.ln2_g], grads[L.ln2_b], sums, M, d, m.ln_eps, s, parts));
+      HIP_TRY(c, launch_bw_layernorm(dt, F(W.xmid), T(c, L.ln2_g), dy.at, dx, dx, F(v.stats), grads[L.ln2_g], grads[L.ln2_b], sums, M, d, m.ln_eps, s, dy.parts));
     }
     // x_mid (or y1) = x_in + ctx Wo^T + bo
     if ((st = linear_backward(dx, nullptr, d, T(c, L.wo), d, ws + W.ctx, 1, &L.wo, &L.bo, dtb, 2)) != ZGR_OK) return st;
     HIP_TRY(c, launch_bw_attention(dt, ws + W.qkv, dtb, lengths, B, Tn, d, H, lm ? 1 : 0, F(v.attn), dqkv, s));
     // q, k, v = h1 W{q,k,v}^T + b{q,k,v}: three column blocks of dqkv; Wq, Wk, Wv are adjacent, one [3 d, d] matrix
     const int wi[3] = {L.wq, L.wk, L.wv}, bi[3] = {L.bq, L.bk, L.bv};
-    parts = 1;
     if ((st = linear_backward(dqkv, nullptr, 3 * d, T(c, L.wq), d, ws + W.h1, 3, wi, bi, dtb, 3, left)) != ZGR_OK) return st;
     HIP_TRY(c, launch_product_group(weights, s));
     weights.count = 0;
     if (m.post_ln) HIP_TRY(c, launch_bw_add(dx, dtb, nx, s));                                    // h1 = x_in
-    else HIP_TRY(c, launch_bw_layernorm(dt, F(W.xin), T(c, L.ln1_g), parts > 1 ? F(v.split) : dtb, dx, dx, F(v.stats), grads[L.ln1_g], grads[L.ln1_b], sums, M, d, m.ln_eps, s, parts));
+    else HIP_TRY(c, launch_bw_layernorm(dt, F(W.xin), T(c, L.ln1_g), dy.at, dx, dx, F(v.stats), grads[L.ln1_g], grads[L.ln1_b], sums, M, d, m.ln_eps, s, dy.parts));
   }
   // post-LN: x_0 = LNF(embedding sum)
   if (m.post_ln) HIP_TRY(c, launch_bw_layernorm(dt, F(v.xfin), T(c, c->lnf_g), dx, nullptr, dx, F(v.stats), grads[c->lnf_g], grads[c->lnf_b], sums, M, d, m.ln_eps, s));
@@ -1597,8 +1615,7 @@ zgr_status zgr_debug_weight_gradient(float* dy, const float* u, int32_t relu, co
   HIP_TRY(nullptr, launch_bw_gradient_planes(dy, u, relu, M, N, ws, x, K, ws + planes, db, parts, sums, s));
   ProductGroup g;
   g.fold = 3;
-  g.K = (int)(3 * Mp);
-  for (int p = 0; p < parts; ++p) g.job[g.count++] = GroupedProduct{ws + (size_t)p * (N / parts) * g.K * 2, ws + planes, dW[p], N / parts, K};
+  for (int p = 0; p < parts; ++p) g.job[g.count++] = GroupedProduct{ws + (size_t)p * (N / parts) * 3 * Mp * 2, ws + planes, dW[p], N / parts, K, (int)(3 * Mp), (int)(3 * Mp), (int)Mp};
   HIP_TRY(nullptr, launch_product_group(g, s));
   HIP_TRY(nullptr, sums.flush());
   return ZGR_OK;

@@ -28,12 +28,15 @@ hipError_t launch_layernorm(int dtype, const float* x, const void* g, const void
 // shared_a: both models read the same A.  resid: what EPI_RESID adds to, where that is not out itself (sums in the order of the tiles then).
 hipError_t launch_gemm(int dtype, const void* A, const void* W, const void* bias, void* out, int epi, int M, int N, int K, hipStream_t s, float* scratch = nullptr,
                        size_t scratch_floats = 0, bool keep_order = false, Twin tw = {}, bool shared_a = false, const float* resid = nullptr);
-// Several bf16 products out = A W^T in one launch, out [M, N] in fp32; all with A's rows of K and W's of K / fold terms.  fold = 3: A's rows hold three runs (the
+// Several bf16 products out = A W^T in one launch, out [M, N] in fp32, A's rows of K and W's of K / fold terms, lda and ldw entries apart.  fold = 3: A's rows hold three runs (the
 // planes of fp32 numbers, planes.h), each of which is multiplied with W's row.  K a multiple of 64 fold, rows on 16 bytes.
 constexpr int kGroupedProducts = 6;
-struct GroupedProduct { const void* A; const void* W; float* out; int M, N; };
-struct ProductGroup { GroupedProduct job[kGroupedProducts]; int count = 0, K = 0, fold = 1; };
+struct GroupedProduct { const void* A; const void* W; float* out; int M, N, K, lda, ldw; };
+struct ProductGroup { GroupedProduct job[kGroupedProducts]; int count = 0, fold = 1; };
 hipError_t launch_product_group(const ProductGroup& g, hipStream_t s);
+// One such product with its sum in slices, which leave parts of M N floats one behind the other for the reader to add up in their order; as many of them as pay, at most `most`.
+int        product_slices(int M, int N, int K, int most);
+hipError_t launch_product_slices(const void* A, const void* W, float* out, int M, int N, int K, int slices, hipStream_t s);
 // The kernel of an fp32 projection (zgr.h, zgr_debug_gemm_form).  whole_rows: K % 4 == 0 and 16-byte aligned operands.
 enum { F32_PLANES_128 = 0, F32_PLANES_64 = 1, F32_TILES_128 = 2, F32_TILES_64 = 3, F32_PRODUCT = 4, F32_VECTOR = 5 };
 int        fp32_projection_form(int M, int N, int K, bool whole_rows, bool keep_order);

@@ -11,6 +11,7 @@
 #include "planes.h"
 #include "wave.h"
 #include "product.h"
+#include <algorithm>
 #include <atomic>
 
 namespace zgr {
@@ -735,7 +736,7 @@ __device__ __forceinline__ void epilogue_bf16(void* out, size_t o, float v) {
 // stay fp32 throughout: they are taken in pieces of kPieceTiles k-tiles, so that the large sum rounds once a piece and not with every instruction
 // (the adding up hides behind the other group's memory phase).
 template <int BM, int BN, int WM, int WN, int BK, int STAGES, int MODE, int PP, int FOLD>
-__device__ __forceinline__ void gemm_bf16_tile(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, int M, int N, int K,
+__device__ __forceinline__ void gemm_bf16_tile(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, int M, int N, int K, int lda, int ldw,
                                                void* out, const bf16_t* __restrict__ bias,      // resid may be out
                                                const int32_t* __restrict__ targets, float* __restrict__ tlogit, const float* resid, int tm, int tn) {
   constexpr int NW = WM * WN;
@@ -797,7 +798,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const bf16_t* __restrict__ A, con
     }
   };
   add_piece(true);
-  const int nk = K / BK, KW = K / FOLD, nkw = nk / FOLD;        // W's row stride and k-tiles
+  const int nk = K / BK, nkw = nk / FOLD;                       // k-tiles of A and of W
   auto w_ktile = [&](int kt) {
     if constexpr (FOLD == 1) return kt;
     else { const int r = kt < nkw ? kt : kt - nkw; return FOLD == 2 || r < nkw ? r : r - nkw; }
@@ -839,12 +840,12 @@ __device__ __forceinline__ void gemm_bf16_tile(const bf16_t* __restrict__ A, con
       int r = (is_a ? m0 : n0) + rl;
       const int lim = is_a ? M : N;
       r = r < lim ? r : lim - 1;
-      uo[u] = ((uint32_t)r * (uint32_t)(is_a ? K : KW) + (((lane & 7) ^ ((frow >> 1) & 7)) << 3)) * 2;   // bytes
+      uo[u] = ((uint32_t)r * (uint32_t)(is_a ? lda : ldw) + (((lane & 7) ^ ((frow >> 1) & 7)) << 3)) * 2;   // bytes
     }
 #if defined(__HIP_DEVICE_COMPILE__)
     // buffer addressing: per-lane byte offset in a register, the k-tile's offset in a scalar, bounds-checked
-    const __amdgpu_buffer_rsrc_t rsA = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(A), 0, (uint32_t)M * (uint32_t)K * 2u, 0x00020000);
-    const __amdgpu_buffer_rsrc_t rsW = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(W), 0, (uint32_t)N * (uint32_t)KW * 2u, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rsA = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(A), 0, ((uint32_t)(M - 1) * (uint32_t)lda + (uint32_t)K) * 2u, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rsW = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(W), 0, ((uint32_t)(N - 1) * (uint32_t)ldw + (uint32_t)(K / FOLD)) * 2u, 0x00020000);
 #endif
     // Transfers are issued unconditionally, so that every wave's count of outstanding transfers is the same in
     // every k-tile: a unit past the last k-tile re-reads the last one into a ring slot nobody reads any more.
@@ -952,13 +953,13 @@ __device__ __forceinline__ void gemm_bf16_tile(const bf16_t* __restrict__ A, con
   for (int g = 0; g < GA; ++g) {
     const int rl = (wave * GA + g) * RPI + lrow;               // row within the tile
     int r = m0 + rl; r = r < M ? r : M - 1;
-    ao[g] = (uint32_t)r * (uint32_t)K + ((lslot ^ ((rl / RPB) % CPR)) << 3);
+    ao[g] = (uint32_t)r * (uint32_t)lda + ((lslot ^ ((rl / RPB) % CPR)) << 3);
   }
 #pragma unroll
   for (int g = 0; g < GW; ++g) {
     const int rl = (wave * GW + g) * RPI + lrow;
     int c = n0 + rl; c = c < N ? c : N - 1;
-    wo[g] = (uint32_t)c * (uint32_t)KW + ((lslot ^ ((rl / RPB) % CPR)) << 3);
+    wo[g] = (uint32_t)c * (uint32_t)ldw + ((lslot ^ ((rl / RPB) % CPR)) << 3);
   }
   auto issue = [&](int kt, int buf) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -1119,10 +1120,10 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_bf16_kernel(const bf16_t* _
   A = ahead(A, model * tw.a); W = ahead(W, model * tw.w); out = ahead(out, model * tw.out); bias = ahead(bias, model * tw.bias);
   if (MODE == EPI_CE) tlogit = ahead(tlogit, model * tw.tlogit);
   if (MODE == EPI_RESID) resid = ahead(resid, model * tw.out);
-  gemm_bf16_tile<BM, BN, WM, WN, BK, STAGES, MODE, PP, 1>(A, W, M, N, K, out, bias, targets, tlogit, resid, tm, tn);
+  gemm_bf16_tile<BM, BN, WM, WN, BK, STAGES, MODE, PP, 1>(A, W, M, N, K, K, K, out, bias, targets, tlogit, resid, tm, tn);
 }
 
-// Several products with the same K and fp32 results in one launch: the tiles of all of them, one after the other, dealt out as those of one product are.
+// Several products with fp32 results in one launch: the tiles of all of them, one after the other, dealt out as those of one product are.
 // The four weight gradients of a block of 768 columns have 144, 144, 36 and 108 tiles of 128 x 128: one by one they left up to six sevenths of the
 // chip idle (2048 tokens: 67 us in four launches, now 36, 0.8 PFLOP/s).
 // FOLD = 3, a block of 1024 columns and 231 tokens: 32 us, 50 MB of results among them; product.hip's kernel, which cuts planes from fp32 operands as they lie, took
@@ -1138,7 +1139,7 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_bf16_group_kernel(ProductGr
   for (; place >= tiles(j); ++j) place -= tiles(j);
   const GroupedProduct p = g.job[j];
   tile_at(place, (p.M + BM - 1) / BM, (p.N + BN - 1) / BN, tm, tn);
-  gemm_bf16_tile<BM, BN, WM, WN, BK, STAGES, EPI_F32, PP, FOLD>(reinterpret_cast<const bf16_t*>(p.A), reinterpret_cast<const bf16_t*>(p.W), p.M, p.N, g.K, p.out, nullptr, nullptr, nullptr, nullptr, tm, tn);
+  gemm_bf16_tile<BM, BN, WM, WN, BK, STAGES, EPI_F32, PP, FOLD>(reinterpret_cast<const bf16_t*>(p.A), reinterpret_cast<const bf16_t*>(p.W), p.M, p.N, p.K, p.lda, p.ldw, p.out, nullptr, nullptr, nullptr, nullptr, tm, tn);
 }
 
 template <int BM, int BN, int WM, int WN, int BK, int STAGES, int PP, int FOLD>
@@ -1887,6 +1888,9 @@ int fp32_projection_form(int M, int N, int K, bool whole_rows, bool keep_order) 
   return !keep_order && product_is_faster(M, N, K) ? F32_PRODUCT : F32_TILES_64;
 }
 
+// 32 x 32 tiles that all get a CU of their own
+static bool few_tiles(int M, int N, int models) { return (int64_t)((M + 31) / 32) * ((N + 31) / 32) * models <= 256; }
+
 hipError_t launch_gemm(int dtype, const void* A, const void* W, const void* bias, void* out, int epi, int M, int N, int K, hipStream_t s, float* scratch, size_t scratch_floats, bool keep_order, Twin tw, bool shared_a, const float* resid) {
   const float* from = resid ? resid : (const float*)out;
   GemmEpi ep{epi, out, bias, from};
@@ -1930,8 +1934,7 @@ hipError_t launch_gemm(int dtype, const void* A, const void* W, const void* bias
     // In between (about one tile per CU): the ping-pong loop on the full ring.
     const long t128 = (long)((M + 127) / 128) * ((N + 127) / 128) * n;
     if (t128 > 256) return launch_gemm_bf16_t<128, 128, 2, 4, 64, 8, 1>(a, w, b, out, epi, M, N, K, s, n, gt, from);
-    const int64_t t32 = (int64_t)((M + 31) / 32) * ((N + 31) / 32) * n;   // 32 x 32 tiles that all get a CU of their own
-    if (t32 <= 256) return launch_gemm_bf16_few(a, w, b, out, epi, M, N, K, s, n, gt, from);
+    if (few_tiles(M, N, n)) return launch_gemm_bf16_few(a, w, b, out, epi, M, N, K, s, n, gt, from);
     if (t128 <= 128) return launch_gemm_bf16_t<64, 64, 2, 2, 64, 4>(a, w, b, out, epi, M, N, K, s, n, gt, from);
     return launch_gemm_bf16_t<128, 128, 2, 4, 64, 20, 1>(a, w, b, out, epi, M, N, K, s, n, gt, from);
   }
@@ -1940,12 +1943,30 @@ hipError_t launch_gemm(int dtype, const void* A, const void* W, const void* bias
 
 hipError_t launch_product_group(const ProductGroup& g, hipStream_t s) {
   if (g.count == 0) return hipSuccess;
-  if (g.count < 0 || g.count > kGroupedProducts || (g.fold != 1 && g.fold != 3) || g.K < 1 || g.K % (GB_K * g.fold)) return hipErrorInvalidValue;
+  if (g.count < 0 || g.count > kGroupedProducts || (g.fold != 1 && g.fold != 3)) return hipErrorInvalidValue;
   for (int j = 0; j < g.count; ++j) {
     const GroupedProduct& p = g.job[j];
-    if (p.M < 1 || p.N < 1 || (size_t)p.M * g.K >= ((size_t)1 << 31) || (size_t)p.N * g.K >= ((size_t)1 << 31)) return hipErrorInvalidValue;      // 32-bit byte offsets
+    if (p.M < 1 || p.N < 1 || p.K < 1 || p.K % (GB_K * g.fold) || p.lda < p.K || p.ldw < p.K / g.fold) return hipErrorInvalidValue;
+    if ((size_t)p.M * p.lda >= ((size_t)1 << 31) || (size_t)p.N * p.ldw >= ((size_t)1 << 31)) return hipErrorInvalidValue;      // 32-bit byte offsets
   }
   return g.fold == 1 ? launch_group_f<1>(g, s) : launch_group_f<3>(g, s);
+}
+
+// Some 24 k-tiles a slice and up to two blocks a CU, where the undivided product would leave half of the CUs without a tile of 128 x 128 (and takes tiles of 64 x 64): the
+// gradients of the inputs of FC1 and of Q, K, V at 2048 tokens and 768 columns (sums of 3072 and 2304) 21.5 us on average, in two slices 16.3, and of the head
+// (50304) 290, in five 185; the LayerNorm rules behind them 9.8 us with one part, 11.7 with two on average.
+int product_slices(int M, int N, int K, int most) {
+  const int64_t t128 = (int64_t)((M + 127) / 128) * ((N + 127) / 128);
+  if (t128 > 128 || few_tiles(M, N, 1)) return 1;
+  return (int)std::max<int64_t>(1, std::min<int64_t>({512 / t128, (K / GB_K + 12) / 24, most, kGroupedProducts}));
+}
+hipError_t launch_product_slices(const void* A, const void* W, float* out, int M, int N, int K, int slices, hipStream_t s) {
+  const int per = (K / GB_K + slices - 1) / slices * GB_K;
+  ProductGroup g;
+  if (slices < 1 || slices > kGroupedProducts || K % GB_K || (int64_t)per * (slices - 1) >= K) return hipErrorInvalidValue;
+  for (int i = 0; i < slices; ++i)
+    g.job[g.count++] = GroupedProduct{(const bf16_t*)A + (size_t)i * per, (const bf16_t*)W + (size_t)i * per, out + (size_t)i * M * N, M, N, std::min(per, K - i * per), K, K};
+  return launch_product_group(g, s);
 }
 
 // Vocabulary projection fused with the row-wise cross-entropy (bf16 storage): logits are never stored.

@@ -384,10 +384,11 @@ def test_argument_errors_are_reported_not_executed():
     ("bf16", 128, 2, 2048, 1, 33),     # four parts, all requested at once
     ("bf16", 576, 9, 4608, 1, 70),     # nine of FC1's, three of Q, K, V's
     ("bf16", 1088, 17, 2048, 1, 31),   # wide rows, where they are requested one by one; the weight gradients' third tile size
+    ("bf16", 512, 8, 4096, 9, 64),     # whole k-tiles of tokens: slices of the products on bf16 operands, three of FC1's and four of the head's
 ])
 def test_layernorm_adds_the_parts_of_a_split_product(dtype, d, n_head, ff, batch, seq):
     """Long sums over few rows: the products in front of the LayerNorm rules leave parts.  Bounds as above."""
-    cfg = I.shrink(I.CONFIGS["cfg3"], name="bw_parts", dtype=dtype, n_layer=2, d_model=d, n_head=n_head, d_ff=ff, vocab=203, max_pos=80, batch=batch, seq=seq, k=8, k_full=8)
+    cfg = I.shrink(I.CONFIGS["cfg3"], name="bw_parts", dtype=dtype, n_layer=2, d_model=d, n_head=n_head, d_ff=ff, vocab=6001 if batch * seq % 64 == 0 else 203, max_pos=80, batch=batch, seq=seq, k=8, k_full=8)
     sess, specs, P = _setup(cfg, scale=2.0)
     arrays = _batch(cfg, 3)
     loss, grads = _device(sess, cfg, arrays)
