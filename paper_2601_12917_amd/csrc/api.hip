@@ -495,6 +495,17 @@ PerturbArgs with_stage(const zgr_ctx* c, PerturbArgs a, size_t gi) {
 zgr_status run_pass(zgr_ctx* c, PerturbArgs a, float coef) {
   const WorkItem* tiles = a.tiles;
   bool staged0 = c->groups.empty();
+  if (staged0)
+    for (int k_class = 0; k_class < 2; ++k_class) {
+      const zgr_ctx::TileRange& r = c->res[k_class];
+      if (r.end == r.begin || c->res[1 - k_class].end != c->res[1 - k_class].begin) continue;
+      PerturbArgs at = a;                              // the only tiles there are
+      at.n_stage = 0; at.tiles = tiles + r.begin; at.n_tiles = (int32_t)(r.end - r.begin); at.max_k = r.max_k; at.min_k = r.min_k;
+      if (!perturb_small(at, c->n_cu)) break;
+      ProfScope ps(c, ZGR_K_PERTURB_TILE);
+      HIP_TRY(c, launch_perturb_small(at, coef, c->stream, c->n_cu));
+      return ZGR_OK;
+    }
   if (a.n_flat > 0) {
     PerturbArgs af = staged0 ? a : with_stage(c, a, 0);
     af.n_tiles = 0;

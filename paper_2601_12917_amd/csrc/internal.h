@@ -80,6 +80,9 @@ struct PerturbArgs {
 // instead write Z of the single tensor in the list as fp32 [rows, cols].
 hipError_t launch_perturb_flat(const PerturbArgs& a, float c, float* zout, hipStream_t s, int n_cu);
 hipError_t launch_perturb_tile(const PerturbArgs& a, float c, float* zout, hipStream_t s, int n_cu);
+// Both lists in one launch, where they are that short.
+bool       perturb_small(const PerturbArgs& a, int n_cu);
+hipError_t launch_perturb_small(const PerturbArgs& a, float c, hipStream_t s, int n_cu);
 
 // The radius table of the current device: filled once per process and device (thread-safe), by a copy on stream s
 // that has completed when the call returns.

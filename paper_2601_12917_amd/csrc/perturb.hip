@@ -248,15 +248,10 @@ template <typename V> __device__ __forceinline__ void wait_here_for(const V& v) 
 // block are requested before the generator runs for the current one, so kFlatSlots vectors per lane are in
 // flight under a whole item's arithmetic: the pass needs about 20 KB of reads in flight per compute unit to
 // keep HBM busy, and one 8-byte request per lane at a time, waited for after one call, supplies less than that.
+// The share of block `block` of `nblk`, 256 threads, the table in LDS.
 template <typename T, int P, int MODE>
-__global__ void __launch_bounds__(256) perturb_flat_kernel(PerturbArgs a, const TensorDesc* __restrict__ descs, const WorkItem* __restrict__ items,
-                                                           float c, const RadiusEntry* __restrict__ gtab) {
-  __shared__ RadiusEntry tab[kRadiusTabEntries];
+__device__ __forceinline__ void flat_share(const PerturbArgs& a, const TensorDesc* __restrict__ descs, const WorkItem* __restrict__ items, float c, const RadiusEntry* tab, int block, int nblk) {
   constexpr int kFlatSlots = flat_slots((int)sizeof(T), P);
-  const int nblk = (int)gridDim.x - a.pull_blocks;               // computing blocks
-  if ((int)blockIdx.x >= nblk) { pull_next_stage(a, (int)blockIdx.x - nblk, a.pull_blocks); return; }
-  load_radius_table(tab, gtab);
-  __syncthreads();
   const int tid = threadIdx.x;
   // Requests the vectors of item w (the last item again once the list is exhausted).  A slot past the end of the
   // item or of the tensor re-reads the tensor's last whole vector, and a tensor shorter than one vector reads the
@@ -276,10 +271,10 @@ __global__ void __launch_bounds__(256) perturb_flat_kernel(PerturbArgs a, const 
     }
   };
   Vec<T, P> cur[kFlatSlots], nxt[kFlatSlots];
-  request(blockIdx.x, cur);
+  request(block, cur);
 #pragma unroll
   for (int j = 0; j < kFlatSlots; ++j) wait_here_for(cur[j]);      // nothing outstanding on entry to the loop
-  for (int w = blockIdx.x; w < a.n_flat; w += nblk) {
+  for (int w = block; w < a.n_flat; w += nblk) {
     request(w + nblk, nxt);
     const WorkItem it = load_const(items + w);
     const TensorDesc d = load_const(descs + it.tensor);
@@ -323,6 +318,16 @@ __global__ void __launch_bounds__(256) perturb_flat_kernel(PerturbArgs a, const 
     for (int j = 0; j < kFlatSlots; ++j) cur[j] = nxt[j];
   }
 }
+template <typename T, int P, int MODE>
+__global__ void __launch_bounds__(256) perturb_flat_kernel(PerturbArgs a, const TensorDesc* __restrict__ descs, const WorkItem* __restrict__ items,
+                                                           float c, const RadiusEntry* __restrict__ gtab) {
+  __shared__ RadiusEntry tab[kRadiusTabEntries];
+  const int nblk = (int)gridDim.x - a.pull_blocks;               // computing blocks
+  if ((int)blockIdx.x >= nblk) { pull_next_stage(a, (int)blockIdx.x - nblk, a.pull_blocks); return; }
+  load_radius_table(tab, gtab);
+  __syncthreads();
+  flat_share<T, P, MODE>(a, descs, items, c, tab, (int)blockIdx.x, nblk);
+}
 
 // ------------------------------------------------------------------ tile
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -348,29 +353,26 @@ __device__ __forceinline__ void finish_row(const TensorDesc& d, const Places<T>&
 // Lane layout: column group cg = lane % 32 owns P consecutive columns, each half of a wave RPL consecutive rows (a lane makes one
 // Philox call per row).  RPL = 16 is for passes that fill the chip; RPL = 1 spreads a small model's matrices over sixteen times the
 // blocks (least-squares layer of 256 x 512: 17 us with 8 blocks of 128 rows, 5.3 with 128 blocks of 8).
+// The share of block `block` of `nblk`; the table, at smem, is on its way into LDS.
 template <typename T, int P, bool WRITE_Z, int MODE, int RPL>
-__global__ void __launch_bounds__(256) perturb_tile_kernel(PerturbArgs a, const TensorDesc* __restrict__ descs, const WorkItem* __restrict__ items,
-                                                           float c, const RadiusEntry* __restrict__ gtab, float* __restrict__ zout, int kp) {
-  extern __shared__ float smem[];
-  RadiusEntry* tab = reinterpret_cast<RadiusEntry*>(smem);
+__device__ __forceinline__ void tile_share(const PerturbArgs& a, const TensorDesc* __restrict__ descs, const WorkItem* __restrict__ items, float c, float* smem, float* __restrict__ zout, int kp,
+                                           int block, int nblk) {
+  const RadiusEntry* tab = reinterpret_cast<const RadiusEntry*>(smem);
   constexpr int TR = 8 * RPL;                        // rows a block covers at a time
   float* Us = smem + kRadiusTabEntries * 3;          // [TR][kp]
   float* Rs = Us + TR * kp;                          // [kp][TC]
   constexpr int TC = 32 * P;
   constexpr int RB = RPL < 8 ? RPL : (P == 4 ? 16 : 8);   // rows a lane holds at once
-  const int nblk = (int)gridDim.x - a.pull_blocks;               // computing blocks
-  if ((int)blockIdx.x >= nblk) { pull_next_stage(a, (int)blockIdx.x - nblk, a.pull_blocks); return; }
-  load_radius_table(tab, gtab);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int cg = lane & 31, rh = lane >> 5;
 
   // A block takes a contiguous run of the list; the list orders the row tiles of one column strip one after the
   // other, so the slice of R in LDS is regenerated only when the strip (or the tensor) changes.
   const int per_block = (a.n_tiles + nblk - 1) / nblk;
-  const int w_end = min(a.n_tiles, ((int)blockIdx.x + 1) * per_block);
+  const int w_end = min(a.n_tiles, (block + 1) * per_block);
   int prev_tensor = -1;
   int64_t prev_col0 = -1;
-  for (int w = (int)blockIdx.x * per_block; w < w_end; ++w) {
+  for (int w = block * per_block; w < w_end; ++w) {
     const WorkItem it = items[w];
     const TensorDesc d = descs[it.tensor];
     const int64_t row0 = it.first >> 32, col0 = it.first & 0xFFFFFFFFll;
@@ -442,6 +444,15 @@ __global__ void __launch_bounds__(256) perturb_tile_kernel(PerturbArgs a, const 
       }
     }
   }
+}
+template <typename T, int P, bool WRITE_Z, int MODE, int RPL>
+__global__ void __launch_bounds__(256) perturb_tile_kernel(PerturbArgs a, const TensorDesc* __restrict__ descs, const WorkItem* __restrict__ items,
+                                                           float c, const RadiusEntry* __restrict__ gtab, float* __restrict__ zout, int kp) {
+  extern __shared__ float smem[];
+  const int nblk = (int)gridDim.x - a.pull_blocks;               // computing blocks
+  if ((int)blockIdx.x >= nblk) { pull_next_stage(a, (int)blockIdx.x - nblk, a.pull_blocks); return; }
+  load_radius_table(reinterpret_cast<RadiusEntry*>(smem), gtab);
+  tile_share<T, P, WRITE_Z, MODE, RPL>(a, descs, items, c, smem, zout, kp, (int)blockIdx.x, nblk);
 }
 
 // ------------------------------------------------------------------ tile, U R on the matrix cores (k >= 16)
@@ -595,20 +606,17 @@ __device__ __forceinline__ void contract(const Tile& tl, const RawEight& first, 
 // and store issued before it, and some 10 KB in flight per compute unit are half of what HBM needs at this rate.
 template <typename T, int P> constexpr int vectors_ahead() { return 64 / (int)(sizeof(T) * P); }      // 16 registers
 
+// The share of block `block` of `nblk`; the table, at smem, is on its way into LDS.
 template <typename T, int P, bool WRITE_Z, int MODE>
-__global__ void __launch_bounds__(64 * kTileWaves) __attribute__((amdgpu_waves_per_eu(4, 8))) perturb_tile_mfma_kernel(PerturbArgs a, const TensorDesc* __restrict__ descs, const WorkItem* __restrict__ items,
-                                                                float c, const RadiusEntry* __restrict__ gtab, float* __restrict__ zout, int kp) {
-  extern __shared__ float smem[];
-  RadiusEntry* tab = reinterpret_cast<RadiusEntry*>(smem);
+__device__ __forceinline__ void tile_mfma_share(const PerturbArgs& a, const TensorDesc* __restrict__ descs, const WorkItem* __restrict__ items, float c, float* smem, float* __restrict__ zout,
+                                                int block, int nblk) {
+  const RadiusEntry* tab = reinterpret_cast<const RadiusEntry*>(smem);
   planes_u32x4* Rs = reinterpret_cast<planes_u32x4*>(smem + kRadiusTabEntries * 3);      // [3][kp / 8][TC]
   constexpr int TC = 32 * P, GC = 16 * P;            // tile columns, columns per group
   constexpr int kAhead = vectors_ahead<T, P>(), kRounds = 8 / kAhead, kGroups = 8 / P;      // kGroups: column groups contracted at a time
   // the row and the column group of a lane's vector number i
   auto row_of = [](int i) { return kGroups == 2 ? i >> 1 : i & 3; };
   auto group_of = [](int i) { return kGroups == 2 ? i & 1 : i >> 2; };
-  const int nblk = (int)gridDim.x - a.pull_blocks;               // computing blocks
-  if ((int)blockIdx.x >= nblk) { pull_next_stage(a, (int)blockIdx.x - nblk, a.pull_blocks); return; }
-  load_radius_table<64 * kTileWaves>(tab, gtab);
 #if defined(__HIP_DEVICE_COMPILE__)
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
 #else
@@ -632,7 +640,7 @@ __global__ void __launch_bounds__(64 * kTileWaves) __attribute__((amdgpu_waves_p
   auto advance = [&]() {                             // the block's next tile; false behind the last one
     if (w + 1 < w_end) { ++w; return true; }
     while (++pass < n_pass) {
-      const int run = by_xcd ? (((int)blockIdx.x & 7) * n_pass + pass) * per_xcd + ((int)blockIdx.x >> 3) : (int)blockIdx.x;
+      const int run = by_xcd ? ((block & 7) * n_pass + pass) * per_xcd + (block >> 3) : block;
       w = (int)((int64_t)run * a.n_tiles / n_runs);
       w_end = (int)(((int64_t)run + 1) * a.n_tiles / n_runs);
       if (w < w_end) return true;
@@ -772,6 +780,43 @@ __global__ void __launch_bounds__(64 * kTileWaves) __attribute__((amdgpu_waves_p
 #pragma unroll
       for (int i = 0; i < kAhead; ++i) cur[i] = nxt[i];
     }
+  }
+}
+template <typename T, int P, bool WRITE_Z, int MODE>
+__global__ void __launch_bounds__(64 * kTileWaves) __attribute__((amdgpu_waves_per_eu(4, 8))) perturb_tile_mfma_kernel(PerturbArgs a, const TensorDesc* __restrict__ descs, const WorkItem* __restrict__ items,
+                                                                float c, const RadiusEntry* __restrict__ gtab, float* __restrict__ zout) {
+  extern __shared__ float smem[];
+  const int nblk = (int)gridDim.x - a.pull_blocks;               // computing blocks
+  if ((int)blockIdx.x >= nblk) { pull_next_stage(a, (int)blockIdx.x - nblk, a.pull_blocks); return; }
+  load_radius_table<64 * kTileWaves>(reinterpret_cast<RadiusEntry*>(smem), gtab);
+  tile_mfma_share<T, P, WRITE_Z, MODE>(a, descs, items, c, smem, zout, (int)blockIdx.x, nblk);
+}
+
+// ------------------------------------------------------------------ a small model's two lists in one launch
+// A block per entry, those of the flat list first (four waves of a block work on them): with so few the launches are latency.  One pass over a model of two blocks
+// of 128 columns 10.3 us (fp32, rank 8) and 14.5 (bf16, rank 16) in two launches, 5.5 and 9.1 in one; four blocks of 256 columns, rank 16 19.9 and 13.3.
+template <typename T, int P, int MODE>
+__global__ void __launch_bounds__(256) perturb_small_kernel(PerturbArgs a, const TensorDesc* __restrict__ descs, const WorkItem* __restrict__ flat, const WorkItem* __restrict__ tiles,
+                                                            float c, const RadiusEntry* __restrict__ gtab, int kp) {
+  extern __shared__ float smem[];
+  load_radius_table(reinterpret_cast<RadiusEntry*>(smem), gtab);
+  if ((int)blockIdx.x < a.n_flat) {
+    __syncthreads();
+    flat_share<T, P, MODE>(a, descs, flat, c, reinterpret_cast<const RadiusEntry*>(smem), (int)blockIdx.x, a.n_flat);
+  } else {
+    tile_share<T, P, false, MODE, kSmallTileRows / 8>(a, descs, tiles, c, smem, nullptr, kp, (int)blockIdx.x - a.n_flat, a.n_tiles);
+  }
+}
+template <typename T, int P, int MODE>
+__global__ void __launch_bounds__(64 * kTileWaves) __attribute__((amdgpu_waves_per_eu(4, 8))) perturb_small_mfma_kernel(PerturbArgs a, const TensorDesc* __restrict__ descs, const WorkItem* __restrict__ flat,
+                                                                                                                        const WorkItem* __restrict__ tiles, float c, const RadiusEntry* __restrict__ gtab) {
+  extern __shared__ float smem[];
+  load_radius_table<64 * kTileWaves>(reinterpret_cast<RadiusEntry*>(smem), gtab);
+  if ((int)blockIdx.x < a.n_flat) {
+    __syncthreads();
+    if (threadIdx.x < 256) flat_share<T, P, MODE>(a, descs, flat, c, reinterpret_cast<const RadiusEntry*>(smem), (int)blockIdx.x, a.n_flat);
+  } else {
+    tile_mfma_share<T, P, false, MODE>(a, descs, tiles, c, smem, nullptr, (int)blockIdx.x - a.n_flat, a.n_tiles);
   }
 }
 
@@ -994,7 +1039,7 @@ hipError_t launch_tile_t(const PerturbArgs& a_in, float c, float* zout, hipStrea
     hipError_t e = tile_launch_setup(km, lds_m, 64 * kTileWaves, 4, cache_m[variant], &per_cu);
     if (e != hipSuccess) return e;
     const int grid_m = split_grid(a, a.n_tiles, n_cu * per_cu);
-    hipLaunchKernelGGL(km, dim3(grid_m), dim3(64 * kTileWaves), lds_m, s, a, a.descs, a.tiles, c, tab, zout, kp);
+    hipLaunchKernelGGL(km, dim3(grid_m), dim3(64 * kTileWaves), lds_m, s, a, a.descs, a.tiles, c, tab, zout);
     return hipGetLastError();
   }
   const bool small = a.tile_rows < kTileRowsPerIter;
@@ -1020,7 +1065,43 @@ hipError_t launch_tile_t(const PerturbArgs& a_in, float c, float* zout, hipStrea
   hipLaunchKernelGGL(kern, dim3(grid), dim3(256), lds, s, a, a.descs, a.tiles, c, tab, zout, kp);
   return hipGetLastError();
 }
+
+template <typename T, int P>
+hipError_t launch_small_t(const PerturbArgs& a, float c, hipStream_t s, const RadiusEntry* tab) {
+  const int kp = (a.max_k + 7) & ~7, mode = mode_of(a);
+  static TileLaunchCache cache[6];
+  int per_cu = 1;
+  const dim3 grid((unsigned)(a.n_flat + a.n_tiles));
+  if (a.min_k >= kMfmaMinK) {
+    const size_t lds = sizeof(RadiusEntry) * (size_t)kRadiusTabEntries + 6 * (size_t)kp * 32 * P;
+    auto kern = mode == kBatch ? perturb_small_mfma_kernel<T, P, kBatch> : (mode == kSpread ? perturb_small_mfma_kernel<T, P, kSpread> : perturb_small_mfma_kernel<T, P, kOne>);
+    const hipError_t e = tile_launch_setup(kern, lds, 64 * kTileWaves, 4, cache[mode], &per_cu);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, grid, dim3(64 * kTileWaves), lds, s, a, a.descs, a.flat, a.tiles, c, tab);
+    return hipGetLastError();
+  }
+  const size_t lds = sizeof(float) * ((size_t)kRadiusTabEntries * 3 + (size_t)kSmallTileRows * kp + (size_t)kp * 32 * P);
+  auto kern = mode == kBatch ? perturb_small_kernel<T, P, kBatch> : (mode == kSpread ? perturb_small_kernel<T, P, kSpread> : perturb_small_kernel<T, P, kOne>);
+  const hipError_t e = tile_launch_setup(kern, lds, 256, 4, cache[3 + mode], &per_cu);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, grid, dim3(256), lds, s, a, a.descs, a.flat, a.tiles, c, tab, kp);
+  return hipGetLastError();
+}
 }  // namespace
+
+// A block per entry of either list, all of them resident at once (two a CU): what a launch of its own costs a list is then all there is to save, and a block has no
+// second entry to work ahead for.  Gaussians four to a call; ranks on one side of kMfmaMinK, below it tiles of eight rows.
+bool perturb_small(const PerturbArgs& a, int n_cu) {
+  return a.bits == 32 && a.n_flat > 0 && a.n_tiles > 0 && a.n_stage == 0 && a.n_flat + a.n_tiles <= 2 * n_cu && (a.min_k >= kMfmaMinK || (a.max_k < kMfmaMinK && a.tile_rows < kTileRowsPerIter));
+}
+hipError_t launch_perturb_small(const PerturbArgs& a, float c, hipStream_t s, int n_cu) {
+  if (!perturb_small(a, n_cu) || a.max_k < 1 || a.max_k > kMaxK || a.pull_blocks != 0) return hipErrorInvalidValue;
+  if (a.n_q < 0 || a.n_q > kMaxBatch || (a.spread && (a.n_q > 0 || a.from_copy)) || ((a.spread || a.from_copy) && !(a.copy[0] && a.copy[1])) || (a.from_copy && a.n_q > 0)) return hipErrorInvalidValue;
+  const RadiusEntry* tab = nullptr;
+  const hipError_t e = ensure_radius_table(&tab, s);
+  if (e != hipSuccess) return e;
+  return a.dtype == 0 ? launch_small_t<float, 4>(a, c, s, tab) : launch_small_t<bf16_t, 4>(a, c, s, tab);
+}
 
 hipError_t launch_perturb_flat(const PerturbArgs& a, float c, float* zout, hipStream_t s, int n_cu) {
   if (a.n_flat <= 0) return hipSuccess;
