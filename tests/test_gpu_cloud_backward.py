@@ -405,3 +405,19 @@ def test_layernorm_adds_the_parts_of_a_split_product(dtype, d, n_head, ff, batch
             ratio = float(np.linalg.norm(grads[i]) / np.linalg.norm(want))
             assert cos >= 0.995 and abs(ratio - 1.0) <= 0.05, (s.name, cos, ratio)
     sess.close()
+
+
+@pytest.mark.parametrize("vocab,d,seq,batch", [(4, 8, 530, 3), (1500, 520, 257, 4), (3, 16, 15, 1)])
+def test_embedding_rows_of_frequent_and_of_rare_tokens(vocab, d, seq, batch):
+    """Rows of a token are listed 1024 tokens at a time and requested sixteen at a time: lists over two pieces, lists of one row, and fewer rows
+    than one request; 520 columns take a second block.  Bounds as above."""
+    cfg = I.shrink(I.CONFIGS["cfg2"], **dict(TINY_LM, name="bw_embed", n_layer=1, d_model=d, n_head=d // 8, d_ff=16, vocab=vocab, max_pos=540, batch=batch, seq=seq))
+    sess, specs, P = _setup(cfg)
+    arrays = _batch(cfg, 3)
+    _, grads = _device(sess, cfg, arrays)
+    _, grads_or = _oracle(cfg, P, arrays)
+    floor = 1e-6 * max(np.abs(g).max() for g in grads_or.values())
+    for i, s in enumerate(specs):
+        want = grads_or[s.name]
+        assert np.abs(grads[i] - want).max() <= 2e-4 * np.abs(want).max() + floor, s.name
+    sess.close()
