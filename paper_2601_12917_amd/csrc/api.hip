@@ -1131,7 +1131,7 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
   const int32_t* tok = reinterpret_cast<const int32_t*>(b->x);
   const int32_t* lengths = lm ? nullptr : b->lengths;
   const size_t xbytes = (size_t)M * d * 4;
-  // The products of the backward half.  fp32 models and ragged token counts: fp32 products on the operands as they lie.  bf16 models
+  // The products of the backward half.  fp32 models and ragged token counts (but for their weights' gradients, on_planes): fp32 products on the operands as they lie.  bf16 models
   // (token count a multiple of 64): the forward pass's matrix-core GEMM, which contracts along the rows of both
   // operands, on bf16 copies written out with the contraction index innermost.
   auto product = [&](const void* A, bool a_k, int64_t lda, const void* B, int64_t ldb, float* C, int64_t ldc, int Mp, int Np, int Kp, float* a_sums, int row_blocks = 1, int* parts_left = nullptr) {

@@ -138,8 +138,9 @@ __global__ void __launch_bounds__(256) stage_only_kernel(PerturbArgs a) { pull_n
 //   kBatch:  the same with a sum of perturbations in place of Z
 //   kSpread: what three passes with c, -2c and c leave behind, from one generation of Z and one read of theta: copy 0 <- rnd(theta + c Z),
 //            copy 1 <- rnd(copy 0 - 2c Z), theta <- rnd(copy 1 + c Z) (theta stays as it is when a.restore is 0)
-// The generator is what bounds kOne (466 cycles a call against 420 for the bytes); kSpread calls it once for four times a value's bytes and is
-// bound by those.  Steps of 1.3B bf16 parameters 29.0 -> 26.1 ms, of 350M 10.0 -> 9.1, of 125M 3.30 -> 3.21.
+// Vector instructions are what bounds kOne (the generator alone 425 cycles a call against 420 for the bytes, some 200 more for the rest); kSpread
+// calls the generator once for four times a value's bytes and is bound by those.  Against three passes, when it was written: steps of 1.3B bf16
+// parameters 29.0 -> 26.1 ms, of 350M 10.0 -> 9.1, of 125M 3.30 -> 3.21.
 enum { kOne = 0, kBatch = 1, kSpread = 2 };
 
 // The P Gaussians of Philox call q of one stream.  kBatch: instead the combination sum_i qcoef[i] * (those of step
