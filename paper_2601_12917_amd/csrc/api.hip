@@ -141,10 +141,10 @@ size_t flat_items_of(int64_t numel, int P, int dtype) {
 }
 // Row tiles of 128 rows: fine enough that a launch over one layer's matrices (a stage of the layer pipeline) still
 // gives every block several tiles, and a block keeps its slice of R across the consecutive row tiles of a strip.
-// A model with few of them altogether (kFewTiles: a quarter of the CUs with a block each) takes tiles of 8 rows, or of the 64 rows
-// the matrix-core kernel covers at a time: more blocks make up for the slices of R that several of them draw (64 tiles, 1024 x 1024, fp32:
-// rank 1 16 us -> 7, rank 15 21 -> 10, rank 16 14 -> 8, rank 64 21 -> 13).  Between 64 tiles and the few hundred that fill the chip no
-// height was measured.
+// A model with few of them altogether (kFewTiles: a quarter of the CUs with a block each) takes tiles of 8 rows or, from rank 16 on, of 64: more blocks make up
+// for the slices of R that several of them draw (64 tiles, 1024 x 1024, fp32: rank 1 16 us -> 7, rank 15 21 -> 10).  The matrix-core kernel's blocks have
+// waves for 128 rows; with 64 every SIMD has one of the four that work and the other four pass by (rank 16, 1024 x 1024, fp32: tiles of 16 rows 10.7 us, 32 9.4,
+// 64 9.0, 128 10.5; rank 64 16.4, 12.7, 12.3 and 14.2).  Between 64 tiles and the few hundred that fill the chip no height was measured.
 constexpr size_t kFewTiles = 64;
 int tile_rows_of(bool few, int k) { return !few ? kTileRowsPerIter : (k >= kMfmaMinK ? 64 : kSmallTileRows); }
 size_t tile_items_of(int64_t rows, int64_t cols, int P, int64_t tr = kTileRowsPerIter) {

@@ -35,7 +35,7 @@ struct WorkItem {
 // keeps in flight while it works on the previous item): 8 for bf16 with 4 elements per call, down to 2 for fp32 with 8.
 constexpr int flat_slots(int elem_bytes, int P) { return 64 / (elem_bytes * P) < 1 ? 1 : 64 / (elem_bytes * P); }
 constexpr int flat_groups_per_item(int elem_bytes, int P) { return 256 * flat_slots(elem_bytes, P); }
-constexpr int kTileRowsPerIter   = 128;    // rows one block covers per iteration (4 waves x 32)
+constexpr int kTileRowsPerIter   = 128;    // rows one block covers per iteration (vector kernel: 4 waves x 32, matrix-core kernel: 8 x 16)
 constexpr int kSmallTileRows     = 8;      // and where the whole model has few tiles (vector kernel)
 constexpr int kMaxK              = 64;
 constexpr int kMfmaMinK          = 16;     // from this rank on the U R contraction of a tile runs on the matrix cores

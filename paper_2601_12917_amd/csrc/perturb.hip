@@ -642,23 +642,29 @@ __device__ __forceinline__ void tile_mfma_share(const PerturbArgs& a, const Tens
     if (w + 1 < w_end) { ++w; return true; }
     while (++pass < n_pass) {
       const int run = by_xcd ? ((block & 7) * n_pass + pass) * per_xcd + (block >> 3) : block;
+      if (n_runs == a.n_tiles) { w = run; w_end = run + 1; return true; }
       w = (int)((int64_t)run * a.n_tiles / n_runs);
       w_end = (int)(((int64_t)run + 1) * a.n_tiles / n_runs);
       if (w < w_end) return true;
     }
     return false;
   };
-  auto u_row = [&](const Tile& t) { const int64_t r = t.row0 + 16 * wave + n16; return r < t.d.rows ? r : t.d.rows - 1; };
+  // A wave without rows of a tile (a matrix's last tile, the tiles of a model of few) contracts nothing, and no lane reads theta that another wave may be
+  // storing: a row or column past the tile is read as the wave's own last one, that of a wave without any, or behind the last tile, as the descriptor
+  // table (in bounds, never used; a conditional request takes registers for old and new values behind it, which then spill).
+  auto has_rows = [&](const Tile& t) { return 16 * wave < t.nrows; };
+  auto u_row = [&](const Tile& t) { const int r = 16 * wave + n16; return t.row0 + (r < t.nrows ? r : t.nrows - 1); };
   auto request_u = [&](const Tile& t, RawEight& o) {
     if (!t.eights) return;
     const int c8 = t.n8 > 2 ? rg : rg & 1;
     request_eight(t.d, u_row(t), c8 < t.n8 ? c8 : t.n8 - 1, o);
   };
-  auto request = [&](const Tile& t, int round, Vec<T, P>* buf) {
+  auto request = [&](const Tile& t, int round, Vec<T, P>* buf, bool more) {
     if (WRITE_Z) return;
-    const T* src = places_of<T, MODE>(t.d, a).src + (t.row0 * t.d.cols + t.col0);
-    const int64_t rows_left = t.d.rows - t.row0, cols_left = t.d.cols - t.col0;
-    const uint32_t last_row = rows_left < kTileRowsPerIter ? (uint32_t)rows_left - 1 : kTileRowsPerIter - 1, last_col = cols_left < TC ? (uint32_t)cols_left - P : TC - P;
+    const bool own = more && has_rows(t);
+    const T* src = own ? places_of<T, MODE>(t.d, a).src + (t.row0 * t.d.cols + t.col0) : reinterpret_cast<const T*>(descs);
+    const int64_t cols_left = t.d.cols - t.col0;
+    const uint32_t last_row = own ? (uint32_t)t.nrows - 1 : 0, last_col = !own ? 0 : cols_left < TC ? (uint32_t)cols_left - P : TC - P;
 #pragma unroll
     for (int i = 0; i < kAhead; ++i) {
       const int v = row_of(round * kAhead + i), g = group_of(round * kAhead + i);
@@ -671,7 +677,7 @@ __device__ __forceinline__ void tile_mfma_share(const PerturbArgs& a, const Tens
   Tile t = tile_of(descs, items, w);
   Vec<T, P> cur[kAhead], nxt[kAhead];
   RawEight u8{};
-  request(t, 0, cur);
+  request(t, 0, cur, true);
   request_u(t, u8);
   int prev_tensor = -1;
   int64_t prev_col0 = -1;
@@ -728,13 +734,13 @@ __device__ __forceinline__ void tile_mfma_share(const PerturbArgs& a, const Tens
 #pragma unroll
     for (int round = 0; round < kRounds; ++round) {
       const bool last = round + 1 == kRounds;
-      if (round * kAhead % (4 * kGroups) == 0) contract<P>(t, u8, Rs + group_of(round * kAhead) * GC, u_row(t), n16, rg, acc);
+      if (round * kAhead % (4 * kGroups) == 0 && any) contract<P>(t, u8, Rs + group_of(round * kAhead) * GC, u_row(t), n16, rg, acc);
       if (last) {
         more = advance();
         if (more) t = tile_of(descs, items, w);
         request_u(t, u8);                            // behind the last tile it is requested again
       }
-      request(t, last ? 0 : round + 1, nxt);
+      request(t, last ? 0 : round + 1, nxt, !last || more);
       in_this_order();
       auto arrived = [&]() {                         // all that was requested, in front of the round's last store
         if (WRITE_Z) return;

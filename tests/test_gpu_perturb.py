@@ -235,3 +235,37 @@ def test_basis_entries_beyond_bf16(k):
     rest = np.setdiff1d(np.arange(rows), [70, 130])
     assert np.all(np.abs(got[rest] - Z[rest]) <= bound[rest])
     sess.close()
+
+
+@pytest.mark.parametrize("rows,cols,k,dtype,bits", [
+    (16, 128, 16, "f32", 32),       # a tile with rows for one wave of eight
+    (33, 132, 16, "bf16", 32),      # for three, the last with one row; a strip of 4 columns
+    (80, 128, 24, "f32", 32),       # tiles of 64 and of 16 rows, or one of 80
+    (193, 256, 40, "bf16", 32),     # four tiles of 64, the last of one row; of 128 and of 65
+    (200, 264, 16, "f32", 16),
+    (129, 256, 64, "bf16", 16),
+])
+def test_bits_do_not_depend_on_the_height_of_the_tiles(rows, cols, k, dtype, bits):
+    """The same tensor alone (tiles of 64 rows), with a vector beside it (both in one launch) and in a context of many tiles (128 rows): single passes and sums of
+    several perturbations leave the same bits, and every entry is moved once."""
+    cfg = _single_tensor_cfg(rows, cols, k, dtype)
+    rng = np.random.default_rng(rows + cols)
+
+    def values(r, c):
+        w = (rng.standard_normal((r, c)) * PARAM_SCALE).astype(np.float32)
+        return P.bf16_round(w) if dtype == "bf16" else w
+    W, U = values(rows, cols), _basis(rows, k)
+    vector = (I.TensorSpec("b", I.ROLE_BQ, -1, 1, 333, 5, False), values(1, 333), None)
+    many = (I.TensorSpec("V", I.ROLE_LSQ_W, -1, 1100, 2304, 9, True), values(1100, 2304), _basis(1100, k, 2))
+    c = np.float32(1e-3)
+    want = P.axpy_inplace_value(W, c, P.hybrid_z(cfg.seed, 4, 3, rows, cols, U, k, cfg.alpha, P.SCALE_UNIT, bits), dtype)
+    seen = []
+    for others in ([], [vector], [many]):
+        sess = make_session(cfg, [I.TensorSpec("W", I.ROLE_LSQ_W, -1, rows, cols, 3, True)] + [o[0] for o in others], [W] + [o[1] for o in others], [U] + [o[2] for o in others], bits=bits, arch=-1)
+        sess.perturb(4, float(c))
+        once = sess.get_theta(0)
+        sess.apply_updates([7, 8, 9], [0.5, -0.25, 1.0], 1e-3)
+        seen.append((once, sess.get_theta(0)))
+        sess.close()
+    assert np.all(np.abs(seen[0][0] - want) <= (F32_RTOL if dtype == "f32" else BF16_RTOL) * (np.abs(want) + PARAM_SCALE))
+    assert all(np.array_equal(a, b) for one in seen[1:] for a, b in zip(one, seen[0]))
