@@ -1064,24 +1064,35 @@ BwCarve bw_carve(const zgr_ctx* c, int batch, int seq) {
   v.mfma = c->dtype == ZGR_BF16 && M % 64 == 0;
   v.planes = c->dtype == ZGR_BF16 && M % 64 != 0;
   // those of the whole pass where they are fewer: two LayerNorms a block and the last (or first) one, the biases of four products with bf16 operands
-  const size_t all_sums = (2 * (size_t)m.n_layer + 1) * bw_layernorm_floats((int)M, (int)d) + (v.mfma || v.planes ? (size_t)m.n_layer * bw_bias_floats((int)M, (int)(5 * d + ff)) : 0);
+  const bool bf16 = c->dtype == ZGR_BF16;
+  const size_t all_sums = (2 * (size_t)m.n_layer + 1) * bw_layernorm_floats((int)M, (int)d) + (bf16 ? (size_t)m.n_layer * bw_bias_floats((int)M, (int)(5 * d + ff)) : 0);
   v.part_floats = std::max(std::min(kSumArena, all_sums), bw_scratch_floats((int)d, (int)std::max(std::max(ff, 3 * d), (size_t)m.n_class)));
   v.part = take(4 * v.part_floats);
   v.split = take(kProductScratch * 4);
-  if (v.mfma || v.planes) {
-    // what the products of FC2, FC1, the attention output and Q, K, V take, until the end of a block: gradients transposed (three planes of them where
-    // they stay fp32), the kept input transposed
-    const size_t in[4] = {ff, d, d, d}, out[4] = {d, ff, d, 3 * d}, Mp = align_up(M, 64);
-    for (int i = 0; i < 4; ++i) { v.tC[i] = take(2 * Mp * out[i] * (v.planes ? 3 : 1)); v.tL[2 * i] = take(2 * Mp * in[i]); }
-    if (v.mfma) {
-      // widest contraction of a product: the feed-forward width, the three projections side by side, or (decoder) the
-      // vocabulary, rounded up to the multiple of 64 the GEMM takes
-      const size_t widest = std::max(std::max(ff, 3 * d), m.arch == ZGR_ARCH_DECODER_LM ? align_up((size_t)m.vocab, 64) : (size_t)0);
-      v.tA = take(2 * M * widest);
-      v.tB = take(m.arch == ZGR_ARCH_DECODER_LM ? 2 * M * d : 0);
-      v.tW = take(m.arch == ZGR_ARCH_DECODER_LM ? 2 * d * align_up((size_t)m.vocab, 64) : 0);
-      for (int i = 0; i < 4; ++i) v.tL[2 * i + 1] = take(2 * in[i] * out[i]);      // the weights transposed
-    }
+  if (bf16) {
+    // What the products of FC2, FC1, the attention output and Q, K, V take until the end of a block: gradients transposed (three planes of them where
+    // they stay fp32), the kept input transposed.  Either form may be the larger one, and a caller who asked for its largest batch has room for all smaller ones: that of
+    // the larger of the two at the largest counts of its kind up to M.
+    const size_t in[4] = {ff, d, d, d}, out[4] = {d, ff, d, 3 * d}, base = off;
+    auto lay_out = [&](size_t tokens, bool planes) {
+      const size_t Mp = align_up(tokens, 64);
+      off = base;
+      for (int i = 0; i < 4; ++i) { v.tC[i] = take(2 * Mp * out[i] * (planes ? 3 : 1)); v.tL[2 * i] = take(2 * Mp * in[i]); }
+      if (!planes) {
+        // widest contraction of a product: the feed-forward width, the three projections side by side, or (decoder) the
+        // vocabulary, rounded up to the multiple of 64 the GEMM takes
+        const size_t widest = std::max(std::max(ff, 3 * d), m.arch == ZGR_ARCH_DECODER_LM ? align_up((size_t)m.vocab, 64) : (size_t)0);
+        v.tA = take(2 * Mp * widest);
+        v.tB = take(m.arch == ZGR_ARCH_DECODER_LM ? 2 * Mp * d : 0);
+        v.tW = take(m.arch == ZGR_ARCH_DECODER_LM ? 2 * d * align_up((size_t)m.vocab, 64) : 0);
+        for (int i = 0; i < 4; ++i) v.tL[2 * i + 1] = take(2 * in[i] * out[i]);      // the weights transposed
+      }
+      return off;
+    };
+    const size_t whole = M - M % 64, ragged = M - (M % 64 == 0);
+    const size_t end = std::max(whole ? lay_out(whole, false) : base, lay_out(ragged, true));
+    lay_out(M, v.planes);
+    off = end;
   }
   v.total = off;
   return v;

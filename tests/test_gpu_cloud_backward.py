@@ -170,6 +170,40 @@ def test_workspace_of_a_batch_holds_every_smaller_one(dtype, n_head, arch):
     sess.close()
 
 
+@pytest.mark.parametrize("arch,dtype,d,ff", [(I.ARCH_ENCODER_CLS, "bf16", 256, 1024), (I.ARCH_DECODER_LM, "bf16", 128, 1024), (I.ARCH_ENCODER_CLS, "f32", 64, 64)])
+def test_workspace_of_a_batch_holds_every_shorter_one(arch, dtype, d, ff):
+    """Every length, not only whole ones: bf16 models keep three planes of each gradient where the token count is no multiple of 64, the transposed weights where it is."""
+    cfg = I.shrink(I.CONFIGS["cfg2"], **dict(TINY_CLS if arch == I.ARCH_ENCODER_CLS else TINY_LM, arch=arch, name="bw_ws", n_layer=1, d_model=d, n_head=d // 64, d_ff=ff, max_pos=700,
+                                             batch=16, seq=700, dtype=dtype))
+    sess, _, _ = _setup(cfg)
+    need = lambda b, t: sess.lib.zgr_cloud_backward_workspace(sess.ctx, b, t)
+    for b in (1, 3, 16):
+        sizes = [need(b, t) for t in range(1, 701)]
+        assert all(0 < x <= y for x, y in zip(sizes, sizes[1:])), b
+    for t in (1, 63, 64, 129):
+        sizes = [need(b, t) for b in range(1, 130)]
+        assert all(0 < x <= y for x, y in zip(sizes, sizes[1:])), t
+    sess.close()
+
+
+def test_a_shorter_ragged_batch_runs_in_the_room_of_a_whole_one():
+    import ctypes as Ct
+    import torch
+    from paper_2601_12917_amd import binding as B
+    from tests.util import session_batch
+    cfg = I.shrink(I.CONFIGS["cfg2"], **dict(TINY_CLS, name="bw_room", dtype="bf16", d_model=256, n_head=4, d_ff=1024, max_pos=512, batch=1, seq=512))
+    sess, specs, _ = _setup(cfg, scale=2.0)
+    grads = [torch.zeros(s.rows, s.cols, device="cuda:0") for s in specs]
+    ptrs = (Ct.c_void_p * len(grads))(*[g.data_ptr() for g in grads])
+    work = torch.empty(sess.lib.zgr_cloud_backward_workspace(sess.ctx, 1, 512), dtype=torch.uint8, device="cuda:0")
+    short = I.shrink(cfg, name="bw_short", seq=511)
+    batch, loss = session_batch(sess, short, _batch(short, 3)), Ct.c_double()
+    B.check(sess.lib.zgr_cloud_backward(sess.ctx, Ct.byref(batch), ptrs, len(grads), Ct.byref(loss), work.data_ptr(), work.numel()), sess.ctx)
+    want_loss, want = sess.cloud_backward(batch)
+    assert loss.value == want_loss and all(torch.equal(a.flatten(), b.flatten()) for a, b in zip(grads, want))
+    sess.close()
+
+
 @pytest.mark.parametrize("batch,seq,act,post_ln", [(4, 48, "gelu", False), (3, 37, "gelu", False), (4, 48, "relu", True)])
 def test_bf16_gradients_point_where_the_oracle_gradients_point(batch, seq, act, post_ln, say):
     """192 tokens: the backward products run on the matrix cores; 111 tokens (not a multiple of 64): on the fp32 kernel."""
