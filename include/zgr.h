@@ -390,6 +390,10 @@ zgr_status zgr_debug_product(const void* A, int32_t a_dtype, int32_t a_k, int64_
                              int64_t ldb, int64_t b_batch, float* C, int64_t ldc, int64_t c_batch, int32_t M, int32_t N, int32_t K, float alpha,
                              int32_t batches, float* a_sums, int32_t epilogue, const float* bias, float* scratch, size_t scratch_floats, void* hip_stream);
 
+/* How the cloud's backward pass takes a block's weight gradients of a bf16 model: 0 on gradients rounded to bf16 (token counts that are multiples of 64), 1 on planes of
+ * fp32 gradients, in one launch, 2 on fp32 gradients as they lie, a launch each; -1 for sizes it does not take.  For tests. */
+int32_t zgr_debug_weight_gradient_form(int32_t tokens, int32_t d_model, int32_t d_ff);
+
 /* The weight gradient of the cloud's backward pass for a bf16 model whose token count is no multiple of 64, all DEVICE: with dy <- dy act'(u) (u may be NULL; relu 0
  * erf-GELU, 1 ReLU), dy fp32 [M, N] and x bf16 [M, K], dW[p] [N / parts, K] = rows p N / parts .. of dy^T x and db[p] the sums of those columns of dy (dW and db:
  * HOST arrays of `parts` pointers, 1 to 3).  N and K multiples of 64.  scratch: 6 N Mp + 2 K Mp + 4 (N Mp / 64 + 512) bytes or more, Mp: M rounded up to a multiple of 64.  For tests.   */

@@ -1023,12 +1023,24 @@ struct BwCarve {
   size_t part = 0, part_floats = 0;  // chunk sums of the column reductions until they are added up
   size_t tA = 0, tB = 0, tW = 0, tC[4] = {}, tL[8] = {};     // bf16 operands of the matrix-core products (bf16 models)
   bool mfma = false;                 // a token count that is a multiple of 64: gradients are rounded to bf16 for the products
-  bool planes = false;               // any other: the weights' gradients are taken on the planes of fp32 gradients
+  bool planes = false;               // any other up to plane_tokens: the weights' gradients are taken on the planes of fp32 gradients
   size_t split = 0;                  // parts of split sums
   size_t total = 0;
 };
 constexpr size_t kSumArena = (size_t)1 << 23;          // floats at most: the chunk sums of 8 blocks of the 125M model, 2 of the 1.3B model
 constexpr size_t kProductScratch = ((size_t)1 << 20) + ((size_t)1 << 14);      // floats: split sums take 2048 waves at most, eight to a 64 x 64 result, and 64 row sums each
+
+// Up to how many tokens a bf16 model's weight gradients are taken on planes of dy where the count is no multiple of 64 (a block's four products in one launch,
+// undivided sums of three times the tokens); beyond, product.hip's kernel, a launch each, shares the sums among waves and blocks.  By the 64 x 64 tiles of the four results:
+// one a CU or fewer, and the group is a chain of k-tiles beside idle CUs; some four a CU, and it is the faster one over the longest range; with
+// more, product.hip fills the chip as well and wins when the launches it takes more weigh little.  Whole backward passes of four blocks, group against product.hip:
+//   12 tiles (64 columns): 1240 tokens 613 us against 644, 2046 700 and 649, 8184 1461 and 933      192 (256): 1488 745 and 757, 1736 769 and 752, 8184 2103 and 1731
+//   300 (320): 1736 872 and 891, 3100 1154 and 1187      768 (512): 3100 1753 and 1779, 4092 2104 and 2095, 8184 3760 and 3493
+//   1728 (768): 2046 2022 and 2047, 2480 2318 and 2281, 8184 6553 and 6176      3072 (1024): 1023 1699 and 1729, 1240 2191 and 2176, 2046 2940 and 2752
+size_t plane_tokens(size_t d, size_t ff) {
+  const size_t tiles = (2 * ff + 4 * d) * d / 4096;
+  return tiles <= 256 ? 1536 : tiles <= 1024 ? 4096 : tiles <= 2048 ? 2048 : 1152;
+}
 
 BwCarve bw_carve(const zgr_ctx* c, int batch, int seq) {
   BwCarve v;
@@ -1062,7 +1074,7 @@ BwCarve bw_carve(const zgr_ctx* c, int batch, int seq) {
   v.attn = take(4 * bw_attention_scratch(c->dtype, (int)d, m.n_head, batch, seq, m.arch == ZGR_ARCH_DECODER_LM ? 1 : 0));
   v.stats = take(M * 2 * 4);
   v.mfma = c->dtype == ZGR_BF16 && M % 64 == 0;
-  v.planes = c->dtype == ZGR_BF16 && M % 64 != 0;
+  v.planes = c->dtype == ZGR_BF16 && M % 64 != 0 && M <= plane_tokens(d, ff);
   // those of the whole pass where they are fewer: two LayerNorms a block and the last (or first) one, the biases of four products with bf16 operands
   const bool bf16 = c->dtype == ZGR_BF16;
   const size_t all_sums = (2 * (size_t)m.n_layer + 1) * bw_layernorm_floats((int)M, (int)d) + (bf16 ? (size_t)m.n_layer * bw_bias_floats((int)M, (int)(5 * d + ff)) : 0);
@@ -1089,9 +1101,9 @@ BwCarve bw_carve(const zgr_ctx* c, int batch, int seq) {
       }
       return off;
     };
-    const size_t whole = M - M % 64, ragged = M - (M % 64 == 0);
+    const size_t whole = M - M % 64, planes = std::min(M, plane_tokens(d, ff)), ragged = planes - (planes % 64 == 0);
     const size_t end = std::max(whole ? lay_out(whole, false) : base, lay_out(ragged, true));
-    lay_out(M, v.planes);
+    if (v.mfma || v.planes) lay_out(M, v.planes);
     off = end;
   }
   v.total = off;
@@ -1142,7 +1154,7 @@ zgr_status zgr_cloud_backward(zgr_ctx* c, const zgr_batch* b, float* const* grad
   const int32_t* tok = reinterpret_cast<const int32_t*>(b->x);
   const int32_t* lengths = lm ? nullptr : b->lengths;
   const size_t xbytes = (size_t)M * d * 4;
-  // The products of the backward half.  fp32 models and ragged token counts (but for their weights' gradients, on_planes): fp32 products on the operands as they lie.  bf16 models
+  // The products of the backward half.  fp32 models and ragged token counts (but for their weights' gradients up to plane_tokens): fp32 products on the operands as they lie.  bf16 models
   // (token count a multiple of 64): the forward pass's matrix-core GEMM, which contracts along the rows of both
   // operands, on bf16 copies written out with the contraction index innermost.
   auto product = [&](const void* A, bool a_k, int64_t lda, const void* B, int64_t ldb, float* C, int64_t ldc, int Mp, int Np, int Kp, float* a_sums, int row_blocks = 1, int* parts_left = nullptr) {
@@ -1623,6 +1635,11 @@ zgr_status zgr_debug_product(const void* A, int32_t a_dtype, int32_t a_k, int64_
   p.a_sums = a_sums; p.epilogue = epilogue; p.bias = bias; p.scratch = scratch; p.scratch_floats = scratch_floats;
   HIP_TRY(nullptr, launch_product(p, reinterpret_cast<hipStream_t>(hip_stream)));
   return ZGR_OK;
+}
+
+int32_t zgr_debug_weight_gradient_form(int32_t tokens, int32_t d_model, int32_t d_ff) {
+  if (tokens < 1 || d_model < 64 || d_model % 64 || d_ff < 64 || d_ff % 64) return -1;
+  return tokens % 64 == 0 ? 0 : (size_t)tokens <= plane_tokens((size_t)d_model, (size_t)d_ff) ? 1 : 2;
 }
 
 zgr_status zgr_debug_weight_gradient(float* dy, const float* u, int32_t relu, const void* x, int32_t M, int32_t N, int32_t K, int32_t parts, float* const* dW, float* const* db,

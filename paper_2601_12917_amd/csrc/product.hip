@@ -1,7 +1,7 @@
 // C = epilogue(alpha A B + bias) with fp32 products and sums on the matrix cores, for operands as they lie: fp32 or bf16,
 // contiguous along the summed index or along the other one, any sizes.  These are the backward products of fp32 models, of bf16
-// models whose token count is no multiple of 64 (the gradients of a block's weights only where a side is no multiple of 64 either: forward.hip
-// takes the others on planes of dy), the five products per head of the attention rule, and the projections of fp32 models that are too
+// models whose token count is no multiple of 64 (the gradients of a block's weights only where the count is long: forward.hip
+// takes the others on planes of dy, api.hip's plane_tokens), the five products per head of the attention rule, and the projections of fp32 models that are too
 // small for forward.hip's tiles to fill the chip.
 //
 // Two fp32 operands take the fp32 instruction (v_mfma_f32_16x16x4_f32); with a bf16 operand the products are taken on v_mfma_f32_16x16x32_bf16 (planes.h),

@@ -196,3 +196,21 @@ def test_bench_refuses_more_than_one_gpu():
     r = subprocess.run([sys.executable, os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "bench.py"), "--gpus", "2"],
                        capture_output=True, text=True, timeout=120)
     assert r.returncode == 2 and "one GPU" in r.stderr and r.stdout.strip() == ""
+
+
+@pytest.mark.parametrize("tokens,d,ff,form", [
+    # whole passes measured both ways (us, planes in one launch against a product each): the faster one is taken
+    (64, 64, 256, 0), (2048, 768, 3072, 0),
+    (33, 64, 256, 1), (1240, 64, 256, 1),            # 440 / 486, 613 / 644
+    (2046, 64, 256, 2), (8184, 64, 256, 2),          # 700 / 649, 1461 / 933
+    (1023, 128, 512, 1), (8184, 128, 512, 2),        # 625 / 694, 1628 / 1064
+    (1023, 256, 1024, 1), (4092, 256, 1024, 2),      # 651 / 738, 1223 / 1137
+    (3100, 384, 1536, 1), (8184, 384, 1536, 2),      # 1388 / 1481, 3018 / 2762
+    (2046, 512, 2048, 1), (16368, 512, 2048, 2),     # 1237 / 1317, 7066 / 6219
+    (1240, 768, 3072, 1), (4092, 768, 3072, 2),      # 1363 / 1428, 3537 / 3381
+    (231, 1024, 4096, 1), (2046, 1024, 4096, 2),     # 874 / 933, 2940 / 2752
+    (3100, 2048, 8192, 2),                           # 13401 / 11742
+    (77, 96, 256, -1), (0, 64, 64, -1),
+])
+def test_long_ragged_weight_gradients_are_not_left_to_undivided_sums(lib, tokens, d, ff, form):
+    assert lib.zgr_debug_weight_gradient_form(tokens, d, ff) == form

@@ -455,3 +455,22 @@ def test_embedding_rows_of_frequent_and_of_rare_tokens(vocab, d, seq, batch):
         want = grads_or[s.name]
         assert np.abs(grads[i] - want).max() <= 2e-4 * np.abs(want).max() + floor, s.name
     sess.close()
+
+
+@pytest.mark.parametrize("batch,seq,d,ff,act,post_ln", [(5, 307, 64, 128, "gelu", False), (29, 53, 64, 128, "gelu", False), (2, 1025, 64, 64, "relu", False), (41, 50, 128, 256, "relu", True)])
+def test_ragged_counts_on_either_side_of_the_planes(batch, seq, d, ff, act, post_ln):
+    """1535, 1537 and 2050 tokens: the last count whose weight gradients are taken on planes, and counts that take them on fp32 gradients as they lie.  Bounds as above."""
+    cfg = I.shrink(I.CONFIGS["cfg2"], **dict(TINY_CLS, name="bw_long_ragged", dtype="bf16", n_layer=1, d_model=d, n_head=d // 32, d_ff=ff, max_pos=2050, batch=batch, seq=seq, act=act, post_ln=post_ln))
+    sess, specs, P = _setup(cfg, scale=2.0)
+    arrays = _batch(cfg, 3)
+    loss, grads = _device(sess, cfg, arrays)
+    loss_or, grads_or = _oracle(cfg, P, arrays)
+    assert abs(loss - loss_or) <= 2e-2 * max(1.0, abs(loss_or))
+    for i, s in enumerate(specs):
+        want = grads_or[s.name]
+        if s.role == I.ROLE_BK or not want.any():
+            continue
+        cos = float((grads[i] * want).sum() / (np.linalg.norm(grads[i]) * np.linalg.norm(want)))
+        ratio = float(np.linalg.norm(grads[i]) / np.linalg.norm(want))
+        assert cos >= 0.995 and abs(ratio - 1.0) <= 0.05, (s.name, cos, ratio)
+    sess.close()
