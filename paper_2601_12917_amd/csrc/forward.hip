@@ -1004,6 +1004,39 @@ __device__ __forceinline__ void gemm_bf16_tile(const bf16_t* __restrict__ A, con
     for (int i = 0; i < FM; ++i)
 #pragma unroll
       for (int j = 0; j < FN; ++j) acc[i][j] += total[i][j];
+    // a sum that is not finite: again by the fp32 instructions (planes.h; W's infinities meet the zeros in A's smaller planes), run by run the terms of A's number
+    float zero = 0.f;
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) zero = __builtin_fmaf(acc[i][j][v], 0.f, zero);
+    if (__builtin_expect(__ballot(!(zero == 0.f)) != 0, 0)) {
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+#pragma unroll 1
+      for (int k = half; k < nkw * BK; k += 2) {
+        float a[FM], w[FN];
+#pragma unroll
+        for (int i = 0; i < FM; ++i) {
+          const bf16_t* r = A + (size_t)min(m0 + wm * (BM / WM) + 32 * i + l32, M - 1) * lda + k;
+          a[i] = 0.f;
+#pragma unroll
+          for (int f = 0; f < FOLD; ++f) a[i] += to_f32(r[f * nkw * BK]);
+        }
+#pragma unroll
+        for (int j = 0; j < FN; ++j) w[j] = to_f32(W[(size_t)min(n0 + wn * (BN / WN) + 32 * j + l32, N - 1) * ldw + k]);
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+          for (int j = 0; j < FN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], w[j], acc[i][j], 0, 0, 0);
+      }
+    }
   }
   if (MODE == EPI_CE) {
     // Cross-entropy partials instead of logits.  The product is taken transposed (rows = vocabulary entries,

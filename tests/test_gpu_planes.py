@@ -172,3 +172,19 @@ def test_weight_gradient_of_wild_operands(M):
     dW, db = _weight_gradient(dy.cuda(), None, 0, x.cuda(), 1)
     _same(dW.cpu(), want)
     assert torch.equal(torch.isnan(db.cpu()), torch.isnan(wb))
+
+
+@pytest.mark.parametrize("M,N,K", [(33, 192, 320), (200, 1600, 1536), (77, 2112, 2048)])
+def test_weight_gradient_with_infinite_activations(M, N, K):
+    """An infinite entry of x meets the zeros in dy's second and third plane: what fp32 products leave infinite stays infinite, at each tile size that takes planes."""
+    import torch
+    gen = torch.Generator().manual_seed(M)
+    dy, x = torch.randn(M, N, generator=gen).bfloat16().float(), torch.randn(M, K, generator=gen).bfloat16()
+    dy[:, ::2] += 2.0 ** -12                                       # every other column with entries in its second plane
+    dy[5, 11] = 0.0
+    for i, v in ((0, float("inf")), (5, float("-inf")), (9, 3e38), (M - 1, float("nan"))):
+        x[i, (37 * i) % K] = v
+    want = dy.double().T @ x.double()
+    dW, db = _weight_gradient(dy.cuda(), None, 0, x.cuda(), 1)
+    _same(dW.cpu(), want)
+    assert torch.isinf(dW).sum() > N and torch.all(torch.isfinite(db))
