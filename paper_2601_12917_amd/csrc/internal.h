@@ -66,6 +66,7 @@ struct PerturbArgs {
   int32_t           n_q;
   uint32_t          qstep[kMaxBatch];
   float             qcoef[kMaxBatch];
+  int32_t           extreme;   // set by the launchers: coefficients for which U R is taken on the fp32 instruction
   // spread: the pass leaves theta + c Z in copy[0], that minus 2 c Z in copy[1] and, with restore, that plus c Z in theta, each
   // rounded to the storage type.  from_copy: theta <- copy[1] + c Z.
   unsigned char*    copy[2];

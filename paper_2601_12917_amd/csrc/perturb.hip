@@ -12,7 +12,9 @@
 #include "internal.h"
 #include "planes.h"
 
+#include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <mutex>
 
 namespace zgr {
@@ -469,7 +471,8 @@ __global__ void __launch_bounds__(256) perturb_tile_kernel(PerturbArgs a, const 
 // once 4.54 ms), by writes where three are (2.2 ms, 4.4 TB/s).  On v_mfma_f32_16x16x4f32, whose 32 (rank 32: 64) cycles per four terms the vector
 // instructions do not hide, with four waves to a radius table and theta requested one vector ahead, the same passes took 1.49, 4.6 and 2.3 ms, and
 // 302e6 entries of rank 32 487 and 660 us, now 382 and 534.  Z is off from fp64 by 0.7e-7 of its norm at rank 16, 1.1e-7 at 64 (1.0 and 1.6e-7
-// with the fp32 instruction).  Entries of U below 2^-110 lose their last plane.
+// with the fp32 instruction).  Entries of U that planes don't hold (infinite, too large for bf16, or so small that their last plane is subnormal) send their wave
+// to the fp32 instruction, and so do sums of perturbations with coefficients so far from 1 that planes don't hold R.
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kTilePasses = 3;      // runs of the tile list per block of the matrix-core kernel
 constexpr int kTileWaves = 8;       // of 16 rows each, a tile's: one radius table and one slice of R serve them all
@@ -527,14 +530,21 @@ __device__ __forceinline__ void eight_of(const TensorDesc& d, const RawEight& r,
   }
 }
 
+// Whether three planes hold a number: it does not round up to infinity, and its last place is a normal number or it is zero.
+__device__ __forceinline__ bool planes_hold(float x) {
+  constexpr uint32_t lo = 24u << 23, hi = 0x7F7F7FFFu;       // 2^-103, and the last one that rounds to a finite bf16
+  return ((__float_as_uint(x) << 1) - (lo << 1) <= (hi - lo) << 1) | (x == 0.f);
+}
+
 // acc[t] = U R for the wave's 16 rows and the 16 columns of tile t, eight tiles from R's entries at Rs on; `first` holds the lane's first eight where t.eights.
+// extreme: planes don't hold R.
 template <int P>
-__device__ __forceinline__ void contract(const Tile& tl, const RawEight& first, const planes_u32x4* Rs, int64_t urow, int n16, int rg, f32x4 (&acc)[8]) {
+__device__ __forceinline__ void contract(const Tile& tl, const RawEight& first, const planes_u32x4* Rs, bool extreme, int64_t urow, int n16, int rg, f32x4 (&acc)[8]) {
   constexpr int TC = 32 * P;
   const int n8 = tl.n8, plane = n8 * TC;                      // 16-byte entries of a plane of R
 #pragma unroll
   for (int j = 0; j < 8; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float largest = 0.f;
+  bool held = true;
   auto cut_u = [&](int l8, int c8, bool in, PlanesOf<3>& o) {
     float u[8];
     if (tl.eights) {
@@ -549,7 +559,7 @@ __device__ __forceinline__ void contract(const Tile& tl, const RawEight& first, 
     for (int w = 0; w < 4; ++w) {
       u[2 * w] = in ? u[2 * w] : 0.f; u[2 * w + 1] = in ? u[2 * w + 1] : 0.f;         // past the end: zeros times R's last eight
       cut_pair_rounded(u[2 * w], u[2 * w + 1], w, o);
-      largest = fmaxf(fmaxf(largest, __builtin_fabsf(u[2 * w])), __builtin_fabsf(u[2 * w + 1]));
+      held &= planes_hold(u[2 * w]) & planes_hold(u[2 * w + 1]);
     }
   };
   PlanesOf<3> pu;
@@ -584,7 +594,7 @@ __device__ __forceinline__ void contract(const Tile& tl, const RawEight& first, 
       if (t & 1) in_this_order();
     }
   }
-  if (__builtin_expect(__ballot(largest > 3.3e38f) != 0, 0)) {      // infinite or too large for bf16 (a NaN stays one): on the fp32 instruction
+  if (__builtin_expect(extreme || __ballot(!held) != 0, 0)) {
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
     const uint16_t* r = reinterpret_cast<const uint16_t*>(Rs);
@@ -734,7 +744,7 @@ __device__ __forceinline__ void tile_mfma_share(const PerturbArgs& a, const Tens
 #pragma unroll
     for (int round = 0; round < kRounds; ++round) {
       const bool last = round + 1 == kRounds;
-      if (round * kAhead % (4 * kGroups) == 0 && any) contract<P>(t, u8, Rs + group_of(round * kAhead) * GC, u_row(t), n16, rg, acc);
+      if (round * kAhead % (4 * kGroups) == 0 && any) contract<P>(t, u8, Rs + group_of(round * kAhead) * GC, MODE == kBatch && a.extreme, u_row(t), n16, rg, acc);
       if (last) {
         more = advance();
         if (more) t = tile_of(descs, items, w);
@@ -1012,6 +1022,14 @@ int split_grid(PerturbArgs& a, int items, int capacity) {
   return compute + a.pull_blocks;
 }
 
+// Whether planes (planes.h) may not hold the entries of b R that a sum of perturbations with these coefficients draws: Gaussians are within 2^-35 and 2^3 of 1 (and all but one in 2^15
+// above 2^-15), b within 2^-31 and 2^16.
+bool extreme_coefficients(const PerturbArgs& a) {
+  float largest = 0.f;
+  for (int i = 0; i < a.n_q; ++i) largest = std::max(largest, std::fabs(a.qcoef[i]));
+  return largest != 0.f && !(largest >= 0x1p-57f && largest <= 0x1p100f);
+}
+
 int mode_of(const PerturbArgs& a) { return a.n_q > 0 ? kBatch : (a.spread ? kSpread : kOne); }
 
 template <typename T, int P>
@@ -1036,6 +1054,7 @@ template <typename T, int P>
 hipError_t launch_tile_t(const PerturbArgs& a_in, float c, float* zout, hipStream_t s, int n_cu, const RadiusEntry* tab) {
   PerturbArgs a = a_in;
   const int kp = (a.max_k + 7) & ~7;
+  a.extreme = extreme_coefficients(a);
   if (a.min_k >= kMfmaMinK) {
     const size_t lds_m = sizeof(RadiusEntry) * (size_t)kRadiusTabEntries + 6 * (size_t)kp * 32 * P;      // three planes of two bytes
     const int variant = zout ? 3 : mode_of(a);
@@ -1074,7 +1093,9 @@ hipError_t launch_tile_t(const PerturbArgs& a_in, float c, float* zout, hipStrea
 }
 
 template <typename T, int P>
-hipError_t launch_small_t(const PerturbArgs& a, float c, hipStream_t s, const RadiusEntry* tab) {
+hipError_t launch_small_t(const PerturbArgs& a_in, float c, hipStream_t s, const RadiusEntry* tab) {
+  PerturbArgs a = a_in;
+  a.extreme = extreme_coefficients(a);
   const int kp = (a.max_k + 7) & ~7, mode = mode_of(a);
   static TileLaunchCache cache[6];
   int per_cu = 1;

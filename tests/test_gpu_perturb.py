@@ -269,3 +269,25 @@ def test_bits_do_not_depend_on_the_height_of_the_tiles(rows, cols, k, dtype, bit
         sess.close()
     assert np.all(np.abs(seen[0][0] - want) <= (F32_RTOL if dtype == "f32" else BF16_RTOL) * (np.abs(want) + PARAM_SCALE))
     assert all(np.array_equal(a, b) for one in seen[1:] for a, b in zip(one, seen[0]))
+
+
+@pytest.mark.parametrize("k,bits", [(16, 32), (40, 32), (24, 16)])
+def test_basis_rows_and_coefficients_too_small_for_planes(k, bits):
+    """Rows of U around 2^-114 and 2^-130, whose last bits no plane of normal bf16 numbers holds, and a sum of perturbations with coefficients around 2^-112: within the norm of fp32
+    products (a sum of k terms rounds k times by 2^-24 of its size at most, R by 2 2^-23), each row by itself."""
+    rows, cols = 160, 128
+    cfg = I.shrink(_single_tensor_cfg(rows, cols, k), alpha=0.0)
+    spec = I.TensorSpec("W", I.ROLE_LSQ_W, -1, rows, cols, 3, True)
+    U = _basis(rows, k)
+    U[40:50] *= np.float32(2.0 ** -111)
+    U[50:60] *= np.float32(2.0 ** -127)                             # subnormal ones: results with 2^-22 of their size
+    off = lambda got, want: np.linalg.norm(got - want.astype(np.float64), axis=1) / np.linalg.norm(want.astype(np.float64), axis=1)
+    sess = make_session(cfg, [spec], [np.zeros((rows, cols), np.float32)], [U], bits=bits, arch=-1)
+    Z = P.hybrid_z(cfg.seed, 1, 3, rows, cols, U, k, 0.0, P.SCALE_UNIT, bits)
+    assert off(sess.fill_z(0, 1).astype(np.float64), Z).max() <= (k + 4) * 2.0 ** -24
+    sess.set_basis(0, _basis(rows, k), k)
+    lr, gs = np.float32(1e-30), np.float32([2e-4, -3e-4])
+    sess.apply_updates([1, 2], gs, float(lr))
+    want = sum(-float(np.float32(lr * g)) * P.hybrid_z(cfg.seed, s, 3, rows, cols, _basis(rows, k), k, 0.0, P.SCALE_UNIT, bits).astype(np.float64) for s, g in zip((1, 2), gs))
+    assert off(sess.get_theta(0).astype(np.float64), want).max() <= (k + 8) * 2.0 ** -24
+    sess.close()
