@@ -390,6 +390,9 @@ zgr_status zgr_debug_product(const void* A, int32_t a_dtype, int32_t a_k, int64_
                              int64_t ldb, int64_t b_batch, float* C, int64_t ldc, int64_t c_batch, int32_t M, int32_t N, int32_t K, float alpha,
                              int32_t batches, float* a_sums, int32_t epilogue, const float* bias, float* scratch, size_t scratch_floats, void* hip_stream);
 
+/* How the least-squares row losses and their mean are taken: 0 in one launch, 1 in two; -1 for sizes below 1.  For tests. */
+int32_t zgr_debug_lsq_loss_form(int32_t batch, int32_t n_out);
+
 /* How the cloud's backward pass takes a block's weight gradients of a bf16 model: 0 on gradients rounded to bf16 (token counts that are multiples of 64), 1 on planes of
  * fp32 gradients, in one launch, 2 on fp32 gradients as they lie, a launch each; -1 for sizes it does not take.  For tests. */
 int32_t zgr_debug_weight_gradient_form(int32_t tokens, int32_t d_model, int32_t d_ff);

@@ -91,6 +91,7 @@ SYMBOLS = {
     "zgr_debug_generator_rate": (C.c_int, [C.c_int32, C.c_int32, C.c_int32, C.c_void_p, C.c_void_p]),
     "zgr_debug_gemm": (C.c_int, [C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_void_p]),
     "zgr_debug_gemm_form": (C.c_int32, [C.c_int32, C.c_int32, C.c_int32]),
+    "zgr_debug_lsq_loss_form": (C.c_int32, [C.c_int32, C.c_int32]),
     "zgr_debug_weight_gradient_form": (C.c_int32, [C.c_int32, C.c_int32, C.c_int32]),
     "zgr_debug_weight_gradient": (C.c_int, [C.c_void_p, C.c_void_p, C.c_int32, C.c_void_p, C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_void_p), C.POINTER(C.c_void_p),
                                             C.c_void_p, C.c_size_t, C.c_void_p]),

@@ -1637,6 +1637,8 @@ zgr_status zgr_debug_product(const void* A, int32_t a_dtype, int32_t a_k, int64_
   return ZGR_OK;
 }
 
+int32_t zgr_debug_lsq_loss_form(int32_t batch, int32_t n_out) { return batch < 1 || n_out < 1 ? -1 : lsq_in_one_block(batch, n_out) ? 0 : 1; }
+
 int32_t zgr_debug_weight_gradient_form(int32_t tokens, int32_t d_model, int32_t d_ff) {
   if (tokens < 1 || d_model < 64 || d_model % 64 || d_ff < 64 || d_ff % 64) return -1;
   return tokens % 64 == 0 ? 0 : (size_t)tokens <= plane_tokens((size_t)d_model, (size_t)d_ff) ? 1 : 2;

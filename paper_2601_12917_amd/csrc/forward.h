@@ -50,6 +50,7 @@ hipError_t launch_ce_rows(const float* logits, const int32_t* targets, float* ro
 hipError_t launch_mean_f64(const float* row_loss, int n, double inv_count, double* out, hipStream_t s, Twin tw = {});
 hipError_t launch_cls_head(int dtype, const void* h, const void* Wc, const void* bc, float* logits, int batch, int seq, int d, int n_class, hipStream_t s, Twin tw = {});
 // row losses and, at out (one per model), their mean
+bool       lsq_in_one_block(int batch, int n_out);
 hipError_t launch_lsq_loss(const float* pred, const float* Y, float* row_loss, int batch, int n_out, double* out, hipStream_t s, Twin tw = {});
 
 }  // namespace zgr

@@ -2104,10 +2104,11 @@ hipError_t launch_cls_head(int dtype, const void* h, const void* Wc, const void*
   return hipGetLastError();
 }
 
-// One block a model while a wave has at most four rows and a lane sixteen entries (with a product of 64 columns in front: 32 rows of 256 7.2 us against 9.2 in two launches,
-// 64 of 256 8.6 against 9.0, 16 of 1024 7.8 against 9.2; 64 of 512 10.0 against 8.9, 128 of 128 13.1 against 9.2).
+// One block a model up to 16 entries a thread, or 64 a lane where there are fewer rows than waves (without the product in front: 1 x 4096 4.1 us against 5.9 in two launches,
+// 16 x 1024 4.0 against 5.9, 64 x 256 4.3 against 5.9; 8 x 4096, 32 x 1024 and 64 x 512 6.5 against 5.9; 1 x 8192 6.2 either way, 1 x 16384 10.7 against 9.4).
+bool lsq_in_one_block(int batch, int n_out) { return batch <= 64 && n_out <= 4096 && (int64_t)batch * n_out <= 16384; }
 hipError_t launch_lsq_loss(const float* pred, const float* Y, float* row_loss, int batch, int n_out, double* out, hipStream_t s, Twin tw) {
-  if (batch <= 64 && (int64_t)batch * n_out <= 16384) {
+  if (lsq_in_one_block(batch, n_out)) {
     hipLaunchKernelGGL(lsq_loss_kernel<1024>, dim3(tw.models), dim3(1024), 0, s, pred, Y, row_loss, n_out, batch, 1.0 / batch, out, tw.row_loss);
     return hipGetLastError();
   }

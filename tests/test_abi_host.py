@@ -214,3 +214,13 @@ def test_bench_refuses_more_than_one_gpu():
 ])
 def test_long_ragged_weight_gradients_are_not_left_to_undivided_sums(lib, tokens, d, ff, form):
     assert lib.zgr_debug_weight_gradient_form(tokens, d, ff) == form
+
+
+@pytest.mark.parametrize("batch,n_out,form", [
+    # measured both ways (us, one launch against two)
+    (1, 4096, 0), (3, 4096, 0), (16, 1024, 0), (32, 512, 0), (64, 256, 0),      # 4.1 / 5.9, 4.2 / 5.8, 4.0 / 5.9, 3.9 / 5.9, 4.3 / 5.9
+    (1, 16384, 1), (8, 4096, 1), (16, 1536, 1), (32, 1024, 1), (64, 384, 1),    # 10.7 / 9.4, 6.5 / 5.9, 6.5 / 5.9, 6.6 / 5.9, 6.6 / 5.9
+    (65, 1, 1), (0, 4, -1), (4, 0, -1),
+])
+def test_few_long_rows_are_not_left_to_a_wave_each(lib, batch, n_out, form):
+    assert lib.zgr_debug_lsq_loss_form(batch, n_out) == form

@@ -392,9 +392,9 @@ def test_non_finite_loss_is_reported_and_parameters_are_restored_lm(cfg, fused):
     sess.close()
 
 
-@pytest.mark.parametrize("batch,n_out", [(1, 1), (1, 7), (5, 37), (16, 1024), (17, 65), (64, 256), (64, 257), (65, 252), (33, 497)])
+@pytest.mark.parametrize("batch,n_out", [(1, 1), (1, 7), (5, 37), (16, 1024), (17, 65), (64, 256), (64, 257), (65, 252), (33, 497), (1, 4096), (1, 4097), (3, 5000), (1, 16384)])
 def test_least_squares_rows_and_mean_on_either_side_of_one_block(batch, n_out):
-    """Row losses and their mean in one launch (up to 64 rows and 16384 entries) and in two, for one model and for the step's two.  A prediction of 8 products is
+    """Row losses and their mean in one launch (up to 64 rows of 4096 and 16384 entries) and in two, for one model and for the step's two.  A prediction of 8 products is
     off by at most 9 2^-24 of their magnitudes, a row of n squares by twice that and (two launches) by 2^-24 sqrt(n) more."""
     cfg = I.shrink(I.CONFIGS["cfg1"], name=f"lsq{batch}x{n_out}", lsq_out=n_out, lsq_in=8, batch=batch, k=1, k_full=1)
     specs, values, bases = inputs_of(cfg)
