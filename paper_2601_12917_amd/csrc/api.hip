@@ -1662,6 +1662,18 @@ zgr_status zgr_debug_weight_gradient(float* dy, const float* u, int32_t relu, co
   return ZGR_OK;
 }
 
+zgr_status zgr_debug_product_group(int32_t count, const void* const* A, const void* const* W, float* const* out, const int32_t* M, const int32_t* N, int32_t K, int32_t ld, void* hip_stream) {
+  if (!A || !W || !out || !M || !N) return fail(nullptr, ZGR_ERR_NULL, "NULL argument");
+  if (count < 1 || count > kGroupedProducts || K < 64 || K % 64 || ld < K || ld % 8) return fail(nullptr, ZGR_ERR_SHAPE, "bad shape");
+  ProductGroup g;
+  for (int32_t j = 0; j < count; ++j) {
+    if (!A[j] || !W[j] || !out[j]) return fail(nullptr, ZGR_ERR_NULL, "NULL argument");
+    g.job[g.count++] = GroupedProduct{A[j], W[j], out[j], M[j], N[j], K, ld, ld};
+  }
+  HIP_TRY(nullptr, launch_product_group(g, reinterpret_cast<hipStream_t>(hip_stream)));
+  return ZGR_OK;
+}
+
 zgr_status zgr_debug_rmw(void* buf, size_t bytes, int32_t dtype, float c, int32_t mode, int32_t blocks, void* sink16, void* hip_stream) {
   if (!buf || !sink16) return fail(nullptr, ZGR_ERR_NULL, "NULL argument");
   if (bytes % 16 || ((uintptr_t)buf & 15) || ((uintptr_t)sink16 & 15)) return fail(nullptr, ZGR_ERR_SHAPE, "size and pointers must be multiples of 16 bytes");

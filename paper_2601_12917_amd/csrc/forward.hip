@@ -801,9 +801,9 @@ __device__ __forceinline__ void gemm_bf16_tile(const bf16_t* __restrict__ A, con
   const int nk = K / BK, nkw = nk / FOLD;                       // k-tiles of A and of W
   auto w_ktile = [&](int kt) {
     if constexpr (FOLD == 1) return kt;
-    else { const int r = kt < nkw ? kt : kt - nkw; return FOLD == 2 || r < nkw ? r : r - nkw; }
+    else { const int r = kt < nkw ? kt : kt - nkw; return r < nkw ? r : r - nkw; }
   };
-  static_assert(FOLD <= 3, "runs");
+  static_assert(FOLD == 1 || FOLD == 3, "runs");
   // reader: lane (l32, half) reads row l32 of each fragment, logical chunk 2*ks + half
   const int l32 = lane & 31, half = lane >> 5, swz = (l32 / RPB) % CPR;
   int koff[BK / 16];
@@ -1196,7 +1196,9 @@ static hipError_t launch_group_f(const ProductGroup& g, hipStream_t s) {
     return t;
   };
   const int64_t t256 = tiles(256, 256), t128 = tiles(128, 128);
-  if constexpr (FOLD == 1) {                               // (pieces of sums leave 256 x 256 tiles no registers)
+  // The sizes at which one product takes these tiles (launch_gemm).  256 x 256 against 128 x 128 here: passes of four blocks of 2048 columns, 1024 tokens 2593 us against 2712, 4096
+  // 6364 against 6887.  (Pieces of sums leave them no registers.)
+  if constexpr (FOLD == 1) {
     if (t256 >= 512) return launch_group_t<256, 256, 2, 4, 64, 20, 1, FOLD>(g, t256, s);
   }
   if (t128 > 256) return launch_group_t<128, 128, 2, 4, 64, 8, 1, FOLD>(g, t128, s);
@@ -1987,7 +1989,10 @@ hipError_t launch_product_group(const ProductGroup& g, hipStream_t s) {
 
 // Some 24 k-tiles a slice and up to two blocks a CU, where the undivided product would leave half of the CUs without a tile of 128 x 128 (and takes tiles of 64 x 64): the
 // gradients of the inputs of FC1 and of Q, K, V at 2048 tokens and 768 columns (sums of 3072 and 2304) 21.5 us on average, in two slices 16.3, and of the head
-// (50304) 290, in five 185; the LayerNorm rules behind them 9.8 us with one part, 11.7 with two on average.
+// (50304) 290, in five 185; the LayerNorm rules behind them 9.8 us with one part, 11.7 with two on average.  Where the slices' tiles are still so few that the group takes
+// 64 x 64: the heads' passes of 512 tokens, 768 columns and a vocabulary of 12000 304 -> 273 us, of 3000 219 -> 215.  Whole passes of 64 to 2048 columns and 64 to 8192 tokens were
+// nowhere slower than undivided beyond their noise of 2 % (1536 columns, 256 tokens 1226 -> 1159).  Off from fp64: 2.3e-7 of the norm where undivided 3.4e-7 (2048 x 768, sum of
+// 3072), 6.4e-7 where 14.4e-7 (50304).
 int product_slices(int M, int N, int K, int most) {
   const int64_t t128 = (int64_t)((M + 127) / 128) * ((N + 127) / 128);
   if (t128 > 128 || few_tiles(M, N, 1)) return 1;

@@ -131,3 +131,32 @@ def test_fp32_gemm_matches_linear_layer(M, N, K, what, epi):
     tol = 2e-6 * scale + 2e-7 * np.abs(want)
     bad = np.abs(got - want) > tol
     assert not bad.any(), (what, int(bad.sum()), float(np.abs(got - want).max()))
+
+
+@pytest.mark.parametrize("sizes,K,ld", [
+    ([(1, 1), (64, 65), (130, 70)], 64, 64),                       # tiles of 64 x 64, one k-tile
+    ([(300, 200)] * 6, 192, 1152),                                 # six slices of rows six times as long
+    ([(768, 770), (770, 1536), (300, 128)], 320, 320),               # 128 x 128, one block a CU
+    ([(1000, 2048), (2049, 1030), (70, 3000), (512, 512)], 128, 136),      # two
+    ([(4100, 4096), (4096, 3900), (130, 300)], 64, 64),            # 256 x 256
+    ([(5700, 6016)], 128, 128),
+])
+def test_products_of_a_group_are_each_their_own(sizes, K, ld):
+    """Whole numbers: every product and sum is exact.  Outputs lie one behind the other, so that a row or column too many shows."""
+    import ctypes as C
+    import torch
+    from paper_2601_12917_amd import binding as B
+    gen = torch.Generator(device="cuda").manual_seed(K + len(sizes))
+    draw = lambda n: torch.randint(-8, 9, (n, ld), generator=gen, device="cuda").bfloat16()
+    A, W = [draw(m) for m, _ in sizes], [draw(n) for _, n in sizes]
+    starts = np.cumsum([0] + [m * n + 16 for m, n in sizes])
+    slab = torch.full((int(starts[-1]),), 7.5, device="cuda")
+    ptrs = lambda t: (C.c_void_p * len(t))(*t)
+    ints = lambda t: (C.c_int32 * len(t))(*t)
+    B.check(B.lib().zgr_debug_product_group(len(sizes), ptrs([a.data_ptr() for a in A]), ptrs([w.data_ptr() for w in W]), ptrs([slab.data_ptr() + 4 * int(o) for o in starts[:-1]]),
+                                            ints([m for m, _ in sizes]), ints([n for _, n in sizes]), K, ld, torch.cuda.current_stream().cuda_stream))
+    torch.cuda.synchronize()
+    for (m, n), a, w, o in zip(sizes, A, W, starts):
+        got = slab[int(o):int(o) + m * n].view(m, n)
+        assert torch.equal(got, a[:, :K].float() @ w[:, :K].float().T)
+        assert torch.all(slab[int(o) + m * n:int(o) + m * n + 16] == 7.5)

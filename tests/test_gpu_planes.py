@@ -144,7 +144,7 @@ def _weight_gradient(dy, u, relu, x, parts):
 @pytest.mark.parametrize("M,N,K,parts", [(1, 64, 64, 1), (63, 192, 64, 3), (65, 1536, 1600, 1), (77, 2112, 2048, 3), (231, 3072, 2048, 3), (130, 5696, 6016, 1), (8191, 128, 192, 2)],
                          ids=lambda v: str(v))
 def test_weight_gradient_is_as_close_as_fp32(M, N, K, parts):
-    """Each tile size of the group (64 x 64, 128 x 128 with one and two blocks a CU, 256 x 256), ragged tiles, tokens on either side of a multiple of 64.  Nothing is left
+    """Each tile size that takes planes (64 x 64, 128 x 128 with one and two blocks a CU), ragged tiles, tokens on either side of a multiple of 64.  Nothing is left
     out; a sum rounds once per 16 terms of a plane, by at most 2^-24 of its size, here counted twice.  GELU's slope in fp32 is within 6 2^-24."""
     import torch
     gen = torch.Generator(device="cuda").manual_seed(M + N + K)
