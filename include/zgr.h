@@ -337,7 +337,7 @@ void        zgr_destroy(zgr_ctx* ctx);
 const char* zgr_last_error(const zgr_ctx* ctx); /* ctx may be NULL: last error of a failed zgr_init */
 
 /* ---- profiling: HIP-event timing of kernel classes on the context's stream ---- */
-typedef enum { ZGR_K_PERTURB_TILE = 0 /* guided matrices */, ZGR_K_PERTURB_FLAT = 1 /* isotropic tensors */,
+typedef enum { ZGR_K_PERTURB_TILE = 0 /* guided matrices, and a small model's isotropic tensors in the same launch */, ZGR_K_PERTURB_FLAT = 1 /* isotropic tensors */,
                ZGR_K_GEMM = 2, ZGR_K_ATTN = 3, ZGR_K_NORM = 4, ZGR_K_EMBED = 5, ZGR_K_LOSS = 6,
                ZGR_K_COUNT = 7 } zgr_kernel_class;
 /* Enables (1) / disables (0) event recording around every launch and clears the totals. */

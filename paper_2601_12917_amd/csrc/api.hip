@@ -489,7 +489,7 @@ PerturbArgs with_stage(const zgr_ctx* c, PerturbArgs a, size_t gi) {
 }
 
 // One pass over all parameters with the arguments `a` (single or batched) and coefficient coef: isotropic tensors
-// and resident guided tensors in one launch each, then the streamed groups layer by layer (Sec. 3.3): the launch of
+// and resident guided tensors in one launch each (a small model's in one, perturb_small), then the streamed groups layer by layer (Sec. 3.3): the launch of
 // layer l also pulls the bases of layer l + 1 out of host memory into the other staging slot, so the transfer runs
 // under the arithmetic of layer l and needs no second stream; the first launch of the pass pulls layer 0.
 zgr_status run_pass(zgr_ctx* c, PerturbArgs a, float coef) {

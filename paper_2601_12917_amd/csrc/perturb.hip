@@ -826,7 +826,7 @@ __global__ void __launch_bounds__(256) perturb_small_kernel(PerturbArgs a, const
 }
 template <typename T, int P, int MODE>
 __global__ void __launch_bounds__(64 * kTileWaves) __attribute__((amdgpu_waves_per_eu(4, 8))) perturb_small_mfma_kernel(PerturbArgs a, const TensorDesc* __restrict__ descs, const WorkItem* __restrict__ flat,
-                                                                                                                        const WorkItem* __restrict__ tiles, float c, const RadiusEntry* __restrict__ gtab) {
+                                                                                                                        const WorkItem* __restrict__ tiles, float c, const RadiusEntry* __restrict__ gtab, int) {
   extern __shared__ float smem[];
   load_radius_table<64 * kTileWaves>(reinterpret_cast<RadiusEntry*>(smem), gtab);
   if ((int)blockIdx.x < a.n_flat) {
@@ -1092,43 +1092,47 @@ hipError_t launch_tile_t(const PerturbArgs& a_in, float c, float* zout, hipStrea
   return hipGetLastError();
 }
 
+// The kernel that takes both lists of `a`, and how many of its blocks a CU holds.
+struct SmallKernel {
+  void (*kern)(PerturbArgs, const TensorDesc*, const WorkItem*, const WorkItem*, float, const RadiusEntry*, int);
+  int threads, per_cu;
+  size_t lds;
+};
 template <typename T, int P>
-hipError_t launch_small_t(const PerturbArgs& a_in, float c, hipStream_t s, const RadiusEntry* tab) {
-  PerturbArgs a = a_in;
-  a.extreme = extreme_coefficients(a);
+hipError_t small_kernel_t(const PerturbArgs& a, SmallKernel* k) {
   const int kp = (a.max_k + 7) & ~7, mode = mode_of(a);
+  const bool mfma = a.min_k >= kMfmaMinK;
+  if (mfma) k->kern = mode == kBatch ? perturb_small_mfma_kernel<T, P, kBatch> : (mode == kSpread ? perturb_small_mfma_kernel<T, P, kSpread> : perturb_small_mfma_kernel<T, P, kOne>);
+  else      k->kern = mode == kBatch ? perturb_small_kernel<T, P, kBatch> : (mode == kSpread ? perturb_small_kernel<T, P, kSpread> : perturb_small_kernel<T, P, kOne>);
+  k->threads = mfma ? 64 * kTileWaves : 256;
+  k->lds = sizeof(RadiusEntry) * (size_t)kRadiusTabEntries + (mfma ? 6 * (size_t)kp * 32 * P : sizeof(float) * ((size_t)kSmallTileRows * kp + (size_t)kp * 32 * P));
   static TileLaunchCache cache[6];
-  int per_cu = 1;
-  const dim3 grid((unsigned)(a.n_flat + a.n_tiles));
-  if (a.min_k >= kMfmaMinK) {
-    const size_t lds = sizeof(RadiusEntry) * (size_t)kRadiusTabEntries + 6 * (size_t)kp * 32 * P;
-    auto kern = mode == kBatch ? perturb_small_mfma_kernel<T, P, kBatch> : (mode == kSpread ? perturb_small_mfma_kernel<T, P, kSpread> : perturb_small_mfma_kernel<T, P, kOne>);
-    const hipError_t e = tile_launch_setup(kern, lds, 64 * kTileWaves, 4, cache[mode], &per_cu);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, grid, dim3(64 * kTileWaves), lds, s, a, a.descs, a.flat, a.tiles, c, tab);
-    return hipGetLastError();
-  }
-  const size_t lds = sizeof(float) * ((size_t)kRadiusTabEntries * 3 + (size_t)kSmallTileRows * kp + (size_t)kp * 32 * P);
-  auto kern = mode == kBatch ? perturb_small_kernel<T, P, kBatch> : (mode == kSpread ? perturb_small_kernel<T, P, kSpread> : perturb_small_kernel<T, P, kOne>);
-  const hipError_t e = tile_launch_setup(kern, lds, 256, 4, cache[3 + mode], &per_cu);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, grid, dim3(256), lds, s, a, a.descs, a.flat, a.tiles, c, tab, kp);
-  return hipGetLastError();
+  return tile_launch_setup(k->kern, k->lds, k->threads, 2, cache[mode + (mfma ? 0 : 3)], &k->per_cu);
 }
+hipError_t small_kernel(const PerturbArgs& a, SmallKernel* k) { return a.dtype == 0 ? small_kernel_t<float, 4>(a, k) : small_kernel_t<bf16_t, 4>(a, k); }
 }  // namespace
 
-// A block per entry of either list, all of them resident at once (two a CU): what a launch of its own costs a list is then all there is to save, and a block has no
+// A block per entry of either list, all of them resident at once and at most two a CU: what a launch of its own costs a list is then all there is to save, and a block has no
 // second entry to work ahead for.  Gaussians four to a call; ranks on one side of kMfmaMinK, below it tiles of eight rows.
 bool perturb_small(const PerturbArgs& a, int n_cu) {
-  return a.bits == 32 && a.n_flat > 0 && a.n_tiles > 0 && a.n_stage == 0 && a.n_flat + a.n_tiles <= 2 * n_cu && (a.min_k >= kMfmaMinK || (a.max_k < kMfmaMinK && a.tile_rows < kTileRowsPerIter));
+  if (a.bits != 32 || a.n_flat <= 0 || a.n_tiles <= 0 || a.n_stage != 0 || a.n_flat + a.n_tiles > 2 * n_cu || a.max_k < 1 || a.max_k > kMaxK) return false;
+  if (a.min_k < kMfmaMinK && (a.max_k >= kMfmaMinK || a.tile_rows >= kTileRowsPerIter)) return false;
+  SmallKernel k;
+  return small_kernel(a, &k) == hipSuccess && a.n_flat + a.n_tiles <= k.per_cu * n_cu;
 }
-hipError_t launch_perturb_small(const PerturbArgs& a, float c, hipStream_t s, int n_cu) {
-  if (!perturb_small(a, n_cu) || a.max_k < 1 || a.max_k > kMaxK || a.pull_blocks != 0) return hipErrorInvalidValue;
+hipError_t launch_perturb_small(const PerturbArgs& a_in, float c, hipStream_t s, int n_cu) {
+  PerturbArgs a = a_in;
+  a.extreme = extreme_coefficients(a);
+  if (!perturb_small(a, n_cu) || a.pull_blocks != 0) return hipErrorInvalidValue;
   if (a.n_q < 0 || a.n_q > kMaxBatch || (a.spread && (a.n_q > 0 || a.from_copy)) || ((a.spread || a.from_copy) && !(a.copy[0] && a.copy[1])) || (a.from_copy && a.n_q > 0)) return hipErrorInvalidValue;
   const RadiusEntry* tab = nullptr;
-  const hipError_t e = ensure_radius_table(&tab, s);
+  hipError_t e = ensure_radius_table(&tab, s);
   if (e != hipSuccess) return e;
-  return a.dtype == 0 ? launch_small_t<float, 4>(a, c, s, tab) : launch_small_t<bf16_t, 4>(a, c, s, tab);
+  SmallKernel k;
+  e = small_kernel(a, &k);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k.kern, dim3((unsigned)(a.n_flat + a.n_tiles)), dim3((unsigned)k.threads), k.lds, s, a, a.descs, a.flat, a.tiles, c, tab, (a.max_k + 7) & ~7);
+  return hipGetLastError();
 }
 
 hipError_t launch_perturb_flat(const PerturbArgs& a, float c, float* zout, hipStream_t s, int n_cu) {

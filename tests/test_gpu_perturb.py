@@ -291,3 +291,30 @@ def test_basis_rows_and_coefficients_too_small_for_planes(k, bits):
     want = sum(-float(np.float32(lr * g)) * P.hybrid_z(cfg.seed, s, 3, rows, cols, _basis(rows, k), k, 0.0, P.SCALE_UNIT, bits).astype(np.float64) for s, g in zip((1, 2), gs))
     assert off(sess.get_theta(0).astype(np.float64), want).max() <= (k + 8) * 2.0 ** -24
     sess.close()
+
+
+@pytest.mark.parametrize("k", [8, 16, 64])
+@pytest.mark.parametrize("blocks", ["one a CU", "two a CU", "more"])
+def test_lists_share_a_launch_while_their_blocks_are_resident(k, blocks):
+    """A block per entry of either list, two a CU at most: with one entry more the lists take a launch each, with the same bits."""
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    per_item = 256 * 4 * 4                                                     # fp32: 256 threads of four calls of four Gaussians
+    rows, cols = 64, 128
+    tiles = 1 if k >= 16 else 8
+    flat = {"one a CU": cus - tiles, "two a CU": 2 * cus - tiles, "more": 2 * cus - tiles + 1}[blocks]
+    cfg = _single_tensor_cfg(rows, cols, k)
+    rng = np.random.default_rng(k)
+    W, U = (rng.standard_normal((rows, cols)) * PARAM_SCALE).astype(np.float32), _basis(rows, k)
+    v = (rng.standard_normal((1, flat * per_item)) * PARAM_SCALE).astype(np.float32)
+    spec = I.TensorSpec("W", I.ROLE_LSQ_W, -1, rows, cols, 3, True)
+    sess = make_session(cfg, [spec, I.TensorSpec("b", I.ROLE_BQ, -1, 1, flat * per_item, 5, False)], [W, v], [U, None], arch=-1)
+    sess.profile_enable()
+    sess.perturb(4, 1e-3)
+    assert [n for _, n in sess.profile_read().values()][:2] == ([1, 1] if blocks == "more" else [1, 0])
+    alone = make_session(cfg, [spec], [W], [U], arch=-1)
+    alone.perturb(4, 1e-3)
+    assert np.array_equal(sess.get_theta(0), alone.get_theta(0))
+    want = P.axpy_inplace_value(v, np.float32(1e-3), P.gauss_field(cfg.seed, 4, 5, 0, 1, v.size), "f32")
+    assert np.all(np.abs(sess.get_theta(1) - want) <= F32_RTOL * (np.abs(want) + PARAM_SCALE))
+    sess.close(); alone.close()
