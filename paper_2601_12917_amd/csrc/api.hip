@@ -74,7 +74,7 @@ struct zgr_ctx {
   std::vector<HostBasis> hb;
   // A run of the tile list served by one kernel: class 0 = ranks >= kMfmaMinK (matrix-core kernel), class 1 = smaller
   // ranks (vector kernel).  A context may mix both; each class gets its own launch.
-  struct TileRange { size_t begin = 0, end = 0; int max_k = 0, min_k = kMaxK + 1; };
+  struct TileRange { size_t begin = 0, end = 0; int max_k = 0, min_k = kMaxK + 1; bool whole = true; };      // whole: every tile has kTileRowsPerIter rows
   struct Group { int layer = 0; std::vector<int> tensors; TileRange cls[2];
                  std::vector<StageCopy> copies; };   // host -> staging-slot pieces, contiguous runs merged
   std::vector<Group> groups;   // streamed groups in pass order; their tiles follow the resident ones in `tiles`
@@ -262,6 +262,7 @@ void build_lists(zgr_ctx* c) {
         append_items(c->t[i], i, true, P, c->cv.few_tiles, c->flat, c->tiles);
         cls[k_class].max_k = std::max(cls[k_class].max_k, c->t[i].k);
         cls[k_class].min_k = std::min(cls[k_class].min_k, c->t[i].k);
+        cls[k_class].whole = cls[k_class].whole && !c->cv.few_tiles && c->t[i].rows % kTileRowsPerIter == 0;
       }
       cls[k_class].end = c->tiles.size();
     }
@@ -520,7 +521,7 @@ zgr_status run_pass(zgr_ctx* c, PerturbArgs a, float coef) {
       if (r.end == r.begin) continue;
       PerturbArgs at = pending ? with_stage(c, a, next) : a;
       at.n_stage = pending ? at.n_stage : 0;
-      at.tiles = tiles + r.begin; at.n_tiles = (int32_t)(r.end - r.begin); at.n_flat = 0; at.max_k = r.max_k; at.min_k = r.min_k;
+      at.tiles = tiles + r.begin; at.n_tiles = (int32_t)(r.end - r.begin); at.n_flat = 0; at.max_k = r.max_k; at.min_k = r.min_k; at.whole = r.whole ? 1 : 0;
       ProfScope ps(c, ZGR_K_PERTURB_TILE);
       HIP_TRY(c, launch_perturb_tile(at, coef, nullptr, c->stream, c->n_cu));
       pending = false;

@@ -61,6 +61,7 @@ struct PerturbArgs {
   int32_t           dtype;
   int32_t           max_k;     // largest k among tiled tensors
   int32_t           min_k;     // smallest k among tiled tensors
+  int32_t           whole;     // every tile has kTileRowsPerIter rows
   int32_t           tile_rows; // rows of a tile of the vector kernel: kTileRowsPerIter or kSmallTileRows
   // batched pass: theta += sum_i qcoef[i] Z(seed, qstep[i]); n_q == 0: the single pass theta += c Z(seed, step)
   int32_t           n_q;

@@ -530,12 +530,6 @@ __device__ __forceinline__ void eight_of(const TensorDesc& d, const RawEight& r,
   }
 }
 
-// Whether three planes hold a number: it does not round up to infinity, and its last place is a normal number or it is zero.
-__device__ __forceinline__ bool planes_hold(float x) {
-  constexpr uint32_t lo = 24u << 23, hi = 0x7F7F7FFFu;       // 2^-103, and the last one that rounds to a finite bf16
-  return ((__float_as_uint(x) << 1) - (lo << 1) <= (hi - lo) << 1) | (x == 0.f);
-}
-
 // acc[t] = U R for the wave's 16 rows and the 16 columns of tile t, eight tiles from R's entries at Rs on; `first` holds the lane's first eight where t.eights.
 // extreme: planes don't hold R.
 template <int P>
@@ -555,12 +549,19 @@ __device__ __forceinline__ void contract(const Tile& tl, const RawEight& first, 
 #pragma unroll
       for (int i = 0; i < 8; ++i) u[i] = 8 * c8 + i < tl.d.k ? basis_at(tl.d, urow, 8 * c8 + i) : 0.f;
     }
+    // Three planes hold a number that does not round up to infinity and whose last place is a normal number (2^-103 and above), and zero: twice its bits less those of
+    // 2^-103 wrap round below that, zero least.
+    constexpr uint32_t least = 24u << 24;
+    float most = 0.f;
+    uint32_t wrapped = 0;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
       u[2 * w] = in ? u[2 * w] : 0.f; u[2 * w + 1] = in ? u[2 * w + 1] : 0.f;         // past the end: zeros times R's last eight
       cut_pair_rounded(u[2 * w], u[2 * w + 1], w, o);
-      held &= planes_hold(u[2 * w]) & planes_hold(u[2 * w + 1]);
+      most = fmaxf(fmaxf(most, __builtin_fabsf(u[2 * w])), __builtin_fabsf(u[2 * w + 1]));
+      wrapped = max(wrapped, max((__float_as_uint(u[2 * w]) << 1) - least, (__float_as_uint(u[2 * w + 1]) << 1) - least));
     }
+    held &= (most <= 0x1.fefffep127f) & (wrapped <= 0u - least);
   };
   PlanesOf<3> pu;
   int l8 = 0;
@@ -617,8 +618,9 @@ __device__ __forceinline__ void contract(const Tile& tl, const RawEight& first, 
 // and store issued before it, and some 10 KB in flight per compute unit are half of what HBM needs at this rate.
 template <typename T, int P> constexpr int vectors_ahead() { return 64 / (int)(sizeof(T) * P); }      // 16 registers
 
-// The share of block `block` of `nblk`; the table, at smem, is on its way into LDS.
-template <typename T, int P, bool WRITE_Z, int MODE>
+// The share of block `block` of `nblk`; the table, at smem, is on its way into LDS.  WHOLE: every tile has rows for every wave; looking after waves without costs 2 % of an in-place
+// pass (1.2e9 bf16 entries of rank 16: 1.63 ms -> 1.66), in scalar registers that spill.
+template <typename T, int P, bool WRITE_Z, int MODE, bool WHOLE>
 __device__ __forceinline__ void tile_mfma_share(const PerturbArgs& a, const TensorDesc* __restrict__ descs, const WorkItem* __restrict__ items, float c, float* smem, float* __restrict__ zout,
                                                 int block, int nblk) {
   const RadiusEntry* tab = reinterpret_cast<const RadiusEntry*>(smem);
@@ -671,7 +673,7 @@ __device__ __forceinline__ void tile_mfma_share(const PerturbArgs& a, const Tens
   };
   auto request = [&](const Tile& t, int round, Vec<T, P>* buf, bool more) {
     if (WRITE_Z) return;
-    const bool own = more && has_rows(t);
+    const bool own = WHOLE || (more && has_rows(t));
     const T* src = own ? places_of<T, MODE>(t.d, a).src + (t.row0 * t.d.cols + t.col0) : reinterpret_cast<const T*>(descs);
     const int64_t cols_left = t.d.cols - t.col0;
     const uint32_t last_row = own ? (uint32_t)t.nrows - 1 : 0, last_col = !own ? 0 : cols_left < TC ? (uint32_t)cols_left - P : TC - P;
@@ -732,7 +734,7 @@ __device__ __forceinline__ void tile_mfma_share(const PerturbArgs& a, const Tens
     const uint32_t q_hi = (uint32_t)((uint64_t)origin / P >> 32);
     const bool full = 16 * wave + 16 <= t.nrows && t.row0 + t.nrows <= t.d.rows && t.col0 + TC <= t.d.cols &&
                       q_hi == (uint32_t)((uint64_t)(origin + (int64_t)(t.nrows - 1) * t.d.cols + TC - 1) / P >> 32);
-    const bool any = 16 * wave < t.nrows;
+    const bool any = WHOLE || 16 * wave < t.nrows;
     const int nrows = t.nrows;
     const TensorDesc d = t.d;
     const int64_t row0 = t.row0, col0 = t.col0;
@@ -799,14 +801,14 @@ __device__ __forceinline__ void tile_mfma_share(const PerturbArgs& a, const Tens
     }
   }
 }
-template <typename T, int P, bool WRITE_Z, int MODE>
+template <typename T, int P, bool WRITE_Z, int MODE, bool WHOLE>
 __global__ void __launch_bounds__(64 * kTileWaves) __attribute__((amdgpu_waves_per_eu(4, 8))) perturb_tile_mfma_kernel(PerturbArgs a, const TensorDesc* __restrict__ descs, const WorkItem* __restrict__ items,
                                                                 float c, const RadiusEntry* __restrict__ gtab, float* __restrict__ zout) {
   extern __shared__ float smem[];
   const int nblk = (int)gridDim.x - a.pull_blocks;               // computing blocks
   if ((int)blockIdx.x >= nblk) { pull_next_stage(a, (int)blockIdx.x - nblk, a.pull_blocks); return; }
   load_radius_table<64 * kTileWaves>(reinterpret_cast<RadiusEntry*>(smem), gtab);
-  tile_mfma_share<T, P, WRITE_Z, MODE>(a, descs, items, c, smem, zout, (int)blockIdx.x, nblk);
+  tile_mfma_share<T, P, WRITE_Z, MODE, WHOLE>(a, descs, items, c, smem, zout, (int)blockIdx.x, nblk);
 }
 
 // ------------------------------------------------------------------ a small model's two lists in one launch
@@ -833,7 +835,7 @@ __global__ void __launch_bounds__(64 * kTileWaves) __attribute__((amdgpu_waves_p
     __syncthreads();
     if (threadIdx.x < 256) flat_share<T, P, MODE>(a, descs, flat, c, reinterpret_cast<const RadiusEntry*>(smem), (int)blockIdx.x, a.n_flat);
   } else {
-    tile_mfma_share<T, P, false, MODE>(a, descs, tiles, c, smem, nullptr, (int)blockIdx.x - a.n_flat, a.n_tiles);
+    tile_mfma_share<T, P, false, MODE, false>(a, descs, tiles, c, smem, nullptr, (int)blockIdx.x - a.n_flat, a.n_tiles);
   }
 }
 
@@ -1058,11 +1060,16 @@ hipError_t launch_tile_t(const PerturbArgs& a_in, float c, float* zout, hipStrea
   if (a.min_k >= kMfmaMinK) {
     const size_t lds_m = sizeof(RadiusEntry) * (size_t)kRadiusTabEntries + 6 * (size_t)kp * 32 * P;      // three planes of two bytes
     const int variant = zout ? 3 : mode_of(a);
-    auto km = zout ? perturb_tile_mfma_kernel<T, P, true, kOne>
-                   : (variant == kBatch ? perturb_tile_mfma_kernel<T, P, false, kBatch> : (variant == kSpread ? perturb_tile_mfma_kernel<T, P, false, kSpread> : perturb_tile_mfma_kernel<T, P, false, kOne>));
-    static TileLaunchCache cache_m[4];
+    const bool whole = a.whole != 0;
+    decltype(&perturb_tile_mfma_kernel<T, P, false, kOne, false>) km = perturb_tile_mfma_kernel<T, P, true, kOne, false>;
+    switch (variant) {
+      case kOne:    km = whole ? perturb_tile_mfma_kernel<T, P, false, kOne, true> : perturb_tile_mfma_kernel<T, P, false, kOne, false>; break;
+      case kBatch:  km = whole ? perturb_tile_mfma_kernel<T, P, false, kBatch, true> : perturb_tile_mfma_kernel<T, P, false, kBatch, false>; break;
+      case kSpread: km = whole ? perturb_tile_mfma_kernel<T, P, false, kSpread, true> : perturb_tile_mfma_kernel<T, P, false, kSpread, false>; break;
+    }
+    static TileLaunchCache cache_m[8];
     int per_cu = 1;
-    hipError_t e = tile_launch_setup(km, lds_m, 64 * kTileWaves, 4, cache_m[variant], &per_cu);
+    hipError_t e = tile_launch_setup(km, lds_m, 64 * kTileWaves, 4, cache_m[variant + (whole ? 4 : 0)], &per_cu);
     if (e != hipSuccess) return e;
     const int grid_m = split_grid(a, a.n_tiles, n_cu * per_cu);
     hipLaunchKernelGGL(km, dim3(grid_m), dim3(64 * kTileWaves), lds_m, s, a, a.descs, a.tiles, c, tab, zout);

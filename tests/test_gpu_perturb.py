@@ -244,9 +244,12 @@ def test_basis_entries_beyond_bf16(k):
     (193, 256, 40, "bf16", 32),     # four tiles of 64, the last of one row; of 128 and of 65
     (200, 264, 16, "f32", 16),
     (129, 256, 64, "bf16", 16),
+    (256, 260, 24, "bf16", 32),     # whole tiles of 128 rows, which a launch without ragged ones takes by themselves
+    (128, 264, 40, "f32", 16),
+    (384, 512, 16, "f32", 32),
 ])
 def test_bits_do_not_depend_on_the_height_of_the_tiles(rows, cols, k, dtype, bits):
-    """The same tensor alone (tiles of 64 rows), with a vector beside it (both in one launch) and in a context of many tiles (128 rows): single passes and sums of
+    """The same tensor alone (tiles of 64 rows), with a vector beside it (both in one launch) and in contexts of many tiles (128 rows), one of them with a ragged last: single passes and sums of
     several perturbations leave the same bits, and every entry is moved once."""
     cfg = _single_tensor_cfg(rows, cols, k, dtype)
     rng = np.random.default_rng(rows + cols)
@@ -256,11 +259,11 @@ def test_bits_do_not_depend_on_the_height_of_the_tiles(rows, cols, k, dtype, bit
         return P.bf16_round(w) if dtype == "bf16" else w
     W, U = values(rows, cols), _basis(rows, k)
     vector = (I.TensorSpec("b", I.ROLE_BQ, -1, 1, 333, 5, False), values(1, 333), None)
-    many = (I.TensorSpec("V", I.ROLE_LSQ_W, -1, 1100, 2304, 9, True), values(1100, 2304), _basis(1100, k, 2))
+    many, whole = ((I.TensorSpec("V", I.ROLE_LSQ_W, -1, n, 2304, 9, True), values(n, 2304), _basis(n, k, 2)) for n in (1100, 1152))
     c = np.float32(1e-3)
     want = P.axpy_inplace_value(W, c, P.hybrid_z(cfg.seed, 4, 3, rows, cols, U, k, cfg.alpha, P.SCALE_UNIT, bits), dtype)
     seen = []
-    for others in ([], [vector], [many]):
+    for others in ([], [vector], [many], [whole]):
         sess = make_session(cfg, [I.TensorSpec("W", I.ROLE_LSQ_W, -1, rows, cols, 3, True)] + [o[0] for o in others], [W] + [o[1] for o in others], [U] + [o[2] for o in others], bits=bits, arch=-1)
         sess.perturb(4, float(c))
         once = sess.get_theta(0)
