@@ -11,7 +11,7 @@
 // Off from fp64 no further than the fp32 instructions, whose every fourth (16x16x4) or second (32x32x2) term is
 // followed by a rounding of the sum, here every thirty-second (sixteenth) of each plane (figures where it is used).
 // An infinite factor has NaN in its second plane, one that rounds up to infinity (above 3.39e38) in its third; sums that come out not finite have to be
-// taken again by the fp32 instructions.  The instruction takes a subnormal plane as zero: entries are exact to 2^-126, so numbers below about 2^-110
+// taken again by the fp32 instructions.  The instruction takes a subnormal plane as zero: entries are exact to 2^-126, so numbers below 2^-103
 // lose their last plane (factors of 2^-115 times factors of 2^100: off by 37 2^-24).
 #pragma once
 #include <hip/hip_runtime.h>
