@@ -578,12 +578,20 @@ std::mutex g_loss_mu;
 std::vector<LossPage>& g_loss_pages = *new std::vector<LossPage>();      // never destroyed: contexts may outlast the library's statics
 constexpr size_t kLossPlace = 64, kLossPlaces = 64;
 
+// A capture of another stream (torch's are of the mode that concerns all threads) neither refuses what this thread allocates or frees meanwhile, nor ends by it.
+struct OutsideCaptures {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  OutsideCaptures() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  ~OutsideCaptures() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
 double* take_loss_place() {
   std::lock_guard<std::mutex> lock(g_loss_mu);
   for (LossPage& p : g_loss_pages)
     for (size_t i = 0; i < kLossPlaces; ++i)
       if (!(p.used >> i & 1)) { p.used |= (uint64_t)1 << i; return reinterpret_cast<double*>(p.at + i * kLossPlace); }
   void* at = nullptr;
+  const OutsideCaptures guard;
   if (hipHostMalloc(&at, kLossPlace * kLossPlaces, hipHostMallocMapped | hipHostMallocPortable) != hipSuccess) return nullptr;
   g_loss_pages.push_back({reinterpret_cast<unsigned char*>(at), 1});
   return reinterpret_cast<double*>(at);
@@ -596,6 +604,7 @@ void give_loss_place(double* place) {
     const size_t off = (size_t)(reinterpret_cast<unsigned char*>(place) - p.at);
     if (reinterpret_cast<unsigned char*>(place) < p.at || off >= kLossPlace * kLossPlaces) continue;
     p.used &= ~((uint64_t)1 << (off / kLossPlace));
+    const OutsideCaptures guard;
     if (p.used == 0 && g_loss_pages.size() > 1) { (void)hipHostFree(p.at); g_loss_pages.erase(g_loss_pages.begin() + (std::ptrdiff_t)k); }
     return;
   }

@@ -446,3 +446,33 @@ def test_many_contexts_have_losses_of_their_own():
     i, sess, b = open_one(0)
     assert sess.loss(b) == want[0]
     sess.close()
+
+
+def test_contexts_are_made_while_a_stream_is_captured():
+    """zgr_init of a model takes a place for its losses, now and then a page of pinned memory for 64 of them: a capture elsewhere in the process neither refuses that nor
+    ends by it."""
+    import ctypes as C
+    import torch
+    from paper_2601_12917_amd import binding as B
+    cfg = I.shrink(I.CONFIGS["cfg1"], name="captured", lsq_out=6, lsq_in=8, batch=3, k=1, k_full=1)
+    specs, values, _ = inputs_of(cfg)
+    sess = make_session(cfg, specs, values, [None])
+    want = sess.loss(session_batch(sess, cfg, make_batch_arrays(cfg)))
+    contexts = [C.c_void_p() for _ in range(66)]                  # a page's worth and more
+    x = torch.zeros(64, device="cuda:0")
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        x += 1.0
+        status = [sess.lib.zgr_init(C.byref(c), C.byref(sess.model), sess.table, len(specs), C.byref(sess.config), sess.workspace.data_ptr(), sess.workspace.numel(), 3, 2, side.cuda_stream)
+                  for c in contexts]
+        x *= 2.0
+    assert status == [B.ZGR_OK] * len(contexts)
+    for n in range(3):
+        graph.replay()
+    torch.cuda.synchronize()
+    assert torch.all(x == 14.0)
+    for c in contexts:
+        sess.lib.zgr_destroy(c)
+    assert sess.loss(session_batch(sess, cfg, make_batch_arrays(cfg))) == want
+    sess.close()
