@@ -405,7 +405,7 @@ zgr_status zgr_debug_weight_gradient(float* dy, const float* u, int32_t relu, co
 
 /* Up to six bf16 products in one launch, as the cloud's backward pass takes the weight gradients of a block and the slices of a long sum: out[j] [M[j], N[j]] (fp32) =
  * A[j] W[j]^T, rows of K entries (a multiple of 64), ld entries (a multiple of 8) apart.  A, W, out, M and N are HOST arrays of `count` entries, what the first three point to is
- * DEVICE, on 16 bytes.  For tests. */
+ * DEVICE, A and W on 16 bytes.  For tests. */
 zgr_status zgr_debug_product_group(int32_t count, const void* const* A, const void* const* W, float* const* out, const int32_t* M, const int32_t* N, int32_t K, int32_t ld,
                                    void* hip_stream);
 

@@ -1678,6 +1678,7 @@ zgr_status zgr_debug_product_group(int32_t count, const void* const* A, const vo
   ProductGroup g;
   for (int32_t j = 0; j < count; ++j) {
     if (!A[j] || !W[j] || !out[j]) return fail(nullptr, ZGR_ERR_NULL, "NULL argument");
+    if (((uintptr_t)A[j] | (uintptr_t)W[j]) & 15 || (uintptr_t)out[j] & 3 || M[j] < 1 || N[j] < 1) return fail(nullptr, ZGR_ERR_SHAPE, "bad shape or alignment");
     g.job[g.count++] = GroupedProduct{A[j], W[j], out[j], M[j], N[j], K, ld, ld};
   }
   HIP_TRY(nullptr, launch_product_group(g, reinterpret_cast<hipStream_t>(hip_stream)));
